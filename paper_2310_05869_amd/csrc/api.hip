@@ -169,7 +169,7 @@ static int static_scratch(void** addr) {
 }
 
 static int run_attention(const AttnArgs& a, int mode, hipStream_t st) {
-  return use_mfma(a.g) ? launch_attn_mfma(a, mode, st) : launch_attn_generic(a, mode, st);
+  return use_mfma(a.g) ? launch_attn_mfma(a, mode, st) : launch_attn_f32(a, mode, st);
 }
 
 // Algorithm 4's diagonal blocks: exact causal attention on every block of base_len rows, whose

@@ -1,5 +1,5 @@
-// Work decomposition and key-list construction shared by the MFMA and the
-// generic attention kernels.
+// Work decomposition and key-list construction shared by the bf16 and the fp32
+// attention kernels.
 //
 // One workgroup = one tile of QT consecutive sorted query positions inside one
 // b-block of one node (node mode), or QT consecutive query rows of one diagonal

@@ -1,0 +1,308 @@
+// fp32 attention on the fp32 matrix cores: the arithmetic path for HA_FP32 tensors
+// (v_mfma_f32_32x32x2_f32: fp32 products, fp32 sums), with the same node / exact
+// modes and the same outputs as the bf16 kernel (attn_mfma.hip).
+//
+// What bounds it: the matrix pipe.  One 32 x 32 tile of scores and its product with V
+// take D/2 + D/2 instructions of 64 cycles each, against 8 KiB of K and 8 KiB of V
+// fragments at d = 64 that every wave reads straight from the caches into the operand
+// layout (16 B/clk per CU where four waves share nothing): no LDS staging, hence no
+// barrier in the loop and waves that run independently of each other.
+//
+// A wave owns 32 query rows and computes S^T = K Q^T, so that a lane holds 16 keys of
+// ONE query (as in the bf16 kernel) and an accumulator register, exponentiated, is
+// directly the B operand of O^T += V^T P^T: the two lanes of a query hold the keys
+// 8 g + z and 8 g + 4 + z of the instruction's pair.  The columns of d are walked in
+// the order the lanes load them (lane half h: columns 8 j + 4 h ... + 3), which the
+// K and the Q fragments share.
+//
+// KW waves of a workgroup share one group of 32 queries, every wave taking each KW-th
+// key tile, and their results are merged through LDS.  KW = 4 quarters the serial
+// chain of a small problem (the one-head n = 1024 call has 32 groups of queries for
+// 1024 SIMDs) and lets a workgroup fit blocks of 32 rows.
+//
+// Measured (MI355X; fp32 matrix peak 157 TFLOP/s, library product of 8192^3: 154), against
+// one thread per query row with LDS-broadcast keys, the form before: exact attention,
+// 32 heads, n = 8192: d = 64 14.8 -> 4.8 ms (114 TFLOP/s), d = 128 95 -> 8.9 ms (124);
+// n = 1024, one head, d = 64, b = m = 64: whole forward call 124 -> 35 us.
+#include "attn_common.h"
+
+namespace ha {
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kFKT = 32;   // keys per tile
+constexpr int kFNT = 256;  // threads: four waves
+
+template <int D>
+struct F32Lds {
+  static constexpr int ROW = D + 4;                // floats per staged output row
+  static constexpr int BYTES = 4 * 32 * ROW * 4 + 4 * 32 * 2 * 4;
+};
+
+template <int D>
+__host__ __device__ inline size_t f32_lds_bytes(int b, int m, int mode) {
+  const size_t list = mode == kModeNode ? (size_t)(((b + m + 63) & ~63) + 64) * 4 + 64 : 0;
+  return list > (size_t)F32Lds<D>::BYTES ? list : (size_t)F32Lds<D>::BYTES;
+}
+
+template <int D, int MODE, int KW>
+__global__ __launch_bounds__(kFNT, D == 64 ? 3 : 2) void attn_f32_kernel(AttnArgs a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  constexpr int kQT = 32 * (4 / KW);
+  constexpr int KJ = D / 8;    // 16-byte pieces of a row per lane
+  constexpr int DT = D / 32;
+  constexpr int DTA = DT < 2 ? DT : 2;  // V columns are fetched 64 at a time
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, wave = tid >> 6;
+  const int lq = lane & 31, h = lane >> 5;
+  const int kw = wave % KW;
+
+  int32_t* scratch = reinterpret_cast<int32_t*>(smem);
+  int32_t* list = scratch + 16;
+
+  const int bid = logical_block(blockIdx.x, gridDim.x);
+  TileWork w;
+  int nb, nkeys;
+  if (MODE == kModeNode) {
+    w = decode_node_tile<kQT>(a, bid);
+    nkeys = build_key_list<kFNT>(a, w, list, scratch, &nb);
+  } else {
+    w = decode_exact_tile<kQT>(a, bid);
+    nkeys = max(0, w.k1 - w.k0);
+    nb = 0x7fffffff;
+  }
+  const int ntiles = (nkeys + kFKT - 1) / kFKT;
+  const float nat_bias = (MODE == kModeNode && a.g.m > 0) ? logf((float)w.nr.s / (float)a.g.m) : 0.f;
+
+  const float* Qh = reinterpret_cast<const float*>(a.Q) + (int64_t)w.bh * a.q_bh_stride;
+  const float* Kh = reinterpret_cast<const float*>(a.K) + (int64_t)w.bh * a.k_bh_stride;
+  const float* Vh = reinterpret_cast<const float*>(a.V) + (int64_t)w.bh * a.k_bh_stride;
+  const int r_in_tile = (wave / KW) * 32 + lq;
+  const int r_use = r_in_tile < w.rows_valid ? r_in_tile : 0;
+  int qrow, q_global = 0;
+  if (MODE == kModeNode) {
+    qrow = a.perm_q ? a.perm_q[w.seg_off + w.p0 + r_use] : w.nr.q_start + w.p0 + r_use;
+  } else {
+    q_global = w.q0 + r_in_tile;
+    qrow = w.q0 + r_use;
+  }
+  f32x4 q[KJ];
+#pragma unroll
+  for (int j = 0; j < KJ; ++j) q[j] = *reinterpret_cast<const f32x4*>(Qh + (int64_t)qrow * D + 8 * j + 4 * h);
+
+  // rows past the end of the keys read as zeros (such keys are masked by position)
+  const uint32_t bytes = (uint32_t)(MODE == kModeNode ? a.g.n : w.k1) * (uint32_t)(D * 4);
+  const __amdgpu_buffer_rsrc_t krsrc = __builtin_amdgcn_make_buffer_rsrc((void*)Kh, 0, (int)bytes, 0x00020000);
+  const __amdgpu_buffer_rsrc_t vrsrc = __builtin_amdgcn_make_buffer_rsrc((void*)Vh, 0, (int)bytes, 0x00020000);
+  f32x4 kf[KJ];
+  auto load_k = [&](int kt) {
+    const int row = MODE == kModeNode ? list[kt * kFKT + lq] : w.k0 + kt * kFKT + lq;
+    const int off = row * (D * 4) + 16 * h;
+#pragma unroll
+    for (int j = 0; j < KJ; ++j)
+      kf[j] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(krsrc, off, 32 * j, 0));
+  };
+  // V rows of the tile, columns 32 dt + lq for dt in [dt0, dt0 + DTA): element i of a lane is key
+  // 8 (i / 4) + 4 h + i % 4, the key of accumulator register i
+  auto load_v = [&](int kt, int dt0, float (&v)[16][DTA]) {
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      i32x4 rows;
+      if (MODE == kModeNode) {
+        rows = *reinterpret_cast<const i32x4*>(list + kt * kFKT + 8 * g + 4 * h);
+      } else {
+        const int r0 = w.k0 + kt * kFKT + 8 * g + 4 * h;
+        rows = (i32x4){r0, r0 + 1, r0 + 2, r0 + 3};
+      }
+#pragma unroll
+      for (int z = 0; z < 4; ++z)
+#pragma unroll
+        for (int dt = 0; dt < DTA; ++dt)
+          v[4 * g + z][dt] = __uint_as_float(
+              __builtin_amdgcn_raw_buffer_load_b32(vrsrc, rows[z] * (D * 4) + 4 * lq, 128 * (dt0 + dt), 0));
+    }
+  };
+
+  f32x16 o[DT];
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) o[dt][i] = 0.f;
+  float m_run = -INFINITY, l_run = 0.f;
+
+  if (kw < ntiles) load_k(kw);
+  for (int kt = kw; kt < ntiles; kt += KW) {
+    float va[16][DTA];
+    if constexpr (DT == 2) load_v(kt, 0, va);
+    f32x16 c;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) c[i] = 0.f;
+#pragma unroll
+    for (int j = 0; j < KJ; ++j) {
+      if (DT > 2 && j == KJ / 2) {  // d = 128: V takes the registers of the K pieces already multiplied
+        __builtin_amdgcn_sched_barrier(0);
+        load_v(kt, 0, va);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) c = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[j][e], q[j][e], c, 0, 0, 0);
+    }
+
+    const int base = kt * kFKT;
+    const bool plain = base + kFKT <= min(nkeys, nb) &&
+                       !(MODE == kModeExact && a.exact_causal && w.k0 + base + kFKT - 1 > w.q0 + (wave / KW) * 32);
+    if (!plain) {
+      int lim = nkeys;
+      if (MODE == kModeExact && a.exact_causal) lim = min(lim, q_global - w.k0 + 1);
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int pos = base + 8 * (i / 4) + 4 * h + (i % 4);
+        const float s = c[i] + (pos >= nb ? nat_bias : 0.f);
+        c[i] = pos >= lim ? -INFINITY : s;
+      }
+    }
+    float mx = c[0];
+#pragma unroll
+    for (int i = 1; i < 16; ++i) mx = fmaxf(mx, c[i]);
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    if (__any(mx > m_run)) {
+      const float m_new = fmaxf(m_run, mx);
+      const float alpha = expf(m_run - (m_new == -INFINITY ? 0.f : m_new));
+      l_run *= alpha;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o[dt][i] *= alpha;
+      m_run = m_new;
+    }
+    const float m_use = m_run == -INFINITY ? 0.f : m_run;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      c[i] = expf(c[i] - m_use);
+      l_run += c[i];
+    }
+    if constexpr (DT == 2) {
+      if (kt + KW < ntiles) load_k(kt + KW);
+    }
+    float vb[16][DTA];
+    if constexpr (DT > 2) load_v(kt, 2, vb);
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+#pragma unroll
+      for (int dt = 0; dt < DTA; ++dt) o[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(va[i][dt], c[i], o[dt], 0, 0, 0);
+    if constexpr (DT > 2) {
+      __builtin_amdgcn_sched_barrier(0);  // the next K rows take the registers of the first half of V
+      if (kt + KW < ntiles) load_k(kt + KW);
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+#pragma unroll
+        for (int dt = 0; dt < DTA; ++dt)
+          o[2 + dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(vb[i][dt], c[i], o[2 + dt], 0, 0, 0);
+    }
+  }
+
+  // ---- results: every wave's rows through LDS, where the KW parts of a row are merged and rows
+  // leave as whole 16-byte pieces of consecutive lanes ----
+  constexpr int RS = F32Lds<D>::ROW;
+  float* orow = reinterpret_cast<float*>(smem);   // [4 waves][32][RS]
+  float* ml = orow + 4 * 32 * RS;                 // [4 waves][32][2]: reference, row sum
+  const float l_tot = l_run + __shfl_xor(l_run, 32);
+  __syncthreads();  // the key list is read no more
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      *reinterpret_cast<f32x4*>(orow + (wave * 32 + lq) * RS + 32 * dt + 8 * g + 4 * h) =
+          (f32x4){o[dt][4 * g], o[dt][4 * g + 1], o[dt][4 * g + 2], o[dt][4 * g + 3]};
+  if (h == 0) {
+    ml[(wave * 32 + lq) * 2] = m_run;
+    ml[(wave * 32 + lq) * 2 + 1] = l_tot;
+  }
+  __syncthreads();
+  constexpr int LPR = D / 4;  // lanes per row
+  const bool to_partial = MODE == kModeNode && a.part_o != nullptr;
+  for (int idx = tid; idx < w.rows_valid * LPR; idx += kFNT) {
+    const int r = idx / LPR, col = (idx % LPR) * 4;
+    const int w0 = (r / 32) * KW;  // first of the waves that hold the row
+    float mx = -INFINITY;
+#pragma unroll
+    for (int k = 0; k < KW; ++k) mx = fmaxf(mx, ml[((w0 + k) * 32 + (r & 31)) * 2]);
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    float l = 0.f;
+#pragma unroll
+    for (int k = 0; k < KW; ++k) {
+      const int at = (w0 + k) * 32 + (r & 31);
+      const float wk = KW == 1 ? 1.f : (mx == -INFINITY ? 0.f : expf(ml[at * 2] - mx));
+      l += wk * ml[at * 2 + 1];
+      acc += wk * *reinterpret_cast<const f32x4*>(orow + at * RS + col);
+    }
+    const bool empty = !(l > 0.f);
+    float lse = empty ? -INFINITY : mx + logf(l);
+    acc *= empty ? 0.f : 1.f / l;
+    RowDest dest{};
+    if (MODE == kModeNode) {
+      dest = node_row_dest(a, w, r);
+    } else {
+      dest.row_in_head = w.q0 + r;
+      dest.out_row = (int64_t)w.bh * (a.out_bh_stride / D) + w.q0 + r;
+    }
+    if (to_partial) {
+      *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(a.part_o) + dest.part_row * D + col) = acc;
+      if (col == 0) a.part_l[dest.part_row] = lse;
+      continue;
+    }
+    if (MODE == kModeExact && a.merge_levels > 0) {
+      float rmx, den;
+      const float Lm = merged_lse(a, w.bh, dest.row_in_head, lse, &rmx, &den);
+      acc *= lse == -INFINITY ? 0.f : expf(lse - rmx) / den;
+      for (int l2 = 0; l2 < a.merge_levels; ++l2) {
+        int64_t pr;
+        if (!level_touches(a.g, w.bh, dest.row_in_head, l2, &pr)) continue;
+        const float lp = a.part_l[pr];
+        if (lp == -INFINITY) continue;
+        acc += (expf(lp - rmx) / den) * *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(a.part_o) + pr * D + col);
+      }
+      lse = Lm;
+    }
+    if (a.out != nullptr) *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(a.out) + dest.out_row * D + col) = acc;
+    if (a.lse != nullptr && col == 0) a.lse[dest.out_row] = lse;
+  }
+}
+
+template <int D, int MODE, int KW>
+static int launch_f32_one(const AttnArgs& a, hipStream_t st) {
+  constexpr int kQT = 32 * (4 / KW);
+  const int64_t grid = MODE == kModeNode ? node_grid<kQT>(a.g) : exact_grid<kQT>(a);
+  if (grid <= 0) return HA_OK;
+  if (grid > kMaxGrid) return HA_ERR_SHAPE;
+  const size_t lds = f32_lds_bytes<D>(a.g.b, a.g.m, MODE);
+  static std::atomic<uint64_t> lds_set{0};  // per instantiation: devices on which the LDS limit is raised
+  if (allow_full_lds(reinterpret_cast<const void*>(&attn_f32_kernel<D, MODE, KW>), lds_set) != HA_OK) return HA_ERR_LAUNCH;
+  hipLaunchKernelGGL((attn_f32_kernel<D, MODE, KW>), dim3((unsigned)grid), dim3(kFNT), lds, st, a);
+  return check_launch();
+}
+
+// Waves that share a group of 32 queries: as few as leave the chip's 1024 SIMDs two waves each, but
+// enough that a workgroup's 128 / KW rows do not outgrow the run of rows it is cut from (a block of b
+// sorted positions, an exact diagonal block) by more than a third: idle rows cost matrix time like real
+// ones, while the merge of KW results costs a few LDS reads per row.
+template <int D, int MODE>
+static int launch_f32_mode(const AttnArgs& a, hipStream_t st) {
+  const int run = MODE == kModeNode ? a.g.b : (a.exact_block < a.exact_rows_q ? a.exact_block : a.exact_rows_q);
+  auto padded = [&](int qt) { return (int64_t)((run + qt - 1) / qt) * qt; };
+  const int64_t waves = 4 * (MODE == kModeNode ? node_grid<128>(a.g) : exact_grid<128>(a));
+  if (waves >= 2048 && 3 * padded(128) <= 4 * (int64_t)run) return launch_f32_one<D, MODE, 1>(a, st);
+  if (waves >= 1024 && 3 * padded(64) <= 4 * (int64_t)run) return launch_f32_one<D, MODE, 2>(a, st);
+  return launch_f32_one<D, MODE, 4>(a, st);
+}
+
+int launch_attn_f32(const AttnArgs& a, int mode, hipStream_t st) {
+  if (a.g.dtype != HA_FP32) return HA_ERR_DTYPE;
+  if (a.g.d == 128) return mode == kModeNode ? launch_f32_mode<128, kModeNode>(a, st) : launch_f32_mode<128, kModeExact>(a, st);
+  if (a.g.d == 64) return mode == kModeNode ? launch_f32_mode<64, kModeNode>(a, st) : launch_f32_mode<64, kModeExact>(a, st);
+  return HA_ERR_SHAPE;
+}
+
+}  // namespace ha

@@ -73,7 +73,7 @@ __host__ __device__ inline NodeRef node_ref(const Geometry& g, int level, int no
 }
 
 // ---------------------------------------------------------------------------
-// Arguments of the attention kernels (MFMA and generic share them).
+// Arguments of the attention kernels (the bf16 and the fp32 kernels share them).
 // ---------------------------------------------------------------------------
 enum AttnMode : int32_t {
   kModeNode = 0,   // unmasked node(s): block keys by list + kept sampled keys
@@ -133,7 +133,7 @@ int launch_prep(float* R_ws, const float* R_dev, const uint16_t* R_bf16_host, in
                 const int32_t* samples_dev, const Geometry& g, uint64_t seed, hipStream_t st);
 int launch_attn_mfma(const AttnArgs& a, int mode, hipStream_t st);
 int64_t attn_mfma_grid(const AttnArgs& a, int mode);  // workgroups of the four-wave launch of that mode
-int launch_attn_generic(const AttnArgs& a, int mode, hipStream_t st);
+int launch_attn_f32(const AttnArgs& a, int mode, hipStream_t st);
 int launch_gather_rows(const void* src, const int32_t* idx, void* dst, int groups, int n, int d, int dtype,
                        hipStream_t st);
 int launch_merge_unpermute(const float* o_b, const float* lse_b, const float* o_r, const float* lse_r,

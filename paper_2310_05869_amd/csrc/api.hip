@@ -321,19 +321,9 @@ static int stage_geometry(Geometry* g, int groups, int n, int d, int dtype, int 
 // ---------------------------------------------------------------------------
 // Backward pass
 // ---------------------------------------------------------------------------
-// bf16 tensors: matrix cores; fp32 tensors: the fp32 FMA kernel with the same passes
+// bf16 tensors: bf16 matrix cores; fp32 tensors: fp32 matrix cores, the same passes
 static int launch_attn_bwd(const BwdArgs& a, int mode, hipStream_t st) {
-  return use_mfma(a.f.g) ? launch_attn_bwd_mfma(a, mode, st) : launch_attn_bwd_generic(a, mode, st);
-}
-
-static int64_t bwd_sample_rows(const Geometry& g) {
-  int64_t rows = 0;
-  if (g.m <= 0) return 0;
-  for (int l = 0; l < g.levels; ++l) {
-    const int nodes = g.causal ? (1 << l) : 1;
-    rows += (int64_t)g.BH * nodes * bwd_chunks_per_node(g, l) * g.m;
-  }
-  return rows;
+  return use_mfma(a.f.g) ? launch_attn_bwd_mfma(a, mode, st) : launch_attn_bwd_f32(a, mode, st);
 }
 
 static void fill_bwd_layout(const Geometry& g, ha_bwd_ws_layout* l) {
@@ -350,7 +340,7 @@ static void fill_bwd_layout(const Geometry& g, ha_bwd_ws_layout* l) {
   // accumulated node rows: dQ first, then (dQ being written out) dK in the same region, dV in the second
   l->acc_a = take(g.levels > 0 ? rows * rowb : 0);
   l->acc_b = take(g.levels > 0 ? rows * rowb : 0);
-  const size_t srows = (size_t)bwd_sample_rows(g);
+  const size_t srows = (size_t)bwd_sample_chunks(g, bwd_chunk(g)) * g.m;  // one per (head, node, query chunk, sample)
   l->samp_k = take(srows * rowb);
   l->samp_v = take(srows * rowb);
   l->total_bytes = off < 256 ? 256 : off;
@@ -409,18 +399,14 @@ static int backward_impl(const void* Q, const void* K, const void* V, const void
   a.lse = lse;
   a.delta = delta;
   {
-    int wg = 0;
-    int64_t row = 0;
-    const int spn = (g.m + 127) / 128;
+    a.chunk = bwd_chunk(g);
+    int off = 0;
     for (int l = 0; l < g.levels; ++l) {
-      const int nodes = g.causal ? (1 << l) : 1;
-      const int cpn = bwd_chunks_per_node(g, l);
-      a.samp_wg_off[l] = wg;
-      a.samp_row_off[l] = row;
-      wg += g.BH * nodes * cpn * spn;
-      row += (int64_t)g.BH * nodes * cpn * g.m;
+      a.samp_off[l] = off;
+      a.samp_row_off[l] = (int64_t)off * g.m;
+      off += g.BH * (g.causal ? (1 << l) : 1) * bwd_chunks_per_node(g, a.chunk, l);
     }
-    a.samp_wg_off[g.levels] = wg;
+    a.samp_off[g.levels] = off;
   }
 
   mark(0);
@@ -429,11 +415,11 @@ static int backward_impl(const void* Q, const void* K, const void* V, const void
   mark(1);
   // node passes: one launch per level, in level order, so that a row's contributions from different levels
   // are added one after the other
-  const int64_t wgs_per_level = bwd_grid(a, kBwdDqNode);
-  if (wgs_per_level * g.levels > 0x7fffffff) return HA_ERR_SHAPE;
+  // (workgroup numbers of all levels are 32-bit; 32 rows per workgroup is the smallest form)
+  if (g.levels > 0 && node_grid<32>(g) > kMaxGrid) return HA_ERR_SHAPE;
   auto node_levels = [&](int mode) -> int {
     for (int l = 0; l < g.levels; ++l) {
-      a.wg_base = (int32_t)(l * wgs_per_level);
+      a.level = l;
       const int r = launch_attn_bwd(a, mode, st);
       if (r != HA_OK) return r;
     }

@@ -1,0 +1,314 @@
+// Backward pass on the fp32 matrix cores: the arithmetic path for HA_FP32 tensors
+// (v_mfma_f32_32x32x2_f32: every product and sum in fp32), with the same passes and the
+// same buffers as the bf16 backward kernel, so that the host sequence is one and the same.
+//
+// As there, a row of the forward is one softmax over its block keys, its kept sampled keys (weight
+// s/m) and, when causal, the keys of its base-case block (Algorithms 1, 2, 4), and with the final
+// log row sum L_i and delta_i = <dO_i, O_i> every (query, key) pair contributes on its own:
+//   P_ij = w_ij exp(<q_i, k_j> - L_i),  dV_j += P_ij dO_i,  dS_ij = P_ij (<dO_i, v_j> - delta_i),
+//   dQ_i += dS_ij k_j,  dK_j += dS_ij q_i.
+//
+// A wave owns 32 "R rows" (queries in the dQ passes, keys in the dK / dV passes): the row, the operand of
+// dP and the accumulators live in its registers.  The "T rows" (keys, resp. queries) come in tiles of 32
+// straight from the caches in operand layout, once row-major for the scores and dP and once
+// transposed for the accumulating products (attn_f32.hip has the layouts): no LDS staging and no
+// barrier, because 64-cycle instructions leave the caches 16 B/clk per CU to deliver.  The dK / dV passes
+// form S and dP once and accumulate both gradients: 4 products, 3 in the dQ passes.
+//
+// KW waves share a group of R rows, each taking every KW-th tile; their sums are added through LDS in
+// wave order, so results are bit-reproducible.
+//
+// What bounds it: the matrix pipe.  Measured (MI355X, backward of exact attention, the five algorithmic products
+// counted, seven executed), against two lanes per row with fp32 FMA and separate dK and dV passes, the form before:
+// 8 heads, n = 4096, d = 64 5.5 -> 1.29 ms, d = 128 12.0 -> 2.4 ms; 32 heads, n = 8192, d = 64 17.1 ms = 80 TFLOP/s
+// (112 executed, of 157); 4 causal heads, n = 4096, n_min = 1024, forward + backward 4.07 -> 0.45 ms.
+#include "attn_common.h"
+#include "bwd_common.h"
+
+namespace ha {
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kFTT = 32;   // T rows per tile
+constexpr int kFBT = 256;  // threads: four waves
+
+template <int D>
+struct F32BwdLds {
+  static constexpr int ROW = D + 4;  // floats per staged row
+  static constexpr int BYTES = 4 * 32 * ROW * 4;
+};
+
+template <int D>
+__host__ __device__ inline size_t bwd_f32_lds_bytes(const Geometry& g, int mode) {
+  const size_t list = mode == kBwdDqNode ? (size_t)(((g.b + g.m + 63) & ~63) + 64) * 4 + 64 : 0;
+  return list > (size_t)F32BwdLds<D>::BYTES ? list : (size_t)F32BwdLds<D>::BYTES;
+}
+
+// d = 128 keeps up to 416 values per lane (two fragments in flight beside rows and accumulators): one wave per SIMD
+template <int D, int MODE, int KW>
+__global__ __launch_bounds__(kFBT, D == 64 ? 2 : 1) void attn_bwd_f32_kernel(BwdArgs a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  constexpr bool kDq = (MODE == kBwdDqNode || MODE == kBwdDqExact);
+  constexpr bool kExact = (MODE == kBwdDqExact || MODE == kBwdDkvExact);
+  constexpr bool kSorted = (MODE == kBwdDkvBlock || MODE == kBwdDkvSamp);
+  constexpr int kRT = 32 * (4 / KW);
+  constexpr int KJ = D / 8;
+  constexpr int DT = D / 32;
+  const AttnArgs& f = a.f;
+  const Geometry& g = f.g;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, wave = tid >> 6;
+  const int lq = lane & 31, h = lane >> 5;
+  const int kw = wave % KW, grp = wave / KW;
+  int32_t* scratch = reinterpret_cast<int32_t*>(smem);
+  int32_t* list = scratch + 16;
+
+  // ---- which part of the problem this workgroup owns ----
+  BwdWork b = decode_bwd_work<kRT, MODE>(a, logical_block(blockIdx.x, gridDim.x));
+  const TileWork& w = b.w;
+
+  const int64_t hs = f.q_bh_stride;
+  const float* Qh = reinterpret_cast<const float*>(f.Q) + (int64_t)w.bh * hs;
+  const float* Kh = reinterpret_cast<const float*>(f.K) + (int64_t)w.bh * hs;
+  const float* Vh = reinterpret_cast<const float*>(f.V) + (int64_t)w.bh * hs;
+  const float* Gh = reinterpret_cast<const float*>(a.dO) + (int64_t)w.bh * hs;
+  const float* lse_h = a.lse + (int64_t)w.bh * g.n;
+  const float* del_h = a.delta + (int64_t)w.bh * g.n;
+  const float* Xh = kDq ? Qh : Kh;   // R rows: operand of the scores
+  const float* Ah = kDq ? Gh : Vh;   // R rows: operand of dP
+  const float* Yh = kDq ? Kh : Qh;   // T rows: operand of the scores and of dQ / dK
+  const float* Bh = kDq ? Vh : Gh;   // T rows: operand of dP and of dV
+
+  // ---- this lane's R row ----
+  const int r_in_tile = grp * 32 + lq;
+  const int r_use = r_in_tile < w.rows_valid ? r_in_tile : 0;
+  int blk_r = -1;
+  const int r_row = bwd_r_row<MODE>(a, b, r_use, &blk_r);
+  f32x4 x[KJ], av[KJ];
+#pragma unroll
+  for (int j = 0; j < KJ; ++j) {
+    x[j] = *reinterpret_cast<const f32x4*>(Xh + (int64_t)r_row * D + 8 * j + 4 * h);
+    av[j] = *reinterpret_cast<const f32x4*>(Ah + (int64_t)r_row * D + 8 * j + 4 * h);
+  }
+  float L_r = 0.f, del_r = 0.f;
+  if (kDq) {
+    L_r = lse_h[r_row];
+    del_r = del_h[r_row];
+  }
+
+  // ---- the T rows ----
+  int nT, nb = 0x7fffffff;
+  const int32_t* tperm = nullptr;
+  if (MODE == kBwdDqNode) {
+    nT = build_key_list<kFBT>(f, w, list, scratch, &nb);
+  } else if (MODE == kBwdDkvBlock) {
+    nT = g.b;
+    tperm = f.perm_q + w.seg_off + (int64_t)w.t * g.b;
+  } else if (MODE == kBwdDkvSamp) {
+    nT = b.chunk_len;
+    tperm = f.perm_q + w.seg_off + b.chunk_start;
+  } else {
+    nT = max(0, w.k1 - w.k0);
+  }
+  const float nat_bias = ((MODE == kBwdDqNode || MODE == kBwdDkvSamp) && g.m > 0) ? logf((float)w.nr.s / (float)g.m) : 0.f;
+  // tiles of this wave's group: causal passes leave out those that lie wholly on the masked side
+  int kt_lo = 0, kt_hi = (nT + kFTT - 1) / kFTT;
+  if (MODE == kBwdDqExact && f.exact_causal) kt_hi = min(kt_hi, (w.q0 - w.k0 + grp * 32 + 31) / kFTT + 1);
+  if (MODE == kBwdDkvExact && f.exact_causal) kt_lo = grp;  // T starts at the workgroup's first key
+  auto t_row = [&](int kt) -> int {  // row within the head of T position kt * 32 + lq (clamped to an existing one)
+    const int tp = min(kt * kFTT + lq, nT - 1);
+    if (kExact) return w.k0 + tp;
+    if (kSorted) return tperm[tp];
+    return list[tp];
+  };
+
+  const uint32_t bytes = (uint32_t)g.n * (uint32_t)(D * 4);
+  const __amdgpu_buffer_rsrc_t yrsrc = __builtin_amdgcn_make_buffer_rsrc((void*)Yh, 0, (int)bytes, 0x00020000);
+  const __amdgpu_buffer_rsrc_t brsrc = __builtin_amdgcn_make_buffer_rsrc((void*)Bh, 0, (int)bytes, 0x00020000);
+  auto load_rows = [&](const __amdgpu_buffer_rsrc_t& rsrc, int row, f32x4 (&v)[KJ]) {
+#pragma unroll
+    for (int j = 0; j < KJ; ++j)
+      v[j] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, row * (D * 4) + 16 * h, 32 * j, 0));
+  };
+  // element i of an accumulator is T row 8 (i / 4) + 4 h + i % 4 of the tile; lane l < 32 holds row l's values
+  auto of_elem = [&](auto v, int i) { return __shfl(v, 8 * (i / 4) + 4 * h + (i % 4)); };
+  auto load_cols = [&](const __amdgpu_buffer_rsrc_t& rsrc, int row, float (&v)[16][DT], int i0, int count) {
+#pragma unroll
+    for (int i = i0; i < i0 + count; ++i) {
+      const int off = of_elem(row, i) * (D * 4) + 4 * lq;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) v[i][dt] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, off, 128 * dt, 0));
+    }
+  };
+
+  f32x16 acc1[DT], acc2[kDq ? 1 : DT];  // dQ or dK; dV
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) acc1[dt][i] = 0.f;
+#pragma unroll
+    for (int dt = 0; dt < (kDq ? 1 : DT); ++dt) acc2[dt][i] = 0.f;
+  }
+
+  int row = 0;
+  float sc_l = 0.f, sc_d = 0.f;  // dK / dV passes: L and delta of the T row this lane holds
+  f32x4 yf[KJ];
+  auto fetch = [&](int kt) {
+    row = t_row(kt);
+    load_rows(yrsrc, row, yf);
+    if (!kDq) {
+      sc_l = lse_h[row];
+      sc_d = del_h[row];
+    }
+  };
+  if (kt_lo + kw < kt_hi) fetch(kt_lo + kw);
+  for (int kt = kt_lo + kw; kt < kt_hi; kt += KW) {
+    const int row_c = row;
+    const float scl = sc_l, scd = sc_d;
+    f32x4 bf[KJ];
+    load_rows(brsrc, row_c, bf);
+    f32x16 c, e;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      c[i] = 0.f;
+      e[i] = 0.f;
+    }
+#pragma unroll
+    for (int j = 0; j < KJ; ++j)
+#pragma unroll
+      for (int z = 0; z < 4; ++z) c = __builtin_amdgcn_mfma_f32_32x32x2f32(yf[j][z], x[j][z], c, 0, 0, 0);
+    float tv[16][DT];
+    load_cols(kDq ? yrsrc : brsrc, row_c, tv, 0, 16);
+#pragma unroll
+    for (int j = 0; j < KJ; ++j)
+#pragma unroll
+      for (int z = 0; z < 4; ++z) e = __builtin_amdgcn_mfma_f32_32x32x2f32(bf[j][z], av[j][z], e, 0, 0, 0);
+
+    const int tbase = kt * kFTT;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int tpos = tbase + 8 * (i / 4) + 4 * h + (i % 4);
+      bool masked = tpos >= nT;
+      float bias = 0.f;
+      if (MODE == kBwdDqNode) bias = tpos >= nb ? nat_bias : 0.f;
+      if (MODE == kBwdDkvSamp) {
+        bias = nat_bias;
+        // queries of the key's own block: factor 1 - M of Algorithm 2
+        masked = masked || (unsigned)(b.chunk_start + tpos - blk_r * g.b) < (unsigned)g.b;
+      }
+      if (MODE == kBwdDqExact && f.exact_causal) masked = masked || (w.k0 + tpos > r_row);   // keys after the query
+      if (MODE == kBwdDkvExact && f.exact_causal) masked = masked || (w.k0 + tpos < r_row);  // queries before the key
+      const float L = kDq ? L_r : of_elem(scl, i);
+      const float dl = kDq ? del_r : of_elem(scd, i);
+      const float p = (masked || L == -INFINITY) ? 0.f : expf(c[i] + bias - L);
+      c[i] = p;
+      e[i] = p * (e[i] - dl);
+    }
+    if constexpr (!kDq) {
+      // dV and dK half a tile at a time: the Q rows of a half arrive while the other half's dV products run
+      float yv[16][DT];
+#pragma unroll
+      for (int hf = 0; hf < 2; ++hf) {
+        load_cols(yrsrc, row_c, yv, 8 * hf, 8);
+#pragma unroll
+        for (int i = 8 * hf; i < 8 * hf + 8; ++i)
+#pragma unroll
+          for (int dt = 0; dt < DT; ++dt) acc2[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(tv[i][dt], c[i], acc2[dt], 0, 0, 0);
+      }
+      if (kt + KW < kt_hi) fetch(kt + KW);
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) acc1[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(yv[i][dt], e[i], acc1[dt], 0, 0, 0);
+    } else {
+      if (kt + KW < kt_hi) fetch(kt + KW);
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) acc1[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(tv[i][dt], e[i], acc1[dt], 0, 0, 0);
+    }
+  }
+
+  // ---- results: the waves' rows through LDS, the KW parts of a row added in wave order.  Node passes write
+  // (the first level that holds the row on the pass's side) or add (later levels) fp32 rows of the accumulated
+  // gradient; exact passes write the final gradient after adding the accumulated row where some level
+  // holds this row (queries: second half of the node; keys: first half) ----
+  constexpr int RS = F32BwdLds<D>::ROW;
+  float* rows_lds = reinterpret_cast<float*>(smem);
+  auto write_out = [&](const auto& acc, float* node_dst, float* fin, const float* lvl) {
+    __syncthreads();  // the key list, or the rows of the other gradient, are read no more
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4)
+        *reinterpret_cast<f32x4*>(rows_lds + (wave * 32 + lq) * RS + 32 * dt + 8 * q4 + 4 * h) =
+            (f32x4){acc[dt][4 * q4], acc[dt][4 * q4 + 1], acc[dt][4 * q4 + 2], acc[dt][4 * q4 + 3]};
+    __syncthreads();
+    constexpr int LPR = D / 4;  // lanes per row
+    for (int idx = tid; idx < w.rows_valid * LPR; idx += kFBT) {
+      const int r = idx / LPR, col = (idx % LPR) * 4;
+      const float* src = rows_lds + ((r / 32) * KW * 32 + (r & 31)) * RS + col;
+      f32x4 v = *reinterpret_cast<const f32x4*>(src);
+#pragma unroll
+      for (int k = 1; k < KW; ++k) v += *reinterpret_cast<const f32x4*>(src + k * 32 * RS);
+      int dummy;
+      const int rr = bwd_r_row<MODE>(a, b, r, &dummy);
+      const int64_t out_row = bwd_out_row<MODE>(a, b, r, rr);
+      bool add = false;
+      if (MODE == kBwdDqNode) add = node_levels_hold(g, rr, true, w.level);
+      if (MODE == kBwdDkvBlock) add = node_levels_hold(g, rr, false, w.level);
+      if (kExact) add = lvl != nullptr && node_levels_hold(g, rr, kDq, g.levels);
+      const float* from = kExact ? lvl : node_dst;
+      if (add) v += *reinterpret_cast<const f32x4*>(from + out_row * D + col);
+      *reinterpret_cast<f32x4*>((kExact ? fin : node_dst) + out_row * D + col) = v;
+    }
+  };
+  write_out(acc1, a.out1, reinterpret_cast<float*>(a.fin1), a.lvl1);
+  if constexpr (!kDq) write_out(acc2, a.out2, reinterpret_cast<float*>(a.fin2), a.lvl2);
+}
+
+template <int D, int MODE, int KW>
+static int launch_bwd_f32_one(const BwdArgs& a, hipStream_t st) {
+  const int64_t grid = bwd_grid<32 * (4 / KW)>(a, MODE);
+  if (grid <= 0) return HA_OK;
+  if (grid > kMaxGrid) return HA_ERR_SHAPE;
+  const size_t lds = bwd_f32_lds_bytes<D>(a.f.g, MODE);
+  static std::atomic<uint64_t> lds_set{0};  // per instantiation: devices on which the LDS limit is raised
+  if (allow_full_lds(reinterpret_cast<const void*>(&attn_bwd_f32_kernel<D, MODE, KW>), lds_set) != HA_OK) return HA_ERR_LAUNCH;
+  hipLaunchKernelGGL((attn_bwd_f32_kernel<D, MODE, KW>), dim3((unsigned)grid), dim3(kFBT), lds, st, a);
+  return check_launch();
+}
+
+// Waves that share a group of 32 R rows, by the rule of the forward (launch_f32_mode): few groups or short runs
+// of rows (blocks, sample sets) take four.
+template <int D, int MODE>
+static int launch_bwd_f32_mode(const BwdArgs& a, hipStream_t st) {
+  const Geometry& g = a.f.g;
+  const int run = MODE == kBwdDkvSamp ? g.m : (MODE == kBwdDqNode || MODE == kBwdDkvBlock) ? g.b : a.f.exact_block;
+  const bool fits = 3 * (int64_t)((run + 127) / 128 * 128) <= 4 * (int64_t)run;
+  if (fits && 4 * bwd_grid<128>(a, MODE) >= 2048) return launch_bwd_f32_one<D, MODE, 1>(a, st);
+  return launch_bwd_f32_one<D, MODE, 4>(a, st);
+}
+
+template <int D>
+static int launch_bwd_f32_d(const BwdArgs& a, int mode, hipStream_t st) {
+  switch (mode) {
+    case kBwdDqNode: return launch_bwd_f32_mode<D, kBwdDqNode>(a, st);
+    case kBwdDqExact: return launch_bwd_f32_mode<D, kBwdDqExact>(a, st);
+    case kBwdDkvBlock: return launch_bwd_f32_mode<D, kBwdDkvBlock>(a, st);
+    case kBwdDkvSamp: return launch_bwd_f32_mode<D, kBwdDkvSamp>(a, st);
+    case kBwdDkvExact: return launch_bwd_f32_mode<D, kBwdDkvExact>(a, st);
+    default: return HA_ERR_SHAPE;
+  }
+}
+
+int launch_attn_bwd_f32(const BwdArgs& a, int mode, hipStream_t st) {
+  if (a.f.g.dtype != HA_FP32) return HA_ERR_DTYPE;
+  if (a.f.g.d == 128) return launch_bwd_f32_d<128>(a, mode, st);
+  if (a.f.g.d == 64) return launch_bwd_f32_d<64>(a, mode, st);
+  return HA_ERR_SHAPE;
+}
+
+}  // namespace ha

@@ -98,65 +98,8 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
   int32_t* list = scratch + 16;
 
   // ---- which part of the problem this workgroup owns ----
-  TileWork w{};
-  int chunk_start = 0, chunk_len = 0, samp0 = 0;  // sampled-key pass
-  int64_t samp_row0 = 0;
-  int t0 = 0;                                      // exact dK/dV pass: first query row of the T range
-  if (MODE == kBwdDqNode || MODE == kBwdDkvBlock) {
-    w = decode_node_tile<kRT>(f, a.wg_base + logical_block(blockIdx.x, gridDim.x));
-  } else if (MODE == kBwdDqExact) {
-    w = decode_exact_tile<kRT>(f, logical_block(blockIdx.x, gridDim.x));
-  } else if (MODE == kBwdDkvExact) {
-    // key tiles of the diagonal blocks; early key tiles see the most queries
-    const int eb = f.exact_block;
-    const int tpb = (eb + kRT - 1) / kRT;
-    const int nblk = (f.exact_rows_q + eb - 1) / eb;
-    const int idx = logical_block(blockIdx.x, gridDim.x);
-    const int rest = idx / tpb;
-    const int ktile = (idx % tpb + rest) % tpb;  // starting tile rotated per block: see decode_exact_tile
-    const int blk = rest % nblk;
-    w.bh = rest / nblk;
-    w.q0 = blk * eb + ktile * kRT;  // first KEY row of this tile
-    const int blk_rows = min(eb, f.exact_rows_q - blk * eb);
-    w.rows_valid = max(0, min(kRT, blk_rows - ktile * kRT));
-    t0 = f.exact_causal ? w.q0 : blk * eb;
-    w.k0 = t0;
-    w.k1 = blk * eb + blk_rows;     // queries [t0, k1)
-  } else {  // kBwdDkvSamp
-    // (static indices only: a dynamically indexed kernel-argument array would be copied to scratch)
-    const int sbid = logical_block(blockIdx.x, gridDim.x);  // slabs of one chunk meet in one L2
-    int level = 0, wg0 = 0;
-    int64_t srow0 = 0;
-#pragma unroll
-    for (int l = 0; l < kBwdMaxLevels; ++l)
-      if (l < g.levels && sbid >= a.samp_wg_off[l]) {
-        level = l;
-        wg0 = a.samp_wg_off[l];
-        srow0 = a.samp_row_off[l];
-      }
-    const NodeRef probe = node_ref(g, level, 0);
-    const int clen = min(probe.s, kBwdChunk);
-    const int cpn = (probe.s + clen - 1) / clen;        // chunks per node
-    const int spn = (g.m + kRT - 1) / kRT;              // sample slabs per node
-    const int nodes = g.causal ? (1 << level) : 1;
-    int idx = sbid - wg0;
-    const int slab = idx % spn;
-    idx /= spn;
-    const int qc = idx % cpn;
-    idx /= cpn;
-    const int node = idx % nodes;
-    w.bh = idx / nodes;
-    w.level = level;
-    w.nr = node_ref(g, level, node);
-    w.seg_off = ((int64_t)level * g.BH + w.bh) * g.n_cov + (int64_t)node * w.nr.s;
-    chunk_start = qc * clen;
-    chunk_len = min(clen, w.nr.s - chunk_start);
-    samp0 = slab * kRT;
-    w.rows_valid = min(kRT, g.m - samp0);
-    samp_row0 = srow0;
-    w.t = qc;  // reused: chunk index
-    w.p0 = cpn;
-  }
+  const BwdWork b = decode_bwd_work<kRT, MODE>(a, logical_block(blockIdx.x, gridDim.x));
+  const TileWork& w = b.w;
 
   const int64_t hs = f.q_bh_stride;
   const uint16_t* Qh = reinterpret_cast<const uint16_t*>(f.Q) + (int64_t)w.bh * hs;
@@ -174,26 +117,9 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
   const int r_in_tile = wave * 32 + lq;
   const bool r_valid = r_in_tile < w.rows_valid;
   const int r_use = r_valid ? r_in_tile : 0;
-  int r_row;             // row within the head
-  int64_t out_row;       // row in out1 / out2
   int blk_r = -1;        // sampled-key pass: sorted block of this key
-  if (MODE == kBwdDqNode) {
-    r_row = f.perm_q[w.seg_off + w.p0 + r_use];
-    out_row = (int64_t)w.bh * g.n + r_row;
-  } else if (MODE == kBwdDkvBlock) {
-    r_row = f.perm_k[w.seg_off + w.p0 + r_use];
-    out_row = (int64_t)w.bh * g.n + r_row;
-  } else if (MODE == kBwdDkvSamp) {
-    const int j = samp0 + r_use;
-    r_row = w.nr.k_start + f.samples[(int64_t)w.nr.heap * g.m + j];
-    blk_r = f.samp_blk[((int64_t)w.bh * g.total_nodes + w.nr.heap) * g.m + j];
-    const int nodes = g.causal ? (1 << w.level) : 1;
-    const int node = w.nr.heap - ((1 << w.level) - 1);
-    out_row = samp_row0 + ((((int64_t)w.bh * nodes + node) * w.p0 + w.t) * g.m + j);
-  } else {
-    r_row = w.q0 + r_use;
-    out_row = (int64_t)w.bh * g.n + r_row;
-  }
+  const int r_row = bwd_r_row<MODE>(a, b, r_use, &blk_r);           // row within the head
+  const int64_t out_row = bwd_out_row<MODE>(a, b, r_use, r_row);    // row in out1 / out2
   bf16x8 xreg[KS], areg[kLoadA ? KS : 1];
   {
     const u32x4* xp = reinterpret_cast<const u32x4*>(Xh + (int64_t)r_row * D + 8 * h);
@@ -221,8 +147,8 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
     nT = g.b;
     tperm = f.perm_q + w.seg_off + (int64_t)w.t * g.b;
   } else if (MODE == kBwdDkvSamp) {
-    nT = chunk_len;
-    tperm = f.perm_q + w.seg_off + chunk_start;
+    nT = b.chunk_len;
+    tperm = f.perm_q + w.seg_off + b.chunk_start;
   } else {
     nT = max(0, w.k1 - w.k0);
   }
@@ -328,11 +254,11 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
       }
       if (MODE == kBwdDkvSamp) {
         tile_bias = bias2;
-        mlo2 = blk_r * g.b - (chunk_start + tbase) - 4 * h;
+        mlo2 = blk_r * g.b - (b.chunk_start + tbase) - 4 * h;
         mhi2 = mlo2 + g.b;
       }
       if (MODE == kBwdDqExact && f.exact_causal) hi2 = min(hi2, r_global - w.k0 - tbase + 1 - 4 * h);
-      if (MODE == kBwdDkvExact && f.exact_causal) lo2 = r_global - t0 - tbase - 4 * h;
+      if (MODE == kBwdDkvExact && f.exact_causal) lo2 = r_global - w.k0 - tbase - 4 * h;
       // highest / lowest ko of a lane: 59 / 0
       const bool special = __any(hi2 <= 59 || lo2 > 0 || nb2 <= 59 || (mlo2 <= 59 && mhi2 > 0));
 
@@ -564,16 +490,9 @@ static int launch_bwd_d(const BwdArgs& a, int mode, int grid, hipStream_t st) {
     default: return HA_ERR_SHAPE;
   }
 }
-int64_t bwd_grid(const BwdArgs& a, int mode) {
-  const Geometry& g = a.f.g;
-  if (mode == kBwdDqNode || mode == kBwdDkvBlock) return g.levels > 0 ? node_grid<kRT>(g) / g.levels : 0;  // one level per launch
-  if (mode == kBwdDqExact || mode == kBwdDkvExact) return exact_grid<kRT>(a.f);
-  return a.samp_wg_off[g.levels];
-}
-
 int launch_attn_bwd_mfma(const BwdArgs& a, int mode, hipStream_t st) {
   if (a.f.g.dtype != HA_BF16) return HA_ERR_DTYPE;
-  const int64_t grid64 = bwd_grid(a, mode);
+  const int64_t grid64 = bwd_grid<kRT>(a, mode);
   if (grid64 > kMaxGrid) return HA_ERR_SHAPE;
   const int grid = (int)grid64;
   if (a.f.g.d == 128) return launch_bwd_d<128>(a, mode, grid, st);

@@ -1,11 +1,11 @@
 // Declarations shared by the backward-pass kernels and their host driver.
 #pragma once
 
-#include "ha_common.h"
+#include "attn_common.h"
 
 namespace ha {
 
-// Passes of the MFMA backward kernel.
+// Passes of the backward kernels.
 enum BwdMode : int32_t {
   kBwdDqNode = 0,    // dQ of the node parts: query tiles over their key lists (block keys + kept samples)
   kBwdDqExact = 1,   // dQ of exact attention / the causal base case
@@ -15,7 +15,6 @@ enum BwdMode : int32_t {
 };
 
 constexpr int kBwdMaxLevels = 24;
-constexpr int kBwdChunk = 2048;  // sorted query positions per workgroup of the sampled-key pass
 
 struct BwdArgs {
   AttnArgs f;          // tensors, permutations, samples and geometry as in the forward
@@ -28,15 +27,17 @@ struct BwdArgs {
   // (per level, head, node, query chunk, sample) into out1 / out2 instead.
   float* out1;
   float* out2;
-  int32_t wg_base;     // node passes: first workgroup of the launch's level in the all-level numbering
+  int32_t level;       // node passes: the launch's level
   // exact passes write the final gradients (tensors' dtype): fin1 = dQ or dK, fin2 = dV, after adding
   // the accumulated node rows lvl1 / lvl2 (null: none) where some level holds the row on that side
   void* fin1;
   void* fin2;
   const float* lvl1;
   const float* lvl2;
-  // sampled-key pass: first workgroup and first output row of every level
-  int32_t samp_wg_off[kBwdMaxLevels + 1];
+  // sampled-key pass: sorted query positions per workgroup, first (head, node, query chunk) and first
+  // output row of every level
+  int32_t chunk;
+  int32_t samp_off[kBwdMaxLevels + 1];
   int64_t samp_row_off[kBwdMaxLevels];
 };
 
@@ -53,16 +54,118 @@ __host__ __device__ inline bool node_levels_hold(const Geometry& g, int i, bool 
 }
 
 // Chunks of sorted query positions per node at a level, for the sampled-key pass.
-__host__ __device__ inline int bwd_chunks_per_node(const Geometry& g, int level) {
+__host__ __device__ inline int bwd_chunks_per_node(const Geometry& g, int chunk, int level) {
   const int s = g.causal ? (g.n >> (level + 1)) : g.n;
-  const int clen = s < kBwdChunk ? s : kBwdChunk;
+  const int clen = s < chunk ? s : chunk;
   return (s + clen - 1) / clen;
 }
 
-// workgroups of a launch (128 R rows each), the same for both kernels; node passes: of one level
-int64_t bwd_grid(const BwdArgs& a, int mode);
-int launch_attn_bwd_mfma(const BwdArgs& a, int mode, hipStream_t st);     // bf16 tensors
-int launch_attn_bwd_generic(const BwdArgs& a, int mode, hipStream_t st);  // fp32 tensors
+// (head, node, query chunk) triples over all levels
+inline int64_t bwd_sample_chunks(const Geometry& g, int chunk) {
+  int64_t total = 0;
+  for (int l = 0; l < g.levels; ++l) total += (int64_t)g.BH * (g.causal ? (1 << l) : 1) * bwd_chunks_per_node(g, chunk, l);
+  return total;
+}
+
+// Sorted query positions per workgroup of the sampled-key pass.
+inline int bwd_chunk(const Geometry&) { return 2048; }
+
+// What a workgroup of QT "R rows" owns in each pass (TileWork: the head, the node, the rows; exact dK / dV
+// pass: q0 = first KEY row, [k0, k1) = its queries).
+struct BwdWork {
+  TileWork w;
+  int chunk_start, chunk_len;   // sampled-key pass: run of sorted query positions
+  int samp0;                    // first sample
+  int64_t samp_row0;            // row of sample 0 of this (head, node, chunk) in the pass's output
+};
+
+template <int QT, int MODE>
+__device__ inline BwdWork decode_bwd_work(const BwdArgs& a, int idx) {
+  const AttnArgs& f = a.f;
+  const Geometry& g = f.g;
+  BwdWork b{};
+  if (MODE == kBwdDqNode || MODE == kBwdDkvBlock) {
+    b.w = decode_node_tile<QT>(f, a.level * (int)gridDim.x + idx);
+  } else if (MODE == kBwdDqExact) {
+    b.w = decode_exact_tile<QT>(f, idx);
+  } else if (MODE == kBwdDkvExact) {
+    // key tiles of the diagonal blocks; early key tiles see the most queries
+    const int eb = f.exact_block;
+    const int tpb = (eb + QT - 1) / QT;
+    const int nblk = (f.exact_rows_q + eb - 1) / eb;
+    const int rest = idx / tpb;
+    const int ktile = (idx % tpb + rest) % tpb;  // starting tile rotated per block: see decode_exact_tile
+    const int blk = rest % nblk;
+    b.w.bh = rest / nblk;
+    b.w.q0 = blk * eb + ktile * QT;  // first KEY row of this tile
+    const int blk_rows = min(eb, f.exact_rows_q - blk * eb);
+    b.w.rows_valid = max(0, min(QT, blk_rows - ktile * QT));
+    b.w.k0 = f.exact_causal ? b.w.q0 : blk * eb;
+    b.w.k1 = blk * eb + blk_rows;     // queries [k0, k1)
+  } else {  // kBwdDkvSamp: a slab of QT samples over one chunk of the node's sorted queries
+    const int spn = (g.m + QT - 1) / QT;              // sample slabs per node
+    const int slab = idx % spn;
+    const int cidx = idx / spn;
+    // (static indices only: a dynamically indexed kernel-argument array would be copied to scratch)
+    int level = 0, first = 0;
+    int64_t srow0 = 0;
+#pragma unroll
+    for (int l = 0; l < kBwdMaxLevels; ++l)
+      if (l < g.levels && cidx >= a.samp_off[l]) {
+        level = l;
+        first = a.samp_off[l];
+        srow0 = a.samp_row_off[l];
+      }
+    const int cpn = bwd_chunks_per_node(g, a.chunk, level);
+    const int nodes = g.causal ? (1 << level) : 1;
+    const int qc = (cidx - first) % cpn;
+    const int hn = (cidx - first) / cpn;               // (head, node)
+    const int node = hn % nodes;
+    b.w.bh = hn / nodes;
+    b.w.level = level;
+    b.w.nr = node_ref(g, level, node);
+    b.w.seg_off = ((int64_t)level * g.BH + b.w.bh) * g.n_cov + (int64_t)node * b.w.nr.s;
+    b.chunk_start = qc * a.chunk;
+    b.chunk_len = min(a.chunk, b.w.nr.s - b.chunk_start);
+    b.samp0 = slab * QT;
+    b.w.rows_valid = min(QT, g.m - b.samp0);
+    b.samp_row0 = srow0 + (int64_t)(cidx - first) * g.m;
+  }
+  return b;
+}
+
+// Row within the head of the workgroup's R row r; sampled-key pass: *blk_r = the sorted block of that key.
+template <int MODE>
+__device__ inline int bwd_r_row(const BwdArgs& a, const BwdWork& b, int r, int* blk_r) {
+  const AttnArgs& f = a.f;
+  if (MODE == kBwdDqNode) return f.perm_q[b.w.seg_off + b.w.p0 + r];
+  if (MODE == kBwdDkvBlock) return f.perm_k[b.w.seg_off + b.w.p0 + r];
+  if (MODE == kBwdDkvSamp) {
+    const int j = b.samp0 + r;
+    *blk_r = f.samp_blk[((int64_t)b.w.bh * f.g.total_nodes + b.w.nr.heap) * f.g.m + j];
+    return b.w.nr.k_start + f.samples[(int64_t)b.w.nr.heap * f.g.m + j];
+  }
+  return b.w.q0 + r;
+}
+
+// Where its gradient goes: row of out1 / out2 (sampled-key pass: a row of its own per sample) or of fin1 / fin2.
+template <int MODE>
+__device__ inline int64_t bwd_out_row(const BwdArgs& a, const BwdWork& b, int r, int row) {
+  if (MODE == kBwdDkvSamp) return b.samp_row0 + b.samp0 + r;
+  return (int64_t)b.w.bh * a.f.g.n + row;
+}
+
+// Workgroups of QT R rows in a launch; node passes: of one level.
+template <int QT>
+inline int64_t bwd_grid(const BwdArgs& a, int mode) {
+  const Geometry& g = a.f.g;
+  if (mode == kBwdDqNode || mode == kBwdDkvBlock) return g.levels > 0 ? node_grid<QT>(g) / g.levels : 0;
+  if (mode == kBwdDqExact || mode == kBwdDkvExact) return exact_grid<QT>(a.f);
+  return (int64_t)a.samp_off[g.levels] * ((g.m + QT - 1) / QT);
+}
+
+int launch_attn_bwd_mfma(const BwdArgs& a, int mode, hipStream_t st);  // bf16 tensors
+int launch_attn_bwd_f32(const BwdArgs& a, int mode, hipStream_t st);   // fp32 tensors
 // delta_i = <dO_i, O_i>; bf16 tensors: O from its unrounded fp32 copy when O_f32 is non-null, else from the tensor
 int launch_bwd_delta(const void* O, const float* O_f32, const void* dO, float* delta, int64_t rows, int d, int dtype,
                      hipStream_t st);

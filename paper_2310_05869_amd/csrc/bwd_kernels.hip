@@ -117,7 +117,7 @@ __global__ __launch_bounds__(64 * kScatterWaves) void bwd_sample_scatter_kernel(
   const int node = rest % nodes;
   const int heap = (1 << level) - 1 + node;
   const NodeRef nr = node_ref(g, level, node);
-  const int cpn = bwd_chunks_per_node(g, level);
+  const int cpn = bwd_chunks_per_node(g, a.chunk, level);
   const int64_t key_row0 = (int64_t)bh * g.n + nr.k_start;  // the node's first key in the accumulated rows
   int64_t lvl_row0 = 0;
 #pragma unroll

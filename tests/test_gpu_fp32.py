@@ -40,3 +40,56 @@ def test_exact_attention_fp32_forms(H, n, d, causal):
     ref_o, ref_l = orc.exact_attention(*(x[0, hd] for x in (Q, K, V)), causal=causal)
     assert_close(to_host(out)[0, hd], ref_o, "fp32", "out")
     assert_lse_close(to_host(lse)[0, hd], ref_l, "fp32", "lse")
+
+
+@pytest.mark.parametrize("H,n,d,b,m,causal,n_min", [
+    (32, 4096, 64, 128, 100, 0, 4096),    # one wave per group in every pass, samples included
+    (32, 4096, 128, 128, 128, 1, 2048),
+    (5, 2112, 64, 33, 65, 0, 4096),       # four waves per group, one row in the second 32-row tile
+    (1, 264, 128, 33, 5, 1, 132)])
+def test_backward_fp32_forms(H, n, d, b, m, causal, n_min):
+    """Criterion |got - ref| <= 2^-14 bound (fp32 sums of up to 2^10 terms; bound: the oracle on absolute values)."""
+    import torch
+
+    import paper_2310_05869_amd as ha
+    print(f"fp32 backward forms H={H} n={n} d={d} b={b} m={m} causal={causal}", flush=True)
+    cfg = dict(B=1, H=H, n=n, d=d, dtype="fp32", law="iid", b=b, m=m, r=7, causal=causal, n_min=n_min, seed=1)
+    Q, K, V = synth_inputs.make_qkv(cfg)
+    G = synth_inputs.iid_qkv(1, H, n, d, "fp32", seed=5)[0]
+    tq, tk, tv, tg = (to_device(x, "fp32") for x in (Q, K, V, G))
+    kw = dict(causal=bool(causal), n_min=n_min, seed=1)
+    ws = ha.alloc_workspace(ha.make_shape(1, H, n, d, ha.HA_FP32), ha.make_params(b, m, 7, causal, n_min, 1))
+    out, lse = ha.hyperattn_forward(tq, tk, tv, b, m, 7, workspace=ws, **kw)
+    got = ha.hyperattn_backward(tq, tk, tv, out, lse, tg, b, m, 7, fwd_workspace=ws, **kw)
+    again = ha.hyperattn_backward(tq, tk, tv, out, lse, tg, b, m, 7, fwd_workspace=ws, **kw)
+    assert all(torch.equal(x, y) for x, y in zip(got, again))
+    hd = H - 1
+    one = [x[:, hd:hd + 1] for x in (Q, K, V, G)]
+    ref = orc.hyperattn_backward(*one, b=b, m=m, r=7, **kw)
+    bound = orc.hyperattn_backward(*one, b=b, m=m, r=7, absolute=True, **kw)
+    for name, x, y, lim in zip(("dQ", "dK", "dV"), got, ref, bound):
+        err = abs(to_host(x)[:, hd:hd + 1] - y)
+        assert (err <= 2.0 ** -14 * lim + 2.0 ** -100).all(), (name, err.max())
+
+
+@pytest.mark.parametrize("H,n,d,causal", [(32, 2079, 64, True), (32, 2079, 128, True), (16, 4100, 128, False)])
+def test_exact_backward_fp32_forms(H, n, d, causal):
+    import torch
+
+    import paper_2310_05869_amd as ha
+    print(f"fp32 exact backward forms H={H} n={n} d={d} causal={causal}", flush=True)
+    Q, K, V = synth_inputs.iid_qkv(1, H, n, d, "fp32")
+    G = synth_inputs.iid_qkv(1, H, n, d, "fp32", seed=5)[0]
+    tq, tk, tv, tg = (to_device(x, "fp32") for x in (Q, K, V, G))
+    out, lse = ha.exact_attn_forward(tq, tk, tv, causal=causal)
+    got = ha.exact_attn_backward(tq, tk, tv, out, lse, tg, causal=causal)
+    torch.cuda.synchronize()
+    hd = H - 1
+    one = [x[:, hd:hd + 1] for x in (Q, K, V, G)]
+    okw = dict(b=1, m=0, r=1, causal=True, n_min=n) if causal else dict(b=n, m=0, r=1, causal=False)
+    ref = orc.hyperattn_backward(*one, **okw)
+    bound = orc.hyperattn_backward(*one, absolute=True, **okw)
+    for name, x, y, lim in zip(("dQ", "dK", "dV"), got, ref, bound):
+        err = abs(to_host(x)[:, hd:hd + 1] - y)
+        # sums of up to 4100 terms, 2^-24 each
+        assert (err <= 2.0 ** -12 * lim + 2.0 ** -100).all(), (name, err.max())

@@ -24,8 +24,16 @@
 // to bf16 are directly the B operands of the accumulating products, whose A
 // operands (T tile transposed) come from the transposing LDS read.
 //
-// The dK/dV passes run twice, once accumulating dK (scores, dP, dS) and once
-// dV (scores, P): one accumulator set each, so two waves fit per SIMD.
+// The dK / dV passes form S and dP once and accumulate both gradients (4 products; 3 in the dQ passes).
+// At d = 128 that is 128 accumulator registers, 64 of R rows and 32 of scores out of the 256 that two waves
+// per SIMD leave each, so the T tiles go to LDS by DMA (buffer loads with an LDS destination) and never
+// pass through registers.  A DMA instruction fills 1 KiB of consecutive LDS, so rows cannot be padded
+// against bank conflicts; instead the 16-byte pieces of a row are swizzled (BwdLds), which the lanes do
+// by choosing which piece of the row they fetch.
+// Measured (MI355X, 32 causal heads, n = 131072, d = 128, b = m = 256), against dK and dV in passes of their own and
+// tiles staged through registers: dK / dV of the base case 13.9 -> 10.0 ms, of the sampled keys 5.5 -> 4.1 ms, of the
+// blocks (one launch that walked the rows twice) 7.65 -> 6.25 ms, dQ of the base case 7.1 -> 6.8 ms;
+// forward + backward 50.5 -> 43.5 ms.  Results are bit-identical.
 //
 // Sums over parts are taken in a fixed order, never by floating-point atomics: the node passes run
 // level by level and add their fp32 rows to one accumulated row per tensor row (the first level
@@ -47,44 +55,60 @@ constexpr int kTT = 64;    // T rows per step
 constexpr int kRT = 128;   // R rows per workgroup (4 waves x 32)
 constexpr int kBNT = 256;  // threads
 
+// A T tile: 64 rows of D * 2 bytes, unpadded; piece c (16 bytes) of row r sits at place c ^ swz(r).
+// Both readers are conflict-free: the row-major reads take one piece of 16 rows at a time (swz is a
+// bijection on 16 rows, together with the row's parity at d = 64), the transposing reads 64
+// consecutive bytes of four rows (which swz sends to four different quarters of the banks).
 template <int D>
 struct BwdLds {
-  static constexpr int TSTR = (D + 24) * 2;     // bytes per T row: serves both the 16-byte row reads and the transposing reads
-  static constexpr int TILE = kTT * TSTR;       // one tensor's tile
+  static constexpr int ROWB = D * 2;
+  static constexpr int TILE = kTT * ROWB;       // one tensor's tile
   static constexpr int BUF = 2 * TILE;          // y tile + bt tile
   static constexpr int SC = 2 * kTT * 4;        // per buffer: -L log2(e) and delta of the T rows
   static constexpr int EP_ROW = D * 4 + 16;
   static constexpr int EP_WAVE = 32 * EP_ROW + 256;  // rows, row ids
+  __device__ static int swz(int row) {
+    if (D == 128) return ((row & 3) << 2) | ((row >> 2) & 3);
+    return ((row & 2) << 1) | ((row >> 2) & 3);
+  }
 };
 
-__host__ __device__ inline int bwd_list_capacity(const Geometry& g, int mode) {
+// rows of the T positions, where they are not consecutive: the key list (dQ of a node), the block's or the chunk's
+// queries (dK / dV of a node)
+__host__ __device__ inline int bwd_list_capacity(const BwdArgs& a, int mode) {
+  const Geometry& g = a.f.g;
   if (mode == kBwdDqNode) return ((g.b + g.m + 63) & ~63) + 64;
+  if (mode == kBwdDkvBlock) return (g.b + 63) & ~63;
+  if (mode == kBwdDkvSamp) return ((a.chunk < g.n_cov ? a.chunk : g.n_cov) + 63) & ~63;
   return 0;
 }
 
 template <int D>
-__host__ __device__ inline size_t bwd_lds_bytes(const Geometry& g, int mode) {
-  return 2 * (size_t)BwdLds<D>::BUF + 2 * BwdLds<D>::SC + 64 + (size_t)bwd_list_capacity(g, mode) * 4;
+__host__ __device__ inline size_t bwd_lds_bytes(const BwdArgs& a, int mode) {
+  const size_t s = 2 * (size_t)BwdLds<D>::BUF + 2 * BwdLds<D>::SC + 64 + (size_t)bwd_list_capacity(a, mode) * 4;
+  return s > (size_t)4 * BwdLds<D>::EP_WAVE ? s : (size_t)4 * BwdLds<D>::EP_WAVE;
 }
 
-// WHAT: which product the pass accumulates.
-enum BwdWhat : int { kAccDs = 0,    // acc += Y^T dS^T : dQ (dQ passes) or dK (dK/dV passes)
-                     kAccP = 1,     // acc += Bt^T P^T : dV (dK/dV passes only)
-                     kAccBoth = 2 };  // dK, then dV, in one launch: the workgroup keeps its R rows and walks its T rows twice
+// 16 bytes per lane from buffer memory to 1 KiB of LDS starting at byte lds_at (wave-uniform).  Inline assembly
+// because the compiler's wait counts would serialise the builtin with every LDS read; the kernel
+// waits for these requests itself, once per tile.
+__device__ inline void dma_1k(const __amdgpu_buffer_rsrc_t& rsrc, uint32_t lds_at, int voff) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds_at), "v"(voff), "s"(rsrc)
+               : "memory");
+}
 
-template <int D, int MODE, int WHAT>
+template <int D, int MODE>
 __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   using L = BwdLds<D>;
   constexpr bool kDq = (MODE == kBwdDqNode || MODE == kBwdDqExact);
   constexpr bool kExact = (MODE == kBwdDqExact || MODE == kBwdDkvExact);
   constexpr bool kSorted = (MODE == kBwdDkvBlock || MODE == kBwdDkvSamp);  // T rows = a run of sorted query positions
-  constexpr bool kLoadA = (WHAT != kAccP);  // the operand of dP is needed whenever dS is formed
-  static_assert(WHAT == kAccDs || !kDq, "the dQ passes accumulate dS only");
   constexpr int KS = D / 16;
   constexpr int DT = D / 32;
-  constexpr int CPR = D / 8;                 // 16-byte chunks per row
-  constexpr int NKC = kTT * CPR / kBNT;      // chunks per thread and tensor
+  constexpr int CPR = D / 8;                 // 16-byte pieces per row
+  constexpr int RPI = 64 / CPR;              // rows per DMA instruction
+  constexpr int NDMA = kTT / RPI / 4;        // instructions per wave and tensor tile
 
   const AttnArgs& f = a.f;
   const Geometry& g = f.g;
@@ -120,14 +144,14 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
   int blk_r = -1;        // sampled-key pass: sorted block of this key
   const int r_row = bwd_r_row<MODE>(a, b, r_use, &blk_r);           // row within the head
   const int64_t out_row = bwd_out_row<MODE>(a, b, r_use, r_row);    // row in out1 / out2
-  bf16x8 xreg[KS], areg[kLoadA ? KS : 1];
+  bf16x8 xreg[KS], areg[KS];
   {
     const u32x4* xp = reinterpret_cast<const u32x4*>(Xh + (int64_t)r_row * D + 8 * h);
     const u32x4* ap = reinterpret_cast<const u32x4*>(Ah + (int64_t)r_row * D + 8 * h);
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
       xreg[ks] = __builtin_bit_cast(bf16x8, xp[2 * ks]);
-      if constexpr (kLoadA) areg[ks] = __builtin_bit_cast(bf16x8, ap[2 * ks]);
+      areg[ks] = __builtin_bit_cast(bf16x8, ap[2 * ks]);
     }
   }
   float nl2_r = 0.f, del_r = 0.f;  // dQ passes: -L log2(e) and delta of the R row
@@ -138,224 +162,198 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
   }
 
   // ---- the T rows: the key list in LDS (dQ of a node), a run of sorted query
-  // positions read through P_Q (dK/dV of a node), or a contiguous range ----
+  // positions through P_Q, listed in LDS too (dK/dV of a node), or a contiguous range ----
   int nT, nb = 0x7fffffff;
-  const int32_t* tperm = nullptr;  // sorted passes: P_Q at T position 0
   if (MODE == kBwdDqNode) {
     nT = build_key_list<kBNT>(f, w, list, scratch, &nb);
-  } else if (MODE == kBwdDkvBlock) {
-    nT = g.b;
-    tperm = f.perm_q + w.seg_off + (int64_t)w.t * g.b;
-  } else if (MODE == kBwdDkvSamp) {
-    nT = b.chunk_len;
-    tperm = f.perm_q + w.seg_off + b.chunk_start;
+  } else if (kSorted) {
+    nT = MODE == kBwdDkvBlock ? g.b : b.chunk_len;
+    const int32_t* tperm = f.perm_q + w.seg_off + (MODE == kBwdDkvBlock ? (int64_t)w.t * g.b : (int64_t)b.chunk_start);
+    for (int i = tid; i < ((nT + 63) & ~63); i += kBNT) list[i] = tperm[min(i, nT - 1)];
+    __syncthreads();
   } else {
     nT = max(0, w.k1 - w.k0);
   }
   const int ntiles = (nT + kTT - 1) / kTT;
   const float bias2 = ((MODE == kBwdDqNode || MODE == kBwdDkvSamp) && g.m > 0) ? log2f((float)w.nr.s / (float)g.m) : 0.f;
 
-  // ---- tile movers: rows through buffer loads (out-of-range rows read as zero) ----
+  // ---- tile movers: DMA from buffer memory ----
   const uint32_t head_bytes = (uint32_t)(g.n * (D * 2));
   const __amdgpu_buffer_rsrc_t yrsrc = __builtin_amdgcn_make_buffer_rsrc((void*)Yh, 0, (int)head_bytes, 0x00020000);
   const __amdgpu_buffer_rsrc_t brsrc = __builtin_amdgcn_make_buffer_rsrc((void*)Bh, 0, (int)head_bytes, 0x00020000);
-  u32x4 yreg[NKC], breg[NKC];
+  // instruction ii of this wave fills rows RPI (4 ii + wave) ... of the tile; this lane fetches the piece of its row
+  // that belongs at its place (the row's swizzle does not depend on ii)
+  const int wave_s = __builtin_amdgcn_readfirstlane(wave);
+  const int drow = RPI * wave_s + lane / CPR;
+  const int dcol = ((lane % CPR) ^ L::swz(drow)) * 16;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)bufs + 1024 * wave_s;
   float sc_l = 0.f, sc_d = 0.f;
-  // sorted passes: the rows of the tile to be loaded next, fetched one tile ahead of its loads
-  int tix[NKC], six = 0;
-  auto fetch_rows = [&](int kt) {
+  auto request_tile = [&](int kt) {
+    const uint32_t at = lds0 + (kt & 1) * L::BUF;
 #pragma unroll
-    for (int i = 0; i < NKC; ++i) tix[i] = tperm[min(kt * kTT + (tid + i * kBNT) / CPR, nT - 1)];
-    if (tid < kTT) six = tperm[min(kt * kTT + tid, nT - 1)];
-  };
-  auto load_tile = [&](int kt) {
-#pragma unroll
-    for (int i = 0; i < NKC; ++i) {
-      const int c = tid + i * kBNT;
-      const int row = c / CPR, col = c % CPR;
-      int voff, soff;
-      if (kExact) {
-        voff = row * (D * 2) + col * 16;
-        soff = (w.k0 + kt * kTT) * (D * 2);
-      } else if (kSorted) {
-        voff = tix[i] * (D * 2) + col * 16;
-        soff = 0;
-      } else {
-        voff = list[kt * kTT + row] * (D * 2) + col * 16;
-        soff = 0;
-      }
-      yreg[i] = __builtin_amdgcn_raw_buffer_load_b128(yrsrc, voff, soff, 0);
-      breg[i] = __builtin_amdgcn_raw_buffer_load_b128(brsrc, voff, soff, 0);
+    for (int ii = 0; ii < NDMA; ++ii) {
+      const int t = kt * kTT + 4 * RPI * ii + drow;
+      const int row = kExact ? min(w.k0 + t, g.n - 1) : list[t];  // past the end: some existing row, masked
+      const int voff = row * (D * 2) + dcol;
+      dma_1k(yrsrc, at + 4096 * ii, voff);
+      dma_1k(brsrc, at + L::TILE + 4096 * ii, voff);
     }
     if (!kDq && tid < kTT) {
-      int row = kSorted ? six : min(w.k0 + kt * kTT + tid, g.n - 1);
+      const int row = kSorted ? list[kt * kTT + tid] : min(w.k0 + kt * kTT + tid, g.n - 1);
       const float lv = lse_h[row];
       sc_l = (lv == -INFINITY) ? -INFINITY : -lv * kLog2e;
       sc_d = del_h[row];
     }
-    if (kSorted && (kt + 1) * kTT < nT) fetch_rows(kt + 1);
   };
-  auto store_tile = [&](int kt) {
-    unsigned char* yb = bufs + (kt & 1) * L::BUF;
-    unsigned char* bb = yb + L::TILE;
-#pragma unroll
-    for (int i = 0; i < NKC; ++i) {
-      const int c = tid + i * kBNT;
-      const int row = c / CPR, col = c % CPR;
-      *reinterpret_cast<u32x4*>(yb + row * L::TSTR + col * 16) = yreg[i];
-      *reinterpret_cast<u32x4*>(bb + row * L::TSTR + col * 16) = breg[i];
-    }
+  auto finish_tile = [&](int kt) {  // everything requested for tile kt has landed, for the whole workgroup on return
     if (!kDq && tid < kTT) {
       float* s = sc + (kt & 1) * (2 * kTT);
       s[tid] = sc_l;
       s[kTT + tid] = sc_d;
     }
-  };
-  const int vtr_off = ((lane & 15) >> 2) * L::TSTR + ((lane & 3) * 4 + ((lane >> 4) & 1) * 16) * 2 + (4 * h) * L::TSTR;
-
-  // One pass over the T rows: accumulate, then write the wave's rows.  `what_tag` says what is
-  // accumulated (dS products or P products).
-  auto run_pass = [&](auto what_tag) {
-    constexpr bool kWantDs = (decltype(what_tag)::value == kAccDs);
-    f32x16 acc[DT];
-  #pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-  #pragma unroll
-      for (int i = 0; i < 16; ++i) acc[dt][i] = 0.f;
-
-    if (ntiles > 0) {
-      if (kSorted) fetch_rows(0);
-      load_tile(0);
-      store_tile(0);
-    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
+  };
+  // row-major fragments: piece 2 j + h of row lq (+ 32 sub); transposed: 4 rows x 16 columns per 16-lane group, lane i of
+  // a group at row i / 4, columns 4 (i % 4) ...
+  const int rd_row = lq * L::ROWB + ((h ^ L::swz(lq)) << 4);   // ^ 32 j
+  const int r4 = (lane & 15) >> 2;
+  const int rd_col = (4 * h + r4) * L::ROWB + (((((lane >> 4) & 1) * 2 + ((lane & 3) >> 1)) ^ L::swz(4 * h + r4)) << 4) +
+                     (lane & 1) * 8;                            // ^ (64 dt + 32 hi)
 
-    const int r_global = r_row;  // exact passes: for the causal mask
-    for (int kt = 0; kt < ntiles; ++kt) {
-      const bool more = kt + 1 < ntiles;
-      if (more) load_tile(kt + 1);
+  f32x16 acc1[DT], acc2[kDq ? 1 : DT];  // dQ or dK; dV
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) acc1[dt][i] = 0.f;
+#pragma unroll
+    for (int dt = 0; dt < (kDq ? 1 : DT); ++dt) acc2[dt][i] = 0.f;
+  }
+  if (ntiles > 0) {
+    request_tile(0);
+    finish_tile(0);
+  }
 
-      const unsigned char* yb = bufs + (kt & 1) * L::BUF;
-      const unsigned char* bb = yb + L::TILE;
-      const float* scb = sc + (kt & 1) * (2 * kTT);
+  const int r_global = r_row;  // exact passes: for the causal mask
+  for (int kt = 0; kt < ntiles; ++kt) {
+    const bool more = kt + 1 < ntiles;
+    if (more) request_tile(kt + 1);
 
-      // ---- P^T and dS^T ----
-      // Masks as limits on the in-tile row offset ko = koff - 4 h of an accumulator element
-      // (koff = 32 sub + 8 (i / 4) + 4 h + i % 4): masked iff ko >= hi2 (end of the T rows; keys
-      // after the query), ko < lo2 (queries before the key) or mlo2 <= ko < mhi2 (queries of
-      // the sampled key's own block, factor 1 - M of Algorithm 2).
-      const int tbase = kt * kTT;
-      int hi2 = nT - tbase - 4 * h;
-      int lo2 = -0x40000000, mlo2 = 0x40000000, mhi2 = 0x40000000, nb2 = 0x40000000;
-      float tile_bias = 0.f;
-      if (MODE == kBwdDqNode) {
-        tile_bias = (tbase >= nb) ? bias2 : 0.f;
-        if (tbase < nb) nb2 = nb - tbase - 4 * h;  // tile_bias is 0 on a tile that straddles nb
-      }
-      if (MODE == kBwdDkvSamp) {
-        tile_bias = bias2;
-        mlo2 = blk_r * g.b - (b.chunk_start + tbase) - 4 * h;
-        mhi2 = mlo2 + g.b;
-      }
-      if (MODE == kBwdDqExact && f.exact_causal) hi2 = min(hi2, r_global - w.k0 - tbase + 1 - 4 * h);
-      if (MODE == kBwdDkvExact && f.exact_causal) lo2 = r_global - w.k0 - tbase - 4 * h;
-      // highest / lowest ko of a lane: 59 / 0
-      const bool special = __any(hi2 <= 59 || lo2 > 0 || nb2 <= 59 || (mlo2 <= 59 && mhi2 > 0));
+    const unsigned char* yb = bufs + (kt & 1) * L::BUF;
+    const unsigned char* bb = yb + L::TILE;
+    const float* scb = sc + (kt & 1) * (2 * kTT);
 
-      bf16x8 bf[2];  // B operand of the accumulating product (per half): dS^T or P^T as bf16
-      // one 32-row half of the tile at a time: S^T = Y X^T and dP^T = Bt A^T, then P^T / dS^T
-  #pragma unroll
-      for (int sub = 0; sub < 2; ++sub) {
-        f32x16 cs, es;
-  #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          cs[i] = 0.f;
-          es[i] = 0.f;
-        }
-        // the wave holds issue priority over its SIMD neighbour while it issues its S^T / dP^T products (measured:
-        // dQ of the base case -9 %, its dK / dV -3 %; the short loops of the block passes lose 1-2 % and go without)
-        constexpr bool kPrio = kExact || MODE == kBwdDkvSamp;
-        if constexpr (kPrio) __builtin_amdgcn_s_setprio(1);
-        {
-          const unsigned char* yp0 = yb + (32 * sub + lq) * L::TSTR + 16 * h;
-          const unsigned char* bp0 = bb + (32 * sub + lq) * L::TSTR + 16 * h;
-  #pragma unroll
-          for (int j = 0; j < KS; ++j) {
-            cs = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(yp0 + 32 * j), xreg[j], cs, 0, 0, 0);
-            if constexpr (kWantDs)
-              es = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(bp0 + 32 * j), areg[j], es, 0, 0, 0);
-          }
-        }
-        if constexpr (kPrio) __builtin_amdgcn_s_setprio(0);
-        f32x4 nlq = {0.f, 0.f, 0.f, 0.f}, dq4 = {0.f, 0.f, 0.f, 0.f};  // -L log2(e), delta of four T rows (dK/dV passes)
-  #pragma unroll
-        for (int jj = 0; jj < 2; ++jj) {
-          u32x4 pk, dk;
-  #pragma unroll
-          for (int ee = 0; ee < 4; ++ee) {
-            // elements 8 jj + 2 ee, + 1: T rows 32 sub + 16 jj + 8 (ee / 2) + 4 h + 2 (ee % 2), + 1
-            f32x4 nlT = {0.f, 0.f, 0.f, 0.f}, dT = {0.f, 0.f, 0.f, 0.f};
-            if (!kDq && (ee % 2 == 0)) {
-              const int at = 32 * sub + 16 * jj + 8 * (ee / 2) + 4 * h;
-              nlq = *reinterpret_cast<const f32x4*>(scb + at);
-              dq4 = *reinterpret_cast<const f32x4*>(scb + kTT + at);
-            }
-            nlT = nlq;
-            dT = dq4;
-            float pv[2], dv[2];
-  #pragma unroll
-            for (int z = 0; z < 2; ++z) {
-              const int i = 8 * jj + 2 * ee + z;          // accumulator element
-              float arg;
-              float dsub;
-              if (kDq) {
-                arg = __builtin_fmaf(cs[i], kLog2e, nl2_r + tile_bias);
-                dsub = del_r;
-              } else {
-                arg = __builtin_fmaf(cs[i], kLog2e, nlT[i % 4] + tile_bias);
-                dsub = dT[i % 4];
-              }
-              if (special) {
-                const int ko = 32 * sub + 8 * (i / 4) + (i % 4);
-                if (MODE == kBwdDqNode && ko >= nb2) arg += bias2;
-                bool msk = ko >= hi2;
-                if (MODE == kBwdDkvExact) msk = msk || (ko < lo2);
-                if (MODE == kBwdDkvSamp) msk = msk || ((unsigned)(ko - mlo2) < (unsigned)g.b);
-                if (msk) arg = -INFINITY;
-              }
-              const float p = __builtin_amdgcn_exp2f(arg);
-              pv[z] = p;
-              dv[z] = p * (es[i] - dsub);
-            }
-            pk[ee] = pack_bf16x2(pv[0], pv[1]);
-            dk[ee] = pack_bf16x2(dv[0], dv[1]);
-          }
-          bf[jj] = __builtin_bit_cast(bf16x8, kWantDs ? dk : pk);
-        }
-        // ---- acc^T += Y^T dS^T  or  acc^T += Bt^T P^T  for the 32 rows of this half ----
-        {
-          typedef short s16x4 __attribute__((ext_vector_type(4)));
-          typedef short s16x8 __attribute__((ext_vector_type(8)));
-          typedef s16x4 __attribute__((address_space(3))) * lds_s16x4_ptr;
-          const unsigned char* tb = (kWantDs ? yb : bb) + vtr_off;
-  #pragma unroll
-          for (int jj = 0; jj < 2; ++jj) {
-            const int j = 2 * sub + jj;
-  #pragma unroll
-            for (int dt = 0; dt < DT; ++dt) {
-              const unsigned char* tp = tb + (16 * j) * L::TSTR + (32 * dt) * 2;
-              const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(tp));
-              const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(tp + 8 * L::TSTR));
-              const s16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-              acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, both), bf[jj], acc[dt], 0, 0, 0);
-            }
-          }
-        }
-      }
-      if (more) store_tile(kt + 1);
-      __syncthreads();
+    // ---- P^T and dS^T ----
+    // Masks as limits on the in-tile row offset ko = koff - 4 h of an accumulator element
+    // (koff = 32 sub + 8 (i / 4) + 4 h + i % 4): masked iff ko >= hi2 (end of the T rows; keys
+    // after the query), ko < lo2 (queries before the key) or mlo2 <= ko < mhi2 (queries of
+    // the sampled key's own block, factor 1 - M of Algorithm 2).
+    const int tbase = kt * kTT;
+    int hi2 = nT - tbase - 4 * h;
+    int lo2 = -0x40000000, mlo2 = 0x40000000, mhi2 = 0x40000000, nb2 = 0x40000000;
+    float tile_bias = 0.f;
+    if (MODE == kBwdDqNode) {
+      tile_bias = (tbase >= nb) ? bias2 : 0.f;
+      if (tbase < nb) nb2 = nb - tbase - 4 * h;  // tile_bias is 0 on a tile that straddles nb
     }
+    if (MODE == kBwdDkvSamp) {
+      tile_bias = bias2;
+      mlo2 = blk_r * g.b - (b.chunk_start + tbase) - 4 * h;
+      mhi2 = mlo2 + g.b;
+    }
+    if (MODE == kBwdDqExact && f.exact_causal) hi2 = min(hi2, r_global - w.k0 - tbase + 1 - 4 * h);
+    if (MODE == kBwdDkvExact && f.exact_causal) lo2 = r_global - w.k0 - tbase - 4 * h;
+    // highest / lowest ko of a lane: 59 / 0
+    const bool special = __any(hi2 <= 59 || lo2 > 0 || nb2 <= 59 || (mlo2 <= 59 && mhi2 > 0));
 
+    // one 32-row half of the tile at a time: S^T = Y X^T and dP^T = Bt A^T, then P^T / dS^T
+#pragma unroll
+    for (int sub = 0; sub < 2; ++sub) {
+      f32x16 cs, es;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        cs[i] = 0.f;
+        es[i] = 0.f;
+      }
+      // the wave holds issue priority over its SIMD neighbour while it issues its S^T / dP^T products
+      constexpr bool kPrio = kExact || MODE == kBwdDkvSamp;
+      if constexpr (kPrio) __builtin_amdgcn_s_setprio(1);
+      // the eight addresses are formed where they are used: kept across the loop they would cost eight registers
+      int rr = rd_row;
+      asm volatile("" : "+v"(rr));
+#pragma unroll
+      for (int j = 0; j < KS; ++j) {
+        const int at = (rr ^ (32 * j)) + sub * 32 * L::ROWB;
+        cs = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(yb + at), xreg[j], cs, 0, 0, 0);
+        es = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(bb + at), areg[j], es, 0, 0, 0);
+      }
+      if constexpr (kPrio) __builtin_amdgcn_s_setprio(0);
+      bf16x8 pf[2], df[2];  // B operands of the accumulating products
+#pragma unroll
+      for (int jj = 0; jj < 2; ++jj) {
+        u32x4 pk, dk;
+#pragma unroll
+        for (int e2 = 0; e2 < 2; ++e2) {
+          // elements 8 jj + 4 e2 + z: T rows 32 sub + 16 jj + 8 e2 + 4 h + z
+          f32x4 nl4 = {0.f, 0.f, 0.f, 0.f}, de4 = {0.f, 0.f, 0.f, 0.f};
+          if (!kDq) {
+            const int at = 32 * sub + 16 * jj + 8 * e2 + 4 * h;
+            nl4 = *reinterpret_cast<const f32x4*>(scb + at);
+            de4 = *reinterpret_cast<const f32x4*>(scb + kTT + at);
+          }
+          float pv[4], dv[4];
+#pragma unroll
+          for (int z = 0; z < 4; ++z) {
+            const int i = 8 * jj + 4 * e2 + z;
+            float arg = __builtin_fmaf(cs[i], kLog2e, (kDq ? nl2_r : nl4[z]) + tile_bias);
+            const float dsub = kDq ? del_r : de4[z];
+            if (special) {
+              const int ko = 32 * sub + 8 * (i / 4) + (i % 4);
+              if (MODE == kBwdDqNode && ko >= nb2) arg += bias2;
+              bool msk = ko >= hi2;
+              if (MODE == kBwdDkvExact) msk = msk || (ko < lo2);
+              if (MODE == kBwdDkvSamp) msk = msk || ((unsigned)(ko - mlo2) < (unsigned)g.b);
+              if (msk) arg = -INFINITY;
+            }
+            pv[z] = __builtin_amdgcn_exp2f(arg);
+            dv[z] = pv[z] * (es[i] - dsub);
+          }
+#pragma unroll
+          for (int z2 = 0; z2 < 2; ++z2) {
+            pk[2 * e2 + z2] = pack_bf16x2(pv[2 * z2], pv[2 * z2 + 1]);
+            dk[2 * e2 + z2] = pack_bf16x2(dv[2 * z2], dv[2 * z2 + 1]);
+          }
+        }
+        pf[jj] = __builtin_bit_cast(bf16x8, pk);
+        df[jj] = __builtin_bit_cast(bf16x8, dk);
+      }
+      // ---- acc1^T += Y^T dS^T and acc2^T += Bt^T P^T for the 32 rows of this half ----
+      typedef short s16x4 __attribute__((ext_vector_type(4)));
+      typedef short s16x8 __attribute__((ext_vector_type(8)));
+      typedef s16x4 __attribute__((address_space(3))) * lds_s16x4_ptr;
+      int rc = rd_col;
+      asm volatile("" : "+v"(rc));
+      auto column_frag = [&](const unsigned char* tile, int j, int dt) {
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(tile + (rc ^ (64 * dt)) + 16 * j * L::ROWB));
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(tile + (rc ^ (64 * dt + 32)) + (16 * j + 8) * L::ROWB));
+        return __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+      };
+#pragma unroll
+      for (int jj = 0; jj < 2; ++jj) {
+        const int j = 2 * sub + jj;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) {
+          if constexpr (!kDq) acc2[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(column_frag(bb, j, dt), pf[jj], acc2[dt], 0, 0, 0);
+          acc1[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(column_frag(yb, j, dt), df[jj], acc1[dt], 0, 0, 0);
+        }
+      }
+      if constexpr (!kDq) __builtin_amdgcn_sched_barrier(0);  // the next half's scores take this half's registers
+    }
+    if (more) finish_tile(kt + 1);
+  }
+  __syncthreads();  // the tiles are read no more
+
+  auto write_out = [&](const auto& acc, float* dst32, uint16_t* dst16, const float* lvl) {
     // ---- epilogue: the wave's 32 rows leave through an LDS transpose as whole rows.
     // Node passes write or add fp32 rows into the accumulated rows.  Exact passes (the
     // base case of Algorithm 4) write the final gradient in the tensors' dtype, after
@@ -364,15 +362,14 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
     unsigned char* ep = smem + wave * L::EP_WAVE;
     int64_t* ep_rows = reinterpret_cast<int64_t*>(ep + 32 * L::EP_ROW);
     if (h == 0) ep_rows[lq] = r_valid ? out_row : (int64_t)-1;
-  #pragma unroll
+#pragma unroll
     for (int dt = 0; dt < DT; ++dt)
-  #pragma unroll
+#pragma unroll
       for (int g4 = 0; g4 < 4; ++g4) {
         const int col = 32 * dt + 8 * g4 + 4 * h;
         const f32x4 v = {acc[dt][4 * g4], acc[dt][4 * g4 + 1], acc[dt][4 * g4 + 2], acc[dt][4 * g4 + 3]};
         *reinterpret_cast<f32x4*>(ep + lq * L::EP_ROW + col * 4) = v;
       }
-    float* dst32 = kWantDs ? a.out1 : a.out2;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -415,8 +412,6 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
       }
       return;
     }
-    uint16_t* dst16 = reinterpret_cast<uint16_t*>(kWantDs ? a.fin1 : a.fin2);
-    const float* lvl = kWantDs ? a.lvl1 : a.lvl2;
     // the 32 rows of a wave lie in one n_min block: the node passes hold all of them or none
     const int i0 = w.q0 + 32 * __builtin_amdgcn_readfirstlane(wave);
     const bool fold = lvl != nullptr && node_levels_hold(g, i0, kDq, g.levels);
@@ -451,45 +446,37 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
       if (r64[it] >= 0) *reinterpret_cast<u32x4*>(dst16 + r64[it] * D + ch * 8) = pk;
     }
   };
-  if constexpr (WHAT == kAccBoth) {
-    static_assert(WHAT != kAccBoth || !kExact, "the two-in-one form writes per-level rows only");
-    run_pass(std::integral_constant<int, kAccDs>{});
-    __syncthreads();  // the epilogue staged rows where the T tiles go
-    run_pass(std::integral_constant<int, kAccP>{});
-  } else {
-    run_pass(std::integral_constant<int, WHAT>{});
+  write_out(acc1, a.out1, reinterpret_cast<uint16_t*>(a.fin1), a.lvl1);
+  if constexpr (!kDq) {
+    // (a wave rewrites only its own staging area, which its own reads above have left)
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    write_out(acc2, a.out2, reinterpret_cast<uint16_t*>(a.fin2), a.lvl2);
   }
 }
 
-template <int D, int MODE, int WHAT>
+template <int D, int MODE>
 static int launch_bwd_one(const BwdArgs& a, int grid, hipStream_t st) {
   if (grid <= 0) return HA_OK;
-  size_t lds = bwd_lds_bytes<D>(a.f.g, MODE);
-  if (lds < (size_t)4 * BwdLds<D>::EP_WAVE) lds = (size_t)4 * BwdLds<D>::EP_WAVE;
   static std::atomic<uint64_t> lds_set{0};  // per instantiation: devices on which the LDS limit is raised
-  if (allow_full_lds(reinterpret_cast<const void*>(&attn_bwd_kernel<D, MODE, WHAT>), lds_set) != HA_OK) return HA_ERR_LAUNCH;
-  hipLaunchKernelGGL((attn_bwd_kernel<D, MODE, WHAT>), dim3((unsigned)grid), dim3(kBNT), lds, st, a);
+  if (allow_full_lds(reinterpret_cast<const void*>(&attn_bwd_kernel<D, MODE>), lds_set) != HA_OK) return HA_ERR_LAUNCH;
+  hipLaunchKernelGGL((attn_bwd_kernel<D, MODE>), dim3((unsigned)grid), dim3(kBNT), bwd_lds_bytes<D>(a, MODE), st, a);
   return check_launch();
-}
-
-// dK/dV passes: two launches, dK into out1 and dV into out2
-template <int D, int MODE>
-static int launch_bwd_pair(const BwdArgs& a, int grid, hipStream_t st) {
-  const int rc = launch_bwd_one<D, MODE, kAccDs>(a, grid, st);
-  return rc != HA_OK ? rc : launch_bwd_one<D, MODE, kAccP>(a, grid, st);
 }
 
 template <int D>
 static int launch_bwd_d(const BwdArgs& a, int mode, int grid, hipStream_t st) {
   switch (mode) {
-    case kBwdDqNode: return launch_bwd_one<D, kBwdDqNode, kAccDs>(a, grid, st);
-    case kBwdDqExact: return launch_bwd_one<D, kBwdDqExact, kAccDs>(a, grid, st);
-    case kBwdDkvBlock: return launch_bwd_one<D, kBwdDkvBlock, kAccBoth>(a, grid, st);  // short T loops: one launch, shared prologue
-    case kBwdDkvSamp: return launch_bwd_pair<D, kBwdDkvSamp>(a, grid, st);
-    case kBwdDkvExact: return launch_bwd_pair<D, kBwdDkvExact>(a, grid, st);
+    case kBwdDqNode: return launch_bwd_one<D, kBwdDqNode>(a, grid, st);
+    case kBwdDqExact: return launch_bwd_one<D, kBwdDqExact>(a, grid, st);
+    case kBwdDkvBlock: return launch_bwd_one<D, kBwdDkvBlock>(a, grid, st);
+    case kBwdDkvSamp: return launch_bwd_one<D, kBwdDkvSamp>(a, grid, st);
+    case kBwdDkvExact: return launch_bwd_one<D, kBwdDkvExact>(a, grid, st);
     default: return HA_ERR_SHAPE;
   }
 }
+
 int launch_attn_bwd_mfma(const BwdArgs& a, int mode, hipStream_t st) {
   if (a.f.g.dtype != HA_BF16) return HA_ERR_DTYPE;
   const int64_t grid64 = bwd_grid<kRT>(a, mode);

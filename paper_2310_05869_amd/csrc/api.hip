@@ -398,16 +398,8 @@ static int backward_impl(const void* Q, const void* K, const void* V, const void
   a.dO = d_out;
   a.lse = lse;
   a.delta = delta;
-  {
-    a.chunk = bwd_chunk(g);
-    int off = 0;
-    for (int l = 0; l < g.levels; ++l) {
-      a.samp_off[l] = off;
-      a.samp_row_off[l] = (int64_t)off * g.m;
-      off += g.BH * (g.causal ? (1 << l) : 1) * bwd_chunks_per_node(g, a.chunk, l);
-    }
-    a.samp_off[g.levels] = off;
-  }
+  a.chunk = bwd_chunk(g);
+  a.samp_chunks = (int32_t)bwd_sample_chunks(g, a.chunk);
 
   mark(0);
   rc = launch_bwd_delta(out, out_f32, d_out, delta, (int64_t)g.BH * g.n, g.d, g.dtype, st);

@@ -30,10 +30,14 @@
 // pass through registers.  A DMA instruction fills 1 KiB of consecutive LDS, so rows cannot be padded
 // against bank conflicts; instead the 16-byte pieces of a row are swizzled (BwdLds), which the lanes do
 // by choosing which piece of the row they fetch.
-// Measured (MI355X, 32 causal heads, n = 131072, d = 128, b = m = 256), against dK and dV in passes of their own and
-// tiles staged through registers: dK / dV of the base case 13.9 -> 10.0 ms, of the sampled keys 5.5 -> 4.1 ms, of the
-// blocks (one launch that walked the rows twice) 7.65 -> 6.25 ms, dQ of the base case 7.1 -> 6.8 ms;
-// forward + backward 50.5 -> 43.5 ms.  Results are bit-identical.
+// What bounds it: the order in which a wave issues reads, products and vector work (two waves per SIMD, 64 products
+// of 32 cycles per tile and wave in the dK / dV passes).  So that order is written out and pinned (below), the rare
+// masks sit behind a branch, and nothing in the loop waits for memory but the one wait per tile.
+// Measured (MI355X, 32 causal heads, n = 131072, d = 128, b = m = 256).  First form: dK and dV in passes of their own,
+// tiles staged through registers; second: one pass, tiles by DMA; third: this one, pinned order.
+//   dK / dV of the base case 13.9 -> 10.0 -> 8.2 ms, of the sampled keys 5.5 -> 4.1 -> 2.9 ms, of the blocks
+//   7.65 -> 6.25 -> 5.75 ms, dQ of the base case 7.1 -> 6.8 -> 6.6 ms, of the nodes 6.0 -> 5.95 -> 5.6 ms;
+//   forward + backward 50.5 -> 43.5 -> 39.3 ms.
 //
 // Sums over parts are taken in a fixed order, never by floating-point atomics: the node passes run
 // level by level and add their fp32 rows to one accumulated row per tensor row (the first level
@@ -64,7 +68,7 @@ struct BwdLds {
   static constexpr int ROWB = D * 2;
   static constexpr int TILE = kTT * ROWB;       // one tensor's tile
   static constexpr int BUF = 2 * TILE;          // y tile + bt tile
-  static constexpr int SC = 2 * kTT * 4;        // per buffer: -L log2(e) and delta of the T rows
+  static constexpr int SC = 2 * kTT * 4;        // per buffer: bias - L and -delta of the T rows
   static constexpr int EP_ROW = D * 4 + 16;
   static constexpr int EP_WAVE = 32 * EP_ROW + 256;  // rows, row ids
   __device__ static int swz(int row) {
@@ -139,11 +143,9 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
 
   // ---- this lane's R row ----
   const int r_in_tile = wave * 32 + lq;
-  const bool r_valid = r_in_tile < w.rows_valid;
-  const int r_use = r_valid ? r_in_tile : 0;
+  const int r_use = r_in_tile < w.rows_valid ? r_in_tile : 0;
   int blk_r = -1;        // sampled-key pass: sorted block of this key
   const int r_row = bwd_r_row<MODE>(a, b, r_use, &blk_r);           // row within the head
-  const int64_t out_row = bwd_out_row<MODE>(a, b, r_use, r_row);    // row in out1 / out2
   bf16x8 xreg[KS], areg[KS];
   {
     const u32x4* xp = reinterpret_cast<const u32x4*>(Xh + (int64_t)r_row * D + 8 * h);
@@ -153,6 +155,13 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
       xreg[ks] = __builtin_bit_cast(bf16x8, xp[2 * ks]);
       areg[ks] = __builtin_bit_cast(bf16x8, ap[2 * ks]);
     }
+  }
+  // (a use in registers, so that the loop does not wait for these loads again: behind the tile requests such a
+  // wait would be one for the whole next tile)
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) {
+    asm volatile("" : "+v"(xreg[ks]));
+    asm volatile("" : "+v"(areg[ks]));
   }
   float nl2_r = 0.f, del_r = 0.f;  // dQ passes: -L log2(e) and delta of the R row
   if (kDq) {
@@ -176,6 +185,7 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
   }
   const int ntiles = (nT + kTT - 1) / kTT;
   const float bias2 = ((MODE == kBwdDqNode || MODE == kBwdDkvSamp) && g.m > 0) ? log2f((float)w.nr.s / (float)g.m) : 0.f;
+  const float nat_bias = bias2 * kLn2;
 
   // ---- tile movers: DMA from buffer memory ----
   const uint32_t head_bytes = (uint32_t)(g.n * (D * 2));
@@ -189,6 +199,11 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)bufs + 1024 * wave_s;
   float sc_l = 0.f, sc_d = 0.f;
   auto request_tile = [&](int kt) {
+    if (!kDq && tid < kTT) {
+      const int row = kSorted ? list[kt * kTT + tid] : min(w.k0 + kt * kTT + tid, g.n - 1);
+      sc_l = lse_h[row];
+      sc_d = del_h[row];
+    }
     const uint32_t at = lds0 + (kt & 1) * L::BUF;
 #pragma unroll
     for (int ii = 0; ii < NDMA; ++ii) {
@@ -198,18 +213,12 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
       dma_1k(yrsrc, at + 4096 * ii, voff);
       dma_1k(brsrc, at + L::TILE + 4096 * ii, voff);
     }
-    if (!kDq && tid < kTT) {
-      const int row = kSorted ? list[kt * kTT + tid] : min(w.k0 + kt * kTT + tid, g.n - 1);
-      const float lv = lse_h[row];
-      sc_l = (lv == -INFINITY) ? -INFINITY : -lv * kLog2e;
-      sc_d = del_h[row];
-    }
   };
   auto finish_tile = [&](int kt) {  // everything requested for tile kt has landed, for the whole workgroup on return
     if (!kDq && tid < kTT) {
       float* s = sc + (kt & 1) * (2 * kTT);
-      s[tid] = sc_l;
-      s[kTT + tid] = sc_d;
+      s[tid] = (sc_l == -INFINITY) ? -INFINITY : nat_bias - sc_l;
+      s[kTT + tid] = -sc_d;
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
@@ -229,12 +238,12 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
 #pragma unroll
     for (int dt = 0; dt < (kDq ? 1 : DT); ++dt) acc2[dt][i] = 0.f;
   }
+  asm volatile("" : "+v"(nl2_r), "+v"(del_r));
   if (ntiles > 0) {
     request_tile(0);
     finish_tile(0);
   }
 
-  const int r_global = r_row;  // exact passes: for the causal mask
   for (int kt = 0; kt < ntiles; ++kt) {
     const bool more = kt + 1 < ntiles;
     if (more) request_tile(kt + 1);
@@ -248,32 +257,39 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
     // (koff = 32 sub + 8 (i / 4) + 4 h + i % 4): masked iff ko >= hi2 (end of the T rows; keys
     // after the query), ko < lo2 (queries before the key) or mlo2 <= ko < mhi2 (queries of
     // the sampled key's own block, factor 1 - M of Algorithm 2).
+    // Whether the tile has any is known from scalars, except in the sampled-key pass, whose keys differ by lane;
+    // the limits themselves are formed inside the branch, so that they hold no registers across the products.
     const int tbase = kt * kTT;
-    int hi2 = nT - tbase - 4 * h;
-    int lo2 = -0x40000000, mlo2 = 0x40000000, mhi2 = 0x40000000, nb2 = 0x40000000;
-    float tile_bias = 0.f;
-    if (MODE == kBwdDqNode) {
-      tile_bias = (tbase >= nb) ? bias2 : 0.f;
-      if (tbase < nb) nb2 = nb - tbase - 4 * h;  // tile_bias is 0 on a tile that straddles nb
-    }
+    float nl2_t = nl2_r;
+    if (MODE == kBwdDqNode && tbase >= nb) nl2_t += bias2;
+    const int r_first = w.q0 + 32 * wave_s;   // exact passes: the wave's first R row
+    bool special = tbase + kTT > nT;
+    if (MODE == kBwdDqNode) special = special || (tbase < nb && tbase + kTT > nb);
+    if (MODE == kBwdDqExact && f.exact_causal) special = special || (w.k0 + tbase + kTT - 1 > r_first);
+    if (MODE == kBwdDkvExact && f.exact_causal) special = special || (w.k0 + tbase < r_first + 31);
     if (MODE == kBwdDkvSamp) {
-      tile_bias = bias2;
-      mlo2 = blk_r * g.b - (b.chunk_start + tbase) - 4 * h;
-      mhi2 = mlo2 + g.b;
+      const int mlo = blk_r * g.b - (b.chunk_start + tbase);
+      special = special || __any(mlo < kTT && mlo + g.b > 0);
     }
-    if (MODE == kBwdDqExact && f.exact_causal) hi2 = min(hi2, r_global - w.k0 - tbase + 1 - 4 * h);
-    if (MODE == kBwdDkvExact && f.exact_causal) lo2 = r_global - w.k0 - tbase - 4 * h;
-    // highest / lowest ko of a lane: 59 / 0
-    const bool special = __any(hi2 <= 59 || lo2 > 0 || nb2 <= 59 || (mlo2 <= 59 && mhi2 > 0));
 
     // one 32-row half of the tile at a time: S^T = Y X^T and dP^T = Bt A^T, then P^T / dS^T
 #pragma unroll
     for (int sub = 0; sub < 2; ++sub) {
+      // dK / dV passes start the sums at bias - L and -delta of the T rows, straight from LDS; in the dQ passes,
+      // where these belong to the lane, they enter with the exponential and the product below
       f32x16 cs, es;
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        cs[i] = 0.f;
-        es[i] = 0.f;
+      for (int i4 = 0; i4 < 4; ++i4) {
+        f32x4 l4 = {0.f, 0.f, 0.f, 0.f}, d4 = l4;
+        if (!kDq) {
+          l4 = *reinterpret_cast<const f32x4*>(scb + 32 * sub + 8 * i4 + 4 * h);
+          d4 = *reinterpret_cast<const f32x4*>(scb + kTT + 32 * sub + 8 * i4 + 4 * h);
+        }
+#pragma unroll
+        for (int z = 0; z < 4; ++z) {
+          cs[4 * i4 + z] = l4[z];
+          es[4 * i4 + z] = d4[z];
+        }
       }
       // the wave holds issue priority over its SIMD neighbour while it issues its S^T / dP^T products
       constexpr bool kPrio = kExact || MODE == kBwdDkvSamp;
@@ -281,52 +297,54 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
       // the eight addresses are formed where they are used: kept across the loop they would cost eight registers
       int rr = rd_row;
       asm volatile("" : "+v"(rr));
+      // Fragment q of the half is piece q / 2 of the Y tile (even q) or the Bt tile (odd q).  The order is written
+      // out and pinned: kPre fragments are read ahead and every product is followed by one more read; left to
+      // itself the compiler keeps one fragment register and waits for every read in full.
+      auto row_frag = [&](int q) {
+        return *reinterpret_cast<const bf16x8*>((q & 1 ? bb : yb) + (rr ^ (32 * (q >> 1))) + sub * 32 * L::ROWB);
+      };
+      constexpr int kPre = (D == 128 && !kDq) ? 3 : 4;
+      bf16x8 fr[kPre];
 #pragma unroll
-      for (int j = 0; j < KS; ++j) {
-        const int at = (rr ^ (32 * j)) + sub * 32 * L::ROWB;
-        cs = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(yb + at), xreg[j], cs, 0, 0, 0);
-        es = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(bb + at), areg[j], es, 0, 0, 0);
+      for (int q = 0; q < kPre; ++q) fr[q] = row_frag(q);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int q = 0; q < 2 * KS; ++q) {
+        if (q & 1) es = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[q % kPre], areg[q >> 1], es, 0, 0, 0);
+        else cs = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[q % kPre], xreg[q >> 1], cs, 0, 0, 0);
+        if (q + kPre < 2 * KS) fr[q % kPre] = row_frag(q + kPre);
+        __builtin_amdgcn_sched_barrier(0);
       }
       if constexpr (kPrio) __builtin_amdgcn_s_setprio(0);
-      bf16x8 pf[2], df[2];  // B operands of the accumulating products
+      if (special) {  // rare tiles, behind a branch: folded into the weights' code the tests would double it
+        int hi2 = nT - tbase - 4 * h, lo2 = 0;
+        if (MODE == kBwdDqExact && f.exact_causal) hi2 = min(hi2, r_row - w.k0 - tbase + 1 - 4 * h);
+        if (MODE == kBwdDkvExact && f.exact_causal) lo2 = r_row - w.k0 - tbase - 4 * h;
+        const int mlo2 = blk_r * g.b - (b.chunk_start + tbase) - 4 * h;
+        const int nb2 = (tbase < nb ? nb : 0x40000000) - tbase - 4 * h;  // a tile past nb has its bias already
 #pragma unroll
-      for (int jj = 0; jj < 2; ++jj) {
-        u32x4 pk, dk;
-#pragma unroll
-        for (int e2 = 0; e2 < 2; ++e2) {
-          // elements 8 jj + 4 e2 + z: T rows 32 sub + 16 jj + 8 e2 + 4 h + z
-          f32x4 nl4 = {0.f, 0.f, 0.f, 0.f}, de4 = {0.f, 0.f, 0.f, 0.f};
-          if (!kDq) {
-            const int at = 32 * sub + 16 * jj + 8 * e2 + 4 * h;
-            nl4 = *reinterpret_cast<const f32x4*>(scb + at);
-            de4 = *reinterpret_cast<const f32x4*>(scb + kTT + at);
-          }
-          float pv[4], dv[4];
-#pragma unroll
-          for (int z = 0; z < 4; ++z) {
-            const int i = 8 * jj + 4 * e2 + z;
-            float arg = __builtin_fmaf(cs[i], kLog2e, (kDq ? nl2_r : nl4[z]) + tile_bias);
-            const float dsub = kDq ? del_r : de4[z];
-            if (special) {
-              const int ko = 32 * sub + 8 * (i / 4) + (i % 4);
-              if (MODE == kBwdDqNode && ko >= nb2) arg += bias2;
-              bool msk = ko >= hi2;
-              if (MODE == kBwdDkvExact) msk = msk || (ko < lo2);
-              if (MODE == kBwdDkvSamp) msk = msk || ((unsigned)(ko - mlo2) < (unsigned)g.b);
-              if (msk) arg = -INFINITY;
-            }
-            pv[z] = __builtin_amdgcn_exp2f(arg);
-            dv[z] = pv[z] * (es[i] - dsub);
-          }
-#pragma unroll
-          for (int z2 = 0; z2 < 2; ++z2) {
-            pk[2 * e2 + z2] = pack_bf16x2(pv[2 * z2], pv[2 * z2 + 1]);
-            dk[2 * e2 + z2] = pack_bf16x2(dv[2 * z2], dv[2 * z2 + 1]);
-          }
+        for (int i = 0; i < 16; ++i) {
+          const int ko = 32 * sub + 8 * (i / 4) + (i % 4);
+          if (MODE == kBwdDqNode && ko >= nb2) cs[i] += nat_bias;
+          bool msk = ko >= hi2;
+          if (MODE == kBwdDkvExact) msk = msk || (ko < lo2);
+          if (MODE == kBwdDkvSamp) msk = msk || ((unsigned)(ko - mlo2) < (unsigned)g.b);
+          if (msk) cs[i] = -INFINITY;
         }
-        pf[jj] = __builtin_bit_cast(bf16x8, pk);
-        df[jj] = __builtin_bit_cast(bf16x8, dk);
       }
+      // weights of elements 2 e, 2 e + 1, as bf16: the B operands of the accumulating products
+      uint32_t pw[8], dw[8];
+      auto weights = [&](int e) {
+        float pv[2], dv[2];
+#pragma unroll
+        for (int z = 0; z < 2; ++z) {
+          const int i = 2 * e + z;
+          pv[z] = __builtin_amdgcn_exp2f(kDq ? __builtin_fmaf(cs[i], kLog2e, nl2_t) : cs[i] * kLog2e);
+          dv[z] = pv[z] * (kDq ? es[i] - del_r : es[i]);
+        }
+        if (!kDq) pw[e] = pack_bf16x2(pv[0], pv[1]);
+        dw[e] = pack_bf16x2(dv[0], dv[1]);
+      };
       // ---- acc1^T += Y^T dS^T and acc2^T += Bt^T P^T for the 32 rows of this half ----
       typedef short s16x4 __attribute__((ext_vector_type(4)));
       typedef short s16x8 __attribute__((ext_vector_type(8)));
@@ -338,16 +356,46 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
         const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(tile + (rc ^ (64 * dt + 32)) + (16 * j + 8) * L::ROWB));
         return __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
       };
+      // Product q accumulates column tile dt of jj, the 16-row step of the half; again the order is pinned: weights of the first
+      // step, kPreC fragments, then per product the next fragment and, during the first step's products, a
+      // slice of the second step's weights.
+      constexpr int kPer = kDq ? DT : 2 * DT;    // products per step
+      constexpr int kAcc = 2 * kPer;
+      constexpr int kPreC = (D == 128 && !kDq) ? 3 : 4;
+      auto col_frag = [&](int q) {
+        const int jj = q / kPer, u = q % kPer;
+        return kDq ? column_frag(yb, 2 * sub + jj, u) : column_frag(u & 1 ? yb : bb, 2 * sub + jj, u >> 1);
+      };
+      bf16x8 fc[kPreC];
 #pragma unroll
-      for (int jj = 0; jj < 2; ++jj) {
-        const int j = 2 * sub + jj;
+      for (int e = 0; e < 4; ++e) {
+        if (e == (D == 128 && !kDq ? 2 : 0)) {
+          __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt) {
-          if constexpr (!kDq) acc2[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(column_frag(bb, j, dt), pf[jj], acc2[dt], 0, 0, 0);
-          acc1[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(column_frag(yb, j, dt), df[jj], acc1[dt], 0, 0, 0);
+          for (int q = 0; q < kPreC; ++q) fc[q] = col_frag(q);
         }
+        weights(e);
       }
-      if constexpr (!kDq) __builtin_amdgcn_sched_barrier(0);  // the next half's scores take this half's registers
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int q = 0; q < kAcc; ++q) {
+        const int jj = q / kPer, u = q % kPer;
+        const bf16x8 df = __builtin_bit_cast(bf16x8, (u32x4){dw[4 * jj], dw[4 * jj + 1], dw[4 * jj + 2], dw[4 * jj + 3]});
+        if constexpr (kDq) {
+          acc1[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fc[q % kPreC], df, acc1[u], 0, 0, 0);
+        } else {
+          const bf16x8 pf = __builtin_bit_cast(bf16x8, (u32x4){pw[4 * jj], pw[4 * jj + 1], pw[4 * jj + 2], pw[4 * jj + 3]});
+          if (u & 1) acc1[u >> 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fc[q % kPreC], df, acc1[u >> 1], 0, 0, 0);
+          else acc2[u >> 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fc[q % kPreC], pf, acc2[u >> 1], 0, 0, 0);
+        }
+        if (q + kPreC == kPer) asm volatile("" : "+v"(rc));  // the second step forms its addresses anew, as above
+        if (q + kPreC < kAcc) fc[q % kPreC] = col_frag(q + kPreC);
+        if (q < kPer) {
+#pragma unroll
+          for (int e = 4 + 4 * q / kPer; e < 4 + 4 * (q + 1) / kPer; ++e) weights(e);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
     if (more) finish_tile(kt + 1);
   }
@@ -361,7 +409,11 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
     // side (queries: second half of the node; keys: first half).
     unsigned char* ep = smem + wave * L::EP_WAVE;
     int64_t* ep_rows = reinterpret_cast<int64_t*>(ep + 32 * L::EP_ROW);
-    if (h == 0) ep_rows[lq] = r_valid ? out_row : (int64_t)-1;
+    if (h == 0) {  // (the row's index is fetched again: kept across the loop it would cost registers)
+      int r = wave * 32 + lq, blk;
+      asm volatile("" : "+v"(r));
+      ep_rows[lq] = r < w.rows_valid ? bwd_out_row<MODE>(a, b, r, bwd_r_row<MODE>(a, b, r, &blk)) : (int64_t)-1;
+    }
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
 #pragma unroll

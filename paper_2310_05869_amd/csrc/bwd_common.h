@@ -34,11 +34,10 @@ struct BwdArgs {
   void* fin2;
   const float* lvl1;
   const float* lvl2;
-  // sampled-key pass: sorted query positions per workgroup, first (head, node, query chunk) and first
-  // output row of every level
+  // sampled-key pass: sorted query positions per workgroup, and (head, node, query chunk) triples over all
+  // levels, level after level; a triple owns m consecutive output rows
   int32_t chunk;
-  int32_t samp_off[kBwdMaxLevels + 1];
-  int64_t samp_row_off[kBwdMaxLevels];
+  int32_t samp_chunks;
 };
 
 // Whether row i of a head lies, at some level l in [0, upto), on the given side of its level-l node of
@@ -115,20 +114,17 @@ __device__ inline BwdWork decode_bwd_work(const BwdArgs& a, int idx) {
     const int spn = (g.m + QT - 1) / QT;              // sample slabs per node
     const int slab = idx % spn;
     const int cidx = idx / spn;
-    // (static indices only: a dynamically indexed kernel-argument array would be copied to scratch)
-    int level = 0, first = 0;
-    int64_t srow0 = 0;
-#pragma unroll
-    for (int l = 0; l < kBwdMaxLevels; ++l)
-      if (l < g.levels && cidx >= a.samp_off[l]) {
-        level = l;
-        first = a.samp_off[l];
-        srow0 = a.samp_row_off[l];
-      }
-    const int cpn = bwd_chunks_per_node(g, a.chunk, level);
+    int level = 0, left = cidx, cpn;
+    for (;;) {
+      cpn = bwd_chunks_per_node(g, a.chunk, level);
+      const int here = g.BH * (g.causal ? (1 << level) : 1) * cpn;
+      if (left < here || level + 1 >= g.levels) break;
+      left -= here;
+      ++level;
+    }
     const int nodes = g.causal ? (1 << level) : 1;
-    const int qc = (cidx - first) % cpn;
-    const int hn = (cidx - first) / cpn;               // (head, node)
+    const int qc = left % cpn;
+    const int hn = left / cpn;                         // (head, node)
     const int node = hn % nodes;
     b.w.bh = hn / nodes;
     b.w.level = level;
@@ -138,7 +134,7 @@ __device__ inline BwdWork decode_bwd_work(const BwdArgs& a, int idx) {
     b.chunk_len = min(a.chunk, b.w.nr.s - b.chunk_start);
     b.samp0 = slab * QT;
     b.w.rows_valid = min(QT, g.m - b.samp0);
-    b.samp_row0 = srow0 + (int64_t)(cidx - first) * g.m;
+    b.samp_row0 = (int64_t)cidx * g.m;
   }
   return b;
 }
@@ -170,7 +166,7 @@ inline int64_t bwd_grid(const BwdArgs& a, int mode) {
   const Geometry& g = a.f.g;
   if (mode == kBwdDqNode || mode == kBwdDkvBlock) return g.levels > 0 ? node_grid<QT>(g) / g.levels : 0;
   if (mode == kBwdDqExact || mode == kBwdDkvExact) return exact_grid<QT>(a.f);
-  return (int64_t)a.samp_off[g.levels] * ((g.m + QT - 1) / QT);
+  return (int64_t)a.samp_chunks * ((g.m + QT - 1) / QT);
 }
 
 int launch_attn_bwd_mfma(const BwdArgs& a, int mode, hipStream_t st);  // bf16 tensors

@@ -119,10 +119,8 @@ __global__ __launch_bounds__(64 * kScatterWaves) void bwd_sample_scatter_kernel(
   const NodeRef nr = node_ref(g, level, node);
   const int cpn = bwd_chunks_per_node(g, a.chunk, level);
   const int64_t key_row0 = (int64_t)bh * g.n + nr.k_start;  // the node's first key in the accumulated rows
-  int64_t lvl_row0 = 0;
-#pragma unroll
-  for (int l = 0; l < kBwdMaxLevels; ++l)
-    if (l == level) lvl_row0 = a.samp_row_off[l];
+  int64_t lvl_row0 = 0;  // rows of the levels before
+  for (int l = 0; l < level; ++l) lvl_row0 += (int64_t)g.BH * (g.causal ? (1 << l) : 1) * bwd_chunks_per_node(g, a.chunk, l) * m;
   const int64_t row0 = lvl_row0 + ((int64_t)bh * nodes + node) * cpn * m;
 
   for (int j = threadIdx.x; j < m; j += blockDim.x) keys[j] = a.f.samples[(int64_t)heap * m + j];

@@ -66,7 +66,7 @@ __global__ __launch_bounds__(kFBT, D == 64 ? 2 : 1) void attn_bwd_f32_kernel(Bwd
   int32_t* list = scratch + 16;
 
   // ---- which part of the problem this workgroup owns ----
-  BwdWork b = decode_bwd_work<kRT, MODE>(a, logical_block(blockIdx.x, gridDim.x));
+  BwdWork b = decode_bwd_work<kRT, MODE>(a, kExact ? (int)blockIdx.x : logical_block(blockIdx.x, gridDim.x));
   const TileWork& w = b.w;
 
   const int64_t hs = f.q_bh_stride;

@@ -66,20 +66,69 @@ __host__ __device__ inline int64_t node_grid(const Geometry& g) {
   return (int64_t)g.levels * g.BH * (g.n_cov / g.b) * tpb;
 }
 
+// Order of an exact launch's workgroups.  Causal tiles differ in length up to (tiles per block)-fold, and a launch
+// that fits the chip at once (two or three workgroups per CU) is placed before any of them has finished: workgroup i
+// goes to XCD i mod 8 and, within it, to its 32 CUs in turn, so what a CU gets is fixed by the order.
+//
+// Launches of up to 256 tiles per XCD (in whole blocks): heaviest tiles first ACROSS the blocks, block b on XCD
+// b mod 8 where there are 8 or more (its K and V stay in one L2); every second round of 32 tiles of an XCD runs
+// backwards, so the CU (and the shader engine) that got the heaviest tile of one round gets the lightest of the next.
+// Block after block, the order before, gave a CU the same rank of several blocks: 186 key tiles on the fullest CU
+// against 99 on average at 24 blocks of 32 tiles.  Measured (MI355X): forward, 12 heads, n = 8192, d = 64: 141 ->
+// 119 us (122 with every round forwards); forward + backward: fp32, 4 heads, n = 4096: 336 -> 283 (305) us;
+// exact, 12 heads, n = 5000, d = 128: 530 -> 408 (437) us.
+//
+// Larger launches, where workgroups are replaced as they finish: every XCD takes a contiguous range, block after
+// block, heaviest first, the starting tile rotated from one block to the next: an XCD's workgroups are dealt to its
+// four shader engines in turn, and a fixed order would hand one of them every fourth, the heaviest, tile of
+// every block.  The order above, in groups of 64 tiles per XCD, is 0.8 % slower there (forward, 32 heads, n = 131072,
+// d = 128: 9.14 against 9.22 ms; 9.31 with 256): more blocks in flight than an L2 holds.
+struct ExactPlace {
+  int bh, blk;
+  int rank;  // tile within the block, heaviest first
+};
+
+constexpr int kOrderRound = 32;   // CUs of an XCD
+constexpr int kOrderWhole = 256;  // tiles per XCD ordered as one
+
 template <int QT>
-__device__ inline TileWork decode_exact_tile(const AttnArgs& a, int idx) {
-  TileWork w{};
+__device__ inline ExactPlace exact_place(const AttnArgs& a, int wg) {
   const int eb = a.exact_block;
   const int tpb = (eb + QT - 1) / QT;
   const int nblk = (a.exact_rows_q + eb - 1) / eb;
-  // Heavy (late) causal tiles first, and the starting tile rotated from one block to the next: the
-  // workgroups of an XCD are dealt to its four shader engines in turn (workgroup i to engine i mod 4,
-  // whatever their load), so a fixed order would hand one engine every fourth tile, the heaviest
-  // ones, of every block (36 against 30 key tiles on average at 32 tiles per block).
-  const int rest = idx / tpb;
-  const int qt = tpb - 1 - (idx % tpb + rest) % tpb;
-  const int blk = rest % nblk;
-  w.bh = rest / nblk;
+  const int blocks = nblk * a.g.BH;
+  ExactPlace e;
+  int b;
+  if (blocks > 8 * ((kOrderWhole + tpb - 1) / tpb)) {
+    const int idx = logical_block(wg, blocks * tpb);
+    b = idx / tpb;
+    e.rank = (idx % tpb + b) % tpb;
+  } else {
+    const int xcd = wg & 7, j = wg >> 3;
+    const int round = j / kOrderRound;
+    int p = wg;
+    if (round & 1) {
+      const int left = ((blocks * tpb - xcd + 7) >> 3) - round * kOrderRound;  // the XCD's tiles from this round on
+      const int cnt = left < kOrderRound ? left : kOrderRound;
+      p = (2 * round * kOrderRound + cnt - 1 - j) * 8 + xcd;
+    }
+    e.rank = p / blocks;
+    b = p % blocks;
+  }
+  e.blk = b % nblk;
+  e.bh = b / nblk;
+  return e;
+}
+
+template <int QT>
+__device__ inline TileWork decode_exact_tile(const AttnArgs& a, int wg) {
+  TileWork w{};
+  const int eb = a.exact_block;
+  const int tpb = (eb + QT - 1) / QT;
+  const ExactPlace e = exact_place<QT>(a, wg);
+  const int qt = tpb - 1 - e.rank;
+  const int blk = e.blk;
+  w.bh = e.bh;
   w.q0 = blk * eb + qt * QT;
   const int blk_rows = min(eb, a.exact_rows_q - blk * eb);
   w.rows_valid = max(0, min(QT, blk_rows - qt * QT));

@@ -63,7 +63,7 @@ __global__ __launch_bounds__(kFNT, D == 64 ? 3 : 2) void attn_f32_kernel(AttnArg
   int32_t* scratch = reinterpret_cast<int32_t*>(smem);
   int32_t* list = scratch + 16;
 
-  const int bid = logical_block(blockIdx.x, gridDim.x);
+  const int bid = MODE == kModeNode ? logical_block(blockIdx.x, gridDim.x) : (int)blockIdx.x;
   TileWork w;
   int nb, nkeys;
   if (MODE == kModeNode) {

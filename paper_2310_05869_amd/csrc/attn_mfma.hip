@@ -108,7 +108,7 @@ __global__ __launch_bounds__(64 * NW, (D == 64 && NW == 4) ? 3 : 2) void attn_mf
   if constexpr (STAMPS) stamp_w = (long long)wall_clock64();
   stamp(0);
 
-  const int bid = logical_block(blockIdx.x, gridDim.x);
+  const int bid = MODE == kModeNode ? logical_block(blockIdx.x, gridDim.x) : (int)blockIdx.x;
   TileWork w;
   if (MODE == kModeNode) w = decode_node_tile<kQT>(a, bid);
   else w = decode_exact_tile<kQT>(a, bid);

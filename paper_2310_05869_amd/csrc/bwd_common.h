@@ -97,14 +97,12 @@ __device__ inline BwdWork decode_bwd_work(const BwdArgs& a, int idx) {
   } else if (MODE == kBwdDqExact) {
     b.w = decode_exact_tile<QT>(f, idx);
   } else if (MODE == kBwdDkvExact) {
-    // key tiles of the diagonal blocks; early key tiles see the most queries
+    // key tiles of the diagonal blocks
     const int eb = f.exact_block;
-    const int tpb = (eb + QT - 1) / QT;
-    const int nblk = (f.exact_rows_q + eb - 1) / eb;
-    const int rest = idx / tpb;
-    const int ktile = (idx % tpb + rest) % tpb;  // starting tile rotated per block: see decode_exact_tile
-    const int blk = rest % nblk;
-    b.w.bh = rest / nblk;
+    const ExactPlace e = exact_place<QT>(f, idx);
+    const int ktile = e.rank;  // early key tiles see the most queries
+    const int blk = e.blk;
+    b.w.bh = e.bh;
     b.w.q0 = blk * eb + ktile * QT;  // first KEY row of this tile
     const int blk_rows = min(eb, f.exact_rows_q - blk * eb);
     b.w.rows_valid = max(0, min(QT, blk_rows - ktile * QT));

@@ -344,3 +344,37 @@ def test_forward_and_backward_on_random_small_problems(ha, torch, d, n, n_min, b
     ref_out, ref_lse, absv = run_oracle(Q, K, V, cfg, flip=flips or None, with_absv=True)
     assert_close(to_host(out), ref_out, "bf16", "out", absv, 0.005 if (0 < m < 16 or causal) else 1e-5)
     assert_lse_close(to_host(lse), ref_lse, "bf16", "lse")
+
+
+@pytest.mark.parametrize("dtype,d,H,n", [("bf16", 64, 33, 130),     # part of a round
+                                         ("bf16", 64, 256, 1000),   # the most tiles of the one order: every second round of 32 backwards
+                                         ("bf16", 64, 257, 1000),   # the fewest of the other
+                                         ("bf16", 128, 101, 300),   # a partial round backwards
+                                         ("bf16", 128, 3, 2500), ("bf16", 64, 1, 100),
+                                         ("fp32", 64, 9, 1000), ("fp32", 128, 70, 300)])
+def test_every_tile_of_a_causal_launch_runs_once(ha, torch, dtype, d, H, n):
+    """The order of an exact launch's tiles is a permutation of them: outputs
+    start as NaN, and every head is compared with fp32 attention and its gradients.  Criterion per head: the module's
+    Frobenius bounds (a missing or foreign tile of 128 rows moves a head by tens of percent)."""
+    print(f"tile order {dtype} d={d} H={H} n={n}", flush=True)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(H * n)
+    q, k, v, g = ((torch.randn((1, H, n, d), generator=gen, device="cuda") * d ** -0.25).to(dt) for _ in range(4))
+    out = torch.full_like(q, float("nan"))
+    lse = torch.full((1, H, n), float("nan"), device="cuda")
+    grads = tuple(torch.full_like(q, float("nan")) for _ in range(3))
+    out32 = torch.full(q.shape, float("nan"), device="cuda") if dtype == "bf16" else None
+    ha.exact_attn_forward(q, k, v, causal=True, out=out, lse=lse, out_f32=out32)
+    ha.exact_attn_backward(q, k, v, out, lse, g, causal=True, grads=grads, out_f32=out32)
+    qf, kf, vf = (x[0].float().requires_grad_() for x in (q, k, v))
+    s = torch.bmm(qf, kf.transpose(1, 2).contiguous())
+    s = s.masked_fill(torch.ones(n, n, dtype=torch.bool, device="cuda").triu(1), float("-inf"))
+    ref = torch.bmm(s.softmax(-1), vf)
+    ref.backward(g[0].float())
+    tol = FRO_TOL if dtype == "bf16" else FRO_TOL_FP32
+    assert torch.allclose(lse[0], s.detach().logsumexp(-1), atol=1e-3 if dtype == "bf16" else 2e-5)
+    for name, got, want in zip(("out", "dQ", "dK", "dV"), (out, *grads), (ref.detach(), qf.grad, kf.grad, vf.grad)):
+        diff = (got[0].float() - want).flatten(1).norm(dim=1) / want.flatten(1).norm(dim=1)
+        print(f"  {name}: worst head {diff.max().item():.2e}", flush=True)
+        assert (diff <= tol).all(), name

@@ -4,9 +4,9 @@
 //
 // Launch sequence of hyperattn_forward (Algorithm 3 in its Section 4 form;
 // Algorithm 4 when causal):
-//   prep        R and the per-node sample indices into the workspace
-//   lsh_hash    x2 (Q, K): one pass over all rows; the causal recursion reuses
-//               the same codes at every node (same hyperplanes everywhere)
+//   lsh_hash    one pass over all rows of Q and K; the causal recursion reuses
+//               the same codes at every node (same hyperplanes everywhere); also
+//               stores R and the per-node sample indices in the workspace
 //   seg_sort    all nodes of all levels, Q and K, in one launch
 //   attention   all nodes of all levels in one launch (block part + sampled
 //               residual, shared normaliser); unmasked problem: final output;
@@ -31,6 +31,7 @@
 #include "ha_common.h"
 #include "alg2_common.h"
 #include "bwd_common.h"
+#include "hash_common.h"
 
 namespace ha {
 
@@ -137,6 +138,29 @@ static uint16_t projection_bits(uint64_t seed, int c, int k) {
   return (uint16_t)(bits >> 16);
 }
 
+// Hashes the rows of Q and K and stores the call's draws (R, sample indices) in the workspace, in one launch.
+static int run_hash(const void* Q, const void* K, uint8_t* codes_q, uint8_t* codes_k, const Geometry& g, uint64_t seed,
+                    const float* R_dev, const int32_t* samples_dev, float* proj, int32_t* samples, hipStream_t st) {
+  HashArgs a{};
+  a.X[0] = Q;
+  a.X[1] = K;
+  a.codes[0] = codes_q;
+  a.codes[1] = codes_k;
+  a.rows = (int64_t)g.BH * g.n;
+  a.R = R_dev;
+  a.r = g.r;
+  a.store_draws = 1;
+  a.R_ws = proj;
+  a.samples_ws = samples;
+  a.samples_dev = samples_dev;
+  a.g = g;
+  a.seed = seed;
+  if (!R_dev)
+    for (int k = 0; k < g.r; ++k)
+      for (int c = 0; c < g.d; ++c) a.Rb[k][c] = projection_bits(seed, c, k);
+  return launch_lsh_hash(a, g.d, g.dtype, st);
+}
+
 static bool use_mfma(const Geometry& g) { return g.dtype == HA_BF16; }
 
 // ---------------------------------------------------------------------------
@@ -205,7 +229,7 @@ static int run_base_case(const void* Q, const void* K, const void* V, void* out,
 }
 
 // ev, when non-null, receives 6 events recorded on the stream: start, after
-// prep, after hashing, after sorting, after the node attention, after the base case.
+// again (draws: part of the hashing launch), after hashing, after sorting, after the node attention, after the base case.
 // node_stamps / base_stamps, when non-null, select the measuring instantiation of the
 // node launch / the base-case launch and receive its workgroups' stamp records.
 static int forward_impl(const void* Q, const void* K, const void* V, void* out, float* lse, const ha_shape* sh,
@@ -242,16 +266,8 @@ static int forward_impl(const void* Q, const void* K, const void* V, void* out, 
 
   mark(0);
   if (g.levels > 0) {
-    uint16_t Rb[1024];
-    if (!R_dev)
-      for (int c = 0; c < g.d; ++c)
-        for (int k = 0; k < g.r; ++k) Rb[c * g.r + k] = projection_bits(p->seed, c, k);
-    rc = launch_prep(proj, R_dev, R_dev ? nullptr : Rb, samples, samples_dev, g, p->seed, st);
-    if (rc != HA_OK) return rc;
     mark(1);
-    rc = launch_lsh_hash(Q, codes_q, (int64_t)g.BH * g.n, g.d, g.dtype, proj, g.r, st);
-    if (rc != HA_OK) return rc;
-    rc = launch_lsh_hash(K, codes_k, (int64_t)g.BH * g.n, g.d, g.dtype, proj, g.r, st);
+    rc = run_hash(Q, K, codes_q, codes_k, g, p->seed, R_dev, samples_dev, proj, samples, st);
     if (rc != HA_OK) return rc;
     mark(2);
     rc = launch_seg_sort_nodes(codes_q, codes_k, perm_q, perm_k, pos_k, g.m > 0 ? samples : nullptr, samp_blk,
@@ -671,7 +687,13 @@ int ha_lsh_hash(const void* X, uint8_t* codes, int64_t rows, int32_t d, int32_t 
   if (rows == 0) return HA_OK;
   if (!X || !codes || !R_dev) return HA_ERR_NULL;
   if (any_misaligned16(X) || any_misaligned4(R_dev)) return HA_ERR_ALIGN;
-  return launch_lsh_hash(X, codes, rows, d, dtype, R_dev, r, (hipStream_t)stream);
+  HashArgs a{};
+  a.X[0] = X;
+  a.codes[0] = codes;
+  a.rows = rows;
+  a.R = R_dev;
+  a.r = r;
+  return launch_lsh_hash(a, d, dtype, (hipStream_t)stream);
 }
 
 int ha_seg_sort(const uint8_t* codes, int32_t* perm, int32_t* pos, int32_t n_seg, int32_t seg_len,
@@ -898,18 +920,11 @@ int hyperattn_forward_alg2(const void* Q, const void* K, const void* V, void* ou
   float* part_l = (float*)(base + lay.part_l);
   if (g.levels > 0) {
     // hash, sort and draws exactly as the forward does them
-    uint16_t Rb[1024];
-    for (int c = 0; c < g.d; ++c)
-      for (int k = 0; k < g.r; ++k) Rb[c * g.r + k] = projection_bits(params->seed, c, k);
     float* proj = (float*)(base + lay.proj);
     int32_t* samples = (int32_t*)(base + lay.samples);
-    rc = launch_prep(proj, nullptr, Rb, samples, nullptr, g, params->seed, st);
-    if (rc != HA_OK) return rc;
     uint8_t* codes_q = base + lay.codes_q;
     uint8_t* codes_k = base + lay.codes_k;
-    rc = launch_lsh_hash(Q, codes_q, (int64_t)g.BH * g.n, g.d, g.dtype, proj, g.r, st);
-    if (rc != HA_OK) return rc;
-    rc = launch_lsh_hash(K, codes_k, (int64_t)g.BH * g.n, g.d, g.dtype, proj, g.r, st);
+    rc = run_hash(Q, K, codes_q, codes_k, g, params->seed, nullptr, nullptr, proj, samples, st);
     if (rc != HA_OK) return rc;
     rc = launch_seg_sort_nodes(codes_q, codes_k, (int32_t*)(base + lay.perm_q), (int32_t*)(base + lay.perm_k),
                                (int32_t*)(base + lay.pos_k), g.m > 0 ? samples : nullptr,

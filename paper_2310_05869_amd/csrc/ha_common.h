@@ -119,18 +119,12 @@ struct AttnArgs {
 constexpr int kStampWords = HA_STAMP_WORDS;
 
 // launchers (defined in the .hip files)
-int launch_lsh_hash(const void* X, uint8_t* codes, int64_t rows, int d, int dtype, const float* R_dev,
-                    int r, hipStream_t st);
-int launch_lsh_hash_mfma(const void* X, uint8_t* codes, int64_t rows, int d, const float* R_dev, int r,
-                         hipStream_t st);
 int launch_seg_sort_nodes(const uint8_t* codes_q, const uint8_t* codes_k, int32_t* perm_q, int32_t* perm_k,
                           int32_t* pos_k, const int32_t* samples, int32_t* samp_blk, uint32_t* chunk_hist,
                           const Geometry& g, hipStream_t st);
 int64_t seg_sort_chunks(const Geometry& g);  // rows of 256 counters the chunked sort needs
 int launch_seg_sort_flat(const uint8_t* codes, int32_t* perm, int32_t* pos, int n_seg, int seg_len,
                          hipStream_t st);
-int launch_prep(float* R_ws, const float* R_dev, const uint16_t* R_bf16_host, int32_t* samples_ws,
-                const int32_t* samples_dev, const Geometry& g, uint64_t seed, hipStream_t st);
 int launch_attn_mfma(const AttnArgs& a, int mode, hipStream_t st);
 int64_t attn_mfma_grid(const AttnArgs& a, int mode);  // workgroups of the four-wave launch of that mode
 int launch_attn_f32(const AttnArgs& a, int mode, hipStream_t st);

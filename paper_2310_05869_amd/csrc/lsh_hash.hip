@@ -1,4 +1,4 @@
-// sortLSH hashing (Definition 1 of the paper; Algorithm 1, "hash rows of Q, K").
+// sortLSH hashing of fp32 rows (Definition 1 of the paper; Algorithm 1, "hash rows of Q, K").
 //
 // code(x) = Gray-sequence position of the word whose bit k is [<x, R[:,k]> > 0].
 //
@@ -11,39 +11,14 @@
 // each exchange halves the number of values a lane carries, so 8 values cost 8
 // exchanges instead of 8*log2(LPR).
 //
-// Accumulation is fp64: inputs are bf16 or fp32 and R is fp32, so every product
+// Accumulation is fp64: inputs and R are fp32, so every product
 // is exact in fp64 and the sum carries a relative error of about d * 2^-53.  A
 // sign can therefore differ from an infinitely precise evaluation only for
 // projections that are zero to ~1e-13, which keeps bucket codes reproducible
 // against any fp64 reference.
-#include "ha_common.h"
+#include "hash_common.h"
 
 namespace ha {
-
-template <typename T>
-struct Elem;
-template <>
-struct Elem<uint16_t> {  // bf16 bit patterns
-  static constexpr int kPerLane = 8;
-  __device__ static void unpack(const uint4& raw, double* x) {
-    const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      x[2 * i] = (double)__uint_as_float(w[i] << 16);
-      x[2 * i + 1] = (double)__uint_as_float(w[i] & 0xFFFF0000u);
-    }
-  }
-};
-template <>
-struct Elem<float> {
-  static constexpr int kPerLane = 4;
-  __device__ static void unpack(const uint4& raw, double* x) {
-    x[0] = (double)__uint_as_float(raw.x);
-    x[1] = (double)__uint_as_float(raw.y);
-    x[2] = (double)__uint_as_float(raw.z);
-    x[3] = (double)__uint_as_float(raw.w);
-  }
-};
 
 // Sum v[k] over the LPR lanes of a row; lane l ends with projection (l / (LPR/8)) & 7.
 template <int LPR>
@@ -74,11 +49,10 @@ __device__ inline double reduce_transposed(const double* v, int l) {
   return w;
 }
 
-template <typename T, int D>
-__global__ __launch_bounds__(256) void lsh_hash_kernel(const T* __restrict__ X, uint8_t* __restrict__ codes,
-                                                        int64_t rows, const float* __restrict__ R, int r) {
-  constexpr int EPL = Elem<T>::kPerLane;
-  constexpr int LPR = D / EPL;   // lanes per row: 8, 16 or 32
+template <int D>
+__global__ __launch_bounds__(256) void lsh_hash_kernel(HashArgs a) {
+  constexpr int EPL = 4;
+  constexpr int LPR = D / EPL;   // lanes per row: 16 or 32
   constexpr int RPW = 64 / LPR;  // rows per wave and load
   constexpr int W3 = LPR / 8;
   constexpr int U = 4;           // loads in flight per lane
@@ -86,31 +60,46 @@ __global__ __launch_bounds__(256) void lsh_hash_kernel(const T* __restrict__ X, 
   const int l = lane % LPR;
   const int jrow = lane / LPR;
   const int c0 = l * EPL;
+  const int r = a.r;
 
   double Rr[EPL][8];
 #pragma unroll
-  for (int e = 0; e < EPL; ++e)
+  for (int k = 0; k < 8; ++k) {
+    if (a.R) {
 #pragma unroll
-    for (int k = 0; k < 8; ++k) Rr[e][k] = (k < r) ? (double)R[(c0 + e) * r + k] : 0.0;
+      for (int e = 0; e < EPL; ++e) Rr[e][k] = (k < r) ? (double)a.R[(c0 + e) * r + k] : 0.0;
+    } else {
+      const uint2 b = *reinterpret_cast<const uint2*>(&a.Rb[k][c0]);
+      Rr[0][k] = (double)__uint_as_float(b.x << 16);
+      Rr[1][k] = (double)__uint_as_float(b.x & 0xFFFF0000u);
+      Rr[2][k] = (double)__uint_as_float(b.y << 16);
+      Rr[3][k] = (double)__uint_as_float(b.y & 0xFFFF0000u);
+    }
+  }
+  if (a.store_draws) store_draws(a);
 
   const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
-  const int64_t ngroups = (rows + RPW - 1) / RPW;
+  const int64_t gpt = (a.rows + RPW - 1) / RPW;  // groups per tensor
+  const int64_t ngroups = a.X[1] ? 2 * gpt : gpt;
 
   for (int64_t g0 = wave; g0 < ngroups; g0 += nwaves * U) {
     uint4 raw[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int64_t row = (g0 + u * nwaves) * RPW + jrow;
+      const int64_t g = g0 + u * nwaves;
+      const int t = g >= gpt;
+      const int64_t row = (g - t * gpt) * RPW + jrow;
       raw[u] = make_uint4(0, 0, 0, 0);
-      if (row < rows) raw[u] = *reinterpret_cast<const uint4*>(X + row * D + c0);
+      if (g < ngroups && row < a.rows)
+        raw[u] = *reinterpret_cast<const uint4*>(reinterpret_cast<const float*>(t ? a.X[1] : a.X[0]) + row * D + c0);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int64_t grp = g0 + u * nwaves;
       if (grp >= ngroups) break;  // wave-uniform
-      double x[EPL];
-      Elem<T>::unpack(raw[u], x);
+      const double x[EPL] = {(double)__uint_as_float(raw[u].x), (double)__uint_as_float(raw[u].y),
+                             (double)__uint_as_float(raw[u].z), (double)__uint_as_float(raw[u].w)};
       double acc[8];
 #pragma unroll
       for (int k = 0; k < 8; ++k) acc[k] = 0.0;
@@ -121,8 +110,9 @@ __global__ __launch_bounds__(256) void lsh_hash_kernel(const T* __restrict__ X, 
       const double p = reduce_transposed<LPR>(acc, l);
       const unsigned long long bal = __ballot(p > 0.0);  // 0 and NaN give bit 0
       if (l == 0) {
-        const int64_t row = grp * RPW + jrow;
-        if (row < rows) {
+        const int t = grp >= gpt;
+        const int64_t row = (grp - t * gpt) * RPW + jrow;
+        if (row < a.rows) {
           const uint32_t rowbits = (uint32_t)(bal >> (jrow * LPR));
           uint32_t word = 0;
           for (int k = 0; k < r; ++k) word |= ((rowbits >> (k * W3)) & 1u) << k;
@@ -131,32 +121,27 @@ __global__ __launch_bounds__(256) void lsh_hash_kernel(const T* __restrict__ X, 
           idx ^= idx >> 1;
           idx ^= idx >> 2;
           idx ^= idx >> 4;
-          codes[row] = (uint8_t)idx;
+          (t ? a.codes[1] : a.codes[0])[row] = (uint8_t)idx;
         }
       }
     }
   }
 }
 
-int launch_lsh_hash(const void* X, uint8_t* codes, int64_t rows, int d, int dtype, const float* R_dev, int r,
-                    hipStream_t st) {
-  if (rows <= 0) return HA_OK;
-  if (dtype == HA_BF16) return launch_lsh_hash_mfma(X, codes, rows, d, R_dev, r, st);  // matrix-core path
-  const int esz = dtype == HA_BF16 ? 2 : 4;
-  const int rpw = 64 / (d * esz / 16);
-  const int64_t ngroups = (rows + rpw - 1) / rpw;
-  int64_t blocks = (ngroups + 4 * 4 - 1) / (4 * 4);  // 4 waves per block, 4 groups per wave and trip
+int launch_lsh_hash(const HashArgs& a, int d, int dtype, hipStream_t st) {
+  if (a.rows <= 0) return HA_OK;
+  if (dtype == HA_BF16) return launch_lsh_hash_mfma(a, d, st);  // matrix-core path
+  const int rpw = 256 / d;
+  const int64_t ngroups = (a.rows + rpw - 1) / rpw * (a.X[1] ? 2 : 1);
+  // one group per wave while that leaves the chip four waves per SIMD, then up to the four of a trip
+  int64_t blocks = (ngroups + 3) / 4;
+  if (blocks > 1024) blocks = (ngroups + 15) / 16 > 1024 ? (ngroups + 15) / 16 : 1024;
   if (blocks > 4096) blocks = 4096;
-  if (blocks < 1) blocks = 1;
   dim3 grid((unsigned)blocks), block(256);
-  if (dtype == HA_BF16 && d == 128)
-    hipLaunchKernelGGL((lsh_hash_kernel<uint16_t, 128>), grid, block, 0, st, (const uint16_t*)X, codes, rows, R_dev, r);
-  else if (dtype == HA_BF16 && d == 64)
-    hipLaunchKernelGGL((lsh_hash_kernel<uint16_t, 64>), grid, block, 0, st, (const uint16_t*)X, codes, rows, R_dev, r);
-  else if (dtype == HA_FP32 && d == 128)
-    hipLaunchKernelGGL((lsh_hash_kernel<float, 128>), grid, block, 0, st, (const float*)X, codes, rows, R_dev, r);
-  else if (dtype == HA_FP32 && d == 64)
-    hipLaunchKernelGGL((lsh_hash_kernel<float, 64>), grid, block, 0, st, (const float*)X, codes, rows, R_dev, r);
+  if (d == 128)
+    hipLaunchKernelGGL((lsh_hash_kernel<128>), grid, block, 0, st, a);
+  else if (d == 64)
+    hipLaunchKernelGGL((lsh_hash_kernel<64>), grid, block, 0, st, a);
   else
     return HA_ERR_SHAPE;
   return check_launch();

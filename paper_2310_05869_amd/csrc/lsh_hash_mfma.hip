@@ -21,7 +21,7 @@
 //
 // If R holds values that are not bf16-representable (caller-supplied
 // hyperplanes), every row takes the fp64 path.
-#include "ha_common.h"
+#include "hash_common.h"
 
 namespace ha {
 
@@ -40,32 +40,60 @@ __device__ inline uint32_t scale_bf16x2_down14(uint32_t v) {
   return lo2 | (hi2 << 16);
 }
 
-template <int D>
-__global__ __launch_bounds__(256) void lsh_hash_mfma_kernel(const uint16_t* __restrict__ X,
-                                                             uint8_t* __restrict__ codes, int64_t rows,
-                                                             const float* __restrict__ R, int r) {
+// ARGS: R comes in the arguments (bf16 values by construction), else from a.R.
+template <int D, bool ARGS>
+__global__ __launch_bounds__(256) void lsh_hash_mfma_kernel(HashArgs a) {
   constexpr int KS = D / 16;
   constexpr int EL = D / 64;  // elements per lane on the fp64 path
   const int lane = threadIdx.x & 63;
   const int n = lane & 31, h = lane >> 5;
+  const int r = a.r;
+  const int64_t rows = a.rows;
+  const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+  const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
+  const int64_t gpt = (rows + 31) / 32;  // groups of 32 rows per tensor
+  const int64_t ngroups = a.X[1] ? 2 * gpt : gpt;
+
+  auto load_group = [&](int64_t g, u32x4 (&xa)[KS]) {
+    const bool second = g >= gpt;
+    const uint16_t* X = reinterpret_cast<const uint16_t*>(second ? a.X[1] : a.X[0]);
+    int64_t lrow = (second ? g - gpt : g) * 32 + n;
+    if (lrow >= rows) lrow = rows - 1;
+    const u32x4* xp = reinterpret_cast<const u32x4*>(X + lrow * D + 8 * h);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) xa[ks] = xp[2 * ks];
+  };
+  // the rows of the next two trips are in flight while the current one is
+  // processed; three register sets rotate so nothing is copied
+  u32x4 xa[KS], xb[KS], xc[KS];
+  int64_t g = wave;
+  if (g < ngroups) {
+    load_group(g, xa);
+    load_group(g + nwaves < ngroups ? g + nwaves : g, xb);
+  }
 
   // matrix operands R^T and |R|^T as bf16: projection n (zero for n >= r)
   u32x4 rb[KS], rabs[KS];
   bool exact = true;
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) {
-    uint32_t pk[4];
+    if constexpr (ARGS) {
+      rb[ks] = (u32x4){0, 0, 0, 0};
+      if (n < 8) rb[ks] = *reinterpret_cast<const u32x4*>(&a.Rb[n][16 * ks + 8 * h]);
+    } else {
+      uint32_t pk[4];
 #pragma unroll
-    for (int e2 = 0; e2 < 4; ++e2) {
-      uint32_t lo = 0, hi = 0;
-      if (n < r) {
-        lo = __float_as_uint(R[(16 * ks + 8 * h + 2 * e2) * r + n]);
-        hi = __float_as_uint(R[(16 * ks + 8 * h + 2 * e2 + 1) * r + n]);
+      for (int e2 = 0; e2 < 4; ++e2) {
+        uint32_t lo = 0, hi = 0;
+        if (n < r) {
+          lo = __float_as_uint(a.R[(16 * ks + 8 * h + 2 * e2) * r + n]);
+          hi = __float_as_uint(a.R[(16 * ks + 8 * h + 2 * e2 + 1) * r + n]);
+        }
+        exact = exact && ((lo & 0xFFFFu) == 0) && ((hi & 0xFFFFu) == 0);
+        pk[e2] = (lo >> 16) | (hi & 0xFFFF0000u);
       }
-      exact = exact && ((lo & 0xFFFFu) == 0) && ((hi & 0xFFFFu) == 0);
-      pk[e2] = (lo >> 16) | (hi & 0xFFFF0000u);
+      rb[ks] = (u32x4){pk[0], pk[1], pk[2], pk[3]};
     }
-    rb[ks] = (u32x4){pk[0], pk[1], pk[2], pk[3]};
     rabs[ks] = rb[ks] & 0x7FFF7FFFu;
   }
   // |R| * 2^-14, so that the second MFMA chain yields the doubt threshold itself
@@ -74,30 +102,25 @@ __global__ __launch_bounds__(256) void lsh_hash_mfma_kernel(const uint16_t* __re
   for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
     for (int e = 0; e < 4; ++e) rabs[ks][e] = scale_bf16x2_down14(rabs[ks][e]);
-  const bool all_exact = __all(exact);
+  const bool all_exact = ARGS || __all(exact);
 
   // for the fp64 path: R in fp32, eight columns per row (zero beyond r), and one
   // row of X per wave
   __shared__ __attribute__((aligned(16))) float Rs[D * 8];
   __shared__ __attribute__((aligned(16))) uint16_t xrow[4][D];
   const int wv = threadIdx.x >> 6;
-  for (int i = threadIdx.x; i < D * 8; i += blockDim.x) Rs[i] = (i % 8) < r ? R[(i / 8) * r + (i % 8)] : 0.f;
+  for (int i = threadIdx.x; i < D * 8; i += blockDim.x) {
+    const int c = ARGS ? i % D : i / 8, k = ARGS ? i / D : i % 8;
+    if constexpr (ARGS) Rs[c * 8 + k] = __uint_as_float((uint32_t)a.Rb[k][c] << 16);
+    else Rs[i] = k < r ? a.R[c * r + k] : 0.f;
+  }
+  if (a.store_draws) store_draws(a);
   __syncthreads();
 
-  const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
-  const int64_t ngroups = (rows + 31) / 32;
-
-  auto load_group = [&](int64_t g, u32x4 (&xa)[KS]) {
-    int64_t lrow = g * 32 + n;
-    if (lrow >= rows) lrow = rows - 1;
-    const u32x4* xp = reinterpret_cast<const u32x4*>(X + lrow * D + 8 * h);
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) xa[ks] = xp[2 * ks];
-  };
   const uint32_t mask_r = (1u << r) - 1u;
   auto trip = [&](int64_t g, u32x4 (&xa)[KS], u32x4 (&xn)[KS]) {
-    const int64_t row0 = g * 32;
+    const bool second = g >= gpt;
+    const int64_t row0 = (second ? g - gpt : g) * 32;
     // unconditional (past the end: this trip's own rows again, a cache hit), so
     // the count of loads in flight is the same on every path and the waits
     // before the MFMAs below leave the two younger groups in flight
@@ -200,16 +223,9 @@ __global__ __launch_bounds__(256) void lsh_hash_mfma_kernel(const uint16_t* __re
       idx ^= idx >> 1;
       idx ^= idx >> 2;
       idx ^= idx >> 4;
-      codes[row0 + lane] = (uint8_t)idx;
+      (second ? a.codes[1] : a.codes[0])[row0 + lane] = (uint8_t)idx;
     }
   };
-  // the rows of the next two trips are in flight while the current one is
-  // processed; three register sets rotate so nothing is copied
-  u32x4 xa[KS], xb[KS], xc[KS];
-  int64_t g = wave;
-  if (g >= ngroups) return;
-  load_group(g, xa);
-  load_group(g + nwaves < ngroups ? g + nwaves : g, xb);
   while (g < ngroups) {
     trip(g, xa, xc);
     g += nwaves;
@@ -228,19 +244,21 @@ __global__ __launch_bounds__(256) void lsh_hash_mfma_kernel(const uint16_t* __re
 // resident-sized grid (two 4-wave blocks per CU): every wave streams many 32-row groups
 constexpr int kHashBlocks = HA_HASH_BLOCKS;
 
-int launch_lsh_hash_mfma(const void* X, uint8_t* codes, int64_t rows, int d, const float* R_dev, int r,
-                         hipStream_t st) {
-  if (rows <= 0) return HA_OK;
-  const int64_t ngroups = (rows + 31) / 32;
+template <int D>
+static void launch_d(const HashArgs& a, dim3 grid, hipStream_t st) {
+  if (a.R) hipLaunchKernelGGL((lsh_hash_mfma_kernel<D, false>), grid, dim3(256), 0, st, a);
+  else hipLaunchKernelGGL((lsh_hash_mfma_kernel<D, true>), grid, dim3(256), 0, st, a);
+}
+
+int launch_lsh_hash_mfma(const HashArgs& a, int d, hipStream_t st) {
+  if (a.rows <= 0) return HA_OK;
+  const int64_t ngroups = (a.rows + 31) / 32 * (a.X[1] ? 2 : 1);
   int64_t blocks = (ngroups + 3) / 4;
   if (blocks > kHashBlocks) blocks = kHashBlocks;
-  dim3 grid((unsigned)blocks), block(256);
-  if (d == 128)
-    hipLaunchKernelGGL((lsh_hash_mfma_kernel<128>), grid, block, 0, st, (const uint16_t*)X, codes, rows, R_dev, r);
-  else if (d == 64)
-    hipLaunchKernelGGL((lsh_hash_mfma_kernel<64>), grid, block, 0, st, (const uint16_t*)X, codes, rows, R_dev, r);
-  else
-    return HA_ERR_SHAPE;
+  const dim3 grid((unsigned)blocks);
+  if (d == 128) launch_d<128>(a, grid, st);
+  else if (d == 64) launch_d<64>(a, grid, st);
+  else return HA_ERR_SHAPE;
   return check_launch();
 }
 

@@ -1,8 +1,4 @@
 // Small streaming kernels around the attention kernels:
-//   prep            puts the call's random draws into the workspace: the
-//                   hyperplane matrix R (Definition 1) and the per-node sample
-//                   indices l_1..l_m (Algorithm 2), either derived from the
-//                   seed or copied from caller-supplied device arrays
 //   gather_rows     the row permutation of Section 4 ("permuting n rows") as a
 //                   stage of its own
 //   merge_unpermute Algorithm 2's last step (row sum = block part + estimate)
@@ -13,56 +9,6 @@
 #include "ha_common.h"
 
 namespace ha {
-
-struct PrepArgs {
-  float* R_ws;
-  const float* R_dev;
-  int32_t* samples_ws;
-  const int32_t* samples_dev;
-  Geometry g;
-  uint64_t seed;
-  uint16_t Rb[1024];  // seed-derived R as bf16 bit patterns, [c*r + k]
-};
-
-__global__ __launch_bounds__(256) void prep_kernel(PrepArgs a) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int nR = a.g.d * a.g.r;
-  if (i < nR) a.R_ws[i] = a.R_dev ? a.R_dev[i] : __uint_as_float((uint32_t)a.Rb[i] << 16);
-  const int64_t nS = (int64_t)a.g.total_nodes * a.g.m;
-  if (i < nS && a.g.levels > 0) {
-    const int heap = (int)(i / a.g.m);
-    const int j = (int)(i % a.g.m);
-    const int level = 31 - __clz(heap + 1);
-    const int node = heap + 1 - (1 << level);
-    const NodeRef nr = node_ref(a.g, level, node);
-    int32_t v;
-    if (a.samples_dev) {
-      v = a.samples_dev[i];
-      v = v < 0 ? 0 : (v >= nr.s ? nr.s - 1 : v);  // never index outside the node
-    } else {
-      v = sample_index(a.seed, level, node, nr.s, j);
-    }
-    a.samples_ws[i] = v;
-  }
-}
-
-int launch_prep(float* R_ws, const float* R_dev, const uint16_t* R_bf16_host, int32_t* samples_ws,
-                const int32_t* samples_dev, const Geometry& g, uint64_t seed, hipStream_t st) {
-  PrepArgs a{};
-  a.R_ws = R_ws;
-  a.R_dev = R_dev;
-  a.samples_ws = samples_ws;
-  a.samples_dev = samples_dev;
-  a.g = g;
-  a.seed = seed;
-  if (R_bf16_host)
-    for (int i = 0; i < g.d * g.r; ++i) a.Rb[i] = R_bf16_host[i];
-  int64_t work = (int64_t)g.total_nodes * g.m;
-  if (work < g.d * g.r) work = g.d * g.r;
-  dim3 grid((unsigned)((work + 255) / 256)), block(256);
-  hipLaunchKernelGGL(prep_kernel, grid, block, 0, st, a);
-  return check_launch();
-}
 
 // ---------------------------------------------------------------------------
 // 16 bytes per lane; a row of `chunks` 16-byte pieces is read and written by

@@ -16,7 +16,8 @@
 //
 // Long segments (the upper levels of the causal recursion have 64 segments of
 // 65536 keys) would leave most of the chip idle, so the forward pass sorts in
-// chunks of kChunk keys, one 4-wave workgroup each, in two launches:
+// chunks of kChunk keys, one 4-wave workgroup each, in two launches (small problems: in B alone, see
+// kOneLaunchChunks):
 //   A. every chunk's bucket counts go to a table in the workspace;
 //   B. every chunk finds where its buckets start (buckets before it in the
 //      segment + the same bucket in earlier chunks), ranks its keys and
@@ -54,6 +55,14 @@ struct SortArgs {
   uint32_t* chunk_hist;    // [chunks][256]
   int32_t lvl_wg[kSortMaxLevels + 1];
 };
+
+// One launch, in which a chunk's workgroup (16 waves, a quarter of the walk) counts the segment's other chunks itself,
+// where pass A is only latency: while every chunk finds a CU of its own and a segment has few chunks to read.
+// Forward call (MI355X, d = 64, b = m = 256), two launches -> one: 12 heads, n = 4096 36.4 -> 32.7 us; 4 heads,
+// n = 8192 (2 chunks) 31.0 -> 27.6; 12 heads, 16384 (4) 66.6 -> 64.3; 8 heads, 32768 (8) 81.0 -> 80.4; one
+// head, 65536 (16) 38.8 -> 39.5; 131072 (32) 53.8 -> 59.6.
+constexpr int kOneLaunchChunks = 256;
+constexpr int kOneLaunchLongest = 8;
 
 constexpr int kFlatWaves = 16;   // whole-segment mode: one workgroup has to cover a long segment
 constexpr int kChunkWaves = 4;   // chunked mode: many small workgroups per CU hide each other's barriers
@@ -166,6 +175,8 @@ struct ChunkRef {
   const uint8_t* codes;  // the chunk's keys
   int32_t* perm;         // the segment's permutation (destinations are segment-wide)
   int32_t* pos;          // the chunk's slice of pos_k, or null (queries)
+  const uint8_t* seg_codes;  // the segment's keys
+  int32_t seg_len;
   const uint32_t* seg_hist;  // bucket counts of the segment's chunks [nchunks][256]
   uint32_t* own_hist;        // this chunk's row of that table
   const int32_t* smp;    // key chunks with samples: the node's sample indices ...
@@ -198,6 +209,8 @@ __device__ inline ChunkRef decode_chunk(const SortArgs& a, int wg) {
   c.s = min(kChunk, nr.s - c.chunk_off);
   c.value_base = (which ? nr.k_start : nr.q_start) + c.chunk_off;
   c.codes = (which ? a.codes_k : a.codes_q) + (int64_t)bh * a.g.n + c.value_base;
+  c.seg_codes = c.codes - c.chunk_off;
+  c.seg_len = nr.s;
   const int64_t off = ((int64_t)level * a.g.BH + bh) * a.g.n_cov + (int64_t)node * nr.s;
   c.perm = (which ? a.perm_k : a.perm_q) + off;
   c.pos = which ? a.pos_k + off + c.chunk_off : nullptr;
@@ -242,25 +255,29 @@ __global__ __launch_bounds__(kChunkWaves * 64) void chunk_count_kernel(SortArgs 
   c.own_hist[tid] = hist[tid];
 }
 
-constexpr int kTilesPerWave = kChunk / 64 / kChunkWaves;
-
 // LDS of pass B: the chunk's order (kChunk words, whose first quarter holds the keys
 // until they are in registers), wave totals, and per (wave, bucket) a 64-bit peer
-// mask (later the pair {first place, shift to the destination}) and a counter.
-__host__ __device__ inline size_t chunk_scatter_lds(int nbk) {
-  return (size_t)kChunk * 4 + 64 + (size_t)kChunkWaves * nbk * 12;
+// mask (later the pair {first place, shift to the destination}) and a counter; COUNT: the buckets' keys in earlier
+// and in later chunks.
+__host__ __device__ inline size_t chunk_scatter_lds(int nbk, int waves, bool count) {
+  return (size_t)kChunk * 4 + 64 + (size_t)waves * nbk * 12 + (count ? 2 * 256 * 4 : 0);
 }
 
 // Pass B.  nbk = number of buckets (a power of two >= every code + 1, at most 256).
-__global__ __launch_bounds__(kChunkWaves * 64) void chunk_scatter_kernel(SortArgs a, int nbk) {
+// COUNT: no pass A; the workgroup reads the segment's other chunks and counts their keys itself.
+template <int NW, bool COUNT>
+__global__ __launch_bounds__(NW * 64) void chunk_scatter_kernel(SortArgs a, int nbk) {
   extern __shared__ __attribute__((aligned(16))) unsigned char sm[];
   typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  constexpr int kChunkWaves = NW;
+  constexpr int kTilesPerWave = kChunk / 64 / NW;
   uint32_t* staged = reinterpret_cast<uint32_t*>(sm);
   const uint8_t* codes_lds = sm;
-  uint32_t* wave_tot = staged + kChunk;  // [2][kChunkWaves]
-  unsigned long long* peers = reinterpret_cast<unsigned long long*>(wave_tot + 16);  // [kChunkWaves][nbk]
+  uint32_t* wave_tot = staged + kChunk;  // [2][4]
+  unsigned long long* peers = reinterpret_cast<unsigned long long*>(wave_tot + 16);  // [NW][nbk]
   u32x2* first = reinterpret_cast<u32x2*>(peers);                                    // the same words, after the ranking
-  uint32_t* count = reinterpret_cast<uint32_t*>(peers + kChunkWaves * nbk);          // [kChunkWaves][nbk]
+  uint32_t* count = reinterpret_cast<uint32_t*>(peers + kChunkWaves * nbk);          // [NW][nbk]
+  uint32_t* others = count + kChunkWaves * nbk;                                      // COUNT: [2][256]
 
   const ChunkRef c = decode_chunk(a, (int)blockIdx.x);
   const int tid = threadIdx.x;
@@ -269,7 +286,7 @@ __global__ __launch_bounds__(kChunkWaves * 64) void chunk_scatter_kernel(SortArg
 
   // the bucket's keys in earlier chunks of the segment, and in the whole segment
   uint32_t before = 0, all = 0;
-  if (tid < nbk) {
+  if (!COUNT && tid < nbk) {
     for (int c0 = 0; c0 < c.nchunks; c0 += 8) {
       uint32_t v[8];
 #pragma unroll
@@ -282,14 +299,30 @@ __global__ __launch_bounds__(kChunkWaves * 64) void chunk_scatter_kernel(SortArg
     }
   }
   {
-    const u32x4 v = load_16_codes(c.codes, s, tid);
-    *reinterpret_cast<u32x4*>(sm + 16 * tid) = v;
+    if (tid < kChunk / 16) {
+      const u32x4 v = load_16_codes(c.codes, s, tid);
+      *reinterpret_cast<u32x4*>(sm + 16 * tid) = v;
+    }
+    if (COUNT && tid < 512) others[tid] = 0u;
     for (int i = tid; i < kChunkWaves * nbk; i += kChunkWaves * 64) {
       peers[i] = 0ull;
       count[i] = 0u;
     }
   }
   __syncthreads();
+  if constexpr (COUNT) {
+    static_assert(NW * 64 >= 512, "one thread per counter");
+    for (int u = tid; u < c.nchunks * (kChunk / 16); u += NW * 64) {
+      const int cc = u / (kChunk / 16), t = u % (kChunk / 16);
+      if (cc == c.chunk) continue;
+      const int left = min(kChunk, c.seg_len - cc * kChunk);
+      const u32x4 v = load_16_codes(c.seg_codes + cc * kChunk, left, t);
+      uint32_t* hist = others + (cc < c.chunk ? 0 : 256);
+#pragma unroll
+      for (int j = 0; j < 16; ++j)
+        if (16 * t + j < left) atomicAdd(&hist[(v[j >> 2] >> (8 * (j & 3))) & 255u], 1u);
+    }
+  }
 
   // Wave w ranks tiles [w kTilesPerWave, (w + 1) kTilesPerWave) of the chunk, in order:
   // a key's place among the wave's keys of its bucket = keys of the bucket in the wave's
@@ -336,6 +369,10 @@ __global__ __launch_bounds__(kChunkWaves * 64) void chunk_scatter_kernel(SortArg
       cnt_w[ww] = count[ww * nbk + tid];
       mine += cnt_w[ww];
     }
+    if constexpr (COUNT) {
+      before = others[tid];
+      all = before + mine + others[256 + tid];
+    }
   }
   uint32_t inc_l = mine, inc_g = all;  // contributions of tid >= nbk are zero
 #pragma unroll
@@ -346,18 +383,18 @@ __global__ __launch_bounds__(kChunkWaves * 64) void chunk_scatter_kernel(SortArg
       inc_g += ug;
     }
   }
-  if (lane == 63) {
+  if (lane == 63 && w < 4) {  // (at most 256 buckets: four waves hold them)
     wave_tot[w] = inc_l;
-    wave_tot[kChunkWaves + w] = inc_g;
+    wave_tot[4 + w] = inc_g;
   }
   __syncthreads();
   if (tid < nbk) {
     uint32_t lb = inc_l - mine, gb = inc_g - all + before;
 #pragma unroll
-    for (int ww = 0; ww < kChunkWaves; ++ww)
+    for (int ww = 0; ww < 4; ++ww)
       if (ww < w) {
         lb += wave_tot[ww];
-        gb += wave_tot[kChunkWaves + ww];
+        gb += wave_tot[4 + ww];
       }
     const uint32_t shift = gb - lb;  // destination in the segment = place in the chunk + shift (mod 2^32)
 #pragma unroll
@@ -434,8 +471,13 @@ int launch_seg_sort_nodes(const uint8_t* codes_q, const uint8_t* codes_k, int32_
   a.lvl_wg[g.levels] = (int32_t)wg;
   const int nbk = 1 << g.r;  // bucket codes of Definition 1 are below 2^r
   dim3 grid((unsigned)wg), block(kChunkWaves * 64);
+  const int longest = ((g.causal ? g.n >> 1 : g.n) + kChunk - 1) / kChunk;  // chunks of the longest segment
+  if (wg <= kOneLaunchChunks && longest <= kOneLaunchLongest) {
+    hipLaunchKernelGGL((chunk_scatter_kernel<16, true>), grid, dim3(16 * 64), chunk_scatter_lds(nbk, 16, true), st, a, nbk);
+    return check_launch();
+  }
   hipLaunchKernelGGL(chunk_count_kernel, grid, block, 0, st, a);
-  hipLaunchKernelGGL(chunk_scatter_kernel, grid, block, chunk_scatter_lds(nbk), st, a, nbk);
+  hipLaunchKernelGGL((chunk_scatter_kernel<kChunkWaves, false>), grid, block, chunk_scatter_lds(nbk, kChunkWaves, false), st, a, nbk);
   return check_launch();
 }
 

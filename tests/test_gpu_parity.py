@@ -701,3 +701,39 @@ def test_forward_on_random_small_problems(ha, torch, dtype, d, n, n_min, b, m, r
     cfg = dict(B=1, H=2, n=n, d=d, dtype=dtype, law="iid", b=b, m=m, r=r, causal=causal, n_min=n_min, seed=3 * n + m)
     Q, K, V = synth_inputs.make_qkv(cfg, seed=500 + n + b)
     _forward_and_compare(ha, torch, cfg, Q, K, V)
+
+
+@pytest.mark.parametrize("H,n,b,r,causal,n_min", [
+    (32, 16384, 64, 7, 0, 0), (33, 16384, 64, 7, 0, 0),   # 256 chunks: one launch; 264: two
+    (1, 32768, 256, 8, 0, 0), (1, 32769, 3, 8, 0, 0),     # segments of 8 chunks: one launch; of 9: two
+    (2, 4097, 17, 1, 0, 0), (3, 1, 1, 7, 0, 0),           # a chunk of one key, a segment of one key, two buckets
+    (1, 65536, 32, 7, 1, 1024)])                          # six levels, 8 chunks down to a quarter of one
+def test_node_sort_is_the_stable_order(ha, torch, H, n, b, r, causal, n_min):
+    """Permutations, positions and the sampled keys' blocks of a forward call against a stable sort of its codes:
+    whole numbers, exact."""
+    print(f"node sort H={H} n={n} b={b} r={r} causal={causal}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n + H)
+    Q, K, V = (torch.randn((1, H, n, 64), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(3))
+    m = 40
+    shape, params = ha.make_shape(1, H, n, 64, ha.HA_BF16), ha.make_params(b, m, r, bool(causal), n_min or 4096, 3)
+    ws = ha.alloc_workspace(shape, params)
+    ws.fill_(255)
+    ha.hyperattn_forward(Q, K, V, b, m, r, causal=bool(causal), n_min=n_min or 4096, seed=3, workspace=ws)
+    v = ha.workspace_views(ws, shape, params)
+    lay = ha.ha_workspace_layout(shape, params)
+    cq, ck = (v[x].view(H, n).long() for x in ("codes_q", "codes_k"))
+    for level in range(lay.levels):
+        nodes = 2 ** level if causal else 1
+        s = n >> (level + 1) if causal else n
+        for node in range(nodes):
+            q0, k0 = ((2 * node + 1) * s, 2 * node * s) if causal else (0, 0)
+            at = slice(node * s, (node + 1) * s)
+            pk = ck[:, k0:k0 + s].sort(dim=1, stable=True).indices
+            pos = pk.argsort(dim=1)
+            assert torch.equal(v["perm_q"][level].view(H, -1)[:, at].long(), cq[:, q0:q0 + s].sort(dim=1, stable=True).indices + q0)
+            assert torch.equal(v["perm_k"][level].view(H, -1)[:, at].long(), pk + k0)
+            assert torch.equal(v["pos_k"][level].view(H, -1)[:, at].long(), pos)
+            heap = 2 ** level - 1 + node
+            smp = v["samples"].view(-1, m)[heap].long()
+            assert torch.equal(v["samp_blk"].view(H, -1, m)[:, heap].long(), pos[:, smp] // b)

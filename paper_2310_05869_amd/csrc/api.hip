@@ -138,6 +138,51 @@ static uint16_t projection_bits(uint64_t seed, int c, int k) {
   return (uint16_t)(bits >> 16);
 }
 
+// projection_bits for all of R, hyperplane by hyperplane (row k of Rb: columns 0 .. d - 1).  A call generates R anew, on
+// the host, and the logarithm and cosine of d r entries were 18 us (d = 64, r = 7) to 33 us (d = 128) of a call whose
+// kernels take 20 us at small sizes.  A value is only needed to bf16: series good to 1e-8 give it, unless the fp32 value
+// lies within two units of a rounding boundary of bf16 (one entry in 13 000) or is zero, where projection_bits decides.
+// So the bits are projection_bits' own.  Now 6 and 11 us.
+static void make_projection_rows(uint64_t seed, int d, int r, uint16_t (*Rb)[128]) {
+  const uint64_t gold = 0x9E3779B97F4A7C15ull;
+  const uint64_t key = mix64(seed + gold * (kStreamProjection + 1));  // rand_u64's, once for the stream
+  for (int k = 0; k < r; ++k) {
+    double u1[128], u2[128];
+    float z[128];
+    for (int c = 0; c < d; ++c) {
+      const uint64_t ctr = 2ull * (8ull * (uint64_t)c + (uint64_t)k);
+      u1[c] = ((double)(int64_t)(mix64(key + gold * (ctr + 1)) >> 11) + 0.5) * 0x1.0p-53;
+      u2[c] = ((double)(int64_t)(mix64(key + gold * (ctr + 2)) >> 11) + 0.5) * 0x1.0p-53;
+    }
+    for (int c = 0; c < d; ++c) {  // no branch and no call: two entries per instruction
+      // ln u1 = e ln 2 + 2 atanh(f), u1 = 2^e m, m in [sqrt(1/2), sqrt(2)), |f| < 0.172; u1 > 0 and e > -64
+      uint64_t ub;
+      std::memcpy(&ub, &u1[c], 8);
+      const uint64_t e64 = (ub - 0x3FE6A09E667F3BCDull + (64ull << 52)) >> 52;  // e + 64
+      uint64_t eb = e64 | 0x4330000000000000ull;                               // 2^52 + e + 64 as a double
+      double e, m;
+      std::memcpy(&e, &eb, 8);
+      e -= 0x1.0p52 + 64.0;
+      ub -= (e64 - 64) << 52;
+      std::memcpy(&m, &ub, 8);
+      const double f = (m - 1.0) / (m + 1.0), f2 = f * f;
+      const double ln_m = 2.0 * f * (1.0 + f2 * (1.0 / 3 + f2 * (1.0 / 5 + f2 * (1.0 / 7 + f2 * (1.0 / 9 + f2 * (1.0 / 11))))));
+      // cos(2 pi u2) = sin(x), x = 2 pi (|u2 - 1/2| - 1/4), |x| <= pi / 2
+      const double x = 2.0 * M_PI * (__builtin_fabs(u2[c] - 0.5) - 0.25), x2 = x * x;
+      const double sn = x * (1.0 + x2 * (-1.0 / 6 + x2 * (1.0 / 120 + x2 * (-1.0 / 5040 + x2 * (1.0 / 362880 +
+                        x2 * (-1.0 / 39916800 + x2 * (1.0 / 6227020800.0)))))));
+      z[c] = (float)(__builtin_elementwise_sqrt(-2.0 * (e * M_LN2 + ln_m)) * sn);
+    }
+    for (int c = 0; c < d; ++c) {
+      uint32_t bits;
+      std::memcpy(&bits, &z[c], 4);
+      const uint32_t low = bits & 0xFFFFu;
+      const bool certain = (low < 0x7FFEu || low > 0x8002u) && (bits & 0x7F800000u) != 0;
+      Rb[k][c] = certain ? (uint16_t)((bits + 0x7FFFu + ((bits >> 16) & 1u)) >> 16) : projection_bits(seed, c, k);
+    }
+  }
+}
+
 // Hashes the rows of Q and K and stores the call's draws (R, sample indices) in the workspace, in one launch.
 static int run_hash(const void* Q, const void* K, uint8_t* codes_q, uint8_t* codes_k, const Geometry& g, uint64_t seed,
                     const float* R_dev, const int32_t* samples_dev, float* proj, int32_t* samples, hipStream_t st) {
@@ -155,9 +200,7 @@ static int run_hash(const void* Q, const void* K, uint8_t* codes_q, uint8_t* cod
   a.samples_dev = samples_dev;
   a.g = g;
   a.seed = seed;
-  if (!R_dev)
-    for (int k = 0; k < g.r; ++k)
-      for (int c = 0; c < g.d; ++c) a.Rb[k][c] = projection_bits(seed, c, k);
+  if (!R_dev) make_projection_rows(seed, g.d, g.r, a.Rb);
   return launch_lsh_hash(a, g.d, g.dtype, st);
 }
 
@@ -665,9 +708,11 @@ int exact_attn_forward_train(const void* Q, const void* K, const void* V, void* 
 int ha_make_projection(uint64_t seed, int32_t d, int32_t r, float* R_host) {
   if (!R_host) return HA_ERR_NULL;
   if (d < 1 || d > 128 || r < 1 || r > 8) return HA_ERR_SHAPE;
+  uint16_t Rb[8][128];
+  make_projection_rows(seed, d, r, Rb);
   for (int c = 0; c < d; ++c)
     for (int k = 0; k < r; ++k) {
-      const uint32_t bits = (uint32_t)projection_bits(seed, c, k) << 16;
+      const uint32_t bits = (uint32_t)Rb[k][c] << 16;
       std::memcpy(&R_host[c * r + k], &bits, 4);
     }
   return HA_OK;

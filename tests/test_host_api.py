@@ -50,6 +50,14 @@ def test_projection_bit_identical_to_oracle(ha, seed, d, r):
     np.testing.assert_array_equal(R.astype(np.float64), orc.make_projection(seed, d, r))
 
 
+@pytest.mark.parametrize("first", [0, 1 << 40])
+def test_projection_series_agree_with_the_library_functions(ha, first):
+    """R is generated from series and falls back to log / cos near a rounding boundary of bf16: 32 seeds x 1024
+    entries (several boundary cases among them) hold the oracle's bits."""
+    for seed in range(first, first + 32):
+        np.testing.assert_array_equal(ha.ha_make_projection(seed, 128, 8).astype(np.float64), orc.make_projection(seed, 128, 8))
+
+
 @pytest.mark.parametrize("seed,level,node,n_keys,m", [(0, 0, 0, 32768, 256), (0, 4, 15, 4096, 256), (7, 2, 3, 1000, 33),
                                                       (1, 0, 0, 1, 5), (3, 1, 0, 2 ** 24, 512)])
 def test_samples_bit_identical_to_oracle(ha, seed, level, node, n_keys, m):

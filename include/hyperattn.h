@@ -285,10 +285,9 @@ int ha_merge_unpermute(const float* o_b, const float* lse_b, const float* o_r, c
  *
  * hyperattn_backward_timed: the same, and WAITS for the stream; stage_ms_host
  * (host, 8 floats) receives the times between events on the stream: delta, dQ
- * of the nodes, dQ of the base case (unmasked problems: conversion of the one
- * node's rows), dK/dV of the block keys, dK/dV of the sampled keys with their
- * reduction, dK/dV of the base case, conversion of dK and dV (unmasked problems
- * only; the causal base-case passes write the final tensors themselves), total.
+ * of the nodes, dQ of the base case (unmasked problems: 0), dK/dV of the block
+ * keys, dK/dV of the sampled keys with their reduction, dK/dV of the base case, 0 (the passes write the final
+ * tensors themselves), total.
  *
  * exact_attn_backward: gradients of exact_attn_forward (Section 1.1; causal:
  * Section 3.1), the denominator of the forward + backward speed-up.  workspace
@@ -296,7 +295,7 @@ int ha_merge_unpermute(const float* o_b, const float* lse_b, const float* o_r, c
 typedef struct {
   size_t delta;                      /* fp32 [B*H][n] */
   size_t acc_a, acc_b;               /* fp32 [B*H][n][d] each: the node parts' rows, added up level by level
-                                        (acc_a: dQ, afterwards dK; acc_b: dV) */
+                                        (acc_a: dQ, afterwards dK; acc_b: dV); not used by unmasked problems */
   size_t samp_k, samp_v;             /* fp32 rows of the sampled keys per (level, head, node, query chunk, sample) */
   size_t total_bytes;
 } ha_bwd_ws_layout;

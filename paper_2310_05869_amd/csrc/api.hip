@@ -25,7 +25,9 @@
 //               sampled keys of every node (partial sums per query chunk) and
 //               their ordered reduction into the same rows, level by level;
 //               then the base-case pass, which adds the rows and writes dK, dV
+// (unmasked problems: the one node's passes write the gradients; its sampled keys come before its block keys)
 #include <cmath>
+#include <utility>
 #include <cstring>
 
 #include "ha_common.h"
@@ -405,9 +407,8 @@ static void fill_bwd_layout(const Geometry& g, ha_bwd_ws_layout* l) {
   l->total_bytes = off < 256 ? 256 : off;
 }
 
-// ev, when non-null, receives 8 events: start, after delta, dQ of the nodes, dQ of the base case (unmasked
-// problems: its conversion), dK/dV of the block keys, of the sampled keys (with their reduction), of the base
-// case, after the conversion of dK and dV (unmasked problems).
+// ev, when non-null, receives 8 events: start, after delta, dQ of the nodes, dQ of the base case, dK/dV of the block keys,
+// of the sampled keys (with their reduction; unmasked problems: these two the other way round), of the base case, end.
 static int backward_impl(const void* Q, const void* K, const void* V, const void* out, const float* out_f32,
                          const float* lse, const void* d_out, void* dQ, void* dK, void* dV, const ha_shape* sh,
                          const ha_params* p,
@@ -476,18 +477,40 @@ static int backward_impl(const void* Q, const void* K, const void* V, const void
     }
     return HA_OK;
   };
+  if (!g.causal) {  // the one node is the whole result: its passes write the gradients
+    a.fin1 = dQ;
+    rc = launch_attn_bwd(a, kBwdDqNode, st);
+    if (rc != HA_OK) return rc;
+    mark(2);
+    mark(3);
+    if (g.m > 0) {
+      a.out1 = samp_k;
+      a.out2 = samp_v;
+      rc = launch_attn_bwd(a, kBwdDkvSamp, st);
+      if (rc != HA_OK) return rc;
+      rc = launch_bwd_sample_reduce(a, samp_k, samp_v, st);
+      if (rc != HA_OK) return rc;
+      a.samp1 = samp_k;
+      a.samp2 = samp_v;
+    }
+    mark(4);
+    a.fin1 = dK;
+    a.fin2 = dV;
+    rc = launch_attn_bwd(a, kBwdDkvBlock, st);
+    if (rc != HA_OK) return rc;
+    mark(5);
+    mark(6);
+    mark(7);
+    return HA_OK;
+  }
   a.out1 = acc_a;
   a.out2 = nullptr;
   rc = node_levels(kBwdDqNode);
   if (rc != HA_OK) return rc;
   mark(2);
-  if (g.causal) {
-    a.fin1 = dQ;
-    a.lvl1 = g.levels > 0 ? acc_a : nullptr;
-    rc = launch_attn_bwd(a, kBwdDqExact, st);
-  } else {  // one node, no base case: its rows are the result
-    rc = launch_bwd_convert(acc_a, dQ, g, st);
-  }
+  a.fin1 = dQ;
+  a.lvl1 = g.levels > 0 ? acc_a : nullptr;
+  rc = launch_attn_bwd(a, kBwdDqExact, st);
   if (rc != HA_OK) return rc;
   mark(3);
   a.out1 = acc_a;
@@ -506,21 +529,13 @@ static int backward_impl(const void* Q, const void* K, const void* V, const void
     }
   }
   mark(5);
-  if (g.causal) {
-    a.fin1 = dK;
-    a.fin2 = dV;
-    a.lvl1 = g.levels > 0 ? acc_a : nullptr;
-    a.lvl2 = g.levels > 0 ? acc_b : nullptr;
-    rc = launch_attn_bwd(a, kBwdDkvExact, st);
-    if (rc != HA_OK) return rc;
-  }
+  a.fin1 = dK;
+  a.fin2 = dV;
+  a.lvl1 = g.levels > 0 ? acc_a : nullptr;
+  a.lvl2 = g.levels > 0 ? acc_b : nullptr;
+  rc = launch_attn_bwd(a, kBwdDkvExact, st);
+  if (rc != HA_OK) return rc;
   mark(6);
-  if (!g.causal) {
-    rc = launch_bwd_convert(acc_a, dK, g, st);
-    if (rc != HA_OK) return rc;
-    rc = launch_bwd_convert(acc_b, dV, g, st);
-    if (rc != HA_OK) return rc;
-  }
   mark(7);
   return HA_OK;
 }
@@ -867,6 +882,7 @@ int hyperattn_backward_timed(const void* Q, const void* K, const void* V, const 
       if (hipEventElapsedTime(&stage_ms_host[i], ev[i], ev[i + 1]) != hipSuccess) rc = HA_ERR_LAUNCH;
     if (rc == HA_OK && hipEventElapsedTime(&stage_ms_host[NE - 1], ev[0], ev[NE - 1]) != hipSuccess) rc = HA_ERR_LAUNCH;
   }
+  if (ran && !g.causal) std::swap(stage_ms_host[3], stage_ms_host[4]);  // reported: block keys, then sampled keys
   for (int i = 0; i < NE; ++i) (void)hipEventDestroy(ev[i]);
   return rc;
 }

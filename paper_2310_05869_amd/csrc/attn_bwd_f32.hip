@@ -28,7 +28,6 @@
 namespace ha {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kFTT = 32;   // T rows per tile
@@ -43,16 +42,19 @@ struct F32BwdLds {
 template <int D>
 __host__ __device__ inline size_t bwd_f32_lds_bytes(const Geometry& g, int mode) {
   const size_t list = mode == kBwdDqNode ? (size_t)(((g.b + g.m + 63) & ~63) + 64) * 4 + 64 : 0;
-  return list > (size_t)F32BwdLds<D>::BYTES ? list : (size_t)F32BwdLds<D>::BYTES;
+  const size_t hits = mode == kBwdDkvBlock && !g.causal ? sample_hits_bytes(g) : 0;  // behind the rows
+  return list > (size_t)F32BwdLds<D>::BYTES ? list : (size_t)F32BwdLds<D>::BYTES + hits;
 }
 
 // d = 128 keeps up to 416 values per lane (two fragments in flight beside rows and accumulators): one wave per SIMD
-template <int D, int MODE, int KW>
+// FINAL: the node passes of an unmasked problem, which write the final gradients.
+template <int D, int MODE, int KW, bool FINAL>
 __global__ __launch_bounds__(kFBT, D == 64 ? 2 : 1) void attn_bwd_f32_kernel(BwdArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   constexpr bool kDq = (MODE == kBwdDqNode || MODE == kBwdDqExact);
   constexpr bool kExact = (MODE == kBwdDqExact || MODE == kBwdDkvExact);
   constexpr bool kSorted = (MODE == kBwdDkvBlock || MODE == kBwdDkvSamp);
+  constexpr bool kHits = FINAL && MODE == kBwdDkvBlock;  // sampled keys' sums added here
   constexpr int kRT = 32 * (4 / KW);
   constexpr int KJ = D / 8;
   constexpr int DT = D / 32;
@@ -97,6 +99,9 @@ __global__ __launch_bounds__(kFBT, D == 64 ? 2 : 1) void attn_bwd_f32_kernel(Bwd
     L_r = lse_h[r_row];
     del_r = del_h[r_row];
   }
+
+  const SampleHits sh = sample_hits(smem + F32BwdLds<D>::BYTES);
+  if (kHits) find_sample_hits<kFBT>(a, b, sh, fetch_sample_head(a, b, tid));
 
   // ---- the T rows ----
   int nT, nb = 0x7fffffff;
@@ -237,7 +242,8 @@ __global__ __launch_bounds__(kFBT, D == 64 ? 2 : 1) void attn_bwd_f32_kernel(Bwd
   // holds this row (queries: second half of the node; keys: first half) ----
   constexpr int RS = F32BwdLds<D>::ROW;
   float* rows_lds = reinterpret_cast<float*>(smem);
-  auto write_out = [&](const auto& acc, float* node_dst, float* fin, const float* lvl) {
+  const int64_t srow0 = (int64_t)w.bh * bwd_chunks_per_node(g, a.chunk, 0) * g.m;  // sample 0's sums (kHits)
+  auto write_out = [&](const auto& acc, float* node_dst, const float* samp, float* fin, const float* lvl) {
     __syncthreads();  // the key list, or the rows of the other gradient, are read no more
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
@@ -253,20 +259,37 @@ __global__ __launch_bounds__(kFBT, D == 64 ? 2 : 1) void attn_bwd_f32_kernel(Bwd
       f32x4 v = *reinterpret_cast<const f32x4*>(src);
 #pragma unroll
       for (int k = 1; k < KW; ++k) v += *reinterpret_cast<const f32x4*>(src + k * 32 * RS);
+      if (kHits && samp != nullptr) {
+        const int j = sh.first[r];
+        const f32x4 sv = *reinterpret_cast<const f32x4*>(samp + (srow0 + (j != kNoSample ? j : 0)) * D + col);
+        if (j != kNoSample) v += sv;
+        const int nm = *sh.count;
+        for (int e = 0; e < nm; ++e)
+          if (sh.more[e] >> 16 == r) v += *reinterpret_cast<const f32x4*>(samp + (srow0 + (sh.more[e] & 0xffff)) * D + col);
+      }
       int dummy;
       const int rr = bwd_r_row<MODE>(a, b, r, &dummy);
       const int64_t out_row = bwd_out_row<MODE>(a, b, r, rr);
       bool add = false;
-      if (MODE == kBwdDqNode) add = node_levels_hold(g, rr, true, w.level);
-      if (MODE == kBwdDkvBlock) add = node_levels_hold(g, rr, false, w.level);
+      if (MODE == kBwdDqNode && !FINAL) add = node_levels_hold(g, rr, true, w.level);
+      if (MODE == kBwdDkvBlock && !FINAL) add = node_levels_hold(g, rr, false, w.level);
       if (kExact) add = lvl != nullptr && node_levels_hold(g, rr, kDq, g.levels);
       const float* from = kExact ? lvl : node_dst;
       if (add) v += *reinterpret_cast<const f32x4*>(from + out_row * D + col);
-      *reinterpret_cast<f32x4*>((kExact ? fin : node_dst) + out_row * D + col) = v;
+      *reinterpret_cast<f32x4*>((kExact || FINAL ? fin : node_dst) + out_row * D + col) = v;
     }
   };
-  write_out(acc1, a.out1, reinterpret_cast<float*>(a.fin1), a.lvl1);
-  if constexpr (!kDq) write_out(acc2, a.out2, reinterpret_cast<float*>(a.fin2), a.lvl2);
+  write_out(acc1, a.out1, a.samp1, reinterpret_cast<float*>(a.fin1), a.lvl1);
+  if constexpr (!kDq) write_out(acc2, a.out2, a.samp2, reinterpret_cast<float*>(a.fin2), a.lvl2);
+}
+
+template <int D, int MODE, int KW, bool FINAL>
+static int launch_bwd_f32_form(const BwdArgs& a, int grid, hipStream_t st) {
+  const size_t lds = bwd_f32_lds_bytes<D>(a.f.g, MODE);
+  static std::atomic<uint64_t> lds_set{0};  // per instantiation: devices on which the LDS limit is raised
+  if (allow_full_lds(reinterpret_cast<const void*>(&attn_bwd_f32_kernel<D, MODE, KW, FINAL>), lds_set) != HA_OK) return HA_ERR_LAUNCH;
+  hipLaunchKernelGGL((attn_bwd_f32_kernel<D, MODE, KW, FINAL>), dim3((unsigned)grid), dim3(kFBT), lds, st, a);
+  return check_launch();
 }
 
 template <int D, int MODE, int KW>
@@ -274,11 +297,9 @@ static int launch_bwd_f32_one(const BwdArgs& a, hipStream_t st) {
   const int64_t grid = bwd_grid<32 * (4 / KW)>(a, MODE);
   if (grid <= 0) return HA_OK;
   if (grid > kMaxGrid) return HA_ERR_SHAPE;
-  const size_t lds = bwd_f32_lds_bytes<D>(a.f.g, MODE);
-  static std::atomic<uint64_t> lds_set{0};  // per instantiation: devices on which the LDS limit is raised
-  if (allow_full_lds(reinterpret_cast<const void*>(&attn_bwd_f32_kernel<D, MODE, KW>), lds_set) != HA_OK) return HA_ERR_LAUNCH;
-  hipLaunchKernelGGL((attn_bwd_f32_kernel<D, MODE, KW>), dim3((unsigned)grid), dim3(kFBT), lds, st, a);
-  return check_launch();
+  if constexpr (MODE == kBwdDqNode || MODE == kBwdDkvBlock)
+    if (!a.f.g.causal) return launch_bwd_f32_form<D, MODE, KW, true>(a, (int)grid, st);
+  return launch_bwd_f32_form<D, MODE, KW, false>(a, (int)grid, st);
 }
 
 // Waves that share a group of 32 R rows, by the rule of the forward (launch_f32_mode): few groups or short runs

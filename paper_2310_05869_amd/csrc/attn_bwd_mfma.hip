@@ -52,7 +52,6 @@ namespace ha {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kTT = 64;    // T rows per step
@@ -87,10 +86,16 @@ __host__ __device__ inline int bwd_list_capacity(const BwdArgs& a, int mode) {
   return 0;
 }
 
+// block-key pass: the workgroup's sampled keys lie behind all else, from the prologue to the end
 template <int D>
-__host__ __device__ inline size_t bwd_lds_bytes(const BwdArgs& a, int mode) {
+__host__ __device__ inline size_t bwd_hits_at(const BwdArgs& a, int mode) {
   const size_t s = 2 * (size_t)BwdLds<D>::BUF + 2 * BwdLds<D>::SC + 64 + (size_t)bwd_list_capacity(a, mode) * 4;
   return s > (size_t)4 * BwdLds<D>::EP_WAVE ? s : (size_t)4 * BwdLds<D>::EP_WAVE;
+}
+
+template <int D>
+__host__ __device__ inline size_t bwd_lds_bytes(const BwdArgs& a, int mode) {
+  return bwd_hits_at<D>(a, mode) + (mode == kBwdDkvBlock && !a.f.g.causal ? sample_hits_bytes(a.f.g) : 0);
 }
 
 // 16 bytes per lane from buffer memory to 1 KiB of LDS starting at byte lds_at (wave-uniform).  Inline assembly
@@ -101,13 +106,15 @@ __device__ inline void dma_1k(const __amdgpu_buffer_rsrc_t& rsrc, uint32_t lds_a
                : "memory");
 }
 
-template <int D, int MODE>
+// FINAL: the node passes of an unmasked problem, which write the final gradients.
+template <int D, int MODE, bool FINAL>
 __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   using L = BwdLds<D>;
   constexpr bool kDq = (MODE == kBwdDqNode || MODE == kBwdDqExact);
   constexpr bool kExact = (MODE == kBwdDqExact || MODE == kBwdDkvExact);
   constexpr bool kSorted = (MODE == kBwdDkvBlock || MODE == kBwdDkvSamp);  // T rows = a run of sorted query positions
+  constexpr bool kHits = FINAL && MODE == kBwdDkvBlock;  // sampled keys' sums added here
   constexpr int KS = D / 16;
   constexpr int DT = D / 32;
   constexpr int CPR = D / 8;                 // 16-byte pieces per row
@@ -146,6 +153,8 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
   const int r_use = r_in_tile < w.rows_valid ? r_in_tile : 0;
   int blk_r = -1;        // sampled-key pass: sorted block of this key
   const int r_row = bwd_r_row<MODE>(a, b, r_use, &blk_r);           // row within the head
+  SampleHead shead{-1, 0};
+  if (kHits) shead = fetch_sample_head(a, b, tid);
   bf16x8 xreg[KS], areg[KS];
   {
     const u32x4* xp = reinterpret_cast<const u32x4*>(Xh + (int64_t)r_row * D + 8 * h);
@@ -241,6 +250,7 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
   asm volatile("" : "+v"(nl2_r), "+v"(del_r));
   if (ntiles > 0) {
     request_tile(0);
+    if (kHits) find_sample_hits<kBNT>(a, b, sample_hits(smem + bwd_hits_at<D>(a, MODE)), shead);  // while the first tile is on its way
     finish_tile(0);
   }
 
@@ -401,10 +411,10 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
   }
   __syncthreads();  // the tiles are read no more
 
-  auto write_out = [&](const auto& acc, float* dst32, uint16_t* dst16, const float* lvl) {
+  auto write_out = [&](const auto& acc, float* dst32, const float* samp, uint16_t* dst16, const float* lvl) {
     // ---- epilogue: the wave's 32 rows leave through an LDS transpose as whole rows.
-    // Node passes write or add fp32 rows into the accumulated rows.  Exact passes (the
-    // base case of Algorithm 4) write the final gradient in the tensors' dtype, after
+    // Node passes write or add fp32 rows into the accumulated rows (unmasked problems: write the final gradient).
+    // Exact passes (the base case of Algorithm 4) write the final gradient in the tensors' dtype, after
     // adding the accumulated row where some level's node holds the row on the pass's
     // side (queries: second half of the node; keys: first half).
     unsigned char* ep = smem + wave * L::EP_WAVE;
@@ -431,7 +441,27 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
     // fall back to "everything", and each piece would also wait for the previous piece's stores.
     const int64_t row_first = ep_rows[0];
     if (row_first < 0) return;
-    if (!kExact) {
+    // sums of the wave's sampled keys: requested together with the rows' earlier sums below; the further
+    // draws of a row are added here, by the lanes of its group (a quarter or half of the wave per row)
+    const float* sums = nullptr;  // null: no sampled key in the wave's rows
+    const int32_t* first = nullptr;
+    if (kHits && samp != nullptr) {
+      const SampleHits sh = sample_hits(smem + bwd_hits_at<D>(a, MODE));
+      first = sh.first + 32 * wave;
+      if (__any(first[lq] != kNoSample)) sums = samp + (int64_t)w.bh * bwd_chunks_per_node(g, a.chunk, 0) * g.m * D;
+      const int nm = sums ? *sh.count : 0;
+      constexpr int LPR = D / 4, G = 64 / LPR;
+      for (int e = 0; e < nm; ++e) {
+        const int row = sh.more[e] >> 16;
+        if ((row >> 5) != wave || (row & (G - 1)) != lane / LPR) continue;
+        f32x4* at = reinterpret_cast<f32x4*>(ep + (row & 31) * L::EP_ROW + (lane % LPR) * 16);
+        *at = *at + *reinterpret_cast<const f32x4*>(sums + (int64_t)(sh.more[e] & 0xffff) * D + (lane % LPR) * 4);
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+    if (!kExact && !FINAL) {
       // node passes add to what earlier levels left in the row; all rows of a node lie on the same side of
       // every ancestor, so the whole workgroup either adds or writes
       bool add = false;
@@ -466,7 +496,7 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
     }
     // the 32 rows of a wave lie in one n_min block: the node passes hold all of them or none
     const int i0 = w.q0 + 32 * __builtin_amdgcn_readfirstlane(wave);
-    const bool fold = lvl != nullptr && node_levels_hold(g, i0, kDq, g.levels);
+    const bool fold = kExact && lvl != nullptr && node_levels_hold(g, i0, kDq, g.levels);
     const float* acc_rows = lvl + ((int64_t)w.bh * g.n + i0) * D;
     constexpr int CH8 = D / 8;             // 8-element pieces per row
     constexpr int IT8 = 32 * CH8 / 64;     // pieces per lane
@@ -488,6 +518,22 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
         p1[it] = *reinterpret_cast<const f32x4*>(pp + 4);
       }
     }
+    if (kHits && sums != nullptr) {  // (a row without a sample reads sample 0's sums and drops them)
+#pragma unroll
+      for (int it = 0; it < IT8; ++it) {
+        const int idx = lane + 64 * it, j = first[idx / CH8];
+        const float* pp = sums + (int64_t)(j != kNoSample ? j : 0) * D + (idx % CH8) * 8;
+        p0[it] = *reinterpret_cast<const f32x4*>(pp);
+        p1[it] = *reinterpret_cast<const f32x4*>(pp + 4);
+      }
+#pragma unroll
+      for (int it = 0; it < IT8; ++it) {
+        const bool none = first[(lane + 64 * it) / CH8] == kNoSample;
+        const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+        p0[it] = none ? zero : p0[it];
+        p1[it] = none ? zero : p1[it];
+      }
+    }
 #pragma unroll
     for (int it = 0; it < IT8; ++it) {
       const int idx = lane + 64 * it;
@@ -498,23 +544,30 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
       if (r64[it] >= 0) *reinterpret_cast<u32x4*>(dst16 + r64[it] * D + ch * 8) = pk;
     }
   };
-  write_out(acc1, a.out1, reinterpret_cast<uint16_t*>(a.fin1), a.lvl1);
+  write_out(acc1, a.out1, a.samp1, reinterpret_cast<uint16_t*>(a.fin1), a.lvl1);
   if constexpr (!kDq) {
     // (a wave rewrites only its own staging area, which its own reads above have left)
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    write_out(acc2, a.out2, reinterpret_cast<uint16_t*>(a.fin2), a.lvl2);
+    write_out(acc2, a.out2, a.samp2, reinterpret_cast<uint16_t*>(a.fin2), a.lvl2);
   }
+}
+
+template <int D, int MODE, bool FINAL>
+static int launch_bwd_form(const BwdArgs& a, int grid, hipStream_t st) {
+  static std::atomic<uint64_t> lds_set{0};  // per instantiation: devices on which the LDS limit is raised
+  if (allow_full_lds(reinterpret_cast<const void*>(&attn_bwd_kernel<D, MODE, FINAL>), lds_set) != HA_OK) return HA_ERR_LAUNCH;
+  hipLaunchKernelGGL((attn_bwd_kernel<D, MODE, FINAL>), dim3((unsigned)grid), dim3(kBNT), bwd_lds_bytes<D>(a, MODE), st, a);
+  return check_launch();
 }
 
 template <int D, int MODE>
 static int launch_bwd_one(const BwdArgs& a, int grid, hipStream_t st) {
   if (grid <= 0) return HA_OK;
-  static std::atomic<uint64_t> lds_set{0};  // per instantiation: devices on which the LDS limit is raised
-  if (allow_full_lds(reinterpret_cast<const void*>(&attn_bwd_kernel<D, MODE>), lds_set) != HA_OK) return HA_ERR_LAUNCH;
-  hipLaunchKernelGGL((attn_bwd_kernel<D, MODE>), dim3((unsigned)grid), dim3(kBNT), bwd_lds_bytes<D>(a, MODE), st, a);
-  return check_launch();
+  if constexpr (MODE == kBwdDqNode || MODE == kBwdDkvBlock)
+    if (!a.f.g.causal) return launch_bwd_form<D, MODE, true>(a, grid, st);
+  return launch_bwd_form<D, MODE, false>(a, grid, st);
 }
 
 template <int D>

@@ -1,7 +1,5 @@
-// Small kernels around the backward passes: delta_i = <dO_i, O_i>, the ordered
-// reduction of the sampled keys' gradients of one level into the accumulated
-// key rows, and the conversion of accumulated rows to the tensors' dtype
-// (unmasked problems, whose single node holds the whole result).
+// Small kernels around the backward passes: delta_i = <dO_i, O_i>, and the ordered reduction of the sampled keys'
+// gradients: of one level into the accumulated key rows (causal), over the query chunks (unmasked).
 // Every sum is taken in a fixed order: results are bit-reproducible.
 #include "attn_common.h"
 #include "bwd_common.h"
@@ -9,7 +7,6 @@
 namespace ha {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // One group of D/8 lanes per row; 8 elements per lane.  O is read from its
 // unrounded fp32 copy when there is one: with the bf16 tensor, delta carries the
@@ -181,41 +178,41 @@ int launch_bwd_sample_scatter(const BwdArgs& a, int level, const float* samp_k, 
   return check_launch();
 }
 
-// Accumulated fp32 rows to the tensors' dtype.
-template <typename T, int D>
-__global__ __launch_bounds__(256) void bwd_convert_kernel(const float* __restrict__ acc, T* __restrict__ dst, int64_t rows) {
-  constexpr int LPR = D / 8;
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t row = t / LPR;
-  const int piece = (int)(t % LPR);
-  if (row >= rows) return;
-  const f32x4 v0 = *reinterpret_cast<const f32x4*>(acc + row * D + piece * 8);
-  const f32x4 v1 = *reinterpret_cast<const f32x4*>(acc + row * D + piece * 8 + 4);
-  if constexpr (sizeof(T) == 4) {
-    *reinterpret_cast<f32x4*>(dst + row * D + piece * 8) = v0;
-    *reinterpret_cast<f32x4*>(dst + row * D + piece * 8 + 4) = v1;
-  } else {
-    const u32x4 pk = {pack_bf16x2(v0.x, v0.y), pack_bf16x2(v0.z, v0.w), pack_bf16x2(v1.x, v1.y), pack_bf16x2(v1.z, v1.w)};
-    *reinterpret_cast<u32x4*>(dst + row * D + piece * 8) = pk;
+// Unmasked problems, whose block-key pass adds the sampled sums itself: the rows of the sampled-key pass summed over the
+// query chunks, one thread per four columns of a (head, sample) row of dK or dV, in place into the first chunk's row.
+// Bound by the rows it reads (12 heads, n = 16384, m = 256, d = 64: 50 MB in 9.8 us); left to the block-key pass,
+// where few waves hold a sampled key and wait for its chunks one after the other, that pass took 76 instead of 46 us.
+__global__ __launch_bounds__(256) void bwd_sample_reduce_kernel(float* samp_k, float* samp_v, int cpn, int m, int d, int64_t total) {
+  int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= total) return;
+  const int q4 = d / 4;
+  const int c4 = (int)(t % q4) * 4;
+  t /= q4;
+  float* samp = (t & 1) ? samp_v : samp_k;
+  t >>= 1;
+  float* p = samp + (t / m * cpn * m + t % m) * d + c4;
+  const int64_t step = (int64_t)m * d;
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  f32x4 part[8];
+#pragma unroll
+  for (int u = 0; u < 8; ++u) part[u] = zero;
+  for (int q = 0; q < cpn; q += 8) {  // eight rows in flight: requested unconditionally (a load under a branch is waited for alone)
+    f32x4 v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const f32x4*>(p + min(q + u, cpn - 1) * step);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) part[u] += q + u < cpn ? v[u] : zero;
   }
+  *reinterpret_cast<f32x4*>(p) = ((part[0] + part[1]) + (part[2] + part[3])) + ((part[4] + part[5]) + (part[6] + part[7]));
 }
 
-int launch_bwd_convert(const float* acc, void* dst, const Geometry& g, hipStream_t st) {
-  const int64_t rows = (int64_t)g.BH * g.n;
-  if (rows <= 0) return HA_OK;
-  const int lpr = g.d / 8;
-  const unsigned grid = (unsigned)((rows * lpr + 255) / 256);
-  const bool f32 = g.dtype == HA_FP32;
-  if (g.d == 128 && f32)
-    hipLaunchKernelGGL((bwd_convert_kernel<float, 128>), dim3(grid), dim3(256), 0, st, acc, (float*)dst, rows);
-  else if (g.d == 64 && f32)
-    hipLaunchKernelGGL((bwd_convert_kernel<float, 64>), dim3(grid), dim3(256), 0, st, acc, (float*)dst, rows);
-  else if (g.d == 128)
-    hipLaunchKernelGGL((bwd_convert_kernel<uint16_t, 128>), dim3(grid), dim3(256), 0, st, acc, (uint16_t*)dst, rows);
-  else if (g.d == 64)
-    hipLaunchKernelGGL((bwd_convert_kernel<uint16_t, 64>), dim3(grid), dim3(256), 0, st, acc, (uint16_t*)dst, rows);
-  else
-    return HA_ERR_SHAPE;
+int launch_bwd_sample_reduce(const BwdArgs& a, float* samp_k, float* samp_v, hipStream_t st) {
+  const Geometry& g = a.f.g;
+  const int cpn = bwd_chunks_per_node(g, a.chunk, 0);
+  if (cpn == 1) return HA_OK;
+  const int64_t total = (int64_t)g.BH * g.m * 2 * (g.d / 4), grid = (total + 255) / 256;
+  if (grid > kMaxGrid) return HA_ERR_SHAPE;
+  hipLaunchKernelGGL(bwd_sample_reduce_kernel, dim3((unsigned)grid), dim3(256), 0, st, samp_k, samp_v, cpn, g.m, g.d, total);
   return check_launch();
 }
 

@@ -133,6 +133,21 @@ def test_backward_unmasked(ha, torch, d, n, b, m):
     _run_case(ha, torch, cfg)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("d,n,b,m", [(64, 512, 64, 700),      # keys drawn several times, samples in three batches of threads
+                                     (128, 300, 100, 513),    # the same, blocks of 100 rows, a ragged tile
+                                     (64, 4096, 128, 300),    # several query chunks, few sampled keys per tile
+                                     (128, 96, 1, 40)])       # one key per block
+def test_backward_unmasked_sampled_keys(ha, torch, d, n, b, m, dtype):
+    """The block-key pass of an unmasked problem adds the sampled keys' sums to its own rows: a key's first draw with the
+    other rows, further draws from a list."""
+    print(f"backward, sampled keys d={d} n={n} b={b} m={m} {dtype}", flush=True)
+    cfg = dict(B=1, H=2, n=n, d=d, dtype=dtype, law="iid", b=b, m=m, r=7, causal=0, n_min=4096, seed=2)
+    (gq, gk, gv), (Q, K, V, out, lse, dO, ws, out32) = _run_case(ha, torch, cfg)
+    again = ha.hyperattn_backward(Q, K, V, out, lse, dO, b, m, 7, fwd_workspace=ws, causal=0, n_min=4096, seed=2, out_f32=out32)
+    assert all(torch.equal(x, y) for x, y in zip((gq, gk, gv), again))
+
+
 @pytest.mark.parametrize("d,n,n_min,b,m", [(128, 2048, 256, 128, 64), (64, 4096, 1024, 256, 256),
                                            (128, 1024, 4096, 256, 256), (128, 1024, 512, 512, 0),
                                            (64, 2048, 64, 32, 16), (128, 8192, 1024, 256, 256),

@@ -49,17 +49,18 @@ __global__ __launch_bounds__(256) void lsh_hash_mfma_kernel(HashArgs a) {
   const int n = lane & 31, h = lane >> 5;
   const int r = a.r;
   const int64_t rows = a.rows;
-  const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
+  // wave-uniform, and known to be: group numbers and row addresses stay in scalar registers
+  const int64_t wave = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t nwaves = (int64_t)gridDim.x * 4;
   const int64_t gpt = (rows + 31) / 32;  // groups of 32 rows per tensor
   const int64_t ngroups = a.X[1] ? 2 * gpt : gpt;
 
   auto load_group = [&](int64_t g, u32x4 (&xa)[KS]) {
     const bool second = g >= gpt;
-    const uint16_t* X = reinterpret_cast<const uint16_t*>(second ? a.X[1] : a.X[0]);
-    int64_t lrow = (second ? g - gpt : g) * 32 + n;
-    if (lrow >= rows) lrow = rows - 1;
-    const u32x4* xp = reinterpret_cast<const u32x4*>(X + lrow * D + 8 * h);
+    const int64_t row0 = (second ? g - gpt : g) * 32;
+    const uint16_t* X = reinterpret_cast<const uint16_t*>(second ? a.X[1] : a.X[0]) + row0 * D;
+    const int last = (int)(rows - row0 < 32 ? rows - row0 - 1 : 31);
+    const u32x4* xp = reinterpret_cast<const u32x4*>(X + (n < last ? n : last) * D + 8 * h);
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) xa[ks] = xp[2 * ks];
   };

@@ -254,12 +254,6 @@ __global__ __launch_bounds__(256) void alg2_tau_kernel(Alg2Args a) {
   }
 }
 
-__device__ inline float logaddexpf(float x, float y) {
-  const float hi = fmaxf(x, y), lo = fminf(x, y);
-  if (hi == -INFINITY) return -INFINITY;
-  return hi + log1pf(expf(lo - hi));
-}
-
 // log tau = the largest log unmasked row sum over the rows of T, one workgroup per head; where the
 // sums came in over ranges of keys they are added up first (and kept in log_unm_t).
 __global__ __launch_bounds__(256) void alg2_tau_max_kernel(Alg2Args a) {
@@ -468,7 +462,7 @@ static int launch_alg2_t(const Alg2Args& a_in, hipStream_t st) {
     }
   }
   hipLaunchKernelGGL(alg2_tau_max_kernel, dim3((unsigned)g.BH), dim3(256), 0, st, a);
-  if (mfma) return launch_alg2_main_mfma(a, st);
+  if (mfma) return a.vnorm ? launch_alg2_main_mfma(a, st) : check_launch();  // (without value sampling: the caller's node launch)
   const int tpb = (g.b + kA2Rows - 1) / kA2Rows;
   const unsigned grid = (unsigned)((int64_t)g.BH * (g.n / g.b) * tpb);
   if (g.d == 128)

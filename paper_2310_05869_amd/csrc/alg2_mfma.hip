@@ -1,25 +1,26 @@
 // bf16 MFMA kernels for the estimator of Algorithm 2 as printed and the value
 // product of Lemma 2 / Algorithm 3 (the options beside the Section 4 form):
 //
-//   tau role    log of the unmasked row sum <1 - M^H_j, A_j> of the rows j in T
+//   tau         log of the unmasked row sum <1 - M^H_j, A_j> of the rows j in T
 //               (Algorithm 2's tau is their maximum): 128 rows of T per
-//               workgroup against every key of the head, keys of the row's own
-//               sorted block left out.
-//   main role   for 128 queries of one sorted block: the masked row sum over the
-//               block's keys, the capped estimate d_i over the uniform samples,
-//               d~_i = masked + max(d_i, tau / kappa), and the numerator, either
-//               Section 4's (block keys + (n/m) kept samples) or Lemma 2's (rows
-//               of V drawn by squared norm, each with its 1 / (m p_l)).
+//               workgroup against a range of the node's keys in sorted order,
+//               keys of the row's own sorted block left out.
+//   main        with Lemma 2's value product: for 128 queries of one sorted block
+//               the masked row sum over the block's keys, the capped estimate d_i
+//               over the uniform samples, d~_i = masked + max(d_i, tau / kappa),
+//               and the numerator over rows of V drawn by squared norm, each with
+//               its 1 / (m p_l).  (Section 4's value product with the caps is a
+//               mode of the forward kernel: the same keys feed sums and numerator.)
 //
 // Tiling as in the forward kernel: 4 waves x 32 queries, 64 keys per step,
 // S^T = K Q^T with v_mfma_f32_32x32x16_bf16 so that a lane holds 16 keys of one
 // query, weights converted to bf16 in place as the B operand of O^T += V^T P^T,
-// V^T fragments from the transposing LDS read.  The loop is not software
-// pipelined (these are options, not the hot path): the next tile's rows are
-// fetched into registers while the current tile is computed.
+// V^T fragments from the transposing LDS read.  The loops are not software
+// pipelined: the next tile's rows are fetched into registers while the current
+// tile is computed.
 //
-// The key list of the main role has three segments, each padded to whole tiles:
-// A the block's keys, B the m uniform samples, C (Lemma 2 only) the m rows drawn
+// The key list of the main kernel has three segments, each padded to whole tiles:
+// A the block's keys, B the m uniform samples, C the m rows drawn
 // by squared norm.  An entry is a row index, or its complement when the key is
 // to be left out (padding; a sample that falls into the row's own block, the
 // factor 1 - M_{i,l_j}); segment C carries a log weight per key.  One running
@@ -40,8 +41,6 @@ constexpr int kA2KT = 64;    // keys per step
 constexpr int kA2QT = 128;   // queries per workgroup
 constexpr int kA2NT = 256;   // threads
 
-enum Alg2Role : int { kA2Tau = 0, kA2Main = 1 };
-
 template <int D>
 struct A2Lds {
   static constexpr int KSTR = (D + 8) * 2;    // bytes per K row (conflict-free 16-byte row reads)
@@ -49,33 +48,160 @@ struct A2Lds {
   static constexpr int K_BYTES = kA2KT * KSTR;
   static constexpr int V_BYTES = kA2KT * VSTR;
   static constexpr int BUF = K_BYTES + V_BYTES;
-  static constexpr int AUX = 2 * kA2KT * 4;   // tau role: sorted block of every key of the two tiles in flight
   static constexpr int EP_ROW = D * 4 + 16;
   static constexpr int EP_WAVE = 32 * EP_ROW + 32 * 8;
 };
 
 __host__ __device__ inline int a2_tiles(int count) { return (count + kA2KT - 1) / kA2KT; }
 
-// list entries (main role): segments A, B, C and the log weights of C
-__host__ __device__ inline int a2_list_entries(const Geometry& g, int vnorm) {
-  return (a2_tiles(g.b) + a2_tiles(g.m) * (vnorm ? 2 : 1)) * kA2KT;
-}
+// list entries: segments A, B, C (the log weights of C follow)
+__host__ __device__ inline int a2_list_entries(const Geometry& g) { return (a2_tiles(g.b) + 2 * a2_tiles(g.m)) * kA2KT; }
 
 template <int D>
-__host__ __device__ inline size_t a2_lds_bytes(const Geometry& g, int role, int vnorm) {
-  size_t s = 2 * (size_t)A2Lds<D>::BUF + A2Lds<D>::AUX;
-  if (role == kA2Main) s += (size_t)a2_list_entries(g, vnorm) * 4 + (vnorm ? (size_t)a2_tiles(g.m) * kA2KT * 4 : 0);
+__host__ __device__ inline size_t a2_lds_bytes(const Geometry& g) {
+  const size_t s = 2 * (size_t)A2Lds<D>::BUF + (size_t)a2_list_entries(g) * 4 + (size_t)a2_tiles(g.m) * kA2KT * 4;
   const size_t ep = 4 * (size_t)A2Lds<D>::EP_WAVE;
   return s > ep ? s : ep;
 }
 
-__device__ inline float a2_logaddexp(float x, float y) {
-  const float hi = fmaxf(x, y), lo = fminf(x, y);
-  if (hi == -INFINITY) return -INFINITY;
-  return hi + log1pf(expf(lo - hi));
+// Row sums of the rows of T.  Keys are walked in sorted order, so that a row's own block is one run of positions and
+// only the tiles that touch the run of one of a wave's rows carry a mask; in storage order every score of every
+// tile had to be compared with its key's block (two of seven vector instructions per score), and vector issue is
+// what bounds a kernel with one product per score.  A range of keys is shared by two groups of four waves, tile about,
+// whose sums are merged through LDS: with kAlg2TauSplits ranges alone 32 heads of 256 rows are two waves per
+// SIMD, which cannot cover each other.  The row tiles of a range are neighbours on one XCD (its keys meet in one L2).
+// Measured (MI355X, 32 heads, n = 32768, d = 128, m = 256): 171 -> 134 us.
+template <int D>
+__global__ __launch_bounds__(2 * kA2NT, 4) void alg2_tau_mfma_kernel(Alg2Args a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  using L = A2Lds<D>;
+  constexpr int KS = D / 16;
+  constexpr int CPR = D / 8;
+  constexpr int NKC = kA2KT * CPR / kA2NT;
+  const Geometry& g = a.g;
+  const int tid = threadIdx.x & (kA2NT - 1), grp = threadIdx.x / kA2NT;
+  const int lane = tid & 63, wave = tid >> 6;
+  const int lq = lane & 31, h = lane >> 5;
+  unsigned char* bufs = smem + grp * 2 * L::K_BYTES;
+
+  const int row_tiles = (g.m + kA2QT - 1) / kA2QT;
+  const int idx = logical_block(blockIdx.x, gridDim.x);
+  const int j0 = (idx % row_tiles) * kA2QT;
+  const int split = idx / row_tiles % kAlg2TauSplits;
+  const int bh = idx / row_tiles / kAlg2TauSplits;
+  const int rows_valid = min(kA2QT, g.m - j0);
+  const int64_t hb = (int64_t)bh * g.n;
+  const Alg2Node nd = alg2_node(a, bh);
+  const uint16_t* Qh = reinterpret_cast<const uint16_t*>(a.Q) + (int64_t)nd.head * a.n_full * D;
+  const uint16_t* Kh = reinterpret_cast<const uint16_t*>(a.K) + (int64_t)nd.head * a.n_full * D;
+
+  const int r_in_tile = wave * 32 + lq;
+  const int r_use = r_in_tile < rows_valid ? r_in_tile : 0;
+  const int q_in_node = a.tau_rows[(int64_t)nd.heap * g.m + j0 + r_use];
+  const int own = a.pos_q[hb + q_in_node] / g.b * g.b;  // first position of the row's own block
+  bf16x8 qreg[KS];
+  {
+    const u32x4* qp = reinterpret_cast<const u32x4*>(Qh + (int64_t)(nd.q_start + q_in_node) * D + 8 * h);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) qreg[ks] = __builtin_bit_cast(bf16x8, qp[2 * ks]);
+  }
+
+  const int ntiles = a2_tiles(g.n);
+  const int kt_lo = (int)((int64_t)ntiles * split / kAlg2TauSplits);
+  const int kt_hi = (int)((int64_t)ntiles * (split + 1) / kAlg2TauSplits);
+  const int32_t* keys = a.perm_k + hb;
+  int krow[NKC];
+  u32x4 kreg[NKC];
+  // row indices of a tile are requested a step before its rows (past the end: the last position, masked)
+  auto load_index = [&](int kt) {
+#pragma unroll
+    for (int i = 0; i < NKC; ++i) krow[i] = keys[min(kt * kA2KT + (tid + i * kA2NT) / CPR, g.n - 1)];
+  };
+  auto load_tile = [&]() {
+#pragma unroll
+    for (int i = 0; i < NKC; ++i)
+      kreg[i] = *reinterpret_cast<const u32x4*>(Kh + (int64_t)krow[i] * D + (tid + i * kA2NT) % CPR * 8);
+  };
+  auto store_tile = [&](int buf) {
+#pragma unroll
+    for (int i = 0; i < NKC; ++i) {
+      const int c = tid + i * kA2NT;
+      *reinterpret_cast<u32x4*>(bufs + buf * L::K_BYTES + c / CPR * L::KSTR + c % CPR * 16) = kreg[i];
+    }
+  };
+
+  float m_run = -INFINITY, sum = 0.f;  // reference (log2 domain) and this lane's share of the row sum / 2^m_run
+  const int trips = (kt_hi - kt_lo + 1) / 2;
+  load_index(kt_lo + grp);
+  load_tile();
+  load_index(kt_lo + grp + 2);
+  store_tile(0);
+  __syncthreads();
+  for (int it = 0; it < trips; ++it) {
+    const int kt = kt_lo + grp + 2 * it;
+    load_tile();  // (past the range: existing rows that are not used)
+    load_index(kt + 4);
+    if (kt < kt_hi) {
+      const unsigned char* kp0 = bufs + (it & 1) * L::K_BYTES + lq * L::KSTR + 16 * h;
+      const unsigned char* kp1 = kp0 + 32 * L::KSTR;
+      f32x16 c[2];
+#pragma unroll
+      for (int sub = 0; sub < 2; ++sub)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) c[sub][i] = 0.f;
+#pragma unroll
+      for (int j = 0; j < KS; ++j) {
+        c[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(kp0 + 32 * j), qreg[j], c[0], 0, 0, 0);
+        c[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(kp1 + 32 * j), qreg[j], c[1], 0, 0, 0);
+      }
+      // element i of c[sub] is position 32 sub + 8 (i / 4) + 4 h + i % 4 of the tile
+      const int mlo = own - kt * kA2KT, tail = g.n - kt * kA2KT;
+      if (tail < kA2KT || __any(mlo < kA2KT && mlo + g.b > 0)) {
+#pragma unroll
+        for (int sub = 0; sub < 2; ++sub)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) {
+            const int koff = 32 * sub + 8 * (i / 4) + (i % 4);
+            if (koff >= tail - 4 * h || (unsigned)(koff - (mlo - 4 * h)) < (unsigned)g.b) c[sub][i] = -INFINITY;
+          }
+      }
+      float mx = fmaxf(c[0][0], c[1][0]);
+#pragma unroll
+      for (int i = 1; i < 16; ++i) mx = __builtin_fmaxf(__builtin_fmaxf(mx, c[0][i]), c[1][i]);
+      mx = fmaxf(mx, __shfl_xor(mx, 32)) * kLog2e;
+      if (__any(mx > m_run + 8.0f)) {
+        const float m_new = fmaxf(m_run, mx);
+        sum *= __builtin_amdgcn_exp2f(m_run - ((m_new == -INFINITY) ? 0.f : m_new));
+        m_run = m_new;
+      }
+      const float shift = (m_run == -INFINITY) ? 0.f : -m_run;
+      float s4[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int sub = 0; sub < 2; ++sub)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s4[i & 3] += __builtin_amdgcn_exp2f(__builtin_fmaf(c[sub][i], kLog2e, shift));
+      sum += (s4[0] + s4[1]) + (s4[2] + s4[3]);
+    }
+    store_tile((it + 1) & 1);
+    __syncthreads();
+  }
+
+  sum += __shfl_xor(sum, 32);
+  float* part = reinterpret_cast<float*>(smem);  // [2][kA2QT]: the tiles are read no more
+  if (grp == 1 && h == 0) {
+    part[r_in_tile] = m_run;
+    part[kA2QT + r_in_tile] = sum;
+  }
+  __syncthreads();
+  if (grp == 0 && h == 0 && r_in_tile < rows_valid) {
+    const float m1 = part[r_in_tile], m = fmaxf(m_run, m1);
+    const float ref = (m == -INFINITY) ? 0.f : m;
+    const float total = sum * __builtin_amdgcn_exp2f(m_run - ref) + part[kA2QT + r_in_tile] * __builtin_amdgcn_exp2f(m1 - ref);
+    a.log_unm_parts[((int64_t)split * g.BH + bh) * g.m + j0 + r_in_tile] = (total > 0.f) ? (m + log2f(total)) * kLn2 : -INFINITY;
+  }
 }
 
-template <int D, int ROLE>
+template <int D>
 __global__ __launch_bounds__(kA2NT, 2) void alg2_mfma_kernel(Alg2Args a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   using L = A2Lds<D>;
@@ -89,29 +215,17 @@ __global__ __launch_bounds__(kA2NT, 2) void alg2_mfma_kernel(Alg2Args a) {
   const int lq = lane & 31, h = lane >> 5;
 
   unsigned char* bufs = smem;
-  int32_t* kblk = reinterpret_cast<int32_t*>(smem + 2 * L::BUF);  // [2][64]
-  int32_t* list = kblk + 2 * kA2KT;
+  int32_t* list = reinterpret_cast<int32_t*>(smem + 2 * L::BUF);
 
   // ---- which rows this workgroup owns ----
-  int bh, t = 0, p0 = 0, j0 = 0, rows_valid, split = 0;
-  if (ROLE == kA2Main) {
-    const int tpb = (g.b + kA2QT - 1) / kA2QT;
-    const int per_head = (g.n / g.b) * tpb;
-    const int tile = blockIdx.x % per_head;
-    bh = blockIdx.x / per_head;
-    t = tile / tpb;
-    const int chunk = tile % tpb;
-    p0 = t * g.b + chunk * kA2QT;
-    rows_valid = min(kA2QT, g.b - chunk * kA2QT);
-  } else {
-    // (head, 128 rows of T, one of kAlg2TauSplits ranges of key tiles)
-    const int per_head = (g.m + kA2QT - 1) / kA2QT;
-    split = blockIdx.x % kAlg2TauSplits;
-    const int rest = blockIdx.x / kAlg2TauSplits;
-    bh = rest / per_head;
-    j0 = (rest % per_head) * kA2QT;
-    rows_valid = min(kA2QT, g.m - j0);
-  }
+  const int tpb = (g.b + kA2QT - 1) / kA2QT;
+  const int per_head = (g.n / g.b) * tpb;
+  const int tile = blockIdx.x % per_head;
+  const int bh = blockIdx.x / per_head;
+  const int t = tile / tpb;
+  const int chunk = tile % tpb;
+  const int p0 = t * g.b + chunk * kA2QT;
+  const int rows_valid = min(kA2QT, g.b - chunk * kA2QT);
   // bh is a view head: one node of the level (alg2_common.h).  Row indices below are rows of the
   // real head (permutation entries already are; node-local draws get the node's first row added).
   const int64_t hb = (int64_t)bh * g.n;
@@ -125,9 +239,7 @@ __global__ __launch_bounds__(kA2NT, 2) void alg2_mfma_kernel(Alg2Args a) {
   const int r_in_tile = wave * 32 + lq;
   const bool valid = r_in_tile < rows_valid;
   const int r_use = valid ? r_in_tile : 0;
-  const int qrow = (ROLE == kA2Main) ? a.perm_q[hb + p0 + r_use]
-                                     : nd.q_start + a.tau_rows[(int64_t)nd.heap * g.m + j0 + r_use];
-  const int my_blk = (ROLE == kA2Tau) ? a.pos_q[hb + (qrow - nd.q_start)] / g.b : 0;
+  const int qrow = a.perm_q[hb + p0 + r_use];
   bf16x8 qreg[KS];
   {
     const u32x4* qp = reinterpret_cast<const u32x4*>(Qh + (int64_t)qrow * D + 8 * h);
@@ -136,17 +248,10 @@ __global__ __launch_bounds__(kA2NT, 2) void alg2_mfma_kernel(Alg2Args a) {
   }
 
   // ---- the keys ----
-  const int nA = (ROLE == kA2Main) ? a2_tiles(g.b) : a2_tiles(g.n);  // tau role: every key of the head, in place
-  const int nB = (ROLE == kA2Main) ? a2_tiles(g.m) : 0;
-  const int nC = (ROLE == kA2Main && a.vnorm) ? a2_tiles(g.m) : 0;
+  const int nA = a2_tiles(g.b), nB = a2_tiles(g.m), nC = nB;
   const int ntiles = nA + nB + nC;
-  int kt_lo = 0, kt_hi = ntiles;
-  if (ROLE == kA2Tau) {
-    kt_lo = (int)((int64_t)ntiles * split / kAlg2TauSplits);
-    kt_hi = (int)((int64_t)ntiles * (split + 1) / kAlg2TauSplits);
-  }
   const float* bias_c = reinterpret_cast<const float*>(list + (nA + nB + nC) * kA2KT);  // log2-domain weights of segment C
-  if (ROLE == kA2Main) {
+  {
     int32_t* la = list;
     int32_t* lb = la + nA * kA2KT;
     int32_t* lc = lb + nB * kA2KT;
@@ -168,37 +273,25 @@ __global__ __launch_bounds__(kA2NT, 2) void alg2_mfma_kernel(Alg2Args a) {
   }
   const float ratio = g.m > 0 ? (float)g.n / (float)g.m : 1.f;
   const float log2ratio = log2f(ratio);
-  const float floor_term = (ROLE == kA2Main && a.kappa > 0.f)
+  const float floor_term = (a.kappa > 0.f)
                                ? a.log_tau[(int64_t)nd.head * a.total_nodes + nd.heap] - logf(a.kappa) : -INFINITY;
-  auto need_v = [&](int kt) -> bool { return ROLE == kA2Main && (a.vnorm ? kt >= nA + nB : true); };
+  auto need_v = [&](int kt) -> bool { return kt >= nA + nB; };
 
   // ---- tile movers (buffer loads: rows past the head read as zeros and are left out by their entries) ----
   const uint32_t head_bytes = (uint32_t)(a.n_full * (D * 2));
   const __amdgpu_buffer_rsrc_t krsrc = __builtin_amdgcn_make_buffer_rsrc((void*)Kh, 0, (int)head_bytes, 0x00020000);
   const __amdgpu_buffer_rsrc_t vrsrc = __builtin_amdgcn_make_buffer_rsrc((void*)Vh, 0, (int)head_bytes, 0x00020000);
   u32x4 kreg[NKC], vreg[NKC];
-  int kb_next = -1;  // tau role: sorted block of key tid of the tile being fetched
   auto load_tile = [&](int kt) {
     const bool with_v = need_v(kt);
 #pragma unroll
     for (int i = 0; i < NKC; ++i) {
       const int c = tid + i * kA2NT;
       const int key = c / CPR, col = c % CPR;
-      int voff, soff;
-      if (ROLE == kA2Main) {
-        const int e = list[kt * kA2KT + key];
-        voff = (e < 0 ? ~e : e) * (D * 2) + col * 16;
-        soff = 0;
-      } else {
-        voff = key * (D * 2) + col * 16;
-        soff = (nd.k_start + kt * kA2KT) * (D * 2);   // keys past the node's end are left out through kblk
-      }
-      kreg[i] = __builtin_amdgcn_raw_buffer_load_b128(krsrc, voff, soff, 0);
-      if (with_v) vreg[i] = __builtin_amdgcn_raw_buffer_load_b128(vrsrc, voff, soff, 0);
-    }
-    if (ROLE == kA2Tau && tid < kA2KT) {
-      const int key = kt * kA2KT + tid;
-      kb_next = (key < g.n) ? a.pos_k[hb + key] / g.b : -1;
+      const int e = list[kt * kA2KT + key];
+      const int voff = (e < 0 ? ~e : e) * (D * 2) + col * 16;
+      kreg[i] = __builtin_amdgcn_raw_buffer_load_b128(krsrc, voff, 0, 0);
+      if (with_v) vreg[i] = __builtin_amdgcn_raw_buffer_load_b128(vrsrc, voff, 0, 0);
     }
   };
   auto store_tile = [&](int kt) {
@@ -212,7 +305,6 @@ __global__ __launch_bounds__(kA2NT, 2) void alg2_mfma_kernel(Alg2Args a) {
       *reinterpret_cast<u32x4*>(kbuf + key * L::KSTR + col * 16) = kreg[i];
       if (with_v) *reinterpret_cast<u32x4*>(vbuf + key * L::VSTR + col * 16) = vreg[i];
     }
-    if (ROLE == kA2Tau && tid < kA2KT) kblk[(kt & 1) * kA2KT + tid] = kb_next;
   };
   const int vtr_off = ((lane & 15) >> 2) * L::VSTR + ((lane & 3) * 4 + ((lane >> 4) & 1) * 16) * 2 + (4 * h) * L::VSTR;
 
@@ -223,26 +315,24 @@ __global__ __launch_bounds__(kA2NT, 2) void alg2_mfma_kernel(Alg2Args a) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) o[dt][i] = 0.f;
   float m_run = -INFINITY;  // reference of every exponential, log2 domain
-  float msum = 0.f;         // this lane's share of the masked row sum (tau role: of the unmasked one) / 2^m_run
+  float msum = 0.f;         // this lane's share of the masked row sum / 2^m_run
   float dsum = 0.f;         // this lane's share of (n/m) sum of capped kept samples / 2^m_run
   float log2capw = INFINITY;  // log2 of (n/m) C_i, known once segment A is done
 
-  if (kt_lo < kt_hi) {
-    load_tile(kt_lo);
-    store_tile(kt_lo);
-  }
+  load_tile(0);
+  store_tile(0);
   __syncthreads();
 
-  for (int kt = kt_lo; kt < kt_hi; ++kt) {
-    const bool more = kt + 1 < kt_hi;
+  for (int kt = 0; kt < ntiles; ++kt) {
+    const bool more = kt + 1 < ntiles;
     if (more) load_tile(kt + 1);
 
-    if (ROLE == kA2Main && kt == nA && nB > 0) {
+    if (kt == nA && nB > 0) {
       // the masked row sum is complete: the cap C_i of Algorithm 2
       const float mt = msum + __shfl_xor(msum, 32);
       const float log_masked = (mt > 0.f) ? (m_run + log2f(mt)) * kLn2 : -INFINITY;
       if (a.cap_scale > 0.f) {
-        const float log_cap = logf(a.cap_scale * (float)g.m / ((float)g.n * logf((float)g.n))) + a2_logaddexp(log_masked, floor_term);
+        const float log_cap = logf(a.cap_scale * (float)g.m / ((float)g.n * logf((float)g.n))) + logaddexpf(log_masked, floor_term);
         log2capw = log_cap * kLog2e + log2ratio;
       }
     }
@@ -266,7 +356,7 @@ __global__ __launch_bounds__(kA2NT, 2) void alg2_mfma_kernel(Alg2Args a) {
     }
     // ---- log2-domain arguments: score + the key's log weight, -inf where the key is left out.
     // Element i of c[sub] is key 32 sub + 8 (i / 4) + 4 h + i % 4 of the tile.
-    const int seg = (ROLE == kA2Tau) ? 0 : (kt < nA ? 0 : (kt < nA + nB ? 1 : 2));
+    const int seg = kt < nA ? 0 : (kt < nA + nB ? 1 : 2);
     const float segbias = (seg == 1) ? log2ratio : 0.f;
     float tmax = -INFINITY;
 #pragma unroll
@@ -274,18 +364,12 @@ __global__ __launch_bounds__(kA2NT, 2) void alg2_mfma_kernel(Alg2Args a) {
 #pragma unroll
       for (int g4 = 0; g4 < 4; ++g4) {
         const int at = 32 * sub + 8 * g4 + 4 * h;
-        i32x4 e4;
         f32x4 b4 = {segbias, segbias, segbias, segbias};
-        if (ROLE == kA2Main) {
-          e4 = *reinterpret_cast<const i32x4*>(list + kt * kA2KT + at);
-          if (seg == 2) b4 = *reinterpret_cast<const f32x4*>(bias_c + (kt - nA - nB) * kA2KT + at);
-        } else {
-          e4 = *reinterpret_cast<const i32x4*>(kblk + (kt & 1) * kA2KT + at);
-        }
+        const i32x4 e4 = *reinterpret_cast<const i32x4*>(list + kt * kA2KT + at);
+        if (seg == 2) b4 = *reinterpret_cast<const f32x4*>(bias_c + (kt - nA - nB) * kA2KT + at);
 #pragma unroll
         for (int z = 0; z < 4; ++z) {
-          const bool out_of_it = (ROLE == kA2Main) ? (e4[z] < 0) : (e4[z] < 0 || e4[z] == my_blk);
-          const float v = out_of_it ? -INFINITY : __builtin_fmaf(c[sub][4 * g4 + z], kLog2e, b4[z]);
+          const float v = e4[z] < 0 ? -INFINITY : __builtin_fmaf(c[sub][4 * g4 + z], kLog2e, b4[z]);
           c[sub][4 * g4 + z] = v;
           tmax = fmaxf(tmax, v);
         }
@@ -317,7 +401,7 @@ __global__ __launch_bounds__(kA2NT, 2) void alg2_mfma_kernel(Alg2Args a) {
           const float p0w = __builtin_amdgcn_exp2f(c[sub][8 * jj + 2 * e] - mref);
           const float p1w = __builtin_amdgcn_exp2f(c[sub][8 * jj + 2 * e + 1] - mref);
           sp += p0w + p1w;
-          if (ROLE == kA2Main) sd += fminf(p0w, capw) + fminf(p1w, capw);
+          sd += fminf(p0w, capw) + fminf(p1w, capw);
           pk[e] = pack_bf16x2(p0w, p1w);
         }
         pf[2 * sub + jj] = __builtin_bit_cast(bf16x8, pk);
@@ -348,15 +432,10 @@ __global__ __launch_bounds__(kA2NT, 2) void alg2_mfma_kernel(Alg2Args a) {
 
   // ---- results ----
   const float mt = msum + __shfl_xor(msum, 32);
-  if (ROLE == kA2Tau) {
-    if (valid && h == 0)
-      a.log_unm_parts[((int64_t)split * g.BH + bh) * g.m + j0 + r_in_tile] = (mt > 0.f) ? (m_run + log2f(mt)) * kLn2 : -INFINITY;
-    return;
-  }
   const float dt_ = dsum + __shfl_xor(dsum, 32);
   const float log_masked = (mt > 0.f) ? (m_run + log2f(mt)) * kLn2 : -INFINITY;
   const float log_d = (dt_ > 0.f) ? (m_run + log2f(dt_)) * kLn2 : -INFINITY;
-  const float log_dt = a2_logaddexp(log_masked, fmaxf(log_d, floor_term));   // d~_i = masked + max(d_i, tau / kappa)
+  const float log_dt = logaddexpf(log_masked, fmaxf(log_d, floor_term));   // d~_i = masked + max(d_i, tau / kappa)
   const float f = (m_run == -INFINITY || log_dt == -INFINITY) ? 0.f : expf(m_run * kLn2 - log_dt);
   const int64_t out_row = hb + (qrow - nd.q_start);
   if (valid && h == 0) a.lse[out_row] = log_dt;
@@ -389,36 +468,43 @@ __global__ __launch_bounds__(kA2NT, 2) void alg2_mfma_kernel(Alg2Args a) {
   }
 }
 
-template <int D, int ROLE>
-static int launch_a2(const Alg2Args& a, int64_t grid, hipStream_t st) {
-  if (grid <= 0) return HA_OK;
-  if (grid > kMaxGrid) return HA_ERR_SHAPE;
-  const size_t lds = a2_lds_bytes<D>(a.g, ROLE, a.vnorm);
-  static std::atomic<uint64_t> lds_set{0};  // per instantiation: devices on which the LDS limit is raised
-  if (allow_full_lds(reinterpret_cast<const void*>(&alg2_mfma_kernel<D, ROLE>), lds_set) != HA_OK) return HA_ERR_LAUNCH;
-  hipLaunchKernelGGL((alg2_mfma_kernel<D, ROLE>), dim3((unsigned)grid), dim3(kA2NT), lds, st, a);
-  return check_launch();
-}
-
 // Whether the MFMA kernels take this problem: bf16 tensors, d of 64 or 128, and a key list that fits in LDS.
 bool alg2_mfma_supported(const Alg2Args& a) {
   const Geometry& g = a.g;
   if (g.dtype != HA_BF16 || (g.d != 64 && g.d != 128)) return false;
-  const size_t lds = g.d == 128 ? a2_lds_bytes<128>(g, kA2Main, a.vnorm) : a2_lds_bytes<64>(g, kA2Main, a.vnorm);
-  return lds <= 160 * 1024;
+  return (g.d == 128 ? a2_lds_bytes<128>(g) : a2_lds_bytes<64>(g)) <= 160 * 1024;
+}
+
+template <int D>
+static int launch_tau(const Alg2Args& a, unsigned grid, hipStream_t st) {
+  static std::atomic<uint64_t> lds_set{0};  // per instantiation: devices on which the LDS limit is raised
+  if (allow_full_lds(reinterpret_cast<const void*>(&alg2_tau_mfma_kernel<D>), lds_set) != HA_OK) return HA_ERR_LAUNCH;
+  hipLaunchKernelGGL((alg2_tau_mfma_kernel<D>), dim3(grid), dim3(2 * kA2NT), 4 * A2Lds<D>::K_BYTES, st, a);
+  return check_launch();
 }
 
 int launch_alg2_tau_mfma(const Alg2Args& a, hipStream_t st) {
   const Geometry& g = a.g;
   const int64_t grid = (int64_t)g.BH * ((g.m + kA2QT - 1) / kA2QT) * kAlg2TauSplits;
-  return g.d == 128 ? launch_a2<128, kA2Tau>(a, grid, st) : launch_a2<64, kA2Tau>(a, grid, st);
+  if (grid <= 0) return HA_OK;
+  if (grid > kMaxGrid) return HA_ERR_SHAPE;
+  return g.d == 128 ? launch_tau<128>(a, (unsigned)grid, st) : launch_tau<64>(a, (unsigned)grid, st);
+}
+
+template <int D>
+static int launch_a2(const Alg2Args& a, hipStream_t st) {
+  const Geometry& g = a.g;
+  const int64_t grid = (int64_t)g.BH * (g.n / g.b) * ((g.b + kA2QT - 1) / kA2QT);
+  if (grid <= 0) return HA_OK;
+  if (grid > kMaxGrid) return HA_ERR_SHAPE;
+  static std::atomic<uint64_t> lds_set{0};  // per instantiation: devices on which the LDS limit is raised
+  if (allow_full_lds(reinterpret_cast<const void*>(&alg2_mfma_kernel<D>), lds_set) != HA_OK) return HA_ERR_LAUNCH;
+  hipLaunchKernelGGL((alg2_mfma_kernel<D>), dim3((unsigned)grid), dim3(kA2NT), a2_lds_bytes<D>(g), st, a);
+  return check_launch();
 }
 
 int launch_alg2_main_mfma(const Alg2Args& a, hipStream_t st) {
-  const Geometry& g = a.g;
-  const int tpb = (g.b + kA2QT - 1) / kA2QT;
-  const int64_t grid = (int64_t)g.BH * (g.n / g.b) * tpb;
-  return g.d == 128 ? launch_a2<128, kA2Main>(a, grid, st) : launch_a2<64, kA2Main>(a, grid, st);
+  return a.g.d == 128 ? launch_a2<128>(a, st) : launch_a2<64>(a, st);
 }
 
 }  // namespace ha

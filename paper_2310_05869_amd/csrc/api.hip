@@ -273,6 +273,35 @@ static int run_base_case(const void* Q, const void* K, const void* V, void* out,
   return run_attention(a, kModeExact, st);
 }
 
+// All off-diagonal nodes of Algorithm 4 (unmasked problem: its one node), from a workspace in which their rows are
+// hashed and sorted; causal: results go to the per-level partial rows.
+static AttnArgs node_args(const void* Q, const void* K, const void* V, void* out, float* lse, float* out_f32,
+                          const Geometry& g, unsigned char* ws, const ha_ws_layout& lay) {
+  AttnArgs a{};
+  a.Q = Q;
+  a.K = K;
+  a.V = V;
+  a.q_bh_stride = a.k_bh_stride = a.out_bh_stride = (int64_t)g.n * g.d;
+  a.perm_q = (const int32_t*)(ws + lay.perm_q);
+  a.perm_k = (const int32_t*)(ws + lay.perm_k);
+  a.pos_k = (const int32_t*)(ws + lay.pos_k);
+  a.samples = g.m > 0 ? (const int32_t*)(ws + lay.samples) : nullptr;
+  a.samp_blk = g.m > 0 ? (const int32_t*)(ws + lay.samp_blk) : nullptr;
+  a.use_block = 1;
+  a.scatter_out = 1;
+  a.g = g;
+  if (g.causal) {
+    a.part_o = (void*)(ws + lay.part_o);
+    a.part_l = (float*)(ws + lay.part_l);
+    a.part_bf16 = g.dtype == HA_BF16;
+  } else {
+    a.out = out;
+    a.lse = lse;
+    a.out_f32 = out_f32;
+  }
+  return a;
+}
+
 // ev, when non-null, receives 6 events recorded on the stream: start, after
 // again (draws: part of the hashing launch), after hashing, after sorting, after the node attention, after the base case.
 // node_stamps / base_stamps, when non-null, select the measuring instantiation of the
@@ -304,7 +333,6 @@ static int forward_impl(const void* Q, const void* K, const void* V, void* out, 
   float* proj = (float*)(base + lay.proj);
   void* part_o = (void*)(base + lay.part_o);
   float* part_l = (float*)(base + lay.part_l);
-  const int64_t head_stride = (int64_t)g.n * g.d;
   auto mark = [&](int i) {
     if (ev) (void)hipEventRecord(ev[i], st);
   };
@@ -320,29 +348,7 @@ static int forward_impl(const void* Q, const void* K, const void* V, void* out, 
     if (rc != HA_OK) return rc;
     mark(3);
 
-    AttnArgs a{};
-    a.Q = Q;
-    a.K = K;
-    a.V = V;
-    a.q_bh_stride = a.k_bh_stride = head_stride;
-    a.perm_q = perm_q;
-    a.perm_k = perm_k;
-    a.pos_k = pos_k;
-    a.samples = g.m > 0 ? samples : nullptr;
-    a.samp_blk = g.m > 0 ? samp_blk : nullptr;
-    a.use_block = 1;
-    a.out_bh_stride = head_stride;
-    a.scatter_out = 1;
-    a.g = g;
-    if (g.causal) {
-      a.part_o = part_o;
-      a.part_l = part_l;
-      a.part_bf16 = g.dtype == HA_BF16;
-    } else {
-      a.out = out;
-      a.lse = lse;
-      a.out_f32 = out_f32;
-    }
+    AttnArgs a = node_args(Q, K, V, out, lse, out_f32, g, base, lay);
     a.stamps = node_stamps;
     rc = run_attention(a, kModeNode, st);
     if (rc != HA_OK) return rc;
@@ -1033,6 +1039,14 @@ int hyperattn_forward_alg2(const void* Q, const void* K, const void* V, void* ou
       a.kappa = opt->kappa;
       a.vnorm = opt->vnorm_sampling ? 1 : 0;
       rc = launch_alg2(a, st);
+      if (rc != HA_OK) return rc;
+    }
+    if (use_mfma(g) && !opt->vnorm_sampling) {  // with every node's tau known, all nodes in one launch, as in the forward
+      AttnArgs a = node_args(Q, K, V, out, lse, nullptr, g, base, lay);
+      a.log_tau = (const float*)(base + al.log_tau);
+      a.cap_scale = opt->cap_scale;
+      a.kappa = opt->kappa;
+      rc = run_attention(a, kModeCap, st);
       if (rc != HA_OK) return rc;
     }
   }

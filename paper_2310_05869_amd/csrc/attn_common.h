@@ -176,7 +176,8 @@ __device__ inline KeyListHead key_list_fetch(const AttnArgs& a, const TileWork& 
 // threads call it; on return (after its final barrier) list[0..pad) holds row
 // indices within the head, *nb_out the block keys and the return value nkeys.
 // `kh` = key_list_fetch's values of the calling thread.
-template <int NT>
+// PADDED: the block's keys are padded to whole tiles of 64, so that no tile holds both parts.
+template <int NT, bool PADDED = false>
 __device__ inline int build_key_list(const AttnArgs& a, const TileWork& w, int32_t* list, int32_t* scratch,
                                      int* nb_out, const KeyListHead& kh) {
   const Geometry& g = a.g;
@@ -197,7 +198,9 @@ __device__ inline int build_key_list(const AttnArgs& a, const TileWork& w, int32
   const int pk0 = kh.pk0, l0 = kh.l0, blk0 = kh.blk0;
   if (tid < nb) list[tid] = pk0;
   for (int i = tid + NT; i < nb; i += NT) list[i] = block_key(i);
-  int base = nb;
+  int base = PADDED ? (nb + 63) & ~63 : nb;
+  if (PADDED)
+    for (int i = nb + tid; i < base; i += NT) list[i] = w.nr.k_start;
   for (int j0 = 0; j0 < m; j0 += NT) {
     const int j = j0 + tid;
     int l = l0, blk = blk0;
@@ -232,6 +235,12 @@ template <int NT>
 __device__ inline int build_key_list(const AttnArgs& a, const TileWork& w, int32_t* list, int32_t* scratch,
                                      int* nb_out) {
   return build_key_list<NT>(a, w, list, scratch, nb_out, key_list_fetch<NT>(a, w));
+}
+
+__device__ inline float logaddexpf(float x, float y) {
+  const float hi = fmaxf(x, y), lo = fminf(x, y);
+  if (hi == -INFINITY) return -INFINITY;
+  return hi + log1pf(expf(lo - hi));
 }
 
 __device__ inline uint32_t pack_bf16x2(float lo, float hi) {

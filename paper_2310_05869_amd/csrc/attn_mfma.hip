@@ -64,7 +64,7 @@ __host__ __device__ inline int list_capacity(int b, int m) { return ((b + m + 63
 template <int D>
 __host__ __device__ inline size_t mfma_lds_bytes(int b, int m, int mode) {
   size_t s = 2 * (size_t)Lds<D>::BUF + 64;  // + wave counters
-  if (mode == kModeNode) s += (size_t)list_capacity(b, m) * 4;
+  if (mode != kModeExact) s += (size_t)list_capacity(b, m) * 4;
   return s;
 }
 
@@ -82,6 +82,8 @@ struct TileRegs {
 template <int D, int MODE, int NW, bool STAMPS = false>
 __global__ __launch_bounds__(64 * NW, (D == 64 && NW == 4) ? 3 : 2) void attn_mfma_kernel(AttnArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  constexpr bool kCap = MODE == kModeCap;
+  constexpr bool kNode = MODE == kModeNode || kCap;
   constexpr int kQT = 32 * NW;  // queries per workgroup
   constexpr int kNT = 64 * NW;  // threads
   using L = Lds<D>;
@@ -108,9 +110,9 @@ __global__ __launch_bounds__(64 * NW, (D == 64 && NW == 4) ? 3 : 2) void attn_mf
   if constexpr (STAMPS) stamp_w = (long long)wall_clock64();
   stamp(0);
 
-  const int bid = MODE == kModeNode ? logical_block(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+  const int bid = kNode ? logical_block(blockIdx.x, gridDim.x) : (int)blockIdx.x;
   TileWork w;
-  if (MODE == kModeNode) w = decode_node_tile<kQT>(a, bid);
+  if (kNode) w = decode_node_tile<kQT>(a, bid);
   else w = decode_exact_tile<kQT>(a, bid);
 
   const uint16_t* Qh = reinterpret_cast<const uint16_t*>(a.Q) + (int64_t)w.bh * a.q_bh_stride;
@@ -121,12 +123,12 @@ __global__ __launch_bounds__(64 * NW, (D == 64 && NW == 4) ? 3 : 2) void attn_mf
   // Node mode: the key list's first index values and the row's own index (through P_Q) travel
   // in one round trip; the (gathered) row is then in flight while the key list is built.
   KeyListHead klh{0, 0, 0};
-  if (MODE == kModeNode) klh = key_list_fetch<kNT>(a, w);
+  if (kNode) klh = key_list_fetch<kNT>(a, w);
   const int r_in_tile = wave * 32 + lq;
   RowDest dest;
   int qrow_load;   // row to load (always a valid row)
   int q_global;    // exact mode: row index within the head, for the causal mask
-  if (MODE == kModeNode) {
+  if (kNode) {
     dest = node_row_dest(a, w, r_in_tile);
     const int p = w.p0 + (dest.valid ? r_in_tile : 0);
     qrow_load = a.perm_q ? a.perm_q[w.seg_off + p] : w.nr.q_start + p;
@@ -147,14 +149,14 @@ __global__ __launch_bounds__(64 * NW, (D == 64 && NW == 4) ? 3 : 2) void attn_mf
   }
 
   int nb, nkeys;
-  if (MODE == kModeNode) {
-    nkeys = build_key_list<kNT>(a, w, list, scratch, &nb, klh);
+  if (kNode) {
+    nkeys = build_key_list<kNT, kCap>(a, w, list, scratch, &nb, klh);
   } else {
     nkeys = max(0, w.k1 - w.k0);
     nb = 0x7fffffff;
   }
   const int ntiles = (nkeys + kKT - 1) / kKT;
-  const float bias2 = (MODE == kModeNode && a.g.m > 0) ? log2f((float)w.nr.s / (float)a.g.m) : 0.f;
+  const float bias2 = (kNode && a.g.m > 0) ? log2f((float)w.nr.s / (float)a.g.m) : 0.f;
   stamp(1);
 
   // ---- tile movers ----
@@ -162,7 +164,7 @@ __global__ __launch_bounds__(64 * NW, (D == 64 && NW == 4) ? 3 : 2) void attn_mf
   // (row * row_bytes + column, from the key list in node mode, fixed in exact
   // mode) plus a scalar offset that advances with the tile.  Offsets past the
   // end of the head's tensor return zeros (such keys are masked by position).
-  const uint32_t head_bytes = (uint32_t)((MODE == kModeNode ? a.g.n : a.exact_rows_k) * (D * 2));
+  const uint32_t head_bytes = (uint32_t)((kNode ? a.g.n : a.exact_rows_k) * (D * 2));
   const __amdgpu_buffer_rsrc_t krsrc = __builtin_amdgcn_make_buffer_rsrc((void*)Kh, 0, (int)head_bytes, 0x00020000);
   const __amdgpu_buffer_rsrc_t vrsrc = __builtin_amdgcn_make_buffer_rsrc((void*)Vh, 0, (int)head_bytes, 0x00020000);
   u32x4 kreg[TR::NKC], vreg[TR::NKC];
@@ -172,7 +174,7 @@ __global__ __launch_bounds__(64 * NW, (D == 64 && NW == 4) ? 3 : 2) void attn_mf
       const int c = tid + i * kNT;
       const int key = c / TR::CPR, col = c % TR::CPR;
       int voff, soff;
-      if (MODE == kModeNode) {
+      if (kNode) {
         voff = list[kt * kKT + key] * (D * 2) + col * 16;
         soff = 0;
       } else {
@@ -209,6 +211,13 @@ __global__ __launch_bounds__(64 * NW, (D == 64 && NW == 4) ? 3 : 2) void attn_mf
   // skipped.  Log2 domain.
   float m_run = -INFINITY;
   float l_run = 0.f;  // this lane's share of the row sum
+  // Cap mode (Algorithm 2 as printed): once the block's keys are done (tile nb_tiles on) l_run becomes the capped sum of
+  // the samples and msum keeps the masked row sum, from which the row's cap C_i follows.
+  // One more vector instruction per score than the plain node mode (420 us where this takes 500: 32 heads, n = 32768,
+  // d = 128, b = m = 256), against 600 in a kernel of its own without the software pipeline below.
+  const int nb_tiles = kCap ? (nb + kKT - 1) / kKT : 0;
+  float msum = 0.f, log2capw = INFINITY;  // log2 of (s / m) C_i
+  const float floor_term = kCap && a.kappa > 0.f ? a.log_tau[(int64_t)w.bh * a.g.total_nodes + w.nr.heap] - logf(a.kappa) : -INFINITY;
 
   // Masks of a score tile (rare tiles only): tail of the key list, causal
   // diagonal, and a tile that straddles the block / sampled boundary.  `bias` is
@@ -216,14 +225,14 @@ __global__ __launch_bounds__(64 * NW, (D == 64 && NW == 4) ? 3 : 2) void attn_mf
   auto mask_tile = [&](f32x16 (&c)[2], int t, float& bias) {
     const int key_base = t * kKT;
     const bool tail = key_base + kKT > nkeys;
-    const bool mixed = (key_base < nb) && (key_base + kKT > nb);
+    const bool mixed = (key_base < nb) && (key_base + kKT > nb);  // (cap mode: the block's last, padded tile)
     const bool diag = (MODE == kModeExact) && a.exact_causal && (w.k0 + key_base + kKT - 1 > w.q0 + wave * 32);
     bias = (key_base >= nb) ? bias2 : 0.f;
     if (tail || mixed || diag) {
-      int lim = nkeys;
+      int lim = kCap && mixed ? nb : nkeys;
       if (MODE == kModeExact && a.exact_causal) lim = min(lim, q_global - w.k0 + 1);
       const int lim2 = lim - key_base - 4 * h;  // element i is masked iff koff_i >= lim2
-      const int nb2 = mixed ? nb - key_base - 4 * h : 0x7fffffff;
+      const int nb2 = !kCap && mixed ? nb - key_base - 4 * h : 0x7fffffff;
       const float nat_bias = bias2 * kLn2;
 #pragma unroll
       for (int sub = 0; sub < 2; ++sub)
@@ -306,7 +315,22 @@ __global__ __launch_bounds__(64 * NW, (D == 64 && NW == 4) ? 3 : 2) void attn_mf
 #pragma unroll
         for (int i = 0; i < 16; ++i) o[dt][i] *= alpha;
       l_run *= alpha;
+      if (kCap) msum *= alpha;
       m_run = m_new;
+    }
+    float capw = INFINITY;
+    if constexpr (kCap) {
+      if (kt == nb_tiles) {
+        const float mt = l_run + __shfl_xor(l_run, 32);
+        const float log_masked = (mt > 0.f) ? (m_run + log2f(mt)) * kLn2 : -INFINITY;
+        msum = l_run;
+        l_run = 0.f;
+        if (a.cap_scale > 0.f) {
+          const float n = (float)w.nr.s;
+          log2capw = (logf(a.cap_scale * (float)a.g.m / (n * logf(n))) + logaddexpf(log_masked, floor_term)) * kLog2e + bias2;
+        }
+      }
+      if (kt >= nb_tiles) capw = __builtin_amdgcn_exp2f(fminf(log2capw - ((m_run == -INFINITY) ? 0.f : m_run), 120.f));
     }
     const float shift = bias - ((m_run == -INFINITY) ? 0.f : m_run);
 
@@ -354,7 +378,7 @@ __global__ __launch_bounds__(64 * NW, (D == 64 && NW == 4) ? 3 : 2) void attn_mf
           for (int e = 0; e < 4; ++e) {
             const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(c[sub][8 * jj + 2 * e], kLog2e, shift));
             const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(c[sub][8 * jj + 2 * e + 1], kLog2e, shift));
-            ls[e] += p0 + p1;
+            ls[e] += kCap ? fminf(p0, capw) + fminf(p1, capw) : p0 + p1;
             pk[e] = pack_bf16x2(p0, p1);
           }
           pf[2 * sub + jj] = __builtin_bit_cast(bf16x8, pk);
@@ -434,10 +458,20 @@ __global__ __launch_bounds__(64 * NW, (D == 64 && NW == 4) ? 3 : 2) void attn_mf
   stamp(3);
 
   // ---- epilogue ----
+  if (kCap && ntiles <= nb_tiles) {  // no sample was kept
+    msum = l_run;
+    l_run = 0.f;
+  }
   const float l_tot = l_run + __shfl_xor(l_run, 32);
   const bool empty = !(l_tot > 0.f);
-  const float inv = empty ? 0.f : 1.f / l_tot;
+  float inv = empty ? 0.f : 1.f / l_tot;
   float lse_own = empty ? -INFINITY : (m_run + log2f(l_tot)) * kLn2;
+  if constexpr (kCap) {  // d~_i = masked + max(d_i, tau / kappa)
+    const float mt = msum + __shfl_xor(msum, 32);
+    const float log_masked = (mt > 0.f) ? (m_run + log2f(mt)) * kLn2 : -INFINITY;
+    lse_own = logaddexpf(log_masked, fmaxf(lse_own, floor_term));
+    inv = (m_run == -INFINITY || lse_own == -INFINITY) ? 0.f : expf(m_run * kLn2 - lse_own);
+  }
   // Where the row goes: a partial result of the causal recursion (node mode) or
   // the final output; in exact mode the partial results of every level of
   // Algorithm 4 are folded in first (row sum = D_21 + D_C22 at every split).
@@ -445,7 +479,7 @@ __global__ __launch_bounds__(64 * NW, (D == 64 && NW == 4) ? 3 : 2) void attn_mf
   // The wave's 32 rows are transposed through LDS in fp32 (free now: the last
   // barrier of the loop is behind every wave), so that rows leave, and partial
   // rows arrive, as whole 16-byte pieces on consecutive lanes.
-  const bool to_partial = (MODE == kModeNode) && a.part_o != nullptr;
+  const bool to_partial = (kNode) && a.part_o != nullptr;
   unsigned char* ep = smem + wave * EpLds<D>::WAVE;
   float* ep_w = reinterpret_cast<float*>(ep + 32 * EpLds<D>::ROW);
   int64_t* ep_rows = reinterpret_cast<int64_t*>(ep + 32 * EpLds<D>::ROW + 32 * kMaxFold * 4);
@@ -661,7 +695,7 @@ __global__ __launch_bounds__(64 * NW, (D == 64 && NW == 4) ? 3 : 2) void attn_mf
 
 template <int D, int MODE, int NW, bool STAMPS = false>
 static int launch_one(const AttnArgs& a, hipStream_t st) {
-  const int64_t grid = MODE == kModeNode ? node_grid<32 * NW>(a.g) : exact_grid<32 * NW>(a);
+  const int64_t grid = MODE != kModeExact ? node_grid<32 * NW>(a.g) : exact_grid<32 * NW>(a);
   if (grid <= 0) return HA_OK;
   if (grid > kMaxGrid) return HA_ERR_SHAPE;
   size_t lds = mfma_lds_bytes<D>(a.g.b, a.g.m, MODE);
@@ -705,10 +739,12 @@ int launch_attn_mfma(const AttnArgs& a, int mode, hipStream_t st) {
                     a.exact_block >= kWideExactMinRows && a.exact_rows_q >= kWideExactMinRows;
   if (a.g.d == 128) {
     if (mode == kModeNode) return launch_one<128, kModeNode, HA_NW_NODE>(a, st);
+    if (mode == kModeCap) return launch_one<128, kModeCap, HA_NW_NODE>(a, st);
     return wide ? launch_one<128, kModeExact, 8>(a, st) : launch_one<128, kModeExact, HA_NW_EXACT>(a, st);
   }
   if (a.g.d == 64) {
     if (mode == kModeNode) return launch_one<64, kModeNode, HA_NW_NODE>(a, st);
+    if (mode == kModeCap) return launch_one<64, kModeCap, HA_NW_NODE>(a, st);
     return launch_one<64, kModeExact, HA_NW_EXACT>(a, st);  // no gain from the wide form at d = 64
   }
   return HA_ERR_SHAPE;

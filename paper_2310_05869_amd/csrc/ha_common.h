@@ -78,6 +78,7 @@ __host__ __device__ inline NodeRef node_ref(const Geometry& g, int level, int no
 enum AttnMode : int32_t {
   kModeNode = 0,   // unmasked node(s): block keys by list + kept sampled keys
   kModeExact = 1,  // contiguous keys, optional causal mask (exact attention / causal base case)
+  kModeCap = 2,    // node mode with Algorithm 2's cap on every sampled entry and its lower cap (bf16)
 };
 
 struct AttnArgs {
@@ -103,6 +104,9 @@ struct AttnArgs {
   int64_t out_bh_stride;  // elements between heads of `out` ; lse stride = out_bh_stride / d
   int32_t scatter_out;    // node mode: 1 => write row perm_q[p], 0 => write sorted position p
   Geometry g;
+  // cap mode: log tau of every node [BH][total_nodes], the constant of C_i and kappa (<= 0: that cap is off)
+  const float* log_tau;
+  float cap_scale, kappa;
   // exact mode
   int32_t exact_rows_q, exact_rows_k;  // rows per head (full problem)
   int32_t exact_block;                 // rows per independent diagonal block (== rows for full attention)

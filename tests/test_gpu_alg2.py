@@ -171,3 +171,14 @@ def test_alg2_rejects_bad_arguments(ha, torch):
     out, lse, _ = ha.hyperattn_forward_alg2(q, q, q, 64, 16, 7, causal=True, n_min=256, cap_scale=2.0, kappa=1.5)
     ref, _ = ha.exact_attn_forward(q, q, q, causal=True)
     assert torch.equal(out.view(torch.int16), ref.view(torch.int16))
+
+
+@pytest.mark.parametrize("dtype,d,n,b,m,r,cap_scale,kappa,vnorm", [
+    ("bf16", 64, 300, 100, 130, 4, 6.0, 1.3, False),    # a block's last tile padded after a full one
+    ("bf16", 128, 256, 256, 40, 5, 0.0, 0.0, False),    # one block: no sample is kept, every row of T sums nothing
+    ("bf16", 64, 48, 16, 33, 3, 5.0, 1.2, False),       # one key tile, seven of eight ranges empty
+    ("bf16", 128, 2080, 65, 300, 6, 6.0, 1.4, False),   # ranges of four and five tiles, the last ragged; blocks across tiles
+    ("bf16", 64, 2080, 65, 257, 6, 0.0, 1.4, False)])   # lower cap alone, three row tiles, the last of one row
+def test_alg2_caps_in_the_node_kernel(ha, torch, dtype, d, n, b, m, r, cap_scale, kappa, vnorm):
+    """The forward kernel's cap mode and the sorted walk of the rows of T at the edges of their tiles: criteria as above."""
+    test_alg2_options_match_the_oracle(ha, torch, dtype, d, n, b, m, r, cap_scale, kappa, vnorm)

@@ -39,20 +39,27 @@ __device__ inline int logical_block(int bid, int total) {
 }
 
 template <int QT>
+inline void set_node_divs(AttnArgs& a) {
+  const Geometry& g = a.g;
+  const int tpb = (g.b + QT - 1) / QT;
+  a.div_tpl = make_fast_div((int64_t)(g.n_cov / g.b) * tpb);
+  a.div_bh = make_fast_div(g.BH);
+  a.div_tpb = make_fast_div(tpb);
+  a.div_unit = make_fast_div(g.causal ? g.n_min / g.b : g.n / g.b);  // a node of level l: 2^(levels - 1 - l) times as many
+}
+
+template <int QT>
 __device__ inline TileWork decode_node_tile(const AttnArgs& a, int idx) {
   const Geometry& g = a.g;
   TileWork w{};
-  const int tpb = (g.b + QT - 1) / QT;  // tiles per block
-  const int tiles_per_level = (g.n_cov / g.b) * tpb;
-  const int tile = idx % tiles_per_level;
-  const int rest = idx / tiles_per_level;
-  w.bh = rest % g.BH;
-  w.level = rest / g.BH;
-  const int blk = tile / tpb, chunk = tile % tpb;
-  const NodeRef probe = node_ref(g, w.level, 0);
-  const int bpn = probe.s / g.b;  // blocks per node
-  const int node = blk / bpn;
-  w.t = blk % bpn;
+  const int rest = a.div_tpl.div(idx);
+  const int tile = idx - rest * (int)a.div_tpl.d;
+  w.level = a.div_bh.div(rest);
+  w.bh = rest - w.level * g.BH;
+  const int blk = a.div_tpb.div(tile), chunk = tile - blk * (int)a.div_tpb.d;
+  const int below = g.levels - 1 - w.level;
+  const int node = a.div_unit.div(blk >> below);
+  w.t = blk - ((node * (int)a.div_unit.d) << below);
   w.nr = node_ref(g, w.level, node);
   w.p0 = w.t * g.b + chunk * QT;
   w.rows_valid = min(QT, g.b - chunk * QT);
@@ -221,7 +228,7 @@ __device__ inline int build_key_list(const AttnArgs& a, const TileWork& w, int32
     }
     if (keep) list[base + before + __popcll(bal & ((1ull << lane) - 1ull))] = w.nr.k_start + l;
     base += total;
-    __syncthreads();
+    if (j0 + NT < m) __syncthreads();  // before the counters are written again
   }
   const int nkeys = base;
   const int pad = (nkeys + 63) & ~63;
@@ -272,7 +279,7 @@ __device__ inline RowDest node_row_dest(const AttnArgs& a, const TileWork& w, in
   const int p = w.p0 + (d.valid ? r_in_tile : 0);
   const int row = (a.scatter_out && a.perm_q) ? a.perm_q[w.seg_off + p] : w.nr.q_start + p;
   d.row_in_head = row;
-  d.out_row = (int64_t)w.bh * (a.out_bh_stride / a.g.d) + row;
+  d.out_row = (int64_t)w.bh * a.g.n + row;
   d.part_row = w.seg_off + (row - w.nr.q_start);
   return d;
 }

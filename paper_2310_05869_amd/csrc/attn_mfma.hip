@@ -694,7 +694,9 @@ __global__ __launch_bounds__(64 * NW, (D == 64 && NW == 4) ? 3 : 2) void attn_mf
 }
 
 template <int D, int MODE, int NW, bool STAMPS = false>
-static int launch_one(const AttnArgs& a, hipStream_t st) {
+static int launch_one(const AttnArgs& args, hipStream_t st) {
+  AttnArgs a = args;
+  if (MODE != kModeExact) set_node_divs<32 * NW>(a);
   const int64_t grid = MODE != kModeExact ? node_grid<32 * NW>(a.g) : exact_grid<32 * NW>(a);
   if (grid <= 0) return HA_OK;
   if (grid > kMaxGrid) return HA_ERR_SHAPE;

@@ -81,6 +81,26 @@ enum AttnMode : int32_t {
   kModeCap = 2,    // node mode with Algorithm 2's cap on every sampled entry and its lower cap (bf16)
 };
 
+// Division of 0 <= n < 2^31 by a divisor known on the host: two scalar multiplications and a shift, where
+// a division by a kernel argument is some thirty vector instructions.  A node workgroup's place took eight of them (and a
+// 64-bit one) ahead of its first load.  Measured (MI355X) with one barrier less in the key list: forward + backward,
+// 12 heads, n = 16384, d = 64: 234.7 -> 231.8 us; forward, 15 heads, n = 6300, d = 128: 54.3 -> 53.5; 64 heads,
+// n = 65536, d = 64: 1363 -> 1353; others within 0.5 %.
+struct FastDiv {
+  uint32_t mul, shift, d;
+  __host__ __device__ inline int div(int n) const { return (int)(((uint64_t)(uint32_t)n * mul) >> shift); }
+  __host__ __device__ inline int mod(int n) const { return n - div(n) * (int)d; }
+};
+inline FastDiv make_fast_div(int64_t divisor) {  // 1 <= divisor < 2^31: mul = ceil(2^shift / divisor) < 2^32, 2^shift >= 2^31 divisor
+  FastDiv f;
+  f.d = (uint32_t)(divisor < 1 ? 1 : divisor);
+  uint32_t log = 0;
+  while ((1ull << log) < f.d) ++log;
+  f.shift = 31 + log;
+  f.mul = (uint32_t)(((1ull << f.shift) + f.d - 1) / f.d);
+  return f;
+}
+
 struct AttnArgs {
   const void* Q;  // [BH][rows_q][d]
   const void* K;  // [BH][rows_k][d]
@@ -104,6 +124,8 @@ struct AttnArgs {
   int64_t out_bh_stride;  // elements between heads of `out` ; lse stride = out_bh_stride / d
   int32_t scatter_out;    // node mode: 1 => write row perm_q[p], 0 => write sorted position p
   Geometry g;
+  // node mode, set by the launchers (set_node_divs): tiles per level, heads, tiles per block, blocks of the last level's nodes
+  FastDiv div_tpl, div_bh, div_tpb, div_unit;
   // cap mode: log tau of every node [BH][total_nodes], the constant of C_i and kappa (<= 0: that cap is off)
   const float* log_tau;
   float cap_scale, kappa;

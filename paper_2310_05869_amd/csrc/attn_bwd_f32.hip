@@ -21,7 +21,9 @@
 // What bounds it: the matrix pipe.  Measured (MI355X, backward of exact attention, the five algorithmic products
 // counted, seven executed), against two lanes per row with fp32 FMA and separate dK and dV passes, the form before:
 // 8 heads, n = 4096, d = 64 5.5 -> 1.29 ms, d = 128 12.0 -> 2.4 ms; 32 heads, n = 8192, d = 64 17.1 ms = 80 TFLOP/s
-// (112 executed, of 157); 4 causal heads, n = 4096, n_min = 1024, forward + backward 4.07 -> 0.45 ms.
+// (112 executed, of 157); 4 causal heads, n = 4096, n_min = 1024, forward + backward 4.07 -> 0.45 ms.  Then the vector
+// work beside the products (masks behind a branch; in the exact passes row addresses in the instructions' offsets and
+// L, delta as four values per load instead of lane exchanges): there dQ 51 -> 45, dK / dV 68 -> 61 us.
 #include "attn_common.h"
 #include "bwd_common.h"
 
@@ -61,7 +63,7 @@ __global__ __launch_bounds__(kFBT, D == 64 ? 2 : 1) void attn_bwd_f32_kernel(Bwd
   const AttnArgs& f = a.f;
   const Geometry& g = f.g;
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lq = lane & 31, h = lane >> 5;
   const int kw = wave % KW, grp = wave / KW;
   int32_t* scratch = reinterpret_cast<int32_t*>(smem);
@@ -123,15 +125,18 @@ __global__ __launch_bounds__(kFBT, D == 64 ? 2 : 1) void attn_bwd_f32_kernel(Bwd
   if (MODE == kBwdDqExact && f.exact_causal) kt_hi = min(kt_hi, (w.q0 - w.k0 + grp * 32 + 31) / kFTT + 1);
   if (MODE == kBwdDkvExact && f.exact_causal) kt_lo = grp;  // T starts at the workgroup's first key
   auto t_row = [&](int kt) -> int {  // row within the head of T position kt * 32 + lq (clamped to an existing one)
+    if (kExact) return w.k0 + kt * kFTT + lq;
     const int tp = min(kt * kFTT + lq, nT - 1);
-    if (kExact) return w.k0 + tp;
     if (kSorted) return tperm[tp];
     return list[tp];
   };
 
-  const uint32_t bytes = (uint32_t)g.n * (uint32_t)(D * 4);
+  // (exact passes: rows past the T rows' end read as zeros and are masked)
+  const uint32_t bytes = (uint32_t)(kExact ? w.k1 : g.n) * (uint32_t)(D * 4);
   const __amdgpu_buffer_rsrc_t yrsrc = __builtin_amdgcn_make_buffer_rsrc((void*)Yh, 0, (int)bytes, 0x00020000);
   const __amdgpu_buffer_rsrc_t brsrc = __builtin_amdgcn_make_buffer_rsrc((void*)Bh, 0, (int)bytes, 0x00020000);
+  const __amdgpu_buffer_rsrc_t lrsrc = __builtin_amdgcn_make_buffer_rsrc((void*)lse_h, 0, (kExact ? w.k1 : g.n) * 4, 0x00020000);
+  const __amdgpu_buffer_rsrc_t drsrc = __builtin_amdgcn_make_buffer_rsrc((void*)del_h, 0, (kExact ? w.k1 : g.n) * 4, 0x00020000);
   auto load_rows = [&](const __amdgpu_buffer_rsrc_t& rsrc, int row, f32x4 (&v)[KJ]) {
 #pragma unroll
     for (int j = 0; j < KJ; ++j)
@@ -139,7 +144,16 @@ __global__ __launch_bounds__(kFBT, D == 64 ? 2 : 1) void attn_bwd_f32_kernel(Bwd
   };
   // element i of an accumulator is T row 8 (i / 4) + 4 h + i % 4 of the tile; lane l < 32 holds row l's values
   auto of_elem = [&](auto v, int i) { return __shfl(v, 8 * (i / 4) + 4 * h + (i % 4)); };
-  auto load_cols = [&](const __amdgpu_buffer_rsrc_t& rsrc, int row, float (&v)[16][DT], int i0, int count) {
+  auto load_cols = [&](const __amdgpu_buffer_rsrc_t& rsrc, int row, int kt, float (&v)[16][DT], int i0, int count) {
+    if (kExact) {  // consecutive rows: one address, the rest in the instructions' offsets
+      const int off = (w.k0 + kt * kFTT + 4 * h) * (D * 4) + 4 * lq;
+#pragma unroll
+      for (int i = i0; i < i0 + count; ++i)
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+          v[i][dt] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, off + (i % 4) * (D * 4) + 128 * dt, 8 * (i / 4) * (D * 4), 0));
+      return;
+    }
 #pragma unroll
     for (int i = i0; i < i0 + count; ++i) {
       const int off = of_elem(row, i) * (D * 4) + 4 * lq;
@@ -163,7 +177,7 @@ __global__ __launch_bounds__(kFBT, D == 64 ? 2 : 1) void attn_bwd_f32_kernel(Bwd
   auto fetch = [&](int kt) {
     row = t_row(kt);
     load_rows(yrsrc, row, yf);
-    if (!kDq) {
+    if (!kDq && !kExact) {
       sc_l = lse_h[row];
       sc_d = del_h[row];
     }
@@ -172,6 +186,15 @@ __global__ __launch_bounds__(kFBT, D == 64 ? 2 : 1) void attn_bwd_f32_kernel(Bwd
   for (int kt = kt_lo + kw; kt < kt_hi; kt += KW) {
     const int row_c = row;
     const float scl = sc_l, scd = sc_d;
+    f32x4 l4[4], d4[4];  // dK / dV of exact attention: L and delta of the lane's T rows, four consecutive ones at a time
+    if (kExact && !kDq) {
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        const int at = (w.k0 + kt * kFTT + 8 * q4 + 4 * h) * 4;
+        l4[q4] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(lrsrc, at, 0, 0));
+        d4[q4] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(drsrc, at, 0, 0));
+      }
+    }
     f32x4 bf[KJ];
     load_rows(brsrc, row_c, bf);
     f32x16 c, e;
@@ -185,29 +208,43 @@ __global__ __launch_bounds__(kFBT, D == 64 ? 2 : 1) void attn_bwd_f32_kernel(Bwd
 #pragma unroll
       for (int z = 0; z < 4; ++z) c = __builtin_amdgcn_mfma_f32_32x32x2f32(yf[j][z], x[j][z], c, 0, 0, 0);
     float tv[16][DT];
-    load_cols(kDq ? yrsrc : brsrc, row_c, tv, 0, 16);
+    load_cols(kDq ? yrsrc : brsrc, row_c, kt, tv, 0, 16);
 #pragma unroll
     for (int j = 0; j < KJ; ++j)
 #pragma unroll
       for (int z = 0; z < 4; ++z) e = __builtin_amdgcn_mfma_f32_32x32x2f32(bf[j][z], av[j][z], e, 0, 0, 0);
 
+    // masks, on the tiles that have any: in the sampled-key pass the keys differ by lane
     const int tbase = kt * kFTT;
+    bool special = tbase + kFTT > nT;
+    if (MODE == kBwdDqNode) special = special || (tbase < nb && tbase + kFTT > nb);
+    if (MODE == kBwdDqExact && f.exact_causal) special = special || (w.k0 + tbase + kFTT - 1 > w.q0 + grp * 32);
+    if (MODE == kBwdDkvExact && f.exact_causal) special = special || (w.k0 + tbase < w.q0 + grp * 32 + 31);
+    if (MODE == kBwdDkvSamp) {
+      const int mlo = blk_r * g.b - (b.chunk_start + tbase);
+      special = special || __any(mlo < kFTT && mlo + g.b > 0);
+    }
+    float tile_bias = MODE == kBwdDkvSamp ? nat_bias : 0.f;
+    if (MODE == kBwdDqNode && tbase >= nb) tile_bias = nat_bias;
+    if (special) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int tpos = tbase + 8 * (i / 4) + 4 * h + (i % 4);
+        bool masked = tpos >= nT;
+        if (MODE == kBwdDqNode && tbase < nb && tpos >= nb) c[i] += nat_bias;
+        // queries of the key's own block: factor 1 - M of Algorithm 2
+        if (MODE == kBwdDkvSamp) masked = masked || (unsigned)(b.chunk_start + tpos - blk_r * g.b) < (unsigned)g.b;
+        if (MODE == kBwdDqExact && f.exact_causal) masked = masked || (w.k0 + tpos > r_row);   // keys after the query
+        if (MODE == kBwdDkvExact && f.exact_causal) masked = masked || (w.k0 + tpos < r_row);  // queries before the key
+        if (masked) c[i] = -INFINITY;
+      }
+    }
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-      const int tpos = tbase + 8 * (i / 4) + 4 * h + (i % 4);
-      bool masked = tpos >= nT;
-      float bias = 0.f;
-      if (MODE == kBwdDqNode) bias = tpos >= nb ? nat_bias : 0.f;
-      if (MODE == kBwdDkvSamp) {
-        bias = nat_bias;
-        // queries of the key's own block: factor 1 - M of Algorithm 2
-        masked = masked || (unsigned)(b.chunk_start + tpos - blk_r * g.b) < (unsigned)g.b;
-      }
-      if (MODE == kBwdDqExact && f.exact_causal) masked = masked || (w.k0 + tpos > r_row);   // keys after the query
-      if (MODE == kBwdDkvExact && f.exact_causal) masked = masked || (w.k0 + tpos < r_row);  // queries before the key
-      const float L = kDq ? L_r : of_elem(scl, i);
-      const float dl = kDq ? del_r : of_elem(scd, i);
-      const float p = (masked || L == -INFINITY) ? 0.f : expf(c[i] + bias - L);
+      const float L = kDq ? L_r : kExact ? l4[i / 4][i % 4] : of_elem(scl, i);
+      const float dl = kDq ? del_r : kExact ? d4[i / 4][i % 4] : of_elem(scd, i);
+      float p = exp_split(c[i] + tile_bias - L);
+      if (L == -INFINITY) p = 0.f;  // (a row without keys)
       c[i] = p;
       e[i] = p * (e[i] - dl);
     }
@@ -216,7 +253,7 @@ __global__ __launch_bounds__(kFBT, D == 64 ? 2 : 1) void attn_bwd_f32_kernel(Bwd
       float yv[16][DT];
 #pragma unroll
       for (int hf = 0; hf < 2; ++hf) {
-        load_cols(yrsrc, row_c, yv, 8 * hf, 8);
+        load_cols(yrsrc, row_c, kt, yv, 8 * hf, 8);
 #pragma unroll
         for (int i = 8 * hf; i < 8 * hf + 8; ++i)
 #pragma unroll

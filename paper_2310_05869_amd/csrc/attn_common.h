@@ -244,6 +244,17 @@ __device__ inline int build_key_list(const AttnArgs& a, const TileWork& w, int32
   return build_key_list<NT>(a, w, list, scratch, nb_out, key_list_fetch<NT>(a, w));
 }
 
+// e^x to one or two units in the last place, like the library's, in seven instructions against its thirteen: the
+// hardware's 2^t at t = fl(x log2 e), times 1 + r ln 2 for what the rounding of t left out, r = x log2 e - t.
+// (r is bounded so that x = -inf gives 0; results below 2^-126 are 0; NaN stays NaN.)
+__device__ inline float exp_split(float x) {
+  constexpr float kHi = 1.44269502f, kLo = 1.92596303e-8f;  // log2 e = kHi + kLo
+  const float t = x * kHi;
+  const float r = __builtin_fmaf(x, kLo, __builtin_fmaf(x, kHi, -t));
+  const float e = __builtin_amdgcn_exp2f(t);
+  return __builtin_fmaf(e * __builtin_amdgcn_fmed3f(r, -1.f, 1.f), kLn2, e);
+}
+
 __device__ inline float logaddexpf(float x, float y) {
   const float hi = fmaxf(x, y), lo = fminf(x, y);
   if (hi == -INFINITY) return -INFINITY;

@@ -718,10 +718,14 @@ static int launch_one(const AttnArgs& args, hipStream_t st) {
 #define HA_NW_EXACT 4
 #endif
 
-// Exact attention over long key ranges, causal or not, shares each K / V tile among 8
-// waves (one workgroup per CU): 3-4 % faster there at d = 128; the short
-// loops of the base case prefer two 4-wave workgroups per CU.
+// Exact attention over long key ranges shares each K / V tile among 8 waves (one workgroup per CU) at d = 128: 3-6 %
+// faster where that leaves every CU a workgroup, and causal ones, of unequal length, several; with fewer, twice as many
+// 4-wave workgroups reach the idle CUs.  8 waves -> 4 waves (MI355X, d = 128), unmasked: 8 heads, n = 8192 (256 wide
+// workgroups) 243 -> 259 us, 2 heads, n = 16384 (128) 361 -> 288, one head (64) 358 -> 268; causal: 4 heads,
+// n = 16384 (256) 370 -> 310, 8 heads (512) 578 -> 540, 16 heads (1024) 1032 -> 1029.
+// The short loops of the base case prefer two 4-wave workgroups per CU.
 constexpr int kWideExactMinRows = 8192;
+constexpr int64_t kWideExactMinGrid = 256, kWideExactMinGridCausal = 1024;
 
 int64_t attn_mfma_grid(const AttnArgs& a, int mode) {
   return mode == kModeNode ? node_grid<32 * HA_NW_NODE>(a.g) : exact_grid<32 * HA_NW_EXACT>(a);
@@ -738,7 +742,8 @@ int launch_attn_mfma(const AttnArgs& a, int mode, hipStream_t st) {
     return HA_ERR_SHAPE;
   }
   const bool wide = mode == kModeExact && a.merge_levels == 0 &&
-                    a.exact_block >= kWideExactMinRows && a.exact_rows_q >= kWideExactMinRows;
+                    a.exact_block >= kWideExactMinRows && a.exact_rows_q >= kWideExactMinRows &&
+                    exact_grid<256>(a) >= (a.exact_causal ? kWideExactMinGridCausal : kWideExactMinGrid);
   if (a.g.d == 128) {
     if (mode == kModeNode) return launch_one<128, kModeNode, HA_NW_NODE>(a, st);
     if (mode == kModeCap) return launch_one<128, kModeCap, HA_NW_NODE>(a, st);

@@ -737,3 +737,24 @@ def test_node_sort_is_the_stable_order(ha, torch, H, n, b, r, causal, n_min):
             heap = 2 ** level - 1 + node
             smp = v["samples"].view(-1, m)[heap].long()
             assert torch.equal(v["samp_blk"].view(H, -1, m)[:, heap].long(), pos[:, smp] // b)
+
+
+@pytest.mark.parametrize("H,n,causal", [(8, 8192, False), (7, 8192, False), (32, 8192, True), (31, 8192, True), (9, 8200, False)])
+def test_exact_attention_around_the_wide_form(ha, torch, H, n, causal):
+    """The 8-wave form of exact attention at d = 128 starts at 256 (causal: 1024) workgroups of 256 rows: both sides of
+    the line, rows of every kind of tile against fp32 attention; criterion: the plain one of the forward."""
+    print(f"wide exact H={H} n={n} causal={causal}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(H)
+    Q, K, V = ((torch.randn((1, H, n, 128), generator=gen, device="cuda") * 128 ** -0.25).to(torch.bfloat16) for _ in range(3))
+    out = torch.full_like(Q, float("nan"))
+    out, lse = ha.exact_attn_forward(Q, K, V, causal=causal, out=out)
+    assert torch.isfinite(out).all()
+    rows = torch.tensor([0, 1, 127, 128, 255, 256, 4095, 4096, n - 129, n - 1], device="cuda")
+    for hd in (0, H - 1):
+        s = Q[0, hd][rows].float() @ K[0, hd].float().T.contiguous()
+        if causal:
+            s = s.masked_fill(torch.arange(n, device="cuda")[None, :] > rows[:, None], float("-inf"))
+        ref = s.softmax(-1) @ V[0, hd].float()
+        assert_close(to_host(out[0, hd][rows]), ref.double().cpu().numpy(), "bf16", f"out head {hd}")
+        assert_lse_close(to_host(lse[0, hd][rows]), s.logsumexp(-1).double().cpu().numpy(), "bf16", f"lse head {hd}")

@@ -79,24 +79,27 @@ struct TileRegs {
 // NW waves per workgroup (32 queries each); two waves per SIMD at d = 128, three (four-wave workgroups) at d = 64.
 // STAMPS: the measuring instantiation, which also records counter readings at its phase
 // boundaries (a.stamps); the product launches use STAMPS = false and carry none of it.
-template <int D, int MODE, int NW, bool STAMPS = false>
-__global__ __launch_bounds__(64 * NW, (D == 64 && NW == 4) ? 3 : 2) void attn_mfma_kernel(AttnArgs a) {
+// NG = 2 (exact mode): two groups of NW waves take the key tiles in turn, each with tile buffers of its own, and their
+// results are merged through LDS.
+template <int D, int MODE, int NW, bool STAMPS = false, int NG = 1>
+__global__ __launch_bounds__(64 * NW * NG, (D == 64 && NW == 4 && NG == 1) ? 3 : 2) void attn_mfma_kernel(AttnArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   constexpr bool kCap = MODE == kModeCap;
   constexpr bool kNode = MODE == kModeNode || kCap;
   constexpr int kQT = 32 * NW;  // queries per workgroup
-  constexpr int kNT = 64 * NW;  // threads
+  constexpr int kNT = 64 * NW;  // threads of a group
   using L = Lds<D>;
   using TR = TileRegs<D, kNT>;
   constexpr int KS = D / 16;  // MFMA k-steps of the score product
   constexpr int DT = D / 32;  // 32-wide d tiles of the output
 
-  const int tid = threadIdx.x;
+  const int tid = NG == 1 ? threadIdx.x : threadIdx.x % kNT;
+  const int grp = NG == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / kNT);
   const int lane = tid & 63, wave = tid >> 6;
   const int lq = lane & 31, h = lane >> 5;
 
-  unsigned char* bufs = smem;
-  int32_t* scratch = reinterpret_cast<int32_t*>(smem + 2 * L::BUF);
+  unsigned char* bufs = smem + grp * 2 * L::BUF;
+  int32_t* scratch = reinterpret_cast<int32_t*>(smem + NG * 2 * L::BUF);
   int32_t* list = scratch + 16;
 
   long long stamp_c[5] = {0, 0, 0, 0, 0}, stamp_w = 0;
@@ -155,7 +158,7 @@ __global__ __launch_bounds__(64 * NW, (D == 64 && NW == 4) ? 3 : 2) void attn_mf
     nkeys = max(0, w.k1 - w.k0);
     nb = 0x7fffffff;
   }
-  const int ntiles = (nkeys + kKT - 1) / kKT;
+  const int ntiles = (nkeys + NG * kKT - 1) / (NG * kKT);  // of the group; its tile t is tile NG t + grp of the keys
   const float bias2 = (kNode && a.g.m > 0) ? log2f((float)w.nr.s / (float)a.g.m) : 0.f;
   stamp(1);
 
@@ -179,7 +182,7 @@ __global__ __launch_bounds__(64 * NW, (D == 64 && NW == 4) ? 3 : 2) void attn_mf
         soff = 0;
       } else {
         voff = key * (D * 2) + col * 16;
-        soff = (w.k0 + kt * kKT) * (D * 2);
+        soff = (w.k0 + (NG * kt + grp) * kKT) * (D * 2);
       }
       reg[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff, soff, 0);
     }
@@ -223,7 +226,7 @@ __global__ __launch_bounds__(64 * NW, (D == 64 && NW == 4) ? 3 : 2) void attn_mf
   // diagonal, and a tile that straddles the block / sampled boundary.  `bias` is
   // the tile-uniform log2-domain bias (log2(s/m) on sampled tiles).
   auto mask_tile = [&](f32x16 (&c)[2], int t, float& bias) {
-    const int key_base = t * kKT;
+    const int key_base = (NG * t + grp) * kKT;
     const bool tail = key_base + kKT > nkeys;
     const bool mixed = (key_base < nb) && (key_base + kKT > nb);  // (cap mode: the block's last, padded tile)
     const bool diag = (MODE == kModeExact) && a.exact_causal && (w.k0 + key_base + kKT - 1 > w.q0 + wave * 32);
@@ -457,6 +460,34 @@ __global__ __launch_bounds__(64 * NW, (D == 64 && NW == 4) ? 3 : 2) void attn_mf
   }
   stamp(3);
 
+  if constexpr (NG == 2) {  // the second group's sums through LDS (the tiles are read no more)
+    f32x4* part = reinterpret_cast<f32x4*>(smem + NW * EpLds<D>::WAVE) + tid;  // [4 DT][kNT], then references and row sums
+    float* ml = reinterpret_cast<float*>(reinterpret_cast<f32x4*>(smem + NW * EpLds<D>::WAVE) + 4 * DT * kNT) + tid;
+    if (grp == 1) {
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int g4 = 0; g4 < 4; ++g4)
+          part[(4 * dt + g4) * kNT] = (f32x4){o[dt][4 * g4], o[dt][4 * g4 + 1], o[dt][4 * g4 + 2], o[dt][4 * g4 + 3]};
+      ml[0] = m_run;
+      ml[kNT] = l_run;
+    }
+    __syncthreads();
+    if (grp == 1) return;
+    const float m1 = ml[0], m = fmaxf(m_run, m1), ref = (m == -INFINITY) ? 0.f : m;
+    const float w0 = __builtin_amdgcn_exp2f(m_run - ref), w1 = __builtin_amdgcn_exp2f(m1 - ref);
+    l_run = l_run * w0 + ml[kNT] * w1;
+    m_run = m;
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+      for (int g4 = 0; g4 < 4; ++g4) {
+        const f32x4 v = part[(4 * dt + g4) * kNT];
+#pragma unroll
+        for (int z = 0; z < 4; ++z) o[dt][4 * g4 + z] = o[dt][4 * g4 + z] * w0 + v[z] * w1;
+      }
+  }
+
   // ---- epilogue ----
   if (kCap && ntiles <= nb_tiles) {  // no sample was kept
     msum = l_run;
@@ -688,23 +719,24 @@ __global__ __launch_bounds__(64 * NW, (D == 64 && NW == 4) ? 3 : 2) void attn_mf
       // where it ran: the hardware id register (wave, SIMD, CU, shader engine) and the XCD number
       const unsigned hw = __builtin_amdgcn_s_getreg(4 | (0 << 6) | (31 << 11));   // HW_ID, all 32 bits
       const unsigned xcc = __builtin_amdgcn_s_getreg(20 | (0 << 6) | (3 << 11));  // XCC_ID, bits 0-3
-      rec[7] = (long long)(ntiles & 0xffff) | ((long long)hw << 16) | ((long long)(xcc & 15u) << 48);
+      rec[7] = (long long)(((nkeys + kKT - 1) / kKT) & 0xffff) | ((long long)hw << 16) | ((long long)(xcc & 15u) << 48);
     }
   }
 }
 
-template <int D, int MODE, int NW, bool STAMPS = false>
+template <int D, int MODE, int NW, bool STAMPS = false, int NG = 1>
 static int launch_one(const AttnArgs& args, hipStream_t st) {
   AttnArgs a = args;
   if (MODE != kModeExact) set_node_divs<32 * NW>(a);
   const int64_t grid = MODE != kModeExact ? node_grid<32 * NW>(a.g) : exact_grid<32 * NW>(a);
   if (grid <= 0) return HA_OK;
   if (grid > kMaxGrid) return HA_ERR_SHAPE;
-  size_t lds = mfma_lds_bytes<D>(a.g.b, a.g.m, MODE);
-  if (lds < (size_t)NW * EpLds<D>::WAVE) lds = (size_t)NW * EpLds<D>::WAVE;
+  size_t lds = mfma_lds_bytes<D>(a.g.b, a.g.m, MODE) + (NG - 1) * 2 * (size_t)Lds<D>::BUF;
+  const size_t ep = (size_t)NW * EpLds<D>::WAVE + (NG - 1) * (size_t)(D / 8 * 16 + 8) * 64 * NW;
+  if (lds < ep) lds = ep;
   static std::atomic<uint64_t> lds_set{0};  // per instantiation: devices on which the LDS limit is raised
-  if (allow_full_lds(reinterpret_cast<const void*>(&attn_mfma_kernel<D, MODE, NW, STAMPS>), lds_set) != HA_OK) return HA_ERR_LAUNCH;
-  hipLaunchKernelGGL((attn_mfma_kernel<D, MODE, NW, STAMPS>), dim3((unsigned)grid), dim3(64 * NW), lds, st, a);
+  if (allow_full_lds(reinterpret_cast<const void*>(&attn_mfma_kernel<D, MODE, NW, STAMPS, NG>), lds_set) != HA_OK) return HA_ERR_LAUNCH;
+  hipLaunchKernelGGL((attn_mfma_kernel<D, MODE, NW, STAMPS, NG>), dim3((unsigned)grid), dim3(64 * NW * NG), lds, st, a);
   return check_launch();
 }
 
@@ -725,6 +757,13 @@ static int launch_one(const AttnArgs& args, hipStream_t st) {
 // n = 16384 (256) 370 -> 310, 8 heads (512) 578 -> 540, 16 heads (1024) 1032 -> 1029.
 // The short loops of the base case prefer two 4-wave workgroups per CU.
 constexpr int kWideExactMinRows = 8192;
+// Launches that leave a CU at most one workgroup (causal: up to one and a half, their tiles being unequal) are bound by
+// the longest chain of key tiles of a workgroup: two groups of four waves then share it.  One group -> two (MI355X):
+// 4 heads, n = 4096, d = 64 52.8 -> 41.2 us, d = 128 70.8 -> 59.3; one head, n = 16384, d = 64 202 -> 149, d = 128
+// 267 -> 215; causal, 12 heads, n = 4096 (384 workgroups) d = 64 54.3 -> 45.4, d = 128 77.0 -> 68.9; 14 heads (448)
+// 79.0 -> 82.9; unmasked, 12 heads 73.2 -> 83.5; base case of 4 heads, n = 8192, d = 64 (256): call 81.1 -> 69.2.
+constexpr int64_t kSplitExactMaxGrid = 256, kSplitExactMaxGridCausal = 384;
+constexpr int kSplitExactMinRows = 256;
 constexpr int64_t kWideExactMinGrid = 256, kWideExactMinGridCausal = 1024;
 
 int64_t attn_mfma_grid(const AttnArgs& a, int mode) {
@@ -734,11 +773,17 @@ int64_t attn_mfma_grid(const AttnArgs& a, int mode) {
 int launch_attn_mfma(const AttnArgs& a, int mode, hipStream_t st) {
   if (a.g.dtype != HA_BF16) return HA_ERR_DTYPE;
   if (mode == kModeExact && a.merge_levels > 0 && !a.part_bf16) return HA_ERR_DTYPE;  // this kernel folds bf16 partial rows
-  if (a.stamps != nullptr) {  // the measuring instantiations: the four-wave forms the forward pass launches
-    if (a.g.d == 128)
-      return mode == kModeNode ? launch_one<128, kModeNode, HA_NW_NODE, true>(a, st) : launch_one<128, kModeExact, HA_NW_EXACT, true>(a, st);
-    if (a.g.d == 64)
-      return mode == kModeNode ? launch_one<64, kModeNode, HA_NW_NODE, true>(a, st) : launch_one<64, kModeExact, HA_NW_EXACT, true>(a, st);
+  const bool split = mode == kModeExact && exact_grid<128>(a) <= (a.exact_causal ? kSplitExactMaxGridCausal : kSplitExactMaxGrid) &&
+                     a.exact_block >= kSplitExactMinRows && a.exact_rows_q >= kSplitExactMinRows;
+  if (a.stamps != nullptr) {  // the measuring instantiations of the forms the forward pass launches
+    if (a.g.d == 128) {
+      if (mode == kModeNode) return launch_one<128, kModeNode, HA_NW_NODE, true>(a, st);
+      return split ? launch_one<128, kModeExact, 4, true, 2>(a, st) : launch_one<128, kModeExact, HA_NW_EXACT, true>(a, st);
+    }
+    if (a.g.d == 64) {
+      if (mode == kModeNode) return launch_one<64, kModeNode, HA_NW_NODE, true>(a, st);
+      return split ? launch_one<64, kModeExact, 4, true, 2>(a, st) : launch_one<64, kModeExact, HA_NW_EXACT, true>(a, st);
+    }
     return HA_ERR_SHAPE;
   }
   const bool wide = mode == kModeExact && a.merge_levels == 0 &&
@@ -747,11 +792,13 @@ int launch_attn_mfma(const AttnArgs& a, int mode, hipStream_t st) {
   if (a.g.d == 128) {
     if (mode == kModeNode) return launch_one<128, kModeNode, HA_NW_NODE>(a, st);
     if (mode == kModeCap) return launch_one<128, kModeCap, HA_NW_NODE>(a, st);
+    if (split) return launch_one<128, kModeExact, 4, false, 2>(a, st);
     return wide ? launch_one<128, kModeExact, 8>(a, st) : launch_one<128, kModeExact, HA_NW_EXACT>(a, st);
   }
   if (a.g.d == 64) {
     if (mode == kModeNode) return launch_one<64, kModeNode, HA_NW_NODE>(a, st);
     if (mode == kModeCap) return launch_one<64, kModeCap, HA_NW_NODE>(a, st);
+    if (split) return launch_one<64, kModeExact, 4, false, 2>(a, st);
     return launch_one<64, kModeExact, HA_NW_EXACT>(a, st);  // no gain from the wide form at d = 64
   }
   return HA_ERR_SHAPE;

@@ -758,3 +758,25 @@ def test_exact_attention_around_the_wide_form(ha, torch, H, n, causal):
         ref = s.softmax(-1) @ V[0, hd].float()
         assert_close(to_host(out[0, hd][rows]), ref.double().cpu().numpy(), "bf16", f"out head {hd}")
         assert_lse_close(to_host(lse[0, hd][rows]), s.logsumexp(-1).double().cpu().numpy(), "bf16", f"lse head {hd}")
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("H,n,causal", [(2, 256, True), (2, 257, True), (1, 321, False), (3, 384, False),   # odd and even numbers of key tiles
+                                        (32, 1024, False), (33, 1024, False),                              # 256 and 264 workgroups
+                                        (48, 1024, True), (49, 1024, True)])                               # causal: 384 and 392
+def test_exact_attention_with_shared_key_ranges(ha, torch, H, n, causal, d):
+    """Few workgroups: two groups of waves take a workgroup's key tiles in turn.  First and last head, all rows, against
+    fp32 attention under the plain criterion; log row sums with it."""
+    print(f"shared key ranges H={H} n={n} causal={causal} d={d}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(H + n)
+    Q, K, V = ((torch.randn((1, H, n, d), generator=gen, device="cuda") * d ** -0.25).to(torch.bfloat16) for _ in range(3))
+    out, lse = ha.exact_attn_forward(Q, K, V, causal=causal, out=torch.full_like(Q, float("nan")))
+    for hd in (0, H - 1):
+        s = Q[0, hd].float() @ K[0, hd].float().T.contiguous()
+        if causal:
+            s = s.masked_fill(torch.ones(n, n, dtype=torch.bool, device="cuda").triu(1), float("-inf"))
+        ref = (s.softmax(-1) @ V[0, hd].float()).double().cpu().numpy()
+        absv = (s.softmax(-1) @ V[0, hd].float().abs()).double().cpu().numpy()
+        assert_close(to_host(out[0, hd]), ref, "bf16", f"out head {hd}", absv=absv, max_plain_frac=5e-3 if causal else 1e-5)
+        assert_lse_close(to_host(lse[0, hd]), s.logsumexp(-1).double().cpu().numpy(), "bf16", f"lse head {hd}")

@@ -163,28 +163,26 @@ __global__ __launch_bounds__(64 * NW * NG, (D == 64 && NW == 4 && NG == 1) ? 3 :
   stamp(1);
 
   // ---- tile movers ----
-  // K and V rows are fetched with buffer loads: a 32-bit per-lane byte offset
-  // (row * row_bytes + column, from the key list in node mode, fixed in exact
-  // mode) plus a scalar offset that advances with the tile.  Offsets past the
-  // end of the head's tensor return zeros (such keys are masked by position).
-  const uint32_t head_bytes = (uint32_t)((kNode ? a.g.n : a.exact_rows_k) * (D * 2));
-  const __amdgpu_buffer_rsrc_t krsrc = __builtin_amdgcn_make_buffer_rsrc((void*)Kh, 0, (int)head_bytes, 0x00020000);
-  const __amdgpu_buffer_rsrc_t vrsrc = __builtin_amdgcn_make_buffer_rsrc((void*)Vh, 0, (int)head_bytes, 0x00020000);
+  // K and V rows are fetched with buffer loads at a 32-bit per-lane byte offset.  Node mode: the key list's rows, all of
+  // them rows of the head.  Exact mode: the tile's descriptor starts at the tile's first row and ends with the
+  // workgroup's keys, so the lane's offset, the one part of an address that the bounds check covers for certain, is checked
+  // against what is left: rows past the keys (the next diagonal block, the next head, the end of the
+  // tensor) are not read and count as zeros.  Masking their scores alone would not do: weight 0 times a V that is Inf or
+  // NaN is NaN, and with two wave groups a whole tile can lie there.
+  auto rows_rsrc = [&](const uint16_t* head, int kt) {
+    if (kNode) return __builtin_amdgcn_make_buffer_rsrc((void*)head, 0, (int)((uint32_t)a.g.n * (D * 2)), 0x00020000);
+    const int row = w.k0 + (NG * kt + grp) * kKT;
+    return __builtin_amdgcn_make_buffer_rsrc((void*)(head + (int64_t)row * D), 0, max(0, w.k1 - row) * (D * 2), 0x00020000);
+  };
   u32x4 kreg[TR::NKC], vreg[TR::NKC];
-  auto load_rows = [&](int kt, const __amdgpu_buffer_rsrc_t& rsrc, u32x4 (&reg)[TR::NKC]) {
+  auto load_rows = [&](int kt, const uint16_t* head, u32x4 (&reg)[TR::NKC]) {
+    const __amdgpu_buffer_rsrc_t rsrc = rows_rsrc(head, kt);
 #pragma unroll
     for (int i = 0; i < TR::NKC; ++i) {
       const int c = tid + i * kNT;
       const int key = c / TR::CPR, col = c % TR::CPR;
-      int voff, soff;
-      if (kNode) {
-        voff = list[kt * kKT + key] * (D * 2) + col * 16;
-        soff = 0;
-      } else {
-        voff = key * (D * 2) + col * 16;
-        soff = (w.k0 + (NG * kt + grp) * kKT) * (D * 2);
-      }
-      reg[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff, soff, 0);
+      const int row = kNode ? list[kt * kKT + key] : key;
+      reg[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, row * (D * 2) + col * 16, 0, 0);
     }
   };
   auto store_rows = [&](unsigned char* dst, int stride, const u32x4 (&reg)[TR::NKC]) {
@@ -271,9 +269,9 @@ __global__ __launch_bounds__(64 * NW * NG, (D == 64 && NW == 4 && NG == 1) ? 3 :
   if (ntiles > 0) {
     // all three tiles are requested before any is stored: one global round trip
     u32x4 kreg1[TR::NKC];
-    load_rows(0, krsrc, kreg);
-    load_rows(0, vrsrc, vreg);
-    if (ntiles > 1) load_rows(1, krsrc, kreg1);
+    load_rows(0, Kh, kreg);
+    load_rows(0, Vh, vreg);
+    if (ntiles > 1) load_rows(1, Kh, kreg1);
     store_rows(kbuf_at(0), L::KSTR, kreg);
     store_rows(vbuf_at(0), L::VSTR, vreg);
     if (ntiles > 1) store_rows(kbuf_at(1), L::KSTR, kreg1);
@@ -306,8 +304,8 @@ __global__ __launch_bounds__(64 * NW * NG, (D == 64 && NW == 4 && NG == 1) ? 3 :
     // LDS: there they are issued here, ahead of the block.
     constexpr bool kRequestInBlock = D == 64;
     if constexpr (!kRequestInBlock) {
-      if (more_k) load_rows(kt + 2, krsrc, kreg);
-      if (HN) load_rows(kt + 1, vrsrc, vreg);
+      if (more_k) load_rows(kt + 2, Kh, kreg);
+      if (HN) load_rows(kt + 1, Vh, vreg);
     }
 
     if (__any(t_max > m_run + 8.0f)) {
@@ -348,8 +346,8 @@ __global__ __launch_bounds__(64 * NW * NG, (D == 64 && NW == 4 && NG == 1) ? 3 :
     if constexpr (kPrio) __builtin_amdgcn_s_setprio(1);
     if constexpr (kRequestInBlock && HN) {
       // no branch here: past the end the last tile is requested again (and not stored)
-      load_rows(min(kt + 2, ntiles - 1), krsrc, kreg);
-      load_rows(kt + 1, vrsrc, vreg);
+      load_rows(min(kt + 2, ntiles - 1), Kh, kreg);
+      load_rows(kt + 1, Vh, vreg);
     }
     {
       if (HN) {

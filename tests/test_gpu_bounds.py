@@ -1,0 +1,79 @@
+"""Rows that a call has no business with do not reach its results: rows behind the tensors, rows of the next head and rows
+of the next diagonal block hold NaN or Inf, and what does not depend on them stays bit for bit what it is without them
+(a masked weight is 0, and 0 times NaN or Inf is NaN: such rows must not be loaded at all)."""
+import pytest
+
+from ha_testutil import have_gpu
+
+pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not have_gpu(), reason="needs a GPU")]
+
+
+@pytest.fixture(scope="module")
+def ha():
+    import paper_2310_05869_amd as mod
+    mod.lib()
+    return mod
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as t
+    return t
+
+
+def _dtype(torch, name):
+    return torch.bfloat16 if name == "bf16" else torch.float32
+
+
+def _rows(torch, gen, H, n, d, dtype, behind, poisoned_heads=()):
+    """[1, H, n, d] at the front of a buffer whose next 256 rows hold `behind`; heads of `poisoned_heads` hold it too."""
+    buf = torch.full(((H * n + 256) * d,), behind, dtype=dtype, device="cuda")
+    x = buf[:H * n * d].view(1, H, n, d)
+    x.copy_((torch.randn((1, H, n, d), generator=gen, device="cuda") * d ** -0.25).to(dtype))
+    for h in poisoned_heads:
+        x[:, h] = behind
+    return x
+
+
+def _generator(torch, seed):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    return gen
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("dtype,d,H,n", [("bf16", 64, 1, 257), ("bf16", 128, 1, 257), ("bf16", 64, 2, 321), ("bf16", 128, 2, 321),
+                                         ("bf16", 64, 2, 5), ("bf16", 128, 100, 300),   # one wave group
+                                         ("bf16", 128, 40, 8200),                       # eight waves
+                                         ("fp32", 64, 2, 33), ("fp32", 128, 2, 5), ("fp32", 64, 20, 2050)])
+def test_exact_forward_reads_its_own_rows_only(ha, torch, dtype, d, H, n, causal):
+    print(f"exact forward bounds {dtype} d={d} H={H} n={n} causal={causal}", flush=True)
+    dt = _dtype(torch, dtype)
+    results = []
+    for behind in (0.0, float("nan"), float("inf")):
+        gen = _generator(torch, n)
+        q, k, v = (_rows(torch, gen, H, n, d, dt, behind, (H - 1,) if H > 1 else ()) for _ in range(3))
+        results.append(ha.exact_attn_forward(q, k, v, causal=causal))
+    own = slice(0, H - 1) if H > 1 else slice(0, 1)
+    assert torch.isfinite(results[0][0]).all()
+    for out, lse in results[1:]:
+        assert torch.equal(out[:, own], results[0][0][:, own])
+        assert torch.equal(lse[:, own], results[0][1][:, own])
+
+
+@pytest.mark.parametrize("dtype,d,H,n_min", [("bf16", 64, 2, 320), ("bf16", 128, 2, 320), ("bf16", 64, 70, 320),
+                                             ("bf16", 128, 3, 65), ("fp32", 64, 2, 320), ("fp32", 128, 2, 33)])
+def test_next_diagonal_block_stays_out(ha, torch, dtype, d, H, n_min):
+    """The first n_min rows of a causal call see nothing of the rows behind them."""
+    print(f"next block {dtype} d={d} H={H} n_min={n_min}", flush=True)
+    dt = _dtype(torch, dtype)
+    results = []
+    for value in (0.0, float("inf"), float("nan")):
+        gen = _generator(torch, n_min)
+        q, k, v = (_rows(torch, gen, H, 2 * n_min, d, dt, 0.0) for _ in range(3))
+        v[:, :, n_min:] = value
+        results.append(ha.hyperattn_forward(q, k, v, n_min if n_min < 64 else n_min // 5, 16, 7, causal=True, n_min=n_min, seed=1))
+    assert torch.isfinite(results[0][0]).all()
+    for out, lse in results[1:]:
+        assert torch.equal(out[:, :, :n_min], results[0][0][:, :, :n_min])
+        assert torch.equal(lse, results[0][1])

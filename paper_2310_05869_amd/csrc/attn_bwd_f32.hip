@@ -145,13 +145,13 @@ __global__ __launch_bounds__(kFBT, D == 64 ? 2 : 1) void attn_bwd_f32_kernel(Bwd
   // element i of an accumulator is T row 8 (i / 4) + 4 h + i % 4 of the tile; lane l < 32 holds row l's values
   auto of_elem = [&](auto v, int i) { return __shfl(v, 8 * (i / 4) + 4 * h + (i % 4)); };
   auto load_cols = [&](const __amdgpu_buffer_rsrc_t& rsrc, int row, int kt, float (&v)[16][DT], int i0, int count) {
-    if (kExact) {  // consecutive rows: one address, the rest in the instructions' offsets
+    if (kExact) {  // consecutive rows: one address, the rest constants of the lane's offset (the bounds check covers it, not the scalar one)
       const int off = (w.k0 + kt * kFTT + 4 * h) * (D * 4) + 4 * lq;
 #pragma unroll
       for (int i = i0; i < i0 + count; ++i)
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
-          v[i][dt] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, off + (i % 4) * (D * 4) + 128 * dt, 8 * (i / 4) * (D * 4), 0));
+          v[i][dt] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, off + (8 * (i / 4) + i % 4) * (D * 4) + 128 * dt, 0, 0));
       return;
     }
 #pragma unroll
@@ -237,6 +237,10 @@ __global__ __launch_bounds__(kFBT, D == 64 ? 2 : 1) void attn_bwd_f32_kernel(Bwd
         if (MODE == kBwdDqExact && f.exact_causal) masked = masked || (w.k0 + tpos > r_row);   // keys after the query
         if (MODE == kBwdDkvExact && f.exact_causal) masked = masked || (w.k0 + tpos < r_row);  // queries before the key
         if (masked) c[i] = -INFINITY;
+        if (kExact && !kDq && masked) {  // (a piece of four values can end past the head's last row)
+          l4[i / 4][i % 4] = 0.f;
+          d4[i / 4][i % 4] = 0.f;
+        }
       }
     }
 #pragma unroll

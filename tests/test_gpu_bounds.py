@@ -77,3 +77,26 @@ def test_next_diagonal_block_stays_out(ha, torch, dtype, d, H, n_min):
     for out, lse in results[1:]:
         assert torch.equal(out[:, :, :n_min], results[0][0][:, :, :n_min])
         assert torch.equal(lse, results[0][1])
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("dtype,d,H,n", [("fp32", 64, 1, 1), ("fp32", 128, 2, 5), ("fp32", 64, 2, 23), ("fp32", 128, 1, 33),
+                                         ("fp32", 64, 2, 300), ("fp32", 64, 40, 2079), ("fp32", 128, 40, 2050),  # one wave per 32 rows
+                                         ("bf16", 64, 1, 1), ("bf16", 128, 2, 65), ("bf16", 64, 2, 321)])
+def test_exact_backward_reads_its_own_rows_only(ha, torch, dtype, d, H, n, causal):
+    """NaN behind Q, K, V, dO, the output and the log row sums, and in the last of several heads: the same gradients."""
+    print(f"exact backward bounds {dtype} d={d} H={H} n={n} causal={causal}", flush=True)
+    dt = _dtype(torch, dtype)
+    own = slice(0, H - 1) if H > 1 else slice(0, 1)
+    results = []
+    for behind in (0.0, float("nan")):
+        gen = _generator(torch, n)
+        q, k, v, g = (_rows(torch, gen, H, n, d, dt, behind, (H - 1,) if H > 1 else ()) for _ in range(4))
+        out = _rows(torch, gen, H, n, d, dt, behind)
+        lse = _rows(torch, gen, H, n, 1, torch.float32, behind).view(1, H, n)
+        out32 = _rows(torch, gen, H, n, d, torch.float32, behind) if dtype == "bf16" else None
+        ha.exact_attn_forward(q, k, v, causal=causal, out=out, lse=lse, out_f32=out32)
+        results.append(ha.exact_attn_backward(q, k, v, out, lse, g, causal=causal, out_f32=out32))
+    for x, y in zip(*results):
+        assert torch.isfinite(x).all()
+        assert torch.equal(x[:, own], y[:, own])

@@ -77,7 +77,10 @@ __global__ __launch_bounds__(kFNT, D == 64 ? 3 : 2) void attn_f32_kernel(AttnArg
     nkeys = max(0, w.k1 - w.k0);
     nb = 0x7fffffff;
   }
-  const int ntiles = (nkeys + kFKT - 1) / kFKT;
+  int ntiles = (nkeys + kFKT - 1) / kFKT;
+  // causal: a wave ends with the tile that holds its own last row.  Tiles wholly behind its rows are not only idle work:
+  // weight 0 times a V that is Inf or NaN is NaN.
+  if (MODE == kModeExact && a.exact_causal) ntiles = min(ntiles, (w.q0 - w.k0) / kFKT + wave / KW + 1);
   const float nat_bias = (MODE == kModeNode && a.g.m > 0) ? logf((float)w.nr.s / (float)a.g.m) : 0.f;
 
   const float* Qh = reinterpret_cast<const float*>(a.Q) + (int64_t)w.bh * a.q_bh_stride;

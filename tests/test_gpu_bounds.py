@@ -100,3 +100,20 @@ def test_exact_backward_reads_its_own_rows_only(ha, torch, dtype, d, H, n, causa
     for x, y in zip(*results):
         assert torch.isfinite(x).all()
         assert torch.equal(x[:, own], y[:, own])
+
+
+@pytest.mark.parametrize("d,H,n,n_min", [(64, 32, 2048, 0), (128, 32, 2048, 0), (64, 16, 2048, 0), (64, 1, 512, 0),  # one, two, four waves
+                                         (64, 32, 2048, 1024), (128, 2, 1024, 256)])
+@pytest.mark.parametrize("first", [64, 192])
+def test_fp32_causal_rows_see_no_later_tile(ha, torch, d, H, n, n_min, first):
+    """fp32, causal: rows of V from a multiple of 64 on are Inf; the rows before it do not load them."""
+    print(f"fp32 later rows d={d} H={H} n={n} n_min={n_min} first={first}", flush=True)
+    results = []
+    for value in (0.0, float("inf")):
+        gen = _generator(torch, n + H)
+        q, k, v = (_rows(torch, gen, H, n, d, torch.float32, 0.0) for _ in range(3))
+        v[:, :, first:] = value
+        results.append(ha.hyperattn_forward(q, k, v, 64, 16, 7, causal=True, n_min=n_min, seed=1) if n_min
+                       else ha.exact_attn_forward(q, k, v, causal=True))
+    assert torch.isfinite(results[0][0]).all()
+    assert torch.equal(results[0][0][:, :, :first], results[1][0][:, :, :first])

@@ -183,7 +183,8 @@ __device__ inline KeyListHead key_list_fetch(const AttnArgs& a, const TileWork& 
 // threads call it; on return (after its final barrier) list[0..pad) holds row
 // indices within the head, *nb_out the block keys and the return value nkeys.
 // `kh` = key_list_fetch's values of the calling thread.
-// PADDED: the block's keys are padded to whole tiles of 64, so that no tile holds both parts.
+// PADDED: the block's keys are padded to whole tiles of 64, so that no tile holds both parts.  All padding is then a key
+// of the block, one that the rows see anyway: a masked key's weight is 0, but 0 times a V that is Inf or NaN is NaN.
 template <int NT, bool PADDED = false>
 __device__ inline int build_key_list(const AttnArgs& a, const TileWork& w, int32_t* list, int32_t* scratch,
                                      int* nb_out, const KeyListHead& kh) {
@@ -207,7 +208,7 @@ __device__ inline int build_key_list(const AttnArgs& a, const TileWork& w, int32
   for (int i = tid + NT; i < nb; i += NT) list[i] = block_key(i);
   int base = PADDED ? (nb + 63) & ~63 : nb;
   if (PADDED)
-    for (int i = nb + tid; i < base; i += NT) list[i] = w.nr.k_start;
+    for (int i = nb + tid; i < base; i += NT) list[i] = block_key(nb - 1);
   for (int j0 = 0; j0 < m; j0 += NT) {
     const int j = j0 + tid;
     int l = l0, blk = blk0;
@@ -232,7 +233,8 @@ __device__ inline int build_key_list(const AttnArgs& a, const TileWork& w, int32
   }
   const int nkeys = base;
   const int pad = (nkeys + 63) & ~63;
-  for (int i = nkeys + tid; i < pad; i += NT) list[i] = w.nr.k_start;  // loadable, masked by position
+  // loadable, masked by position (PADDED: there are samples, so a barrier lies behind the block's keys)
+  for (int i = nkeys + tid; i < pad; i += NT) list[i] = PADDED ? list[nb - 1] : w.nr.k_start;
   __syncthreads();
   *nb_out = nb;
   return nkeys;

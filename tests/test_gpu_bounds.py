@@ -117,3 +117,22 @@ def test_fp32_causal_rows_see_no_later_tile(ha, torch, d, H, n, n_min, first):
                        else ha.exact_attn_forward(q, k, v, causal=True))
     assert torch.isfinite(results[0][0]).all()
     assert torch.equal(results[0][0][:, :, :first], results[1][0][:, :, :first])
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("b,m", [(32, 0), (32, 40), (64, 40), (128, 17)])
+def test_capped_rows_see_only_their_keys(ha, torch, d, b, m):
+    """Algorithm 2's caps, causal: Inf in the value of a node's first key reaches the one sorted block that holds the key
+    (and sampled rows, none here), not the rows whose key lists are filled up to whole tiles."""
+    print(f"caps, filled key lists d={d} b={b} m={m}", flush=True)
+    n, n_min = 1024, 256
+    seed = next(s for s in range(100) if m == 0 or 0 not in set(ha.ha_make_samples(s, 1, 1, 256, m)))
+    gen = _generator(torch, d + b)
+    q, k, v = (_rows(torch, gen, 2, n, d, torch.bfloat16, 0.0) for _ in range(3))
+    v[:, :, 512] = float("inf")   # the second node of level 1: keys 512 ... 767, queries 768 ... 1023
+    out, lse, _ = ha.hyperattn_forward_alg2(q, k, v, b, m, 7, seed=seed, cap_scale=6.0 if m else 0.0, kappa=1.2 if m else 0.0,
+                                            causal=True, n_min=n_min)
+    assert torch.isfinite(lse).all()
+    assert torch.isfinite(out[:, :, :512]).all()
+    hit = ~torch.isfinite(out[:, :, 768:]).all(dim=-1)
+    assert (hit.sum(dim=-1) == b).all(), hit.sum(dim=-1)

@@ -51,7 +51,8 @@ __host__ __device__ inline size_t f32_lds_bytes(int b, int m, int mode) {
   return list > (size_t)F32Lds<D>::BYTES ? list : (size_t)F32Lds<D>::BYTES;
 }
 
-template <int D, int MODE, int KW>
+// FAR (node mode): a head's rows pass the reach of a buffer load's 32-bit offset, so they are addressed in 64 bits.
+template <int D, int MODE, int KW, bool FAR>
 __global__ __launch_bounds__(kFNT, D == 64 ? 3 : 2) void attn_f32_kernel(AttnArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   constexpr int kQT = 32 * (4 / KW);
@@ -106,6 +107,11 @@ __global__ __launch_bounds__(kFNT, D == 64 ? 3 : 2) void attn_f32_kernel(AttnArg
   f32x4 kf[KJ];
   auto load_k = [&](int kt) {
     const int row = MODE == kModeNode ? list[kt * kFKT + lq] : w.k0 + kt * kFKT + lq;
+    if constexpr (FAR) {  // (every row of the list exists)
+#pragma unroll
+      for (int j = 0; j < KJ; ++j) kf[j] = *reinterpret_cast<const f32x4*>(Kh + (int64_t)row * D + 8 * j + 4 * h);
+      return;
+    }
     const int off = row * (D * 4) + 16 * h;
 #pragma unroll
     for (int j = 0; j < KJ; ++j)
@@ -127,8 +133,9 @@ __global__ __launch_bounds__(kFNT, D == 64 ? 3 : 2) void attn_f32_kernel(AttnArg
       for (int z = 0; z < 4; ++z)
 #pragma unroll
         for (int dt = 0; dt < DTA; ++dt)
-          v[4 * g + z][dt] = __uint_as_float(
-              __builtin_amdgcn_raw_buffer_load_b32(vrsrc, rows[z] * (D * 4) + 4 * lq, 128 * (dt0 + dt), 0));
+          v[4 * g + z][dt] = FAR ? Vh[(int64_t)rows[z] * D + 32 * (dt0 + dt) + lq]
+                                 : __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(vrsrc, rows[z] * (D * 4) + 4 * lq,
+                                                                                       128 * (dt0 + dt), 0));
     }
   };
 
@@ -278,7 +285,7 @@ __global__ __launch_bounds__(kFNT, D == 64 ? 3 : 2) void attn_f32_kernel(AttnArg
   }
 }
 
-template <int D, int MODE, int KW>
+template <int D, int MODE, int KW, bool FAR = false>
 static int launch_f32_one(const AttnArgs& args, hipStream_t st) {
   constexpr int kQT = 32 * (4 / KW);
   AttnArgs a = args;
@@ -288,8 +295,8 @@ static int launch_f32_one(const AttnArgs& args, hipStream_t st) {
   if (grid > kMaxGrid) return HA_ERR_SHAPE;
   const size_t lds = f32_lds_bytes<D>(a.g.b, a.g.m, MODE);
   static std::atomic<uint64_t> lds_set{0};  // per instantiation: devices on which the LDS limit is raised
-  if (allow_full_lds(reinterpret_cast<const void*>(&attn_f32_kernel<D, MODE, KW>), lds_set) != HA_OK) return HA_ERR_LAUNCH;
-  hipLaunchKernelGGL((attn_f32_kernel<D, MODE, KW>), dim3((unsigned)grid), dim3(kFNT), lds, st, a);
+  if (allow_full_lds(reinterpret_cast<const void*>(&attn_f32_kernel<D, MODE, KW, FAR>), lds_set) != HA_OK) return HA_ERR_LAUNCH;
+  hipLaunchKernelGGL((attn_f32_kernel<D, MODE, KW, FAR>), dim3((unsigned)grid), dim3(kFNT), lds, st, a);
   return check_launch();
 }
 
@@ -299,6 +306,8 @@ static int launch_f32_one(const AttnArgs& args, hipStream_t st) {
 // ones, while the merge of KW results costs a few LDS reads per row.
 template <int D, int MODE>
 static int launch_f32_mode(const AttnArgs& a, hipStream_t st) {
+  if constexpr (MODE == kModeNode)  // stage calls alone: the whole-call entry points take up to 2^22 rows per head
+    if ((int64_t)a.g.n * (D * 4) > 0x7fffffff + 1ll) return launch_f32_one<D, MODE, 4, true>(a, st);
   const int run = MODE == kModeNode ? a.g.b : (a.exact_block < a.exact_rows_q ? a.exact_block : a.exact_rows_q);
   auto padded = [&](int qt) { return (int64_t)((run + qt - 1) / qt) * qt; };
   const int64_t waves = 4 * (MODE == kModeNode ? node_grid<128>(a.g) : exact_grid<128>(a));

@@ -93,3 +93,35 @@ def test_exact_backward_fp32_forms(H, n, d, causal):
         err = abs(to_host(x)[:, hd:hd + 1] - y)
         # sums of up to 4100 terms, 2^-24 each
         assert (err <= 2.0 ** -12 * lim + 2.0 ** -100).all(), (name, err.max())
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_stages_past_four_gib(d):
+    """Block and sampled stage of one fp32 head whose tensors pass 4 GiB, the reach of a 32-bit byte offset: blocks at the
+    start, beyond 2 GiB and at the end against fp64 attention, 2^-14 of the values' magnitude (sums of 64 terms)."""
+    import torch
+
+    import paper_2310_05869_amd as ha
+    n = (1 << 30) // d + 128  # a multiple of 64
+    print(f"fp32 stages n={n} d={d}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(d)
+    rows = torch.randn((n + 192, d), generator=gen, device="cuda") * d ** -0.25
+    q, k, v = (rows[at:at + n].view(1, n, d) for at in (0, 64, 192))
+    samples = torch.tensor([0, 1, n // 2, n // 2 + 1, n - 2, n - 1, n // 3, 5], dtype=torch.int32, device="cuda")
+    for stage in ("block", "sampled"):
+        if stage == "block":
+            out, lse = ha.ha_block_attn(q, k, v, 64)
+        else:
+            out, lse = ha.ha_sampled_attn(q, k, v, samples, torch.arange(n, dtype=torch.int32, device="cuda").view(1, n), 64)
+        for at in (0, n // 2 // 64 * 64 + 64, n // 64 * 64 - 128, n - 64):
+            mine = slice(at, at + 64)
+            keys = torch.arange(at, at + 64, device="cuda") if stage == "block" else samples[samples // 64 != at // 64].long()
+            s = q[0, mine].double() @ k[0, keys].double().T.contiguous()
+            if stage == "sampled":
+                s = s + torch.log(torch.tensor(n / samples.numel(), dtype=torch.float64))
+            ref = s.softmax(-1) @ v[0, keys].double()
+            bound = s.softmax(-1) @ v[0, keys].double().abs()
+            assert ((out[0, mine] - ref).abs() <= 2.0 ** -14 * bound).all(), (stage, at)
+            assert torch.allclose(lse[0, mine].double(), s.logsumexp(-1), atol=2e-5), (stage, at)
+        del out, lse

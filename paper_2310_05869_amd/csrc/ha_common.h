@@ -126,6 +126,7 @@ struct AttnArgs {
   Geometry g;
   // node mode, set by the launchers (set_node_divs): tiles per level, heads, tiles per block, blocks of the last level's nodes
   FastDiv div_tpl, div_bh, div_tpb, div_unit;
+  int32_t wg_first;  // fp32 kernel: number of the launch's first workgroup, where a call takes several launches
   // cap mode: log tau of every node [BH][total_nodes], the constant of C_i and kappa (<= 0: that cap is off)
   const float* log_tau;
   float cap_scale, kappa;

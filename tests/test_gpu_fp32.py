@@ -125,3 +125,20 @@ def test_stages_past_four_gib(d):
             assert ((out[0, mine] - ref).abs() <= 2.0 ** -14 * bound).all(), (stage, at)
             assert torch.allclose(lse[0, mine].double(), s.logsumexp(-1), atol=2e-5), (stage, at)
         del out, lse
+
+
+def test_more_workgroups_than_one_launch_holds():
+    """2^24 + 64 blocks of one row: a launch of 256 threads each would count past 32 bits.  A softmax over one key is 1, so
+    every row's result is its value row, bit for bit."""
+    import torch
+
+    import paper_2310_05869_amd as ha
+    groups, n, d = 4, (1 << 22) + 16, 64
+    print(f"fp32 block stage, {groups * n} workgroups", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(1)
+    v = torch.randn((groups, n, d), generator=gen, device="cuda")
+    q = 0.1 * v
+    out, lse = ha.ha_block_attn(q, q, v, 1)
+    assert torch.equal(out, v)
+    assert torch.allclose(lse, (q.double() ** 2).sum(-1).float(), atol=1e-5, rtol=1e-5)

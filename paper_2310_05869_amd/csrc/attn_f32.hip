@@ -38,7 +38,6 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kFKT = 32;   // keys per tile
 constexpr int kFNT = 256;  // threads: four waves
-constexpr int64_t kFMaxLaunch = 1 << 23;  // workgroups of a launch: the threads of one are counted in 32 bits
 
 template <int D>
 struct F32Lds {
@@ -297,9 +296,9 @@ static int launch_f32_one(const AttnArgs& args, hipStream_t st) {
   const size_t lds = f32_lds_bytes<D>(a.g.b, a.g.m, MODE);
   static std::atomic<uint64_t> lds_set{0};  // per instantiation: devices on which the LDS limit is raised
   if (allow_full_lds(reinterpret_cast<const void*>(&attn_f32_kernel<D, MODE, KW, FAR>), lds_set) != HA_OK) return HA_ERR_LAUNCH;
-  for (int64_t first = 0; first < grid; first += kFMaxLaunch) {
+  for (int64_t first = 0; first < grid; first += kMaxLaunch) {
     a.wg_first = (int32_t)first;
-    const int64_t count = grid - first < kFMaxLaunch ? grid - first : kFMaxLaunch;
+    const int64_t count = grid - first < kMaxLaunch ? grid - first : kMaxLaunch;
     hipLaunchKernelGGL((attn_f32_kernel<D, MODE, KW, FAR>), dim3((unsigned)count), dim3(kFNT), lds, st, a);
     const int rc = check_launch();
     if (rc != HA_OK) return rc;

@@ -113,7 +113,7 @@ __global__ __launch_bounds__(64 * NW * NG, (D == 64 && NW == 4 && NG == 1) ? 3 :
   if constexpr (STAMPS) stamp_w = (long long)wall_clock64();
   stamp(0);
 
-  const int bid = kNode ? logical_block(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+  const int bid = (kCap ? a.wg_first : 0) + (kNode ? logical_block(blockIdx.x, gridDim.x) : (int)blockIdx.x);
   TileWork w;
   if (kNode) w = decode_node_tile<kQT>(a, bid);
   else w = decode_exact_tile<kQT>(a, bid);
@@ -734,6 +734,16 @@ static int launch_one(const AttnArgs& args, hipStream_t st) {
   if (lds < ep) lds = ep;
   static std::atomic<uint64_t> lds_set{0};  // per instantiation: devices on which the LDS limit is raised
   if (allow_full_lds(reinterpret_cast<const void*>(&attn_mfma_kernel<D, MODE, NW, STAMPS, NG>), lds_set) != HA_OK) return HA_ERR_LAUNCH;
+  if constexpr (MODE == kModeCap) {  // all levels in one launch, or in as many as their workgroups take
+    for (int64_t first = 0; first < grid; first += kMaxLaunch) {
+      a.wg_first = (int32_t)first;
+      const int64_t count = grid - first < kMaxLaunch ? grid - first : kMaxLaunch;
+      hipLaunchKernelGGL((attn_mfma_kernel<D, MODE, NW, STAMPS, NG>), dim3((unsigned)count), dim3(64 * NW * NG), lds, st, a);
+      const int rc = check_launch();
+      if (rc != HA_OK) return rc;
+    }
+    return HA_OK;
+  }
   hipLaunchKernelGGL((attn_mfma_kernel<D, MODE, NW, STAMPS, NG>), dim3((unsigned)grid), dim3(64 * NW * NG), lds, st, a);
   return check_launch();
 }

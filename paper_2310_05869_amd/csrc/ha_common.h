@@ -126,7 +126,7 @@ struct AttnArgs {
   Geometry g;
   // node mode, set by the launchers (set_node_divs): tiles per level, heads, tiles per block, blocks of the last level's nodes
   FastDiv div_tpl, div_bh, div_tpb, div_unit;
-  int32_t wg_first;  // fp32 kernel: number of the launch's first workgroup, where a call takes several launches
+  int32_t wg_first;  // fp32 kernel and cap mode: number of the launch's first workgroup, where a call takes several launches
   // cap mode: log tau of every node [BH][total_nodes], the constant of C_i and kappa (<= 0: that cap is off)
   const float* log_tau;
   float cap_scale, kappa;
@@ -144,6 +144,8 @@ struct AttnArgs {
 // before the tile loop (first scores done), after the loop and at the end; the constant-rate
 // counter at entry and at the end; the number of key tiles.
 constexpr int kStampWords = HA_STAMP_WORDS;
+
+constexpr int64_t kMaxLaunch = 1 << 23;  // workgroups of 256 threads per launch: the threads of one are counted in 32 bits
 
 // launchers (defined in the .hip files)
 int launch_seg_sort_nodes(const uint8_t* codes_q, const uint8_t* codes_k, int32_t* perm_q, int32_t* perm_k,

@@ -182,3 +182,18 @@ def test_alg2_rejects_bad_arguments(ha, torch):
 def test_alg2_caps_in_the_node_kernel(ha, torch, dtype, d, n, b, m, r, cap_scale, kappa, vnorm):
     """The forward kernel's cap mode and the sorted walk of the rows of T at the edges of their tiles: criteria as above."""
     test_alg2_options_match_the_oracle(ha, torch, dtype, d, n, b, m, r, cap_scale, kappa, vnorm)
+
+
+def test_alg2_more_workgroups_than_one_launch_holds(ha, torch):
+    """All levels' nodes together are 20 M workgroups of 256 threads, each level's own 4 M: more than a launch counts.  Heads
+    are independent and share the draws, so halves of the heads give the same bits."""
+    H, n, n_min = 8, 1 << 20, 1 << 15
+    print(f"alg2 {H * (n // 2) * 5} workgroups", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(4)
+    q, k, v = ((torch.randn((1, H, n, 64), generator=gen, device="cuda") / 8 ** 0.5).to(torch.bfloat16) for _ in range(3))
+    kw = dict(causal=True, n_min=n_min, seed=2)
+    out, lse, _ = ha.hyperattn_forward_alg2(q, k, v, 1, 0, 7, **kw)
+    for half in (slice(0, H // 2), slice(H // 2, H)):
+        o, l, _ = ha.hyperattn_forward_alg2(*(x[:, half].contiguous() for x in (q, k, v)), 1, 0, 7, **kw)
+        assert torch.equal(out[:, half], o) and torch.equal(lse[:, half], l)

@@ -473,6 +473,8 @@ int launch_seg_sort_nodes(const uint8_t* codes_q, const uint8_t* codes_k, int32_
   dim3 grid((unsigned)wg), block(kChunkWaves * 64);
   const int longest = ((g.causal ? g.n >> 1 : g.n) + kChunk - 1) / kChunk;  // chunks of the longest segment
   if (wg <= kOneLaunchChunks && longest <= kOneLaunchLongest) {
+    static std::atomic<uint64_t> lds_set{0};  // devices on which the LDS limit is raised: 66 KiB at r = 8
+    if (allow_full_lds(reinterpret_cast<const void*>(&chunk_scatter_kernel<16, true>), lds_set) != HA_OK) return HA_ERR_LAUNCH;
     hipLaunchKernelGGL((chunk_scatter_kernel<16, true>), grid, dim3(16 * 64), chunk_scatter_lds(nbk, 16, true), st, a, nbk);
     return check_launch();
   }

@@ -706,6 +706,7 @@ def test_forward_on_random_small_problems(ha, torch, dtype, d, n, n_min, b, m, r
 @pytest.mark.parametrize("H,n,b,r,causal,n_min", [
     (32, 16384, 64, 7, 0, 0), (33, 16384, 64, 7, 0, 0),   # 256 chunks: one launch; 264: two
     (1, 32768, 256, 8, 0, 0), (1, 32769, 3, 8, 0, 0),     # segments of 8 chunks: one launch; of 9: two
+    (2, 300, 30, 8, 0, 0), (3, 4096, 32, 8, 1, 512),      # one launch, 256 buckets: 66 KiB of LDS
     (2, 4097, 17, 1, 0, 0), (3, 1, 1, 7, 0, 0),           # a chunk of one key, a segment of one key, two buckets
     (1, 65536, 32, 7, 1, 1024)])                          # six levels, 8 chunks down to a quarter of one
 def test_node_sort_is_the_stable_order(ha, torch, H, n, b, r, causal, n_min):

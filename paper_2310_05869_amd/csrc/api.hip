@@ -407,7 +407,7 @@ static void fill_bwd_layout(const Geometry& g, ha_bwd_ws_layout* l) {
   // accumulated node rows: dQ first, then (dQ being written out) dK in the same region, dV in the second
   l->acc_a = take(g.levels > 0 ? rows * rowb : 0);
   l->acc_b = take(g.levels > 0 ? rows * rowb : 0);
-  const size_t srows = (size_t)bwd_sample_chunks(g, bwd_chunk(g)) * g.m;  // one per (head, node, query chunk, sample)
+  const size_t srows = (size_t)bwd_sample_rows(g);
   l->samp_k = take(srows * rowb);
   l->samp_v = take(srows * rowb);
   l->total_bytes = off < 256 ? 256 : off;

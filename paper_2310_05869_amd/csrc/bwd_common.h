@@ -84,6 +84,19 @@ inline int bwd_chunk(const Geometry& g) {
   return chunk;
 }
 
+// Rows of the sampled-key pass that the workspace holds: at least one per (head, node, query chunk, sample), by a bound
+// that never falls when the rows, heads or samples grow, though the chunk does, so that a workspace
+// of the largest problem serves the smaller ones.  A chunk below 2048 is at least 256 and 2 m, which bounds a
+// node's rows by s / 2 + m, and came from one twice as long with at most 1023 workgroups of up to 128 samples.
+inline int64_t bwd_sample_rows(const Geometry& g) {
+  const int64_t longest = bwd_sample_chunks(g, 2048) * g.m;
+  int64_t rows = bwd_sample_chunks(g, 256) * g.m;
+  const int64_t half = (int64_t)g.levels * g.BH * ((g.n_cov + 1) / 2) + (int64_t)g.BH * g.total_nodes * g.m;
+  if (rows > half) rows = half;
+  if (rows > 2 * 1023 * 128) rows = 2 * 1023 * 128;
+  return rows > longest ? rows : longest;
+}
+
 // What a workgroup of QT "R rows" owns in each pass (TileWork: the head, the node, the rows; exact dK / dV
 // pass: q0 = first KEY row, [k0, k1) = its queries).
 struct BwdWork {

@@ -106,6 +106,47 @@ def test_backward_workspace_layout(ha):
     assert ha.ha_backward_workspace_bytes(sh, p0) == rows * 4
 
 
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("dtype_d", [("HA_BF16", 64), ("HA_FP32", 128)])
+def test_backward_workspace_grows_with_the_problem(ha, causal, dtype_d):
+    """A workspace of a problem serves every one with fewer rows, heads or samples, although short problems cut their
+    queries into shorter chunks and keep more rows per sample; and it holds the rows of its own chunks."""
+    dtype, d = getattr(ha, dtype_d[0]), dtype_d[1]
+    b, n_min = 8, 512
+    sizes = [n_min << k for k in range(1, 11)] if causal else [b * k for k in (1, 31, 32, 255, 256, 4095, 8192, 37500, 65535, 65536, 131071, 131072)]
+
+    def layout(H, n, m):
+        lay = ha.binding.HaBwdWsLayout()
+        sh, p = ha.make_shape(1, H, n, d, dtype), ha.make_params(b, m, 7, causal, n_min, 0)
+        assert ha.lib().ha_backward_workspace_layout(ctypes.byref(sh), ctypes.byref(p), ctypes.byref(lay)) == 0
+        return lay
+
+    def rows_needed(H, n, m):
+        nodes = [(2 ** l, n >> (l + 1)) for l in range((n // n_min).bit_length() - 1)] if causal else [(1, n)]
+        chunks = lambda c: H * sum(k * -(-s // min(s, c)) for k, s in nodes)
+        chunk = 2048
+        while chunk // 2 >= 256 and chunk // 2 >= 2 * m and chunks(chunk) * -(-m // 128) < 1024:
+            chunk //= 2
+        return chunks(chunk) * m
+
+    total = {}
+    for H in (1, 3, 12, 64):
+        for n in sizes:
+            for m in (0, 1, 127, 128, 129, 256, 700, 1024, 1025, 4096):
+                lay = layout(H, n, m)
+                assert lay.samp_v - lay.samp_k >= rows_needed(H, n, m) * d * 4, (H, n, m)
+                assert lay.total_bytes - lay.samp_v >= rows_needed(H, n, m) * d * 4, (H, n, m)
+                total[H, n, m] = lay.total_bytes
+    for axis in range(3):
+        values = sorted({key[axis] for key in total})
+        for key, size in total.items():
+            at = values.index(key[axis])
+            if at > 0:
+                below = tuple(values[at - 1] if x == axis else key[x] for x in range(3))
+                assert total[below] <= size, (below, total[below], key, size)
+
+
+
 def test_forward_workgroup_counts(ha):
     """Records of the stamped forward: one per 128-query tile of every node (levels x half the rows when causal)
     and of the base case; none for fp32 tensors, which run the kernel without matrix cores."""

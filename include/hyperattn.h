@@ -295,7 +295,7 @@ int ha_merge_unpermute(const float* o_b, const float* lse_b, const float* o_r, c
 typedef struct {
   size_t delta;                      /* fp32 [B*H][n] */
   size_t acc_a, acc_b;               /* fp32 [B*H][n][d] each: the node parts' rows, added up level by level
-                                        (acc_a: dQ, afterwards dK; acc_b: dV); not used by unmasked problems */
+                                        (acc_a: dQ, afterwards dK; acc_b: dV); empty for unmasked problems */
   size_t samp_k, samp_v;             /* fp32 rows of the sampled keys per (level, head, node, query chunk, sample) */
   size_t total_bytes;
 } ha_bwd_ws_layout;

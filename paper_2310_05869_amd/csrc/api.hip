@@ -405,8 +405,10 @@ static void fill_bwd_layout(const Geometry& g, ha_bwd_ws_layout* l) {
   const size_t rowb = (size_t)g.d * 4;
   l->delta = take(rows * 4);
   // accumulated node rows: dQ first, then (dQ being written out) dK in the same region, dV in the second
-  l->acc_a = take(g.levels > 0 ? rows * rowb : 0);
-  l->acc_b = take(g.levels > 0 ? rows * rowb : 0);
+  // (an unmasked problem's passes write the gradients)
+  const bool accumulates = g.causal && g.levels > 0;
+  l->acc_a = take(accumulates ? rows * rowb : 0);
+  l->acc_b = take(accumulates ? rows * rowb : 0);
   const size_t srows = (size_t)bwd_sample_rows(g);
   l->samp_k = take(srows * rowb);
   l->samp_v = take(srows * rowb);

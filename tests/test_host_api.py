@@ -106,6 +106,18 @@ def test_backward_workspace_layout(ha):
     assert ha.ha_backward_workspace_bytes(sh, p0) == rows * 4
 
 
+def test_backward_workspace_of_an_unmasked_problem(ha):
+    """Its passes write the gradients: delta and the sampled keys' rows, no accumulated rows; bounded by 2 * 1023 * 128
+    sampled rows where the chunks are short."""
+    lay = ha.binding.HaBwdWsLayout()
+    sh, p = ha.make_shape(1, 12, 16384, 64, ha.HA_BF16), ha.make_params(256, 256, 7, False, 4096, 0)
+    assert ha.lib().ha_backward_workspace_layout(ctypes.byref(sh), ctypes.byref(p), ctypes.byref(lay)) == 0
+    rows = 12 * 16384
+    assert lay.acc_a == lay.acc_b == lay.samp_k == rows * 4
+    assert lay.samp_v - lay.samp_k == (rows // 2 + 12 * 256) * 64 * 4   # chunks of 512: 32 per head, 256 rows each, below the bound s / 2 + m
+    assert ha.ha_backward_workspace_bytes(sh, ha.make_params(256, 0, 7, False, 4096, 0)) == rows * 4
+
+
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("dtype_d", [("HA_BF16", 64), ("HA_FP32", 128)])
 def test_backward_workspace_grows_with_the_problem(ha, causal, dtype_d):

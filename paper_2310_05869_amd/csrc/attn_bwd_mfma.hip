@@ -102,8 +102,8 @@ __host__ __device__ inline size_t bwd_lds_bytes(const BwdArgs& a, int mode) {
 // because the compiler's wait counts would serialise the builtin with every LDS read; the kernel
 // waits for these requests itself, once per tile.
 __device__ inline void dma_1k(const __amdgpu_buffer_rsrc_t& rsrc, uint32_t lds_at, int voff) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds_at), "v"(voff), "s"(rsrc)
-               : "memory");
+  // (m0 as an operand: the compiler writes it and knows; it takes no clobber of a reserved register)
+  asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"{m0}"(lds_at), "v"(voff), "s"(rsrc) : "memory");
 }
 
 // FINAL: the node passes of an unmasked problem, which write the final gradients.

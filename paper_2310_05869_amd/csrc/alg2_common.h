@@ -34,7 +34,7 @@ struct Alg2Args {
   int32_t* pos_q;          // [view]
   int32_t* tau_rows;       // [total_nodes][m] node-local query indices
   float* log_unm_t;        // [view heads][m]
-  float* log_unm_parts;    // [kAlg2TauSplits][view heads][m]: the same over ranges of keys (matrix-core form)
+  float* log_unm_parts;    // [kAlg2TauSplits][view heads][m]: the same over ranges of keys (bf16)
   int32_t tau_splits;      // 0: log_unm_t is final; else the number of key ranges to combine
   float* log_tau;          // [heads][total_nodes]
   double* vw;              // [view] squared norms of the value rows
@@ -62,8 +62,7 @@ __host__ __device__ inline Alg2Node alg2_node(const Alg2Args& a, int vh) {
 
 int launch_alg2(const Alg2Args& a, hipStream_t st);
 
-// bf16 matrix-core forms of the two heavy steps (alg2_mfma.hip); the fp32 FMA kernels take what they do not
-bool alg2_mfma_supported(const Alg2Args& a);
+// bf16 tensors: matrix-core forms of the two heavy steps (alg2_mfma.hip)
 int launch_alg2_tau_mfma(const Alg2Args& a, hipStream_t st);
 int launch_alg2_main_mfma(const Alg2Args& a, hipStream_t st);
 

@@ -8,10 +8,10 @@
 //         or = (1 / d~_i) (masked part + (n/m) sum_j (1 - M) exp<q_i,k_{l_j}> v_{l_j})                (Section 4)
 // The constants the paper leaves open (the Theta in C_i, kappa) are the caller's.
 // A launch sequence handles one level of nodes (alg2_common.h): the unmasked problem, or one
-// level of Algorithm 4's off-diagonal nodes, every node with its own draws.  The kernels here are plain fp32 FMA code (one thread per query row,
-// K / V rows staged through LDS): they serve fp32 tensors and whatever the bf16 matrix-core
-// forms of the two heavy steps (alg2_mfma.hip) do not take; the draws, weights and prefix
-// sums are computed here for both.
+// level of Algorithm 4's off-diagonal nodes, every node with its own draws.  The draws, weights and prefix sums are
+// computed here for both dtypes; the two heavy steps here are plain fp32 FMA code (one thread per query row, K / V rows
+// staged through LDS) and serve fp32 tensors, bf16 tensors take the matrix-core forms (alg2_mfma.hip; the caps
+// without value sampling: a mode of the forward kernel).
 //
 // Lemma 2's rows are drawn with p_l = |V_l|^2 / |V|_F^2 (V the node's value rows) by inverting
 // the cumulative distribution in fp64: draw r of head bh at the node with heap index h takes the
@@ -154,12 +154,12 @@ __global__ void vnorm_sample_kernel(Alg2Args a) {
 // a thread owns one key of the tile for some of the rows and keeps their running log sums.
 constexpr int kTauRows = 8;
 
-template <typename T, int D>
+template <int D>
 __global__ __launch_bounds__(256) void alg2_tau_kernel(Alg2Args a) {
-  constexpr int kKeys = sizeof(T) == 2 ? 128 : 64;   // keys per tile
+  constexpr int kKeys = 64;   // keys per tile
   constexpr int kGroups = 256 / kKeys;               // thread groups, each with its own rows
   constexpr int kRpt = kTauRows / kGroups;           // rows per thread
-  constexpr int kRowBytes = D * (int)sizeof(T);
+  constexpr int kRowBytes = D * 4;
   constexpr int kStride = kRowBytes + 4;             // odd number of words: no bank conflicts between the keys
   __shared__ __attribute__((aligned(16))) unsigned char tile[kKeys * kStride];
   __shared__ __attribute__((aligned(16))) float qs[kTauRows][D];
@@ -172,12 +172,12 @@ __global__ __launch_bounds__(256) void alg2_tau_kernel(Alg2Args a) {
   const int64_t hb = (int64_t)bh * g.n;   // bh: view head (one node)
   const Alg2Node nd = alg2_node(a, bh);
   const int32_t* trows = a.tau_rows + (int64_t)nd.heap * g.m;
-  const T* Qh = reinterpret_cast<const T*>(a.Q) + ((int64_t)nd.head * a.n_full + nd.q_start) * D;
+  const float* Qh = reinterpret_cast<const float*>(a.Q) + ((int64_t)nd.head * a.n_full + nd.q_start) * D;
   const unsigned char* Kh = reinterpret_cast<const unsigned char*>(a.K) + ((int64_t)nd.head * a.n_full + nd.k_start) * kRowBytes;
   const int tid = threadIdx.x;
   for (int e = tid; e < kTauRows * D; e += 256) {
     const int r = e / D, c = e % D;
-    qs[r][c] = r < nr ? elem<T>(Qh + (int64_t)trows[j0 + r] * D + c) : 0.f;
+    qs[r][c] = r < nr ? *(Qh + (int64_t)trows[j0 + r] * D + c) : 0.f;
   }
   if (tid < kTauRows) blk_of[tid] = tid < nr ? a.pos_q[hb + trows[j0 + tid]] / g.b : -1;
   const int k = tid % kKeys, grp = tid / kKeys;
@@ -198,7 +198,7 @@ __global__ __launch_bounds__(256) void alg2_tau_kernel(Alg2Args a) {
     __syncthreads();
     if (k >= cnt) continue;
     const int kblk = a.pos_k[hb + l0 + k] / g.b;
-    const T* kr = reinterpret_cast<const T*>(tile + k * kStride);
+    const float* kr = reinterpret_cast<const float*>(tile + k * kStride);
     float s[kRpt];
 #pragma unroll
     for (int r = 0; r < kRpt; ++r) s[r] = 0.f;
@@ -207,16 +207,8 @@ __global__ __launch_bounds__(256) void alg2_tau_kernel(Alg2Args a) {
 #pragma unroll 4
     for (int c = 0; c < D; c += 4) {
       float x[4];
-      if (sizeof(T) == 2) {
-        const uint32_t lo = *reinterpret_cast<const uint32_t*>(kr + c), hi = *reinterpret_cast<const uint32_t*>(kr + c + 2);
-        x[0] = __uint_as_float(lo << 16);
-        x[1] = __uint_as_float(lo & 0xFFFF0000u);
-        x[2] = __uint_as_float(hi << 16);
-        x[3] = __uint_as_float(hi & 0xFFFF0000u);
-      } else {
 #pragma unroll
-        for (int z = 0; z < 4; ++z) x[z] = elem<T>(kr + c + z);
-      }
+      for (int z = 0; z < 4; ++z) x[z] = kr[c + z];
 #pragma unroll
       for (int r = 0; r < kRpt; ++r) {
         const float4 qv = *reinterpret_cast<const float4*>(&qs[grp * kRpt + r][c]);
@@ -288,7 +280,7 @@ constexpr int kA2Rows = 64;  // query rows (threads) per workgroup
 constexpr int kA2Tile = 32;  // key rows per LDS tile
 
 // One thread per query row; 64 consecutive sorted positions of one block per workgroup.
-template <typename T, int D>
+template <int D>
 __global__ __launch_bounds__(kA2Rows) void alg2_main_kernel(Alg2Args a) {
   __shared__ float Ks[kA2Tile * D];
   __shared__ float Vs[kA2Tile * D];
@@ -305,15 +297,15 @@ __global__ __launch_bounds__(kA2Rows) void alg2_main_kernel(Alg2Args a) {
   const int64_t hb = (int64_t)bh * g.n;   // bh: view head (one node); perm values are rows of the real head
   const Alg2Node nd = alg2_node(a, bh);
   const int qrow = a.perm_q[hb + (valid ? p0 + tid : p0)];
-  const T* Qh = reinterpret_cast<const T*>(a.Q) + (int64_t)nd.head * a.n_full * D;
-  const T* Kh = reinterpret_cast<const T*>(a.K) + (int64_t)nd.head * a.n_full * D;
-  const T* Vh = reinterpret_cast<const T*>(a.V) + (int64_t)nd.head * a.n_full * D;
+  const float* Qh = reinterpret_cast<const float*>(a.Q) + (int64_t)nd.head * a.n_full * D;
+  const float* Kh = reinterpret_cast<const float*>(a.K) + (int64_t)nd.head * a.n_full * D;
+  const float* Vh = reinterpret_cast<const float*>(a.V) + (int64_t)nd.head * a.n_full * D;
   const int64_t draws = ((int64_t)nd.head * a.total_nodes + nd.heap) * g.m;   // this node's entries of the per-node arrays
 
   float q[D], o[D];
 #pragma unroll
   for (int c = 0; c < D; ++c) {
-    q[c] = elem<T>(Qh + (int64_t)qrow * D + c);
+    q[c] = *(Qh + (int64_t)qrow * D + c);
     o[c] = 0.f;
   }
   float M = -INFINITY;      // reference of every exponential below
@@ -337,8 +329,8 @@ __global__ __launch_bounds__(kA2Rows) void alg2_main_kernel(Alg2Args a) {
   auto stage = [&](int cnt, bool with_v) {
     for (int e = tid; e < cnt * D; e += kA2Rows) {
       const int j = e / D, c = e % D;
-      Ks[e] = elem<T>(Kh + (int64_t)rows[j] * D + c);
-      if (with_v) Vs[e] = elem<T>(Vh + (int64_t)rows[j] * D + c);
+      Ks[e] = *(Kh + (int64_t)rows[j] * D + c);
+      if (with_v) Vs[e] = *(Vh + (int64_t)rows[j] * D + c);
     }
   };
 
@@ -424,22 +416,16 @@ __global__ __launch_bounds__(kA2Rows) void alg2_main_kernel(Alg2Args a) {
   if (!valid) return;
   const int64_t orow = hb + (qrow - nd.q_start);
   a.lse[orow] = log_dt;
-  if (sizeof(T) == 4) {
-    float* op = reinterpret_cast<float*>(a.out) + orow * D;
+  float* op = reinterpret_cast<float*>(a.out) + orow * D;
 #pragma unroll
-    for (int c = 0; c < D; ++c) op[c] = o[c] * f;
-  } else {
-    uint16_t* op = reinterpret_cast<uint16_t*>(a.out) + orow * D;
-#pragma unroll
-    for (int c = 0; c < D; c += 2) *reinterpret_cast<uint32_t*>(op + c) = pack_bf16x2(o[c] * f, o[c + 1] * f);
-  }
+  for (int c = 0; c < D; ++c) op[c] = o[c] * f;
 }
 
 template <typename T>
 static int launch_alg2_t(const Alg2Args& a_in, hipStream_t st) {
   const Geometry& g = a_in.g;
   Alg2Args a = a_in;
-  const bool mfma = alg2_mfma_supported(a);
+  constexpr bool mfma = sizeof(T) == 2;
   a.tau_splits = mfma ? kAlg2TauSplits : 0;
   const int64_t rows = (int64_t)g.BH * g.n;
   int64_t prep = rows > (int64_t)a.nodes * g.m ? rows : (int64_t)a.nodes * g.m;
@@ -451,25 +437,26 @@ static int launch_alg2_t(const Alg2Args& a_in, hipStream_t st) {
     hipLaunchKernelGGL(vnorm_scan_kernel, dim3((unsigned)g.BH), dim3(kScanThreads), 0, st, a);
     hipLaunchKernelGGL(vnorm_sample_kernel, dim3((unsigned)(((int64_t)g.BH * g.m + 255) / 256)), dim3(256), 0, st, a);
   }
-  if (g.m > 0) {
-    if (mfma) {
+  if constexpr (mfma) {
+    if (g.m > 0) {
       const int rc = launch_alg2_tau_mfma(a, st);
       if (rc != HA_OK) return rc;
-    } else {
-      const unsigned tau_grid = (unsigned)((int64_t)g.BH * ((g.m + kTauRows - 1) / kTauRows));
-      if (g.d == 128) hipLaunchKernelGGL((alg2_tau_kernel<T, 128>), dim3(tau_grid), dim3(256), 0, st, a);
-      else hipLaunchKernelGGL((alg2_tau_kernel<T, 64>), dim3(tau_grid), dim3(256), 0, st, a);
     }
+    hipLaunchKernelGGL(alg2_tau_max_kernel, dim3((unsigned)g.BH), dim3(256), 0, st, a);
+    return a.vnorm ? launch_alg2_main_mfma(a, st) : check_launch();  // (without value sampling: the caller's node launch)
+  } else {
+    if (g.m > 0) {
+      const unsigned tau_grid = (unsigned)((int64_t)g.BH * ((g.m + kTauRows - 1) / kTauRows));
+      if (g.d == 128) hipLaunchKernelGGL((alg2_tau_kernel<128>), dim3(tau_grid), dim3(256), 0, st, a);
+      else hipLaunchKernelGGL((alg2_tau_kernel<64>), dim3(tau_grid), dim3(256), 0, st, a);
+    }
+    hipLaunchKernelGGL(alg2_tau_max_kernel, dim3((unsigned)g.BH), dim3(256), 0, st, a);
+    const int tpb = (g.b + kA2Rows - 1) / kA2Rows;
+    const unsigned grid = (unsigned)((int64_t)g.BH * (g.n / g.b) * tpb);
+    if (g.d == 128) hipLaunchKernelGGL((alg2_main_kernel<128>), dim3(grid), dim3(kA2Rows), 0, st, a);
+    else hipLaunchKernelGGL((alg2_main_kernel<64>), dim3(grid), dim3(kA2Rows), 0, st, a);
+    return check_launch();
   }
-  hipLaunchKernelGGL(alg2_tau_max_kernel, dim3((unsigned)g.BH), dim3(256), 0, st, a);
-  if (mfma) return a.vnorm ? launch_alg2_main_mfma(a, st) : check_launch();  // (without value sampling: the caller's node launch)
-  const int tpb = (g.b + kA2Rows - 1) / kA2Rows;
-  const unsigned grid = (unsigned)((int64_t)g.BH * (g.n / g.b) * tpb);
-  if (g.d == 128)
-    hipLaunchKernelGGL((alg2_main_kernel<T, 128>), dim3(grid), dim3(kA2Rows), 0, st, a);
-  else
-    hipLaunchKernelGGL((alg2_main_kernel<T, 64>), dim3(grid), dim3(kA2Rows), 0, st, a);
-  return check_launch();
 }
 
 int launch_alg2(const Alg2Args& a, hipStream_t st) {

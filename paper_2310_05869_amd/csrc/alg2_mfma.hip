@@ -468,13 +468,6 @@ __global__ __launch_bounds__(kA2NT, 2) void alg2_mfma_kernel(Alg2Args a) {
   }
 }
 
-// Whether the MFMA kernels take this problem: bf16 tensors, d of 64 or 128, and a key list that fits in LDS.
-bool alg2_mfma_supported(const Alg2Args& a) {
-  const Geometry& g = a.g;
-  if (g.dtype != HA_BF16 || (g.d != 64 && g.d != 128)) return false;
-  return (g.d == 128 ? a2_lds_bytes<128>(g) : a2_lds_bytes<64>(g)) <= 160 * 1024;
-}
-
 template <int D>
 static int launch_tau(const Alg2Args& a, unsigned grid, hipStream_t st) {
   static std::atomic<uint64_t> lds_set{0};  // per instantiation: devices on which the LDS limit is raised

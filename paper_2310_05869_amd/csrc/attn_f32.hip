@@ -34,7 +34,6 @@ namespace ha {
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kFKT = 32;   // keys per tile
 constexpr int kFNT = 256;  // threads: four waves

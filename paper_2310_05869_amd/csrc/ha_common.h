@@ -89,7 +89,6 @@ enum AttnMode : int32_t {
 struct FastDiv {
   uint32_t mul, shift, d;
   __host__ __device__ inline int div(int n) const { return (int)(((uint64_t)(uint32_t)n * mul) >> shift); }
-  __host__ __device__ inline int mod(int n) const { return n - div(n) * (int)d; }
 };
 inline FastDiv make_fast_div(int64_t divisor) {  // 1 <= divisor < 2^31: mul = ceil(2^shift / divisor) < 2^32, 2^shift >= 2^31 divisor
   FastDiv f;

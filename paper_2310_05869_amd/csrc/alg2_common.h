@@ -44,6 +44,7 @@ struct Alg2Args {
   uint64_t seed;
   float cap_scale, kappa;
   int32_t vnorm;
+  int32_t wg_first;        // tau kernel (bf16): number of the launch's first workgroup, where a call takes several launches
 };
 
 // Where view head `vh` of a level sits: its real head, node, heap index and first query / key row.

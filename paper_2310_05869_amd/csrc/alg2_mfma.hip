@@ -85,7 +85,7 @@ __global__ __launch_bounds__(2 * kA2NT, 4) void alg2_tau_mfma_kernel(Alg2Args a)
   unsigned char* bufs = smem + grp * 2 * L::K_BYTES;
 
   const int row_tiles = (g.m + kA2QT - 1) / kA2QT;
-  const int idx = logical_block(blockIdx.x, gridDim.x);
+  const int idx = a.wg_first + logical_block(blockIdx.x, gridDim.x);
   const int j0 = (idx % row_tiles) * kA2QT;
   const int split = idx / row_tiles % kAlg2TauSplits;
   const int bh = idx / row_tiles / kAlg2TauSplits;
@@ -469,11 +469,19 @@ __global__ __launch_bounds__(kA2NT, 2) void alg2_mfma_kernel(Alg2Args a) {
 }
 
 template <int D>
-static int launch_tau(const Alg2Args& a, unsigned grid, hipStream_t st) {
+static int launch_tau(const Alg2Args& args, int64_t grid, hipStream_t st) {
   static std::atomic<uint64_t> lds_set{0};  // per instantiation: devices on which the LDS limit is raised
   if (allow_full_lds(reinterpret_cast<const void*>(&alg2_tau_mfma_kernel<D>), lds_set) != HA_OK) return HA_ERR_LAUNCH;
-  hipLaunchKernelGGL((alg2_tau_mfma_kernel<D>), dim3(grid), dim3(2 * kA2NT), 4 * A2Lds<D>::K_BYTES, st, a);
-  return check_launch();
+  Alg2Args a = args;
+  constexpr int64_t kStep = kMaxLaunch / 2;  // (512 threads)
+  for (int64_t first = 0; first < grid; first += kStep) {
+    a.wg_first = (int32_t)first;
+    const unsigned count = (unsigned)(grid - first < kStep ? grid - first : kStep);
+    hipLaunchKernelGGL((alg2_tau_mfma_kernel<D>), dim3(count), dim3(2 * kA2NT), 4 * A2Lds<D>::K_BYTES, st, a);
+    const int rc = check_launch();
+    if (rc != HA_OK) return rc;
+  }
+  return HA_OK;
 }
 
 int launch_alg2_tau_mfma(const Alg2Args& a, hipStream_t st) {
@@ -481,7 +489,7 @@ int launch_alg2_tau_mfma(const Alg2Args& a, hipStream_t st) {
   const int64_t grid = (int64_t)g.BH * ((g.m + kA2QT - 1) / kA2QT) * kAlg2TauSplits;
   if (grid <= 0) return HA_OK;
   if (grid > kMaxGrid) return HA_ERR_SHAPE;
-  return g.d == 128 ? launch_tau<128>(a, (unsigned)grid, st) : launch_tau<64>(a, (unsigned)grid, st);
+  return g.d == 128 ? launch_tau<128>(a, grid, st) : launch_tau<64>(a, grid, st);
 }
 
 template <int D>

@@ -197,3 +197,18 @@ def test_alg2_more_workgroups_than_one_launch_holds(ha, torch):
     for half in (slice(0, H // 2), slice(H // 2, H)):
         o, l, _ = ha.hyperattn_forward_alg2(*(x[:, half].contiguous() for x in (q, k, v)), 1, 0, 7, **kw)
         assert torch.equal(out[:, half], o) and torch.equal(lse[:, half], l)
+
+
+def test_alg2_more_heads_than_one_launch_holds(ha, torch):
+    """2^20 heads, the most that a call takes: 2^23 workgroups of 512 threads sum the rows of T.  Halves of the heads give
+    the same bits."""
+    H, n = 1 << 20, 16
+    print(f"alg2 {H} heads", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(6)
+    q, k, v = ((torch.randn((1, H, n, 64), generator=gen, device="cuda") / 8 ** 0.5).to(torch.bfloat16) for _ in range(3))
+    kw = dict(seed=2, cap_scale=4.0, kappa=1.2)
+    out, lse, _ = ha.hyperattn_forward_alg2(q, k, v, 8, 4, 3, **kw)
+    for half in (slice(0, H // 2), slice(H // 2, H)):
+        o, l, _ = ha.hyperattn_forward_alg2(*(x[:, half].contiguous() for x in (q, k, v)), 8, 4, 3, **kw)
+        assert torch.equal(out[:, half], o) and torch.equal(lse[:, half], l)

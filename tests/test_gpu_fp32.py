@@ -95,6 +95,25 @@ def test_exact_backward_fp32_forms(H, n, d, causal):
         assert (err <= 2.0 ** -12 * lim + 2.0 ** -100).all(), (name, err.max())
 
 
+def _frobenius(got, ref):
+    return float(((got - ref) ** 2).sum() ** 0.5 / (ref ** 2).sum() ** 0.5)
+
+
+@pytest.mark.parametrize("d,n,b,m,causal,n_min", [(64, 2048, 128, 128, 0, 4096), (128, 2048, 256, 256, 0, 4096)])
+def test_log_row_sums_fp32_rounding(d, n, b, m, causal, n_min):
+    """Log row sums near ln 2048 + 1/2 = 8.1: one rounding of the result is 2^-20 / sqrt(12) = 2.8e-7 at the root mean square,
+    3.4e-8 of the value; sums and scores add to it.  Bound 4.2e-8, below what a logarithm of the result's own size adds (1.4e-7
+    and the function's own error: 5e-8 in all)."""
+    import paper_2310_05869_amd as ha
+    print(f"fp32 log row sums d={d} n={n}", flush=True)
+    cfg = dict(B=1, H=2, n=n, d=d, dtype="fp32", law="iid", b=b, m=m, r=7, causal=causal, n_min=n_min, seed=3)
+    Q, K, V = synth_inputs.make_qkv(cfg, seed=9)
+    _, lse = ha.hyperattn_forward(*(to_device(x, "fp32") for x in (Q, K, V)), b, m, 7, causal=bool(causal), n_min=n_min, seed=3)
+    err = _frobenius(to_host(lse), run_oracle(Q, K, V, cfg)[1])
+    print(f"  {err:.2e}", flush=True)
+    assert err <= 4.2e-8
+
+
 @pytest.mark.parametrize("d", [64, 128])
 def test_stages_past_four_gib(d):
     """Block and sampled stage of one fp32 head whose tensors pass 4 GiB, the reach of a 32-bit byte offset: blocks at the

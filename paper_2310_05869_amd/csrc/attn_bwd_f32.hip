@@ -60,6 +60,12 @@ __global__ __launch_bounds__(kFBT, D == 64 ? 2 : 1) void attn_bwd_f32_kernel(Bwd
   constexpr int kRT = 32 * (4 / KW);
   constexpr int KJ = D / 8;
   constexpr int DT = D / 32;
+  // dQ: a dP is two sums of half the columns each; as one chain of d products it had dQ's error above that of the half-row
+  // sums of the form before (4 blocks of 256 rows, d = 128: 4.8e-7 against 4.2e-7 relative; with this and log row sums of
+  // one rounding 4.0e-7).  The scores stay one chain, the forward's: P = exp(S - L) then cancels their rounding where
+  // scores are large (64 clusters, scores to 250: dQ's error 2.1e-5, with halves 1.7e-4).  The dK / dV passes have no
+  // registers for it, and their errors are below those of the form before.
+  constexpr int kChains = kDq ? 2 : 1;
   const AttnArgs& f = a.f;
   const Geometry& g = f.g;
   const int tid = threadIdx.x;
@@ -197,11 +203,12 @@ __global__ __launch_bounds__(kFBT, D == 64 ? 2 : 1) void attn_bwd_f32_kernel(Bwd
     }
     f32x4 bf[KJ];
     load_rows(brsrc, row_c, bf);
-    f32x16 c, e;
+    f32x16 c, es[kChains];
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       c[i] = 0.f;
-      e[i] = 0.f;
+#pragma unroll
+      for (int k = 0; k < kChains; ++k) es[k][i] = 0.f;
     }
 #pragma unroll
     for (int j = 0; j < KJ; ++j)
@@ -212,7 +219,10 @@ __global__ __launch_bounds__(kFBT, D == 64 ? 2 : 1) void attn_bwd_f32_kernel(Bwd
 #pragma unroll
     for (int j = 0; j < KJ; ++j)
 #pragma unroll
-      for (int z = 0; z < 4; ++z) e = __builtin_amdgcn_mfma_f32_32x32x2f32(bf[j][z], av[j][z], e, 0, 0, 0);
+      for (int z = 0; z < 4; ++z) es[j % kChains] = __builtin_amdgcn_mfma_f32_32x32x2f32(bf[j][z], av[j][z], es[j % kChains], 0, 0, 0);
+
+    f32x16 e = es[0];
+    if constexpr (kChains == 2) e += es[1];
 
     // masks, on the tiles that have any: in the sampled-key pass the keys differ by lane
     const int tbase = kt * kFTT;

@@ -114,6 +114,26 @@ def test_log_row_sums_fp32_rounding(d, n, b, m, causal, n_min):
     assert err <= 4.2e-8
 
 
+def test_query_gradients_fp32_rounding():
+    """dQ of a causal problem against 64 bits, relative Frobenius.  dS = P (dP - delta): a chain of k fp32 products is off by
+    about sqrt(k) times a rounding; bound 4.4e-7 between the two forms measured, dP as two chains of 64 (4.0e-7) and
+    as one of 128 (4.8e-7)."""
+    import paper_2310_05869_amd as ha
+    d, n, b, m, n_min = 128, 1024, 128, 64, 256
+    print("fp32 dQ rounding", flush=True)
+    cfg = dict(B=1, H=2, n=n, d=d, dtype="fp32", law="iid", b=b, m=m, r=7, causal=1, n_min=n_min, seed=3)
+    Q, K, V = synth_inputs.make_qkv(cfg, seed=9)
+    G = synth_inputs.iid_qkv(1, 2, n, d, "fp32", seed=5)[0]
+    t = [to_device(x, "fp32") for x in (Q, K, V, G)]
+    kw = dict(causal=True, n_min=n_min, seed=3)
+    ws = ha.alloc_workspace(ha.make_shape(1, 2, n, d, ha.HA_FP32), ha.make_params(b, m, 7, 1, n_min, 3))
+    out, lse = ha.hyperattn_forward(*t[:3], b, m, 7, workspace=ws, **kw)
+    dQ = ha.hyperattn_backward(*t[:3], out, lse, t[3], b, m, 7, fwd_workspace=ws, **kw)[0]
+    err = _frobenius(to_host(dQ), orc.hyperattn_backward(Q, K, V, G, b=b, m=m, r=7, **kw)[0])
+    print(f"  {err:.2e}", flush=True)
+    assert err <= 4.4e-7
+
+
 @pytest.mark.parametrize("d", [64, 128])
 def test_stages_past_four_gib(d):
     """Block and sampled stage of one fp32 head whose tensors pass 4 GiB, the reach of a 32-bit byte offset: blocks at the

@@ -150,8 +150,9 @@ int hyperattn_forward_ex(const void* Q, const void* K, const void* V, void* out,
 /* Measurement variant of hyperattn_forward (same computation, same launches):
  * HIP events are recorded on `stream` between the stages, the call WAITS for the
  * last one, and stage_ms_host[0..5] (host memory) receive the elapsed
- * milliseconds of: [0] random draws into the workspace, [1] sortLSH hashing of Q
- * and K, [2] the sort (Algorithm 1's permutations), [3] block + sampled
+ * milliseconds of: [0] always 0 (the random draws, once a launch of their own, are
+ * stored by the hashing launch), [1] sortLSH hashing of Q and K with the draws, [2] the
+ * sort (Algorithm 1's permutations), [3] block + sampled
  * attention of all nodes, [4] the exact causal base case with the Algorithm 4
  * merge (0 when not causal), [5] the whole call.  Unlike every other entry
  * point this one synchronises with the stream. */

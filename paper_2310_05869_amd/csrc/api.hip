@@ -302,8 +302,8 @@ static AttnArgs node_args(const void* Q, const void* K, const void* V, void* out
   return a;
 }
 
-// ev, when non-null, receives 6 events recorded on the stream: start, after
-// again (draws: part of the hashing launch), after hashing, after sorting, after the node attention, after the base case.
+// ev, when non-null, receives 5 events recorded on the stream: start, after hashing (with the call's draws), after sorting,
+// after the node attention, after the base case.
 // node_stamps / base_stamps, when non-null, select the measuring instantiation of the
 // node launch / the base-case launch and receive its workgroups' stamp records.
 static int forward_impl(const void* Q, const void* K, const void* V, void* out, float* lse, const ha_shape* sh,
@@ -339,14 +339,13 @@ static int forward_impl(const void* Q, const void* K, const void* V, void* out, 
 
   mark(0);
   if (g.levels > 0) {
-    mark(1);
     rc = run_hash(Q, K, codes_q, codes_k, g, p->seed, R_dev, samples_dev, proj, samples, st);
     if (rc != HA_OK) return rc;
-    mark(2);
+    mark(1);
     rc = launch_seg_sort_nodes(codes_q, codes_k, perm_q, perm_k, pos_k, g.m > 0 ? samples : nullptr, samp_blk,
                                (uint32_t*)(base + lay.sort_hist), g, st);
     if (rc != HA_OK) return rc;
-    mark(3);
+    mark(2);
 
     AttnArgs a = node_args(Q, K, V, out, lse, out_f32, g, base, lay);
     a.stamps = node_stamps;
@@ -355,14 +354,13 @@ static int forward_impl(const void* Q, const void* K, const void* V, void* out, 
   } else {
     mark(1);
     mark(2);
-    mark(3);
   }
-  mark(4);
+  mark(3);
   if (g.causal) {
     rc = run_base_case(Q, K, V, out, lse, out_f32, g, part_o, part_l, st, base_stamps);
     if (rc != HA_OK) return rc;
   }
-  mark(5);
+  mark(4);
   return HA_OK;
 }
 
@@ -631,23 +629,24 @@ int hyperattn_forward_timed(const void* Q, const void* K, const void* V, void* o
                             const ha_shape* shape, const ha_params* params, void* workspace,
                             size_t workspace_bytes, void* stream, float* stage_ms_host) {
   if (!stage_ms_host) return HA_ERR_NULL;
-  hipEvent_t ev[6];
-  for (int i = 0; i < 6; ++i)
+  constexpr int NE = 5;
+  hipEvent_t ev[NE];
+  for (int i = 0; i < NE; ++i)
     if (hipEventCreate(&ev[i]) != hipSuccess) {
       for (int j = 0; j < i; ++j) (void)hipEventDestroy(ev[j]);
       return HA_ERR_LAUNCH;
     }
   int rc = forward_impl(Q, K, V, out, lse, shape, params, nullptr, nullptr, workspace, workspace_bytes, stream, ev);
-  for (int i = 0; i < 6; ++i) stage_ms_host[i] = 0.f;
+  for (int i = 0; i <= NE; ++i) stage_ms_host[i] = 0.f;
   Geometry g;
   const bool ran = rc == HA_OK && make_geometry(shape, params, &g) == HA_OK && g.BH > 0 && g.n > 0;
   if (ran) {
-    if (hipEventSynchronize(ev[5]) != hipSuccess) rc = HA_ERR_LAUNCH;
-    for (int i = 0; i < 5 && rc == HA_OK; ++i)
-      if (hipEventElapsedTime(&stage_ms_host[i], ev[i], ev[i + 1]) != hipSuccess) rc = HA_ERR_LAUNCH;
-    if (rc == HA_OK && hipEventElapsedTime(&stage_ms_host[5], ev[0], ev[5]) != hipSuccess) rc = HA_ERR_LAUNCH;
+    if (hipEventSynchronize(ev[NE - 1]) != hipSuccess) rc = HA_ERR_LAUNCH;
+    for (int i = 0; i < NE - 1 && rc == HA_OK; ++i)
+      if (hipEventElapsedTime(&stage_ms_host[i + 1], ev[i], ev[i + 1]) != hipSuccess) rc = HA_ERR_LAUNCH;
+    if (rc == HA_OK && hipEventElapsedTime(&stage_ms_host[NE], ev[0], ev[NE - 1]) != hipSuccess) rc = HA_ERR_LAUNCH;
   }
-  for (int i = 0; i < 6; ++i) (void)hipEventDestroy(ev[i]);
+  for (int i = 0; i < NE; ++i) (void)hipEventDestroy(ev[i]);
   return rc;
 }
 

@@ -781,3 +781,13 @@ def test_exact_attention_with_shared_key_ranges(ha, torch, H, n, causal, d):
         absv = (s.softmax(-1) @ V[0, hd].float().abs()).double().cpu().numpy()
         assert_close(to_host(out[0, hd]), ref, "bf16", f"out head {hd}", absv=absv, max_plain_frac=5e-3 if causal else 1e-5)
         assert_lse_close(to_host(lse[0, hd]), s.logsumexp(-1).double().cpu().numpy(), "bf16", f"lse head {hd}")
+
+
+def test_stage_times_add_up(ha, torch):
+    """Stages of the timed forward: the draws' own is 0 (the hashing launch stores them), the others follow each other."""
+    Q, K, V = (torch.randn((1, 4, 8192, 64), device="cuda").to(torch.bfloat16) for _ in range(3))
+    for _ in range(3):
+        ms = ha.hyperattn_forward_timed(Q, K, V, 256, 256, 7, causal=True, n_min=4096)[2]
+    assert ms["prep"] == 0.0
+    assert all(ms[k] > 0 for k in ("lsh_hash", "seg_sort", "node_attn", "causal_base"))
+    assert abs(sum(ms[k] for k in ("lsh_hash", "seg_sort", "node_attn", "causal_base")) - ms["total"]) < 1e-3

@@ -77,16 +77,18 @@ __host__ __device__ inline int64_t node_grid(const Geometry& g) {
 // that fits the chip at once (two or three workgroups per CU) is placed before any of them has finished: workgroup i
 // goes to XCD i mod 8 and, within it, to its 32 CUs in turn, so what a CU gets is fixed by the order.
 //
-// Launches of up to 256 tiles per XCD (in whole blocks): heaviest tiles first ACROSS the blocks, block b on XCD
-// b mod 8 where there are 8 or more (its K and V stay in one L2); every second round of 32 tiles of an XCD runs
-// backwards, so the CU (and the shader engine) that got the heaviest tile of one round gets the lightest of the next.
+// Causal launches of up to 256 tiles per XCD (in whole blocks): heaviest tiles first ACROSS the blocks; every second round of
+// 32 tiles of an XCD runs backwards, so the CU (and the shader engine) that got the heaviest tile of one round gets the
+// lightest of the next.  Where the number of blocks is a multiple of 8, block b stays on XCD b mod 8 (its K and V in one
+// L2); 12 blocks share two XCDs each, an odd number all eight.
 // Block after block, the order before, gave a CU the same rank of several blocks: 186 key tiles on the fullest CU
 // against 99 on average at 24 blocks of 32 tiles.  Measured (MI355X): forward, 12 heads, n = 8192, d = 64: 141 ->
 // 119 us (122 with every round forwards); forward + backward: fp32, 4 heads, n = 4096: 336 -> 283 (305) us;
 // exact, 12 heads, n = 5000, d = 128: 530 -> 408 (437) us.
 //
-// Larger launches, where workgroups are replaced as they finish: every XCD takes a contiguous range, block after
-// block, heaviest first, the starting tile rotated from one block to the next: an XCD's workgroups are dealt to its
+// Unmasked launches, whose tiles are all alike, and larger causal ones, where workgroups are replaced as they finish: every
+// XCD takes a contiguous range, block after block (across the blocks an unmasked launch was 1 % slower: 12 heads,
+// n = 16384, d = 64: 947 -> 955 us), heaviest first, the starting tile rotated from one block to the next: an XCD's workgroups are dealt to its
 // four shader engines in turn, and a fixed order would hand one of them every fourth, the heaviest, tile of
 // every block.  The order above, in groups of 64 tiles per XCD, is 0.8 % slower there (forward, 32 heads, n = 131072,
 // d = 128: 9.14 against 9.22 ms; 9.31 with 256): more blocks in flight than an L2 holds.
@@ -106,7 +108,7 @@ __device__ inline ExactPlace exact_place(const AttnArgs& a, int wg) {
   const int blocks = nblk * a.g.BH;
   ExactPlace e;
   int b;
-  if (blocks > 8 * ((kOrderWhole + tpb - 1) / tpb)) {
+  if (!a.exact_causal || blocks > 8 * ((kOrderWhole + tpb - 1) / tpb)) {
     const int idx = logical_block(wg, blocks * tpb);
     b = idx / tpb;
     e.rank = (idx % tpb + b) % tpb;

@@ -171,8 +171,9 @@ __global__ __launch_bounds__(64 * NW * NG, (D == 64 && NW == 4 && NG == 1) ? 3 :
   // NaN is NaN, and with two wave groups a whole tile can lie there.
   auto rows_rsrc = [&](const uint16_t* head, int kt) {
     if (kNode) return __builtin_amdgcn_make_buffer_rsrc((void*)head, 0, (int)((uint32_t)a.g.n * (D * 2)), 0x00020000);
-    const int row = w.k0 + (NG * kt + grp) * kKT;
-    return __builtin_amdgcn_make_buffer_rsrc((void*)(head + (int64_t)row * D), 0, max(0, w.k1 - row) * (D * 2), 0x00020000);
+    const int off = (w.k0 + (NG * kt + grp) * kKT) * (D * 2);
+    return __builtin_amdgcn_make_buffer_rsrc((void*)(reinterpret_cast<const unsigned char*>(head) + (uint32_t)off), 0,
+                                             max(0, w.k1 * (D * 2) - off), 0x00020000);
   };
   u32x4 kreg[TR::NKC], vreg[TR::NKC];
   auto load_rows = [&](int kt, const uint16_t* head, u32x4 (&reg)[TR::NKC]) {

@@ -766,13 +766,24 @@ static int launch_one(const AttnArgs& args, hipStream_t st) {
 // n = 16384 (256) 370 -> 310, 8 heads (512) 578 -> 540, 16 heads (1024) 1032 -> 1029.
 // The short loops of the base case prefer two 4-wave workgroups per CU.
 constexpr int kWideExactMinRows = 8192;
-// Launches that leave a CU at most one workgroup (causal: up to one and a half, their tiles being unequal) are bound by
-// the longest chain of key tiles of a workgroup: two groups of four waves then share it.  One group -> two (MI355X):
-// 4 heads, n = 4096, d = 64 52.8 -> 41.2 us, d = 128 70.8 -> 59.3; one head, n = 16384, d = 64 202 -> 149, d = 128
-// 267 -> 215; causal, 12 heads, n = 4096 (384 workgroups) d = 64 54.3 -> 45.4, d = 128 77.0 -> 68.9; 14 heads (448)
-// 79.0 -> 82.9; unmasked, 12 heads 73.2 -> 83.5; base case of 4 heads, n = 8192, d = 64 (256): call 81.1 -> 69.2.
-constexpr int64_t kSplitExactMaxGrid = 256, kSplitExactMaxGridCausal = 384;
-constexpr int kSplitExactMinRows = 256;
+// Launches that leave a CU at most one workgroup are bound by the longest chain of key tiles of a workgroup: two groups of
+// four waves then share it.  One such workgroup fills a CU, so past 256 a second round begins: in causal launches
+// with the lightest tiles, which is worth it the longer the rows.  Short rows gain nothing.  One group -> two (MI355X, us):
+//   unmasked: 4 heads, n = 4096, d = 64 54.4 -> 42.0, d = 128 73.0 -> 60.6; 32 heads (256), n = 1024: 17.3 -> 15.4, 23.7 -> 23.5;
+//     32 heads (192), n = 768: 13.7 -> 12.4, 18.4 -> 17.5; 42 heads (252): 15.9 -> 14.9, but d = 128 22.1 -> 23.1; 64 heads (192),
+//     n = 384: 11.2 -> 11.7, 12.0 -> 12.2
+//   causal: 12 heads (384), n = 4096: 55.9 -> 45.4, 77.5 -> 68.5; 16 heads (384), n = 3072: 42.8 -> 36.2, 59.7 -> 54.6; 24 heads (384),
+//     n = 2048: 30.5 -> 29.4, but 42.8 -> 43.6, 22 heads (352): 32.0 -> 26.5, 42.4 -> 39.7; 40 heads (320), n = 1024: 18.0 -> 16.7,
+//     24.8 -> 24.6, but 48 heads (384): 18.0 -> 20.1, 25.9 -> 29.7; 96 heads (384), n = 512: 11.7 -> 15.5, 17.6 -> 23.3
+//   base case of 4 heads, n = 8192, d = 64 (256): call 81.1 -> 69.2
+constexpr int kSplitExactMinRows = 640;
+static bool split_exact(const AttnArgs& a) {
+  const int rows = a.exact_block < a.exact_rows_q ? a.exact_block : a.exact_rows_q;
+  if (rows < kSplitExactMinRows) return false;
+  const int64_t grid = exact_grid<128>(a);
+  if (!a.exact_causal) return grid <= (a.g.d == 128 && rows < 1024 ? 160 : 256);
+  return grid <= (rows < 1024 ? 256 : rows < 1536 ? 320 : rows < 3072 ? 352 : 384);
+}
 constexpr int64_t kWideExactMinGrid = 256, kWideExactMinGridCausal = 1024;
 
 int64_t attn_mfma_grid(const AttnArgs& a, int mode) {
@@ -782,8 +793,7 @@ int64_t attn_mfma_grid(const AttnArgs& a, int mode) {
 int launch_attn_mfma(const AttnArgs& a, int mode, hipStream_t st) {
   if (a.g.dtype != HA_BF16) return HA_ERR_DTYPE;
   if (mode == kModeExact && a.merge_levels > 0 && !a.part_bf16) return HA_ERR_DTYPE;  // this kernel folds bf16 partial rows
-  const bool split = mode == kModeExact && exact_grid<128>(a) <= (a.exact_causal ? kSplitExactMaxGridCausal : kSplitExactMaxGrid) &&
-                     a.exact_block >= kSplitExactMinRows && a.exact_rows_q >= kSplitExactMinRows;
+  const bool split = mode == kModeExact && split_exact(a);
   if (a.stamps != nullptr) {  // the measuring instantiations of the forms the forward pass launches
     if (a.g.d == 128) {
       if (mode == kModeNode) return launch_one<128, kModeNode, HA_NW_NODE, true>(a, st);

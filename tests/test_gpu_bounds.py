@@ -43,6 +43,7 @@ def _generator(torch, seed):
 
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("dtype,d,H,n", [("bf16", 64, 1, 257), ("bf16", 128, 1, 257), ("bf16", 64, 2, 321), ("bf16", 128, 2, 321),
+                                         ("bf16", 64, 2, 641), ("bf16", 128, 2, 705),   # two wave groups, the second's last tile past the end
                                          ("bf16", 64, 2, 5), ("bf16", 128, 100, 300),   # one wave group
                                          ("bf16", 128, 40, 8200),                       # eight waves
                                          ("fp32", 64, 2, 33), ("fp32", 128, 2, 5), ("fp32", 64, 20, 2050)])
@@ -61,7 +62,7 @@ def test_exact_forward_reads_its_own_rows_only(ha, torch, dtype, d, H, n, causal
         assert torch.equal(lse[:, own], results[0][1][:, own])
 
 
-@pytest.mark.parametrize("dtype,d,H,n_min", [("bf16", 64, 2, 320), ("bf16", 128, 2, 320), ("bf16", 64, 70, 320),
+@pytest.mark.parametrize("dtype,d,H,n_min", [("bf16", 64, 2, 320), ("bf16", 128, 2, 320), ("bf16", 64, 2, 704), ("bf16", 128, 2, 704), ("bf16", 64, 70, 320),
                                              ("bf16", 128, 3, 65), ("fp32", 64, 2, 320), ("fp32", 128, 2, 33)])
 def test_next_diagonal_block_stays_out(ha, torch, dtype, d, H, n_min):
     """The first n_min rows of a causal call see nothing of the rows behind them."""
@@ -72,7 +73,7 @@ def test_next_diagonal_block_stays_out(ha, torch, dtype, d, H, n_min):
         gen = _generator(torch, n_min)
         q, k, v = (_rows(torch, gen, H, 2 * n_min, d, dt, 0.0) for _ in range(3))
         v[:, :, n_min:] = value
-        results.append(ha.hyperattn_forward(q, k, v, n_min if n_min < 64 else n_min // 5, 16, 7, causal=True, n_min=n_min, seed=1))
+        results.append(ha.hyperattn_forward(q, k, v, n_min if n_min < 64 else n_min // 5 if n_min % 5 == 0 else n_min // 11, 16, 7, causal=True, n_min=n_min, seed=1))
     assert torch.isfinite(results[0][0]).all()
     for out, lse in results[1:]:
         assert torch.equal(out[:, :, :n_min], results[0][0][:, :, :n_min])

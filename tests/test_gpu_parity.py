@@ -783,6 +783,16 @@ def test_exact_attention_with_shared_key_ranges(ha, torch, H, n, causal, d):
         assert_lse_close(to_host(lse[0, hd]), s.logsumexp(-1).double().cpu().numpy(), "bf16", f"lse head {hd}")
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("H,n,causal", [(2, 640, True), (2, 641, True), (1, 705, False), (3, 768, True),   # odd and even numbers of key tiles
+                                        (26, 768, False), (27, 768, False),                                # d = 128: 156 and 162 workgroups
+                                        (40, 1024, True), (41, 1024, True),                                # 320 and 328
+                                        (22, 2048, True), (23, 2048, True)])                               # 352 and 368
+def test_exact_attention_around_the_shared_form(ha, torch, H, n, causal, d):
+    """Where the form of two wave groups begins and ends: row counts and workgroups on both sides of its rule."""
+    test_exact_attention_with_shared_key_ranges(ha, torch, H, n, causal, d)
+
+
 def test_stage_times_add_up(ha, torch):
     """Stages of the timed forward: the draws' own is 0 (the hashing launch stores them), the others follow each other."""
     Q, K, V = (torch.randn((1, 4, 8192, 64), device="cuda").to(torch.bfloat16) for _ in range(3))

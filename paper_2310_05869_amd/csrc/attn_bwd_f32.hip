@@ -18,7 +18,11 @@
 // KW waves share a group of R rows, each taking every KW-th tile; their sums are added through LDS in
 // wave order, so results are bit-reproducible.
 //
-// What bounds it: the matrix pipe.  Measured (MI355X, backward of exact attention, the five algorithmic products
+// What bounds it: the matrix pipe where the chip is full.  At 4 heads, n = 4096 (at most two waves per SIMD) it is busy
+// 52 - 57 % of the cycles in the exact passes and 14 - 24 % in the node passes; waves wait for issue 55 - 65 % of their
+// time in the former.  The dK / dV passes at d = 64 spill 56 to 92 bytes per lane (two fragments in flight beside rows and
+// accumulators in 256 registers).
+// Measured (MI355X, backward of exact attention, the five algorithmic products
 // counted, seven executed), against two lanes per row with fp32 FMA and separate dK and dV passes, the form before:
 // 8 heads, n = 4096, d = 64 5.5 -> 1.29 ms, d = 128 12.0 -> 2.4 ms; 32 heads, n = 8192, d = 64 17.1 ms = 80 TFLOP/s
 // (112 executed, of 157); 4 causal heads, n = 4096, n_min = 1024, forward + backward 4.07 -> 0.45 ms.  Then the vector
@@ -48,7 +52,7 @@ __host__ __device__ inline size_t bwd_f32_lds_bytes(const Geometry& g, int mode)
   return list > (size_t)F32BwdLds<D>::BYTES ? list : (size_t)F32BwdLds<D>::BYTES + hits;
 }
 
-// d = 128 keeps up to 416 values per lane (two fragments in flight beside rows and accumulators): one wave per SIMD
+// d = 128 keeps up to 483 registers per lane (two fragments in flight beside rows and accumulators): one wave per SIMD
 // FINAL: the node passes of an unmasked problem, which write the final gradients.
 template <int D, int MODE, int KW, bool FINAL>
 __global__ __launch_bounds__(kFBT, D == 64 ? 2 : 1) void attn_bwd_f32_kernel(BwdArgs a) {

@@ -86,12 +86,12 @@ __host__ __device__ inline int64_t node_grid(const Geometry& g) {
 // 119 us (122 with every round forwards); forward + backward: fp32, 4 heads, n = 4096: 336 -> 283 (305) us;
 // exact, 12 heads, n = 5000, d = 128: 530 -> 408 (437) us.
 //
-// Unmasked launches, whose tiles are all alike, and larger causal ones, where workgroups are replaced as they finish: every
-// XCD takes a contiguous range, block after block (across the blocks an unmasked launch was 1 % slower: 12 heads,
-// n = 16384, d = 64: 947 -> 955 us), heaviest first, the starting tile rotated from one block to the next: an XCD's workgroups are dealt to its
-// four shader engines in turn, and a fixed order would hand one of them every fourth, the heaviest, tile of
-// every block.  The order above, in groups of 64 tiles per XCD, is 0.8 % slower there (forward, 32 heads, n = 131072,
-// d = 128: 9.14 against 9.22 ms; 9.31 with 256): more blocks in flight than an L2 holds.
+// Unmasked launches, whose tiles are all alike, and larger causal ones, where workgroups are replaced as they finish:
+// every XCD takes a contiguous range, block after block (across the blocks an unmasked launch was 1 % slower: 12
+// heads, n = 16384, d = 64: 947 -> 955 us), heaviest first, the starting tile rotated from one block to the next: an XCD's
+// workgroups are dealt to its four shader engines in turn, and a fixed order would hand one of them every fourth, the
+// heaviest, tile of every block.  The causal order above, in groups of 64 tiles per XCD, is 0.8 % slower there (forward, 32
+// heads, n = 131072, d = 128: 9.14 against 9.22 ms; 9.31 with 256): more blocks in flight than an L2 holds.
 struct ExactPlace {
   int bh, blk;
   int rank;  // tile within the block, heaviest first

@@ -2,7 +2,8 @@
 // (v_mfma_f32_32x32x2_f32: fp32 products, fp32 sums), with the same node / exact
 // modes and the same outputs as the bf16 kernel (attn_mfma.hip).
 //
-// What bounds it: the matrix pipe.  One 32 x 32 tile of scores and its product with V
+// What bounds it: the matrix pipe where the chip is full (4 heads, n = 4096 in blocks of 1024, two waves per SIMD: busy 46 %
+// of the cycles).  At d = 128, 32 to 64 bytes per lane spill (256 registers).  One 32 x 32 tile of scores and its product with V
 // take D/2 + D/2 instructions of 64 cycles each, against 8 KiB of K and 8 KiB of V
 // fragments at d = 64 that every wave reads straight from the caches into the operand
 // layout (16 B/clk per CU where four waves share nothing): no LDS staging, hence no

@@ -72,11 +72,11 @@ inline int64_t bwd_sample_chunks(const Geometry& g, int chunk) {
   return total;
 }
 
-// Sorted query positions per workgroup of the sampled-key pass: 2048, halved while the pass has fewer than
-// 1024 workgroups of 128 samples (four per CU), but not below 2 m: every chunk writes two fp32 rows per sample, at
-// 2 m as many bytes as the bf16 query rows it reads.  Measured against 2048 always: 12 heads, n = 16384, d = 64,
-// b = m = 256 (192 workgroups of 256 CUs -> 768) forward + backward 411 -> 342 us; fp32, 4 causal heads, n = 4096,
-// m = 64: 445 -> 337 us.
+// Sorted query positions per workgroup of the sampled-key pass: 2048, halved while the pass has fewer than 1024
+// workgroups of 128 samples (two rounds of the two that a CU holds), but not below 2 m: every chunk writes two fp32 rows
+// per sample, at 2 m as many bytes as the bf16 query rows it reads.  Measured against 2048 always: 12 heads, n = 16384,
+// d = 64, b = m = 256 (192 workgroups of 256 CUs -> 768) forward + backward 411 -> 342 us; fp32, 4 causal heads,
+// n = 4096, m = 64: 445 -> 337 us.
 inline int bwd_chunk(const Geometry& g) {
   int chunk = 2048;
   const int64_t slabs = (g.m + 127) / 128;

@@ -84,8 +84,8 @@ enum AttnMode : int32_t {
 // Division of 0 <= n < 2^31 by a divisor known on the host: two scalar multiplications and a shift, where
 // a division by a kernel argument is some thirty vector instructions.  A node workgroup's place took eight of them (and a
 // 64-bit one) ahead of its first load.  Measured (MI355X) with one barrier less in the key list: forward + backward,
-// 12 heads, n = 16384, d = 64: 234.7 -> 231.8 us; forward, 15 heads, n = 6300, d = 128: 54.3 -> 53.5; 64 heads,
-// n = 65536, d = 64: 1363 -> 1353; others within 0.5 %.
+// 12 heads, n = 16384, d = 64: 234.7 -> 231.8 us; what the forwards gained (up to 1 %) is no more than two runs of one
+// build differ.
 struct FastDiv {
   uint32_t mul, shift, d;
   __host__ __device__ inline int div(int n) const { return (int)(((uint64_t)(uint32_t)n * mul) >> shift); }

@@ -37,7 +37,7 @@
 // of 32 cycles per tile and wave in the dK / dV passes).  So that order is written out and pinned (below), the rare
 // masks sit behind a branch, and nothing in the loop waits for memory but the one wait per tile.  Counters (32 causal
 // heads, n = 32768, d = 128): matrix pipe busy 60 % at 1.73 GHz in the exact dK / dV pass, 55 % in the exact dQ pass, 48 % with the
-// sampled keys (the steady loop of the forward: 62 % at 1.65 GHz); the block keys move 4.6 TB/s, a copy 4.9.
+// sampled keys (the steady loop of the forward: 62 % at 1.65 GHz); the block keys move 4.4 TB/s, a copy 4.9.
 // Measured (MI355X, 32 causal heads, n = 131072, d = 128, b = m = 256).  First form: dK and dV in passes of their own,
 // tiles staged through registers; second: one pass, tiles by DMA; third: this one, pinned order.
 //   dK / dV of the base case 13.9 -> 10.0 -> 8.2 ms, of the sampled keys 5.5 -> 4.1 -> 2.9 ms, of the blocks

@@ -215,9 +215,9 @@ __global__ __launch_bounds__(64 * NW * NG, (D == 64 && NW == 4 && NG == 1) ? 3 :
   float l_run = 0.f;  // this lane's share of the row sum
   // Cap mode (Algorithm 2 as printed): once the block's keys are done (tile nb_tiles on) l_run becomes the capped sum of
   // the samples and msum keeps the masked row sum, from which the row's cap C_i follows.
-  // One more vector instruction per score than the plain node mode (32 heads, n = 32768, d = 128, b = m = 256: 487 us where
-  // that launch takes 424; vector issue 51 against 44 % of the cycles), against 600 in a kernel of its own without the
-  // software pipeline below.  At d = 64 the 168 registers that three workgroups per CU leave cost it 20 bytes of scratch per lane.
+  // One more vector instruction per score than the plain node mode (32 heads, n = 32768, d = 128, b = m = 256: 8 % more
+  // cycles, vector issue 50 against 44 % of them; 414 to 487 us, by the clock of the run, where a kernel of its own without
+  // the software pipeline below took 600).  At d = 64 the 168 registers that three workgroups per CU leave cost it 20 bytes of scratch per lane.
   const int nb_tiles = kCap ? (nb + kKT - 1) / kKT : 0;
   float msum = 0.f, log2capw = INFINITY;  // log2 of (s / m) C_i
   const float floor_term = kCap && a.kappa > 0.f ? a.log_tau[(int64_t)w.bh * a.g.total_nodes + w.nr.heap] - logf(a.kappa) : -INFINITY;

@@ -760,11 +760,12 @@ static int launch_one(const AttnArgs& args, hipStream_t st) {
 #define HA_NW_EXACT 4
 #endif
 
-// Exact attention over long key ranges shares each K / V tile among 8 waves (one workgroup per CU) at d = 128: 3-6 %
-// faster where that leaves every CU a workgroup, and causal ones, of unequal length, several; with fewer, twice as many
-// 4-wave workgroups reach the idle CUs.  8 waves -> 4 waves (MI355X, d = 128), unmasked: 8 heads, n = 8192 (256 wide
-// workgroups) 243 -> 259 us, 2 heads, n = 16384 (128) 361 -> 288, one head (64) 358 -> 268; causal: 4 heads,
-// n = 16384 (256) 370 -> 310, 8 heads (512) 578 -> 540, 16 heads (1024) 1032 -> 1029.
+// Exact attention over long key ranges shares each K / V tile among 8 waves (one workgroup per CU) at d = 128.  Unmasked:
+// wherever the 4-wave form would put two workgroups on some CUs, which all then wait for (up to 256 of them, 128 wide
+// ones, two wave groups share the keys instead); causal, of unequal length: where every CU gets several.
+// 8 waves -> 4 waves (MI355X, d = 128), unmasked, n = 8192: 8 heads (256 wide workgroups) 243 -> 259 us, 5 heads (160) 188 ->
+// 198, 7 heads (224) 224 -> 233; 2 heads, n = 16384 (128) 361 -> 288, 3 heads (192) 400 -> 416, one head (64) 358 -> 268;
+// causal: 4 heads, n = 16384 (256) 370 -> 310, 8 heads (512) 578 -> 540, 16 heads (1024) 1032 -> 1029.
 // The short loops of the base case prefer two 4-wave workgroups per CU.
 constexpr int kWideExactMinRows = 8192;
 // Launches that leave a CU at most one workgroup are bound by the longest chain of key tiles of a workgroup: two groups of
@@ -785,7 +786,7 @@ static bool split_exact(const AttnArgs& a) {
   if (!a.exact_causal) return grid <= (a.g.d == 128 && rows < 1024 ? 160 : 256);
   return grid <= (rows < 1024 ? 256 : rows < 1536 ? 320 : rows < 3072 ? 352 : 384);
 }
-constexpr int64_t kWideExactMinGrid = 256, kWideExactMinGridCausal = 1024;
+constexpr int64_t kWideExactMinGrid = 129, kWideExactMinGridCausal = 1024;
 
 int64_t attn_mfma_grid(const AttnArgs& a, int mode) {
   return mode == kModeNode ? node_grid<32 * HA_NW_NODE>(a.g) : exact_grid<32 * HA_NW_EXACT>(a);

@@ -635,9 +635,9 @@ def test_forward_on_a_side_stream_and_under_graph_capture(ha, torch):
 
 
 def test_exact_attention_wide_workgroups_sampled_rows(ha, torch):
-    """Exact attention at n = 8192, causal or not, takes the 8-wave form of the kernel at d = 128; rows
+    """Exact attention of two heads at n = 8192, causal or not (two wave groups share a workgroup's keys); rows
     sampled across the sequence are checked against the definition."""
-    print("exact attention, 8-wave workgroups", flush=True)
+    print("exact attention, long rows", flush=True)
     for d, causal in ((128, False), (128, True), (64, False)):
         cfg = dict(B=1, H=2, n=8192, d=d, dtype="bf16", law="iid")
         Q, K, V = synth_inputs.make_qkv(cfg, seed=17)
@@ -740,9 +740,10 @@ def test_node_sort_is_the_stable_order(ha, torch, H, n, b, r, causal, n_min):
             assert torch.equal(v["samp_blk"].view(H, -1, m)[:, heap].long(), pos[:, smp] // b)
 
 
-@pytest.mark.parametrize("H,n,causal", [(8, 8192, False), (7, 8192, False), (32, 8192, True), (31, 8192, True), (9, 8200, False)])
+@pytest.mark.parametrize("H,n,causal", [(8, 8192, False), (7, 8192, False), (32, 8192, True), (31, 8192, True), (9, 8200, False),
+                                        (5, 8192, False), (4, 8192, False), (5, 8200, False)])
 def test_exact_attention_around_the_wide_form(ha, torch, H, n, causal):
-    """The 8-wave form of exact attention at d = 128 starts at 256 (causal: 1024) workgroups of 256 rows: both sides of
+    """The 8-wave form of exact attention at d = 128 starts at 129 (causal: 1024) workgroups of 256 rows: both sides of
     the line, rows of every kind of tile against fp32 attention; criterion: the plain one of the forward."""
     print(f"wide exact H={H} n={n} causal={causal}", flush=True)
     gen = torch.Generator(device="cuda")

@@ -350,6 +350,7 @@ template <int D, int MODE, int KW, bool FINAL>
 static int launch_bwd_f32_form(const BwdArgs& args, int grid, hipStream_t st) {
   BwdArgs a = args;
   if (MODE == kBwdDqNode || MODE == kBwdDkvBlock) set_node_divs<32 * (4 / KW)>(a.f);
+  if (MODE == kBwdDqExact || MODE == kBwdDkvExact) set_exact_divs<32 * (4 / KW)>(a.f);
   const size_t lds = bwd_f32_lds_bytes<D>(a.f.g, MODE);
   static std::atomic<uint64_t> lds_set{0};  // per instantiation: devices on which the LDS limit is raised
   if (allow_full_lds(reinterpret_cast<const void*>(&attn_bwd_f32_kernel<D, MODE, KW, FINAL>), lds_set) != HA_OK) return HA_ERR_LAUNCH;

@@ -563,6 +563,7 @@ template <int D, int MODE, bool FINAL>
 static int launch_bwd_form(const BwdArgs& args, int grid, hipStream_t st) {
   BwdArgs a = args;
   if (MODE == kBwdDqNode || MODE == kBwdDkvBlock) set_node_divs<kRT>(a.f);
+  if (MODE == kBwdDqExact || MODE == kBwdDkvExact) set_exact_divs<kRT>(a.f);
   static std::atomic<uint64_t> lds_set{0};  // per instantiation: devices on which the LDS limit is raised
   if (allow_full_lds(reinterpret_cast<const void*>(&attn_bwd_kernel<D, MODE, FINAL>), lds_set) != HA_OK) return HA_ERR_LAUNCH;
   hipLaunchKernelGGL((attn_bwd_kernel<D, MODE, FINAL>), dim3((unsigned)grid), dim3(kBNT), bwd_lds_bytes<D>(a, MODE), st, a);

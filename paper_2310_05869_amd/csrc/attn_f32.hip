@@ -303,6 +303,7 @@ static int launch_f32_one(const AttnArgs& args, hipStream_t st) {
   constexpr int kQT = 32 * (4 / KW);
   AttnArgs a = args;
   if (MODE == kModeNode) set_node_divs<kQT>(a);
+  else set_exact_divs<kQT>(a);
   const int64_t grid = MODE == kModeNode ? node_grid<kQT>(a.g) : exact_grid<kQT>(a);
   if (grid <= 0) return HA_OK;
   if (grid > kMaxGrid) return HA_ERR_SHAPE;

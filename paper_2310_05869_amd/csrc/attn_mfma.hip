@@ -728,6 +728,7 @@ template <int D, int MODE, int NW, bool STAMPS = false, int NG = 1>
 static int launch_one(const AttnArgs& args, hipStream_t st) {
   AttnArgs a = args;
   if (MODE != kModeExact) set_node_divs<32 * NW>(a);
+  else set_exact_divs<32 * NW>(a);
   const int64_t grid = MODE != kModeExact ? node_grid<32 * NW>(a.g) : exact_grid<32 * NW>(a);
   if (grid <= 0) return HA_OK;
   if (grid > kMaxGrid) return HA_ERR_SHAPE;

@@ -118,7 +118,7 @@ __device__ inline BwdWork decode_bwd_work(const BwdArgs& a, int idx) {
   } else if (MODE == kBwdDkvExact) {
     // key tiles of the diagonal blocks
     const int eb = f.exact_block;
-    const ExactPlace e = exact_place<QT>(f, idx);
+    const ExactPlace e = exact_place(f, idx);
     const int ktile = e.rank;  // early key tiles see the most queries
     const int blk = e.blk;
     b.w.bh = e.bh;

@@ -123,7 +123,8 @@ struct AttnArgs {
   int64_t out_bh_stride;  // elements between heads of `out` ; lse stride = out_bh_stride / d
   int32_t scatter_out;    // node mode: 1 => write row perm_q[p], 0 => write sorted position p
   Geometry g;
-  // node mode, set by the launchers (set_node_divs): tiles per level, heads, tiles per block, blocks of the last level's nodes
+  // node mode, set by the launchers (set_node_divs): tiles per level, heads, tiles per block, blocks of the last level's nodes;
+  // exact mode (set_exact_divs): div_tpb tiles per block, div_unit blocks per head, div_tpl blocks of all heads
   FastDiv div_tpl, div_bh, div_tpb, div_unit;
   int32_t wg_first;  // fp32 kernel and cap mode: number of the launch's first workgroup, where a call takes several launches
   // cap mode: log tau of every node [BH][total_nodes], the constant of C_i and kappa (<= 0: that cap is off)

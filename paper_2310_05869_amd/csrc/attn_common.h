@@ -85,6 +85,8 @@ __host__ __device__ inline int64_t node_grid(const Geometry& g) {
 // against 99 on average at 24 blocks of 32 tiles.  Measured (MI355X): forward, 12 heads, n = 8192, d = 64: 141 ->
 // 119 us (122 with every round forwards); forward + backward: fp32, 4 heads, n = 4096: 336 -> 283 (305) us;
 // exact, 12 heads, n = 5000, d = 128: 530 -> 408 (437) us.
+// Workgroups that take a CU each (exact_lpt: two wave groups) are not all placed at once, and with the rounds backwards the
+// last to start would be the second round's heaviest: they come heaviest first throughout.
 //
 // Unmasked launches, whose tiles are all alike, and larger causal ones, where workgroups are replaced as they finish:
 // every XCD takes a contiguous range, block after block (across the blocks an unmasked launch was 1 % slower: 12
@@ -124,7 +126,7 @@ __device__ inline ExactPlace exact_place(const AttnArgs& a, int wg) {
     const int xcd = wg & 7, j = wg >> 3;
     const int round = j / kOrderRound;
     int p = wg;
-    if (round & 1) {
+    if ((round & 1) && !a.exact_lpt) {
       const int left = ((blocks * tpb - xcd + 7) >> 3) - round * kOrderRound;  // the XCD's tiles from this round on
       const int cnt = left < kOrderRound ? left : kOrderRound;
       p = (2 * round * kOrderRound + cnt - 1 - j) * 8 + xcd;

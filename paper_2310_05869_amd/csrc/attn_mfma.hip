@@ -730,6 +730,7 @@ static int launch_one(const AttnArgs& args, hipStream_t st) {
   AttnArgs a = args;
   if (MODE != kModeExact) set_node_divs<32 * NW>(a);
   else set_exact_divs<32 * NW>(a);
+  a.exact_lpt = NG == 2;
   const int64_t grid = MODE != kModeExact ? node_grid<32 * NW>(a.g) : exact_grid<32 * NW>(a);
   if (grid <= 0) return HA_OK;
   if (grid > kMaxGrid) return HA_ERR_SHAPE;
@@ -770,23 +771,29 @@ static int launch_one(const AttnArgs& args, hipStream_t st) {
 // causal: 4 heads, n = 16384 (256) 370 -> 310, 8 heads (512) 578 -> 540, 16 heads (1024) 1032 -> 1029.
 // The short loops of the base case prefer two 4-wave workgroups per CU.
 constexpr int kWideExactMinRows = 8192;
-// Launches that leave a CU at most one workgroup are bound by the longest chain of key tiles of a workgroup: two groups of
-// four waves then share it.  One such workgroup fills a CU, so past 256 a second round begins: in causal launches
-// with the lightest tiles, which is worth it the longer the rows.  Short rows gain nothing.  One group -> two (MI355X, us):
+// Launches that leave a CU at most one or two workgroups are bound by the longest chain of key tiles of a workgroup: two groups
+// of four waves then share it.  One such workgroup fills a CU, so past 256 a second round begins, whose workgroups start as
+// CUs become free: causal tiles then come heaviest first throughout (exact_lpt), and up to two rounds are worth it, the more
+// the longer the rows.  Short rows gain nothing.  One group -> two (MI355X, us):
 //   unmasked: 4 heads, n = 4096, d = 64 54.4 -> 42.0, d = 128 73.0 -> 60.6; 32 heads (256), n = 1024: 17.3 -> 15.4, 23.7 -> 23.5;
 //     32 heads (192), n = 768: 13.7 -> 12.4, 18.4 -> 17.5; 42 heads (252): 15.9 -> 14.9, but d = 128 22.1 -> 23.1; 64 heads (192),
 //     n = 384: 11.2 -> 11.7, 12.0 -> 12.2
-//   causal: 12 heads (384), n = 4096: 55.9 -> 45.4, 77.5 -> 68.5; 16 heads (384), n = 3072: 42.8 -> 36.2, 59.7 -> 54.6; 24 heads (384),
-//     n = 2048: 30.5 -> 29.4, but 42.8 -> 43.6, 22 heads (352): 32.0 -> 26.5, 42.4 -> 39.7; 40 heads (320), n = 1024: 18.0 -> 16.7,
-//     24.8 -> 24.6, but 48 heads (384): 18.0 -> 20.1, 25.9 -> 29.7; 96 heads (384), n = 512: 11.7 -> 15.5, 17.6 -> 23.3
-//   base case of 4 heads, n = 8192, d = 64 (256): call 81.1 -> 69.2
+//   causal (in brackets, where measured: every second round of 32 backwards, the order of the one-group form), d = 64:
+//     8 heads (512), n = 8192 107.5 -> 92.4 (109.8), 9 heads (576) 118.7 -> 113.8, 10 (640) 124.9 -> 123.7; 16 heads (512), n = 4096
+//     56.0 -> 50.8 (60.5), 18 (576) 61.8 -> 62.2; 24 heads (384), n = 2048 30.4 -> 24.5 (29.1), 32 (512) 30.9 -> 29.9, 36 (576) 34.0 ->
+//     38.7; 48 heads (384), n = 1024 18.2 -> 17.5 (20.3), 56 (448) 18.2 -> 19.6; 64 heads (320), n = 640 13.1 -> 12.7, 77 (385) 15.0 -> 16.5
+//   d = 128: 8 heads (512), n = 8192 159 -> 144 (170), 9 (576) 177 -> 178; 16 heads (512), n = 4096 83.2 -> 78.7 (90.8), 17 (544) 89.4 ->
+//     93.6; 19 heads (456), n = 3072 63.4 -> 60.9, 21 (504) 65.8 -> 67.1; 28 heads (448), n = 2048 43.5 -> 42.8, 32 (512) 45.5 -> 45.1; 32
+//     heads (384), n = 1536 33.1 -> 30.4, 37 (444) 38.5 -> 39.1; 40 heads (320), n = 1024 24.4 -> 22.0, 48 (384) 25.0 -> 25.8; 51
+//     heads (255), n = 640 18.6 -> 18.3, 64 (320) 18.4 -> 19.6
 constexpr int kSplitExactMinRows = 640;
 static bool split_exact(const AttnArgs& a) {
   const int rows = a.exact_block < a.exact_rows_q ? a.exact_block : a.exact_rows_q;
   if (rows < kSplitExactMinRows) return false;
   const int64_t grid = exact_grid<128>(a);
   if (!a.exact_causal) return grid <= (a.g.d == 128 && rows < 1024 ? 160 : 256);
-  return grid <= (rows < 1024 ? 256 : rows < 1536 ? 320 : rows < 3072 ? 352 : 384);
+  if (a.g.d == 64) return grid <= (rows < 1024 ? 320 : rows < 1536 ? 384 : rows < 8192 ? 512 : 576);
+  return grid <= (rows < 1024 ? 256 : rows < 1536 ? 320 : rows < 2048 ? 384 : rows < 4096 ? 448 : 512);
 }
 constexpr int64_t kWideExactMinGrid = 129, kWideExactMinGridCausal = 1024;
 

@@ -134,6 +134,7 @@ struct AttnArgs {
   int32_t exact_rows_q, exact_rows_k;  // rows per head (full problem)
   int32_t exact_block;                 // rows per independent diagonal block (== rows for full attention)
   int32_t exact_causal;
+  int32_t exact_lpt;                   // set by the launchers: workgroups that fill a CU each (exact_place)
   int32_t merge_levels;                // exact mode: merge part_o/part_l of this many levels into the result
   // measurement only (null in every product call): kStampWords 64-bit words per workgroup, indexed by the
   // workgroup's logical tile number, written by the instrumented instantiation of the MFMA kernel

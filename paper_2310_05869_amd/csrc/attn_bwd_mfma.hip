@@ -92,15 +92,15 @@ __host__ __device__ inline int bwd_list_capacity(const BwdArgs& a, int mode) {
 }
 
 // block-key pass: the workgroup's sampled keys lie behind all else, from the prologue to the end
-template <int D>
+template <int D, int NG>
 __host__ __device__ inline size_t bwd_hits_at(const BwdArgs& a, int mode) {
-  const size_t s = 2 * (size_t)BwdLds<D>::BUF + 2 * BwdLds<D>::SC + 64 + (size_t)bwd_list_capacity(a, mode) * 4;
-  return s > (size_t)4 * BwdLds<D>::EP_WAVE ? s : (size_t)4 * BwdLds<D>::EP_WAVE;
+  const size_t s = NG * (2 * (size_t)BwdLds<D>::BUF + 2 * BwdLds<D>::SC) + 64 + (size_t)bwd_list_capacity(a, mode) * 4;
+  return s > (size_t)4 * NG * BwdLds<D>::EP_WAVE ? s : (size_t)4 * NG * BwdLds<D>::EP_WAVE;
 }
 
-template <int D>
+template <int D, int NG>
 __host__ __device__ inline size_t bwd_lds_bytes(const BwdArgs& a, int mode) {
-  return bwd_hits_at<D>(a, mode) + (mode == kBwdDkvBlock && !a.f.g.causal ? sample_hits_bytes(a.f.g) : 0);
+  return bwd_hits_at<D, NG>(a, mode) + (mode == kBwdDkvBlock && !a.f.g.causal ? sample_hits_bytes(a.f.g) : 0);
 }
 
 // 16 bytes per lane from buffer memory to 1 KiB of LDS starting at byte lds_at (wave-uniform).  Inline assembly
@@ -112,8 +112,10 @@ __device__ inline void dma_1k(const __amdgpu_buffer_rsrc_t& rsrc, uint32_t lds_a
 }
 
 // FINAL: the node passes of an unmasked problem, which write the final gradients.
-template <int D, int MODE, bool FINAL>
-__global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
+// NG = 2: two groups of four waves take the T tiles in turn, each with tile buffers of its own; their sums are added
+// through LDS.
+template <int D, int MODE, bool FINAL, int NG>
+__global__ __launch_bounds__(kBNT * NG, 2) void attn_bwd_kernel(BwdArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   using L = BwdLds<D>;
   constexpr bool kDq = (MODE == kBwdDqNode || MODE == kBwdDqExact);
@@ -125,16 +127,18 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
   constexpr int CPR = D / 8;                 // 16-byte pieces per row
   constexpr int RPI = 64 / CPR;              // rows per DMA instruction
   constexpr int NDMA = kTT / RPI / 4;        // instructions per wave and tensor tile
+  constexpr int kNT = kBNT * NG;             // threads
 
   const AttnArgs& f = a.f;
   const Geometry& g = f.g;
-  const int tid = threadIdx.x;
+  const int tid = NG == 1 ? threadIdx.x : threadIdx.x % kBNT;  // within the group
+  const int grp = NG == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / kBNT);
   const int lane = tid & 63, wave = tid >> 6;
   const int lq = lane & 31, h = lane >> 5;
 
-  unsigned char* bufs = smem;
-  float* sc = reinterpret_cast<float*>(smem + 2 * L::BUF);
-  int32_t* scratch = reinterpret_cast<int32_t*>(smem + 2 * L::BUF + 2 * L::SC);
+  unsigned char* bufs = smem + grp * 2 * L::BUF;
+  float* sc = reinterpret_cast<float*>(smem + NG * 2 * L::BUF + grp * 2 * L::SC);
+  int32_t* scratch = reinterpret_cast<int32_t*>(smem + NG * (2 * L::BUF + 2 * L::SC));
   int32_t* list = scratch + 16;
 
   // ---- which part of the problem this workgroup owns ----
@@ -159,7 +163,7 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
   int blk_r = -1;        // sampled-key pass: sorted block of this key
   const int r_row = bwd_r_row<MODE>(a, b, r_use, &blk_r);           // row within the head
   SampleHead shead{-1, 0};
-  if (kHits) shead = fetch_sample_head(a, b, tid);
+  if (kHits) shead = fetch_sample_head(a, b, threadIdx.x);
   bf16x8 xreg[KS], areg[KS];
   {
     const u32x4* xp = reinterpret_cast<const u32x4*>(Xh + (int64_t)r_row * D + 8 * h);
@@ -188,16 +192,16 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
   // positions through P_Q, listed in LDS too (dK/dV of a node), or a contiguous range ----
   int nT, nb = 0x7fffffff;
   if (MODE == kBwdDqNode) {
-    nT = build_key_list<kBNT>(f, w, list, scratch, &nb);
+    nT = build_key_list<kNT>(f, w, list, scratch, &nb);
   } else if (kSorted) {
     nT = MODE == kBwdDkvBlock ? g.b : b.chunk_len;
     const int32_t* tperm = f.perm_q + w.seg_off + (MODE == kBwdDkvBlock ? (int64_t)w.t * g.b : (int64_t)b.chunk_start);
-    for (int i = tid; i < ((nT + 63) & ~63); i += kBNT) list[i] = tperm[min(i, nT - 1)];
+    for (int i = threadIdx.x; i < ((nT + 63) & ~63); i += kNT) list[i] = tperm[min(i, nT - 1)];
     __syncthreads();
   } else {
     nT = max(0, w.k1 - w.k0);
   }
-  const int ntiles = (nT + kTT - 1) / kTT;
+  const int ntiles = (nT + NG * kTT - 1) / (NG * kTT);  // of the group; its tile kt is tile NG kt + grp of the T rows
   const float bias2 = ((MODE == kBwdDqNode || MODE == kBwdDkvSamp) && g.m > 0) ? log2f((float)w.nr.s / (float)g.m) : 0.f;
   const float nat_bias = bias2 * kLn2;
 
@@ -213,15 +217,17 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)bufs + 1024 * wave_s;
   float sc_l = 0.f, sc_d = 0.f;
   auto request_tile = [&](int kt) {
+    const int t0 = (NG * kt + grp) * kTT;
+    if (NG == 2 && t0 >= nT) return;  // (the other group has the last tile)
     if (!kDq && tid < kTT) {
-      const int row = kSorted ? list[kt * kTT + tid] : min(w.k0 + kt * kTT + tid, g.n - 1);
+      const int row = kSorted ? list[t0 + tid] : min(w.k0 + t0 + tid, g.n - 1);
       sc_l = lse_h[row];
       sc_d = del_h[row];
     }
     const uint32_t at = lds0 + (kt & 1) * L::BUF;
 #pragma unroll
     for (int ii = 0; ii < NDMA; ++ii) {
-      const int t = kt * kTT + 4 * RPI * ii + drow;
+      const int t = t0 + 4 * RPI * ii + drow;
       const int row = kExact ? min(w.k0 + t, g.n - 1) : list[t];  // past the end: some existing row, masked
       const int voff = row * (D * 2) + dcol;
       dma_1k(yrsrc, at + 4096 * ii, voff);
@@ -255,7 +261,7 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
   asm volatile("" : "+v"(nl2_r), "+v"(del_r));
   if (ntiles > 0) {
     request_tile(0);
-    if (kHits) find_sample_hits<kBNT>(a, b, sample_hits(smem + bwd_hits_at<D>(a, MODE)), shead);  // while the first tile is on its way
+    if (kHits) find_sample_hits<kNT>(a, b, sample_hits(smem + bwd_hits_at<D, NG>(a, MODE)), shead);  // while the first tile is on its way
     finish_tile(0);
   }
 
@@ -274,7 +280,7 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
     // the sampled key's own block, factor 1 - M of Algorithm 2).
     // Whether the tile has any is known from scalars, except in the sampled-key pass, whose keys differ by lane;
     // the limits themselves are formed inside the branch, so that they hold no registers across the products.
-    const int tbase = kt * kTT;
+    const int tbase = (NG * kt + grp) * kTT;
     float nl2_t = nl2_r;
     if (MODE == kBwdDqNode && tbase >= nb) nl2_t += bias2;
     const int r_first = w.q0 + 32 * wave_s;   // exact passes: the wave's first R row
@@ -288,6 +294,7 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
     }
 
     // one 32-row half of the tile at a time: S^T = Y X^T and dP^T = Bt A^T, then P^T / dS^T
+    if (NG == 1 || tbase < nT)
 #pragma unroll
     for (int sub = 0; sub < 2; ++sub) {
       // dK / dV passes start the sums at bias - L and -delta of the T rows, straight from LDS; in the dQ passes,
@@ -416,14 +423,25 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
   }
   __syncthreads();  // the tiles are read no more
 
+  auto staged = [&]() {  // a wave's own staging area, or both groups'
+    if (NG == 2) {
+      __syncthreads();
+      return;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
   auto write_out = [&](const auto& acc, float* dst32, const float* samp, uint16_t* dst16, const float* lvl) {
     // ---- epilogue: the wave's 32 rows leave through an LDS transpose as whole rows.
     // Node passes write or add fp32 rows into the accumulated rows (unmasked problems: write the final gradient).
     // Exact passes (the base case of Algorithm 4) write the final gradient in the tensors' dtype, after
     // adding the accumulated row where some level's node holds the row on the pass's
     // side (queries: second half of the node; keys: first half).
+    // Two groups: both stage their sums of the rows; each takes half of the rows on and adds the two.
     unsigned char* ep = smem + wave * L::EP_WAVE;
-    int64_t* ep_rows = reinterpret_cast<int64_t*>(ep + 32 * L::EP_ROW);
+    unsigned char* ep_own = ep + 4 * grp * L::EP_WAVE;
+    int64_t* ep_rows = reinterpret_cast<int64_t*>(ep_own + 32 * L::EP_ROW);
     if (h == 0) {  // (the row's index is fetched again: kept across the loop it would cost registers)
       int r = wave * 32 + lq, blk;
       asm volatile("" : "+v"(r));
@@ -435,11 +453,15 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
       for (int g4 = 0; g4 < 4; ++g4) {
         const int col = 32 * dt + 8 * g4 + 4 * h;
         const f32x4 v = {acc[dt][4 * g4], acc[dt][4 * g4 + 1], acc[dt][4 * g4 + 2], acc[dt][4 * g4 + 3]};
-        *reinterpret_cast<f32x4*>(ep + lq * L::EP_ROW + col * 4) = v;
+        *reinterpret_cast<f32x4*>(ep_own + lq * L::EP_ROW + col * 4) = v;
       }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    staged();
+    const int row0 = NG == 2 ? 16 * grp : 0;  // this wave's first row of the 32
+    auto sums_at = [&](int row, int byte) -> f32x4 {
+      f32x4 v = *reinterpret_cast<const f32x4*>(ep + row * L::EP_ROW + byte);
+      if (NG == 2) v += *reinterpret_cast<const f32x4*>(ep + 4 * L::EP_WAVE + row * L::EP_ROW + byte);
+      return v;
+    };
     // Rows that are not stored (past the end of the tile; valid rows are a prefix) re-read the wave's first
     // row, so that every load below is unconditional and all of them are requested before the first is
     // used; only the stores sit under a branch.  With loads under a branch the compiler's wait counts
@@ -451,7 +473,7 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
     const float* sums = nullptr;  // null: no sampled key in the wave's rows
     const int32_t* first = nullptr;
     if (kHits && samp != nullptr) {
-      const SampleHits sh = sample_hits(smem + bwd_hits_at<D>(a, MODE));
+      const SampleHits sh = sample_hits(smem + bwd_hits_at<D, NG>(a, MODE));
       first = sh.first + 32 * wave;
       if (__any(first[lq] != kNoSample)) sums = samp + (int64_t)w.bh * bwd_chunks_per_node(g, a.chunk, 0) * g.m * D;
       const int nm = sums ? *sh.count : 0;
@@ -459,6 +481,7 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
       for (int e = 0; e < nm; ++e) {
         const int row = sh.more[e] >> 16;
         if ((row >> 5) != wave || (row & (G - 1)) != lane / LPR) continue;
+        if (NG == 2 && ((row >> 4) & 1) != grp) continue;
         f32x4* at = reinterpret_cast<f32x4*>(ep + (row & 31) * L::EP_ROW + (lane % LPR) * 16);
         *at = *at + *reinterpret_cast<const f32x4*>(sums + (int64_t)(sh.more[e] & 0xffff) * D + (lane % LPR) * 4);
       }
@@ -473,13 +496,13 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
       if (MODE == kBwdDqNode) add = node_levels_hold(g, w.nr.q_start, true, w.level);
       if (MODE == kBwdDkvBlock) add = node_levels_hold(g, w.nr.k_start, false, w.level);
       constexpr int CH = D / 4;            // 16-byte pieces per fp32 row
-      constexpr int IT = 32 * CH / 64;     // pieces per lane
+      constexpr int IT = 32 / NG * CH / 64;  // pieces per lane
       int64_t r64[IT];
       f32x4 prev[IT];
 #pragma unroll
       for (int it = 0; it < IT; ++it) {
         const int idx = lane + 64 * it;
-        r64[it] = ep_rows[idx / CH];
+        r64[it] = ep_rows[row0 + idx / CH];
         prev[it] = (f32x4){0.f, 0.f, 0.f, 0.f};
       }
       if (add) {
@@ -493,8 +516,8 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
 #pragma unroll
       for (int it = 0; it < IT; ++it) {
         const int idx = lane + 64 * it;
-        const int row = idx / CH, ch = idx % CH;
-        const f32x4 v = *reinterpret_cast<const f32x4*>(ep + row * L::EP_ROW + ch * 16) + prev[it];
+        const int row = row0 + idx / CH, ch = idx % CH;
+        const f32x4 v = sums_at(row, ch * 16) + prev[it];
         if (r64[it] >= 0) *reinterpret_cast<f32x4*>(dst32 + r64[it] * D + ch * 4) = v;
       }
       return;
@@ -504,12 +527,12 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
     const bool fold = kExact && lvl != nullptr && node_levels_hold(g, i0, kDq, g.levels);
     const float* acc_rows = lvl + ((int64_t)w.bh * g.n + i0) * D;
     constexpr int CH8 = D / 8;             // 8-element pieces per row
-    constexpr int IT8 = 32 * CH8 / 64;     // pieces per lane
+    constexpr int IT8 = 32 / NG * CH8 / 64;  // pieces per lane
     int64_t r64[IT8];
     f32x4 p0[IT8], p1[IT8];
 #pragma unroll
     for (int it = 0; it < IT8; ++it) {
-      r64[it] = ep_rows[(lane + 64 * it) / CH8];
+      r64[it] = ep_rows[row0 + (lane + 64 * it) / CH8];
       p0[it] = (f32x4){0.f, 0.f, 0.f, 0.f};
       p1[it] = p0[it];
     }
@@ -517,7 +540,7 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
 #pragma unroll
       for (int it = 0; it < IT8; ++it) {
         const int idx = lane + 64 * it;
-        const int row = r64[it] >= 0 ? idx / CH8 : 0, ch = idx % CH8;
+        const int row = r64[it] >= 0 ? row0 + idx / CH8 : 0, ch = idx % CH8;
         const float* pp = acc_rows + (int64_t)row * D + ch * 8;
         p0[it] = *reinterpret_cast<const f32x4*>(pp);
         p1[it] = *reinterpret_cast<const f32x4*>(pp + 4);
@@ -526,14 +549,14 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
     if (kHits && sums != nullptr) {  // (a row without a sample reads sample 0's sums and drops them)
 #pragma unroll
       for (int it = 0; it < IT8; ++it) {
-        const int idx = lane + 64 * it, j = first[idx / CH8];
+        const int idx = lane + 64 * it, j = first[row0 + idx / CH8];
         const float* pp = sums + (int64_t)(j != kNoSample ? j : 0) * D + (idx % CH8) * 8;
         p0[it] = *reinterpret_cast<const f32x4*>(pp);
         p1[it] = *reinterpret_cast<const f32x4*>(pp + 4);
       }
 #pragma unroll
       for (int it = 0; it < IT8; ++it) {
-        const bool none = first[(lane + 64 * it) / CH8] == kNoSample;
+        const bool none = first[row0 + (lane + 64 * it) / CH8] == kNoSample;
         const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
         p0[it] = none ? zero : p0[it];
         p1[it] = none ? zero : p1[it];
@@ -542,40 +565,61 @@ __global__ __launch_bounds__(kBNT, 2) void attn_bwd_kernel(BwdArgs a) {
 #pragma unroll
     for (int it = 0; it < IT8; ++it) {
       const int idx = lane + 64 * it;
-      const int row = idx / CH8, ch = idx % CH8;
-      const f32x4 v0 = *reinterpret_cast<const f32x4*>(ep + row * L::EP_ROW + ch * 32) + p0[it];
-      const f32x4 v1 = *reinterpret_cast<const f32x4*>(ep + row * L::EP_ROW + ch * 32 + 16) + p1[it];
+      const int row = row0 + idx / CH8, ch = idx % CH8;
+      const f32x4 v0 = sums_at(row, ch * 32) + p0[it];
+      const f32x4 v1 = sums_at(row, ch * 32 + 16) + p1[it];
       const u32x4 pk = {pack_bf16x2(v0.x, v0.y), pack_bf16x2(v0.z, v0.w), pack_bf16x2(v1.x, v1.y), pack_bf16x2(v1.z, v1.w)};
       if (r64[it] >= 0) *reinterpret_cast<u32x4*>(dst16 + r64[it] * D + ch * 8) = pk;
     }
   };
   write_out(acc1, a.out1, a.samp1, reinterpret_cast<uint16_t*>(a.fin1), a.lvl1);
   if constexpr (!kDq) {
-    // (a wave rewrites only its own staging area, which its own reads above have left)
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    staged();  // (one group: a wave rewrites only its own staging area, which its own reads above have left)
     write_out(acc2, a.out2, a.samp2, reinterpret_cast<uint16_t*>(a.fin2), a.lvl2);
   }
 }
 
-template <int D, int MODE, bool FINAL>
+template <int D, int MODE, bool FINAL, int NG>
 static int launch_bwd_form(const BwdArgs& args, int grid, hipStream_t st) {
   BwdArgs a = args;
   if (MODE == kBwdDqNode || MODE == kBwdDkvBlock) set_node_divs<kRT>(a.f);
   if (MODE == kBwdDqExact || MODE == kBwdDkvExact) set_exact_divs<kRT>(a.f);
+  a.f.exact_lpt = NG == 2;
+  const size_t lds = bwd_lds_bytes<D, NG>(a, MODE);
   static std::atomic<uint64_t> lds_set{0};  // per instantiation: devices on which the LDS limit is raised
-  if (allow_full_lds(reinterpret_cast<const void*>(&attn_bwd_kernel<D, MODE, FINAL>), lds_set) != HA_OK) return HA_ERR_LAUNCH;
-  hipLaunchKernelGGL((attn_bwd_kernel<D, MODE, FINAL>), dim3((unsigned)grid), dim3(kBNT), bwd_lds_bytes<D>(a, MODE), st, a);
+  if (allow_full_lds(reinterpret_cast<const void*>(&attn_bwd_kernel<D, MODE, FINAL, NG>), lds_set) != HA_OK) return HA_ERR_LAUNCH;
+  hipLaunchKernelGGL((attn_bwd_kernel<D, MODE, FINAL, NG>), dim3((unsigned)grid), dim3(kBNT * NG), lds, st, a);
   return check_launch();
+}
+
+// Exact passes of few workgroups are bound by the longest chain of T tiles of one of them, as in the forward (split_exact,
+// attn_mfma.hip): two groups of four waves then share it, a workgroup that fills a CU.  Up to one round of those unmasked, up
+// to two in causal launches, whose second round's are the lightest.  Forward + backward of exact attention, one group -> two
+// in the backward's passes (MI355X, us; in brackets the workgroups of a pass):
+//   causal, d = 64: 8 heads, n = 8192 (512) 399 -> 359, 9 heads (576) 446 -> 437, 10 (640) 478 -> 487; 16 heads, n = 4096 (512) 215 ->
+//     196, 18 (576) 240 -> 243; 32 heads, n = 2048 (512) 122 -> 116, 36 (576) 134 -> 141; 37 heads, n = 1536 (444) 97.1 -> 94.3, 43 (516)
+//     103 -> 112; 48 heads, n = 1024 (384) 71.4 -> 69.0, 56 (448) 72.7 -> 75.7; 64 heads, n = 640 (320) 54.8 -> 51.8, 77 (385) 57.3 -> 61.1
+//   causal, d = 128: 8 heads, n = 8192 (512) 656 -> 605, 9 (576) 738 -> 733, 10 (640) 791 -> 811; 12 heads, n = 4096 (384) 318 -> 287, 16
+//     (512) 352 -> 328, 18 (576) 393 -> 402; 32 heads, n = 2048 (512) 198 -> 190, 36 (576) 219 -> 232; 48 heads, n = 1024 (384) 108 -> 106;
+//     64 heads, n = 512 (256) 65.5 -> 62.9, 96 (384) 75.3 -> 82.4
+//   unmasked, n = 8192: 4 heads (256) d = 64 362 -> 336, d = 128 601 -> 569, 5 heads (320) 540 -> 587, 888 -> 937; 51 heads, n = 640
+//     (255): d = 64 50.2 -> 48.6, d = 128 77.8 -> 79.3; 64 heads, n = 384 (192): 36.9 -> 36.6, 55.0 -> 55.3
+constexpr int kSplitBwdMinRows = 512;
+static bool split_bwd_exact(const BwdArgs& a, int grid) {
+  const int rows = a.f.exact_block < a.f.exact_rows_q ? a.f.exact_block : a.f.exact_rows_q;
+  if (rows < kSplitBwdMinRows) return false;
+  if (!a.f.exact_causal) return grid <= (a.f.g.d == 128 && rows < 1024 ? 160 : 256);
+  return grid <= (rows < 1024 ? 320 : rows < 1536 ? 384 : rows < 2048 ? 448 : 512);
 }
 
 template <int D, int MODE>
 static int launch_bwd_one(const BwdArgs& a, int grid, hipStream_t st) {
   if (grid <= 0) return HA_OK;
+  if constexpr (MODE == kBwdDqExact || MODE == kBwdDkvExact)
+    if (split_bwd_exact(a, grid)) return launch_bwd_form<D, MODE, false, 2>(a, grid, st);
   if constexpr (MODE == kBwdDqNode || MODE == kBwdDkvBlock)
-    if (!a.f.g.causal) return launch_bwd_form<D, MODE, true>(a, grid, st);
-  return launch_bwd_form<D, MODE, false>(a, grid, st);
+    if (!a.f.g.causal) return launch_bwd_form<D, MODE, true, 1>(a, grid, st);
+  return launch_bwd_form<D, MODE, false, 1>(a, grid, st);
 }
 
 template <int D>

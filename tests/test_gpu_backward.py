@@ -193,6 +193,34 @@ def test_exact_attn_backward(ha, torch, d, n, causal, dtype):
         _assert_grad_close(to_host(got), r_, b_, name, FRO_TOL if dtype == "bf16" else FRO_TOL_FP32, dtype)
 
 
+# the two-group form of the exact kernels: one workgroup whose second group has no tile (the last key rows), odd numbers of
+# tiles, ragged ends, and launches of more workgroups than CUs (heads 52 x 6 and 33 x 9 tiles)
+@pytest.mark.parametrize("d,H,n,causal", [(64, 1, 513, True), (128, 1, 641, False), (64, 2, 1000, False), (128, 2, 705, True),
+                                          (64, 52, 700, True), (128, 33, 1025, True)])
+def test_exact_attn_two_wave_groups(ha, torch, d, H, n, causal):
+    print(f"exact, two groups, d={d} H={H} n={n} causal={causal}", flush=True)
+    cfg = dict(B=1, H=H, n=n, d=d, dtype="bf16", law="iid")
+    Q, K, V = synth_inputs.make_qkv(cfg, seed=15)
+    G = _cotangent(Q.shape, 16)
+    tq, tk, tv, tg = (to_device(x, "bf16") for x in (Q, K, V, G))
+    out32 = torch.empty(tq.shape, dtype=torch.float32, device="cuda")
+    out, lse = ha.exact_attn_forward(tq, tk, tv, causal=causal, out_f32=out32)
+    grads = ha.exact_attn_backward(tq, tk, tv, out, lse, tg, causal=causal, out_f32=out32)
+    torch.cuda.synchronize()
+    okw = dict(b=1, m=0, r=1, causal=True, n_min=n) if causal else dict(b=n, m=0, r=1, causal=False)
+    for hd in sorted({0, H - 1}):
+        q, k, v, g = (x[:, hd:hd + 1] for x in (Q, K, V, G))
+        ref_o, ref_l = orc.hyperattn_forward(q, k, v, seed=0, **okw)
+        assert np.abs(lse[:, hd:hd + 1].cpu().numpy() - ref_l).max() <= 1e-3 * max(1.0, np.abs(ref_l).max())
+        # weights enter the products as bf16 (2^-9 each, so 2^-8 of sum_j P_ij |v_j|), the result is rounded once
+        mass = orc.hyperattn_forward(q, k, np.abs(v), seed=0, **okw)[0]
+        assert (np.abs(to_host(out32[:, hd:hd + 1]) - ref_o) <= 2.0 ** -8 * mass).all()
+        ref = orc.hyperattn_backward(q, k, v, g, **okw)
+        bnd = orc.hyperattn_backward(q, k, v, g, absolute=True, **okw)
+        for got, r_, b_, name in zip(grads, ref, bnd, ("dQ", "dK", "dV")):
+            _assert_grad_close(to_host(got[:, hd:hd + 1]), r_, b_, name, FRO_TOL, "bf16")
+
+
 def test_backward_on_the_mixture_law(ha, torch):
     """Peaked attention rows (scores up to +-250), where dS = P (dP - delta) cancels: the same
     per-element criterion as everywhere, whose bound grows with sum_j P_ij |dP_ij| + |delta_i|."""

@@ -7,7 +7,7 @@
 //   lsh_hash    one pass over all rows of Q and K; the causal recursion reuses
 //               the same codes at every node (same hyperplanes everywhere); also
 //               stores R and the per-node sample indices in the workspace
-//   seg_sort    all nodes of all levels, Q and K, in one launch
+//   seg_sort    all nodes of all levels, Q and K, in one launch or two; small problems: in the attention launch
 //   attention   all nodes of all levels in one launch (block part + sampled
 //               residual, shared normaliser); unmasked problem: final output;
 //               causal: partial results per level, in the tensors' dtype
@@ -34,6 +34,7 @@
 #include "alg2_common.h"
 #include "bwd_common.h"
 #include "hash_common.h"
+#include "node_sort.h"
 
 namespace ha {
 
@@ -302,6 +303,25 @@ static AttnArgs node_args(const void* Q, const void* K, const void* V, void* out
   return a;
 }
 
+// Whether the attention launch sorts its nodes by itself (node_sort.h).  Every workgroup then counts its whole node, some 2.5 us
+// of a workgroup's life at 4096 keys and twice that at 8192, against a sorting launch of 6.5 to 8 us and 2.5 us of the host's time for
+// it: worth it while the workgroups fit the chip about once and the codes they count are few.  Forward, sorting launch -> in the
+// attention (MI355X, us; workgroups):
+//   bf16, d = 64: 8 heads, n = 4096 (256) 26.7 -> 23.9, 12 (384) 30.8 -> 29.5, 16 (512) 32.1 -> 30.7, 32 (1024) 48.6 -> 52.1; 32 heads,
+//     n = 2048 (512) 31.0 -> 30.6; 64 heads, n = 1024 (512) 30.7 -> 31.1; 16 heads, n = 1024, b = m = 64 (256) 22.6 -> 18.8; 4 heads,
+//     n = 8192 (256) 26.9 -> 25.2, 6 (384) 31.5 -> 31.6, 12 (768) 42.3 -> 49.3; causal, 12 heads, n = 8192 (384) 111.8 -> 110.1
+//   bf16, d = 128: 8 heads, n = 4096 (256) 34.1 -> 31.8, 12 (384) 42.9 -> 41.5, 16 (512) 45.1 -> 44.5; 32 heads, n = 2048 (512) 43.8 -> 44.2; 64
+//     heads, n = 1024 (512) 43.2 -> 44.4; 4 heads, n = 8192 (256) 35.0 -> 33.4; 15 heads, n = 6300, b = 100, m = 77 (945) 52.8 -> 61.8
+//   fp32, d = 64: one head, n = 1024, b = m = 64 (32) 21.3 -> 19.5; 8 heads, n = 4096, b = m = 64 (1024) 42.8 -> 39.5, 16 (2048) 69.7 -> 71.8;
+//     d = 128: 16 heads, n = 2048 (512) 116.7 -> 115.1; 8 heads, n = 8192, b = m = 128 (512) 141.5 -> 141.0
+static bool sort_in_attention(const Geometry& g) {
+  const int rows = node_sort_rows(g);
+  if (rows > kNodeSortMax) return false;
+  const int64_t wgs = use_mfma(g) ? node_grid<128>(g) : attn_f32_node_grid(g);
+  const int64_t most = use_mfma(g) ? (g.d == 64 ? 512 : 384) : 1024;
+  return wgs <= most && wgs * rows <= (use_mfma(g) ? 2 : 4) << 20;
+}
+
 // ev, when non-null, receives 5 events recorded on the stream: start, after hashing (with the call's draws), after sorting,
 // after the node attention, after the base case.
 // node_stamps / base_stamps, when non-null, select the measuring instantiation of the
@@ -342,13 +362,21 @@ static int forward_impl(const void* Q, const void* K, const void* V, void* out, 
     rc = run_hash(Q, K, codes_q, codes_k, g, p->seed, R_dev, samples_dev, proj, samples, st);
     if (rc != HA_OK) return rc;
     mark(1);
-    rc = launch_seg_sort_nodes(codes_q, codes_k, perm_q, perm_k, pos_k, g.m > 0 ? samples : nullptr, samp_blk,
-                               (uint32_t*)(base + lay.sort_hist), g, st);
-    if (rc != HA_OK) return rc;
-    mark(2);
-
     AttnArgs a = node_args(Q, K, V, out, lse, out_f32, g, base, lay);
     a.stamps = node_stamps;
+    if (sort_in_attention(g) && !ev && !node_stamps) {
+      a.codes_q = codes_q;
+      a.codes_k = codes_k;
+      a.perm_q_out = perm_q;
+      a.perm_k_out = perm_k;
+      a.pos_k_out = pos_k;
+      a.samp_blk_out = samp_blk;
+    } else {
+      rc = launch_seg_sort_nodes(codes_q, codes_k, perm_q, perm_k, pos_k, g.m > 0 ? samples : nullptr, samp_blk,
+                                 (uint32_t*)(base + lay.sort_hist), g, st);
+      if (rc != HA_OK) return rc;
+    }
+    mark(2);
     rc = run_attention(a, kModeNode, st);
     if (rc != HA_OK) return rc;
   } else {

@@ -29,6 +29,7 @@
 // possible descriptors), exponentials in seven instructions, fewer rescales: 32 heads, n = 1024, d = 64, unmasked:
 // 111 -> 79 us; 4 heads, n = 4096 in causal blocks of 1024: 50 -> 39 us.  Errors against 64 bits as before.
 #include "attn_common.h"
+#include "node_sort.h"
 
 namespace ha {
 
@@ -51,6 +52,14 @@ __host__ __device__ inline size_t f32_lds_bytes(int b, int m, int mode) {
   return list > (size_t)F32Lds<D>::BYTES ? list : (size_t)F32Lds<D>::BYTES;
 }
 
+// SORT: the sort's tables lie behind the list, the tile's query rows behind all else
+template <int D>
+__host__ __device__ inline size_t f32_qrows_at(const Geometry& g) {
+  const size_t list = ((size_t)(((g.b + g.m + 63) & ~63) + 64) * 4 + 64 + 15) & ~(size_t)15;
+  const size_t both = list + ((node_sort_lds_bytes(g) + 15) & ~(size_t)15);
+  return both > (size_t)F32Lds<D>::BYTES ? both : (size_t)F32Lds<D>::BYTES;
+}
+
 // m + ln l to one rounding of the result: l = f 2^k with f in [1/2, 1), m + k ln 2 kept in two parts.  The reference m only
 // moves by steps, so ln l can be as large as the result, and logf of all of it had an error of that size beside the
 // result's own: log row sums of blocks and samples (n = 2048, b = m = 128, d = 64) 5.4e-8 off against 64 bits where a
@@ -65,7 +74,8 @@ __device__ inline float add_log(float m, float l) {
 }
 
 // FAR (node mode): a head's rows pass the reach of a buffer load's 32-bit offset, so they are addressed in 64 bits.
-template <int D, int MODE, int KW, bool FAR>
+// SORT (node mode): the workgroup finds its rows from the node's bucket codes (node_sort.h).
+template <int D, int MODE, int KW, bool FAR, bool SORT>
 __global__ __launch_bounds__(kFNT, D == 64 ? 3 : 2) void attn_f32_kernel(AttnArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   constexpr int kQT = 32 * (4 / KW);
@@ -83,7 +93,15 @@ __global__ __launch_bounds__(kFNT, D == 64 ? 3 : 2) void attn_f32_kernel(AttnArg
   const int bid = a.wg_first + (MODE == kModeNode ? logical_block(blockIdx.x, gridDim.x) : (int)blockIdx.x);
   TileWork w;
   int nb, nkeys;
-  if (MODE == kModeNode) {
+  int32_t* qrows = reinterpret_cast<int32_t*>(smem + (SORT ? f32_qrows_at<D>(a.g) : 0));
+  if constexpr (SORT) {
+    w = decode_node_tile<kQT>(a, bid);
+    const int l0 = first_node_sample(a, w);
+    unsigned char* sort_lds = reinterpret_cast<unsigned char*>(list) + (((((a.g.b + a.g.m + 63) & ~63) + 64) * 4 + 15) & ~15);
+    sort_node_tile(a, w, sort_lds, list, qrows);
+    nb = a.g.b;
+    nkeys = append_node_samples(a, w, sort_lds, list, scratch, l0);
+  } else if (MODE == kModeNode) {
     w = decode_node_tile<kQT>(a, bid);
     nkeys = build_key_list<kFNT>(a, w, list, scratch, &nb);
   } else {
@@ -103,7 +121,9 @@ __global__ __launch_bounds__(kFNT, D == 64 ? 3 : 2) void attn_f32_kernel(AttnArg
   const int r_in_tile = (wave / KW) * 32 + lq;
   const int r_use = r_in_tile < w.rows_valid ? r_in_tile : 0;
   int qrow, q_global = 0;
-  if (MODE == kModeNode) {
+  if constexpr (SORT) {
+    qrow = qrows[r_use];
+  } else if (MODE == kModeNode) {
     qrow = a.perm_q ? a.perm_q[w.seg_off + w.p0 + r_use] : w.nr.q_start + w.p0 + r_use;
   } else {
     q_global = w.q0 + r_in_tile;
@@ -269,7 +289,10 @@ __global__ __launch_bounds__(kFNT, D == 64 ? 3 : 2) void attn_f32_kernel(AttnArg
     float lse = empty ? -INFINITY : add_log(mx, l);
     acc *= empty ? 0.f : 1.f / l;
     RowDest dest{};
-    if (MODE == kModeNode) {
+    if constexpr (SORT) {
+      dest.out_row = (int64_t)w.bh * a.g.n + qrows[r];
+      dest.part_row = w.seg_off + (qrows[r] - w.nr.q_start);
+    } else if (MODE == kModeNode) {
       dest = node_row_dest(a, w, r);
     } else {
       dest.row_in_head = w.q0 + r;
@@ -298,7 +321,7 @@ __global__ __launch_bounds__(kFNT, D == 64 ? 3 : 2) void attn_f32_kernel(AttnArg
   }
 }
 
-template <int D, int MODE, int KW, bool FAR = false>
+template <int D, int MODE, int KW, bool FAR = false, bool SORT = false>
 static int launch_f32_one(const AttnArgs& args, hipStream_t st) {
   constexpr int kQT = 32 * (4 / KW);
   AttnArgs a = args;
@@ -307,13 +330,13 @@ static int launch_f32_one(const AttnArgs& args, hipStream_t st) {
   const int64_t grid = MODE == kModeNode ? node_grid<kQT>(a.g) : exact_grid<kQT>(a);
   if (grid <= 0) return HA_OK;
   if (grid > kMaxGrid) return HA_ERR_SHAPE;
-  const size_t lds = f32_lds_bytes<D>(a.g.b, a.g.m, MODE);
+  const size_t lds = SORT ? f32_qrows_at<D>(a.g) + kQT * 4 : f32_lds_bytes<D>(a.g.b, a.g.m, MODE);
   static std::atomic<uint64_t> lds_set{0};  // per instantiation: devices on which the LDS limit is raised
-  if (allow_full_lds(reinterpret_cast<const void*>(&attn_f32_kernel<D, MODE, KW, FAR>), lds_set) != HA_OK) return HA_ERR_LAUNCH;
+  if (allow_full_lds(reinterpret_cast<const void*>(&attn_f32_kernel<D, MODE, KW, FAR, SORT>), lds_set) != HA_OK) return HA_ERR_LAUNCH;
   for (int64_t first = 0; first < grid; first += kMaxLaunch) {
     a.wg_first = (int32_t)first;
     const int64_t count = grid - first < kMaxLaunch ? grid - first : kMaxLaunch;
-    hipLaunchKernelGGL((attn_f32_kernel<D, MODE, KW, FAR>), dim3((unsigned)count), dim3(kFNT), lds, st, a);
+    hipLaunchKernelGGL((attn_f32_kernel<D, MODE, KW, FAR, SORT>), dim3((unsigned)count), dim3(kFNT), lds, st, a);
     const int rc = check_launch();
     if (rc != HA_OK) return rc;
   }
@@ -324,16 +347,31 @@ static int launch_f32_one(const AttnArgs& args, hipStream_t st) {
 // enough that a workgroup's 128 / KW rows do not outgrow the run of rows it is cut from (a block of b
 // sorted positions, an exact diagonal block) by more than a third: idle rows cost matrix time like real
 // ones, while the merge of KW results costs a few LDS reads per row.
+static int f32_waves_per_group(int run, int64_t grid128) {
+  auto padded = [&](int qt) { return (int64_t)((run + qt - 1) / qt) * qt; };
+  const int64_t waves = 4 * grid128;
+  if (waves >= 2048 && 3 * padded(128) <= 4 * (int64_t)run) return 1;
+  return waves >= 1024 && 3 * padded(64) <= 4 * (int64_t)run ? 2 : 4;
+}
+
+int64_t attn_f32_node_grid(const Geometry& g) {
+  const int kw = f32_waves_per_group(g.b, node_grid<128>(g));
+  return kw == 1 ? node_grid<128>(g) : kw == 2 ? node_grid<64>(g) : node_grid<32>(g);
+}
+
 template <int D, int MODE>
 static int launch_f32_mode(const AttnArgs& a, hipStream_t st) {
   if constexpr (MODE == kModeNode)  // stage calls alone: the whole-call entry points take up to 2^22 rows per head
     if ((int64_t)a.g.n * (D * 4) > 0x7fffffff + 1ll) return launch_f32_one<D, MODE, 4, true>(a, st);
   const int run = MODE == kModeNode ? a.g.b : (a.exact_block < a.exact_rows_q ? a.exact_block : a.exact_rows_q);
-  auto padded = [&](int qt) { return (int64_t)((run + qt - 1) / qt) * qt; };
-  const int64_t waves = 4 * (MODE == kModeNode ? node_grid<128>(a.g) : exact_grid<128>(a));
-  if (waves >= 2048 && 3 * padded(128) <= 4 * (int64_t)run) return launch_f32_one<D, MODE, 1>(a, st);
-  if (waves >= 1024 && 3 * padded(64) <= 4 * (int64_t)run) return launch_f32_one<D, MODE, 2>(a, st);
-  return launch_f32_one<D, MODE, 4>(a, st);
+  const int kw = f32_waves_per_group(run, MODE == kModeNode ? node_grid<128>(a.g) : exact_grid<128>(a));
+  if constexpr (MODE == kModeNode)
+    if (a.codes_q) {
+      if (kw == 1) return launch_f32_one<D, MODE, 1, false, true>(a, st);
+      return kw == 2 ? launch_f32_one<D, MODE, 2, false, true>(a, st) : launch_f32_one<D, MODE, 4, false, true>(a, st);
+    }
+  if (kw == 1) return launch_f32_one<D, MODE, 1>(a, st);
+  return kw == 2 ? launch_f32_one<D, MODE, 2>(a, st) : launch_f32_one<D, MODE, 4>(a, st);
 }
 
 int launch_attn_f32(const AttnArgs& a, int mode, hipStream_t st) {

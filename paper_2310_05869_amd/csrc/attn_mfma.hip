@@ -30,6 +30,7 @@
 #include <type_traits>
 
 #include "attn_common.h"
+#include "node_sort.h"
 
 namespace ha {
 
@@ -68,6 +69,14 @@ __host__ __device__ inline size_t mfma_lds_bytes(int b, int m, int mode) {
   return s;
 }
 
+// SORT: the sort's tables lie where the tiles will, and push the list back where they are larger; the tile's query rows
+// lie behind the list
+template <int D>
+__host__ __device__ inline size_t sort_pushes_list(const Geometry& g) {
+  const size_t sort = (node_sort_lds_bytes(g) + 15) & ~(size_t)15;
+  return sort > 2 * (size_t)Lds<D>::BUF ? sort - 2 * (size_t)Lds<D>::BUF : 0;
+}
+
 __device__ inline float max3f(float a, float b, float c) { return __builtin_fmaxf(__builtin_fmaxf(a, b), c); }
 
 template <int D, int NT>
@@ -81,7 +90,8 @@ struct TileRegs {
 // boundaries (a.stamps); the product launches use STAMPS = false and carry none of it.
 // NG = 2 (exact mode): two groups of NW waves take the key tiles in turn, each with tile buffers of its own, and their
 // results are merged through LDS.
-template <int D, int MODE, int NW, bool STAMPS = false, int NG = 1>
+// SORT (node mode): the workgroup finds its rows from the node's bucket codes (node_sort.h).
+template <int D, int MODE, int NW, bool STAMPS = false, int NG = 1, bool SORT = false>
 __global__ __launch_bounds__(64 * NW * NG, (D == 64 && NW == 4 && NG == 1) ? 3 : 2) void attn_mfma_kernel(AttnArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   constexpr bool kCap = MODE == kModeCap;
@@ -99,8 +109,9 @@ __global__ __launch_bounds__(64 * NW * NG, (D == 64 && NW == 4 && NG == 1) ? 3 :
   const int lq = lane & 31, h = lane >> 5;
 
   unsigned char* bufs = smem + grp * 2 * L::BUF;
-  int32_t* scratch = reinterpret_cast<int32_t*>(smem + NG * 2 * L::BUF);
+  int32_t* scratch = reinterpret_cast<int32_t*>(smem + NG * 2 * L::BUF + (SORT ? sort_pushes_list<D>(a.g) : 0));
   int32_t* list = scratch + 16;
+  int32_t* qrows = list + (SORT ? list_capacity(a.g.b, a.g.m) : 0);
 
   long long stamp_c[5] = {0, 0, 0, 0, 0}, stamp_w = 0;
   auto stamp = [&](int i) {
@@ -126,12 +137,24 @@ __global__ __launch_bounds__(64 * NW * NG, (D == 64 && NW == 4 && NG == 1) ? 3 :
   // Node mode: the key list's first index values and the row's own index (through P_Q) travel
   // in one round trip; the (gathered) row is then in flight while the key list is built.
   KeyListHead klh{0, 0, 0};
-  if (kNode) klh = key_list_fetch<kNT>(a, w);
+  if (kNode && !SORT) klh = key_list_fetch<kNT>(a, w);
+  if constexpr (SORT) {
+    klh.l0 = first_node_sample(a, w);
+    sort_node_tile(a, w, smem, list, qrows);
+  }
   const int r_in_tile = wave * 32 + lq;
   RowDest dest;
   int qrow_load;   // row to load (always a valid row)
   int q_global;    // exact mode: row index within the head, for the causal mask
-  if (kNode) {
+  if constexpr (SORT) {
+    dest = RowDest{};
+    dest.valid = r_in_tile < w.rows_valid;
+    qrow_load = qrows[dest.valid ? r_in_tile : 0];
+    dest.row_in_head = qrow_load;
+    dest.out_row = (int64_t)w.bh * a.g.n + qrow_load;
+    dest.part_row = w.seg_off + (qrow_load - w.nr.q_start);
+    q_global = 0;
+  } else if (kNode) {
     dest = node_row_dest(a, w, r_in_tile);
     const int p = w.p0 + (dest.valid ? r_in_tile : 0);
     qrow_load = a.perm_q ? a.perm_q[w.seg_off + p] : w.nr.q_start + p;
@@ -152,7 +175,10 @@ __global__ __launch_bounds__(64 * NW * NG, (D == 64 && NW == 4 && NG == 1) ? 3 :
   }
 
   int nb, nkeys;
-  if (kNode) {
+  if constexpr (SORT) {
+    nb = a.g.b;
+    nkeys = append_node_samples(a, w, smem, list, scratch, klh.l0);
+  } else if (kNode) {
     nkeys = build_key_list<kNT, kCap>(a, w, list, scratch, &nb, klh);
   } else {
     nkeys = max(0, w.k1 - w.k0);
@@ -725,7 +751,7 @@ __global__ __launch_bounds__(64 * NW * NG, (D == 64 && NW == 4 && NG == 1) ? 3 :
   }
 }
 
-template <int D, int MODE, int NW, bool STAMPS = false, int NG = 1>
+template <int D, int MODE, int NW, bool STAMPS = false, int NG = 1, bool SORT = false>
 static int launch_one(const AttnArgs& args, hipStream_t st) {
   AttnArgs a = args;
   if (MODE != kModeExact) set_node_divs<32 * NW>(a);
@@ -736,20 +762,21 @@ static int launch_one(const AttnArgs& args, hipStream_t st) {
   if (grid > kMaxGrid) return HA_ERR_SHAPE;
   size_t lds = mfma_lds_bytes<D>(a.g.b, a.g.m, MODE) + (NG - 1) * 2 * (size_t)Lds<D>::BUF;
   const size_t ep = (size_t)NW * EpLds<D>::WAVE + (NG - 1) * (size_t)(D / 8 * 16 + 8) * 64 * NW;
+  if (SORT) lds += sort_pushes_list<D>(a.g) + 32 * NW * 4;
   if (lds < ep) lds = ep;
   static std::atomic<uint64_t> lds_set{0};  // per instantiation: devices on which the LDS limit is raised
-  if (allow_full_lds(reinterpret_cast<const void*>(&attn_mfma_kernel<D, MODE, NW, STAMPS, NG>), lds_set) != HA_OK) return HA_ERR_LAUNCH;
+  if (allow_full_lds(reinterpret_cast<const void*>(&attn_mfma_kernel<D, MODE, NW, STAMPS, NG, SORT>), lds_set) != HA_OK) return HA_ERR_LAUNCH;
   if constexpr (MODE == kModeCap) {  // all levels in one launch, or in as many as their workgroups take
     for (int64_t first = 0; first < grid; first += kMaxLaunch) {
       a.wg_first = (int32_t)first;
       const int64_t count = grid - first < kMaxLaunch ? grid - first : kMaxLaunch;
-      hipLaunchKernelGGL((attn_mfma_kernel<D, MODE, NW, STAMPS, NG>), dim3((unsigned)count), dim3(64 * NW * NG), lds, st, a);
+      hipLaunchKernelGGL((attn_mfma_kernel<D, MODE, NW, STAMPS, NG, SORT>), dim3((unsigned)count), dim3(64 * NW * NG), lds, st, a);
       const int rc = check_launch();
       if (rc != HA_OK) return rc;
     }
     return HA_OK;
   }
-  hipLaunchKernelGGL((attn_mfma_kernel<D, MODE, NW, STAMPS, NG>), dim3((unsigned)grid), dim3(64 * NW * NG), lds, st, a);
+  hipLaunchKernelGGL((attn_mfma_kernel<D, MODE, NW, STAMPS, NG, SORT>), dim3((unsigned)grid), dim3(64 * NW * NG), lds, st, a);
   return check_launch();
 }
 
@@ -820,12 +847,14 @@ int launch_attn_mfma(const AttnArgs& a, int mode, hipStream_t st) {
                     a.exact_block >= kWideExactMinRows && a.exact_rows_q >= kWideExactMinRows &&
                     exact_grid<256>(a) >= (a.exact_causal ? kWideExactMinGridCausal : kWideExactMinGrid);
   if (a.g.d == 128) {
+    if (mode == kModeNode && a.codes_q) return launch_one<128, kModeNode, 4, false, 1, true>(a, st);
     if (mode == kModeNode) return launch_one<128, kModeNode, HA_NW_NODE>(a, st);
     if (mode == kModeCap) return launch_one<128, kModeCap, HA_NW_NODE>(a, st);
     if (split) return launch_one<128, kModeExact, 4, false, 2>(a, st);
     return wide ? launch_one<128, kModeExact, 8>(a, st) : launch_one<128, kModeExact, HA_NW_EXACT>(a, st);
   }
   if (a.g.d == 64) {
+    if (mode == kModeNode && a.codes_q) return launch_one<64, kModeNode, 4, false, 1, true>(a, st);
     if (mode == kModeNode) return launch_one<64, kModeNode, HA_NW_NODE>(a, st);
     if (mode == kModeCap) return launch_one<64, kModeCap, HA_NW_NODE>(a, st);
     if (split) return launch_one<64, kModeExact, 4, false, 2>(a, st);

@@ -112,6 +112,13 @@ struct AttnArgs {
   const int32_t* samples;  // [total_nodes][m] node-local key indices; null or m == 0 => none
   const int32_t* samp_blk; // [BH][total_nodes][m] sorted block of each sampled key; null => look up pos_k
   int32_t use_block;       // 0: residual part alone
+  // small nodes (node_sort.h): bucket codes [BH][n]; the attention launch sorts by itself and writes the four arrays above
+  const uint8_t* codes_q;  // null: they are there
+  const uint8_t* codes_k;
+  int32_t* perm_q_out;
+  int32_t* perm_k_out;
+  int32_t* pos_k_out;
+  int32_t* samp_blk_out;
   // outputs
   void* out;        // final output in dtype (may be null)
   float* lse;       // final log row sum (may be null)
@@ -158,6 +165,7 @@ int launch_seg_sort_flat(const uint8_t* codes, int32_t* perm, int32_t* pos, int 
 int launch_attn_mfma(const AttnArgs& a, int mode, hipStream_t st);
 int64_t attn_mfma_grid(const AttnArgs& a, int mode);  // workgroups of the four-wave launch of that mode
 int launch_attn_f32(const AttnArgs& a, int mode, hipStream_t st);
+int64_t attn_f32_node_grid(const Geometry& g);        // workgroups of the node launch
 int launch_gather_rows(const void* src, const int32_t* idx, void* dst, int groups, int n, int d, int dtype,
                        hipStream_t st);
 int launch_merge_unpermute(const float* o_b, const float* lse_b, const float* o_r, const float* lse_r,

@@ -1,0 +1,280 @@
+// The sort of a small node inside the attention kernels: every workgroup finds the rows of its own tile from the node's
+// bucket codes, instead of reading them from a permutation that a launch ahead of it wrote.
+//
+// What bounds a small call is the number of dependent launches, each some 1.5 us before its first instruction and 2 us
+// until its first data has arrived, so a chain of LDS passes over the node's codes in every workgroup (2 to 3 us) beats a
+// sorting launch (6.5 to 8 us), though each workgroup counts the whole node.  A stable counting sort by bucket, of which
+// only what lies in the workgroup's range of sorted positions is carried out: all keys are counted, the range is found in
+// the bucket starts, and only keys of buckets that touch it are ranked.
+//
+// The workgroup also writes its part of perm_q, perm_k, pos_k and samp_blk (the block's first tile: its keys), bit
+// for bit what the sorting launches write: the backward and the workspace's readers need them.
+#pragma once
+
+#include "attn_common.h"
+
+namespace ha {
+
+typedef uint32_t codes16 __attribute__((ext_vector_type(4)));
+
+// Keys [16 t, 16 t + 16) of a run of s bucket codes, at any address (heads of an odd number of rows): one 16-byte load where the
+// run starts at a 16-byte boundary, else the aligned words that hold a key of the run.  Keys past the end are undefined.
+__device__ inline codes16 load_16_codes(const uint8_t* codes, int s, int t) {
+  const int i0 = 16 * t, left = s - i0 < 16 ? s - i0 : 16;
+  codes16 v = {0, 0, 0, 0};
+  if (left <= 0) return v;
+  const uintptr_t addr = reinterpret_cast<uintptr_t>(codes) + i0;
+  if ((reinterpret_cast<uintptr_t>(codes) & 15u) == 0 && left == 16) return *reinterpret_cast<const codes16*>(addr);
+  const int skip = (int)(addr & 3u), last = (skip + left - 1) >> 2;
+  const uint32_t* words = reinterpret_cast<const uint32_t*>(addr - skip);
+  uint32_t raw[5];
+#pragma unroll
+  for (int k = 0; k < 5; ++k) raw[k] = words[k < last ? k : last];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) v[k] = __builtin_amdgcn_alignbyte(raw[k + 1], raw[k], skip);
+  return v;
+}
+
+constexpr int kNodeSortWaves = 4;
+constexpr int kNodeSortMax = 32 * 64 * kNodeSortWaves;  // keys of a node: 32 per thread
+
+__host__ __device__ inline int node_sort_rows(const Geometry& g) { return ((g.causal ? g.n >> 1 : g.n) + 63) & ~63; }
+
+struct NodeSortLds {
+  uint32_t* rel;               // [2][rows] keys of the buckets that touch the range, wave by wave: bucket << 16 | index in the node
+  unsigned long long* peers;   // [2][waves][buckets]
+  uint32_t* count;             // [2][waves][buckets] (bucket by bucket over the banks)
+  uint32_t* member;            // [rows / 32] bits: keys of the workgroup's block
+  uint32_t* limits;            // first and last of those buckets, queries and keys
+};
+__host__ __device__ inline size_t node_sort_lds_bytes(const Geometry& g) {
+  const size_t rows = node_sort_rows(g), buckets = (size_t)1 << g.r;
+  return 8 * rows + 2 * kNodeSortWaves * buckets * 12 + rows / 8 + 16;
+}
+__device__ inline NodeSortLds node_sort_lds(const Geometry& g, unsigned char* sm) {
+  const int rows = node_sort_rows(g), buckets = 1 << g.r;
+  NodeSortLds l;
+  l.rel = reinterpret_cast<uint32_t*>(sm);
+  l.peers = reinterpret_cast<unsigned long long*>(sm + 8 * rows);
+  l.count = reinterpret_cast<uint32_t*>(l.peers + 2 * kNodeSortWaves * buckets);
+  l.member = l.count + 2 * kNodeSortWaves * buckets;
+  l.limits = l.member + rows / 32;
+  return l;
+}
+
+// inclusive sums over the wave's lanes
+__device__ inline uint32_t wave_scan(uint32_t x) {
+  const int lane = threadIdx.x & 63;
+  // within rows of 16 lanes, then the last lane of the row before, then of the first half
+  x += __builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, true);
+  x += __builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, true);
+  x += __builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, true);
+  x += __builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, true);
+  const uint32_t r0 = __builtin_amdgcn_readlane(x, 15), r1 = __builtin_amdgcn_readlane(x, 31), r2 = __builtin_amdgcn_readlane(x, 47);
+  return x + (lane >= 16 ? r0 : 0u) + (lane >= 32 ? r1 : 0u) + (lane >= 48 ? r2 : 0u);
+}
+
+// The tile's query rows to qrows[0 .. rows_valid) and its block's key rows to list[0 .. b), both rows within the head.
+// All threads call it; the results are visible on return.
+__device__ inline void sort_node_tile(const AttnArgs& a, const TileWork& w, unsigned char* sm, int32_t* list, int32_t* qrows) {
+  constexpr int NW = kNodeSortWaves, NT = 64 * NW;
+  const Geometry& g = a.g;
+  const NodeSortLds l = node_sort_lds(g, sm);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int s = w.nr.s, rows = node_sort_rows(g), buckets = 1 << g.r;
+  const uint32_t code_mask = (uint32_t)(buckets - 1);
+  const int lo[2] = {w.p0, w.t * g.b}, hi[2] = {w.p0 + w.rows_valid, w.t * g.b + g.b};
+  const bool first_tile = w.p0 == w.t * g.b;  // of its block: it writes the block's keys
+
+  // a thread's keys are consecutive, 16 or (nodes of more than 16 per thread) 32; so are a wave's
+  const bool two = s > 16 * NT;
+  const int per = two ? 32 : 16, i0 = per * tid;
+  codes16 v[2][2];
+  {
+    const uint8_t* codes[2] = {a.codes_q + (int64_t)w.bh * g.n + w.nr.q_start, a.codes_k + (int64_t)w.bh * g.n + w.nr.k_start};
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      v[t][0] = load_16_codes(codes[t], s, i0 / 16);
+      v[t][1] = two ? load_16_codes(codes[t], s, i0 / 16 + 1) : v[t][0];
+    }
+  }
+  for (int i = tid; i < 2 * NW * buckets; i += NT) {
+    l.peers[i] = 0ull;
+    l.count[i] = 0u;
+  }
+  for (int i = tid; i < rows / 32; i += NT) l.member[i] = 0u;
+  __syncthreads();
+
+  const int left = s - i0;  // the thread's keys
+  auto each_key = [&](auto&& f) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      if (u == 1 && !two) break;
+#pragma unroll
+      for (int j = 0; j < 16; ++j) f(16 * u + j, (v[0][u][j >> 2] >> (8 * (j & 3))) & code_mask, (v[1][u][j >> 2] >> (8 * (j & 3))) & code_mask);
+    }
+  };
+  each_key([&](int j, uint32_t cq, uint32_t ck) {
+    if (j < left) {
+      atomicAdd(&l.count[wave * buckets + cq], 1u);
+      atomicAdd(&l.count[(NW + wave) * buckets + ck], 1u);
+    }
+  });
+  __syncthreads();
+
+  // counts to the sorted position of every wave's first key of a bucket, and the first and the last bucket that touch the
+  // range: wave 0 for the queries, 1 for the keys
+  if (wave < 2) {
+    uint32_t* count = l.count + wave * NW * buckets;
+    uint32_t c[NW][4], sum = 0;
+#pragma unroll
+    for (int ww = 0; ww < NW; ++ww)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        c[ww][j] = 4 * lane + j < buckets ? count[ww * buckets + 4 * lane + j] : 0u;
+        sum += c[ww][j];
+      }
+    uint32_t at = wave_scan(sum) - sum;
+    const uint32_t from = (uint32_t)lo[wave], to = (uint32_t)hi[wave];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t bucket_at = at;
+#pragma unroll
+      for (int ww = 0; ww < NW; ++ww) {
+        if (4 * lane + j < buckets) count[ww * buckets + 4 * lane + j] = at;
+        at += c[ww][j];
+      }
+      if (bucket_at <= from && from < at) l.limits[2 * wave] = 4 * lane + j;
+      if (bucket_at < to && to <= at) l.limits[2 * wave + 1] = 4 * lane + j;
+    }
+  }
+  __syncthreads();
+
+  // the wave's keys of those buckets, in order, to rel
+  const uint32_t b0[2] = {l.limits[0], l.limits[2]}, span[2] = {l.limits[1] - l.limits[0], l.limits[3] - l.limits[2]};
+  uint32_t hit[2] = {0u, 0u};  // bits: the thread's keys
+  each_key([&](int j, uint32_t cq, uint32_t ck) {
+    hit[0] |= (cq - b0[0] <= span[0] ? 1u : 0u) << j;
+    hit[1] |= (ck - b0[1] <= span[1] ? 1u : 0u) << j;
+  });
+  const uint32_t real = left >= 32 ? ~0u : left > 0 ? (1u << left) - 1u : 0u;
+  int n[2];
+  {
+    const uint32_t mine = __popc(hit[0] & real) | __popc(hit[1] & real) << 16;
+    const uint32_t incl = wave_scan(mine), total = __builtin_amdgcn_readlane(incl, 63), at = incl - mine;
+    n[0] = (int)(total & 0xffffu);
+    n[1] = (int)(total >> 16);
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      uint32_t* dst = l.rel + t * rows + min(64 * per * wave, rows) + (t ? at >> 16 : at & 0xffffu);
+      for (uint32_t bits = hit[t] & real; bits; bits &= bits - 1) {
+        const int j = __builtin_ctz(bits);
+        const codes16 piece = j & 16 ? v[t][1] : v[t][0];
+        const uint32_t word = j & 8 ? (j & 4 ? piece.w : piece.z) : (j & 4 ? piece.y : piece.x);
+        *dst++ = ((word >> (8 * (j & 3))) & code_mask) << 16 | (uint32_t)(i0 + j);
+      }
+    }
+  }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+
+  // sorted positions: a key's place among the equal keys of its 64 from the lanes' bits in a word per bucket
+  const unsigned long long lane_bit = 1ull << lane;
+  const int most = n[0] > n[1] ? n[0] : n[1];
+  for (int k0 = 0; k0 < most; k0 += 64) {
+    uint32_t e[2];
+    bool valid[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      valid[t] = k0 + lane < n[t];
+      e[t] = valid[t] ? l.rel[t * rows + 64 * per * wave + k0 + lane] : 0u;
+      if (valid[t]) atomicOr(&l.peers[(t * NW + wave) * buckets + (e[t] >> 16)], lane_bit);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    unsigned long long pm[2];
+    uint32_t seen[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      pm[t] = l.peers[(t * NW + wave) * buckets + (e[t] >> 16)];
+      seen[t] = l.count[(t * NW + wave) * buckets + (e[t] >> 16)];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      if (!valid[t]) continue;
+      const int c = (int)(e[t] >> 16), i = (int)(e[t] & 0xffffu);
+      const uint32_t rank = __popcll(pm[t] & (lane_bit - 1ull)), cnt = __popcll(pm[t]);
+      if (rank == cnt - 1) {  // one lane per distinct key
+        l.peers[(t * NW + wave) * buckets + c] = 0ull;
+        l.count[(t * NW + wave) * buckets + c] = seen[t] + cnt;
+      }
+      const int p = (int)(seen[t] + rank);
+      if (p < lo[t] || p >= hi[t]) continue;
+      if (t == 0) {
+        qrows[p - lo[0]] = w.nr.q_start + i;
+      } else {
+        list[p - lo[1]] = w.nr.k_start + i;
+        atomicOr(&l.member[i >> 5], 1u << (i & 31));
+        if (first_tile) a.pos_k_out[w.seg_off + i] = p;
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
+  __syncthreads();
+  for (int i = tid; i < w.rows_valid; i += NT) a.perm_q_out[w.seg_off + lo[0] + i] = qrows[i];
+  if (first_tile)
+    for (int i = tid; i < g.b; i += NT) a.perm_k_out[w.seg_off + lo[1] + i] = list[i];
+}
+
+// Appends the kept samples to the block's keys (build_key_list's list): those that are no keys of the block.  All threads call
+// it behind sort_node_tile; on return the list is whole and sm is read no more.  `l0` = sample threadIdx.x, fetched ahead.
+__device__ inline int append_node_samples(const AttnArgs& a, const TileWork& w, unsigned char* sm, int32_t* list,
+                                          int32_t* scratch, int l0) {
+  constexpr int NW = kNodeSortWaves, NT = 64 * NW;
+  const Geometry& g = a.g;
+  const uint32_t* member = node_sort_lds(g, sm).member;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int m = a.samples != nullptr ? g.m : 0;
+  const bool first_tile = w.p0 == w.t * g.b;
+  int base = g.b;
+  for (int j0 = 0; j0 < m; j0 += NT) {
+    const int j = j0 + tid;
+    int l = l0;
+    bool keep = false;
+    if (j < m) {
+      if (j0 > 0) l = a.samples[(int64_t)w.nr.heap * g.m + j];
+      keep = ((member[l >> 5] >> (l & 31)) & 1u) == 0;  // 1 - M_{i, l_j}: same for every row of the block
+      if (first_tile && !keep) a.samp_blk_out[((int64_t)w.bh * g.total_nodes + w.nr.heap) * g.m + j] = w.t;
+    }
+    const unsigned long long bal = __ballot(keep);
+    if (lane == 0) scratch[wave] = __popcll(bal);
+    __syncthreads();
+    int before = 0, total = 0;
+#pragma unroll
+    for (int ww = 0; ww < NW; ++ww) {
+      const int c = scratch[ww];
+      if (ww < wave) before += c;
+      total += c;
+    }
+    if (keep) list[base + before + __popcll(bal & ((1ull << lane) - 1ull))] = w.nr.k_start + l;
+    base += total;
+    if (j0 + NT < m) __syncthreads();  // before the counters are written again
+  }
+  const int pad = (base + 63) & ~63;
+  for (int i = base + tid; i < pad; i += NT) list[i] = w.nr.k_start;  // loadable, masked by position
+  __syncthreads();
+  return base;
+}
+
+__device__ inline int first_node_sample(const AttnArgs& a, const TileWork& w) {
+  return a.samples != nullptr && (int)threadIdx.x < a.g.m ? a.samples[(int64_t)w.nr.heap * a.g.m + threadIdx.x] : 0;
+}
+
+}  // namespace ha

@@ -17,7 +17,7 @@
 // Long segments (the upper levels of the causal recursion have 64 segments of
 // 65536 keys) would leave most of the chip idle, so the forward pass sorts in
 // chunks of kChunk keys, one 4-wave workgroup each, in two launches (small problems: in B alone, see
-// kOneLaunchChunks):
+// kOneLaunchChunks, and the smallest not here at all, see node_sort.h):
 //   A. every chunk's bucket counts go to a table in the workspace;
 //   B. every chunk finds where its buckets start (buckets before it in the
 //      segment + the same bucket in earlier chunks), ranks its keys and
@@ -35,6 +35,7 @@
 // Traffic per key: 1 byte read in each pass, 4 bytes written (the permutation) for queries and
 // 8 (permutation and position) for keys.
 #include "ha_common.h"
+#include "node_sort.h"
 
 namespace ha {
 
@@ -224,28 +225,12 @@ __device__ inline ChunkRef decode_chunk(const SortArgs& a, int wg) {
   return c;
 }
 
-// Thread t of the workgroup fetches keys [16 t, 16 t + 16) of the chunk: one
-// 16-byte load where the address allows it.  Keys past the chunk's end read as 0.
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-__device__ inline u32x4 load_16_codes(const uint8_t* codes, int s, int t) {
-  const int i0 = 16 * t;
-  u32x4 v = {0, 0, 0, 0};
-  if (i0 + 16 <= s && (reinterpret_cast<uintptr_t>(codes) & 15u) == 0) {
-    v = *reinterpret_cast<const u32x4*>(codes + i0);
-  } else {
-#pragma unroll
-    for (int j = 0; j < 16; ++j)
-      if (i0 + j < s) v[j >> 2] |= (uint32_t)codes[i0 + j] << (8 * (j & 3));
-  }
-  return v;
-}
-
 // Pass A: the chunk's bucket counts.
 __global__ __launch_bounds__(kChunkWaves * 64) void chunk_count_kernel(SortArgs a) {
   __shared__ uint32_t hist[256];
   const ChunkRef c = decode_chunk(a, (int)blockIdx.x);
   const int tid = threadIdx.x;
-  const u32x4 v = load_16_codes(c.codes, c.s, tid);
+  const codes16 v = load_16_codes(c.codes, c.s, tid);
   hist[tid] = 0;
   __syncthreads();
 #pragma unroll
@@ -300,8 +285,8 @@ __global__ __launch_bounds__(NW * 64) void chunk_scatter_kernel(SortArgs a, int 
   }
   {
     if (tid < kChunk / 16) {
-      const u32x4 v = load_16_codes(c.codes, s, tid);
-      *reinterpret_cast<u32x4*>(sm + 16 * tid) = v;
+      const codes16 v = load_16_codes(c.codes, s, tid);
+      *reinterpret_cast<codes16*>(sm + 16 * tid) = v;
     }
     if (COUNT && tid < 512) others[tid] = 0u;
     for (int i = tid; i < kChunkWaves * nbk; i += kChunkWaves * 64) {
@@ -316,7 +301,7 @@ __global__ __launch_bounds__(NW * 64) void chunk_scatter_kernel(SortArgs a, int 
       const int cc = u / (kChunk / 16), t = u % (kChunk / 16);
       if (cc == c.chunk) continue;
       const int left = min(kChunk, c.seg_len - cc * kChunk);
-      const u32x4 v = load_16_codes(c.seg_codes + cc * kChunk, left, t);
+      const codes16 v = load_16_codes(c.seg_codes + cc * kChunk, left, t);
       uint32_t* hist = others + (cc < c.chunk ? 0 : 256);
 #pragma unroll
       for (int j = 0; j < 16; ++j)

@@ -31,8 +31,9 @@
 // against bank conflicts; instead the 16-byte pieces of a row are swizzled (BwdLds), which the lanes do
 // by choosing which piece of the row they fetch.
 // The budget does not quite close: at d = 128 the compiler spills 28 (sampled keys), 12 (exact) and 24 bytes per lane (block keys
-// of an unmasked problem); at d = 64 every form gets three workgroups per CU but the sampled-key pass, whose 173 registers are
-// five too many.
+// of an unmasked problem); at d = 64 every form gets three workgroups per CU.  The compiler gave the sampled-key pass 173
+// registers by itself, five too many; asked for three workgroups it needs 168, without spills (forward + backward, 12 heads:
+// n = 16384 234 -> 227 us, where its 768 workgroups then are one round; n = 32768 451 -> 439 us).
 // What bounds it: the order in which a wave issues reads, products and vector work (two waves per SIMD, 64 products
 // of 32 cycles per tile and wave in the dK / dV passes).  So that order is written out and pinned (below), the rare
 // masks sit behind a branch, and nothing in the loop waits for memory but the one wait per tile.  Counters (32 causal
@@ -115,7 +116,7 @@ __device__ inline void dma_1k(const __amdgpu_buffer_rsrc_t& rsrc, uint32_t lds_a
 // NG = 2: two groups of four waves take the T tiles in turn, each with tile buffers of its own; their sums are added
 // through LDS.
 template <int D, int MODE, bool FINAL, int NG>
-__global__ __launch_bounds__(kBNT * NG, 2) void attn_bwd_kernel(BwdArgs a) {
+__global__ __launch_bounds__(kBNT * NG, (D == 64 && MODE == kBwdDkvSamp) ? 3 : 2) void attn_bwd_kernel(BwdArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   using L = BwdLds<D>;
   constexpr bool kDq = (MODE == kBwdDqNode || MODE == kBwdDqExact);

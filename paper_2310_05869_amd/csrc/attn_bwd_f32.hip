@@ -37,12 +37,12 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kFTT = 32;   // T rows per tile
-constexpr int kFBT = 256;  // threads: four waves
+constexpr int f32_bwd_waves(int kw) { return kw == 8 ? 8 : 4; }  // of a workgroup, by the waves that share 32 R rows
 
-template <int D>
+template <int D, int NW = 4>
 struct F32BwdLds {
   static constexpr int ROW = D + 4;  // floats per staged row
-  static constexpr int BYTES = 4 * 32 * ROW * 4;
+  static constexpr int BYTES = NW * 32 * ROW * 4;
 };
 
 template <int D>
@@ -55,13 +55,14 @@ __host__ __device__ inline size_t bwd_f32_lds_bytes(const Geometry& g, int mode)
 // d = 128 keeps up to 483 registers per lane (two fragments in flight beside rows and accumulators): one wave per SIMD
 // FINAL: the node passes of an unmasked problem, which write the final gradients.
 template <int D, int MODE, int KW, bool FINAL>
-__global__ __launch_bounds__(kFBT, D == 64 ? 2 : 1) void attn_bwd_f32_kernel(BwdArgs a) {
+__global__ __launch_bounds__(64 * f32_bwd_waves(KW), D == 64 ? 2 : 1) void attn_bwd_f32_kernel(BwdArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   constexpr bool kDq = (MODE == kBwdDqNode || MODE == kBwdDqExact);
   constexpr bool kExact = (MODE == kBwdDqExact || MODE == kBwdDkvExact);
   constexpr bool kSorted = (MODE == kBwdDkvBlock || MODE == kBwdDkvSamp);
   constexpr bool kHits = FINAL && MODE == kBwdDkvBlock;  // sampled keys' sums added here
-  constexpr int kRT = 32 * (4 / KW);
+  constexpr int NW = f32_bwd_waves(KW), kFBT = 64 * NW;
+  constexpr int kRT = 32 * (NW / KW);
   constexpr int KJ = D / 8;
   constexpr int DT = D / 32;
   // dQ: a dP is two sums of half the columns each; as one chain of d products it had dQ's error above that of the half-row
@@ -363,18 +364,20 @@ __global__ __launch_bounds__(kFBT, D == 64 ? 2 : 1) void attn_bwd_f32_kernel(Bwd
 template <int D, int MODE, int KW, bool FINAL>
 static int launch_bwd_f32_form(const BwdArgs& args, int grid, hipStream_t st) {
   BwdArgs a = args;
-  if (MODE == kBwdDqNode || MODE == kBwdDkvBlock) set_node_divs<32 * (4 / KW)>(a.f);
-  if (MODE == kBwdDqExact || MODE == kBwdDkvExact) set_exact_divs<32 * (4 / KW)>(a.f);
-  const size_t lds = bwd_f32_lds_bytes<D>(a.f.g, MODE);
+  constexpr int NW = f32_bwd_waves(KW);
+  if (MODE == kBwdDqNode || MODE == kBwdDkvBlock) set_node_divs<32 * (NW / KW)>(a.f);
+  if (MODE == kBwdDqExact || MODE == kBwdDkvExact) set_exact_divs<32 * (NW / KW)>(a.f);
+  a.f.exact_lpt = KW == 8;
+  const size_t lds = KW == 8 ? (size_t)F32BwdLds<D, NW>::BYTES : bwd_f32_lds_bytes<D>(a.f.g, MODE);
   static std::atomic<uint64_t> lds_set{0};  // per instantiation: devices on which the LDS limit is raised
   if (allow_full_lds(reinterpret_cast<const void*>(&attn_bwd_f32_kernel<D, MODE, KW, FINAL>), lds_set) != HA_OK) return HA_ERR_LAUNCH;
-  hipLaunchKernelGGL((attn_bwd_f32_kernel<D, MODE, KW, FINAL>), dim3((unsigned)grid), dim3(kFBT), lds, st, a);
+  hipLaunchKernelGGL((attn_bwd_f32_kernel<D, MODE, KW, FINAL>), dim3((unsigned)grid), dim3(64 * NW), lds, st, a);
   return check_launch();
 }
 
 template <int D, int MODE, int KW>
 static int launch_bwd_f32_one(const BwdArgs& a, hipStream_t st) {
-  const int64_t grid = bwd_grid<32 * (4 / KW)>(a, MODE);
+  const int64_t grid = bwd_grid<32 * (f32_bwd_waves(KW) / KW)>(a, MODE);
   if (grid <= 0) return HA_OK;
   if (grid > kMaxGrid) return HA_ERR_SHAPE;
   if constexpr (MODE == kBwdDqNode || MODE == kBwdDkvBlock)
@@ -383,12 +386,15 @@ static int launch_bwd_f32_one(const BwdArgs& a, hipStream_t st) {
 }
 
 // Waves that share a group of 32 R rows, by the rule of the forward (launch_f32_mode): few groups or short runs
-// of rows (blocks, sample sets) take four.
+// of rows (blocks, sample sets) take four; exact launches of few groups and long rows take eight at d = 64 (forward + backward, 6
+// causal heads, n = 2048: 204 -> 183 us; 3 heads, n = 4000: 372 -> 340; at d = 128 a wave's registers leave one per SIMD).
 template <int D, int MODE>
 static int launch_bwd_f32_mode(const BwdArgs& a, hipStream_t st) {
   const Geometry& g = a.f.g;
   const int run = MODE == kBwdDkvSamp ? g.m : (MODE == kBwdDqNode || MODE == kBwdDkvBlock) ? g.b : a.f.exact_block;
   const bool fits = 3 * (int64_t)((run + 127) / 128 * 128) <= 4 * (int64_t)run;
+  if constexpr (D == 64 && (MODE == kBwdDqExact || MODE == kBwdDkvExact))
+    if (f32_exact_eight(a.f)) return launch_bwd_f32_one<D, MODE, 8>(a, st);  // the forward's rule
   if (fits && 4 * bwd_grid<128>(a, MODE) >= 2048) return launch_bwd_f32_one<D, MODE, 1>(a, st);
   return launch_bwd_f32_one<D, MODE, 4>(a, st);
 }

@@ -38,12 +38,12 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kFKT = 32;   // keys per tile
-constexpr int kFNT = 256;  // threads: four waves
+constexpr int f32_waves(int kw) { return kw == 8 ? 8 : 4; }  // of a workgroup, by the waves that share 32 queries
 
-template <int D>
+template <int D, int NW = 4>
 struct F32Lds {
   static constexpr int ROW = D + 4;                // floats per staged output row
-  static constexpr int BYTES = 4 * 32 * ROW * 4 + 4 * 32 * 2 * 4;
+  static constexpr int BYTES = NW * 32 * ROW * 4 + NW * 32 * 2 * 4;
 };
 
 template <int D>
@@ -76,9 +76,10 @@ __device__ inline float add_log(float m, float l) {
 // FAR (node mode): a head's rows pass the reach of a buffer load's 32-bit offset, so they are addressed in 64 bits.
 // SORT (node mode): the workgroup finds its rows from the node's bucket codes (node_sort.h).
 template <int D, int MODE, int KW, bool FAR, bool SORT>
-__global__ __launch_bounds__(kFNT, D == 64 ? 3 : 2) void attn_f32_kernel(AttnArgs a) {
+__global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void attn_f32_kernel(AttnArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  constexpr int kQT = 32 * (4 / KW);
+  constexpr int NW = f32_waves(KW), kFNT = 64 * NW;
+  constexpr int kQT = 32 * (NW / KW);
   constexpr int KJ = D / 8;    // 16-byte pieces of a row per lane
   constexpr int DT = D / 32;
   constexpr int DTA = DT < 2 ? DT : 2;  // V columns are fetched 64 at a time
@@ -253,8 +254,8 @@ __global__ __launch_bounds__(kFNT, D == 64 ? 3 : 2) void attn_f32_kernel(AttnArg
   // ---- results: every wave's rows through LDS, where the KW parts of a row are merged and rows
   // leave as whole 16-byte pieces of consecutive lanes ----
   constexpr int RS = F32Lds<D>::ROW;
-  float* orow = reinterpret_cast<float*>(smem);   // [4 waves][32][RS]
-  float* ml = orow + 4 * 32 * RS;                 // [4 waves][32][2]: reference, row sum
+  float* orow = reinterpret_cast<float*>(smem);   // [waves][32][RS]
+  float* ml = orow + NW * 32 * RS;                // [waves][32][2]: reference, row sum
   const float l_tot = l_run + __shfl_xor(l_run, 32);
   __syncthreads();  // the key list is read no more
 #pragma unroll
@@ -323,20 +324,21 @@ __global__ __launch_bounds__(kFNT, D == 64 ? 3 : 2) void attn_f32_kernel(AttnArg
 
 template <int D, int MODE, int KW, bool FAR = false, bool SORT = false>
 static int launch_f32_one(const AttnArgs& args, hipStream_t st) {
-  constexpr int kQT = 32 * (4 / KW);
+  constexpr int NW = f32_waves(KW), kQT = 32 * (NW / KW);
   AttnArgs a = args;
   if (MODE == kModeNode) set_node_divs<kQT>(a);
   else set_exact_divs<kQT>(a);
+  a.exact_lpt = KW == 8;
   const int64_t grid = MODE == kModeNode ? node_grid<kQT>(a.g) : exact_grid<kQT>(a);
   if (grid <= 0) return HA_OK;
   if (grid > kMaxGrid) return HA_ERR_SHAPE;
-  const size_t lds = SORT ? f32_qrows_at<D>(a.g) + kQT * 4 : f32_lds_bytes<D>(a.g.b, a.g.m, MODE);
+  const size_t lds = KW == 8 ? (size_t)F32Lds<D, NW>::BYTES : SORT ? f32_qrows_at<D>(a.g) + kQT * 4 : f32_lds_bytes<D>(a.g.b, a.g.m, MODE);
   static std::atomic<uint64_t> lds_set{0};  // per instantiation: devices on which the LDS limit is raised
   if (allow_full_lds(reinterpret_cast<const void*>(&attn_f32_kernel<D, MODE, KW, FAR, SORT>), lds_set) != HA_OK) return HA_ERR_LAUNCH;
   for (int64_t first = 0; first < grid; first += kMaxLaunch) {
     a.wg_first = (int32_t)first;
     const int64_t count = grid - first < kMaxLaunch ? grid - first : kMaxLaunch;
-    hipLaunchKernelGGL((attn_f32_kernel<D, MODE, KW, FAR, SORT>), dim3((unsigned)count), dim3(kFNT), lds, st, a);
+    hipLaunchKernelGGL((attn_f32_kernel<D, MODE, KW, FAR, SORT>), dim3((unsigned)count), dim3(64 * NW), lds, st, a);
     const int rc = check_launch();
     if (rc != HA_OK) return rc;
   }
@@ -359,6 +361,20 @@ int64_t attn_f32_node_grid(const Geometry& g) {
   return kw == 1 ? node_grid<128>(g) : kw == 2 ? node_grid<64>(g) : node_grid<32>(g);
 }
 
+// Exact launches of few workgroups and long rows are bound by the longest chain of key tiles: eight waves then share 32 queries,
+// two per SIMD where four left one, a workgroup that fills a CU (causal: up to one and a half or two rounds of those, heaviest first).
+// Four waves -> eight (MI355X, us; groups of 32 rows in brackets): d = 128: causal, 16 heads, n = 512 (256) 29.9 -> 28.8; 12 heads,
+// n = 1024 (384) 54.7 -> 49.5, 16 (512) 55.1 -> 58.9; 8 heads, n = 2048 (512) 96.4 -> 92.9; 4 heads, n = 4000 (500) 176 -> 162, 1 head 179 -> 141;
+// unmasked, 8 heads, n = 1024 (256) 52.1 -> 48.2, 12 (384) 79.8 -> 87.9; 1 head, n = 4000 181 -> 146, 3 (375) 275 -> 285.
+// d = 64: causal, 8 heads, n = 1024 (256) 24.0 -> 25.0; 6 heads, n = 2048 (384) 48.9 -> 41.8, 8 (512) 49.0 -> 50.6; 3 heads, n = 4000 (375)
+// 84.5 -> 75.1; unmasked, 1 head, n = 2048 (64) 42.4 -> 41.9, 4 (256) 42.7 -> 42.6.
+bool f32_exact_eight(const AttnArgs& a) {
+  const int rows = a.exact_block < a.exact_rows_q ? a.exact_block : a.exact_rows_q;
+  const int64_t groups = exact_grid<32>(a);
+  if (a.g.d == 128) return rows >= 512 && groups <= (!a.exact_causal ? 256 : rows < 2048 ? 384 : 512);
+  return rows >= 2048 && groups <= (a.exact_causal ? 384 : 128);
+}
+
 template <int D, int MODE>
 static int launch_f32_mode(const AttnArgs& a, hipStream_t st) {
   if constexpr (MODE == kModeNode)  // stage calls alone: the whole-call entry points take up to 2^22 rows per head
@@ -370,6 +386,8 @@ static int launch_f32_mode(const AttnArgs& a, hipStream_t st) {
       if (kw == 1) return launch_f32_one<D, MODE, 1, false, true>(a, st);
       return kw == 2 ? launch_f32_one<D, MODE, 2, false, true>(a, st) : launch_f32_one<D, MODE, 4, false, true>(a, st);
     }
+  if constexpr (MODE == kModeExact)
+    if (f32_exact_eight(a)) return launch_f32_one<D, MODE, 8>(a, st);
   if (kw == 1) return launch_f32_one<D, MODE, 1>(a, st);
   return kw == 2 ? launch_f32_one<D, MODE, 2>(a, st) : launch_f32_one<D, MODE, 4>(a, st);
 }

@@ -248,6 +248,27 @@ def test_backward_with_delta_from_the_bf16_output(ha, torch):
         _assert_grad_close(to_host(got), r_, b_, what, FRO_TOL)
 
 
+@pytest.mark.parametrize("d,n,b,m", [(64, 770, 77, 40), (128, 512, 256, 64), (64, 515, 515, 0)])
+def test_unmasked_backward_with_delta_from_the_bf16_output(ha, torch, d, n, b, m):
+    """Here the dQ pass forms delta; the criterion as above.  b = n, m = 0: also exact attention's own entry point."""
+    print(f"unmasked backward, delta from bf16 out, d={d} n={n} b={b} m={m}", flush=True)
+    cfg = dict(B=1, H=2, n=n, d=d, dtype="bf16", law="iid")
+    Q, K, V = synth_inputs.make_qkv(cfg, seed=21)
+    G = _cotangent(Q.shape, 22)
+    tq, tk, tv, tg = (to_device(x, "bf16") for x in (Q, K, V, G))
+    ws = ha.alloc_workspace(ha.make_shape(1, 2, n, d, ha.HA_BF16), ha.make_params(b, m, 7, False, 4096, 0))
+    out, lse = ha.hyperattn_forward(tq, tk, tv, b, m, 7, workspace=ws)
+    results = [ha.hyperattn_backward(tq, tk, tv, out, lse, tg, b, m, 7, fwd_workspace=ws)]
+    if b == n and m == 0:
+        results.append(ha.exact_attn_backward(tq, tk, tv, *ha.exact_attn_forward(tq, tk, tv), tg))
+    torch.cuda.synchronize()
+    ref = orc.hyperattn_backward(Q, K, V, G, b=b, m=m, r=7, seed=0)
+    bnd = orc.hyperattn_backward(Q, K, V, G, b=b, m=m, r=7, seed=0, absolute=True)
+    for grads in results:
+        for got, r_, b_, what in zip(grads, ref, bnd, ("dQ", "dK", "dV")):
+            _assert_grad_close(to_host(got), r_, b_, what, FRO_TOL if m == 0 or m >= 16 else None)
+
+
 def test_backward_is_deterministic_and_leaves_inputs_alone(ha, torch):
     print("backward determinism", flush=True)
     cfg = dict(B=1, H=2, n=2048, d=128, dtype="bf16", law="iid", b=128, m=128, r=7, causal=1, n_min=512, seed=1)

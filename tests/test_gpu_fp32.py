@@ -95,6 +95,14 @@ def test_exact_backward_fp32_forms(H, n, d, causal):
         assert (err <= 2.0 ** -12 * lim + 2.0 ** -100).all(), (name, err.max())
 
 
+# eight waves per group of 32 rows: ragged last tiles, a wave without a tile, more workgroups than CUs (11 x 33)
+@pytest.mark.parametrize("H,n,d,causal", [(1, 2079, 64, True), (1, 2100, 64, False), (1, 513, 128, True), (2, 700, 128, False),
+                                          (11, 1025, 128, True)])
+def test_exact_fp32_eight_waves(H, n, d, causal):
+    test_exact_attention_fp32_forms(H, n, d, causal)
+    test_exact_backward_fp32_forms(H, n, d, causal)
+
+
 def _frobenius(got, ref):
     return float(((got - ref) ** 2).sum() ** 0.5 / (ref ** 2).sum() ** 0.5)
 

@@ -288,7 +288,8 @@ int ha_merge_unpermute(const float* o_b, const float* lse_b, const float* o_r, c
  * (host, 8 floats) receives the times between events on the stream: delta, dQ
  * of the nodes, dQ of the base case (unmasked problems: 0), dK/dV of the block
  * keys, dK/dV of the sampled keys with their reduction, dK/dV of the base case, 0 (the passes write the final
- * tensors themselves), total.
+ * tensors themselves), total.  Small fp32 causal problems, whose passes share launches: the second value is 0, the third
+ * the base case with the sampled keys, the fourth all node passes, the fifth the samples' sums, the sixth 0.
  *
  * exact_attn_backward: gradients of exact_attn_forward (Section 1.1; causal:
  * Section 3.1), the denominator of the forward + backward speed-up.  workspace

@@ -447,6 +447,7 @@ static bool delta_in_dq_pass(const Geometry& g) { return g.dtype == HA_BF16 || g
 
 // ev, when non-null, receives 8 events: start, after delta, dQ of the nodes, dQ of the base case, dK/dV of the block keys,
 // of the sampled keys (with their reduction; unmasked problems: these two the other way round), of the base case, end.
+// Small fp32 causal problems, whose passes share launches: nothing, base case and sampled keys, node passes, the samples' sums, nothing.
 static int backward_impl(const void* Q, const void* K, const void* V, const void* out, const float* out_f32,
                          const float* lse, const void* d_out, void* dQ, void* dK, void* dV, const ha_shape* sh,
                          const ha_params* p,
@@ -542,6 +543,39 @@ static int backward_impl(const void* Q, const void* K, const void* V, const void
     a.fin2 = dV;
     rc = launch_attn_bwd(a, kBwdDkvBlock, st);
     if (rc != HA_OK) return rc;
+    mark(5);
+    mark(6);
+    mark(7);
+    return HA_OK;
+  }
+  if (g.dtype == HA_FP32 && g.levels > 0 && bwd_f32_shares(a)) {
+    // passes side by side: the base case writes the gradients, the node passes and the samples' sums add to them
+    const bool has_samp = g.m > 0;
+    a.base_first = 1;
+    BwdArgs dkv = a, dq = a, samp = a;
+    dkv.fin1 = dK;
+    dkv.fin2 = dV;
+    dq.fin1 = dQ;
+    samp.out1 = samp_k;
+    samp.out2 = samp_v;
+    mark(2);
+    rc = launch_attn_bwd_f32_base(dkv, dq, has_samp ? &samp : nullptr, st);
+    if (rc != HA_OK) return rc;
+    mark(3);
+    for (int l = 0; l < g.levels; ++l) {
+      BwdArgs block = a, node = a;
+      block.level = node.level = l;
+      block.out1 = (float*)dK;
+      block.out2 = (float*)dV;
+      node.out1 = (float*)dQ;
+      rc = launch_attn_bwd_f32_level(block, node, st);
+      if (rc != HA_OK) return rc;
+    }
+    mark(4);
+    for (int l = 0; has_samp && l < g.levels; ++l) {
+      rc = launch_bwd_sample_scatter(a, l, samp_k, samp_v, (float*)dK, (float*)dV, st);
+      if (rc != HA_OK) return rc;
+    }
     mark(5);
     mark(6);
     mark(7);

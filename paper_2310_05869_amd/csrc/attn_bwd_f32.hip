@@ -54,9 +54,9 @@ __host__ __device__ inline size_t bwd_f32_lds_bytes(const Geometry& g, int mode)
 
 // d = 128 keeps up to 483 registers per lane (two fragments in flight beside rows and accumulators): one wave per SIMD
 // FINAL: the node passes of an unmasked problem, which write the final gradients.
+// wg: the workgroup's number among the pass's wgs.
 template <int D, int MODE, int KW, bool FINAL>
-__global__ __launch_bounds__(64 * f32_bwd_waves(KW), D == 64 ? 2 : 1) void attn_bwd_f32_kernel(BwdArgs a) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+__device__ __forceinline__ void bwd_f32_pass(const BwdArgs& a, const int wg, const int wgs, unsigned char* smem) {
   constexpr bool kDq = (MODE == kBwdDqNode || MODE == kBwdDqExact);
   constexpr bool kExact = (MODE == kBwdDqExact || MODE == kBwdDkvExact);
   constexpr bool kSorted = (MODE == kBwdDkvBlock || MODE == kBwdDkvSamp);
@@ -81,7 +81,7 @@ __global__ __launch_bounds__(64 * f32_bwd_waves(KW), D == 64 ? 2 : 1) void attn_
   int32_t* list = scratch + 16;
 
   // ---- which part of the problem this workgroup owns ----
-  BwdWork b = decode_bwd_work<kRT, MODE>(a, kExact ? (int)blockIdx.x : logical_block(blockIdx.x, gridDim.x));
+  BwdWork b = decode_bwd_work<kRT, MODE>(a, kExact ? wg : logical_block(wg, wgs), wgs);
   const TileWork& w = b.w;
 
   const int64_t hs = f.q_bh_stride;
@@ -349,8 +349,8 @@ __global__ __launch_bounds__(64 * f32_bwd_waves(KW), D == 64 ? 2 : 1) void attn_
       const int rr = bwd_r_row<MODE>(a, b, r, &dummy);
       const int64_t out_row = bwd_out_row<MODE>(a, b, r, rr);
       bool add = false;
-      if (MODE == kBwdDqNode && !FINAL) add = node_levels_hold(g, rr, true, w.level);
-      if (MODE == kBwdDkvBlock && !FINAL) add = node_levels_hold(g, rr, false, w.level);
+      if (MODE == kBwdDqNode && !FINAL) add = a.base_first || node_levels_hold(g, rr, true, w.level);
+      if (MODE == kBwdDkvBlock && !FINAL) add = a.base_first || node_levels_hold(g, rr, false, w.level);
       if (kExact) add = lvl != nullptr && node_levels_hold(g, rr, kDq, g.levels);
       const float* from = kExact ? lvl : node_dst;
       if (add) v += *reinterpret_cast<const f32x4*>(from + out_row * D + col);
@@ -359,6 +359,43 @@ __global__ __launch_bounds__(64 * f32_bwd_waves(KW), D == 64 ? 2 : 1) void attn_
   };
   write_out(acc1, a.out1, a.samp1, reinterpret_cast<float*>(a.fin1), a.lvl1);
   if constexpr (!kDq) write_out(acc2, a.out2, a.samp2, reinterpret_cast<float*>(a.fin2), a.lvl2);
+}
+
+template <int D, int MODE, int KW, bool FINAL>
+__global__ __launch_bounds__(64 * f32_bwd_waves(KW), D == 64 ? 2 : 1) void attn_bwd_f32_kernel(BwdArgs a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  bwd_f32_pass<D, MODE, KW, FINAL>(a, (int)blockIdx.x, (int)gridDim.x, smem);
+}
+
+// Passes of a small causal problem side by side in one launch.  One behind the other each of them leaves the chip half empty and
+// pays for its start: the node passes are 256 workgroups of a tile or two (4 heads, n = 4096), the sampled keys 128.  The
+// gradients of fp32 tensors can hold the sums over the parts themselves, so the base case, which writes every row, comes
+// first, and nothing but the order of additions ties the passes together: the base case's dK / dV and dQ and the sampled
+// keys are one launch, longest workgroups first, then each level's dK / dV and dQ another.
+// Forward + backward, passes apart -> shared (MI355X): 4 heads, n = 4096, n_min = 1024, b = m = 64, d = 64 239 -> 214 us, d = 128 447 ->
+// 386; 1 head, n = 2048 170 -> 112; 1 head, n = 8192 251 -> 183; 3 heads, n = 1024, n_min = 256 134 -> 85; 12 heads, n = 4096 558 -> 502.
+// Where the passes fill the chip (one wave per group of rows) they stay apart, with the sums in rows of the workspace: base
+// case first there too, 8 heads, n = 8192, n_min = 2048, b = m = 256 took 1319 instead of 1284 us.
+template <int D, bool NODES>
+__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_bwd_f32_shared_kernel(BwdShared m) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int wg = (int)blockIdx.x;
+  const int first1 = m.part[1].first, first2 = m.part[2].first;
+  if constexpr (NODES) {
+    if (wg < first1) {
+      if (wg < m.part[0].count) bwd_f32_pass<D, kBwdDkvBlock, 4, false>(m.part[0].a, wg, m.part[0].count, smem);
+    } else if (wg - first1 < m.part[1].count) {
+      bwd_f32_pass<D, kBwdDqNode, 4, false>(m.part[1].a, wg - first1, m.part[1].count, smem);
+    }
+  } else {
+    if (wg < first1) {
+      if (wg < m.part[0].count) bwd_f32_pass<D, kBwdDkvExact, 4, false>(m.part[0].a, wg, m.part[0].count, smem);
+    } else if (wg < first2) {
+      if (wg - first1 < m.part[1].count) bwd_f32_pass<D, kBwdDqExact, 4, false>(m.part[1].a, wg - first1, m.part[1].count, smem);
+    } else if (wg - first2 < m.part[2].count) {
+      bwd_f32_pass<D, kBwdDkvSamp, 4, false>(m.part[2].a, wg - first2, m.part[2].count, smem);
+    }
+  }
 }
 
 template <int D, int MODE, int KW, bool FINAL>
@@ -383,6 +420,69 @@ static int launch_bwd_f32_one(const BwdArgs& a, hipStream_t st) {
   if constexpr (MODE == kBwdDqNode || MODE == kBwdDkvBlock)
     if (!a.f.g.causal) return launch_bwd_f32_form<D, MODE, KW, true>(a, (int)grid, st);
   return launch_bwd_f32_form<D, MODE, KW, false>(a, (int)grid, st);
+}
+
+template <int MODE>
+static bool four_waves(const BwdArgs& a) {
+  const Geometry& g = a.f.g;
+  const int run = MODE == kBwdDkvSamp ? g.m : (MODE == kBwdDqNode || MODE == kBwdDkvBlock) ? g.b : a.f.exact_block;
+  return 3 * (int64_t)((run + 127) / 128 * 128) > 4 * (int64_t)run || 4 * bwd_grid<128>(a, MODE) < 2048;
+}
+
+bool bwd_f32_shares(const BwdArgs& a) {
+  return four_waves<kBwdDqExact>(a) && !f32_exact_eight(a.f) && four_waves<kBwdDqNode>(a) && (a.f.g.m == 0 || four_waves<kBwdDkvSamp>(a)) &&
+         2 * bwd_grid<32>(a, kBwdDkvExact) + bwd_grid<32>(a, kBwdDkvSamp) < kMaxLaunch;
+}
+
+template <int D, bool NODES>
+static int launch_shared_form(const BwdShared& m, int64_t grid, hipStream_t st) {
+  size_t lds = F32BwdLds<D>::BYTES;
+  if (NODES) {
+    const size_t l = bwd_f32_lds_bytes<D>(m.part[1].a.f.g, kBwdDqNode);
+    lds = l > lds ? l : lds;
+  }
+  static std::atomic<uint64_t> lds_set{0};  // per instantiation: devices on which the LDS limit is raised
+  if (allow_full_lds(reinterpret_cast<const void*>(&attn_bwd_f32_shared_kernel<D, NODES>), lds_set) != HA_OK) return HA_ERR_LAUNCH;
+  hipLaunchKernelGGL((attn_bwd_f32_shared_kernel<D, NODES>), dim3((unsigned)grid), dim3(256), lds, st, m);
+  return check_launch();
+}
+
+// parts one behind the other; a part begins at a multiple of 8, so that its workgroups' XCDs are those of a launch of its own
+static int launch_shared(BwdShared& m, int parts, const int* modes, bool nodes, hipStream_t st) {
+  int64_t at = 0;
+  for (int i = 0; i < 3; ++i) {
+    BwdPart& p = m.part[i];
+    p.first = (int32_t)at;
+    p.count = 0;
+    if (i >= parts) continue;
+    p.count = (int32_t)bwd_grid<32>(p.a, modes[i]);
+    if (nodes) set_node_divs<32>(p.a.f);
+    else if (modes[i] != kBwdDkvSamp) set_exact_divs<32>(p.a.f);
+    at += (p.count + 7) & ~7;
+  }
+  if (at == 0) return HA_OK;
+  const int d = m.part[0].a.f.g.d;
+  if (d != 64 && d != 128) return HA_ERR_SHAPE;
+  if (nodes) return d == 64 ? launch_shared_form<64, true>(m, at, st) : launch_shared_form<128, true>(m, at, st);
+  return d == 64 ? launch_shared_form<64, false>(m, at, st) : launch_shared_form<128, false>(m, at, st);
+}
+
+int launch_attn_bwd_f32_base(const BwdArgs& dkv, const BwdArgs& dq, const BwdArgs* samp, hipStream_t st) {
+  BwdShared m{};
+  m.part[0].a = dkv;
+  m.part[1].a = dq;
+  m.part[1].a.f.exact_lpt = 1;  // placed as the workgroups before them end
+  if (samp) m.part[2].a = *samp;
+  const int modes[3] = {kBwdDkvExact, kBwdDqExact, kBwdDkvSamp};
+  return launch_shared(m, samp ? 3 : 2, modes, false, st);
+}
+
+int launch_attn_bwd_f32_level(const BwdArgs& block, const BwdArgs& dq, hipStream_t st) {
+  BwdShared m{};
+  m.part[0].a = block;
+  m.part[1].a = dq;
+  const int modes[2] = {kBwdDkvBlock, kBwdDqNode};
+  return launch_shared(m, 2, modes, true, st);
 }
 
 // Waves that share a group of 32 R rows, by the rule of the forward (launch_f32_mode): few groups or short runs

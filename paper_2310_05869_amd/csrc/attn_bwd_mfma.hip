@@ -143,7 +143,7 @@ __global__ __launch_bounds__(kBNT * NG, (D == 64 && MODE == kBwdDkvSamp) ? 3 : 2
   int32_t* list = scratch + 16;
 
   // ---- which part of the problem this workgroup owns ----
-  const BwdWork b = decode_bwd_work<kRT, MODE>(a, kExact ? (int)blockIdx.x : logical_block(blockIdx.x, gridDim.x));
+  const BwdWork b = decode_bwd_work<kRT, MODE>(a, kExact ? (int)blockIdx.x : logical_block(blockIdx.x, gridDim.x), (int)gridDim.x);
   const TileWork& w = b.w;
 
   const int64_t hs = f.q_bh_stride;

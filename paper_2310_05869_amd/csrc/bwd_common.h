@@ -31,11 +31,13 @@ struct BwdArgs {
   const float* O32;
   // Node passes (one launch per level, in level order) accumulate fp32 rows [BH][n][d], natural row
   // order: out1 = dQ (dQ pass) or dK (dK/dV passes), out2 = dV.  The first level that holds a row on
-  // the pass's side writes it, later levels add to it.  The sampled-key pass writes its own rows
+  // the pass's side writes it, later levels add to it.  (base_first: the rows are the gradients of fp32 tensors themselves; the
+  // exact passes come first and write every row, and all levels add to it.)  The sampled-key pass writes its own rows
   // (per level, head, node, query chunk, sample) into out1 / out2 instead.
   float* out1;
   float* out2;
   int32_t level;       // node passes: the launch's level
+  int32_t base_first;
   // exact passes write the final gradients (tensors' dtype): fin1 = dQ or dK, fin2 = dV, after adding
   // the accumulated node rows lvl1 / lvl2 (null: none) where some level holds the row on that side; so do the node
   // passes of an unmasked problem, whose one node is the whole result: its block-key pass runs after the sampled-key
@@ -113,12 +115,12 @@ struct BwdWork {
 };
 
 template <int QT, int MODE>
-__device__ inline BwdWork decode_bwd_work(const BwdArgs& a, int idx) {
+__device__ inline BwdWork decode_bwd_work(const BwdArgs& a, int idx, int wgs) {  // workgroup idx of the pass's wgs
   const AttnArgs& f = a.f;
   const Geometry& g = f.g;
   BwdWork b{};
   if (MODE == kBwdDqNode || MODE == kBwdDkvBlock) {
-    b.w = decode_node_tile<QT>(f, a.level * (int)gridDim.x + idx);
+    b.w = decode_node_tile<QT>(f, a.level * wgs + idx);
   } else if (MODE == kBwdDqExact) {
     b.w = decode_exact_tile<QT>(f, idx);
   } else if (MODE == kBwdDkvExact) {
@@ -260,6 +262,18 @@ inline int64_t bwd_grid(const BwdArgs& a, int mode) {
 
 int launch_attn_bwd_mfma(const BwdArgs& a, int mode, hipStream_t st);  // bf16 tensors
 int launch_attn_bwd_f32(const BwdArgs& a, int mode, hipStream_t st);   // fp32 tensors
+// Passes of an fp32 causal problem that do not wait for each other, in one launch: the base case's dK / dV and dQ with the
+// sampled keys, or a level's block keys with its dQ (bwd_f32_shares: whether the problem is small enough for it).
+struct BwdPart {
+  BwdArgs a;
+  int32_t first, count;  // workgroups
+};
+struct BwdShared {
+  BwdPart part[3];
+};
+bool bwd_f32_shares(const BwdArgs& a);
+int launch_attn_bwd_f32_base(const BwdArgs& dkv, const BwdArgs& dq, const BwdArgs* samp, hipStream_t st);
+int launch_attn_bwd_f32_level(const BwdArgs& block, const BwdArgs& dq, hipStream_t st);
 // delta_i = <dO_i, O_i>; bf16 tensors: O from its unrounded fp32 copy when O_f32 is non-null, else from the tensor
 int launch_bwd_delta(const void* O, const float* O_f32, const void* dO, float* delta, int64_t rows, int d, int dtype,
                      hipStream_t st);

@@ -95,6 +95,38 @@ def test_exact_backward_fp32_forms(H, n, d, causal):
         assert (err <= 2.0 ** -12 * lim + 2.0 ** -100).all(), (name, err.max())
 
 
+# passes that share launches: one to four levels, blocks and base blocks that no tile of 32 divides, no samples, more samples
+# than a slab, several draws of a key; and a problem whose passes stay apart (one wave per group of rows)
+@pytest.mark.parametrize("B,H,n,n_min,d,b,m", [(1, 2, 1024, 512, 64, 64, 64), (1, 1, 1600, 100, 64, 50, 33), (2, 1, 1040, 130, 128, 65, 0),
+                                               (1, 3, 512, 256, 128, 32, 200), (1, 16, 4096, 2048, 64, 128, 128)])
+def test_backward_fp32_shared_launches(B, H, n, n_min, d, b, m):
+    import torch
+
+    import paper_2310_05869_amd as ha
+    print(f"fp32 shared launches B={B} H={H} n={n} n_min={n_min} d={d} b={b} m={m}", flush=True)
+    Q, K, V = synth_inputs.iid_qkv(B, H, n, d, "fp32")
+    G = synth_inputs.iid_qkv(B, H, n, d, "fp32", seed=5)[0]
+    tq, tk, tv, tg = (to_device(x, "fp32") for x in (Q, K, V, G))
+    ws = ha.alloc_workspace(ha.make_shape(B, H, n, d, ha.HA_FP32), ha.make_params(b, m, 7, True, n_min, 2))
+    kw = dict(causal=True, n_min=n_min, seed=2)
+    out, lse = ha.hyperattn_forward(tq, tk, tv, b, m, 7, workspace=ws, **kw)
+    got = [torch.full_like(tq, float("nan")) for _ in range(3)]  # every row is written before it is added to
+    ha.hyperattn_backward(tq, tk, tv, out, lse, tg, b, m, 7, fwd_workspace=ws, grads=tuple(got), **kw)
+    again = ha.hyperattn_backward(tq, tk, tv, out, lse, tg, b, m, 7, fwd_workspace=ws, **kw)
+    torch.cuda.synchronize()
+    for x, y in zip(got, again):
+        assert torch.equal(x, y)
+    for bi, hd in sorted({(0, 0), (B - 1, H - 1)}):
+        one = [x[bi:bi + 1, hd:hd + 1] for x in (Q, K, V, G)]
+        okw = dict(b=b, m=m, r=7, causal=True, n_min=n_min, seed=2)
+        ref = orc.hyperattn_backward(*one, **okw)
+        bound = orc.hyperattn_backward(*one, absolute=True, **okw)
+        for name, x, y, lim in zip(("dQ", "dK", "dV"), got, ref, bound):
+            err = abs(to_host(x)[bi:bi + 1, hd:hd + 1] - y)
+            # sums of up to some thousand terms, 2^-24 each
+            assert (err <= 2.0 ** -12 * lim + 2.0 ** -100).all(), (name, err.max())
+
+
 # eight waves per group of 32 rows: ragged last tiles, a wave without a tile, more workgroups than CUs (11 x 33)
 @pytest.mark.parametrize("H,n,d,causal", [(1, 2079, 64, True), (1, 2100, 64, False), (1, 513, 128, True), (2, 700, 128, False),
                                           (11, 1025, 128, True)])

@@ -35,7 +35,8 @@ struct Alg2Args {
   int32_t* tau_rows;       // [total_nodes][m] node-local query indices
   float* log_unm_t;        // [view heads][m]
   float* log_unm_parts;    // [kAlg2TauSplits][view heads][m]: the same over ranges of keys (bf16)
-  int32_t tau_splits;      // 0: log_unm_t is final; else the number of key ranges to combine
+  int32_t has_parts;       // 0: log_unm_t is final; else the key ranges' sums are to be combined
+  int32_t pos_q_done;      // the sort has written pos_q
   float* log_tau;          // [heads][total_nodes]
   double* vw;              // [view] squared norms of the value rows
   double* vprefix;         // [view] their inclusive prefix sums

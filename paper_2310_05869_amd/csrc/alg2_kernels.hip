@@ -24,7 +24,6 @@ namespace ha {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr uint64_t kStreamTauRows = 0;
 constexpr uint64_t kStreamVnorm = 2;
 
 template <typename T>
@@ -34,22 +33,14 @@ __device__ inline float elem<float>(const float* p) { return *p; }
 template <>
 __device__ inline float elem<uint16_t>(const uint16_t* p) { return __uint_as_float((uint32_t)(*p) << 16); }
 
-__global__ void alg2_prep_kernel(Alg2Args a) {
+// pos_q = P_Q^-1 of one level's nodes, node-local (problems of several levels; where there is one, the sort writes it).
+__global__ void alg2_pos_kernel(Alg2Args a) {
   const Geometry& g = a.g;
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  // rows of T of every node of this level: counter heap * m + j of the stream
-  if (t < (int64_t)a.nodes * g.m) {
-    const int node = (int)(t / g.m), j = (int)(t % g.m);
-    const int heap = (1 << a.level) - 1 + node;
-    const uint64_t hi = rand_u64(a.seed, kStreamTauRows, (uint64_t)heap * g.m + j) >> 32;
-    a.tau_rows[(int64_t)heap * g.m + j] = (int32_t)((hi * (uint64_t)g.n) >> 32);
-  }
-  // pos_q = P_Q^-1, node-local
-  if (t < (int64_t)g.BH * g.n) {
-    const int vh = (int)(t / g.n);
-    const Alg2Node nd = alg2_node(a, vh);
-    a.pos_q[(int64_t)vh * g.n + (a.perm_q[t] - nd.q_start)] = (int32_t)(t % g.n);
-  }
+  if (t >= (int64_t)g.BH * g.n) return;
+  const int vh = (int)(t / g.n);
+  const Alg2Node nd = alg2_node(a, vh);
+  a.pos_q[(int64_t)vh * g.n + (a.perm_q[t] - nd.q_start)] = (int32_t)(t % g.n);
 }
 
 // Squared row norms of V in fp64 (one thread per row); 64 rows per workgroup come in through LDS
@@ -255,9 +246,16 @@ __global__ __launch_bounds__(256) void alg2_tau_max_kernel(Alg2Args a) {
   float mx = -INFINITY;
   for (int j = threadIdx.x; j < g.m; j += 256) {
     float v;
-    if (a.tau_splits > 0) {
-      v = -INFINITY;
-      for (int sp = 0; sp < a.tau_splits; ++sp) v = logaddexpf(v, a.log_unm_parts[((int64_t)sp * g.BH + bh) * g.m + j]);
+    if (a.has_parts) {
+      float p[kAlg2TauSplits];  // all requested at once: one after the other, with a logarithm each, they were most of 7 us
+      float top = -INFINITY, sum = 0.f;
+#pragma unroll
+      for (int sp = 0; sp < kAlg2TauSplits; ++sp) p[sp] = a.log_unm_parts[((int64_t)sp * g.BH + bh) * g.m + j];
+#pragma unroll
+      for (int sp = 0; sp < kAlg2TauSplits; ++sp) top = fmaxf(top, p[sp]);
+#pragma unroll
+      for (int sp = 0; sp < kAlg2TauSplits; ++sp) sum += expf(p[sp] - (top == -INFINITY ? 0.f : top));
+      v = top == -INFINITY ? -INFINITY : top + logf(sum);
       a.log_unm_t[(int64_t)bh * g.m + j] = v;
     } else {
       v = a.log_unm_t[(int64_t)bh * g.m + j];
@@ -426,10 +424,11 @@ static int launch_alg2_t(const Alg2Args& a_in, hipStream_t st) {
   const Geometry& g = a_in.g;
   Alg2Args a = a_in;
   constexpr bool mfma = sizeof(T) == 2;
-  a.tau_splits = mfma ? kAlg2TauSplits : 0;
-  const int64_t rows = (int64_t)g.BH * g.n;
-  int64_t prep = rows > (int64_t)a.nodes * g.m ? rows : (int64_t)a.nodes * g.m;
-  hipLaunchKernelGGL(alg2_prep_kernel, dim3((unsigned)((prep + 255) / 256)), dim3(256), 0, st, a);
+  a.has_parts = mfma;
+  if (!a.pos_q_done) {
+    const int64_t rows = (int64_t)g.BH * g.n;
+    hipLaunchKernelGGL(alg2_pos_kernel, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, st, a);
+  }
   if (a.vnorm && g.m > 0) {
     const unsigned vw_grid = (unsigned)((int64_t)g.BH * ((g.n + kVwRows - 1) / kVwRows));
     if (g.d == 128) hipLaunchKernelGGL((vnorm_weight_kernel<T, 128>), dim3(vw_grid), dim3(256), 0, st, a);

@@ -188,7 +188,8 @@ static void make_projection_rows(uint64_t seed, int d, int r, uint16_t (*Rb)[128
 
 // Hashes the rows of Q and K and stores the call's draws (R, sample indices) in the workspace, in one launch.
 static int run_hash(const void* Q, const void* K, uint8_t* codes_q, uint8_t* codes_k, const Geometry& g, uint64_t seed,
-                    const float* R_dev, const int32_t* samples_dev, float* proj, int32_t* samples, hipStream_t st) {
+                    const float* R_dev, const int32_t* samples_dev, float* proj, int32_t* samples, hipStream_t st,
+                    int32_t* tau_rows = nullptr) {
   HashArgs a{};
   a.X[0] = Q;
   a.X[1] = K;
@@ -201,6 +202,7 @@ static int run_hash(const void* Q, const void* K, uint8_t* codes_q, uint8_t* cod
   a.R_ws = proj;
   a.samples_ws = samples;
   a.samples_dev = samples_dev;
+  a.tau_rows_ws = tau_rows;
   a.g = g;
   a.seed = seed;
   if (!R_dev) make_projection_rows(seed, g.d, g.r, a.Rb);
@@ -1070,11 +1072,13 @@ int hyperattn_forward_alg2(const void* Q, const void* K, const void* V, void* ou
     int32_t* samples = (int32_t*)(base + lay.samples);
     uint8_t* codes_q = base + lay.codes_q;
     uint8_t* codes_k = base + lay.codes_k;
-    rc = run_hash(Q, K, codes_q, codes_k, g, params->seed, nullptr, nullptr, proj, samples, st);
+    rc = run_hash(Q, K, codes_q, codes_k, g, params->seed, nullptr, nullptr, proj, samples, st, (int32_t*)(base + al.tau_rows));
     if (rc != HA_OK) return rc;
+    // (pos_q holds one level)
     rc = launch_seg_sort_nodes(codes_q, codes_k, (int32_t*)(base + lay.perm_q), (int32_t*)(base + lay.perm_k),
                                (int32_t*)(base + lay.pos_k), g.m > 0 ? samples : nullptr,
-                               (int32_t*)(base + lay.samp_blk), (uint32_t*)(base + lay.sort_hist), g, st);
+                               (int32_t*)(base + lay.samp_blk), (uint32_t*)(base + lay.sort_hist), g, st,
+                               g.levels == 1 ? (int32_t*)(base + al.pos_q) : nullptr);
     if (rc != HA_OK) return rc;
     // Algorithm 2 on every node, one level at a time: the unmasked problem is its own single node;
     // a causal problem's level l holds 2^l off-diagonal nodes per head (Algorithm 4), whose results
@@ -1105,6 +1109,7 @@ int hyperattn_forward_alg2(const void* Q, const void* K, const void* V, void* ou
       a.samples = samples;
       a.samp_blk = (const int32_t*)(base + lay.samp_blk);
       a.pos_q = (int32_t*)(base + al.pos_q);
+      a.pos_q_done = g.levels == 1;
       a.tau_rows = (int32_t*)(base + al.tau_rows);
       a.log_unm_t = (float*)(base + al.log_unmasked_t);
       a.log_tau = (float*)(base + al.log_tau);

@@ -26,6 +26,7 @@ __host__ __device__ inline uint64_t rand_u64(uint64_t seed, uint64_t stream, uin
   const uint64_t key = mix64(seed + g * (stream + 1));
   return mix64(key + g * (ctr + 1));
 }
+constexpr uint64_t kStreamTauRows = 0;
 constexpr uint64_t kStreamProjection = 1;
 constexpr uint64_t kStreamSamples = 2;  // + heap index (1-based) of the node
 
@@ -158,7 +159,7 @@ constexpr int64_t kMaxLaunch = 1 << 23;  // workgroups of 256 threads per launch
 // launchers (defined in the .hip files)
 int launch_seg_sort_nodes(const uint8_t* codes_q, const uint8_t* codes_k, int32_t* perm_q, int32_t* perm_k,
                           int32_t* pos_k, const int32_t* samples, int32_t* samp_blk, uint32_t* chunk_hist,
-                          const Geometry& g, hipStream_t st);
+                          const Geometry& g, hipStream_t st, int32_t* pos_q = nullptr);  // pos_q: as pos_k, for the queries
 int64_t seg_sort_chunks(const Geometry& g);  // rows of 256 counters the chunked sort needs
 int launch_seg_sort_flat(const uint8_t* codes, int32_t* perm, int32_t* pos, int n_seg, int seg_len,
                          hipStream_t st);

@@ -20,6 +20,7 @@ struct HashArgs {
   float* R_ws;
   int32_t* samples_ws;
   const int32_t* samples_dev;
+  int32_t* tau_rows_ws;    // Algorithm 2: [total_nodes][m] rows of T, node-local query indices; null: not wanted
   Geometry g;
   uint64_t seed;
   alignas(16) uint16_t Rb[8][128];  // seed-derived R as bf16 bit patterns, hyperplane by hyperplane, zero beyond r and d
@@ -47,6 +48,10 @@ __device__ inline void store_draws(const HashArgs& a) {
         v = sample_index(a.seed, level, node, nr.s, j);
       }
       a.samples_ws[i] = v;
+      if (a.tau_rows_ws) {
+        const uint64_t hi = rand_u64(a.seed, kStreamTauRows, (uint64_t)heap * a.g.m + j) >> 32;
+        a.tau_rows_ws[i] = (int32_t)((hi * (uint64_t)nr.s) >> 32);
+      }
     }
   }
 }

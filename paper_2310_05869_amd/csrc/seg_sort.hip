@@ -48,6 +48,7 @@ struct SortArgs {
   int32_t* perm_q;
   int32_t* perm_k;
   int32_t* pos_k;
+  int32_t* pos_q;          // chunked: positions of the queries, or null
   const int32_t* samples;  // chunked: [total_nodes][m] sample indices ...
   int32_t* samp_blk;       // ... and where to put the sorted block of each: [BH][total_nodes][m]
   Geometry g;
@@ -175,7 +176,7 @@ __global__ __launch_bounds__(kFlatWaves * 64) void seg_sort_kernel(SortArgs a) {
 struct ChunkRef {
   const uint8_t* codes;  // the chunk's keys
   int32_t* perm;         // the segment's permutation (destinations are segment-wide)
-  int32_t* pos;          // the chunk's slice of pos_k, or null (queries)
+  int32_t* pos;          // the chunk's slice of pos_k / pos_q, or null
   const uint8_t* seg_codes;  // the segment's keys
   int32_t seg_len;
   const uint32_t* seg_hist;  // bucket counts of the segment's chunks [nchunks][256]
@@ -214,7 +215,7 @@ __device__ inline ChunkRef decode_chunk(const SortArgs& a, int wg) {
   c.seg_len = nr.s;
   const int64_t off = ((int64_t)level * a.g.BH + bh) * a.g.n_cov + (int64_t)node * nr.s;
   c.perm = (which ? a.perm_k : a.perm_q) + off;
-  c.pos = which ? a.pos_k + off + c.chunk_off : nullptr;
+  c.pos = which ? a.pos_k + off + c.chunk_off : a.pos_q ? a.pos_q + off + c.chunk_off : nullptr;
   uint32_t* seg = a.chunk_hist + ((int64_t)wg - c.chunk) * 256;
   c.seg_hist = seg;
   c.own_hist = seg + (int64_t)c.chunk * 256;
@@ -424,7 +425,7 @@ int64_t seg_sort_chunks(const Geometry& g) {
 
 int launch_seg_sort_nodes(const uint8_t* codes_q, const uint8_t* codes_k, int32_t* perm_q, int32_t* perm_k,
                           int32_t* pos_k, const int32_t* samples, int32_t* samp_blk, uint32_t* chunk_hist,
-                          const Geometry& g, hipStream_t st) {
+                          const Geometry& g, hipStream_t st, int32_t* pos_q) {
   if (g.levels <= 0 || g.total_nodes <= 0) return HA_OK;
   if (g.levels > kSortMaxLevels || g.r < 1 || g.r > 8) return HA_ERR_SHAPE;
   SortArgs a{};
@@ -433,6 +434,7 @@ int launch_seg_sort_nodes(const uint8_t* codes_q, const uint8_t* codes_k, int32_
   a.perm_q = perm_q;
   a.perm_k = perm_k;
   a.pos_k = pos_k;
+  a.pos_q = pos_q;
   a.samples = samples;
   a.samp_blk = samp_blk;
   a.g = g;

@@ -34,8 +34,7 @@ struct Alg2Args {
   int32_t* pos_q;          // [view]
   int32_t* tau_rows;       // [total_nodes][m] node-local query indices
   float* log_unm_t;        // [view heads][m]
-  float* log_unm_parts;    // [kAlg2TauSplits][view heads][m]: the same over ranges of keys (bf16)
-  int32_t has_parts;       // 0: log_unm_t is final; else the key ranges' sums are to be combined
+  float* log_unm_parts;    // [kAlg2TauSplits][view heads][m]: the same over ranges of keys
   int32_t pos_q_done;      // the sort has written pos_q
   float* log_tau;          // [heads][total_nodes]
   double* vw;              // [view] squared norms of the value rows
@@ -45,7 +44,7 @@ struct Alg2Args {
   uint64_t seed;
   float cap_scale, kappa;
   int32_t vnorm;
-  int32_t wg_first;        // tau kernel (bf16): number of the launch's first workgroup, where a call takes several launches
+  int32_t wg_first;        // tau kernels: number of the launch's first workgroup, where a call takes several launches
 };
 
 // Where view head `vh` of a level sits: its real head, node, heap index and first query / key row.

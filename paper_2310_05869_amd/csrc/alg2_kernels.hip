@@ -9,9 +9,9 @@
 // The constants the paper leaves open (the Theta in C_i, kappa) are the caller's.
 // A launch sequence handles one level of nodes (alg2_common.h): the unmasked problem, or one
 // level of Algorithm 4's off-diagonal nodes, every node with its own draws.  The draws, weights and prefix sums are
-// computed here for both dtypes; the two heavy steps here are plain fp32 FMA code (one thread per query row, K / V rows
-// staged through LDS) and serve fp32 tensors, bf16 tensors take the matrix-core forms (alg2_mfma.hip; the caps
-// without value sampling: a mode of the forward kernel).
+// computed here for both dtypes.  The caps without value sampling are a mode of either dtype's forward kernel; what is
+// left here for fp32 tensors, the rows of T and the value product, is plain fp32 FMA code (one thread per key or query
+// row, K / V rows staged through LDS), where bf16 tensors take matrix-core forms (alg2_mfma.hip).
 //
 // Lemma 2's rows are drawn with p_l = |V_l|^2 / |V|_F^2 (V the node's value rows) by inverting
 // the cumulative distribution in fp64: draw r of head bh at the node with heap index h takes the
@@ -140,7 +140,9 @@ __global__ void vnorm_sample_kernel(Alg2Args a) {
   a.vlogw[at] = (float)(-log((double)g.m * p));
 }
 
-// log of the unmasked row sum of the rows T_j: one workgroup per head and kTauRows of them.
+// log of the unmasked row sum of the rows T_j over a range of the keys: one workgroup per head, range and kTauRows of them.  One
+// range per head left the chip idle: 64 rows of two heads, n = 4096, d = 128, were 16 workgroups and 582 us; eight ranges 55 us.
+// Bound by LDS reads of the keys (4 heads, n = 2048, m = 256, 1024 workgroups: 84 us).
 // Key rows pass through LDS in tiles (coalesced loads, every key element serves several rows);
 // a thread owns one key of the tile for some of the rows and keeps their running log sums.
 constexpr int kTauRows = 8;
@@ -158,7 +160,9 @@ __global__ __launch_bounds__(256) void alg2_tau_kernel(Alg2Args a) {
   __shared__ int blk_of[kTauRows];
   const Geometry& g = a.g;
   const int groups_per_head = (g.m + kTauRows - 1) / kTauRows;
-  const int bh = blockIdx.x / groups_per_head, j0 = (blockIdx.x % groups_per_head) * kTauRows;
+  const int idx = a.wg_first + (int)blockIdx.x;
+  const int split = idx % kAlg2TauSplits, row_group = idx / kAlg2TauSplits;
+  const int bh = row_group / groups_per_head, j0 = (row_group % groups_per_head) * kTauRows;
   const int nr = min(kTauRows, g.m - j0);
   const int64_t hb = (int64_t)bh * g.n;   // bh: view head (one node)
   const Alg2Node nd = alg2_node(a, bh);
@@ -178,7 +182,9 @@ __global__ __launch_bounds__(256) void alg2_tau_kernel(Alg2Args a) {
     mx[r] = -INFINITY;
     sum[r] = 0.f;
   }
-  for (int l0 = 0; l0 < g.n; l0 += kKeys) {
+  const int ntiles = (g.n + kKeys - 1) / kKeys;
+  const int l_lo = (int)((int64_t)ntiles * split / kAlg2TauSplits) * kKeys, l_hi = (int)((int64_t)ntiles * (split + 1) / kAlg2TauSplits) * kKeys;
+  for (int l0 = l_lo; l0 < l_hi; l0 += kKeys) {
     const int cnt = min(kKeys, g.n - l0);
     __syncthreads();
     for (int e = tid; e < cnt * (kRowBytes / 4); e += 256) {
@@ -233,7 +239,7 @@ __global__ __launch_bounds__(256) void alg2_tau_kernel(Alg2Args a) {
     float S = 0.f;
     for (int t = 0; t < kKeys; ++t)
       if (red_m[tid][t] > -INFINITY) S += red_s[tid][t] * expf(red_m[tid][t] - M);
-    a.log_unm_t[(int64_t)bh * g.m + j0 + tid] = (M == -INFINITY) ? -INFINITY : M + logf(S);
+    a.log_unm_parts[((int64_t)split * g.BH + bh) * g.m + j0 + tid] = (M == -INFINITY) ? -INFINITY : M + logf(S);
   }
 }
 
@@ -245,21 +251,16 @@ __global__ __launch_bounds__(256) void alg2_tau_max_kernel(Alg2Args a) {
   const int bh = blockIdx.x;
   float mx = -INFINITY;
   for (int j = threadIdx.x; j < g.m; j += 256) {
-    float v;
-    if (a.has_parts) {
-      float p[kAlg2TauSplits];  // all requested at once: one after the other, with a logarithm each, they were most of 7 us
-      float top = -INFINITY, sum = 0.f;
+    float p[kAlg2TauSplits];  // all requested at once: one after the other, with a logarithm each, they were most of 7 us
+    float top = -INFINITY, sum = 0.f;
 #pragma unroll
-      for (int sp = 0; sp < kAlg2TauSplits; ++sp) p[sp] = a.log_unm_parts[((int64_t)sp * g.BH + bh) * g.m + j];
+    for (int sp = 0; sp < kAlg2TauSplits; ++sp) p[sp] = a.log_unm_parts[((int64_t)sp * g.BH + bh) * g.m + j];
 #pragma unroll
-      for (int sp = 0; sp < kAlg2TauSplits; ++sp) top = fmaxf(top, p[sp]);
+    for (int sp = 0; sp < kAlg2TauSplits; ++sp) top = fmaxf(top, p[sp]);
 #pragma unroll
-      for (int sp = 0; sp < kAlg2TauSplits; ++sp) sum += expf(p[sp] - (top == -INFINITY ? 0.f : top));
-      v = top == -INFINITY ? -INFINITY : top + logf(sum);
-      a.log_unm_t[(int64_t)bh * g.m + j] = v;
-    } else {
-      v = a.log_unm_t[(int64_t)bh * g.m + j];
-    }
+    for (int sp = 0; sp < kAlg2TauSplits; ++sp) sum += expf(p[sp] - (top == -INFINITY ? 0.f : top));
+    const float v = top == -INFINITY ? -INFINITY : top + logf(sum);
+    a.log_unm_t[(int64_t)bh * g.m + j] = v;
     mx = fmaxf(mx, v);
   }
   red[threadIdx.x] = mx;
@@ -277,7 +278,7 @@ __global__ __launch_bounds__(256) void alg2_tau_max_kernel(Alg2Args a) {
 constexpr int kA2Rows = 64;  // query rows (threads) per workgroup
 constexpr int kA2Tile = 32;  // key rows per LDS tile
 
-// One thread per query row; 64 consecutive sorted positions of one block per workgroup.
+// With value sampling: one thread per query row; 64 consecutive sorted positions of one block per workgroup.
 template <int D>
 __global__ __launch_bounds__(kA2Rows) void alg2_main_kernel(Alg2Args a) {
   __shared__ float Ks[kA2Tile * D];
@@ -338,7 +339,7 @@ __global__ __launch_bounds__(kA2Rows) void alg2_main_kernel(Alg2Args a) {
     __syncthreads();
     if (tid < cnt) rows[tid] = a.perm_k[hb + t * g.b + k0 + tid];
     __syncthreads();
-    stage(cnt, !a.vnorm);
+    stage(cnt, false);
     __syncthreads();
     for (int j = 0; j < cnt; ++j) {
       float s = 0.f;
@@ -347,10 +348,6 @@ __global__ __launch_bounds__(kA2Rows) void alg2_main_kernel(Alg2Args a) {
       rescale_to(s);
       const float p = expf(s - M);
       msum += p;
-      if (!a.vnorm) {
-#pragma unroll
-        for (int c = 0; c < D; ++c) o[c] = __builtin_fmaf(p, Vs[j * D + c], o[c]);
-      }
     }
   }
   const float log_masked = (msum > 0.f) ? M + logf(msum) : -INFINITY;
@@ -358,7 +355,7 @@ __global__ __launch_bounds__(kA2Rows) void alg2_main_kernel(Alg2Args a) {
   const float log_cap = capped ? logf(a.cap_scale * (float)g.m / ((float)g.n * logf((float)g.n))) + logaddexpf(log_masked, floor_term)
                                : INFINITY;
 
-  // ---- pass 2: the uniform samples of Algorithm 2 (row-sum estimate; Section 4's numerator) ----
+  // ---- pass 2: the uniform samples of Algorithm 2 (row-sum estimate) ----
   for (int j0 = 0; j0 < g.m; j0 += kA2Tile) {
     const int cnt = min(kA2Tile, g.m - j0);
     __syncthreads();
@@ -367,7 +364,7 @@ __global__ __launch_bounds__(kA2Rows) void alg2_main_kernel(Alg2Args a) {
       bias[tid] = (a.samp_blk[draws + j0 + tid] == t) ? -INFINITY : 0.f;  // factor 1 - M_{i,l_j}
     }
     __syncthreads();
-    stage(cnt, !a.vnorm);
+    stage(cnt, false);
     __syncthreads();
     for (int j = 0; j < cnt; ++j) {
       if (bias[j] == -INFINITY) continue;
@@ -376,35 +373,28 @@ __global__ __launch_bounds__(kA2Rows) void alg2_main_kernel(Alg2Args a) {
       for (int c = 0; c < D; ++c) s = __builtin_fmaf(q[c], Ks[j * D + c], s);
       rescale_to(s);
       dsum += expf(fminf(s, log_cap) - M);
-      if (!a.vnorm) {
-        const float p = ratio * expf(s - M);
-#pragma unroll
-        for (int c = 0; c < D; ++c) o[c] = __builtin_fmaf(p, Vs[j * D + c], o[c]);
-      }
     }
   }
 
   // ---- pass 3: the value rows drawn by squared norm (Lemma 2), each with its 1 / (m p_l) ----
-  if (a.vnorm) {
-    for (int j0 = 0; j0 < g.m; j0 += kA2Tile) {
-      const int cnt = min(kA2Tile, g.m - j0);
-      __syncthreads();
-      if (tid < cnt) {
-        rows[tid] = nd.k_start + a.vsamp[draws + j0 + tid];
-        bias[tid] = a.vlogw[draws + j0 + tid];
-      }
-      __syncthreads();
-      stage(cnt, true);
-      __syncthreads();
-      for (int j = 0; j < cnt; ++j) {
-        float s = bias[j];
+  for (int j0 = 0; j0 < g.m; j0 += kA2Tile) {
+    const int cnt = min(kA2Tile, g.m - j0);
+    __syncthreads();
+    if (tid < cnt) {
+      rows[tid] = nd.k_start + a.vsamp[draws + j0 + tid];
+      bias[tid] = a.vlogw[draws + j0 + tid];
+    }
+    __syncthreads();
+    stage(cnt, true);
+    __syncthreads();
+    for (int j = 0; j < cnt; ++j) {
+      float s = bias[j];
 #pragma unroll
-        for (int c = 0; c < D; ++c) s = __builtin_fmaf(q[c], Ks[j * D + c], s);
-        rescale_to(s);
-        const float p = expf(s - M);
+      for (int c = 0; c < D; ++c) s = __builtin_fmaf(q[c], Ks[j * D + c], s);
+      rescale_to(s);
+      const float p = expf(s - M);
 #pragma unroll
-        for (int c = 0; c < D; ++c) o[c] = __builtin_fmaf(p, Vs[j * D + c], o[c]);
-      }
+      for (int c = 0; c < D; ++c) o[c] = __builtin_fmaf(p, Vs[j * D + c], o[c]);
     }
   }
 
@@ -424,7 +414,6 @@ static int launch_alg2_t(const Alg2Args& a_in, hipStream_t st) {
   const Geometry& g = a_in.g;
   Alg2Args a = a_in;
   constexpr bool mfma = sizeof(T) == 2;
-  a.has_parts = mfma;
   if (!a.pos_q_done) {
     const int64_t rows = (int64_t)g.BH * g.n;
     hipLaunchKernelGGL(alg2_pos_kernel, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, st, a);
@@ -445,11 +434,17 @@ static int launch_alg2_t(const Alg2Args& a_in, hipStream_t st) {
     return a.vnorm ? launch_alg2_main_mfma(a, st) : check_launch();  // (without value sampling: the caller's node launch)
   } else {
     if (g.m > 0) {
-      const unsigned tau_grid = (unsigned)((int64_t)g.BH * ((g.m + kTauRows - 1) / kTauRows));
-      if (g.d == 128) hipLaunchKernelGGL((alg2_tau_kernel<128>), dim3(tau_grid), dim3(256), 0, st, a);
-      else hipLaunchKernelGGL((alg2_tau_kernel<64>), dim3(tau_grid), dim3(256), 0, st, a);
+      const int64_t tau_grid = (int64_t)g.BH * ((g.m + kTauRows - 1) / kTauRows) * kAlg2TauSplits;
+      if (tau_grid > 0x7fffffff) return HA_ERR_SHAPE;
+      for (int64_t first = 0; first < tau_grid; first += kMaxLaunch) {
+        a.wg_first = (int32_t)first;
+        const unsigned count = (unsigned)(tau_grid - first < kMaxLaunch ? tau_grid - first : kMaxLaunch);
+        if (g.d == 128) hipLaunchKernelGGL((alg2_tau_kernel<128>), dim3(count), dim3(256), 0, st, a);
+        else hipLaunchKernelGGL((alg2_tau_kernel<64>), dim3(count), dim3(256), 0, st, a);
+      }
     }
     hipLaunchKernelGGL(alg2_tau_max_kernel, dim3((unsigned)g.BH), dim3(256), 0, st, a);
+    if (!a.vnorm) return check_launch();  // (the caller's node launch)
     const int tpb = (g.b + kA2Rows - 1) / kA2Rows;
     const unsigned grid = (unsigned)((int64_t)g.BH * (g.n / g.b) * tpb);
     if (g.d == 128) hipLaunchKernelGGL((alg2_main_kernel<128>), dim3(grid), dim3(kA2Rows), 0, st, a);

@@ -1125,7 +1125,7 @@ int hyperattn_forward_alg2(const void* Q, const void* K, const void* V, void* ou
       rc = launch_alg2(a, st);
       if (rc != HA_OK) return rc;
     }
-    if (use_mfma(g) && !opt->vnorm_sampling) {  // with every node's tau known, all nodes in one launch, as in the forward
+    if (!opt->vnorm_sampling) {  // with every node's tau known, all nodes in one launch, as in the forward
       AttnArgs a = node_args(Q, K, V, out, lse, nullptr, g, base, lay);
       a.log_tau = (const float*)(base + al.log_tau);
       a.cap_scale = opt->cap_scale;

@@ -1,5 +1,5 @@
 // fp32 attention on the fp32 matrix cores: the arithmetic path for HA_FP32 tensors
-// (v_mfma_f32_32x32x2_f32: fp32 products, fp32 sums), with the same node / exact
+// (v_mfma_f32_32x32x2_f32: fp32 products, fp32 sums), with the same node / cap / exact
 // modes and the same outputs as the bf16 kernel (attn_mfma.hip).
 //
 // What bounds it: the matrix pipe where the chip is full (4 heads, n = 4096 in blocks of 1024, two waves per SIMD: busy 46 %
@@ -48,8 +48,9 @@ struct F32Lds {
 
 template <int D>
 __host__ __device__ inline size_t f32_lds_bytes(int b, int m, int mode) {
-  const size_t list = mode == kModeNode ? (size_t)(((b + m + 63) & ~63) + 64) * 4 + 64 : 0;
-  return list > (size_t)F32Lds<D>::BYTES ? list : (size_t)F32Lds<D>::BYTES;
+  const size_t list = mode != kModeExact ? (size_t)(((b + m + 63) & ~63) + 64) * 4 + 64 : 0;
+  const size_t cap = mode == kModeCap ? 4 * 32 * 2 * 4 : 0;  // the waves' masked sums behind the list; a third value per staged row
+  return list + cap > (size_t)F32Lds<D>::BYTES + cap / 2 ? list + cap : (size_t)F32Lds<D>::BYTES + cap / 2;
 }
 
 // SORT: the sort's tables lie behind the list, the tile's query rows behind all else
@@ -80,6 +81,7 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   constexpr int NW = f32_waves(KW), kFNT = 64 * NW;
   constexpr int kQT = 32 * (NW / KW);
+  constexpr bool kCap = MODE == kModeCap, kNode = MODE == kModeNode || kCap;
   constexpr int KJ = D / 8;    // 16-byte pieces of a row per lane
   constexpr int DT = D / 32;
   constexpr int DTA = DT < 2 ? DT : 2;  // V columns are fetched 64 at a time
@@ -91,7 +93,7 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
   int32_t* scratch = reinterpret_cast<int32_t*>(smem);
   int32_t* list = scratch + 16;
 
-  const int bid = a.wg_first + (MODE == kModeNode ? logical_block(blockIdx.x, gridDim.x) : (int)blockIdx.x);
+  const int bid = a.wg_first + (kNode ? logical_block(blockIdx.x, gridDim.x) : (int)blockIdx.x);
   TileWork w;
   int nb, nkeys;
   int32_t* qrows = reinterpret_cast<int32_t*>(smem + (SORT ? f32_qrows_at<D>(a.g) : 0));
@@ -102,9 +104,9 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
     sort_node_tile(a, w, sort_lds, list, qrows);
     nb = a.g.b;
     nkeys = append_node_samples(a, w, sort_lds, list, scratch, l0);
-  } else if (MODE == kModeNode) {
+  } else if (kNode) {
     w = decode_node_tile<kQT>(a, bid);
-    nkeys = build_key_list<kFNT>(a, w, list, scratch, &nb);
+    nkeys = build_key_list<kFNT, kCap>(a, w, list, scratch, &nb, key_list_fetch<kFNT>(a, w));
   } else {
     w = decode_exact_tile<kQT>(a, bid);
     nkeys = max(0, w.k1 - w.k0);
@@ -114,7 +116,7 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
   // causal: a wave ends with the tile that holds its own last row.  Tiles wholly behind its rows are not only idle work:
   // weight 0 times a V that is Inf or NaN is NaN.
   if (MODE == kModeExact && a.exact_causal) ntiles = min(ntiles, (w.q0 - w.k0) / kFKT + wave / KW + 1);
-  const float nat_bias = (MODE == kModeNode && a.g.m > 0) ? logf((float)w.nr.s / (float)a.g.m) : 0.f;
+  const float nat_bias = (kNode && a.g.m > 0) ? logf((float)w.nr.s / (float)a.g.m) : 0.f;
 
   const float* Qh = reinterpret_cast<const float*>(a.Q) + (int64_t)w.bh * a.q_bh_stride;
   const float* Kh = reinterpret_cast<const float*>(a.K) + (int64_t)w.bh * a.k_bh_stride;
@@ -124,7 +126,7 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
   int qrow, q_global = 0;
   if constexpr (SORT) {
     qrow = qrows[r_use];
-  } else if (MODE == kModeNode) {
+  } else if (kNode) {
     qrow = a.perm_q ? a.perm_q[w.seg_off + w.p0 + r_use] : w.nr.q_start + w.p0 + r_use;
   } else {
     q_global = w.q0 + r_in_tile;
@@ -135,12 +137,12 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
   for (int j = 0; j < KJ; ++j) q[j] = *reinterpret_cast<const f32x4*>(Qh + (int64_t)qrow * D + 8 * j + 4 * h);
 
   // rows past the end of the keys read as zeros (such keys are masked by position)
-  const uint32_t bytes = (uint32_t)(MODE == kModeNode ? a.g.n : w.k1) * (uint32_t)(D * 4);
+  const uint32_t bytes = (uint32_t)(kNode ? a.g.n : w.k1) * (uint32_t)(D * 4);
   const __amdgpu_buffer_rsrc_t krsrc = __builtin_amdgcn_make_buffer_rsrc((void*)Kh, 0, (int)bytes, 0x00020000);
   const __amdgpu_buffer_rsrc_t vrsrc = __builtin_amdgcn_make_buffer_rsrc((void*)Vh, 0, (int)bytes, 0x00020000);
   f32x4 kf[KJ];
   auto load_k = [&](int kt) {
-    const int row = MODE == kModeNode ? list[kt * kFKT + lq] : w.k0 + kt * kFKT + lq;
+    const int row = kNode ? list[kt * kFKT + lq] : w.k0 + kt * kFKT + lq;
     if constexpr (FAR) {  // (every row of the list exists)
 #pragma unroll
       for (int j = 0; j < KJ; ++j) kf[j] = *reinterpret_cast<const f32x4*>(Kh + (int64_t)row * D + 8 * j + 4 * h);
@@ -157,7 +159,7 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
       i32x4 rows;
-      if (MODE == kModeNode) {
+      if (kNode) {
         rows = *reinterpret_cast<const i32x4*>(list + kt * kFKT + 8 * g + 4 * h);
       } else {
         const int r0 = w.k0 + kt * kFKT + 8 * g + 4 * h;
@@ -180,6 +182,40 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
     for (int i = 0; i < 16; ++i) o[dt][i] = 0.f;
   float m_run = -INFINITY, l_run = 0.f;
 
+  // Cap mode (Algorithm 2 as printed): the block's keys, padded to whole tiles, come first; then every sample's weight
+  // counts at most C_i in the row sum, whose cap follows from the masked sum of all waves of the row.  One thread per query row
+  // had walked both parts before: whole calls 950 -> 98 us with the tau launch's split (2 heads, n = 4096, d = 128, b = m = 64;
+  // this launch 23), 4 heads, n = 2048, b = m = 256 1590 -> 149 (44), 8 heads, n = 1024, d = 64, b = m = 256 609 -> 72 (21).
+  // The switch to the samples sits in the one loop: a loop per part, shared with the other modes, cost those up to 4 %.
+  const int nbt = kCap ? ((nb + 63) & ~63) / kFKT : 0;
+  float msum = 0.f, log_capw = INFINITY;  // log of (s / m) C_i
+  const float floor_term = kCap && a.kappa > 0.f ? a.log_tau[(int64_t)w.bh * a.g.total_nodes + w.nr.heap] - logf(a.kappa) : -INFINITY;
+  bool sampled = false;
+  auto to_samples = [&]() {  // every wave comes here once
+    float* ex = reinterpret_cast<float*>(list + ((a.g.b + a.g.m + 63) & ~63) + 64);  // [4 waves][32][2], behind the list
+    const float mine = l_run + __shfl_xor(l_run, 32);
+    if (h == 0) {
+      ex[(wave * 32 + lq) * 2] = m_run;
+      ex[(wave * 32 + lq) * 2 + 1] = mine;
+    }
+    __syncthreads();
+    float top = -INFINITY, sum = 0.f;
+#pragma unroll
+    for (int k = 0; k < KW; ++k) top = fmaxf(top, ex[((wave / KW * KW + k) * 32 + lq) * 2]);
+#pragma unroll
+    for (int k = 0; k < KW; ++k) {
+      const float* e = ex + ((wave / KW * KW + k) * 32 + lq) * 2;
+      sum += e[1] * (top == -INFINITY ? 0.f : expf(e[0] - top));
+    }
+    const float log_masked = sum > 0.f ? add_log(top, sum) : -INFINITY;
+    if (a.cap_scale > 0.f) {
+      const float n = (float)w.nr.s;
+      log_capw = logf(a.cap_scale * (float)a.g.m / (n * logf(n))) + logaddexpf(log_masked, floor_term) + nat_bias;
+    }
+    msum = l_run;
+    l_run = 0.f;
+    sampled = true;
+  };
   if (kw < ntiles) load_k(kw);
   for (int kt = kw; kt < ntiles; kt += KW) {
     float va[16][DTA];
@@ -198,7 +234,18 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
     }
 
     const int base = kt * kFKT;
-    const bool plain = base + kFKT <= min(nkeys, nb) &&
+    if constexpr (kCap) {
+      if (kt >= nbt && !sampled) to_samples();
+      const int lim = sampled ? nkeys : nb;
+      if (sampled || base + kFKT > lim) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const int pos = base + 8 * (i / 4) + 4 * h + (i % 4);
+          c[i] = pos >= lim ? -INFINITY : c[i] + (sampled ? nat_bias : 0.f);
+        }
+      }
+    }
+    const bool plain = kCap || base + kFKT <= min(nkeys, nb) &&
                        !(MODE == kModeExact && a.exact_causal && w.k0 + base + kFKT - 1 > w.q0 + (wave / KW) * 32);
     if (!plain) {
       int lim = nkeys;
@@ -219,6 +266,7 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
       const float m_new = fmaxf(m_run, mx);
       const float alpha = expf(m_run - (m_new == -INFINITY ? 0.f : m_new));
       l_run *= alpha;
+      if (kCap) msum *= alpha;
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
@@ -226,10 +274,11 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
       m_run = m_new;
     }
     const float m_use = m_run == -INFINITY ? 0.f : m_run;
+    const float capw = kCap && sampled ? expf(log_capw - m_use) : INFINITY;
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       c[i] = exp_split(c[i] - m_use);
-      l_run += c[i];
+      l_run += kCap ? fminf(c[i], capw) : c[i];
     }
     if constexpr (DT == 2) {
       if (kt + KW < ntiles) load_k(kt + KW);
@@ -250,13 +299,18 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
           o[2 + dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(vb[i][dt], c[i], o[2 + dt], 0, 0, 0);
     }
   }
+  if constexpr (kCap) {
+    if (!sampled) to_samples();
+  }
 
   // ---- results: every wave's rows through LDS, where the KW parts of a row are merged and rows
   // leave as whole 16-byte pieces of consecutive lanes ----
   constexpr int RS = F32Lds<D>::ROW;
   float* orow = reinterpret_cast<float*>(smem);   // [waves][32][RS]
-  float* ml = orow + NW * 32 * RS;                // [waves][32][2]: reference, row sum
+  float* ml = orow + NW * 32 * RS;                // [waves][32][ML]: reference, row sum; cap mode: of the samples, masked sum
+  constexpr int ML = kCap ? 3 : 2;
   const float l_tot = l_run + __shfl_xor(l_run, 32);
+  const float m_tot = kCap ? msum + __shfl_xor(msum, 32) : 0.f;
   __syncthreads();  // the key list is read no more
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt)
@@ -265,35 +319,42 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
       *reinterpret_cast<f32x4*>(orow + (wave * 32 + lq) * RS + 32 * dt + 8 * g + 4 * h) =
           (f32x4){o[dt][4 * g], o[dt][4 * g + 1], o[dt][4 * g + 2], o[dt][4 * g + 3]};
   if (h == 0) {
-    ml[(wave * 32 + lq) * 2] = m_run;
-    ml[(wave * 32 + lq) * 2 + 1] = l_tot;
+    ml[(wave * 32 + lq) * ML] = m_run;
+    ml[(wave * 32 + lq) * ML + 1] = l_tot;
+    if (kCap) ml[(wave * 32 + lq) * ML + 2] = m_tot;
   }
   __syncthreads();
   constexpr int LPR = D / 4;  // lanes per row
-  const bool to_partial = MODE == kModeNode && a.part_o != nullptr;
+  const bool to_partial = kNode && a.part_o != nullptr;
   for (int idx = tid; idx < w.rows_valid * LPR; idx += kFNT) {
     const int r = idx / LPR, col = (idx % LPR) * 4;
     const int w0 = (r / 32) * KW;  // first of the waves that hold the row
     float mx = -INFINITY;
 #pragma unroll
-    for (int k = 0; k < KW; ++k) mx = fmaxf(mx, ml[((w0 + k) * 32 + (r & 31)) * 2]);
+    for (int k = 0; k < KW; ++k) mx = fmaxf(mx, ml[((w0 + k) * 32 + (r & 31)) * ML]);
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    float l = 0.f;
+    float l = 0.f, ms = 0.f;
 #pragma unroll
     for (int k = 0; k < KW; ++k) {
       const int at = (w0 + k) * 32 + (r & 31);
-      const float wk = KW == 1 ? 1.f : (mx == -INFINITY ? 0.f : expf(ml[at * 2] - mx));
-      l += wk * ml[at * 2 + 1];
+      const float wk = KW == 1 ? 1.f : (mx == -INFINITY ? 0.f : expf(ml[at * ML] - mx));
+      l += wk * ml[at * ML + 1];
+      if (kCap) ms += wk * ml[at * ML + 2];
       acc += wk * *reinterpret_cast<const f32x4*>(orow + at * RS + col);
     }
     const bool empty = !(l > 0.f);
     float lse = empty ? -INFINITY : add_log(mx, l);
-    acc *= empty ? 0.f : 1.f / l;
+    if constexpr (kCap) {  // d~_i = masked + max(d_i, tau / kappa)
+      lse = logaddexpf(ms > 0.f ? add_log(mx, ms) : -INFINITY, fmaxf(lse, floor_term));
+      acc *= (mx == -INFINITY || lse == -INFINITY) ? 0.f : expf(mx - lse);
+    } else {
+      acc *= empty ? 0.f : 1.f / l;
+    }
     RowDest dest{};
     if constexpr (SORT) {
       dest.out_row = (int64_t)w.bh * a.g.n + qrows[r];
       dest.part_row = w.seg_off + (qrows[r] - w.nr.q_start);
-    } else if (MODE == kModeNode) {
+    } else if (kNode) {
       dest = node_row_dest(a, w, r);
     } else {
       dest.row_in_head = w.q0 + r;
@@ -326,10 +387,10 @@ template <int D, int MODE, int KW, bool FAR = false, bool SORT = false>
 static int launch_f32_one(const AttnArgs& args, hipStream_t st) {
   constexpr int NW = f32_waves(KW), kQT = 32 * (NW / KW);
   AttnArgs a = args;
-  if (MODE == kModeNode) set_node_divs<kQT>(a);
+  if (MODE != kModeExact) set_node_divs<kQT>(a);
   else set_exact_divs<kQT>(a);
   a.exact_lpt = KW == 8;
-  const int64_t grid = MODE == kModeNode ? node_grid<kQT>(a.g) : exact_grid<kQT>(a);
+  const int64_t grid = MODE != kModeExact ? node_grid<kQT>(a.g) : exact_grid<kQT>(a);
   if (grid <= 0) return HA_OK;
   if (grid > kMaxGrid) return HA_ERR_SHAPE;
   const size_t lds = KW == 8 ? (size_t)F32Lds<D, NW>::BYTES : SORT ? f32_qrows_at<D>(a.g) + kQT * 4 : f32_lds_bytes<D>(a.g.b, a.g.m, MODE);
@@ -379,8 +440,8 @@ template <int D, int MODE>
 static int launch_f32_mode(const AttnArgs& a, hipStream_t st) {
   if constexpr (MODE == kModeNode)  // stage calls alone: the whole-call entry points take up to 2^22 rows per head
     if ((int64_t)a.g.n * (D * 4) > 0x7fffffff + 1ll) return launch_f32_one<D, MODE, 4, true>(a, st);
-  const int run = MODE == kModeNode ? a.g.b : (a.exact_block < a.exact_rows_q ? a.exact_block : a.exact_rows_q);
-  const int kw = f32_waves_per_group(run, MODE == kModeNode ? node_grid<128>(a.g) : exact_grid<128>(a));
+  const int run = MODE != kModeExact ? a.g.b : (a.exact_block < a.exact_rows_q ? a.exact_block : a.exact_rows_q);
+  const int kw = f32_waves_per_group(run, MODE != kModeExact ? node_grid<128>(a.g) : exact_grid<128>(a));
   if constexpr (MODE == kModeNode)
     if (a.codes_q) {
       if (kw == 1) return launch_f32_one<D, MODE, 1, false, true>(a, st);
@@ -394,8 +455,10 @@ static int launch_f32_mode(const AttnArgs& a, hipStream_t st) {
 
 int launch_attn_f32(const AttnArgs& a, int mode, hipStream_t st) {
   if (a.g.dtype != HA_FP32) return HA_ERR_DTYPE;
-  if (a.g.d == 128) return mode == kModeNode ? launch_f32_mode<128, kModeNode>(a, st) : launch_f32_mode<128, kModeExact>(a, st);
-  if (a.g.d == 64) return mode == kModeNode ? launch_f32_mode<64, kModeNode>(a, st) : launch_f32_mode<64, kModeExact>(a, st);
+  if (a.g.d != 64 && a.g.d != 128) return HA_ERR_SHAPE;
+  if (mode == kModeNode) return a.g.d == 128 ? launch_f32_mode<128, kModeNode>(a, st) : launch_f32_mode<64, kModeNode>(a, st);
+  if (mode == kModeCap) return a.g.d == 128 ? launch_f32_mode<128, kModeCap>(a, st) : launch_f32_mode<64, kModeCap>(a, st);
+  if (mode == kModeExact) return a.g.d == 128 ? launch_f32_mode<128, kModeExact>(a, st) : launch_f32_mode<64, kModeExact>(a, st);
   return HA_ERR_SHAPE;
 }
 

@@ -184,6 +184,31 @@ def test_alg2_caps_in_the_node_kernel(ha, torch, dtype, d, n, b, m, r, cap_scale
     test_alg2_options_match_the_oracle(ha, torch, dtype, d, n, b, m, r, cap_scale, kappa, vnorm)
 
 
+@pytest.mark.parametrize("d,H,n,b,m,r,cap_scale,kappa", [
+    (64, 2, 300, 100, 130, 4, 6.0, 1.3),     # four waves per row; padded tail of a block, samples from its next tile on
+    (128, 2, 256, 256, 40, 5, 0.0, 0.0),     # one block: no sample is kept, every row of T sums nothing
+    (64, 2, 48, 16, 33, 3, 5.0, 1.2),        # waves without a tile of the block; seven of eight key ranges empty
+    (128, 2, 2080, 65, 300, 6, 6.0, 1.4),    # ragged ranges, blocks across tiles
+    (64, 2, 650, 65, 0, 4, 0.0, 0.0),        # no samples at all
+    (128, 40, 896, 64, 77, 5, 6.0, 1.3),     # two waves per row
+    (64, 80, 896, 128, 31, 5, 6.0, 1.3),     # one wave per row
+    (128, 80, 700, 100, 0, 5, 0.0, 0.0),     # one wave per row, no samples
+    (64, 80, 700, 100, 65, 5, 0.0, 1.4)])    # lower cap alone
+def test_alg2_fp32_caps_in_the_node_kernel(ha, torch, d, H, n, b, m, r, cap_scale, kappa):
+    """The fp32 forward kernel's cap mode at the edges of its tiles and for each number of waves that share a row; the first and
+    the last head (heads share the draws) against the oracle: criteria as above."""
+    print(f"alg2 fp32 d={d} H={H} n={n} b={b} m={m} r={r} cap={cap_scale} kappa={kappa}", flush=True)
+    Q, K, V = (x.astype(np.float32) for x in synth_inputs.make_qkv(dict(B=1, H=H, n=n, d=d, dtype="fp32", law="iid"), seed=n))
+    out, lse, _ = ha.hyperattn_forward_alg2(*(to_device(x, "fp32") for x in (Q, K, V)), b, m, r, seed=5, cap_scale=cap_scale,
+                                            kappa=kappa)
+    torch.cuda.synchronize()
+    ends = [0, H - 1]
+    ref_out, ref_lse, _ = orc.hyperattn_forward_alg2(Q[:, ends], K[:, ends], V[:, ends], b=b, m=m, r=r, seed=5,
+                                                     cap_scale=cap_scale, kappa=kappa)
+    np.testing.assert_allclose(to_host(lse)[:, ends], ref_lse, rtol=3e-5, atol=3e-5)
+    assert_close(to_host(out)[:, ends], ref_out, "fp32", "out")
+
+
 def test_alg2_more_workgroups_than_one_launch_holds(ha, torch):
     """All levels' nodes together are 20 M workgroups of 256 threads, each level's own 4 M: more than a launch counts.  Heads
     are independent and share the draws, so halves of the heads give the same bits."""

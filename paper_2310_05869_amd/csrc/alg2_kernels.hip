@@ -10,8 +10,8 @@
 // A launch sequence handles one level of nodes (alg2_common.h): the unmasked problem, or one
 // level of Algorithm 4's off-diagonal nodes, every node with its own draws.  The draws, weights and prefix sums are
 // computed here for both dtypes.  The caps without value sampling are a mode of either dtype's forward kernel; what is
-// left here for fp32 tensors, the rows of T and the value product, is plain fp32 FMA code (one thread per key or query
-// row, K / V rows staged through LDS), where bf16 tensors take matrix-core forms (alg2_mfma.hip).
+// left here for fp32 tensors are the rows of T and the value product, the latter plain fp32 FMA code (one thread per query
+// row, K / V rows staged through LDS); bf16 tensors take the forms of alg2_mfma.hip.
 //
 // Lemma 2's rows are drawn with p_l = |V_l|^2 / |V|_F^2 (V the node's value rows) by inverting
 // the cumulative distribution in fp64: draw r of head bh at the node with heap index h takes the
@@ -140,24 +140,19 @@ __global__ void vnorm_sample_kernel(Alg2Args a) {
   a.vlogw[at] = (float)(-log((double)g.m * p));
 }
 
-// log of the unmasked row sum of the rows T_j over a range of the keys: one workgroup per head, range and kTauRows of them.  One
-// range per head left the chip idle: 64 rows of two heads, n = 4096, d = 128, were 16 workgroups and 582 us; eight ranges 55 us.
-// Bound by LDS reads of the keys (4 heads, n = 2048, m = 256, 1024 workgroups: 84 us).
-// Key rows pass through LDS in tiles (coalesced loads, every key element serves several rows);
-// a thread owns one key of the tile for some of the rows and keeps their running log sums.
-constexpr int kTauRows = 8;
+// log of the unmasked row sum of the rows T_j over a range of the keys, on the fp32 matrix cores: a workgroup per head, range and
+// 32 rows of T, whose four waves take every fourth tile of 32 keys, as in attn_f32.hip (S^T = K Q^T: a lane holds 16 keys of one
+// row; K fragments straight from the caches; sums merged through LDS at the end).  Bound by latency: a wave has a few tiles.
+// 64 rows of two heads, n = 4096, d = 128: one thread per key and two rows, a head's keys in one range 582 us, in eight 55,
+// this form 19; 4 heads, n = 2048, m = 256: 84 -> 14.
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+constexpr int kTauRows = 32, kTauKeys = 32, kTauWaves = 4;
 
 template <int D>
-__global__ __launch_bounds__(256) void alg2_tau_kernel(Alg2Args a) {
-  constexpr int kKeys = 64;   // keys per tile
-  constexpr int kGroups = 256 / kKeys;               // thread groups, each with its own rows
-  constexpr int kRpt = kTauRows / kGroups;           // rows per thread
-  constexpr int kRowBytes = D * 4;
-  constexpr int kStride = kRowBytes + 4;             // odd number of words: no bank conflicts between the keys
-  __shared__ __attribute__((aligned(16))) unsigned char tile[kKeys * kStride];
-  __shared__ __attribute__((aligned(16))) float qs[kTauRows][D];
-  __shared__ float red_m[kTauRows][kKeys], red_s[kTauRows][kKeys];
-  __shared__ int blk_of[kTauRows];
+__global__ __launch_bounds__(64 * kTauWaves, 2) void alg2_tau_kernel(Alg2Args a) {
+  constexpr int KJ = D / 8;
+  __shared__ float red_m[2 * kTauWaves][kTauRows], red_s[2 * kTauWaves][kTauRows];
   const Geometry& g = a.g;
   const int groups_per_head = (g.m + kTauRows - 1) / kTauRows;
   const int idx = a.wg_first + (int)blockIdx.x;
@@ -166,79 +161,66 @@ __global__ __launch_bounds__(256) void alg2_tau_kernel(Alg2Args a) {
   const int nr = min(kTauRows, g.m - j0);
   const int64_t hb = (int64_t)bh * g.n;   // bh: view head (one node)
   const Alg2Node nd = alg2_node(a, bh);
-  const int32_t* trows = a.tau_rows + (int64_t)nd.heap * g.m;
   const float* Qh = reinterpret_cast<const float*>(a.Q) + ((int64_t)nd.head * a.n_full + nd.q_start) * D;
-  const unsigned char* Kh = reinterpret_cast<const unsigned char*>(a.K) + ((int64_t)nd.head * a.n_full + nd.k_start) * kRowBytes;
+  const float* Kh = reinterpret_cast<const float*>(a.K) + ((int64_t)nd.head * a.n_full + nd.k_start) * D;
   const int tid = threadIdx.x;
-  for (int e = tid; e < kTauRows * D; e += 256) {
-    const int r = e / D, c = e % D;
-    qs[r][c] = r < nr ? *(Qh + (int64_t)trows[j0 + r] * D + c) : 0.f;
-  }
-  if (tid < kTauRows) blk_of[tid] = tid < nr ? a.pos_q[hb + trows[j0 + tid]] / g.b : -1;
-  const int k = tid % kKeys, grp = tid / kKeys;
-  float mx[kRpt], sum[kRpt];
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lq = tid & 31, h = (tid >> 5) & 1;
+  const int ntiles = (g.n + kTauKeys - 1) / kTauKeys;
+  const int t_lo = (int)((int64_t)ntiles * split / kAlg2TauSplits), t_hi = (int)((int64_t)ntiles * (split + 1) / kAlg2TauSplits);
+
+  f32x4 kf[KJ];
+  auto load_k = [&](int kt) {  // (rows past the end: the last one, masked below)
+    const float* kr = Kh + (int64_t)min(kt * kTauKeys + lq, g.n - 1) * D + 4 * h;
 #pragma unroll
-  for (int r = 0; r < kRpt; ++r) {
-    mx[r] = -INFINITY;
-    sum[r] = 0.f;
-  }
-  const int ntiles = (g.n + kKeys - 1) / kKeys;
-  const int l_lo = (int)((int64_t)ntiles * split / kAlg2TauSplits) * kKeys, l_hi = (int)((int64_t)ntiles * (split + 1) / kAlg2TauSplits) * kKeys;
-  for (int l0 = l_lo; l0 < l_hi; l0 += kKeys) {
-    const int cnt = min(kKeys, g.n - l0);
-    __syncthreads();
-    for (int e = tid; e < cnt * (kRowBytes / 4); e += 256) {
-      const int r = e / (kRowBytes / 4), w = e % (kRowBytes / 4);
-      *reinterpret_cast<uint32_t*>(tile + r * kStride + 4 * w) =
-          *reinterpret_cast<const uint32_t*>(Kh + (int64_t)l0 * kRowBytes + (int64_t)e * 4);
+    for (int j = 0; j < KJ; ++j) kf[j] = *reinterpret_cast<const f32x4*>(kr + 8 * j);
+  };
+  if (t_lo + wave < t_hi) load_k(t_lo + wave);
+  const int row = a.tau_rows[(int64_t)nd.heap * g.m + j0 + (lq < nr ? lq : 0)];
+  const int blk0 = a.pos_q[hb + row] / g.b * g.b;  // first sorted position of the row's block
+  f32x4 q[KJ];
+#pragma unroll
+  for (int j = 0; j < KJ; ++j) q[j] = *reinterpret_cast<const f32x4*>(Qh + (int64_t)row * D + 8 * j + 4 * h);
+
+  float mx = -INFINITY, sum = 0.f;
+  for (int kt = t_lo + wave; kt < t_hi; kt += kTauWaves) {
+    const int base = kt * kTauKeys + 4 * h;  // accumulator register i: key base + 8 (i / 4) + i % 4
+    int pos[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) pos[i] = a.pos_k[hb + min(base + 8 * (i / 4) + i % 4, g.n - 1)];
+    f32x16 c;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) c[i] = 0.f;
+#pragma unroll
+    for (int j = 0; j < KJ; ++j)
+#pragma unroll
+      for (int z = 0; z < 4; ++z) c = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[j][z], q[j][z], c, 0, 0, 0);
+    if (kt + kTauWaves < t_hi) load_k(kt + kTauWaves);
+    float top = mx;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const bool out = base + 8 * (i / 4) + i % 4 >= g.n || (uint32_t)(pos[i] - blk0) < (uint32_t)g.b;  // 1 - M
+      c[i] = out ? -INFINITY : c[i];
+      top = fmaxf(top, c[i]);
     }
-    __syncthreads();
-    if (k >= cnt) continue;
-    const int kblk = a.pos_k[hb + l0 + k] / g.b;
-    const float* kr = reinterpret_cast<const float*>(tile + k * kStride);
-    float s[kRpt];
-#pragma unroll
-    for (int r = 0; r < kRpt; ++r) s[r] = 0.f;
-    // ascending columns, one fused multiply-add each (the scores of an fp32 dot product); four columns
-    // per step so that a row of q is read 16 bytes at a time
-#pragma unroll 4
-    for (int c = 0; c < D; c += 4) {
-      float x[4];
-#pragma unroll
-      for (int z = 0; z < 4; ++z) x[z] = kr[c + z];
-#pragma unroll
-      for (int r = 0; r < kRpt; ++r) {
-        const float4 qv = *reinterpret_cast<const float4*>(&qs[grp * kRpt + r][c]);
-        s[r] = __builtin_fmaf(qv.x, x[0], s[r]);
-        s[r] = __builtin_fmaf(qv.y, x[1], s[r]);
-        s[r] = __builtin_fmaf(qv.z, x[2], s[r]);
-        s[r] = __builtin_fmaf(qv.w, x[3], s[r]);
-      }
+    if (top > mx) {
+      sum *= expf(mx - top);
+      mx = top;
     }
+    const float ref = mx == -INFINITY ? 0.f : mx;
 #pragma unroll
-    for (int r = 0; r < kRpt; ++r) {
-      if (kblk == blk_of[grp * kRpt + r]) continue;  // 1 - M (rows beyond nr have block -1 and are dropped below)
-      if (s[r] > mx[r]) {
-        sum[r] = sum[r] * expf(mx[r] - s[r]) + 1.f;
-        mx[r] = s[r];
-      } else {
-        sum[r] += expf(s[r] - mx[r]);
-      }
-    }
+    for (int i = 0; i < 16; ++i) sum += exp_split(c[i] - ref);
   }
-  __syncthreads();
-#pragma unroll
-  for (int r = 0; r < kRpt; ++r) {
-    red_m[grp * kRpt + r][k] = mx[r];
-    red_s[grp * kRpt + r][k] = sum[r];
-  }
+  red_m[2 * wave + h][lq] = mx;
+  red_s[2 * wave + h][lq] = sum;
   __syncthreads();
   if (tid < nr) {
     float M = -INFINITY;
-    for (int t = 0; t < kKeys; ++t) M = fmaxf(M, red_m[tid][t]);
+#pragma unroll
+    for (int t = 0; t < 2 * kTauWaves; ++t) M = fmaxf(M, red_m[t][tid]);
     float S = 0.f;
-    for (int t = 0; t < kKeys; ++t)
-      if (red_m[tid][t] > -INFINITY) S += red_s[tid][t] * expf(red_m[tid][t] - M);
+#pragma unroll
+    for (int t = 0; t < 2 * kTauWaves; ++t)
+      if (red_m[t][tid] > -INFINITY) S += red_s[t][tid] * expf(red_m[t][tid] - M);
     a.log_unm_parts[((int64_t)split * g.BH + bh) * g.m + j0 + tid] = (M == -INFINITY) ? -INFINITY : M + logf(S);
   }
 }

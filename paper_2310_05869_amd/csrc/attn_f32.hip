@@ -184,7 +184,7 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
 
   // Cap mode (Algorithm 2 as printed): the block's keys, padded to whole tiles, come first; then every sample's weight
   // counts at most C_i in the row sum, whose cap follows from the masked sum of all waves of the row.  One thread per query row
-  // had walked both parts before: whole calls 950 -> 98 us with the tau launch's split (2 heads, n = 4096, d = 128, b = m = 64;
+  // had walked both parts before: whole calls with the launch for tau of that time 950 -> 98 us (2 heads, n = 4096, d = 128, b = m = 64;
   // this launch 23), 4 heads, n = 2048, b = m = 256 1590 -> 149 (44), 8 heads, n = 1024, d = 64, b = m = 256 609 -> 72 (21).
   // The switch to the samples sits in the one loop: a loop per part, shared with the other modes, cost those up to 4 %.
   const int nbt = kCap ? ((nb + 63) & ~63) / kFKT : 0;

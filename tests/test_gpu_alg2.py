@@ -195,16 +195,18 @@ def test_alg2_caps_in_the_node_kernel(ha, torch, dtype, d, n, b, m, r, cap_scale
     (128, 80, 700, 100, 0, 5, 0.0, 0.0),     # one wave per row, no samples
     (64, 80, 700, 100, 65, 5, 0.0, 1.4)])    # lower cap alone
 def test_alg2_fp32_caps_in_the_node_kernel(ha, torch, d, H, n, b, m, r, cap_scale, kappa):
-    """The fp32 forward kernel's cap mode at the edges of its tiles and for each number of waves that share a row; the first and
+    """The fp32 forward kernel's cap mode and the sums of the rows of T at the edges of its tiles and for each number of waves that share a row; the first and
     the last head (heads share the draws) against the oracle: criteria as above."""
     print(f"alg2 fp32 d={d} H={H} n={n} b={b} m={m} r={r} cap={cap_scale} kappa={kappa}", flush=True)
     Q, K, V = (x.astype(np.float32) for x in synth_inputs.make_qkv(dict(B=1, H=H, n=n, d=d, dtype="fp32", law="iid"), seed=n))
-    out, lse, _ = ha.hyperattn_forward_alg2(*(to_device(x, "fp32") for x in (Q, K, V)), b, m, r, seed=5, cap_scale=cap_scale,
-                                            kappa=kappa)
+    out, lse, ws = ha.hyperattn_forward_alg2(*(to_device(x, "fp32") for x in (Q, K, V)), b, m, r, seed=5, cap_scale=cap_scale,
+                                             kappa=kappa)
     torch.cuda.synchronize()
+    views = ha.alg2_workspace_views(ws, ha.make_shape(1, H, n, d, ha.HA_FP32), ha.make_params(b, m, r, False, 4096, 5))
     ends = [0, H - 1]
-    ref_out, ref_lse, _ = orc.hyperattn_forward_alg2(Q[:, ends], K[:, ends], V[:, ends], b=b, m=m, r=r, seed=5,
+    ref_out, ref_lse, ref_tau = orc.hyperattn_forward_alg2(Q[:, ends], K[:, ends], V[:, ends], b=b, m=m, r=r, seed=5,
                                                      cap_scale=cap_scale, kappa=kappa)
+    np.testing.assert_allclose(views["log_tau"][ends, 0].cpu().numpy(), ref_tau, rtol=2e-5, atol=2e-5)
     np.testing.assert_allclose(to_host(lse)[:, ends], ref_lse, rtol=3e-5, atol=3e-5)
     assert_close(to_host(out)[:, ends], ref_out, "fp32", "out")
 

@@ -9,9 +9,8 @@
 // The constants the paper leaves open (the Theta in C_i, kappa) are the caller's.
 // A launch sequence handles one level of nodes (alg2_common.h): the unmasked problem, or one
 // level of Algorithm 4's off-diagonal nodes, every node with its own draws.  The draws, weights and prefix sums are
-// computed here for both dtypes.  The caps without value sampling are a mode of either dtype's forward kernel; what is
-// left here for fp32 tensors are the rows of T and the value product, the latter plain fp32 FMA code (one thread per query
-// row, K / V rows staged through LDS); bf16 tensors take the forms of alg2_mfma.hip.
+// computed here for both dtypes, the sums of the rows of T for fp32 tensors (bf16: alg2_mfma.hip).  The caps are a mode of
+// either dtype's forward kernel, with value sampling a mode of the fp32 one and a kernel of alg2_mfma.hip.
 //
 // Lemma 2's rows are drawn with p_l = |V_l|^2 / |V|_F^2 (V the node's value rows) by inverting
 // the cumulative distribution in fp64: draw r of head bh at the node with heap index h takes the
@@ -257,140 +256,6 @@ __global__ __launch_bounds__(256) void alg2_tau_max_kernel(Alg2Args a) {
   }
 }
 
-constexpr int kA2Rows = 64;  // query rows (threads) per workgroup
-constexpr int kA2Tile = 32;  // key rows per LDS tile
-
-// With value sampling: one thread per query row; 64 consecutive sorted positions of one block per workgroup.
-template <int D>
-__global__ __launch_bounds__(kA2Rows) void alg2_main_kernel(Alg2Args a) {
-  __shared__ float Ks[kA2Tile * D];
-  __shared__ float Vs[kA2Tile * D];
-  __shared__ int32_t rows[kA2Tile];
-  __shared__ float bias[kA2Tile];
-  const Geometry& g = a.g;
-  const int tid = threadIdx.x;
-  const int tpb = (g.b + kA2Rows - 1) / kA2Rows;
-  const int tile = blockIdx.x % ((g.n / g.b) * tpb);
-  const int bh = blockIdx.x / ((g.n / g.b) * tpb);
-  const int t = tile / tpb, chunk = tile % tpb;
-  const int p0 = t * g.b + chunk * kA2Rows;
-  const bool valid = chunk * kA2Rows + tid < g.b;
-  const int64_t hb = (int64_t)bh * g.n;   // bh: view head (one node); perm values are rows of the real head
-  const Alg2Node nd = alg2_node(a, bh);
-  const int qrow = a.perm_q[hb + (valid ? p0 + tid : p0)];
-  const float* Qh = reinterpret_cast<const float*>(a.Q) + (int64_t)nd.head * a.n_full * D;
-  const float* Kh = reinterpret_cast<const float*>(a.K) + (int64_t)nd.head * a.n_full * D;
-  const float* Vh = reinterpret_cast<const float*>(a.V) + (int64_t)nd.head * a.n_full * D;
-  const int64_t draws = ((int64_t)nd.head * a.total_nodes + nd.heap) * g.m;   // this node's entries of the per-node arrays
-
-  float q[D], o[D];
-#pragma unroll
-  for (int c = 0; c < D; ++c) {
-    q[c] = *(Qh + (int64_t)qrow * D + c);
-    o[c] = 0.f;
-  }
-  float M = -INFINITY;      // reference of every exponential below
-  float msum = 0.f;         // masked row sum / e^M
-  float dsum = 0.f;         // sum of (capped) kept samples / e^M
-  const float ratio = g.m > 0 ? (float)g.n / (float)g.m : 0.f;
-  const float log_tau = a.log_tau[(int64_t)nd.head * a.total_nodes + nd.heap];
-  const float floor_term = a.kappa > 0.f ? log_tau - logf(a.kappa) : -INFINITY;
-
-  auto rescale_to = [&](float m_new) {
-    if (m_new > M) {
-      const float f = expf(M - m_new);  // M = -inf gives 0 with all sums 0
-      msum *= f;
-      dsum *= f;
-#pragma unroll
-      for (int c = 0; c < D; ++c) o[c] *= f;
-      M = m_new;
-    }
-  };
-  // stage `cnt` key rows (indices and per-row log weights already in LDS) as fp32
-  auto stage = [&](int cnt, bool with_v) {
-    for (int e = tid; e < cnt * D; e += kA2Rows) {
-      const int j = e / D, c = e % D;
-      Ks[e] = *(Kh + (int64_t)rows[j] * D + c);
-      if (with_v) Vs[e] = *(Vh + (int64_t)rows[j] * D + c);
-    }
-  };
-
-  // ---- pass 1: the keys of this block (mask M^H) ----
-  for (int k0 = 0; k0 < g.b; k0 += kA2Tile) {
-    const int cnt = min(kA2Tile, g.b - k0);
-    __syncthreads();
-    if (tid < cnt) rows[tid] = a.perm_k[hb + t * g.b + k0 + tid];
-    __syncthreads();
-    stage(cnt, false);
-    __syncthreads();
-    for (int j = 0; j < cnt; ++j) {
-      float s = 0.f;
-#pragma unroll
-      for (int c = 0; c < D; ++c) s = __builtin_fmaf(q[c], Ks[j * D + c], s);
-      rescale_to(s);
-      const float p = expf(s - M);
-      msum += p;
-    }
-  }
-  const float log_masked = (msum > 0.f) ? M + logf(msum) : -INFINITY;
-  const bool capped = a.cap_scale > 0.f && g.m > 0;
-  const float log_cap = capped ? logf(a.cap_scale * (float)g.m / ((float)g.n * logf((float)g.n))) + logaddexpf(log_masked, floor_term)
-                               : INFINITY;
-
-  // ---- pass 2: the uniform samples of Algorithm 2 (row-sum estimate) ----
-  for (int j0 = 0; j0 < g.m; j0 += kA2Tile) {
-    const int cnt = min(kA2Tile, g.m - j0);
-    __syncthreads();
-    if (tid < cnt) {
-      rows[tid] = nd.k_start + a.samples[(int64_t)nd.heap * g.m + j0 + tid];
-      bias[tid] = (a.samp_blk[draws + j0 + tid] == t) ? -INFINITY : 0.f;  // factor 1 - M_{i,l_j}
-    }
-    __syncthreads();
-    stage(cnt, false);
-    __syncthreads();
-    for (int j = 0; j < cnt; ++j) {
-      if (bias[j] == -INFINITY) continue;
-      float s = 0.f;
-#pragma unroll
-      for (int c = 0; c < D; ++c) s = __builtin_fmaf(q[c], Ks[j * D + c], s);
-      rescale_to(s);
-      dsum += expf(fminf(s, log_cap) - M);
-    }
-  }
-
-  // ---- pass 3: the value rows drawn by squared norm (Lemma 2), each with its 1 / (m p_l) ----
-  for (int j0 = 0; j0 < g.m; j0 += kA2Tile) {
-    const int cnt = min(kA2Tile, g.m - j0);
-    __syncthreads();
-    if (tid < cnt) {
-      rows[tid] = nd.k_start + a.vsamp[draws + j0 + tid];
-      bias[tid] = a.vlogw[draws + j0 + tid];
-    }
-    __syncthreads();
-    stage(cnt, true);
-    __syncthreads();
-    for (int j = 0; j < cnt; ++j) {
-      float s = bias[j];
-#pragma unroll
-      for (int c = 0; c < D; ++c) s = __builtin_fmaf(q[c], Ks[j * D + c], s);
-      rescale_to(s);
-      const float p = expf(s - M);
-#pragma unroll
-      for (int c = 0; c < D; ++c) o[c] = __builtin_fmaf(p, Vs[j * D + c], o[c]);
-    }
-  }
-
-  const float log_d = (dsum > 0.f) ? M + logf(dsum * ratio) : -INFINITY;
-  const float log_dt = logaddexpf(log_masked, fmaxf(log_d, floor_term));
-  const float f = (M == -INFINITY || log_dt == -INFINITY) ? 0.f : expf(M - log_dt);
-  if (!valid) return;
-  const int64_t orow = hb + (qrow - nd.q_start);
-  a.lse[orow] = log_dt;
-  float* op = reinterpret_cast<float*>(a.out) + orow * D;
-#pragma unroll
-  for (int c = 0; c < D; ++c) op[c] = o[c] * f;
-}
-
 template <typename T>
 static int launch_alg2_t(const Alg2Args& a_in, hipStream_t st) {
   const Geometry& g = a_in.g;
@@ -426,12 +291,7 @@ static int launch_alg2_t(const Alg2Args& a_in, hipStream_t st) {
       }
     }
     hipLaunchKernelGGL(alg2_tau_max_kernel, dim3((unsigned)g.BH), dim3(256), 0, st, a);
-    if (!a.vnorm) return check_launch();  // (the caller's node launch)
-    const int tpb = (g.b + kA2Rows - 1) / kA2Rows;
-    const unsigned grid = (unsigned)((int64_t)g.BH * (g.n / g.b) * tpb);
-    if (g.d == 128) hipLaunchKernelGGL((alg2_main_kernel<128>), dim3(grid), dim3(kA2Rows), 0, st, a);
-    else hipLaunchKernelGGL((alg2_main_kernel<64>), dim3(grid), dim3(kA2Rows), 0, st, a);
-    return check_launch();
+    return check_launch();  // (then the caller's node launch)
   }
 }
 

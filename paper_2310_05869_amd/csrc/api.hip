@@ -1125,12 +1125,14 @@ int hyperattn_forward_alg2(const void* Q, const void* K, const void* V, void* ou
       rc = launch_alg2(a, st);
       if (rc != HA_OK) return rc;
     }
-    if (!opt->vnorm_sampling) {  // with every node's tau known, all nodes in one launch, as in the forward
+    if (!opt->vnorm_sampling || !use_mfma(g)) {  // with every node's tau known, all nodes in one launch, as in the forward
       AttnArgs a = node_args(Q, K, V, out, lse, nullptr, g, base, lay);
       a.log_tau = (const float*)(base + al.log_tau);
       a.cap_scale = opt->cap_scale;
       a.kappa = opt->kappa;
-      rc = run_attention(a, kModeCap, st);
+      a.vsamp = (const int32_t*)(base + al.vnorm_samples);
+      a.vlogw = (const float*)(base + al.vnorm_logw);
+      rc = run_attention(a, opt->vnorm_sampling ? kModeValue : kModeCap, st);
       if (rc != HA_OK) return rc;
     }
   }

@@ -49,8 +49,10 @@ struct F32Lds {
 template <int D>
 __host__ __device__ inline size_t f32_lds_bytes(int b, int m, int mode) {
   const size_t list = mode != kModeExact ? (size_t)(((b + m + 63) & ~63) + 64) * 4 + 64 : 0;
-  const size_t cap = mode == kModeCap ? 4 * 32 * 2 * 4 : 0;  // the waves' masked sums behind the list; a third value per staged row
-  return list + cap > (size_t)F32Lds<D>::BYTES + cap / 2 ? list + cap : (size_t)F32Lds<D>::BYTES + cap / 2;
+  // behind the list: the rows drawn by value norm with their weights, the waves' masked sums; a third value per staged row
+  const size_t cap = mode == kModeCap || mode == kModeValue ? 4 * 32 * 2 * 4 : 0;
+  const size_t drawn = mode == kModeValue ? 2 * (size_t)((m + 63) & ~63) * 4 : 0;
+  return list + drawn + cap > (size_t)F32Lds<D>::BYTES + cap / 2 ? list + drawn + cap : (size_t)F32Lds<D>::BYTES + cap / 2;
 }
 
 // SORT: the sort's tables lie behind the list, the tile's query rows behind all else
@@ -81,7 +83,7 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   constexpr int NW = f32_waves(KW), kFNT = 64 * NW;
   constexpr int kQT = 32 * (NW / KW);
-  constexpr bool kCap = MODE == kModeCap, kNode = MODE == kModeNode || kCap;
+  constexpr bool kValue = MODE == kModeValue, kCap = MODE == kModeCap || kValue, kNode = MODE == kModeNode || kCap;
   constexpr int KJ = D / 8;    // 16-byte pieces of a row per lane
   constexpr int DT = D / 32;
   constexpr int DTA = DT < 2 ? DT : 2;  // V columns are fetched 64 at a time
@@ -116,6 +118,18 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
   // causal: a wave ends with the tile that holds its own last row.  Tiles wholly behind its rows are not only idle work:
   // weight 0 times a V that is Inf or NaN is NaN.
   if (MODE == kModeExact && a.exact_causal) ntiles = min(ntiles, (w.q0 - w.k0) / kFKT + wave / KW + 1);
+  // value mode: the rows drawn by value norm, all m of them for every block, follow in tiles of their own
+  const int vt0 = ntiles, drawn_at = (((a.g.b + a.g.m + 63) & ~63) + 64) + ((a.g.m + 63) & ~63);
+  float* drawn_w = reinterpret_cast<float*>(list + drawn_at);  // -log(m p); -inf past the end
+  if constexpr (kValue) {
+    const int64_t draws = ((int64_t)w.bh * a.g.total_nodes + w.nr.heap) * a.g.m;
+    for (int j = tid; j < ((a.g.m + 31) & ~31); j += kFNT) {
+      list[vt0 * kFKT + j] = w.nr.k_start + a.vsamp[draws + min(j, a.g.m - 1)];
+      drawn_w[j] = j < a.g.m ? a.vlogw[draws + j] : -INFINITY;
+    }
+    ntiles += (a.g.m + 31) / kFKT;
+    __syncthreads();
+  }
   const float nat_bias = (kNode && a.g.m > 0) ? logf((float)w.nr.s / (float)a.g.m) : 0.f;
 
   const float* Qh = reinterpret_cast<const float*>(a.Q) + (int64_t)w.bh * a.q_bh_stride;
@@ -186,13 +200,16 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
   // counts at most C_i in the row sum, whose cap follows from the masked sum of all waves of the row.  One thread per query row
   // had walked both parts before: whole calls with the launch for tau of that time 950 -> 98 us (2 heads, n = 4096, d = 128, b = m = 64;
   // this launch 23), 4 heads, n = 2048, b = m = 256 1590 -> 149 (44), 8 heads, n = 1024, d = 64, b = m = 256 609 -> 72 (21).
+  // Value mode (Lemma 2's rows carry the output): block and samples only sum, the drawn rows, with their log weights, only
+  // add to the output.  One thread per query row before: 4 heads, n = 2048, d = 128, b = m = 256 1287 -> 88 us; 8 heads, n = 1024, d = 64
+  // 551 -> 60; 2 heads, n = 4096, d = 128, b = 512, m = 1000 3871 -> 203.
   // The switch to the samples sits in the one loop: a loop per part, shared with the other modes, cost those up to 4 %.
   const int nbt = kCap ? ((nb + 63) & ~63) / kFKT : 0;
   float msum = 0.f, log_capw = INFINITY;  // log of (s / m) C_i
   const float floor_term = kCap && a.kappa > 0.f ? a.log_tau[(int64_t)w.bh * a.g.total_nodes + w.nr.heap] - logf(a.kappa) : -INFINITY;
   bool sampled = false;
   auto to_samples = [&]() {  // every wave comes here once
-    float* ex = reinterpret_cast<float*>(list + ((a.g.b + a.g.m + 63) & ~63) + 64);  // [4 waves][32][2], behind the list
+    float* ex = reinterpret_cast<float*>(list + (kValue ? drawn_at + ((a.g.m + 63) & ~63) : ((a.g.b + a.g.m + 63) & ~63) + 64));  // [4 waves][32][2]
     const float mine = l_run + __shfl_xor(l_run, 32);
     if (h == 0) {
       ex[(wave * 32 + lq) * 2] = m_run;
@@ -219,13 +236,13 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
   if (kw < ntiles) load_k(kw);
   for (int kt = kw; kt < ntiles; kt += KW) {
     float va[16][DTA];
-    if constexpr (DT == 2) load_v(kt, 0, va);
+    if constexpr (DT == 2 && !kValue) load_v(kt, 0, va);
     f32x16 c;
 #pragma unroll
     for (int i = 0; i < 16; ++i) c[i] = 0.f;
 #pragma unroll
     for (int j = 0; j < KJ; ++j) {
-      if (DT > 2 && j == KJ / 2) {  // d = 128: V takes the registers of the K pieces already multiplied
+      if (DT > 2 && !kValue && j == KJ / 2) {  // d = 128: V takes the registers of the K pieces already multiplied
         __builtin_amdgcn_sched_barrier(0);
         load_v(kt, 0, va);
       }
@@ -237,7 +254,14 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
     if constexpr (kCap) {
       if (kt >= nbt && !sampled) to_samples();
       const int lim = sampled ? nkeys : nb;
-      if (sampled || base + kFKT > lim) {
+      if (kValue && kt >= vt0) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const f32x4 lw = *reinterpret_cast<const f32x4*>(drawn_w + (kt - vt0) * kFKT + 8 * g + 4 * h);
+#pragma unroll
+          for (int z = 0; z < 4; ++z) c[4 * g + z] = lw[z] == -INFINITY ? -INFINITY : c[4 * g + z] + lw[z];
+        }
+      } else if (sampled || base + kFKT > lim) {
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
           const int pos = base + 8 * (i / 4) + 4 * h + (i % 4);
@@ -278,12 +302,27 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       c[i] = exp_split(c[i] - m_use);
-      l_run += kCap ? fminf(c[i], capw) : c[i];
+      if (!kValue || kt < vt0) l_run += kCap ? fminf(c[i], capw) : c[i];
     }
     if constexpr (DT == 2) {
       if (kt + KW < ntiles) load_k(kt + KW);
     }
     float vb[16][DTA];
+    if constexpr (kValue) {  // V behind the sums, 64 columns at a time (fetched amid the products, under a branch: 168 spills at d = 128)
+      if (DT > 2 && kt + KW < ntiles) load_k(kt + KW);
+      if (kt < vt0) continue;
+#pragma unroll
+      for (int dt0 = 0; dt0 < DT; dt0 += 2) {
+        load_v(kt, dt0, va);
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+#pragma unroll
+          for (int dt = 0; dt < DTA; ++dt)
+            o[dt0 + dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(va[i][dt], c[i], o[dt0 + dt], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      continue;
+    }
     if constexpr (DT > 2) load_v(kt, 2, vb);
 #pragma unroll
     for (int i = 0; i < 16; ++i)
@@ -458,6 +497,7 @@ int launch_attn_f32(const AttnArgs& a, int mode, hipStream_t st) {
   if (a.g.d != 64 && a.g.d != 128) return HA_ERR_SHAPE;
   if (mode == kModeNode) return a.g.d == 128 ? launch_f32_mode<128, kModeNode>(a, st) : launch_f32_mode<64, kModeNode>(a, st);
   if (mode == kModeCap) return a.g.d == 128 ? launch_f32_mode<128, kModeCap>(a, st) : launch_f32_mode<64, kModeCap>(a, st);
+  if (mode == kModeValue) return a.g.d == 128 ? launch_f32_mode<128, kModeValue>(a, st) : launch_f32_mode<64, kModeValue>(a, st);
   if (mode == kModeExact) return a.g.d == 128 ? launch_f32_mode<128, kModeExact>(a, st) : launch_f32_mode<64, kModeExact>(a, st);
   return HA_ERR_SHAPE;
 }

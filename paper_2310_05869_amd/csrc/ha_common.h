@@ -79,7 +79,8 @@ __host__ __device__ inline NodeRef node_ref(const Geometry& g, int level, int no
 enum AttnMode : int32_t {
   kModeNode = 0,   // unmasked node(s): block keys by list + kept sampled keys
   kModeExact = 1,  // contiguous keys, optional causal mask (exact attention / causal base case)
-  kModeCap = 2,    // node mode with Algorithm 2's cap on every sampled entry and its lower cap (bf16)
+  kModeCap = 2,    // node mode with Algorithm 2's cap on every sampled entry and its lower cap
+  kModeValue = 3,  // cap mode for the row sums, Lemma 2's rows for the output (fp32)
 };
 
 // Division of 0 <= n < 2^31 by a divisor known on the host: two scalar multiplications and a shift, where
@@ -138,6 +139,9 @@ struct AttnArgs {
   // cap mode: log tau of every node [BH][total_nodes], the constant of C_i and kappa (<= 0: that cap is off)
   const float* log_tau;
   float cap_scale, kappa;
+  // value mode: every node's rows drawn by value norm and their log weights, [BH][total_nodes][m]
+  const int32_t* vsamp;
+  const float* vlogw;
   // exact mode
   int32_t exact_rows_q, exact_rows_k;  // rows per head (full problem)
   int32_t exact_block;                 // rows per independent diagonal block (== rows for full attention)

@@ -184,6 +184,7 @@ def test_alg2_caps_in_the_node_kernel(ha, torch, dtype, d, n, b, m, r, cap_scale
     test_alg2_options_match_the_oracle(ha, torch, dtype, d, n, b, m, r, cap_scale, kappa, vnorm)
 
 
+@pytest.mark.parametrize("vnorm", [False, True])
 @pytest.mark.parametrize("d,H,n,b,m,r,cap_scale,kappa", [
     (64, 2, 300, 100, 130, 4, 6.0, 1.3),     # four waves per row; padded tail of a block, samples from its next tile on
     (128, 2, 256, 256, 40, 5, 0.0, 0.0),     # one block: no sample is kept, every row of T sums nothing
@@ -194,18 +195,19 @@ def test_alg2_caps_in_the_node_kernel(ha, torch, dtype, d, n, b, m, r, cap_scale
     (64, 80, 896, 128, 31, 5, 6.0, 1.3),     # one wave per row
     (128, 80, 700, 100, 0, 5, 0.0, 0.0),     # one wave per row, no samples
     (64, 80, 700, 100, 65, 5, 0.0, 1.4)])    # lower cap alone
-def test_alg2_fp32_caps_in_the_node_kernel(ha, torch, d, H, n, b, m, r, cap_scale, kappa):
-    """The fp32 forward kernel's cap mode and the sums of the rows of T at the edges of its tiles and for each number of waves that share a row; the first and
-    the last head (heads share the draws) against the oracle: criteria as above."""
-    print(f"alg2 fp32 d={d} H={H} n={n} b={b} m={m} r={r} cap={cap_scale} kappa={kappa}", flush=True)
+def test_alg2_fp32_caps_in_the_node_kernel(ha, torch, d, H, n, b, m, r, cap_scale, kappa, vnorm):
+    """The fp32 forward kernel's cap and value modes and the sums of the rows of T at the edges of their tiles and for each number of
+    waves that share a row; two heads (all share the draws, but the first two Lemma 2's of such a call) against the oracle:
+    criteria as above."""
+    print(f"alg2 fp32 d={d} H={H} n={n} b={b} m={m} r={r} cap={cap_scale} kappa={kappa} vnorm={vnorm}", flush=True)
     Q, K, V = (x.astype(np.float32) for x in synth_inputs.make_qkv(dict(B=1, H=H, n=n, d=d, dtype="fp32", law="iid"), seed=n))
     out, lse, ws = ha.hyperattn_forward_alg2(*(to_device(x, "fp32") for x in (Q, K, V)), b, m, r, seed=5, cap_scale=cap_scale,
-                                             kappa=kappa)
+                                             kappa=kappa, vnorm_sampling=vnorm)
     torch.cuda.synchronize()
     views = ha.alg2_workspace_views(ws, ha.make_shape(1, H, n, d, ha.HA_FP32), ha.make_params(b, m, r, False, 4096, 5))
-    ends = [0, H - 1]
+    ends = [0, 1 if vnorm else H - 1]
     ref_out, ref_lse, ref_tau = orc.hyperattn_forward_alg2(Q[:, ends], K[:, ends], V[:, ends], b=b, m=m, r=r, seed=5,
-                                                     cap_scale=cap_scale, kappa=kappa)
+                                                           cap_scale=cap_scale, kappa=kappa, vnorm_sampling=vnorm)
     np.testing.assert_allclose(views["log_tau"][ends, 0].cpu().numpy(), ref_tau, rtol=2e-5, atol=2e-5)
     np.testing.assert_allclose(to_host(lse)[:, ends], ref_lse, rtol=3e-5, atol=3e-5)
     assert_close(to_host(out)[:, ends], ref_out, "fp32", "out")

@@ -147,7 +147,8 @@ int hyperattn_forward_ex(const void* Q, const void* K, const void* V, void* out,
                          const float* R_dev, const int32_t* samples_dev,
                          void* workspace, size_t workspace_bytes, void* stream);
 
-/* Measurement variant of hyperattn_forward (same computation, same launches):
+/* Measurement variant of hyperattn_forward (same computation and results; the sort is always a launch of
+ * its own, where hyperattn_forward lets the attention launch of a small problem sort):
  * HIP events are recorded on `stream` between the stages, the call WAITS for the
  * last one, and stage_ms_host[0..5] (host memory) receive the elapsed
  * milliseconds of: [0] always 0 (the random draws, once a launch of their own, are

@@ -574,8 +574,8 @@ static int backward_impl(const void* Q, const void* K, const void* V, const void
       if (rc != HA_OK) return rc;
     }
     mark(4);
-    for (int l = 0; has_samp && l < g.levels; ++l) {
-      rc = launch_bwd_sample_scatter(a, l, samp_k, samp_v, (float*)dK, (float*)dV, st);
+    if (has_samp) {
+      rc = launch_bwd_sample_scatter(a, samp_k, samp_v, (float*)dK, (float*)dV, st);
       if (rc != HA_OK) return rc;
     }
     mark(5);
@@ -603,10 +603,8 @@ static int backward_impl(const void* Q, const void* K, const void* V, const void
     a.out2 = samp_v;
     rc = launch_attn_bwd(a, kBwdDkvSamp, st);
     if (rc != HA_OK) return rc;
-    for (int l = 0; l < g.levels; ++l) {
-      rc = launch_bwd_sample_scatter(a, l, samp_k, samp_v, acc_a, acc_b, st);
-      if (rc != HA_OK) return rc;
-    }
+    rc = launch_bwd_sample_scatter(a, samp_k, samp_v, acc_a, acc_b, st);
+    if (rc != HA_OK) return rc;
   }
   mark(5);
   a.fin1 = dK;

@@ -90,92 +90,138 @@ int launch_bwd_delta(const void* O, const float* O_f32, const void* dO, float* d
   return check_launch();
 }
 
-// Sampled keys' gradients of one level into the accumulated key rows.  One wave per sample j
-// of a (head, node of the level); a lane owns four columns of dK (lanes < d/4) or of dV (the
-// next d/4 lanes).  A key may be drawn more than once: the FIRST sample that
-// drew a key ("owner") adds, in increasing sample order, the sums of every
-// sample of that key, each taken over the node's query chunks in a fixed order;
+// Sampled keys' gradients of levels [level0, level1) into the accumulated key rows.  One wave per sample j
+// of a (head, node); a lane owns four columns of dK (lanes < d/4) or of dV (the
+// next d/4 lanes).  A key may be drawn more than once, by its node and by the nodes of the other levels that hold it: the
+// FIRST sample that drew a key ("owner": lowest level, then lowest sample) adds, level by level and in increasing sample
+// order, the sums of every sample of that key, each taken over the node's query chunks in a fixed order;
 // the other samples of the key do nothing.  One writer per row and a fixed
 // order of additions: reproducible bit for bit.
+//
+// All levels go in one launch where it is small, else level by level: a launch is 5 us of a small problem, whose upper
+// levels have a few workgroups that wait for their chunks, but a wave then looks through the samples of every level's node.
+// Forward + backward, a launch per level -> one (MI355X, us; workgroups of the one): fp32, m = 64: 4 heads, n = 4096, two levels (192)
+// 214.5 -> 211.8; 1 head, n = 8192, three (112) 183.0 -> 176.4; 3 heads, n = 1024, two (144) 90.0 -> 87.3; bf16, m = 256: 1 head, n = 16384,
+// d = 64, five (1984) 222.6 -> 208.0; 4 heads, two (768) 332 -> 329; 8 heads, n = 8192, d = 128, three (3584) 409 -> 405; 32 heads, n = 32768, three (14336)
+// 7967 -> 7987; n = 131072, five (63488) 39250 -> 39440; m = 1000, 4 heads, n = 16384, four (15000) 559 -> 578.
+constexpr int kScatterOneLaunchSamples = 256;
+constexpr int64_t kScatterOneLaunchGrid = 4096;
 constexpr int kScatterWaves = 4;
 
-__global__ __launch_bounds__(64 * kScatterWaves) void bwd_sample_scatter_kernel(BwdArgs a, int level,
+// LEVELS: several; else one, whose samples the waves look through in LDS.
+template <bool LEVELS>
+__global__ __launch_bounds__(64 * kScatterWaves) void bwd_sample_scatter_kernel(BwdArgs a, int level0, int level1, int hn_first,
                                                                                 const float* __restrict__ samp_k,
                                                                                 const float* __restrict__ samp_v,
                                                                                 float* part_k, float* part_v) {
-  __shared__ int32_t keys[4096];
   const Geometry& g = a.f.g;
   const int d = g.d, m = g.m;
   const int groups = (m + kScatterWaves - 1) / kScatterWaves;
-  const int grp = blockIdx.x % groups;
-  const int rest = blockIdx.x / groups;
-  const int nodes = g.causal ? (1 << level) : 1;
-  const int bh = rest / nodes;
-  const int node = rest % nodes;
-  const int heap = (1 << level) - 1 + node;
-  const NodeRef nr = node_ref(g, level, node);
-  const int cpn = bwd_chunks_per_node(g, a.chunk, level);
-  const int64_t key_row0 = (int64_t)bh * g.n + nr.k_start;  // the node's first key in the accumulated rows
-  int64_t lvl_row0 = 0;  // rows of the levels before
-  for (int l = 0; l < level; ++l) lvl_row0 += (int64_t)g.BH * (g.causal ? (1 << l) : 1) * bwd_chunks_per_node(g, a.chunk, l) * m;
-  const int64_t row0 = lvl_row0 + ((int64_t)bh * nodes + node) * cpn * m;
-
-  for (int j = threadIdx.x; j < m; j += blockDim.x) keys[j] = a.f.samples[(int64_t)heap * m + j];
-  __syncthreads();
+  const int grp = (int)blockIdx.x % groups;
+  const int hn = hn_first + (int)blockIdx.x / groups;
+  const int heap = (1 << level0) - 1 + hn / g.BH, bh = hn % g.BH;  // the upper levels, of more chunks, first
+  const int level = 31 - __builtin_clz(heap + 1);
+  const NodeRef nr = node_ref(g, level, heap + 1 - (1 << level));
   const int lane = threadIdx.x & 63;
-  const int j = grp * kScatterWaves + (threadIdx.x >> 6);
-  if (j >= m) return;
-  const int key = keys[j];
-  // an earlier sample of the same key owns it
-  for (int base = 0; base < j; base += 64) {
-    const int jj = base + lane;
-    if (__any(jj < j && keys[jj] == key)) return;
+  const int j = grp * kScatterWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  __shared__ int32_t keys[LEVELS ? 1 : 4096];
+  if constexpr (!LEVELS) {
+    for (int i = threadIdx.x; i < m; i += blockDim.x) keys[i] = a.f.samples[(int64_t)heap * m + i];
+    __syncthreads();
   }
+  if (j >= m) return;
+  auto drawn_by = [&](const NodeRef& o, int i) {
+    if constexpr (LEVELS) return a.f.samples[(int64_t)o.heap * m + i];
+    else return keys[i];
+  };
+  const int row = nr.k_start + drawn_by(nr, j);  // within the head
+
+  // the level's node that holds the row among its keys, if one does
+  auto holder = [&](int l, NodeRef* out) {
+    *out = node_ref(g, l, row / (g.n >> l));
+    return row - out->k_start < out->s;
+  };
+  // whether one of a node's samples [0, end) is the row; several loads in flight
+  auto drawn_in = [&](const NodeRef& o, int end) {
+    const int key = row - o.k_start;
+    bool hit = false;
+#pragma unroll 4
+    for (int base = 0; base < end; base += 64) hit |= base + lane < end && drawn_by(o, min(base + lane, m - 1)) == key;
+    return __any(hit);
+  };
+  // an earlier sample of the same key owns it
+  for (int l = level0; l <= level; ++l) {
+    NodeRef o;
+    if (holder(l, &o) && drawn_in(o, l < level ? m : j)) return;
+  }
+
   const int q4 = d / 4;  // column quads per row
   const bool active = lane < 2 * q4;
   const float* src = lane < q4 ? samp_k : samp_v;
-  float* dst = lane < q4 ? part_k : part_v;
   const int c4 = (lane % q4) * 4;
-  f32x4 total = {0.f, 0.f, 0.f, 0.f};
-  for (int base = j; base < m; base += 64) {
-    const int jl = base + lane;
-    unsigned long long same = __ballot(jl < m && keys[jl] == key);
-    while (same) {
-      const int jj = base + __builtin_ctzll(same);
-      same &= same - 1;
-      if (active) {
-        const float* p = src + (row0 + jj) * d + c4;
-        const int64_t step = (int64_t)m * d;
-        f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0, s2 = s0, s3 = s0;
-        int qc = 0;
-        for (; qc + 4 <= cpn; qc += 4) {
-          s0 += *reinterpret_cast<const f32x4*>(p + (qc + 0) * step);
-          s1 += *reinterpret_cast<const f32x4*>(p + (qc + 1) * step);
-          s2 += *reinterpret_cast<const f32x4*>(p + (qc + 2) * step);
-          s3 += *reinterpret_cast<const f32x4*>(p + (qc + 3) * step);
+  f32x4* out = reinterpret_cast<f32x4*>((lane < q4 ? part_k : part_v) + ((int64_t)bh * g.n + row) * d + c4);
+  f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+  if (active) sum = *out;
+  int64_t lvl_row0 = 0;  // rows of the levels before
+  for (int l = 0; l < level1; ++l) {
+    const int cpn = bwd_chunks_per_node(g, a.chunk, l), nodes = 1 << l;
+    NodeRef o;
+    if (l >= level && holder(l, &o)) {
+      const int key = row - o.k_start;
+      const int64_t row0 = lvl_row0 + ((int64_t)bh * nodes + (o.heap + 1 - nodes)) * cpn * m;
+      f32x4 total = {0.f, 0.f, 0.f, 0.f};
+      for (int base = l == level ? j : 0; base < m; base += 64) {
+        const int jl = base + lane;
+        unsigned long long same = __ballot(jl < m && drawn_by(o, min(jl, m - 1)) == key);
+        while (same) {
+          const int jj = base + __builtin_ctzll(same);
+          same &= same - 1;
+          if (active) {
+            const float* p = src + (row0 + jj) * d + c4;
+            const int64_t step = (int64_t)m * d;
+            f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0, s2 = s0, s3 = s0;
+            int qc = 0;
+            for (; qc + 4 <= cpn; qc += 4) {
+              s0 += *reinterpret_cast<const f32x4*>(p + (qc + 0) * step);
+              s1 += *reinterpret_cast<const f32x4*>(p + (qc + 1) * step);
+              s2 += *reinterpret_cast<const f32x4*>(p + (qc + 2) * step);
+              s3 += *reinterpret_cast<const f32x4*>(p + (qc + 3) * step);
+            }
+            for (; qc < cpn; ++qc) s0 += *reinterpret_cast<const f32x4*>(p + qc * step);
+            total += (s0 + s1) + (s2 + s3);
+          }
         }
-        for (; qc < cpn; ++qc) s0 += *reinterpret_cast<const f32x4*>(p + qc * step);
-        total += (s0 + s1) + (s2 + s3);
       }
+      sum += total;
     }
+    lvl_row0 += (int64_t)g.BH * nodes * cpn * m;
   }
-  if (active) {
-    f32x4* out = reinterpret_cast<f32x4*>(dst + (key_row0 + key) * d + c4);
-    *out = *out + total;
-  }
+  if (active) *out = sum;
 }
 
-int launch_bwd_sample_scatter(const BwdArgs& a, int level, const float* samp_k, const float* samp_v, float* acc_k,
-                              float* acc_v, hipStream_t st) {
+int launch_bwd_sample_scatter(const BwdArgs& a, const float* samp_k, const float* samp_v, float* acc_k, float* acc_v, hipStream_t st) {
   const Geometry& g = a.f.g;
-  if (g.m <= 0 || level < 0 || level >= g.levels) return HA_OK;
-  const int nodes = g.causal ? (1 << level) : 1;
+  if (g.m <= 0 || g.levels <= 0) return HA_OK;
   const int groups = (g.m + kScatterWaves - 1) / kScatterWaves;
-  const int64_t grid = (int64_t)g.BH * nodes * groups;
-  if (grid > kMaxGrid) return HA_ERR_SHAPE;
-  hipLaunchKernelGGL(bwd_sample_scatter_kernel, dim3((unsigned)grid), dim3(64 * kScatterWaves), 0, st, a, level, samp_k,
-                     samp_v, acc_k, acc_v);
-  return check_launch();
+  if ((int64_t)g.BH * (1 << (g.levels - 1)) * groups > kMaxGrid) return HA_ERR_SHAPE;
+  const bool one_launch = g.m <= kScatterOneLaunchSamples && (int64_t)g.BH * g.total_nodes * groups <= kScatterOneLaunchGrid;
+  const int step = one_launch ? g.levels : 1;
+  const int64_t most = kMaxLaunch / groups;  // (heads, nodes) per launch; groups <= 1024
+  for (int l = 0; l < g.levels; l += step) {
+    const int64_t nodes = (int64_t)g.BH * ((1 << (l + step)) - (1 << l));
+    for (int64_t first = 0; first < nodes; first += most) {
+      const unsigned count = (unsigned)((nodes - first < most ? nodes - first : most) * groups);
+      if (step > 1)
+        hipLaunchKernelGGL((bwd_sample_scatter_kernel<true>), dim3(count), dim3(64 * kScatterWaves), 0, st, a, l, l + step, (int)first, samp_k,
+                           samp_v, acc_k, acc_v);
+      else
+        hipLaunchKernelGGL((bwd_sample_scatter_kernel<false>), dim3(count), dim3(64 * kScatterWaves), 0, st, a, l, l + step, (int)first, samp_k,
+                           samp_v, acc_k, acc_v);
+      const int rc = check_launch();
+      if (rc != HA_OK) return rc;
+    }
+  }
+  return HA_OK;
 }
 
 // Unmasked problems, whose block-key pass adds the sampled sums itself: the rows of the sampled-key pass summed over the

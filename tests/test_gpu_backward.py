@@ -171,6 +171,19 @@ def test_backward_fp32(ha, torch, d, n, b, m, causal, n_min):
     _run_case(ha, torch, cfg)
 
 
+# keys drawn by nodes of several levels, several times each: more samples than keys, samples past a wave's 64, one level
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("d,n,n_min,b,m", [(64, 256, 16, 8, 70), (128, 320, 40, 20, 33), (64, 1024, 512, 64, 1000), (128, 192, 24, 24, 3)])
+def test_backward_causal_sampled_keys(ha, torch, d, n, n_min, b, m, dtype):
+    print(f"backward causal sampled keys {dtype} d={d} n={n} n_min={n_min} b={b} m={m}", flush=True)
+    cfg = dict(B=1, H=3, n=n, d=d, dtype=dtype, law="iid", b=b, m=m, r=5, causal=1, n_min=n_min, seed=4)
+    grads, (q, k, v, out, lse, g, ws, out32) = _run_case(ha, torch, cfg)
+    again = ha.hyperattn_backward(q, k, v, out, lse, g, b, m, 5, fwd_workspace=ws, out_f32=out32, causal=1, n_min=n_min, seed=4)
+    torch.cuda.synchronize()
+    for x, y in zip(grads, again):
+        assert torch.equal(x, y)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "fp32"])
 @pytest.mark.parametrize("d,n,causal", [(128, 300, False), (128, 300, True), (64, 1000, True), (64, 257, False)])
 def test_exact_attn_backward(ha, torch, d, n, causal, dtype):

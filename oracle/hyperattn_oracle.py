@@ -569,6 +569,17 @@ def vnorm_samples(Vh, seed: int, bh: int, m: int, replay=None, margin=None, heap
     return idx, logw
 
 
+def _log_row_sums(X) -> np.ndarray:
+    """log sum_j exp(X_ij), every row against its own maximum: the scores of one head can lie further apart (clustered inputs)
+    than the exponents of a double."""
+    if X.shape[1] == 0:
+        return np.full(X.shape[0], -np.inf)
+    ref = X.max(axis=1)
+    ref = np.where(np.isneginf(ref), 0.0, ref)
+    with np.errstate(divide="ignore"):
+        return np.log(np.exp(X - ref[:, None]).sum(axis=1)) + ref
+
+
 def alg2_head_forward(Qh, Kh, Vh, codes_q, codes_k, b, samples, t_rows, cap_scale, kappa, vsamp=None):
     """One head.  Returns (out, log d~, log tau).  vsamp = (indices, log weights) selects
     Algorithm 3's value product D~^-1 A S^T S V; None keeps Section 4's numerator (masked
@@ -581,9 +592,8 @@ def alg2_head_forward(Qh, Kh, Vh, codes_q, codes_k, b, samples, t_rows, cap_scal
     blk_k = pos_k // b
     S = Qh @ Kh.T                                                    # dense: small n only
     Mh = blk_q[:, None] == blk_k[None, :]                            # M^H
-    with np.errstate(divide="ignore"):
-        log_masked = np.log(np.where(Mh, np.exp(S - S.max()), 0.0).sum(axis=1)) + S.max()
-        log_unmasked = np.log(np.where(Mh, 0.0, np.exp(S - S.max())).sum(axis=1)) + S.max()
+    log_masked = _log_row_sums(np.where(Mh, S, -np.inf))
+    log_unmasked = _log_row_sums(np.where(Mh, -np.inf, S))
     log_tau = log_unmasked[t_rows].max() if len(t_rows) else -np.inf            # line "tau <- max_{j in T}"
     floor_term = log_tau - math.log(kappa) if kappa > 0 else -np.inf            # tau / kappa
     samples = np.asarray(samples, dtype=np.int64)
@@ -594,10 +604,7 @@ def alg2_head_forward(Qh, Kh, Vh, codes_q, codes_k, b, samples, t_rows, cap_scal
         Sc = np.minimum(Ss, log_cap[:, None])
     else:
         Sc = Ss
-    with np.errstate(divide="ignore"):
-        ref = max(float(S.max()), 0.0)
-        d_i = np.where(keep, np.exp(Sc - ref), 0.0).sum(axis=1) * (n / m if m else 0.0)
-        log_d = np.log(d_i) + ref                                                # line "d_i <- (n/m) sum ..."
+    log_d = _log_row_sums(np.where(keep, Sc, -np.inf)) + (math.log(n / m) if m else 0.0)   # line "d_i <- (n/m) sum ..."
     log_dt = np.logaddexp(log_masked, np.maximum(log_d, floor_term))             # line "d~_i <- ... + max(d_i, tau/kappa)"
     if vsamp is not None:
         vi, vlogw = vsamp

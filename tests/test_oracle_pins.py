@@ -565,6 +565,23 @@ def test_alg2_tau_cap_and_lower_cap_follow_their_definitions():
     assert (np.maximum(d_plain, tau / kappa) > d_plain).any()      # the lower cap binds somewhere in this instance
 
 
+def test_alg2_row_sums_keep_a_scale_of_their_own():
+    """Scores 2000 apart within one head, beyond the exponents of a double: every row sum against its own largest term."""
+    n, b = 8, 4
+    Q = np.repeat(np.array([[1.0], [2.0]]), 4, axis=0)
+    K = np.repeat(np.array([[-1000.0], [3.0]]), 4, axis=0)
+    V = np.ones((n, 1))
+    codes = np.repeat([0, 1], 4)
+    _, log_dt, log_tau = orc.alg2_head_forward(Q, K, V, codes, codes, b, [4, 4, 0, 0], [4], 0.0, 0.0)
+    # rows of block 0: four keys at -1000, key 4 kept twice with weight n / m = 2 at 3; of block 1: four at 6, key 0 at -2000
+    np.testing.assert_allclose(log_dt, [3 + math.log(4.0)] * 4 + [6 + math.log(4.0)] * 4, rtol=1e-14)
+    np.testing.assert_allclose(log_tau, -2000 + math.log(4.0), rtol=1e-14)
+    with np.errstate(over="ignore"):
+        log_dt = orc.alg2_head_forward(Q, K, V, codes, codes, b, [4, 4, 0, 0], [4], 0.5, 0.0)[1]
+    cap = 0.5 * 4 / (8 * math.log(8.0)) * 4.0          # C_i e^1000 of rows of block 0, below both kept samples
+    np.testing.assert_allclose(log_dt[:4], -1000 + math.log(4.0 + 2 * 2 * cap), rtol=1e-14)
+
+
 def test_causal_alg2_is_algorithm4_over_algorithm2():
     """Causal problems: with the caps off the result is the Section 4 causal forward (dense per-node
     evaluation here, part by part there); at n <= n_min it is exact causal attention; the row sum of a

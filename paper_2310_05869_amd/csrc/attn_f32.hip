@@ -49,10 +49,10 @@ struct F32Lds {
 template <int D>
 __host__ __device__ inline size_t f32_lds_bytes(int b, int m, int mode) {
   const size_t list = mode != kModeExact ? (size_t)(((b + m + 63) & ~63) + 64) * 4 + 64 : 0;
-  // behind the list: the rows drawn by value norm with their weights, the waves' masked sums; a third value per staged row
+  // behind the list: the rows drawn by value norm with their weights, the waves' masked sums; two more values per staged row
   const size_t cap = mode == kModeCap || mode == kModeValue ? 4 * 32 * 2 * 4 : 0;
   const size_t drawn = mode == kModeValue ? 2 * (size_t)((m + 63) & ~63) * 4 : 0;
-  return list + drawn + cap > (size_t)F32Lds<D>::BYTES + cap / 2 ? list + drawn + cap : (size_t)F32Lds<D>::BYTES + cap / 2;
+  return list + drawn + cap > (size_t)F32Lds<D>::BYTES + cap ? list + drawn + cap : (size_t)F32Lds<D>::BYTES + cap;
 }
 
 // SORT: the sort's tables lie behind the list, the tile's query rows behind all else
@@ -199,15 +199,26 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
   // Cap mode (Algorithm 2 as printed): the block's keys, padded to whole tiles, come first; then every sample's weight
   // counts at most C_i in the row sum, whose cap follows from the masked sum of all waves of the row.  One thread per query row
   // had walked both parts before: whole calls with the launch for tau of that time 950 -> 98 us (2 heads, n = 4096, d = 128, b = m = 64;
-  // this launch 23), 4 heads, n = 2048, b = m = 256 1590 -> 149 (44), 8 heads, n = 1024, d = 64, b = m = 256 609 -> 72 (21).
+  // this launch 23), 4 heads, n = 2048, b = m = 256 1590 -> 149 (44), 8 heads, n = 1024, d = 64, b = m = 256 609 -> 72 (21); with the sums of
+  // alg2_tau_kernel as they are 62, 73 and 46.
   // Value mode (Lemma 2's rows carry the output): block and samples only sum, the drawn rows, with their log weights, only
   // add to the output.  One thread per query row before: 4 heads, n = 2048, d = 128, b = m = 256 1287 -> 88 us; 8 heads, n = 1024, d = 64
-  // 551 -> 60; 2 heads, n = 4096, d = 128, b = 512, m = 1000 3871 -> 203.
+  // 551 -> 60; 2 heads, n = 4096, d = 128, b = 512, m = 1000 3871 -> 203 (the first two now 84 and 58).
   // The switch to the samples sits in the one loop: a loop per part, shared with the other modes, cost those up to 4 %.
+  // Scores of one row can lie hundreds apart, so no sum may hang on another's reference: the masked sum is final, as a logarithm,
+  // before the first sample counts.  The samples' sum (l_run) is taken against sum_ref: the output's reference m_run, or the cap
+  // where that is far below, since no capped term exceeds it.  Value mode, whose output has no part in the samples, begins each
+  // part with a reference of its own and keeps the samples' in d_ref.  (With all sums on m_run, rows of clustered inputs lost
+  // log d~ to underflow: 150 of 2048, d = 64, b = m = 64, cap 8.  Time: 32 heads, n = 8192, b = m = 256, d = 64 590 -> 578 us, d = 128 1134 ->
+  // 1122, with value sampling 1214 -> 1210, 4 heads, n = 2048 82.3 -> 83.7.)
   const int nbt = kCap ? ((nb + 63) & ~63) / kFKT : 0;
-  float msum = 0.f, log_capw = INFINITY;  // log of (s / m) C_i
+  float log_masked = -INFINITY, log_capw = INFINITY;  // log of the row's masked sum, of (s / m) C_i
+  float d_ref = -INFINITY;
+  constexpr float kFarCap = 40.f;  // a term that underflows against m_run is then e^-47 of the cap or less
+  auto sum_ref = [&](float m) { return kCap && !kValue && m > log_capw + kFarCap ? log_capw : m; };
+  auto finite_ref = [](float m) { return m == -INFINITY ? 0.f : m; };
   const float floor_term = kCap && a.kappa > 0.f ? a.log_tau[(int64_t)w.bh * a.g.total_nodes + w.nr.heap] - logf(a.kappa) : -INFINITY;
-  bool sampled = false;
+  bool sampled = false, drawn = false;
   auto to_samples = [&]() {  // every wave comes here once
     float* ex = reinterpret_cast<float*>(list + (kValue ? drawn_at + ((a.g.m + 63) & ~63) : ((a.g.b + a.g.m + 63) & ~63) + 64));  // [4 waves][32][2]
     const float mine = l_run + __shfl_xor(l_run, 32);
@@ -224,13 +235,13 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
       const float* e = ex + ((wave / KW * KW + k) * 32 + lq) * 2;
       sum += e[1] * (top == -INFINITY ? 0.f : expf(e[0] - top));
     }
-    const float log_masked = sum > 0.f ? add_log(top, sum) : -INFINITY;
+    log_masked = sum > 0.f ? add_log(top, sum) : -INFINITY;
     if (a.cap_scale > 0.f) {
       const float n = (float)w.nr.s;
       log_capw = logf(a.cap_scale * (float)a.g.m / (n * logf(n))) + logaddexpf(log_masked, floor_term) + nat_bias;
     }
-    msum = l_run;
     l_run = 0.f;
+    if (kValue) m_run = -INFINITY;
     sampled = true;
   };
   if (kw < ntiles) load_k(kw);
@@ -255,6 +266,11 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
       if (kt >= nbt && !sampled) to_samples();
       const int lim = sampled ? nkeys : nb;
       if (kValue && kt >= vt0) {
+        if (!drawn) {
+          d_ref = m_run;
+          m_run = -INFINITY;
+          drawn = true;
+        }
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const f32x4 lw = *reinterpret_cast<const f32x4*>(drawn_w + (kt - vt0) * kFKT + 8 * g + 4 * h);
@@ -266,6 +282,7 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
         for (int i = 0; i < 16; ++i) {
           const int pos = base + 8 * (i / 4) + 4 * h + (i % 4);
           c[i] = pos >= lim ? -INFINITY : c[i] + (sampled ? nat_bias : 0.f);
+          if (kValue && sampled && a.cap_scale > 0.f) c[i] = fminf(c[i], log_capw);
         }
       }
     }
@@ -288,17 +305,25 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
     // (the reference only moves by steps of 2^8, as in the bf16 kernel: a rescale is a twelfth of a tile's vector work)
     if (__any(mx > m_run + 5.5f)) {
       const float m_new = fmaxf(m_run, mx);
-      const float alpha = expf(m_run - (m_new == -INFINITY ? 0.f : m_new));
-      l_run *= alpha;
-      if (kCap) msum *= alpha;
+      const float alpha = expf(m_run - finite_ref(m_new));
+      if (!kValue || kt < vt0) l_run *= kCap ? expf(sum_ref(m_run) - finite_ref(sum_ref(m_new))) : alpha;
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
         for (int i = 0; i < 16; ++i) o[dt][i] *= alpha;
       m_run = m_new;
     }
-    const float m_use = m_run == -INFINITY ? 0.f : m_run;
-    const float capw = kCap && sampled ? expf(log_capw - m_use) : INFINITY;
+    const float m_use = finite_ref(m_run);
+    float capw = INFINITY;
+    if constexpr (kCap && !kValue) {
+      if (sampled) capw = expf(log_capw - m_use);
+      if (sampled && __any(m_run > log_capw + kFarCap)) {  // rare: exponentials of the sum's own
+        const float ref = finite_ref(sum_ref(m_run));
+#pragma unroll
+        for (int i = 0; i < 16; ++i) l_run += exp_split(fminf(c[i], log_capw) - ref);
+        capw = 0.f;
+      }
+    }
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       c[i] = exp_split(c[i] - m_use);
@@ -346,10 +371,10 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
   // leave as whole 16-byte pieces of consecutive lanes ----
   constexpr int RS = F32Lds<D>::ROW;
   float* orow = reinterpret_cast<float*>(smem);   // [waves][32][RS]
-  float* ml = orow + NW * 32 * RS;                // [waves][32][ML]: reference, row sum; cap mode: of the samples, masked sum
-  constexpr int ML = kCap ? 3 : 2;
+  float* ml = orow + NW * 32 * RS;                // [waves][32][ML]: reference, row sum; cap mode: of the samples, its reference, log of the masked sum
+  constexpr int ML = kCap ? 4 : 2;
   const float l_tot = l_run + __shfl_xor(l_run, 32);
-  const float m_tot = kCap ? msum + __shfl_xor(msum, 32) : 0.f;
+  if (kCap && !drawn) d_ref = sum_ref(m_run);
   __syncthreads();  // the key list is read no more
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt)
@@ -360,7 +385,10 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
   if (h == 0) {
     ml[(wave * 32 + lq) * ML] = m_run;
     ml[(wave * 32 + lq) * ML + 1] = l_tot;
-    if (kCap) ml[(wave * 32 + lq) * ML + 2] = m_tot;
+    if (kCap) {
+      ml[(wave * 32 + lq) * ML + 2] = d_ref;
+      ml[(wave * 32 + lq) * ML + 3] = log_masked;  // (the same in all waves of a row)
+    }
   }
   __syncthreads();
   constexpr int LPR = D / 4;  // lanes per row
@@ -368,23 +396,25 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
   for (int idx = tid; idx < w.rows_valid * LPR; idx += kFNT) {
     const int r = idx / LPR, col = (idx % LPR) * 4;
     const int w0 = (r / 32) * KW;  // first of the waves that hold the row
-    float mx = -INFINITY;
+    float mx = -INFINITY, dmx = -INFINITY;
 #pragma unroll
-    for (int k = 0; k < KW; ++k) mx = fmaxf(mx, ml[((w0 + k) * 32 + (r & 31)) * ML]);
+    for (int k = 0; k < KW; ++k) {
+      mx = fmaxf(mx, ml[((w0 + k) * 32 + (r & 31)) * ML]);
+      if (kCap) dmx = fmaxf(dmx, ml[((w0 + k) * 32 + (r & 31)) * ML + 2]);
+    }
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    float l = 0.f, ms = 0.f;
+    float l = 0.f;
 #pragma unroll
     for (int k = 0; k < KW; ++k) {
       const int at = (w0 + k) * 32 + (r & 31);
       const float wk = KW == 1 ? 1.f : (mx == -INFINITY ? 0.f : expf(ml[at * ML] - mx));
-      l += wk * ml[at * ML + 1];
-      if (kCap) ms += wk * ml[at * ML + 2];
+      l += (kCap && KW > 1 ? expf(ml[at * ML + 2] - finite_ref(dmx)) : wk) * ml[at * ML + 1];
       acc += wk * *reinterpret_cast<const f32x4*>(orow + at * RS + col);
     }
     const bool empty = !(l > 0.f);
-    float lse = empty ? -INFINITY : add_log(mx, l);
+    float lse = empty ? -INFINITY : add_log(kCap ? dmx : mx, l);
     if constexpr (kCap) {  // d~_i = masked + max(d_i, tau / kappa)
-      lse = logaddexpf(ms > 0.f ? add_log(mx, ms) : -INFINITY, fmaxf(lse, floor_term));
+      lse = logaddexpf(ml[(w0 * 32 + (r & 31)) * ML + 3], fmaxf(lse, floor_term));
       acc *= (mx == -INFINITY || lse == -INFINITY) ? 0.f : expf(mx - lse);
     } else {
       acc *= empty ? 0.f : 1.f / l;

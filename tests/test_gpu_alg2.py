@@ -13,7 +13,7 @@ import pytest
 
 import synth_inputs
 from oracle import hyperattn_oracle as orc
-from ha_testutil import assert_close, have_gpu, to_device, to_host
+from ha_testutil import LSE_TOL, assert_close, have_gpu, out_tolerance, to_device, to_host
 
 pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not have_gpu(), reason="needs a GPU")]
 
@@ -241,3 +241,64 @@ def test_alg2_more_heads_than_one_launch_holds(ha, torch):
     for half in (slice(0, H // 2), slice(H // 2, H)):
         o, l, _ = ha.hyperattn_forward_alg2(*(x[:, half].contiguous() for x in (q, k, v)), 8, 4, 3, **kw)
         assert torch.equal(out[:, half], o) and torch.equal(lse[:, half], l)
+
+
+@pytest.mark.parametrize("dtype", ["fp32"])
+@pytest.mark.parametrize("cap_scale,kappa", [(8.0, 0.0), (0.0, 0.0), (8.0, 1.3)])
+@pytest.mark.parametrize("vnorm", [False, True])
+@pytest.mark.parametrize("d,H,n,b,m,r,n_min", [
+    (64, 1, 2048, 64, 64, 7, 0),
+    (128, 1, 2048, 128, 128, 7, 0),
+    (64, 1, 4096, 256, 256, 7, 0),
+    (128, 40, 896, 64, 77, 5, 0),      # fp32: two waves per row
+    (64, 80, 896, 128, 31, 5, 0),      # fp32: one wave per row
+    (64, 1, 2048, 64, 64, 7, 512)])    # causal, two levels
+def test_alg2_scores_far_apart(ha, torch, d, H, n, b, m, r, n_min, vnorm, cap_scale, kappa, dtype):
+    """Clustered inputs, whose sampled or drawn keys can exceed all of a row's block by hundreds: the masked sum, the capped sum of
+    the samples and the output's weights have scales of their own.  log d~ of every row within the rounding of the scores: a score is
+    a sum of d products, its error at most (d + 2) 2^-24 sum_c |q_c k_c| <= e (the row's largest), and log d~ moves by no more than twice that
+    (through the cap and by itself) plus LSE_TOL of its own value.  Outputs where the row's weights fit fp32 (sum_j w_j |v_j| <
+    1e30; unmasked problems: a node's partial row can overflow where the merged one would not), within the weights'
+    relative error exp(4 e) - 1 (score and log d~), 2^-8 for bf16 operands."""
+    print(f"alg2 clustered {dtype} d={d} H={H} n={n} b={b} m={m} r={r} n_min={n_min} cap={cap_scale} kappa={kappa} vnorm={vnorm}", flush=True)
+    causal = n_min > 0
+    Q, K, V = synth_inputs.make_qkv(dict(B=1, H=H, n=n, d=d, dtype=dtype, law="mixture"), seed=n + d)
+    kw = dict(seed=5, cap_scale=cap_scale, kappa=kappa, vnorm_sampling=vnorm, causal=causal, n_min=n_min or 4096)
+    out, lse, ws = ha.hyperattn_forward_alg2(*(to_device(x, dtype) for x in (Q, K, V)), b, m, r, **kw)
+    torch.cuda.synchronize()
+    views = ha.alg2_workspace_views(ws, ha.make_shape(1, H, n, d, ha.HA_BF16 if dtype == "bf16" else ha.HA_FP32),
+                                    ha.make_params(b, m, r, causal, n_min or 4096, 5))
+    ends = sorted({0, 1 if vnorm else H - 1} & set(range(H)))
+    replay = {}
+    if vnorm:
+        for bh in ends:
+            for heap in range(views["vnorm_samples"].shape[1]):
+                level = (heap + 1).bit_length() - 1
+                s = n >> (level + 1) if causal else n
+                k0 = 2 * (heap + 1 - (1 << level)) * s
+                marg = []
+                idx, _ = orc.vnorm_samples(V[0, bh, k0:k0 + s], 5, bh, m, margin=marg, heap=heap, n_heads=H)
+                got = views["vnorm_samples"][bh, heap].cpu().numpy()
+                for j in np.nonzero(got != idx)[0]:
+                    assert marg[j] < 1e-9 and abs(int(got[j]) - int(idx[j])) == 1, (bh, heap, j, marg[j])
+                    replay.setdefault((bh, heap), {})[int(j)] = int(got[j])
+    Qe, Ke, Ve = (x[:, ends] for x in (Q, K, V))
+    okw = dict(b=b, m=m, r=r, vnorm_replay=replay, **kw)
+    with np.errstate(over="ignore", invalid="ignore"):
+        ref_out, ref_lse, _ = orc.hyperattn_forward_alg2(Qe, Ke, Ve, **okw)
+        absv = orc.hyperattn_forward_alg2(Qe, Ke, np.abs(Ve), vnorm_from=Ve, **okw)[0]
+    heavy = np.nan_to_num(absv, nan=np.inf).max(axis=-1)
+    far = heavy > 1e45     # a weight beyond e^104 of the row's sum
+    print(f"  rows whose weights exceed their sum by more than e^104: {int(far.sum())}", flush=True)
+    if not causal and kappa == 0 and cap_scale > 0 and n >= 2048:
+        assert far.any()
+    e = (d + 2) * 2.0 ** -24 * (np.abs(Qe) @ np.abs(Ke).swapaxes(-1, -2)).max(axis=-1)
+    got = to_host(lse)[:, ends]
+    err = np.abs(got - ref_lse) - (2 * e + LSE_TOL[dtype] * np.maximum(1.0, np.abs(ref_lse)))
+    assert np.isfinite(got).all() and (err <= 0).all(), (f"log d~: {int((~np.isfinite(got)).sum())} rows not finite, "
+                                                         f"{int((err > 0).sum())} of {err.size} out of tolerance")
+    if not causal:
+        fits = heavy < 1e30
+        o = to_host(out)[:, ends][fits]
+        tol = (np.expm1(4 * e[fits])[:, None] + (2.0 ** -8 if dtype == "bf16" else 0.0)) * absv[fits] + out_tolerance(ref_out[fits], dtype)
+        assert (np.abs(o - ref_out[fits]) <= tol).all(), f"out: worst excess {float((np.abs(o - ref_out[fits]) - tol).max()):.2e}"

@@ -23,9 +23,9 @@
 // A the block's keys, B the m uniform samples, C the m rows drawn
 // by squared norm.  An entry is a row index, or its complement when the key is
 // to be left out (padding; a sample that falls into the row's own block, the
-// factor 1 - M_{i,l_j}); segment C carries a log weight per key.  One running
-// reference serves all exponentials (log2 domain, lazily moved as in the forward
-// kernel), so the three sums and the numerator share their scale.
+// factor 1 - M_{i,l_j}); segment C carries a log weight per key.  The exponentials'
+// reference (log2 domain, lazily moved as in the forward kernel) begins anew with
+// every segment.
 #include "alg2_common.h"
 #include "attn_common.h"
 
@@ -314,10 +314,19 @@ __global__ __launch_bounds__(kA2NT, 2) void alg2_mfma_kernel(Alg2Args a) {
   for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
     for (int i = 0; i < 16; ++i) o[dt][i] = 0.f;
-  float m_run = -INFINITY;  // reference of every exponential, log2 domain
-  float msum = 0.f;         // this lane's share of the masked row sum / 2^m_run
-  float dsum = 0.f;         // this lane's share of (n/m) sum of capped kept samples / 2^m_run
-  float log2capw = INFINITY;  // log2 of (n/m) C_i, known once segment A is done
+  // Scores of one row can lie hundreds apart, so every segment has a reference of its own: the sums of A and B are kept as
+  // logarithms when the next segment begins, and no sample of B counts (or moves the reference) beyond its cap.
+  float m_run = -INFINITY;  // reference of the segment's exponentials, log2 domain
+  float l_run = 0.f;        // this lane's share of the segment's row sum / 2^m_run
+  float log_masked = -INFINITY, log_d = -INFINITY;  // of the block; of (n/m) sum of capped kept samples
+  float log2capw = 3e38f;  // log2 of (n/m) C_i, known once segment A is done; no cap: above every finite score
+  auto end_segment = [&]() -> float {
+    const float l = l_run + __shfl_xor(l_run, 32);
+    const float r = (l > 0.f) ? (m_run + log2f(l)) * kLn2 : -INFINITY;
+    l_run = 0.f;
+    m_run = -INFINITY;
+    return r;
+  };
 
   load_tile(0);
   store_tile(0);
@@ -327,15 +336,15 @@ __global__ __launch_bounds__(kA2NT, 2) void alg2_mfma_kernel(Alg2Args a) {
     const bool more = kt + 1 < ntiles;
     if (more) load_tile(kt + 1);
 
-    if (kt == nA && nB > 0) {
+    if (kt == nA) {
       // the masked row sum is complete: the cap C_i of Algorithm 2
-      const float mt = msum + __shfl_xor(msum, 32);
-      const float log_masked = (mt > 0.f) ? (m_run + log2f(mt)) * kLn2 : -INFINITY;
+      log_masked = end_segment();
       if (a.cap_scale > 0.f) {
         const float log_cap = logf(a.cap_scale * (float)g.m / ((float)g.n * logf((float)g.n))) + logaddexpf(log_masked, floor_term);
         log2capw = log_cap * kLog2e + log2ratio;
       }
     }
+    if (kt == nA + nB) log_d = end_segment();
 
     const unsigned char* kbuf = bufs + (kt & 1) * L::BUF;
     const unsigned char* vbuf = kbuf + L::K_BYTES;
@@ -369,7 +378,8 @@ __global__ __launch_bounds__(kA2NT, 2) void alg2_mfma_kernel(Alg2Args a) {
         if (seg == 2) b4 = *reinterpret_cast<const f32x4*>(bias_c + (kt - nA - nB) * kA2KT + at);
 #pragma unroll
         for (int z = 0; z < 4; ++z) {
-          const float v = e4[z] < 0 ? -INFINITY : __builtin_fmaf(c[sub][4 * g4 + z], kLog2e, b4[z]);
+          float v = e4[z] < 0 ? -INFINITY : __builtin_fmaf(c[sub][4 * g4 + z], kLog2e, b4[z]);
+          if (seg == 1) v = fminf(v, log2capw);
           c[sub][4 * g4 + z] = v;
           tmax = fmaxf(tmax, v);
         }
@@ -382,15 +392,13 @@ __global__ __launch_bounds__(kA2NT, 2) void alg2_mfma_kernel(Alg2Args a) {
       for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
         for (int i = 0; i < 16; ++i) o[dt][i] *= alpha;
-      msum *= alpha;
-      dsum *= alpha;
+      l_run *= alpha;
       m_run = m_new;
     }
     const float mref = (m_run == -INFINITY) ? 0.f : m_run;
-    const float capw = __builtin_amdgcn_exp2f(fminf(log2capw - mref, 120.f));  // (n/m) C_i on the scale of the weights
     // ---- weights, sums, and the B operand of the numerator ----
     bf16x8 pf[4];
-    float sp = 0.f, sd = 0.f;
+    float sp = 0.f;
 #pragma unroll
     for (int sub = 0; sub < 2; ++sub)
 #pragma unroll
@@ -401,13 +409,11 @@ __global__ __launch_bounds__(kA2NT, 2) void alg2_mfma_kernel(Alg2Args a) {
           const float p0w = __builtin_amdgcn_exp2f(c[sub][8 * jj + 2 * e] - mref);
           const float p1w = __builtin_amdgcn_exp2f(c[sub][8 * jj + 2 * e + 1] - mref);
           sp += p0w + p1w;
-          sd += fminf(p0w, capw) + fminf(p1w, capw);
           pk[e] = pack_bf16x2(p0w, p1w);
         }
         pf[2 * sub + jj] = __builtin_bit_cast(bf16x8, pk);
       }
-    if (seg == 0) msum += sp;
-    if (seg == 1) dsum += sd;
+    l_run += sp;
     // ---- numerator: O^T += V^T P^T ----
     if (need_v(kt)) {
       typedef short s16x4 __attribute__((ext_vector_type(4)));
@@ -431,10 +437,7 @@ __global__ __launch_bounds__(kA2NT, 2) void alg2_mfma_kernel(Alg2Args a) {
   }
 
   // ---- results ----
-  const float mt = msum + __shfl_xor(msum, 32);
-  const float dt_ = dsum + __shfl_xor(dsum, 32);
-  const float log_masked = (mt > 0.f) ? (m_run + log2f(mt)) * kLn2 : -INFINITY;
-  const float log_d = (dt_ > 0.f) ? (m_run + log2f(dt_)) * kLn2 : -INFINITY;
+  if (g.m == 0) log_masked = end_segment();
   const float log_dt = logaddexpf(log_masked, fmaxf(log_d, floor_term));   // d~_i = masked + max(d_i, tau / kappa)
   const float f = (m_run == -INFINITY || log_dt == -INFINITY) ? 0.f : expf(m_run * kLn2 - log_dt);
   const int64_t out_row = hb + (qrow - nd.q_start);

@@ -241,12 +241,24 @@ __global__ __launch_bounds__(64 * NW * NG, (D == 64 && NW == 4 && NG == 1) ? 3 :
   float m_run = -INFINITY;
   float l_run = 0.f;  // this lane's share of the row sum
   // Cap mode (Algorithm 2 as printed): once the block's keys are done (tile nb_tiles on) l_run becomes the capped sum of
-  // the samples and msum keeps the masked row sum, from which the row's cap C_i follows.
+  // the samples and log_masked keeps the masked row sum, from which the row's cap C_i follows.  Scores of one row can lie hundreds
+  // apart, so neither may hang on the output's reference: the masked sum is a logarithm before the first sample's reference
+  // is formed, and the samples' sum is taken against sum_ref, the cap where that is far below m_run, since no capped term exceeds it.
   // One more vector instruction per score than the plain node mode (32 heads, n = 32768, d = 128, b = m = 256: 8 % more
   // cycles, vector issue 50 against 44 % of them; 414 to 487 us, by the clock of the run, where a kernel of its own without
-  // the software pipeline below took 600).  At d = 64 the 168 registers that three workgroups per CU leave cost it 20 bytes of scratch per lane.
+  // the software pipeline below took 600).  At d = 64 the 168 registers that three workgroups per CU leave cost it 40 bytes of scratch
+  // per lane, at d = 128 the 256 of two 16.  (With the masked and the capped sum on m_run, 20 and none, rows of clustered inputs lost log d~ to
+  // underflow; calls of 32 heads, n = 32768 with it -> without: d = 128 623 -> 622 us, d = 64 370 -> 367.)
   const int nb_tiles = kCap ? (nb + kKT - 1) / kKT : 0;
-  float msum = 0.f, log2capw = INFINITY;  // log2 of (s / m) C_i
+  float log_masked = -INFINITY, log2capw = INFINITY;  // log2 of (s / m) C_i
+  constexpr float kFarCap = 60.f;  // a term that underflows against m_run is then 2^-66 of the cap or less
+  auto sum_ref = [&](float m) { return kCap && m > log2capw + kFarCap ? log2capw : m; };
+  auto finite_ref = [](float m) { return m == -INFINITY ? 0.f : m; };
+  auto end_masked = [&]() {
+    const float mt = l_run + __shfl_xor(l_run, 32);
+    log_masked = (mt > 0.f) ? (m_run + log2f(mt)) * kLn2 : -INFINITY;
+    l_run = 0.f;
+  };
   const float floor_term = kCap && a.kappa > 0.f ? a.log_tau[(int64_t)w.bh * a.g.total_nodes + w.nr.heap] - logf(a.kappa) : -INFINITY;
 
   // Masks of a score tile (rare tiles only): tail of the key list, causal
@@ -337,6 +349,15 @@ __global__ __launch_bounds__(64 * NW * NG, (D == 64 && NW == 4 && NG == 1) ? 3 :
       if (HN) load_rows(kt + 1, Vh, vreg);
     }
 
+    if constexpr (kCap) {
+      if (kt == nb_tiles) {
+        end_masked();
+        if (a.cap_scale > 0.f) {
+          const float n = (float)w.nr.s;
+          log2capw = (logf(a.cap_scale * (float)a.g.m / (n * logf(n))) + logaddexpf(log_masked, floor_term)) * kLog2e + bias2;
+        }
+      }
+    }
     if (__any(t_max > m_run + 8.0f)) {
       const float m_new = fmaxf(m_run, t_max);
       const float alpha = __builtin_amdgcn_exp2f(m_run - ((m_new == -INFINITY) ? 0.f : m_new));
@@ -344,23 +365,23 @@ __global__ __launch_bounds__(64 * NW * NG, (D == 64 && NW == 4 && NG == 1) ? 3 :
       for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
         for (int i = 0; i < 16; ++i) o[dt][i] *= alpha;
-      l_run *= alpha;
-      if (kCap) msum *= alpha;
+      l_run *= kCap ? __builtin_amdgcn_exp2f(sum_ref(m_run) - finite_ref(sum_ref(m_new))) : alpha;
       m_run = m_new;
     }
     float capw = INFINITY;
     if constexpr (kCap) {
-      if (kt == nb_tiles) {
-        const float mt = l_run + __shfl_xor(l_run, 32);
-        const float log_masked = (mt > 0.f) ? (m_run + log2f(mt)) * kLn2 : -INFINITY;
-        msum = l_run;
-        l_run = 0.f;
-        if (a.cap_scale > 0.f) {
-          const float n = (float)w.nr.s;
-          log2capw = (logf(a.cap_scale * (float)a.g.m / (n * logf(n))) + logaddexpf(log_masked, floor_term)) * kLog2e + bias2;
+      if (kt >= nb_tiles) {
+        capw = __builtin_amdgcn_exp2f(fminf(log2capw - finite_ref(m_run), 120.f));
+        if (__any(m_run > log2capw + kFarCap)) {  // rare: exponentials of the sum's own
+          const float ref = finite_ref(sum_ref(m_run));
+#pragma unroll
+          for (int sub = 0; sub < 2; ++sub)
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+              l_run += __builtin_amdgcn_exp2f(fminf(__builtin_fmaf(c[sub][i], kLog2e, bias), log2capw) - ref);
+          capw = 0.f;
         }
       }
-      if (kt >= nb_tiles) capw = __builtin_amdgcn_exp2f(fminf(log2capw - ((m_run == -INFINITY) ? 0.f : m_run), 120.f));
     }
     const float shift = bias - ((m_run == -INFINITY) ? 0.f : m_run);
 
@@ -516,17 +537,12 @@ __global__ __launch_bounds__(64 * NW * NG, (D == 64 && NW == 4 && NG == 1) ? 3 :
   }
 
   // ---- epilogue ----
-  if (kCap && ntiles <= nb_tiles) {  // no sample was kept
-    msum = l_run;
-    l_run = 0.f;
-  }
+  if (kCap && ntiles <= nb_tiles) end_masked();  // no sample was kept
   const float l_tot = l_run + __shfl_xor(l_run, 32);
   const bool empty = !(l_tot > 0.f);
   float inv = empty ? 0.f : 1.f / l_tot;
-  float lse_own = empty ? -INFINITY : (m_run + log2f(l_tot)) * kLn2;
+  float lse_own = empty ? -INFINITY : (sum_ref(m_run) + log2f(l_tot)) * kLn2;
   if constexpr (kCap) {  // d~_i = masked + max(d_i, tau / kappa)
-    const float mt = msum + __shfl_xor(msum, 32);
-    const float log_masked = (mt > 0.f) ? (m_run + log2f(mt)) * kLn2 : -INFINITY;
     lse_own = logaddexpf(log_masked, fmaxf(lse_own, floor_term));
     inv = (m_run == -INFINITY || lse_own == -INFINITY) ? 0.f : expf(m_run * kLn2 - lse_own);
   }

@@ -243,7 +243,7 @@ def test_alg2_more_heads_than_one_launch_holds(ha, torch):
         assert torch.equal(out[:, half], o) and torch.equal(lse[:, half], l)
 
 
-@pytest.mark.parametrize("dtype", ["fp32"])
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 @pytest.mark.parametrize("cap_scale,kappa", [(8.0, 0.0), (0.0, 0.0), (8.0, 1.3)])
 @pytest.mark.parametrize("vnorm", [False, True])
 @pytest.mark.parametrize("d,H,n,b,m,r,n_min", [

@@ -187,6 +187,11 @@ int hyperattn_forward_stamped(const void* Q, const void* K, const void* V, void*
                               int64_t* node_stamps_dev, size_t node_stamps_bytes,
                               int64_t* base_stamps_dev, size_t base_stamps_bytes);
 
+/* Host only.  Which launches the calls for this shape and params take where small problems have others (tests,
+ * measurements): *sorts_in_attention is 1 if hyperattn_forward lets the attention launch sort, else 0;
+ * *shared_workgroups the workgroups of the larger launch that passes of hyperattn_backward share, 0 if they do not. */
+int ha_call_routes(const ha_shape* shape, const ha_params* params, int32_t* sorts_in_attention, int64_t* shared_workgroups);
+
 /* Plain exact attention D^-1 A V (Section 1.1), or D_C^-1 (M^C . A) V with
  * M^C_ij = 1{i >= j} (Section 3.1) when causal != 0; the denominator of the
  * speed-up ratio.  Any n >= 1; d in {64,128}.  Needs no workspace. */

@@ -68,6 +68,7 @@ _SIGNATURES = {
     "hyperattn_forward_timed": (c_int, [c_void_p] * 5 + [POINTER(HaShape), POINTER(HaParams), c_void_p, c_size_t,
                                                         c_void_p, POINTER(c_float)]),
     "ha_forward_workgroups": (c_int, [POINTER(HaShape), POINTER(HaParams), POINTER(c_int64), POINTER(c_int64)]),
+    "ha_call_routes": (c_int, [POINTER(HaShape), POINTER(HaParams), POINTER(c_int32), POINTER(c_int64)]),
     "hyperattn_forward_stamped": (c_int, [c_void_p] * 5 + [POINTER(HaShape), POINTER(HaParams), c_void_p, c_size_t,
                                                           c_void_p, c_void_p, c_size_t, c_void_p, c_size_t]),
     "exact_attn_forward": (c_int, [c_void_p] * 5 + [POINTER(HaShape), c_int, c_void_p]),
@@ -371,6 +372,13 @@ def ha_forward_workgroups(shape, params):
     _check(lib().ha_forward_workgroups(ctypes.byref(shape), ctypes.byref(params), ctypes.byref(nw), ctypes.byref(bw)),
            "ha_forward_workgroups")
     return int(nw.value), int(bw.value)
+
+
+def ha_call_routes(shape, params):
+    """(whether the attention launch sorts, workgroups of the larger launch that backward passes share or 0)."""
+    sorts, shared = c_int32(0), c_int64(0)
+    _check(lib().ha_call_routes(ctypes.byref(shape), ctypes.byref(params), ctypes.byref(sorts), ctypes.byref(shared)), "ha_call_routes")
+    return bool(sorts.value), int(shared.value)
 
 
 def hyperattn_forward_stamped(Q, K, V, b, m, r, causal=False, n_min=4096, seed=0, workspace=None, out=None, lse=None,

@@ -447,6 +447,19 @@ static void fill_bwd_layout(const Geometry& g, ha_bwd_ws_layout* l) {
 // for the rows of O with nothing beside it (forward + backward, 4 heads, n = 4096: 154.5 -> 156.3 us; d = 64: 91.6 -> 90.0).
 static bool delta_in_dq_pass(const Geometry& g) { return g.dtype == HA_BF16 || g.d == 64; }
 
+// What the passes' grids follow from.
+static BwdArgs bwd_shape_args(const Geometry& g) {
+  BwdArgs a{};
+  a.f.g = g;
+  a.f.exact_rows_q = a.f.exact_rows_k = g.n;
+  a.f.exact_block = g.causal ? g.base_len : g.n;
+  a.f.exact_causal = g.causal;
+  a.chunk = bwd_chunk(g);
+  a.samp_chunks = (int32_t)bwd_sample_chunks(g, a.chunk);
+  return a;
+}
+static bool backward_shares(const BwdArgs& a) { return a.f.g.dtype == HA_FP32 && a.f.g.causal && a.f.g.levels > 0 && bwd_f32_shares(a); }
+
 // ev, when non-null, receives 8 events: start, after delta, dQ of the nodes, dQ of the base case, dK/dV of the block keys,
 // of the sampled keys (with their reduction; unmasked problems: these two the other way round), of the base case, end.
 // Small fp32 causal problems, whose passes share launches: nothing, base case and sampled keys, node passes, the samples' sums, nothing.
@@ -481,7 +494,7 @@ static int backward_impl(const void* Q, const void* K, const void* V, const void
     if (ev) (void)hipEventRecord(ev[i], st);
   };
 
-  BwdArgs a{};
+  BwdArgs a = bwd_shape_args(g);
   a.f.Q = Q;
   a.f.K = K;
   a.f.V = V;
@@ -492,15 +505,9 @@ static int backward_impl(const void* Q, const void* K, const void* V, const void
   a.f.samples = g.m > 0 ? (const int32_t*)(fb + lay.samples) : nullptr;
   a.f.samp_blk = g.m > 0 ? (const int32_t*)(fb + lay.samp_blk) : nullptr;
   a.f.use_block = 1;
-  a.f.g = g;
-  a.f.exact_rows_q = a.f.exact_rows_k = g.n;
-  a.f.exact_block = g.causal ? g.base_len : g.n;
-  a.f.exact_causal = g.causal;
   a.dO = d_out;
   a.lse = lse;
   a.delta = delta;
-  a.chunk = bwd_chunk(g);
-  a.samp_chunks = (int32_t)bwd_sample_chunks(g, a.chunk);
 
   mark(0);
   if ((g.levels == 0 || !g.causal) && delta_in_dq_pass(g)) {  // one dQ pass holds every row once
@@ -550,7 +557,7 @@ static int backward_impl(const void* Q, const void* K, const void* V, const void
     mark(7);
     return HA_OK;
   }
-  if (g.dtype == HA_FP32 && g.levels > 0 && bwd_f32_shares(a)) {
+  if (backward_shares(a)) {
     // passes side by side: the base case writes the gradients, the node passes and the samples' sums add to them
     const bool has_samp = g.m > 0;
     a.base_first = 1;
@@ -736,6 +743,20 @@ int ha_forward_workgroups(const ha_shape* shape, const ha_params* params, int64_
     const AttnArgs e = base_case_args(nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, g, nullptr, nullptr);
     *base_wgs = attn_mfma_grid(e, kModeExact);
   }
+  return HA_OK;
+}
+
+int ha_call_routes(const ha_shape* shape, const ha_params* params, int32_t* sorts_in_attention, int64_t* shared_workgroups) {
+  if (!sorts_in_attention || !shared_workgroups) return HA_ERR_NULL;
+  Geometry g;
+  const int rc = make_geometry(shape, params, &g);
+  if (rc != HA_OK) return rc;
+  *sorts_in_attention = 0;
+  *shared_workgroups = 0;
+  if (g.BH == 0 || g.n == 0) return HA_OK;
+  if (g.levels > 0) *sorts_in_attention = sort_in_attention(g);
+  const BwdArgs a = bwd_shape_args(g);
+  if (backward_shares(a)) *shared_workgroups = bwd_f32_shared_workgroups(a);
   return HA_OK;
 }
 

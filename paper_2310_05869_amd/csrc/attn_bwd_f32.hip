@@ -429,9 +429,19 @@ static bool four_waves(const BwdArgs& a) {
   return 3 * (int64_t)((run + 127) / 128 * 128) > 4 * (int64_t)run || 4 * bwd_grid<128>(a, MODE) < 2048;
 }
 
+// a part begins at a multiple of 8, so that its workgroups' XCDs are those of a launch of its own
+static int64_t part_span(const BwdArgs& a, int mode) { return (bwd_grid<32>(a, mode) + 7) & ~(int64_t)7; }
+
+// (short blocks: a workgroup each in the level's launch, one per 32 rows in that of the base case)
+int64_t bwd_f32_shared_workgroups(const BwdArgs& a) {
+  const int64_t base = part_span(a, kBwdDkvExact) + part_span(a, kBwdDqExact) + part_span(a, kBwdDkvSamp);
+  const int64_t level = part_span(a, kBwdDkvBlock) + part_span(a, kBwdDqNode);
+  return base > level ? base : level;
+}
+
 bool bwd_f32_shares(const BwdArgs& a) {
   return four_waves<kBwdDqExact>(a) && !f32_exact_eight(a.f) && four_waves<kBwdDqNode>(a) && (a.f.g.m == 0 || four_waves<kBwdDkvSamp>(a)) &&
-         2 * bwd_grid<32>(a, kBwdDkvExact) + bwd_grid<32>(a, kBwdDkvSamp) < kMaxLaunch;
+         bwd_f32_shared_workgroups(a) <= kMaxLaunch;
 }
 
 template <int D, bool NODES>
@@ -447,7 +457,7 @@ static int launch_shared_form(const BwdShared& m, int64_t grid, hipStream_t st) 
   return check_launch();
 }
 
-// parts one behind the other; a part begins at a multiple of 8, so that its workgroups' XCDs are those of a launch of its own
+// parts one behind the other
 static int launch_shared(BwdShared& m, int parts, const int* modes, bool nodes, hipStream_t st) {
   int64_t at = 0;
   for (int i = 0; i < 3; ++i) {
@@ -455,10 +465,12 @@ static int launch_shared(BwdShared& m, int parts, const int* modes, bool nodes, 
     p.first = (int32_t)at;
     p.count = 0;
     if (i >= parts) continue;
+    const int64_t span = part_span(p.a, modes[i]);
+    if (at + span > kMaxLaunch) return HA_ERR_SHAPE;
     p.count = (int32_t)bwd_grid<32>(p.a, modes[i]);
     if (nodes) set_node_divs<32>(p.a.f);
     else if (modes[i] != kBwdDkvSamp) set_exact_divs<32>(p.a.f);
-    at += (p.count + 7) & ~7;
+    at += span;
   }
   if (at == 0) return HA_OK;
   const int d = m.part[0].a.f.g.d;

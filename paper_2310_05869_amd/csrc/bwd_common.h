@@ -272,6 +272,7 @@ struct BwdShared {
   BwdPart part[3];
 };
 bool bwd_f32_shares(const BwdArgs& a);
+int64_t bwd_f32_shared_workgroups(const BwdArgs& a);  // of the larger of those launches
 int launch_attn_bwd_f32_base(const BwdArgs& dkv, const BwdArgs& dq, const BwdArgs* samp, hipStream_t st);
 int launch_attn_bwd_f32_level(const BwdArgs& block, const BwdArgs& dq, hipStream_t st);
 // delta_i = <dO_i, O_i>; bf16 tensors: O from its unrounded fp32 copy when O_f32 is non-null, else from the tensor

@@ -159,6 +159,22 @@ def test_backward_workspace_grows_with_the_problem(ha, causal, dtype_d):
 
 
 
+def test_backward_shared_launches_hold_their_workgroups(ha):
+    """A launch of 256 threads per workgroup counts its threads in 32 bits: passes share one of at most 2^23 workgroups.
+    Short blocks, a workgroup each, make the levels' launches far larger than the base case's."""
+    routes = lambda BH, n, d, b, m, n_min: ha.ha_call_routes(ha.make_shape(1, BH, n, d, ha.HA_FP32), ha.make_params(b, m, 7, True, n_min, 0))[1]
+    assert routes(1024, 16384, 64, 1, 0, 64) == 0                # 2^20 in the base case's launch, 2^24 in a level's
+    assert routes(512, 16384, 64, 1, 0, 64) == 1 << 23           # the most that a launch holds
+    assert routes(4, 4096, 64, 64, 64, 1024) == 2 * 4 * 4096 // 32 + 128   # dK / dV, dQ, sampled keys: 64 query chunks, two groups of 32
+    for BH in (1, 48, 1024, 1 << 16):
+        for n_min, b in ((16, 1), (16, 16), (64, 1), (96, 3), (96, 32), (512, 64)):
+            for levels in (1, 4, 8):
+                for m in (0, 33, 256):
+                    if BH * (n_min << levels) <= 1 << 30:
+                        assert routes(BH, n_min << levels, 64, b, m, n_min) <= 1 << 23
+    assert ha.ha_call_routes(ha.make_shape(1, 4, 4096, 64, ha.HA_BF16), ha.make_params(64, 64, 7, True, 1024, 0))[1] == 0
+
+
 def test_forward_workgroup_counts(ha):
     """Records of the stamped forward: one per 128-query tile of every node (levels x half the rows when causal)
     and of the base case; none for fp32 tensors, which run the kernel without matrix cores."""

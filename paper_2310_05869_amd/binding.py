@@ -202,7 +202,8 @@ def _stream(stream):
     if stream is not None:
         return stream.cuda_stream
     torch = _torch()
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)  # no public name: a torch may be without it
+    return torch.cuda.current_stream().cuda_stream if raw is None else raw(torch.cuda.current_device())
 
 
 def _expect(t, name, shape, dtype, like):

@@ -245,6 +245,17 @@ def test_misaligned_arrays_are_rejected_on_the_host(ha):
     assert "aligned" in ha.strerror(-6)
 
 
+@pytest.mark.parametrize("raw", [True, False])
+def test_current_stream_with_and_without_torchs_private_name(ha, monkeypatch, raw):
+    """The current stream's handle, also from a torch whose private shortcut is gone."""
+    from types import SimpleNamespace as NS
+    fake = NS(_C=NS(_cuda_getCurrentRawStream=lambda device: 100 + device) if raw else NS(),
+              cuda=NS(current_device=lambda: 3, current_stream=lambda: NS(cuda_stream=103)))
+    monkeypatch.setattr(ha.binding, "_torch_module", fake)
+    assert ha.binding._stream(None) == 103
+    assert ha.binding._stream(NS(cuda_stream=7)) == 7
+
+
 def test_product_package_does_not_import_the_oracle():
     pkg = os.path.join(ROOT, "paper_2310_05869_amd")
     for dirpath, _, files in os.walk(pkg):

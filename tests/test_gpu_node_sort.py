@@ -36,6 +36,8 @@ CASES = [  # dtype, d, B, H, n, b, m, r, n_min (0: unmasked)
     ("fp32", 128, 1, 3, 777, 21, 50, 8, 0),
     ("fp32", 64, 1, 4, 4096, 64, 64, 7, 1024),
     ("fp32", 64, 2, 8, 2048, 256, 256, 7, 0),
+    ("fp32", 64, 1, 16, 4096, 128, 64, 7, 0),      # one wave per group of rows
+    ("fp32", 128, 1, 32, 2048, 128, 0, 7, 0),      # likewise, no samples
 ]
 
 
@@ -51,15 +53,17 @@ def test_sort_inside_the_attention_launch(ha, torch, dtype, d, B, H, n, b, m, r,
         q, k = (x[:, :, :1].expand(B, H, n, d).contiguous() for x in (q, k))
     shape = ha.make_shape(B, H, n, d, ha.HA_BF16 if dtype == "bf16" else ha.HA_FP32)
     params = ha.make_params(b, m, r, n_min > 0, n_min or 4096, 3)
+    assert ha.ha_call_routes(shape, params)[0]     # by the rule of the dispatch itself
+    names = ("perm_q", "perm_k", "pos_k") + (("samp_blk",) if m else ())
     results = []
     for call in (ha.hyperattn_forward, ha.hyperattn_forward_timed):
         ws = ha.alloc_workspace(shape, params).fill_(0x5A)
         out, lse = call(q, k, v, b, m, r, causal=n_min > 0, n_min=n_min or 4096, seed=3, workspace=ws)[:2]
         torch.cuda.synchronize()
         views = ha.binding.workspace_views(ws, shape, params)
-        results.append((out, lse, {name: views[name].clone() for name in ("perm_q", "perm_k", "pos_k", "samp_blk") if name in views}))
+        results.append((out, lse, {name: views[name].clone() for name in names}))
     (out0, lse0, views0), (out1, lse1, views1) = results
-    for name in views0:
+    for name in names:
         assert torch.equal(views0[name], views1[name]), name
     assert torch.isfinite(out0.float()).all()
     assert torch.equal(out0, out1) and torch.equal(lse0, lse1)

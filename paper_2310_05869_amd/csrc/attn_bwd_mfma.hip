@@ -113,8 +113,8 @@ __device__ inline void dma_1k(const __amdgpu_buffer_rsrc_t& rsrc, uint32_t lds_a
 }
 
 // FINAL: the node passes of an unmasked problem, which write the final gradients.
-// NG = 2: two groups of four waves take the T tiles in turn, each with tile buffers of its own; their sums are added
-// through LDS.
+// NG = 2 (exact passes): two groups of four waves take the T tiles in turn, each with tile buffers of its own; their sums are
+// added through LDS.
 template <int D, int MODE, bool FINAL, int NG>
 __global__ __launch_bounds__(kBNT * NG, (D == 64 && MODE == kBwdDkvSamp) ? 3 : 2) void attn_bwd_kernel(BwdArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -128,7 +128,7 @@ __global__ __launch_bounds__(kBNT * NG, (D == 64 && MODE == kBwdDkvSamp) ? 3 : 2
   constexpr int CPR = D / 8;                 // 16-byte pieces per row
   constexpr int RPI = 64 / CPR;              // rows per DMA instruction
   constexpr int NDMA = kTT / RPI / 4;        // instructions per wave and tensor tile
-  constexpr int kNT = kBNT * NG;             // threads
+  static_assert(NG == 1 || kExact);          // the lists, sampled keys and accumulated rows of the node passes are one group's
 
   const AttnArgs& f = a.f;
   const Geometry& g = f.g;
@@ -164,7 +164,7 @@ __global__ __launch_bounds__(kBNT * NG, (D == 64 && MODE == kBwdDkvSamp) ? 3 : 2
   int blk_r = -1;        // sampled-key pass: sorted block of this key
   const int r_row = bwd_r_row<MODE>(a, b, r_use, &blk_r);           // row within the head
   SampleHead shead{-1, 0};
-  if (kHits) shead = fetch_sample_head(a, b, threadIdx.x);
+  if (kHits) shead = fetch_sample_head(a, b, tid);
   bf16x8 xreg[KS], areg[KS];
   {
     const u32x4* xp = reinterpret_cast<const u32x4*>(Xh + (int64_t)r_row * D + 8 * h);
@@ -232,11 +232,11 @@ __global__ __launch_bounds__(kBNT * NG, (D == 64 && MODE == kBwdDkvSamp) ? 3 : 2
   // positions through P_Q, listed in LDS too (dK/dV of a node), or a contiguous range ----
   int nT, nb = 0x7fffffff;
   if (MODE == kBwdDqNode) {
-    nT = build_key_list<kNT>(f, w, list, scratch, &nb);
+    nT = build_key_list<kBNT>(f, w, list, scratch, &nb);
   } else if (kSorted) {
     nT = MODE == kBwdDkvBlock ? g.b : b.chunk_len;
     const int32_t* tperm = f.perm_q + w.seg_off + (MODE == kBwdDkvBlock ? (int64_t)w.t * g.b : (int64_t)b.chunk_start);
-    for (int i = threadIdx.x; i < ((nT + 63) & ~63); i += kNT) list[i] = tperm[min(i, nT - 1)];
+    for (int i = tid; i < ((nT + 63) & ~63); i += kBNT) list[i] = tperm[min(i, nT - 1)];
     __syncthreads();
   } else {
     nT = max(0, w.k1 - w.k0);
@@ -301,7 +301,7 @@ __global__ __launch_bounds__(kBNT * NG, (D == 64 && MODE == kBwdDkvSamp) ? 3 : 2
   asm volatile("" : "+v"(nl2_r), "+v"(del_r));
   if (ntiles > 0) {
     request_tile(0);
-    if (kHits) find_sample_hits<kNT>(a, b, sample_hits(smem + bwd_hits_at<D, NG>(a, MODE)), shead);  // while the first tile is on its way
+    if (kHits) find_sample_hits<kBNT>(a, b, sample_hits(smem + bwd_hits_at<D, NG>(a, MODE)), shead);  // while the first tile is on its way
     finish_tile(0);
   }
 
@@ -521,7 +521,6 @@ __global__ __launch_bounds__(kBNT * NG, (D == 64 && MODE == kBwdDkvSamp) ? 3 : 2
       for (int e = 0; e < nm; ++e) {
         const int row = sh.more[e] >> 16;
         if ((row >> 5) != wave || (row & (G - 1)) != lane / LPR) continue;
-        if (NG == 2 && ((row >> 4) & 1) != grp) continue;
         f32x4* at = reinterpret_cast<f32x4*>(ep + (row & 31) * L::EP_ROW + (lane % LPR) * 16);
         *at = *at + *reinterpret_cast<const f32x4*>(sums + (int64_t)(sh.more[e] & 0xffff) * D + (lane % LPR) * 4);
       }
@@ -536,13 +535,13 @@ __global__ __launch_bounds__(kBNT * NG, (D == 64 && MODE == kBwdDkvSamp) ? 3 : 2
       if (MODE == kBwdDqNode) add = node_levels_hold(g, w.nr.q_start, true, w.level);
       if (MODE == kBwdDkvBlock) add = node_levels_hold(g, w.nr.k_start, false, w.level);
       constexpr int CH = D / 4;            // 16-byte pieces per fp32 row
-      constexpr int IT = 32 / NG * CH / 64;  // pieces per lane
+      constexpr int IT = 32 * CH / 64;     // pieces per lane
       int64_t r64[IT];
       f32x4 prev[IT];
 #pragma unroll
       for (int it = 0; it < IT; ++it) {
         const int idx = lane + 64 * it;
-        r64[it] = ep_rows[row0 + idx / CH];
+        r64[it] = ep_rows[idx / CH];
         prev[it] = (f32x4){0.f, 0.f, 0.f, 0.f};
       }
       if (add) {
@@ -556,8 +555,8 @@ __global__ __launch_bounds__(kBNT * NG, (D == 64 && MODE == kBwdDkvSamp) ? 3 : 2
 #pragma unroll
       for (int it = 0; it < IT; ++it) {
         const int idx = lane + 64 * it;
-        const int row = row0 + idx / CH, ch = idx % CH;
-        const f32x4 v = sums_at(row, ch * 16) + prev[it];
+        const int row = idx / CH, ch = idx % CH;
+        const f32x4 v = *reinterpret_cast<const f32x4*>(ep + row * L::EP_ROW + ch * 16) + prev[it];
         if (r64[it] >= 0) *reinterpret_cast<f32x4*>(dst32 + r64[it] * D + ch * 4) = v;
       }
       return;
@@ -589,14 +588,14 @@ __global__ __launch_bounds__(kBNT * NG, (D == 64 && MODE == kBwdDkvSamp) ? 3 : 2
     if (kHits && sums != nullptr) {  // (a row without a sample reads sample 0's sums and drops them)
 #pragma unroll
       for (int it = 0; it < IT8; ++it) {
-        const int idx = lane + 64 * it, j = first[row0 + idx / CH8];
+        const int idx = lane + 64 * it, j = first[idx / CH8];
         const float* pp = sums + (int64_t)(j != kNoSample ? j : 0) * D + (idx % CH8) * 8;
         p0[it] = *reinterpret_cast<const f32x4*>(pp);
         p1[it] = *reinterpret_cast<const f32x4*>(pp + 4);
       }
 #pragma unroll
       for (int it = 0; it < IT8; ++it) {
-        const bool none = first[row0 + (lane + 64 * it) / CH8] == kNoSample;
+        const bool none = first[(lane + 64 * it) / CH8] == kNoSample;
         const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
         p0[it] = none ? zero : p0[it];
         p1[it] = none ? zero : p1[it];

@@ -294,7 +294,8 @@ int ha_merge_unpermute(const float* o_b, const float* lse_b, const float* o_r, c
  * (host, 8 floats) receives the times between events on the stream: delta, dQ
  * of the nodes, dQ of the base case (unmasked problems: 0), dK/dV of the block
  * keys, dK/dV of the sampled keys with their reduction, dK/dV of the base case, 0 (the passes write the final
- * tensors themselves), total.  Small fp32 causal problems, whose passes share launches: the second value is 0, the third
+ * tensors themselves), total.  Unmasked problems and causal ones with n <= n_min (but fp32 tensors at d = 128) form delta in the one
+ * dQ pass: the first value is 0 and that pass's holds both.  Small fp32 causal problems, whose passes share launches: the second value is 0, the third
  * the base case with the sampled keys, the fourth all node passes, the fifth the samples' sums, the sixth 0.
  *
  * exact_attn_backward: gradients of exact_attn_forward (Section 1.1; causal:
@@ -303,7 +304,8 @@ int ha_merge_unpermute(const float* o_b, const float* lse_b, const float* o_r, c
 typedef struct {
   size_t delta;                      /* fp32 [B*H][n] */
   size_t acc_a, acc_b;               /* fp32 [B*H][n][d] each: the node parts' rows, added up level by level
-                                        (acc_a: dQ, afterwards dK; acc_b: dV); empty for unmasked problems */
+                                        (acc_a: dQ, afterwards dK; acc_b: dV); empty for unmasked problems,
+                                        not used by small fp32 causal ones, whose gradients hold the sums */
   size_t samp_k, samp_v;             /* fp32 rows of the sampled keys per (level, head, node, query chunk, sample) */
   size_t total_bytes;
 } ha_bwd_ws_layout;
@@ -331,8 +333,8 @@ size_t exact_attn_backward_workspace_bytes(const ha_shape* shape);
 /* ------------------------------------------------------------------------
  * Algorithm 2 as printed and Lemma 2 / Algorithm 3, as options (the Section 4
  * form above leaves them out); both dtypes (bf16 tensors on the matrix cores,
- * weights rounded to bf16 as operands like in the forward; fp32 tensors in
- * plain fp32 arithmetic).  Causal problems run them at every off-diagonal node of
+ * weights rounded to bf16 as operands like in the forward; fp32 tensors with
+ * fp32 products and sums).  Causal problems run them at every off-diagonal node of
  * Algorithm 4 ("the unmasked algorithm on Q_2, K_1"): below, n is then the
  * node's size s, every node has its own subset T, index set and value rows
  * (counters offset by the node's heap index 2^level - 1 + node), the diagonal

@@ -224,8 +224,8 @@ __global__ __launch_bounds__(64 * kTauWaves, 2) void alg2_tau_kernel(Alg2Args a)
   }
 }
 
-// log tau = the largest log unmasked row sum over the rows of T, one workgroup per head; where the
-// sums came in over ranges of keys they are added up first (and kept in log_unm_t).
+// log tau = the largest log unmasked row sum over the rows of T, one workgroup per head; the sums over ranges of keys are
+// added up first (and kept in log_unm_t).
 __global__ __launch_bounds__(256) void alg2_tau_max_kernel(Alg2Args a) {
   __shared__ float red[256];
   const Geometry& g = a.g;

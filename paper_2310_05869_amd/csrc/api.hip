@@ -17,13 +17,14 @@
 // Launch sequence of hyperattn_backward (gradients of the above with the random
 // draws held fixed; every (query, key) pair that occurs contributes on its own,
 // given the final log row sums and delta = <dO, O>):
-//   delta       row dots of dO and the forward's output (unmasked problems: in the dQ pass)
+//   delta       row dots of dO and the forward's output (one dQ pass, but fp32 at d = 128: in it)
 //   dQ          node passes, level by level (query tiles over their key lists),
 //               into one accumulated fp32 row per query; then the base-case
 //               pass, which adds that row and writes dQ
 //   dK, dV      block keys of every node, level by level, into accumulated rows;
 //               sampled keys of every node (partial sums per query chunk) and
-//               their ordered reduction into the same rows, level by level;
+//               their ordered reduction into the same rows, small problems all
+//               levels at once, else level by level;
 //               then the base-case pass, which adds the rows and writes dK, dV
 // (unmasked problems: the one node's passes write the gradients; its sampled keys come before its block keys)
 #include <cmath>
@@ -309,13 +310,15 @@ static AttnArgs node_args(const void* Q, const void* K, const void* V, void* out
 // of a workgroup's life at 4096 keys and twice that at 8192, against a sorting launch of 6.5 to 8 us and 2.5 us of the host's time for
 // it: worth it while the workgroups fit the chip about once and the codes they count are few.  Forward, sorting launch -> in the
 // attention (MI355X, us; workgroups):
-//   bf16, d = 64: 8 heads, n = 4096 (256) 26.7 -> 23.9, 12 (384) 30.8 -> 29.5, 16 (512) 32.1 -> 30.7, 32 (1024) 48.6 -> 52.1; 32 heads,
-//     n = 2048 (512) 31.0 -> 30.6; 64 heads, n = 1024 (512) 30.7 -> 31.1; 16 heads, n = 1024, b = m = 64 (256) 22.6 -> 18.8; 4 heads,
-//     n = 8192 (256) 26.9 -> 25.2, 6 (384) 31.5 -> 31.6, 12 (768) 42.3 -> 49.3; causal, 12 heads, n = 8192 (384) 111.8 -> 110.1
-//   bf16, d = 128: 8 heads, n = 4096 (256) 34.1 -> 31.8, 12 (384) 42.9 -> 41.5, 16 (512) 45.1 -> 44.5; 32 heads, n = 2048 (512) 43.8 -> 44.2; 64
-//     heads, n = 1024 (512) 43.2 -> 44.4; 4 heads, n = 8192 (256) 35.0 -> 33.4; 15 heads, n = 6300, b = 100, m = 77 (945) 52.8 -> 61.8
-//   fp32, d = 64: one head, n = 1024, b = m = 64 (32) 21.3 -> 19.5; 8 heads, n = 4096, b = m = 64 (1024) 42.8 -> 39.5, 16 (2048) 69.7 -> 71.8;
-//     d = 128: 16 heads, n = 2048 (512) 116.7 -> 115.1; 8 heads, n = 8192, b = m = 128 (512) 141.5 -> 141.0
+//   bf16, d = 64: 8 heads, n = 4096 (256) 26.5 -> 24.7, 12 (384) 30.2 -> 28.5, 16 (512) 33.0 -> 31.2, 32 (1024) 48.5 -> 50.2; 32 heads,
+//     n = 2048 (512) 31.8 -> 30.2; 64 heads, n = 1024 (512) 31.4 -> 29.3; 16 heads, n = 1024, b = m = 64 (256) 18.4 -> 15.4; 4 heads,
+//     n = 8192 (256) 26.5 -> 25.2, 6 (384) 30.8 -> 30.3, 12 (768) 41.5 -> 47.9; causal, 12 heads, n = 8192 (384) 112.0 -> 110.6
+//   bf16, d = 128: 8 heads, n = 4096 (256) 33.8 -> 31.7, 12 (384) 42.0 -> 40.1; 4 heads, n = 8192 (256) 34.8 -> 33.0; 15 heads, n = 6300,
+//     b = 100, m = 77 (945) 51.8 -> 55.5
+//   fp32, d = 64, b = m = 64: one head, n = 1024 (32) 21.2 -> 18.5; 8 heads, n = 4096 (512) 40.3 -> 36.4, 16 (1024) 66.7 -> 63.7; d = 128:
+//     16 heads, n = 2048, b = m = 64 (512) 60.9 -> 60.0; 8 heads, n = 8192, b = m = 128 (512) 136.0 -> 135.9
+// (The limits were set when small nodes still sorted on one wave; past them d = 128 now gains at 512 workgroups too: 16 heads, n = 4096
+// 46.1 -> 43.8, 64 heads, n = 1024 44.4 -> 42.6.)
 static bool sort_in_attention(const Geometry& g) {
   const int rows = node_sort_rows(g);
   if (rows > kNodeSortMax) return false;

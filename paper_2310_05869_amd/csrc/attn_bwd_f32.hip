@@ -20,8 +20,9 @@
 //
 // What bounds it: the matrix pipe where the chip is full.  At 4 heads, n = 4096 (at most two waves per SIMD) it is busy
 // 52 - 57 % of the cycles in the exact passes and 14 - 24 % in the node passes; waves wait for issue 55 - 65 % of their
-// time in the former.  The dK / dV passes at d = 64 spill 56 to 92 bytes per lane (two fragments in flight beside rows and
-// accumulators in 256 registers).
+// time in the former.  The dK / dV passes at d = 64 spill 56 to 108 bytes per lane (two fragments in flight beside rows and
+// accumulators in 256 registers), the launches that small causal problems share 144 (base case) and 64 (a level): one allocation serves all
+// their passes.
 // Measured (MI355X, backward of exact attention, the five algorithmic products
 // counted, seven executed), against two lanes per row with fp32 FMA and separate dK and dV passes, the form before:
 // 8 heads, n = 4096, d = 64 5.5 -> 1.29 ms, d = 128 12.0 -> 2.4 ms; 32 heads, n = 8192, d = 64 17.1 ms = 80 TFLOP/s

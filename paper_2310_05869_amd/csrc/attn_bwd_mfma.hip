@@ -643,6 +643,8 @@ static int launch_bwd_form(const BwdArgs& args, int grid, hipStream_t st) {
 //     64 heads, n = 512 (256) 65.5 -> 62.9, 96 (384) 75.3 -> 82.4
 //   unmasked, n = 8192: 4 heads (256) d = 64 362 -> 336, d = 128 601 -> 569, 5 heads (320) 540 -> 587, 888 -> 937; 51 heads, n = 640
 //     (255): d = 64 50.2 -> 48.6, d = 128 77.8 -> 79.3; 64 heads, n = 384 (192): 36.9 -> 36.6, 55.0 -> 55.3
+// Errors against 64 bits, forward and backward of one group each -> of two (12 causal heads, n = 5000, d = 128): dQ 2.387e-3 -> 2.386e-3, dK
+// 2.364e-3 -> 2.365e-3, dV 2.306e-3 both.
 constexpr int kSplitBwdMinRows = 512;
 static bool split_bwd_exact(const BwdArgs& a, int grid) {
   const int rows = a.f.exact_block < a.f.exact_rows_q ? a.f.exact_block : a.f.exact_rows_q;

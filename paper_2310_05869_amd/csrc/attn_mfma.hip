@@ -248,7 +248,8 @@ __global__ __launch_bounds__(64 * NW * NG, (D == 64 && NW == 4 && NG == 1) ? 3 :
   // cycles, vector issue 50 against 44 % of them; 414 to 487 us, by the clock of the run, where a kernel of its own without
   // the software pipeline below took 600).  At d = 64 the 168 registers that three workgroups per CU leave cost it 40 bytes of scratch
   // per lane, at d = 128 the 256 of two 16.  (With the masked and the capped sum on m_run, 20 and none, rows of clustered inputs lost log d~ to
-  // underflow; calls of 32 heads, n = 32768 with it -> without: d = 128 623 -> 622 us, d = 64 370 -> 367.)
+  // underflow; calls of 32 heads, n = 32768 with it -> without, three sessions: d = 128 623 -> 622, 622 -> 623, 627 -> 629 us, d = 64 370 -> 367,
+  // 376 -> 376.)
   const int nb_tiles = kCap ? (nb + kKT - 1) / kKT : 0;
   float log_masked = -INFINITY, log2capw = INFINITY;  // log2 of (s / m) C_i
   constexpr float kFarCap = 60.f;  // a term that underflows against m_run is then 2^-66 of the cap or less
@@ -829,6 +830,9 @@ constexpr int kWideExactMinRows = 8192;
 //     93.6; 19 heads (456), n = 3072 63.4 -> 60.9, 21 (504) 65.8 -> 67.1; 28 heads (448), n = 2048 43.5 -> 42.8, 32 (512) 45.5 -> 45.1; 32
 //     heads (384), n = 1536 33.1 -> 30.4, 37 (444) 38.5 -> 39.1; 40 heads (320), n = 1024 24.4 -> 22.0, 48 (384) 25.0 -> 25.8; 51
 //     heads (255), n = 640 18.6 -> 18.3, 64 (320) 18.4 -> 19.6
+// The groups' references differ, so weights are rounded to bf16 at other points than in the one-group form: results differ by 1.8e-3 (2-norm; 12
+// causal heads, n = 5000, d = 128; unmasked, 4 heads, n = 4096, 2.5e-3), errors against 64 bits do not: 2.13e-3 -> 2.10e-3, 2.334e-3 ->
+// 2.331e-3.
 constexpr int kSplitExactMinRows = 640;
 static bool split_exact(const AttnArgs& a) {
   const int rows = a.exact_block < a.exact_rows_q ? a.exact_block : a.exact_rows_q;

@@ -278,7 +278,7 @@ int launch_attn_bwd_f32_level(const BwdArgs& block, const BwdArgs& dq, hipStream
 // delta_i = <dO_i, O_i>; bf16 tensors: O from its unrounded fp32 copy when O_f32 is non-null, else from the tensor
 int launch_bwd_delta(const void* O, const float* O_f32, const void* dO, float* delta, int64_t rows, int d, int dtype,
                      hipStream_t st);
-// causal: adds the sampled keys' sums of one level into the accumulated key rows acc_k / acc_v [BH][n][d]
+// causal: adds the sampled keys' sums of all levels into the accumulated key rows acc_k / acc_v [BH][n][d]
 int launch_bwd_sample_scatter(const BwdArgs& a, const float* samp_k, const float* samp_v, float* acc_k, float* acc_v, hipStream_t st);
 // unmasked: the sampled keys' rows summed over the query chunks, into those of the first chunk
 int launch_bwd_sample_reduce(const BwdArgs& a, float* samp_k, float* samp_v, hipStream_t st);

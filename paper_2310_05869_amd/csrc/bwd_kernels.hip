@@ -1,5 +1,5 @@
 // Small kernels around the backward passes: delta_i = <dO_i, O_i>, and the ordered reduction of the sampled keys'
-// gradients: of one level into the accumulated key rows (causal), over the query chunks (unmasked).
+// gradients: of all levels or one into the accumulated key rows (causal), over the query chunks (unmasked).
 // Every sum is taken in a fixed order: results are bit-reproducible.
 #include "attn_common.h"
 #include "bwd_common.h"

@@ -373,6 +373,8 @@ typedef struct {
   size_t vnorm_samples;      /* per node, int32 [B*H][total_nodes][m]: l'_r (node-local) */
   size_t vnorm_logw;         /* per node, float [B*H][total_nodes][m]: log(1 / (m p_{l'_r})) */
   size_t log_unmasked_parts; /* per level, float [8][B*H * nodes][m]: scratch, the unmasked row sums of T over eight ranges of keys */
+  size_t part_ref;           /* causal, float [levels][B*H][n_cov]: log of the scale that the rows of part_o are taken against: log d~
+                                (part_l), or the largest weight's where that is larger */
   size_t total_bytes;
 } ha_alg2_ws_layout;
 

@@ -19,6 +19,7 @@ struct Alg2Args {
   const void* V;
   void* out;               // [view][d]: the final output (unmasked) or the level's partial outputs
   float* lse;              // [view]: log d~
+  float* part_ref;         // [view]: log of the scale of the partial rows (AttnArgs::part_ref); null: log d~
   Geometry g;
   int32_t n_full;          // rows per head of Q, K, V
   int32_t nodes;           // nodes per head at this level (1 for the unmasked problem)

@@ -439,9 +439,13 @@ __global__ __launch_bounds__(kA2NT, 2) void alg2_mfma_kernel(Alg2Args a) {
   // ---- results ----
   if (g.m == 0) log_masked = end_segment();
   const float log_dt = logaddexpf(log_masked, fmaxf(log_d, floor_term));   // d~_i = masked + max(d_i, tau / kappa)
-  const float f = (m_run == -INFINITY || log_dt == -INFINITY) ? 0.f : expf(m_run * kLn2 - log_dt);
+  const float ref = a.part_ref != nullptr && log_dt != -INFINITY ? fmaxf(log_dt, m_run * kLn2) : log_dt;
+  const float f = (m_run == -INFINITY || log_dt == -INFINITY) ? 0.f : expf(m_run * kLn2 - ref);
   const int64_t out_row = hb + (qrow - nd.q_start);
-  if (valid && h == 0) a.lse[out_row] = log_dt;
+  if (valid && h == 0) {
+    a.lse[out_row] = log_dt;
+    if (a.part_ref != nullptr) a.part_ref[out_row] = ref;
+  }
 
   // the wave's 32 rows leave through an fp32 LDS transpose as whole 16-byte pieces
   unsigned char* ep = smem + wave * L::EP_WAVE;

@@ -271,9 +271,11 @@ static AttnArgs base_case_args(const void* Q, const void* K, const void* V, void
 }
 
 static int run_base_case(const void* Q, const void* K, const void* V, void* out, float* lse, float* out_f32,
-                         const Geometry& g, void* part_o, float* part_l, hipStream_t st, long long* stamps = nullptr) {
+                         const Geometry& g, void* part_o, float* part_l, hipStream_t st, long long* stamps = nullptr,
+                         float* part_ref = nullptr) {
   AttnArgs a = base_case_args(Q, K, V, out, lse, out_f32, g, part_o, part_l);
   a.stamps = stamps;
+  a.part_ref = part_ref;
   return run_attention(a, kModeExact, st);
 }
 
@@ -654,6 +656,7 @@ static void fill_alg2_layout(const Geometry& g, const ha_ws_layout& fwd, ha_alg2
   l->vnorm_samples = take(nodes_all * g.m * 4);
   l->vnorm_logw = take(nodes_all * g.m * 4);
   l->log_unmasked_parts = take((size_t)kAlg2TauSplits * g.BH * max_nodes * g.m * 4);
+  l->part_ref = take(g.causal ? g.levels * view * 4 : 0);
   l->total_bytes = off;
 }
 
@@ -1088,6 +1091,7 @@ int hyperattn_forward_alg2(const void* Q, const void* K, const void* V, void* ou
   unsigned char* base = (unsigned char*)workspace;
   void* part_o = (void*)(base + lay.part_o);
   float* part_l = (float*)(base + lay.part_l);
+  float* part_ref = g.causal && g.levels > 0 ? (float*)(base + al.part_ref) : nullptr;
   if (g.levels > 0) {
     // hash, sort and draws exactly as the forward does them
     float* proj = (float*)(base + lay.proj);
@@ -1116,6 +1120,7 @@ int hyperattn_forward_alg2(const void* Q, const void* K, const void* V, void* ou
       a.V = V;
       a.out = g.causal ? (void*)((unsigned char*)part_o + lvl * g.d * esz) : out;
       a.lse = g.causal ? part_l + lvl : lse;
+      a.part_ref = g.causal ? part_ref + lvl : nullptr;
       a.g = g;
       a.g.BH = g.BH * nodes;
       a.g.n = s_rows;
@@ -1154,11 +1159,12 @@ int hyperattn_forward_alg2(const void* Q, const void* K, const void* V, void* ou
       a.kappa = opt->kappa;
       a.vsamp = (const int32_t*)(base + al.vnorm_samples);
       a.vlogw = (const float*)(base + al.vnorm_logw);
+      a.part_ref = part_ref;
       rc = run_attention(a, opt->vnorm_sampling ? kModeValue : kModeCap, st);
       if (rc != HA_OK) return rc;
     }
   }
-  if (g.causal) return run_base_case(Q, K, V, out, lse, nullptr, g, part_o, part_l, st);
+  if (g.causal) return run_base_case(Q, K, V, out, lse, nullptr, g, part_o, part_l, st, nullptr, part_ref);
   return HA_OK;
 }
 

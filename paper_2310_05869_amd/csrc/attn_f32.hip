@@ -413,9 +413,11 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
     }
     const bool empty = !(l > 0.f);
     float lse = empty ? -INFINITY : add_log(kCap ? dmx : mx, l);
+    float ref = lse;  // of a partial row
     if constexpr (kCap) {  // d~_i = masked + max(d_i, tau / kappa)
       lse = logaddexpf(ml[(w0 * 32 + (r & 31)) * ML + 3], fmaxf(lse, floor_term));
-      acc *= (mx == -INFINITY || lse == -INFINITY) ? 0.f : expf(mx - lse);
+      ref = to_partial && a.part_ref != nullptr && lse != -INFINITY ? fmaxf(lse, mx) : lse;
+      acc *= (mx == -INFINITY || lse == -INFINITY) ? 0.f : expf(mx - ref);
     } else {
       acc *= empty ? 0.f : 1.f / l;
     }
@@ -432,6 +434,7 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
     if (to_partial) {
       *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(a.part_o) + dest.part_row * D + col) = acc;
       if (col == 0) a.part_l[dest.part_row] = lse;
+      if (kCap && col == 0 && a.part_ref != nullptr) a.part_ref[dest.part_row] = ref;
       continue;
     }
     if (MODE == kModeExact && a.merge_levels > 0) {
@@ -443,7 +446,8 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
         if (!level_touches(a.g, w.bh, dest.row_in_head, l2, &pr)) continue;
         const float lp = a.part_l[pr];
         if (lp == -INFINITY) continue;
-        acc += (expf(lp - rmx) / den) * *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(a.part_o) + pr * D + col);
+        const float rp = a.part_ref != nullptr ? a.part_ref[pr] : lp;
+        acc += (expf(rp - rmx) / den) * *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(a.part_o) + pr * D + col);
       }
       lse = Lm;
     }

@@ -545,7 +545,12 @@ __global__ __launch_bounds__(64 * NW * NG, (D == 64 && NW == 4 && NG == 1) ? 3 :
   float lse_own = empty ? -INFINITY : (sum_ref(m_run) + log2f(l_tot)) * kLn2;
   if constexpr (kCap) {  // d~_i = masked + max(d_i, tau / kappa)
     lse_own = logaddexpf(log_masked, fmaxf(lse_own, floor_term));
-    inv = (m_run == -INFINITY || lse_own == -INFINITY) ? 0.f : expf(m_run * kLn2 - lse_own);
+    float ref = lse_own;
+    if (a.part_ref != nullptr) {
+      if (lse_own != -INFINITY) ref = fmaxf(lse_own, m_run * kLn2);
+      if (dest.valid && h == 0) a.part_ref[dest.part_row] = ref;
+    }
+    inv = (m_run == -INFINITY || lse_own == -INFINITY) ? 0.f : expf(m_run * kLn2 - ref);
   }
   // Where the row goes: a partial result of the causal recursion (node mode) or
   // the final output; in exact mode the partial results of every level of
@@ -601,6 +606,11 @@ __global__ __launch_bounds__(64 * NW * NG, (D == 64 && NW == 4 && NG == 1) ? 3 :
       w_own = e_own * rden;
 #pragma unroll
       for (int u = 0; u < kMaxFold; ++u) wl[u] *= rden;
+      if (a.part_ref != nullptr) {
+#pragma unroll
+        for (int u = 0; u < kMaxFold; ++u)
+          if (((touched >> u) & 1u) && dest.valid) wl[u] = expf(a.part_ref[pr0[u] + lq] - mx) * rden;
+      }
       lse_own = mx + logf(den);
     }
     scale_own = inv * w_own;
@@ -633,7 +643,7 @@ __global__ __launch_bounds__(64 * NW * NG, (D == 64 && NW == 4 && NG == 1) ? 3 :
       if (!level_touches(a.g, w.bh, dest.row_in_head, l, &pr)) continue;
       const float lp = a.part_l[pr];
       if (lp == -INFINITY) continue;
-      const float wl = expf(lp - mx) / den;
+      const float wl = expf((a.part_ref != nullptr ? a.part_ref[pr] : lp) - mx) / den;
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt)
 #pragma unroll

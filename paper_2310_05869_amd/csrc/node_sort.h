@@ -57,25 +57,31 @@ constexpr int kNodeSortMax = 32 * 64 * kNodeSortWaves;  // keys of a node: 32 pe
 
 __host__ __device__ inline int node_sort_rows(const Geometry& g) { return ((g.causal ? g.n >> 1 : g.n) + 63) & ~63; }
 
+typedef uint32_t words4 __attribute__((ext_vector_type(4)));
+
+constexpr int kNodeSortBuckets = 256;
+
 struct NodeSortLds {
-  uint32_t* rel;               // [2][rows] keys of the buckets that touch the range, wave by wave: bucket << 16 | index in the node
+  uint8_t* codes;              // [2][rows] the keys' buckets (a wave reads only what its own lanes wrote)
+  uint16_t* rel;               // [2][rows] keys of the buckets that touch the range, wave by wave: index in the node
+  uint32_t* count;             // [2][wave pairs][kNodeSortBuckets] two waves' counts in a word
+  uint32_t* pos;               // [waves][kNodeSortBuckets] sorted position of a wave's next key, queries | keys << 16
   unsigned long long* peers;   // [2][waves][buckets]
-  uint32_t* count;             // [2][waves][buckets] (bucket by bucket over the banks)
   uint32_t* member;            // [rows / 32] bits: keys of the workgroup's block
-  uint32_t* limits;            // first and last of those buckets, queries and keys
 };
 __host__ __device__ inline size_t node_sort_lds_bytes(const Geometry& g) {
   const size_t rows = node_sort_rows(g), buckets = (size_t)1 << g.r;
-  return 8 * rows + 2 * kNodeSortWaves * buckets * 12 + rows / 8 + 16;
+  return 6 * rows + (2 * kNodeSortWaves / 2 + kNodeSortWaves) * kNodeSortBuckets * 4 + 2 * kNodeSortWaves * buckets * 8 + rows / 8;
 }
 __device__ inline NodeSortLds node_sort_lds(const Geometry& g, unsigned char* sm) {
   const int rows = node_sort_rows(g), buckets = 1 << g.r;
   NodeSortLds l;
-  l.rel = reinterpret_cast<uint32_t*>(sm);
-  l.peers = reinterpret_cast<unsigned long long*>(sm + 8 * rows);
-  l.count = reinterpret_cast<uint32_t*>(l.peers + 2 * kNodeSortWaves * buckets);
-  l.member = l.count + 2 * kNodeSortWaves * buckets;
-  l.limits = l.member + rows / 32;
+  l.codes = sm;
+  l.rel = reinterpret_cast<uint16_t*>(sm + 2 * rows);
+  l.count = reinterpret_cast<uint32_t*>(sm + 6 * rows);
+  l.pos = l.count + 2 * kNodeSortWaves / 2 * kNodeSortBuckets;
+  l.peers = reinterpret_cast<unsigned long long*>(l.pos + kNodeSortWaves * kNodeSortBuckets);
+  l.member = reinterpret_cast<uint32_t*>(l.peers + 2 * kNodeSortWaves * buckets);
   return l;
 }
 
@@ -99,7 +105,6 @@ __device__ inline void sort_node_tile(const AttnArgs& a, const TileWork& w, unsi
   const NodeSortLds l = node_sort_lds(g, sm);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int s = w.nr.s, rows = node_sort_rows(g), buckets = 1 << g.r;
-  const uint32_t code_mask = (uint32_t)(buckets - 1);
   const int lo[2] = {w.p0, w.t * g.b}, hi[2] = {w.p0 + w.rows_valid, w.t * g.b + g.b};
   const bool first_tile = w.p0 == w.t * g.b;  // of its block: it writes the block's keys
 
@@ -118,60 +123,93 @@ __device__ inline void sort_node_tile(const AttnArgs& a, const TileWork& w, unsi
       v[t] = __builtin_shufflevector(lo4, hi4, 0, 1, 2, 3, 4, 5, 6, 7);
     }
   }
-  for (int i = tid; i < 2 * NW * buckets; i += NT) {
-    l.peers[i] = 0ull;
-    l.count[i] = 0u;
-  }
+  const words4 zero = {0u, 0u, 0u, 0u};
+  static_assert(NT * 4 == 2 * NW / 2 * kNodeSortBuckets);
+  reinterpret_cast<words4*>(l.count)[tid] = zero;
+  for (int i = tid; i < NW * buckets; i += NT) reinterpret_cast<words4*>(l.peers)[i] = zero;
   for (int i = tid; i < rows / 32; i += NT) l.member[i] = 0u;
   __syncthreads();
 
   const int left = s - i0;  // the thread's keys
+  const uint32_t code_bytes = (uint32_t)(buckets - 1) * 0x01010101u;
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[t][u] &= code_bytes;
+    if (left <= 0) continue;
+    uint32_t* dst = reinterpret_cast<uint32_t*>(l.codes + t * rows + i0);
+    if (wpt <= 2) {
+      dst[0] = v[t][0];
+      if (wpt == 2) dst[1] = v[t][1];
+    } else {
+      reinterpret_cast<words4*>(dst)[0] = (words4){v[t][0], v[t][1], v[t][2], v[t][3]};
+      if (wpt == 8) reinterpret_cast<words4*>(dst)[1] = (words4){v[t][4], v[t][5], v[t][6], v[t][7]};
+    }
+  }
   auto each_key = [&](auto&& f) {
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
       if (u >= wpt) break;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) f(4 * u + j, (v[0][u] >> (8 * j)) & code_mask, (v[1][u] >> (8 * j)) & code_mask);
+      for (int j = 0; j < 4; ++j) f(4 * u + j, (v[0][u] >> (8 * j)) & 255u, (v[1][u] >> (8 * j)) & 255u);
     }
   };
-  each_key([&](int j, uint32_t cq, uint32_t ck) {
-    if (j < left) {
-      atomicAdd(&l.count[wave * buckets + cq], 1u);
-      atomicAdd(&l.count[(NW + wave) * buckets + ck], 1u);
-    }
-  });
-  __syncthreads();
-
-  // counts to the sorted position of every wave's first key of a bucket, and the first and the last bucket that touch the
-  // range: wave 0 for the queries, 1 for the keys
-  if (wave < 2) {
-    uint32_t* count = l.count + wave * NW * buckets;
-    uint32_t c[NW][4], sum = 0;
-#pragma unroll
-    for (int ww = 0; ww < NW; ++ww)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        c[ww][j] = 4 * lane + j < buckets ? count[ww * buckets + 4 * lane + j] : 0u;
-        sum += c[ww][j];
+  uint32_t* count_q = l.count + (wave >> 1) * kNodeSortBuckets;
+  uint32_t* count_k = count_q + NW / 2 * kNodeSortBuckets;
+  const uint32_t one = 1u << (16 * (wave & 1));
+  if (64 * per * (wave + 1) <= s) {  // no key of the wave is past the end
+    each_key([&](int, uint32_t cq, uint32_t ck) {
+      atomicAdd(&count_q[cq], one);
+      atomicAdd(&count_k[ck], one);
+    });
+  } else {
+    each_key([&](int j, uint32_t cq, uint32_t ck) {
+      if (j < left) {
+        atomicAdd(&count_q[cq], one);
+        atomicAdd(&count_k[ck], one);
       }
-    uint32_t at = wave_scan(sum) - sum;
-    const uint32_t from = (uint32_t)lo[wave], to = (uint32_t)hi[wave];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const uint32_t bucket_at = at;
-#pragma unroll
-      for (int ww = 0; ww < NW; ++ww) {
-        if (4 * lane + j < buckets) count[ww * buckets + 4 * lane + j] = at;
-        at += c[ww][j];
-      }
-      if (bucket_at <= from && from < at) l.limits[2 * wave] = 4 * lane + j;
-      if (bucket_at < to && to <= at) l.limits[2 * wave + 1] = 4 * lane + j;
-    }
+    });
   }
   __syncthreads();
 
+  // Sorted position of the wave's first key of every bucket, queries and keys in the halves of a word (a node has up to 8192), and the
+  // first and the last bucket that touch the range.  Every wave forms them for itself: one wave for the queries and one for the keys had
+  // the others wait at a further barrier.
+  uint32_t b0[2] = {0u, 0u}, b1[2] = {0u, 0u};
+  {
+    const words4* tab = reinterpret_cast<const words4*>(l.count) + lane;
+    words4 c[2][2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int p = 0; p < 2; ++p) c[t][p] = tab[(2 * t + p) * (kNodeSortBuckets / 4)];
+    const uint32_t before0 = wave == 0 ? 0u : wave == 1 ? 0xffffu : ~0u, before1 = wave == 3 ? 0xffffu : 0u;  // earlier waves' halves
+    auto both_halves = [](uint32_t x) { return (x & 0xffffu) + (x >> 16); };
+    uint32_t all[4], sum = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      all[j] = both_halves(c[0][0][j] + c[0][1][j]) | both_halves(c[1][0][j] + c[1][1][j]) << 16;
+      sum += all[j];
+    }
+    uint32_t at = wave_scan(sum) - sum;
+    words4 first;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      first[j] = at + (both_halves((c[0][0][j] & before0) + (c[0][1][j] & before1)) |
+                       both_halves((c[1][0][j] & before0) + (c[1][1][j] & before1)) << 16);
+      at += all[j];
+      const uint32_t end[2] = {at & 0xffffu, at >> 16};
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        b0[t] += __popcll(__ballot(end[t] <= (uint32_t)lo[t]));
+        b1[t] += __popcll(__ballot(end[t] < (uint32_t)hi[t]));
+      }
+    }
+    reinterpret_cast<words4*>(l.pos)[wave * (kNodeSortBuckets / 4) + lane] = first;
+  }
+
   // the wave's keys of those buckets, in order, to rel
-  const uint32_t b0[2] = {l.limits[0], l.limits[2]}, span[2] = {l.limits[1] - l.limits[0], l.limits[3] - l.limits[2]};
+  const uint32_t span[2] = {b1[0] - b0[0], b1[1] - b0[1]};
   uint32_t hit[2] = {0u, 0u};  // bits: the thread's keys
   each_key([&](int j, uint32_t cq, uint32_t ck) {
     hit[0] |= (cq - b0[0] <= span[0] ? 1u : 0u) << j;
@@ -180,20 +218,18 @@ __device__ inline void sort_node_tile(const AttnArgs& a, const TileWork& w, unsi
   const uint32_t real = left >= 32 ? ~0u : left > 0 ? (1u << left) - 1u : 0u;
   int n[2];
   {
-    const uint32_t mine = __popc(hit[0] & real) | __popc(hit[1] & real) << 16;
+    uint32_t bits_q = hit[0] & real, bits_k = hit[1] & real;
+    const uint32_t mine = __popc(bits_q) | __popc(bits_k) << 16;
     const uint32_t incl = wave_scan(mine), total = __builtin_amdgcn_readlane(incl, 63), at = incl - mine;
     n[0] = (int)(total & 0xffffu);
     n[1] = (int)(total >> 16);
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      uint32_t* dst = l.rel + t * rows + min(64 * per * wave, rows) + (t ? at >> 16 : at & 0xffffu);
-      for (uint32_t bits = hit[t] & real; bits; bits &= bits - 1) {
-        const int j = __builtin_ctz(bits);
-        const uint32_t w0 = j & 4 ? v[t][1] : v[t][0], w1 = j & 4 ? v[t][3] : v[t][2];
-        const uint32_t w2 = j & 4 ? v[t][5] : v[t][4], w3 = j & 4 ? v[t][7] : v[t][6];
-        const uint32_t word = j & 16 ? (j & 8 ? w3 : w2) : (j & 8 ? w1 : w0);
-        *dst++ = ((word >> (8 * (j & 3))) & code_mask) << 16 | (uint32_t)(i0 + j);
-      }
+    uint16_t* dst_q = l.rel + min(64 * per * wave, rows) + (at & 0xffffu);
+    uint16_t* dst_k = l.rel + rows + min(64 * per * wave, rows) + (at >> 16);
+    while (bits_q | bits_k) {
+      if (bits_q) *dst_q++ = (uint16_t)(i0 + __builtin_ctz(bits_q));
+      if (bits_k) *dst_k++ = (uint16_t)(i0 + __builtin_ctz(bits_k));
+      bits_q &= bits_q - 1;
+      bits_k &= bits_k - 1;
     }
   }
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -203,14 +239,19 @@ __device__ inline void sort_node_tile(const AttnArgs& a, const TileWork& w, unsi
   // sorted positions: a key's place among the equal keys of its 64 from the lanes' bits in a word per bucket
   const unsigned long long lane_bit = 1ull << lane;
   const int most = n[0] > n[1] ? n[0] : n[1];
+  uint16_t* next = reinterpret_cast<uint16_t*>(l.pos + wave * kNodeSortBuckets);
   for (int k0 = 0; k0 < most; k0 += 64) {
-    uint32_t e[2];
+    uint32_t i[2], c[2];
     bool valid[2];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
       valid[t] = k0 + lane < n[t];
-      e[t] = valid[t] ? l.rel[t * rows + 64 * per * wave + k0 + lane] : 0u;
-      if (valid[t]) atomicOr(&l.peers[(t * NW + wave) * buckets + (e[t] >> 16)], lane_bit);
+      i[t] = valid[t] ? l.rel[t * rows + 64 * per * wave + k0 + lane] : 0u;
+    }
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      c[t] = l.codes[t * rows + i[t]];
+      if (valid[t]) atomicOr(&l.peers[(t * NW + wave) * buckets + c[t]], lane_bit);
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -219,8 +260,8 @@ __device__ inline void sort_node_tile(const AttnArgs& a, const TileWork& w, unsi
     uint32_t seen[2];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-      pm[t] = l.peers[(t * NW + wave) * buckets + (e[t] >> 16)];
-      seen[t] = l.count[(t * NW + wave) * buckets + (e[t] >> 16)];
+      pm[t] = l.peers[(t * NW + wave) * buckets + c[t]];
+      seen[t] = next[2 * c[t] + t];
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -228,20 +269,19 @@ __device__ inline void sort_node_tile(const AttnArgs& a, const TileWork& w, unsi
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
       if (!valid[t]) continue;
-      const int c = (int)(e[t] >> 16), i = (int)(e[t] & 0xffffu);
       const uint32_t rank = __popcll(pm[t] & (lane_bit - 1ull)), cnt = __popcll(pm[t]);
       if (rank == cnt - 1) {  // one lane per distinct key
-        l.peers[(t * NW + wave) * buckets + c] = 0ull;
-        l.count[(t * NW + wave) * buckets + c] = seen[t] + cnt;
+        l.peers[(t * NW + wave) * buckets + c[t]] = 0ull;
+        next[2 * c[t] + t] = (uint16_t)(seen[t] + cnt);
       }
       const int p = (int)(seen[t] + rank);
       if (p < lo[t] || p >= hi[t]) continue;
       if (t == 0) {
-        qrows[p - lo[0]] = w.nr.q_start + i;
+        qrows[p - lo[0]] = w.nr.q_start + (int)i[t];
       } else {
-        list[p - lo[1]] = w.nr.k_start + i;
-        atomicOr(&l.member[i >> 5], 1u << (i & 31));
-        if (first_tile) a.pos_k_out[w.seg_off + i] = p;
+        list[p - lo[1]] = w.nr.k_start + (int)i[t];
+        atomicOr(&l.member[i[t] >> 5], 1u << (i[t] & 31));
+        if (first_tile) a.pos_k_out[w.seg_off + i[t]] = p;
       }
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");

@@ -59,7 +59,7 @@ __host__ __device__ inline size_t f32_lds_bytes(int b, int m, int mode) {
 template <int D>
 __host__ __device__ inline size_t f32_qrows_at(const Geometry& g) {
   const size_t list = ((size_t)(((g.b + g.m + 63) & ~63) + 64) * 4 + 64 + 15) & ~(size_t)15;
-  const size_t both = list + ((node_sort_lds_bytes(g) + 15) & ~(size_t)15);
+  const size_t both = list + ((node_sort_lds_bytes<4>(g) + 15) & ~(size_t)15);
   return both > (size_t)F32Lds<D>::BYTES ? both : (size_t)F32Lds<D>::BYTES;
 }
 
@@ -103,9 +103,9 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
     w = decode_node_tile<kQT>(a, bid);
     const int l0 = first_node_sample(a, w);
     unsigned char* sort_lds = reinterpret_cast<unsigned char*>(list) + (((((a.g.b + a.g.m + 63) & ~63) + 64) * 4 + 15) & ~15);
-    sort_node_tile(a, w, sort_lds, list, qrows);
+    sort_node_tile<4>(a, w, sort_lds, list, qrows);
     nb = a.g.b;
-    nkeys = append_node_samples(a, w, sort_lds, list, scratch, l0);
+    nkeys = append_node_samples<4>(a, w, sort_lds, list, scratch, l0);
   } else if (kNode) {
     w = decode_node_tile<kQT>(a, bid);
     nkeys = build_key_list<kFNT, kCap>(a, w, list, scratch, &nb, key_list_fetch<kFNT>(a, w));

@@ -71,9 +71,9 @@ __host__ __device__ inline size_t mfma_lds_bytes(int b, int m, int mode) {
 
 // SORT: the sort's tables lie where the tiles will, and push the list back where they are larger; the tile's query rows
 // lie behind the list
-template <int D>
+template <int D, int NW>
 __host__ __device__ inline size_t sort_pushes_list(const Geometry& g) {
-  const size_t sort = (node_sort_lds_bytes(g) + 15) & ~(size_t)15;
+  const size_t sort = (node_sort_lds_bytes<NW>(g) + 15) & ~(size_t)15;
   return sort > 2 * (size_t)Lds<D>::BUF ? sort - 2 * (size_t)Lds<D>::BUF : 0;
 }
 
@@ -109,7 +109,7 @@ __global__ __launch_bounds__(64 * NW * NG, (D == 64 && NW == 4 && NG == 1) ? 3 :
   const int lq = lane & 31, h = lane >> 5;
 
   unsigned char* bufs = smem + grp * 2 * L::BUF;
-  int32_t* scratch = reinterpret_cast<int32_t*>(smem + NG * 2 * L::BUF + (SORT ? sort_pushes_list<D>(a.g) : 0));
+  int32_t* scratch = reinterpret_cast<int32_t*>(smem + NG * 2 * L::BUF + (SORT ? sort_pushes_list<D, NW>(a.g) : 0));
   int32_t* list = scratch + 16;
   int32_t* qrows = list + (SORT ? list_capacity(a.g.b, a.g.m) : 0);
 
@@ -140,7 +140,7 @@ __global__ __launch_bounds__(64 * NW * NG, (D == 64 && NW == 4 && NG == 1) ? 3 :
   if (kNode && !SORT) klh = key_list_fetch<kNT>(a, w);
   if constexpr (SORT) {
     klh.l0 = first_node_sample(a, w);
-    sort_node_tile(a, w, smem, list, qrows);
+    sort_node_tile<NW>(a, w, smem, list, qrows);
   }
   const int r_in_tile = wave * 32 + lq;
   RowDest dest;
@@ -177,7 +177,7 @@ __global__ __launch_bounds__(64 * NW * NG, (D == 64 && NW == 4 && NG == 1) ? 3 :
   int nb, nkeys;
   if constexpr (SORT) {
     nb = a.g.b;
-    nkeys = append_node_samples(a, w, smem, list, scratch, klh.l0);
+    nkeys = append_node_samples<NW>(a, w, smem, list, scratch, klh.l0);
   } else if (kNode) {
     nkeys = build_key_list<kNT, kCap>(a, w, list, scratch, &nb, klh);
   } else {
@@ -789,7 +789,7 @@ static int launch_one(const AttnArgs& args, hipStream_t st) {
   if (grid > kMaxGrid) return HA_ERR_SHAPE;
   size_t lds = mfma_lds_bytes<D>(a.g.b, a.g.m, MODE) + (NG - 1) * 2 * (size_t)Lds<D>::BUF;
   const size_t ep = (size_t)NW * EpLds<D>::WAVE + (NG - 1) * (size_t)(D / 8 * 16 + 8) * 64 * NW;
-  if (SORT) lds += sort_pushes_list<D>(a.g) + 32 * NW * 4;
+  if (SORT) lds += sort_pushes_list<D, NW>(a.g) + 32 * NW * 4;
   if (lds < ep) lds = ep;
   static std::atomic<uint64_t> lds_set{0};  // per instantiation: devices on which the LDS limit is raised
   if (allow_full_lds(reinterpret_cast<const void*>(&attn_mfma_kernel<D, MODE, NW, STAMPS, NG, SORT>), lds_set) != HA_OK) return HA_ERR_LAUNCH;
@@ -854,6 +854,13 @@ static bool split_exact(const AttnArgs& a) {
 }
 constexpr int64_t kWideExactMinGrid = 129, kWideExactMinGridCausal = 1024;
 
+// Node launches that sort by themselves: with more than one workgroup of 128 rows per CU some CUs hold two, which count the same node twice
+// side by side and end last (33 k cycles of life where one has a CU, 43 k where two share it).  Where tiles of 256 rows fit
+// the chip once, eight waves do that work once per CU.  Four waves -> eight (MI355X, us; b = m = 256): d = 64: 12 heads, n = 4096 26.4 ->
+// 25.4, 9 heads 25.8 -> 24.8, 16 heads 27.9 -> 27.1; 64 heads, n = 1024 27.8 -> 27.1; 32 heads, n = 2048 28.2 -> 27.3; 8 heads, n = 3900,
+// b = 300 27.7 -> 26.2; d = 128: 12 heads, n = 4096 36.9 -> 35.4, 16 heads 43.4 both.
+static bool wide_sorting_node(const Geometry& g) { return node_grid<128>(g) > 256 && node_grid<256>(g) <= 256; }
+
 int64_t attn_mfma_grid(const AttnArgs& a, int mode) {
   return mode == kModeNode ? node_grid<32 * HA_NW_NODE>(a.g) : exact_grid<32 * HA_NW_EXACT>(a);
 }
@@ -873,10 +880,12 @@ int launch_attn_mfma(const AttnArgs& a, int mode, hipStream_t st) {
     }
     return HA_ERR_SHAPE;
   }
+  const bool wide_node = a.codes_q && wide_sorting_node(a.g);
   const bool wide = mode == kModeExact && a.merge_levels == 0 &&
                     a.exact_block >= kWideExactMinRows && a.exact_rows_q >= kWideExactMinRows &&
                     exact_grid<256>(a) >= (a.exact_causal ? kWideExactMinGridCausal : kWideExactMinGrid);
   if (a.g.d == 128) {
+    if (mode == kModeNode && wide_node) return launch_one<128, kModeNode, 8, false, 1, true>(a, st);
     if (mode == kModeNode && a.codes_q) return launch_one<128, kModeNode, 4, false, 1, true>(a, st);
     if (mode == kModeNode) return launch_one<128, kModeNode, HA_NW_NODE>(a, st);
     if (mode == kModeCap) return launch_one<128, kModeCap, HA_NW_NODE>(a, st);
@@ -884,6 +893,7 @@ int launch_attn_mfma(const AttnArgs& a, int mode, hipStream_t st) {
     return wide ? launch_one<128, kModeExact, 8>(a, st) : launch_one<128, kModeExact, HA_NW_EXACT>(a, st);
   }
   if (a.g.d == 64) {
+    if (mode == kModeNode && wide_node) return launch_one<64, kModeNode, 8, false, 1, true>(a, st);
     if (mode == kModeNode && a.codes_q) return launch_one<64, kModeNode, 4, false, 1, true>(a, st);
     if (mode == kModeNode) return launch_one<64, kModeNode, HA_NW_NODE>(a, st);
     if (mode == kModeCap) return launch_one<64, kModeCap, HA_NW_NODE>(a, st);

@@ -2,8 +2,11 @@
 // bucket codes, instead of reading them from a permutation that a launch ahead of it wrote.
 //
 // What bounds a small call is the number of dependent launches, each some 1.5 us before its first instruction and 2 us
-// until its first data has arrived, so a chain of LDS passes over the node's codes in every workgroup (2 to 3 us) beats a
-// sorting launch (6.5 to 8 us), though each workgroup counts the whole node.  A stable counting sort by bucket, of which
+// until its first data has arrived, so a chain of LDS passes over the node's codes in every workgroup (6 us with the codes' arrival
+// at 4096 keys) beats a sorting launch (6.5 to 8 us and the wait for it), though each workgroup counts the whole node.  Cycles of
+// that (four waves, 4096 keys, 128 buckets): 3.7 k until the codes are there, 2.7 k counting (the LDS atomics), 1.1 k positions, 2.2 k keys
+// of the range, 1.9 k ranks, 1.9 k samples and the last barriers; 17.5 k before two waves' counts shared a word and every wave
+// formed its own positions (forward, 12 heads, n = 4096, d = 64 28.1 -> 26.4 us; fp32, one head, n = 1024 18.5 -> 17.2).  A stable counting sort by bucket, of which
 // only what lies in the workgroup's range of sorted positions is carried out: all keys are counted, the range is found in
 // the bucket starts, and only keys of buckets that touch it are ranked.
 //
@@ -52,8 +55,7 @@ __device__ inline codes32 load_few_codes(const uint8_t* codes, int s, int t) {
   return v;
 }
 
-constexpr int kNodeSortWaves = 4;
-constexpr int kNodeSortMax = 32 * 64 * kNodeSortWaves;  // keys of a node: 32 per thread
+constexpr int kNodeSortMax = 32 * 64 * 4;  // keys of a node: 32 per thread of the smallest form, four waves
 
 __host__ __device__ inline int node_sort_rows(const Geometry& g) { return ((g.causal ? g.n >> 1 : g.n) + 63) & ~63; }
 
@@ -69,19 +71,21 @@ struct NodeSortLds {
   unsigned long long* peers;   // [2][waves][buckets]
   uint32_t* member;            // [rows / 32] bits: keys of the workgroup's block
 };
+template <int NW>  // waves of the workgroup: 4 or 8
 __host__ __device__ inline size_t node_sort_lds_bytes(const Geometry& g) {
   const size_t rows = node_sort_rows(g), buckets = (size_t)1 << g.r;
-  return 6 * rows + (2 * kNodeSortWaves / 2 + kNodeSortWaves) * kNodeSortBuckets * 4 + 2 * kNodeSortWaves * buckets * 8 + rows / 8;
+  return 6 * rows + (NW + NW) * kNodeSortBuckets * 4 + 2 * NW * buckets * 8 + rows / 8;
 }
+template <int NW>
 __device__ inline NodeSortLds node_sort_lds(const Geometry& g, unsigned char* sm) {
   const int rows = node_sort_rows(g), buckets = 1 << g.r;
   NodeSortLds l;
   l.codes = sm;
   l.rel = reinterpret_cast<uint16_t*>(sm + 2 * rows);
   l.count = reinterpret_cast<uint32_t*>(sm + 6 * rows);
-  l.pos = l.count + 2 * kNodeSortWaves / 2 * kNodeSortBuckets;
-  l.peers = reinterpret_cast<unsigned long long*>(l.pos + kNodeSortWaves * kNodeSortBuckets);
-  l.member = reinterpret_cast<uint32_t*>(l.peers + 2 * kNodeSortWaves * buckets);
+  l.pos = l.count + NW * kNodeSortBuckets;
+  l.peers = reinterpret_cast<unsigned long long*>(l.pos + NW * kNodeSortBuckets);
+  l.member = reinterpret_cast<uint32_t*>(l.peers + 2 * NW * buckets);
   return l;
 }
 
@@ -99,17 +103,19 @@ __device__ inline uint32_t wave_scan(uint32_t x) {
 
 // The tile's query rows to qrows[0 .. rows_valid) and its block's key rows to list[0 .. b), both rows within the head.
 // All threads call it; the results are visible on return.
+template <int NW>
 __device__ inline void sort_node_tile(const AttnArgs& a, const TileWork& w, unsigned char* sm, int32_t* list, int32_t* qrows) {
-  constexpr int NW = kNodeSortWaves, NT = 64 * NW;
+  constexpr int NT = 64 * NW;
+  static_assert(NW == 4 || NW == 8);
   const Geometry& g = a.g;
-  const NodeSortLds l = node_sort_lds(g, sm);
+  const NodeSortLds l = node_sort_lds<NW>(g, sm);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int s = w.nr.s, rows = node_sort_rows(g), buckets = 1 << g.r;
   const int lo[2] = {w.p0, w.t * g.b}, hi[2] = {w.p0 + w.rows_valid, w.t * g.b + g.b};
   const bool first_tile = w.p0 == w.t * g.b;  // of its block: it writes the block's keys
 
   // a thread's keys are consecutive, 4, 8, 16 or 32 by the node's size, and so are a wave's: with 16 from the smallest nodes on,
-  // one wave did the work of all (fp32, one head, n = 1024, forward: 19.4 -> 18.5 us; 64 heads, n = 1024, d = 64: 31.8 -> 28.9)
+  // one wave did the work of all
   const int wpt = s <= 4 * NT ? 1 : s <= 8 * NT ? 2 : s <= 16 * NT ? 4 : 8;  // words of four keys
   const int per = 4 * wpt, i0 = per * tid;
   codes32 v[2];
@@ -124,7 +130,7 @@ __device__ inline void sort_node_tile(const AttnArgs& a, const TileWork& w, unsi
     }
   }
   const words4 zero = {0u, 0u, 0u, 0u};
-  static_assert(NT * 4 == 2 * NW / 2 * kNodeSortBuckets);
+  static_assert(NT * 4 == NW * kNodeSortBuckets);
   reinterpret_cast<words4*>(l.count)[tid] = zero;
   for (int i = tid; i < NW * buckets; i += NT) reinterpret_cast<words4*>(l.peers)[i] = zero;
   for (int i = tid; i < rows / 32; i += NT) l.member[i] = 0u;
@@ -178,25 +184,29 @@ __device__ inline void sort_node_tile(const AttnArgs& a, const TileWork& w, unsi
   uint32_t b0[2] = {0u, 0u}, b1[2] = {0u, 0u};
   {
     const words4* tab = reinterpret_cast<const words4*>(l.count) + lane;
-    words4 c[2][2];
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int p = 0; p < 2; ++p) c[t][p] = tab[(2 * t + p) * (kNodeSortBuckets / 4)];
-    const uint32_t before0 = wave == 0 ? 0u : wave == 1 ? 0xffffu : ~0u, before1 = wave == 3 ? 0xffffu : 0u;  // earlier waves' halves
     auto both_halves = [](uint32_t x) { return (x & 0xffffu) + (x >> 16); };
+    words4 of[2] = {zero, zero}, before[2] = {zero, zero};  // counts of all waves and of the earlier ones, two waves to a word
+#pragma unroll
+    for (int p = 0; p < NW / 2; ++p) {
+      const uint32_t earlier = 2 * p + 1 < wave ? ~0u : 2 * p < wave ? 0xffffu : 0u;
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const words4 c = tab[(NW / 2 * t + p) * (kNodeSortBuckets / 4)];
+        of[t] += c;
+        before[t] += c & earlier;
+      }
+    }
     uint32_t all[4], sum = 0;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      all[j] = both_halves(c[0][0][j] + c[0][1][j]) | both_halves(c[1][0][j] + c[1][1][j]) << 16;
+      all[j] = both_halves(of[0][j]) | both_halves(of[1][j]) << 16;
       sum += all[j];
     }
     uint32_t at = wave_scan(sum) - sum;
     words4 first;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      first[j] = at + (both_halves((c[0][0][j] & before0) + (c[0][1][j] & before1)) |
-                       both_halves((c[1][0][j] & before0) + (c[1][1][j] & before1)) << 16);
+      first[j] = at + (both_halves(before[0][j]) | both_halves(before[1][j]) << 16);
       at += all[j];
       const uint32_t end[2] = {at & 0xffffu, at >> 16};
 #pragma unroll
@@ -296,11 +306,12 @@ __device__ inline void sort_node_tile(const AttnArgs& a, const TileWork& w, unsi
 
 // Appends the kept samples to the block's keys (build_key_list's list): those that are no keys of the block.  All threads call
 // it behind sort_node_tile; on return the list is whole and sm is read no more.  `l0` = sample threadIdx.x, fetched ahead.
+template <int NW>
 __device__ inline int append_node_samples(const AttnArgs& a, const TileWork& w, unsigned char* sm, int32_t* list,
                                           int32_t* scratch, int l0) {
-  constexpr int NW = kNodeSortWaves, NT = 64 * NW;
+  constexpr int NT = 64 * NW;
   const Geometry& g = a.g;
-  const uint32_t* member = node_sort_lds(g, sm).member;
+  const uint32_t* member = node_sort_lds<NW>(g, sm).member;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int m = a.samples != nullptr ? g.m : 0;
   const bool first_tile = w.p0 == w.t * g.b;

@@ -32,6 +32,14 @@ CASES = [  # dtype, d, B, H, n, b, m, r, n_min (0: unmasked)
     ("bf16", 64, 1, 3, 5005, 77, 50, 7, 0),        # 32 keys
     ("bf16", 64, 1, 2, 8192, 128, 96, 7, 1024),    # three levels
     ("bf16", 128, 1, 2, 2080, 65, 33, 5, 520),     # two levels, odd sizes
+    # eight waves per workgroup
+    ("bf16", 64, 1, 12, 4096, 256, 256, 7, 0),
+    ("bf16", 64, 1, 12, 8192, 256, 256, 7, 4096),  # one level
+    ("bf16", 128, 1, 8, 8192, 256, 100, 8, 0),     # the longest node, all buckets
+    ("bf16", 64, 4, 25, 300, 150, 20, 3, 0),       # fewer keys than threads
+    ("bf16", 128, 4, 5, 1500, 150, 77, 6, 0),      # 4 keys per thread at odd addresses, the last waves' past the end
+    ("bf16", 64, 1, 16, 2048, 512, 600, 7, 0),     # two tiles per block, more samples than threads
+    ("bf16", 64, 1, 32, 4096, 256, 256, 7, 0),     # the most workgroups
     ("fp32", 64, 1, 1, 1024, 64, 64, 7, 0),
     ("fp32", 128, 1, 3, 777, 21, 50, 8, 0),
     ("fp32", 64, 1, 4, 4096, 64, 64, 7, 1024),

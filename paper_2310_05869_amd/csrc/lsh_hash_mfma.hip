@@ -240,11 +240,13 @@ __global__ __launch_bounds__(256) void lsh_hash_mfma_kernel(HashArgs a) {
   }
 }
 
-#ifndef HA_HASH_BLOCKS
-#define HA_HASH_BLOCKS 512
-#endif
-// resident-sized grid (two 4-wave blocks per CU): every wave streams many 32-row groups
-constexpr int kHashBlocks = HA_HASH_BLOCKS;
+// Workgroups of four waves, at most: one per CU, every wave streaming its 32-row groups with two of them ahead.  With two per CU small
+// calls give some CUs half a round more than others, and rows of 256 bytes do not need them; rows of 128 bytes, whose groups are half
+// the bytes in flight, do from some 32 groups per wave on.  Forward, 512 -> 256 (MI355X, us): d = 128: 6 heads, n = 4096 29.0 -> 26.9, 16 heads
+// 41.9 -> 41.0, 15 heads, n = 6300 51.0 -> 50.1, 12 heads, n = 32768 188.7 -> 187.2, 32 heads 493.8 -> 487.5, 32 causal heads, n = 131072 9137 ->
+// 9123; d = 64: 8 heads, n = 4096 22.0 -> 21.4, 12 heads 25.3 -> 25.4, 16 heads 28.1 -> 27.3, 32 heads, n = 16384 (32 groups) 133.4 -> 132.7, 64
+// heads, n = 65536 (256 groups) 1338 -> 1363.  320 to 448: up to 6 % slower at small sizes, 768: 4 to 6 %.
+static int most_hash_blocks(int64_t ngroups, int d) { return d == 64 && ngroups > 32 * 4 * 256 ? 512 : 256; }
 
 template <int D>
 static void launch_d(const HashArgs& a, dim3 grid, hipStream_t st) {
@@ -256,7 +258,7 @@ int launch_lsh_hash_mfma(const HashArgs& a, int d, hipStream_t st) {
   if (a.rows <= 0) return HA_OK;
   const int64_t ngroups = (a.rows + 31) / 32 * (a.X[1] ? 2 : 1);
   int64_t blocks = (ngroups + 3) / 4;
-  if (blocks > kHashBlocks) blocks = kHashBlocks;
+  if (blocks > most_hash_blocks(ngroups, d)) blocks = most_hash_blocks(ngroups, d);
   const dim3 grid((unsigned)blocks);
   if (d == 128) launch_d<128>(a, grid, st);
   else if (d == 64) launch_d<64>(a, grid, st);

@@ -31,7 +31,7 @@
 // against bank conflicts; instead the 16-byte pieces of a row are swizzled (BwdLds), which the lanes do
 // by choosing which piece of the row they fetch.
 // The budget does not quite close: at d = 128 the compiler spills 28 (sampled keys), 12 (exact) and 24 bytes per lane (block keys
-// of an unmasked problem); at d = 64 every form gets three workgroups per CU.  The compiler gave the sampled-key pass 173
+// of an unmasked problem); at d = 64 every form but the exact dK / dV pass (173 registers) gets three workgroups per CU.  The compiler gave the sampled-key pass 173
 // registers by itself, five too many; asked for three workgroups it needs 168, without spills (forward + backward, 12 heads:
 // n = 16384 234 -> 227 us, where its 768 workgroups then are one round; n = 32768 451 -> 439 us).
 // What bounds it: the order in which a wave issues reads, products and vector work (two waves per SIMD, 64 products
@@ -112,11 +112,21 @@ __device__ inline void dma_1k(const __amdgpu_buffer_rsrc_t& rsrc, uint32_t lds_a
   asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"{m0}"(lds_at), "v"(voff), "s"(rsrc) : "memory");
 }
 
+// Waves per SIMD that the compiler is asked for.  dQ of exact attention at d = 64 takes 135 registers by itself; at 128, with 16 bytes
+// of scratch per lane, a fourth workgroup fits a CU.  Forward + backward, three -> four (MI355X, us; workgroups of the pass): causal exact
+// attention, 16 heads, n = 8192 (1024: one round instead of two) 650.6 -> 636.2, 8 heads, n = 16384 (1024) 1271 -> 1240, 24 heads, n = 4096 (768)
+// 273.1 -> 272.2, 80 heads, n = 1024 (640) 81.5 -> 81.8; unmasked, 12 heads, n = 8192 (768) 892.7 -> 893.2; causal HyperAttention, 32 heads,
+// n = 65536 9371 -> 9344.  The same of the nodes' dQ pass, 20 bytes of scratch, loses (12 heads, n = 16384 215 -> 220; n = 32768 425 -> 442).
+constexpr int bwd_waves_per_simd(int d, int mode, int groups) {
+  if (d == 64 && mode == kBwdDqExact && groups == 1) return 4;
+  return d == 64 && mode == kBwdDkvSamp ? 3 : 2;
+}
+
 // FINAL: the node passes of an unmasked problem, which write the final gradients.
 // NG = 2 (exact passes): two groups of four waves take the T tiles in turn, each with tile buffers of its own; their sums are
 // added through LDS.
 template <int D, int MODE, bool FINAL, int NG>
-__global__ __launch_bounds__(kBNT * NG, (D == 64 && MODE == kBwdDkvSamp) ? 3 : 2) void attn_bwd_kernel(BwdArgs a) {
+__global__ __launch_bounds__(kBNT * NG, bwd_waves_per_simd(D, MODE, NG)) void attn_bwd_kernel(BwdArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   using L = BwdLds<D>;
   constexpr bool kDq = (MODE == kBwdDqNode || MODE == kBwdDqExact);

@@ -149,7 +149,11 @@ __global__ __launch_bounds__(64 * NW * NG, (D == 64 && NW == 4 && NG == 1) ? 3 :
   if constexpr (SORT) {
     dest = RowDest{};
     dest.valid = r_in_tile < w.rows_valid;
-    qrow_load = qrows[dest.valid ? r_in_tile : 0];
+    // A lane past the tile's end repeats a valid row, and counts where its wave decides whether references move.  It is the row that
+    // a tile of 128 rows would repeat, so that eight waves give the bits of four (blocks of b = 200, d = 128, 16 heads, n = 3200: the
+    // last eight rows of one block in 256 differed by a rounding while it was the tile's first row).
+    const int spare = (r_in_tile & ~127) < w.rows_valid ? r_in_tile & ~127 : 0;
+    qrow_load = qrows[dest.valid ? r_in_tile : spare];
     dest.row_in_head = qrow_load;
     dest.out_row = (int64_t)w.bh * a.g.n + qrow_load;
     dest.part_row = w.seg_off + (qrow_load - w.nr.q_start);

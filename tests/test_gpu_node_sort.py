@@ -1,5 +1,7 @@
 """Small calls, whose attention launch sorts its nodes by itself, against the sorting launches (which
 hyperattn_forward_timed always takes): the permutations and everything computed from them are the same bits."""
+import math
+
 import pytest
 
 from ha_testutil import have_gpu
@@ -32,13 +34,7 @@ CASES = [  # dtype, d, B, H, n, b, m, r, n_min (0: unmasked)
     ("bf16", 64, 1, 3, 5005, 77, 50, 7, 0),        # 32 keys
     ("bf16", 64, 1, 2, 8192, 128, 96, 7, 1024),    # three levels
     ("bf16", 128, 1, 2, 2080, 65, 33, 5, 520),     # two levels, odd sizes
-    # eight waves per workgroup
-    ("bf16", 64, 1, 12, 4096, 256, 256, 7, 0),
-    ("bf16", 64, 1, 12, 8192, 256, 256, 7, 4096),  # one level
-    ("bf16", 128, 1, 8, 8192, 256, 100, 8, 0),     # the longest node, all buckets
-    ("bf16", 64, 4, 25, 300, 150, 20, 3, 0),       # fewer keys than threads
-    ("bf16", 128, 4, 5, 1500, 150, 77, 6, 0),      # 4 keys per thread at odd addresses, the last waves' past the end
-    ("bf16", 64, 1, 16, 2048, 512, 600, 7, 0),     # two tiles per block, more samples than threads
+    ("bf16", 64, 1, 16, 2048, 512, 600, 7, 0),     # four tiles per block, more samples than threads
     ("bf16", 64, 1, 32, 4096, 256, 256, 7, 0),     # the most workgroups
     ("fp32", 64, 1, 1, 1024, 64, 64, 7, 0),
     ("fp32", 128, 1, 3, 777, 21, 50, 8, 0),
@@ -48,9 +44,26 @@ CASES = [  # dtype, d, B, H, n, b, m, r, n_min (0: unmasked)
     ("fp32", 128, 1, 32, 2048, 128, 0, 7, 0),      # likewise, no samples
 ]
 
+EIGHT_WAVES = [  # more than 256 tiles of 128 rows, at most 256 of 256: workgroups of eight waves
+    ("bf16", 64, 1, 12, 4096, 256, 256, 7, 0),
+    ("bf16", 64, 1, 12, 8192, 256, 256, 7, 4096),  # one level
+    ("bf16", 128, 1, 8, 8192, 256, 100, 8, 0),     # the longest node, all buckets
+    ("bf16", 64, 4, 25, 300, 150, 20, 3, 0),       # fewer keys than threads
+    ("bf16", 128, 4, 5, 1500, 150, 77, 6, 0),      # 4 keys per thread at odd addresses, the last waves' past the end
+    ("bf16", 64, 1, 24, 2048, 512, 600, 7, 0),     # two tiles per block, more samples than threads
+    ("bf16", 128, 1, 16, 3200, 200, 100, 7, 0),    # waves that end in the second 128 rows of a tile
+    ("bf16", 64, 1, 12, 3000, 300, 100, 7, 0),     # blocks whose second tile holds 44 rows
+]
 
-@pytest.mark.parametrize("law", ["iid", "equal"])
-@pytest.mark.parametrize("dtype,d,B,H,n,b,m,r,n_min", CASES)
+
+def tiles(rows, B, H, n, b, n_min):
+    """Tiles of up to `rows` query rows in the node launch."""
+    levels, covered = (int(math.log2(n // n_min)), n // 2) if n_min else (1, n)
+    return levels * B * H * (covered // b) * -(-b // rows)
+
+
+@pytest.mark.parametrize("law", ["iid", "equal", "steep"])
+@pytest.mark.parametrize("dtype,d,B,H,n,b,m,r,n_min", CASES + EIGHT_WAVES)
 def test_sort_inside_the_attention_launch(ha, torch, dtype, d, B, H, n, b, m, r, n_min, law):
     print(f"node sort {dtype} d={d} B={B} H={H} n={n} b={b} m={m} r={r} n_min={n_min} {law}", flush=True)
     gen = torch.Generator(device="cuda")
@@ -59,9 +72,14 @@ def test_sort_inside_the_attention_launch(ha, torch, dtype, d, B, H, n, b, m, r,
     q, k, v = ((torch.randn((B, H, n, d), generator=gen, device="cuda") * d ** -0.25).to(dt) for _ in range(3))
     if law == "equal":  # every key in one bucket: the order is that of the rows
         q, k = (x[:, :, :1].expand(B, H, n, d).contiguous() for x in (q, k))
+    elif law == "steep":  # scores far apart: references move, by what all lanes of a wave see
+        q = q * 4
     shape = ha.make_shape(B, H, n, d, ha.HA_BF16 if dtype == "bf16" else ha.HA_FP32)
     params = ha.make_params(b, m, r, n_min > 0, n_min or 4096, 3)
     assert ha.ha_call_routes(shape, params)[0]     # by the rule of the dispatch itself
+    if dtype == "bf16":
+        eight = tiles(128, B, H, n, b, n_min) > 256 >= tiles(256, B, H, n, b, n_min)
+        assert eight == ((dtype, d, B, H, n, b, m, r, n_min) in EIGHT_WAVES)
     names = ("perm_q", "perm_k", "pos_k") + (("samp_blk",) if m else ())
     results = []
     for call in (ha.hyperattn_forward, ha.hyperattn_forward_timed):

@@ -308,23 +308,15 @@ static AttnArgs node_args(const void* Q, const void* K, const void* V, void* out
   return a;
 }
 
-// Whether the attention launch sorts its nodes by itself (node_sort.h).  Every workgroup then counts its whole node, some 4 us
-// of a workgroup's life at 4096 keys, against a sorting launch of 6.5 to 8 us and 2.5 us of the host's time for
-// it: worth it while the workgroups fit the chip about once and the codes they count are few.  Forward, sorting launch -> in the
-// attention (MI355X, us; workgroups of 128 rows):
-//   bf16, d = 64: 12 heads, n = 4096 (384) 29.8 -> 25.5, 16 (512) 31.9 -> 27.7, 20 (640) 37.1 -> 33.7, 24 (768) 39.0 -> 35.4, 32 (1024)
-//     46.4 -> 45.2; n = 2048: 48 heads (768) 37.8 -> 34.9, 64 (1024) 45.5 -> 44.7; 96 heads, n = 1024 (768) 37.2 -> 34.1; 6 heads,
-//     n = 8192 (384) 30.4 -> 26.3, 8 (512) 32.4 -> 28.5, 12 (768) 40.2 -> 42.3; 128 heads, n = 1024, b = m = 64 (2048) 37.5 -> 39.0
-//   bf16, d = 128: 8 heads, n = 4096 (256) 32.8 -> 29.8, 16 (512) 44.1 -> 41.2, 20 (640) 55.2 both, 24 (768) 58.6 -> 59.7; 64 heads, n = 1024
-//     (512) 42.4 -> 39.4; 6 heads, n = 8192 (384) 41.2 -> 36.5, 8 (512) 44.8 -> 42.2; 15 heads, n = 6300, b = 100, m = 77 (945) 50.4 -> 55.0
-//   fp32, d = 64, b = m = 64: one head, n = 1024 (32) 21.2 -> 17.2; 16 heads, n = 4096 (1024) 66.4 -> 62.6, 32 (2048) 106.1 -> 108.1;
-//     64 heads, n = 1024 (1024) 65.2 -> 61.7; d = 128: 16 heads, n = 4096 (1024) 110.5 -> 111.5
+// Whether the attention launch sorts its nodes by itself (node_sort.h), instead of a sorting launch ahead of it.  bf16: attn_mfma_sorts.
+// fp32, sorting launch -> in the attention (MI355X, us; workgroups): d = 64, b = m = 64: one head, n = 1024 (32) 21.2 -> 17.2; 16 heads,
+// n = 4096 (1024) 66.4 -> 62.6, 32 (2048) 106.1 -> 108.1; 64 heads, n = 1024 (1024) 65.2 -> 61.7; d = 128: 16 heads, n = 4096 (1024)
+// 110.5 -> 111.5
 static bool sort_in_attention(const Geometry& g) {
+  if (use_mfma(g)) return attn_mfma_sorts(g);
   const int rows = node_sort_rows(g);
-  if (rows > kNodeSortMax) return false;
-  const int64_t wgs = use_mfma(g) ? node_grid<128>(g) : attn_f32_node_grid(g);
-  const int64_t most = use_mfma(g) && g.d == 128 ? 512 : 1024;
-  return wgs <= most && wgs * rows <= 4 << 20;
+  const int64_t wgs = attn_f32_node_grid(g);
+  return rows <= kNodeSortMax && wgs <= 1024 && wgs * rows <= 4 << 20;
 }
 
 // ev, when non-null, receives 5 events recorded on the stream: start, after hashing (with the call's draws), after sorting,

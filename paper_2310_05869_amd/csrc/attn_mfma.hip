@@ -873,6 +873,42 @@ constexpr int64_t kWideExactMinGrid = 129, kWideExactMinGridCausal = 1024;
 // b = 300 27.7 -> 26.2; d = 128: 12 heads, n = 4096 36.9 -> 35.4, 16 heads 43.4 both.
 static bool wide_sorting_node(const Geometry& g) { return node_grid<128>(g) > 256 && node_grid<256>(g) <= 256; }
 
+// Whether a node launch sorts by itself.  Every workgroup then counts its whole node, some 4 us of its life at 4096 keys,
+// against a sorting launch of 6.5 to 8 us and 2.5 us of the host's time for it: worth it while the workgroups fit the chip at
+// once, eight-wave ones by their rule.  At d = 64 three of a CU's 160 KB fit beside each other until the sort's tables take them past a
+// third of it, and the launch that drops to two loses more than the sort.  Sorting launch -> in the attention (MI355X, us; workgroups of 128 rows):
+//   d = 64, one round: 12 heads, n = 4096 (384) 29.8 -> 25.5, 16 (512) 31.9 -> 27.7, 20 (640) 37.2 -> 33.8, 24 (768) 39.3 -> 35.9; b = m = 64:
+//     40 heads, n = 1024 (640) 21.9 -> 18.6, 24 heads, n = 2048 (768) 22.3 -> 19.6, 12 heads, n = 4096 (768) 23.3 -> 20.5, 4 heads, n = 8192
+//     (512) 21.1 -> 19.6; b = m = 128: 24 heads, n = 4096 (768) 32.3 -> 28.7, 8 heads, n = 8192 (512) 27.5 -> 24.5; b = 100, m = 77: 34
+//     heads, n = 2100 (714) 29.1 -> 26.9, 13 heads, n = 5600 (728) 29.7 -> 27.0; causal, 12 heads, n = 8192, n_min = 2048 (768) 80.4 -> 76.3
+//   d = 64, 512 places: b = m = 64: 8 heads, n = 5760 (720, three to a CU) 23.5 -> 22.2, 7 heads, n = 5888 (644) 23.8 -> 27.7; n = 6144: 10 heads (480)
+//     31.5 -> 27.2, 11 (528) 36.3 -> 40.9; n = 4096, m = 1024: 17 heads (544) r = 7 56.3 -> 52.8, r = 8 56.5 -> 63.2
+//   d = 128, 512 places: 16 heads, n = 4096 (512) 44.1 -> 41.2, 20 (640) 55.2 both, 24 (768) 58.6 -> 59.7; 8 heads, n = 8192 (512) 44.8 ->
+//     42.2; b = m = 64: 16 heads, n = 2048 (512) 25.7 -> 23.1, 4 heads, n = 8192 (512) 27.3 -> 24.9; 15 heads, n = 6300, b = 100, m = 77 (945)
+//     50.4 -> 55.0
+// A second round of up to 1024 workgroups at d = 64 gains where a sort's threads hold few keys (up to 8 each, n <= 2048), or nearly the 16
+// they are dealt, loaded 16 bytes at a time: n = 1000, b = 40 (900) 25.8 -> 25.0, n = 1600, b = 100 (800) 31.8 -> 31.3, n = 2048, b = 64 (1024)
+// 26.6 -> 26.2, b = 128 36.3 -> 35.6; n = 1152, b = 128 (990) 36.7 -> 37.2; n = 2112, b = 96 (880) 32.1 -> 32.6; n = 2304, b = 256 (774)
+// 44.1 -> 45.5; n = 3072, b = 128 (792) 36.0 -> 35.5, b = 192 (800) 35.4 -> 35.7, b = 256 (792) 44.1 -> 44.2; n = 3328, b = 128 (780) 37.6 ->
+// 36.1; n = 3500, b = 100, whose heads do not start at 16 bytes (770) 32.8 -> 33.3; n = 4096, b = 32 (896) 25.5 -> 25.6, b = 64 (1024) 27.8 -> 27.3, b = 256
+// (1024) 46.7 -> 45.7; n = 5120, b = 64 (800) 27.0 -> 28.6, b = 256 45.6 -> 47.4.  Past 1024: 128 heads, n = 1024, b = m = 64 (2048) 37.5 -> 39.0.
+bool attn_mfma_sorts(const Geometry& g) {
+  const int rows = node_sort_rows(g);
+  const int64_t wgs = node_grid<128>(g);
+  if (rows > kNodeSortMax || wgs * rows > 4 << 20) return false;
+  if (wide_sorting_node(g)) return true;
+  if (g.d == 128) return wgs <= 512;
+  const size_t plain = mfma_lds_bytes<64>(g.b, g.m, kModeNode), sorting = plain + sort_pushes_list<64, 4>(g) + 32 * 4 * 4;
+  auto per_cu = [](size_t lds) {  // LDS is dealt in 128 pieces of 1280 bytes; a fourth workgroup has no registers
+    const size_t fit = 128 / ((lds + 1279) / 1280);
+    return fit < 3 ? (int64_t)fit : (int64_t)3;
+  };
+  if (wgs <= 256 * per_cu(sorting)) return true;
+  if (per_cu(sorting) < per_cu(plain) || wgs > 1024) return false;
+  const bool whole_words = (g.causal ? g.n_min : g.n) % 16 == 0;
+  return rows <= 2048 || (rows > 3200 && rows <= 4096 && whole_words);
+}
+
 int64_t attn_mfma_grid(const AttnArgs& a, int mode) {
   return mode == kModeNode ? node_grid<32 * HA_NW_NODE>(a.g) : exact_grid<32 * HA_NW_EXACT>(a);
 }

@@ -175,6 +175,32 @@ def test_backward_shared_launches_hold_their_workgroups(ha):
     assert ha.ha_call_routes(ha.make_shape(1, 4, 4096, 64, ha.HA_BF16), ha.make_params(64, 64, 7, True, 1024, 0))[1] == 0
 
 
+@pytest.mark.parametrize("d,H,n,b,m,r,n_min,sorts", [
+    (64, 24, 2048, 64, 64, 7, 0, True),        # 768 workgroups: three to a CU
+    (64, 8, 5760, 64, 64, 7, 0, True),         # the longest node of which three fit the LDS
+    (64, 6, 5888, 64, 64, 7, 0, False),        # two: 552 workgroups have 512 places
+    (64, 5, 5888, 64, 64, 7, 0, True),
+    (64, 10, 6144, 256, 256, 7, 0, True),      # eight waves
+    (64, 11, 6144, 256, 256, 7, 0, False),
+    (64, 6, 12288, 256, 256, 7, 3072, False),  # two levels, 576 workgroups of 6144 keys
+    (64, 17, 4096, 256, 1024, 7, 0, True),
+    (64, 17, 4096, 256, 1024, 8, 0, False),    # more buckets: two
+    (64, 32, 2048, 64, 64, 7, 0, True),        # a second round
+    (64, 33, 2048, 64, 64, 7, 0, False),
+    (64, 40, 2112, 96, 96, 7, 0, False),       # a second round of threads that hold half of what they could
+    (64, 32, 4096, 256, 256, 7, 0, True),
+    (64, 22, 3500, 100, 77, 7, 0, False),      # heads not at 16 bytes
+    (64, 20, 5120, 256, 256, 7, 0, False),
+    (64, 1, 8256, 64, 64, 7, 0, False),        # more keys than a workgroup's threads hold
+    (128, 32, 1024, 64, 64, 7, 0, True),
+    (128, 33, 1024, 64, 64, 7, 0, False),      # two to a CU
+])
+def test_forward_sorts_in_the_attention_launch(ha, d, H, n, b, m, r, n_min, sorts):
+    """While its workgroups fit the chip, the sort's tables in the LDS counted."""
+    params = ha.make_params(b, m, r, n_min > 0, n_min or 4096, 0)
+    assert bool(ha.ha_call_routes(ha.make_shape(1, H, n, d, ha.HA_BF16), params)[0]) == sorts
+
+
 def test_forward_workgroup_counts(ha):
     """Records of the stamped forward: one per 128-query tile of every node (levels x half the rows when causal)
     and of the base case; none for fp32 tensors, which run the kernel without matrix cores."""

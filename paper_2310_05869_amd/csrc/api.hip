@@ -35,7 +35,6 @@
 #include "alg2_common.h"
 #include "bwd_common.h"
 #include "hash_common.h"
-#include "node_sort.h"
 
 namespace ha {
 
@@ -308,16 +307,8 @@ static AttnArgs node_args(const void* Q, const void* K, const void* V, void* out
   return a;
 }
 
-// Whether the attention launch sorts its nodes by itself (node_sort.h), instead of a sorting launch ahead of it.  bf16: attn_mfma_sorts.
-// fp32, sorting launch -> in the attention (MI355X, us; workgroups): d = 64, b = m = 64: one head, n = 1024 (32) 21.2 -> 17.2; 16 heads,
-// n = 4096 (1024) 66.4 -> 62.6, 32 (2048) 106.1 -> 108.1; 64 heads, n = 1024 (1024) 65.2 -> 61.7; d = 128: 16 heads, n = 4096 (1024)
-// 110.5 -> 111.5
-static bool sort_in_attention(const Geometry& g) {
-  if (use_mfma(g)) return attn_mfma_sorts(g);
-  const int rows = node_sort_rows(g);
-  const int64_t wgs = attn_f32_node_grid(g);
-  return rows <= kNodeSortMax && wgs <= 1024 && wgs * rows <= 4 << 20;
-}
+// Whether the attention launch sorts its nodes by itself (node_sort.h), instead of a sorting launch ahead of it.
+static bool sort_in_attention(const Geometry& g) { return use_mfma(g) ? attn_mfma_sorts(g) : attn_f32_sorts(g); }
 
 // ev, when non-null, receives 5 events recorded on the stream: start, after hashing (with the call's draws), after sorting,
 // after the node attention, after the base case.

@@ -495,6 +495,31 @@ int64_t attn_f32_node_grid(const Geometry& g) {
   return kw == 1 ? node_grid<128>(g) : kw == 2 ? node_grid<64>(g) : node_grid<32>(g);
 }
 
+// Whether a node launch sorts by itself (attn_mfma_sorts, for the kernel without it).  d = 64: up to 1024 workgroups.  d = 128 has 512
+// places, two to a CU; past them, from some 580 to 768 workgroups, calls whose workgroups sort take up to a fifth longer (they start and
+// end together, and the second round seems to fall on the CUs unevenly: its places were not recorded).  Sorting launch -> in the attention (MI355X, us; workgroups, of
+// 128 rows, of 64, of 32):
+//   d = 64, b = m = 64: one head, n = 1024 (32) 21.2 -> 17.2; 24 heads, n = 2048 (768) 51.4 -> 46.8; 16 heads, n = 4096 (1024) 66.7 -> 62.7,
+//     32 (2048) 106.1 -> 108.1; 64 heads, n = 1024 (1024) 65.3 -> 61.8; 6 heads, n = 4100, b = 82 (900) 48.6 -> 49.1
+//   d = 128, 128 rows: 32 heads, n = 2048, b = m = 128 (512) 134.0 -> 128.3, 36 (576) 179.9 -> 173.6, 44 (704) 189.2 -> 183.7, 48 (768) 196.7 ->
+//     223.8, 52 (832) 238.0 -> 231.8, 64 (1024) 254.4 -> 247.4; b = m = 256: 40 (640) 287.9 -> 280.0, 48 (768) 334.2 -> 348.1; n = 512, b = 128, m =
+//     32: 180 heads (720) 152.7 -> 158.2; n = 1000, b = 100, m = 64: 56 heads (560) 133.7 -> 129.8, 61 (610) 137.4 -> 151.0, 90 (900) 180.4 -> 175.3
+//   64 rows: 16 heads, n = 2048, b = m = 64 (512) 60.6 -> 59.1, 18 (576) 79.9 -> 78.7, 20 (640) 81.1 -> 80.2, 23 (736) 85.0 -> 87.8, 24 (768) 86.0 ->
+//     97.2, 32 (1024) 109.3 -> 110.2; b = m = 256: 18 (576) 156.8 -> 156.0, 20 (640) 167.7 -> 183.5; n = 6144, b = 64: 4 heads (384) 59.0 -> 58.8,
+//     n = 8192: 2 heads (256) 42.2 -> 38.3, 3 (384) 58.9 -> 60.4; b = 128: 4 heads (512) 80.5 -> 85.2
+//   32 rows, of long blocks: 4 heads, n = 4096, b = m = 256 (512) 70.1 -> 67.0, 6 (768) 99.0 -> 108.2; 8 heads, n = 2100, b = 100 (672) 67.9 -> 68.2;
+//     2 heads, n = 8192, b = 256 (512) 70.8 -> 75.1; of blocks that 64 rows do not fill: 24 heads, n = 1024, b = 32 (768) 57.0 -> 55.0, 32
+//     (1024) 63.9 -> 62.8; 8 heads, n = 4096, b = 32 (1024) 65.1 -> 64.7
+bool attn_f32_sorts(const Geometry& g) {
+  const int rows = node_sort_rows(g);
+  const int64_t wgs = attn_f32_node_grid(g);
+  if (rows > kNodeSortMax || wgs > 1024 || wgs * rows > 4 << 20) return false;
+  const int kw = f32_waves_per_group(g.b, node_grid<128>(g));
+  if (g.d == 64 || 4 * g.b < 3 * 64) return true;
+  if (kw > 1 && wgs * rows > 5 << 19) return false;
+  return wgs <= (kw == 4 ? 512 : kw == 1 && g.b % 128 == 0 ? 704 : 576) || (kw == 1 && wgs > 768);
+}
+
 // Exact launches of few workgroups and long rows are bound by the longest chain of key tiles: eight waves then share 32 queries,
 // two per SIMD where four left one, a workgroup that fills a CU (causal: up to one and a half or two rounds of those, heaviest first).
 // Four waves -> eight (MI355X, us; groups of 32 rows in brackets): d = 128: causal, 16 heads, n = 512 (256) 29.9 -> 28.8; 12 heads,

@@ -175,10 +175,11 @@ int launch_seg_sort_flat(const uint8_t* codes, int32_t* perm, int32_t* pos, int 
                          hipStream_t st);
 int launch_attn_mfma(const AttnArgs& a, int mode, hipStream_t st);
 int64_t attn_mfma_grid(const AttnArgs& a, int mode);  // workgroups of the four-wave launch of that mode
-bool attn_mfma_sorts(const Geometry& g);              // whether the node launch sorts its nodes by itself
+bool attn_mfma_sorts(const Geometry& g);               // whether the node launch sorts its nodes by itself
 int launch_attn_f32(const AttnArgs& a, int mode, hipStream_t st);
 bool f32_exact_eight(const AttnArgs& a);  // whether eight waves share 32 rows of an exact fp32 launch
 int64_t attn_f32_node_grid(const Geometry& g);        // workgroups of the node launch
+bool attn_f32_sorts(const Geometry& g);               // whether it sorts its nodes by itself
 int launch_gather_rows(const void* src, const int32_t* idx, void* dst, int groups, int n, int d, int dtype,
                        hipStream_t st);
 int launch_merge_unpermute(const float* o_b, const float* lse_b, const float* o_r, const float* lse_r,

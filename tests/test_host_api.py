@@ -175,7 +175,7 @@ def test_backward_shared_launches_hold_their_workgroups(ha):
     assert ha.ha_call_routes(ha.make_shape(1, 4, 4096, 64, ha.HA_BF16), ha.make_params(64, 64, 7, True, 1024, 0))[1] == 0
 
 
-@pytest.mark.parametrize("d,H,n,b,m,r,n_min,sorts", [
+@pytest.mark.parametrize("dtype,d,H,n,b,m,r,n_min,sorts", [("bf16", *c) for c in [
     (64, 24, 2048, 64, 64, 7, 0, True),        # 768 workgroups: three to a CU
     (64, 8, 5760, 64, 64, 7, 0, True),         # the longest node of which three fit the LDS
     (64, 6, 5888, 64, 64, 7, 0, False),        # two: 552 workgroups have 512 places
@@ -194,11 +194,27 @@ def test_backward_shared_launches_hold_their_workgroups(ha):
     (64, 1, 8256, 64, 64, 7, 0, False),        # more keys than a workgroup's threads hold
     (128, 32, 1024, 64, 64, 7, 0, True),
     (128, 33, 1024, 64, 64, 7, 0, False),      # two to a CU
-])
-def test_forward_sorts_in_the_attention_launch(ha, d, H, n, b, m, r, n_min, sorts):
+]] + [("fp32", *c) for c in [
+    (64, 16, 4096, 64, 64, 7, 0, True),        # 1024 workgroups
+    (64, 17, 4096, 64, 64, 7, 0, False),
+    (128, 48, 2048, 128, 128, 7, 0, False),    # of 128 rows: 768
+    (128, 44, 2048, 128, 128, 7, 0, True),     # 704
+    (128, 52, 2048, 128, 128, 7, 0, True),     # 832
+    (128, 61, 1000, 100, 64, 7, 0, False),     # 610, blocks that the tiles do not divide
+    (128, 18, 2048, 64, 64, 7, 0, True),       # of 64 rows: 576
+    (128, 24, 2048, 64, 64, 7, 0, False),      # 768
+    (128, 32, 2048, 64, 64, 7, 0, False),      # 1024
+    (128, 2, 8192, 64, 64, 7, 0, True),        # 256 of 8192 keys
+    (128, 4, 8192, 128, 128, 7, 0, False),     # 512
+    (128, 4, 4096, 256, 256, 7, 0, True),      # of 32 rows: 512
+    (128, 6, 4096, 256, 256, 7, 0, False),     # 768
+    (128, 8, 4096, 32, 64, 7, 0, True),        # 1024, of blocks that 64 rows do not fill
+    (128, 12, 4096, 64, 64, 7, 1024, False),   # two levels, 768
+]])
+def test_forward_sorts_in_the_attention_launch(ha, dtype, d, H, n, b, m, r, n_min, sorts):
     """While its workgroups fit the chip, the sort's tables in the LDS counted."""
-    params = ha.make_params(b, m, r, n_min > 0, n_min or 4096, 0)
-    assert bool(ha.ha_call_routes(ha.make_shape(1, H, n, d, ha.HA_BF16), params)[0]) == sorts
+    shape = ha.make_shape(1, H, n, d, ha.HA_BF16 if dtype == "bf16" else ha.HA_FP32)
+    assert bool(ha.ha_call_routes(shape, ha.make_params(b, m, r, n_min > 0, n_min or 4096, 0))[0]) == sorts
 
 
 def test_forward_workgroup_counts(ha):

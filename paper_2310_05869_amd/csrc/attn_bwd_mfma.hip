@@ -31,7 +31,8 @@
 // against bank conflicts; instead the 16-byte pieces of a row are swizzled (BwdLds), which the lanes do
 // by choosing which piece of the row they fetch.
 // The budget does not quite close: at d = 128 the compiler spills 28 (sampled keys), 12 (exact) and 24 bytes per lane (block keys
-// of an unmasked problem); at d = 64 every form but the exact dK / dV pass (173 registers) gets three workgroups per CU.  The compiler gave the sampled-key pass 173
+// of an unmasked problem); at d = 64 every form of one wave group gets three workgroups per CU, the exact dQ pass four where
+// it has more than three to place (bwd_four_workgroups).  The compiler gave the sampled-key pass 173
 // registers by itself, five too many; asked for three workgroups it needs 168, without spills (forward + backward, 12 heads:
 // n = 16384 234 -> 227 us, where its 768 workgroups then are one round; n = 32768 451 -> 439 us).
 // What bounds it: the order in which a wave issues reads, products and vector work (two waves per SIMD, 64 products
@@ -112,21 +113,15 @@ __device__ inline void dma_1k(const __amdgpu_buffer_rsrc_t& rsrc, uint32_t lds_a
   asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"{m0}"(lds_at), "v"(voff), "s"(rsrc) : "memory");
 }
 
-// Waves per SIMD that the compiler is asked for.  dQ of exact attention at d = 64 takes 135 registers by itself; at 128, with 16 bytes
-// of scratch per lane, a fourth workgroup fits a CU.  Forward + backward, three -> four (MI355X, us; workgroups of the pass): causal exact
-// attention, 16 heads, n = 8192 (1024: one round instead of two) 650.6 -> 636.2, 8 heads, n = 16384 (1024) 1271 -> 1240, 24 heads, n = 4096 (768)
-// 273.1 -> 272.2, 80 heads, n = 1024 (640) 81.5 -> 81.8; unmasked, 12 heads, n = 8192 (768) 892.7 -> 893.2; causal HyperAttention, 32 heads,
-// n = 65536 9371 -> 9344.  The same of the nodes' dQ pass, 20 bytes of scratch, loses (12 heads, n = 16384 215 -> 220; n = 32768 425 -> 442).
-constexpr int bwd_waves_per_simd(int d, int mode, int groups) {
-  if (d == 64 && mode == kBwdDqExact && groups == 1) return 4;
-  return d == 64 && mode == kBwdDkvSamp ? 3 : 2;
-}
+// Waves per SIMD that the compiler is asked for.
+constexpr int bwd_waves_per_simd(int d, int mode) { return d == 64 && mode == kBwdDkvSamp ? 3 : 2; }
 
 // FINAL: the node passes of an unmasked problem, which write the final gradients.
 // NG = 2 (exact passes): two groups of four waves take the T tiles in turn, each with tile buffers of its own; their sums are
 // added through LDS.
-template <int D, int MODE, bool FINAL, int NG>
-__global__ __launch_bounds__(kBNT * NG, bwd_waves_per_simd(D, MODE, NG)) void attn_bwd_kernel(BwdArgs a) {
+// FOUR: held to the registers of four waves per SIMD (bwd_four_workgroups).
+template <int D, int MODE, bool FINAL, int NG, bool FOUR>
+__global__ __launch_bounds__(kBNT * NG, FOUR ? 4 : bwd_waves_per_simd(D, MODE)) void attn_bwd_kernel(BwdArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   using L = BwdLds<D>;
   constexpr bool kDq = (MODE == kBwdDqNode || MODE == kBwdDqExact);
@@ -628,7 +623,7 @@ __global__ __launch_bounds__(kBNT * NG, bwd_waves_per_simd(D, MODE, NG)) void at
   }
 }
 
-template <int D, int MODE, bool FINAL, int NG>
+template <int D, int MODE, bool FINAL, int NG, bool FOUR = false>
 static int launch_bwd_form(const BwdArgs& args, int grid, hipStream_t st) {
   BwdArgs a = args;
   if (MODE == kBwdDqNode || MODE == kBwdDkvBlock) set_node_divs<kRT>(a.f);
@@ -636,8 +631,8 @@ static int launch_bwd_form(const BwdArgs& args, int grid, hipStream_t st) {
   a.f.exact_lpt = NG == 2;
   const size_t lds = bwd_lds_bytes<D, NG>(a, MODE);
   static std::atomic<uint64_t> lds_set{0};  // per instantiation: devices on which the LDS limit is raised
-  if (allow_full_lds(reinterpret_cast<const void*>(&attn_bwd_kernel<D, MODE, FINAL, NG>), lds_set) != HA_OK) return HA_ERR_LAUNCH;
-  hipLaunchKernelGGL((attn_bwd_kernel<D, MODE, FINAL, NG>), dim3((unsigned)grid), dim3(kBNT * NG), lds, st, a);
+  if (allow_full_lds(reinterpret_cast<const void*>(&attn_bwd_kernel<D, MODE, FINAL, NG, FOUR>), lds_set) != HA_OK) return HA_ERR_LAUNCH;
+  hipLaunchKernelGGL((attn_bwd_kernel<D, MODE, FINAL, NG, FOUR>), dim3((unsigned)grid), dim3(kBNT * NG), lds, st, a);
   return check_launch();
 }
 
@@ -663,11 +658,22 @@ static bool split_bwd_exact(const BwdArgs& a, int grid) {
   return grid <= (rows < 1024 ? 320 : rows < 1536 ? 384 : rows < 2048 ? 448 : 512);
 }
 
+// dQ of exact attention at d = 64 takes 135 registers by itself, three workgroups per CU; at 128, with 16 bytes of scratch per lane, a
+// fourth fits.  It pays from the 769th workgroup on, where three per CU need a second round.  Forward + backward, three -> four (MI355X, us;
+// workgroups of the pass): causal, 96 heads, n = 1024 (768) 93.7 -> 94.2, 128 (1024) 128.6 -> 124.1; 120 heads, n = 700 (720) 72.8 -> 73.2; 200 heads,
+// n = 600 (1000) 103.4 -> 99.7; 48 heads, n = 2048 (768) 153.3 -> 153.0, 64 (1024) 198.4 -> 196.6; 32 heads, n = 4096 (1024) 346.7 -> 340.4; 16
+// heads, n = 8192 (1024) 648.0 -> 635.8, 24 (1536) 934.0 -> 927.4; 8 heads, n = 16384 (1024) 1272 -> 1243; unmasked, 128 heads, n = 1024 (1024) 185.8 -> 185.7,
+// 16 heads, n = 8192 (1024) 1221 -> 1210; causal HyperAttention, 32 heads, n = 65536 9519 -> 9461.  The same of the nodes' dQ pass, 20 bytes of
+// scratch, loses (12 heads, n = 16384 215 -> 220; n = 32768 425 -> 442).
+static bool bwd_four_workgroups(int grid) { return grid > 768; }
+
 template <int D, int MODE>
 static int launch_bwd_one(const BwdArgs& a, int grid, hipStream_t st) {
   if (grid <= 0) return HA_OK;
   if constexpr (MODE == kBwdDqExact || MODE == kBwdDkvExact)
     if (split_bwd_exact(a, grid)) return launch_bwd_form<D, MODE, false, 2>(a, grid, st);
+  if constexpr (D == 64 && MODE == kBwdDqExact)
+    if (bwd_four_workgroups(grid)) return launch_bwd_form<D, MODE, false, 1, true>(a, grid, st);
   if constexpr (MODE == kBwdDqNode || MODE == kBwdDkvBlock)
     if (!a.f.g.causal) return launch_bwd_form<D, MODE, true, 1>(a, grid, st);
   return launch_bwd_form<D, MODE, false, 1>(a, grid, st);

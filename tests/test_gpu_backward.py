@@ -426,6 +426,8 @@ def test_forward_and_backward_on_random_small_problems(ha, torch, d, n, n_min, b
 @pytest.mark.parametrize("dtype,d,H,n", [("bf16", 64, 33, 130),     # part of a round
                                          ("bf16", 64, 256, 1000),   # the most tiles of the one order: every second round of 32 backwards
                                          ("bf16", 64, 257, 1000),   # the fewest of the other
+                                         ("bf16", 64, 96, 1000),    # the most tiles of three workgroups per CU in the dQ pass
+                                         ("bf16", 64, 97, 1000),    # the fewest of four
                                          ("bf16", 128, 101, 300),   # a partial round backwards
                                          ("bf16", 128, 3, 2500), ("bf16", 64, 1, 100),
                                          ("fp32", 64, 9, 1000), ("fp32", 128, 70, 300)])

@@ -60,11 +60,13 @@ constexpr int kNodeSortMax = 32 * 64 * 4;  // keys of a node: 32 per thread of t
 __host__ __device__ inline int node_sort_rows(const Geometry& g) { return ((g.causal ? g.n >> 1 : g.n) + 63) & ~63; }
 
 typedef uint32_t words4 __attribute__((ext_vector_type(4)));
+// half of a word of `pos`, which is written as words4: no two accesses of the table may be taken for independent by their types
+typedef uint16_t half_word __attribute__((may_alias));
 
 constexpr int kNodeSortBuckets = 256;
 
 struct NodeSortLds {
-  uint8_t* codes;              // [2][rows] the keys' buckets (a wave reads only what its own lanes wrote)
+  uint8_t* codes;              // [2][rows] the keys' buckets (a wave ranks only keys that its own lanes wrote)
   uint16_t* rel;               // [2][rows] keys of the buckets that touch the range, wave by wave: index in the node
   uint32_t* count;             // [2][wave pairs][kNodeSortBuckets] two waves' counts in a word
   uint32_t* pos;               // [waves][kNodeSortBuckets] sorted position of a wave's next key, queries | keys << 16
@@ -249,7 +251,7 @@ __device__ inline void sort_node_tile(const AttnArgs& a, const TileWork& w, unsi
   // sorted positions: a key's place among the equal keys of its 64 from the lanes' bits in a word per bucket
   const unsigned long long lane_bit = 1ull << lane;
   const int most = n[0] > n[1] ? n[0] : n[1];
-  uint16_t* next = reinterpret_cast<uint16_t*>(l.pos + wave * kNodeSortBuckets);
+  half_word* next = reinterpret_cast<half_word*>(l.pos + wave * kNodeSortBuckets);
   for (int k0 = 0; k0 < most; k0 += 64) {
     uint32_t i[2], c[2];
     bool valid[2];

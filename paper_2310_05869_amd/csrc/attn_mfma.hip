@@ -296,7 +296,7 @@ __global__ __launch_bounds__(64 * NW * NG, (D == 64 && NW == 4 && NG == 1) ? 3 :
   };
   // Row maximum of a score tile in the log2 domain, in-lane and then over lane ^ 32.  d = 64: of the lane's own keys; whether any
   // row's reference has to move takes no exchange, so it waits for the branch that moves it, and what the exponentials subtract
-  // is formed there too.  Same bits; 12 heads, n = 4096 25.6 -> 25.3 us, causal, n = 8192 99.6 -> 98.7, 64 heads, n = 65536 1345 -> 1330.
+  // is formed there too.  Same bits; 12 heads, n = 4096 25.6 -> 25.3 us, causal, n = 8192 99.6 -> 98.7, 64 heads, n = 65536 1357 -> 1350.
   // At d = 128 the node kernel then spills (12 bytes per lane) and the calls differ by +-0.4 %.
   constexpr bool kLaneMax = D == 64;
   auto row_max = [](float mx) { return kLaneMax ? fmaxf(mx, __shfl_xor(mx, 32)) : mx; };
@@ -870,7 +870,10 @@ constexpr int64_t kWideExactMinGrid = 129, kWideExactMinGridCausal = 1024;
 // side by side and end last (33 k cycles of life where one has a CU, 43 k where two share it).  Where tiles of 256 rows fit
 // the chip once, eight waves do that work once per CU.  Four waves -> eight (MI355X, us; b = m = 256): d = 64: 12 heads, n = 4096 26.4 ->
 // 25.4, 9 heads 25.8 -> 24.8, 16 heads 27.9 -> 27.1; 64 heads, n = 1024 27.8 -> 27.1; 32 heads, n = 2048 28.2 -> 27.3; 8 heads, n = 3900,
-// b = 300 27.7 -> 26.2; d = 128: 12 heads, n = 4096 36.9 -> 35.4, 16 heads 43.4 both.
+// b = 300 27.7 -> 26.2; other blocks and samples: 24 heads, n = 2048, b = m = 512 34.0 -> 32.0, m = 32 22.3 -> 21.2; 25 heads, n = 1500, b = 150 21.3 ->
+// 20.2, n = 1300, b = 130 19.3 -> 17.8; 8 heads, n = 8192, m = 64 25.6 -> 24.5; causal, 12 heads, n = 8192 102.9 -> 101.5; d = 128: 12 heads,
+// n = 4096 36.9 -> 35.4, 16 heads 43.4 both; 32 heads, n = 2048, m = 64 34.6 -> 34.0; 14 heads, n = 1300, b = 130 23.3 -> 23.5; causal, 16 heads,
+// n = 8192 192.8 -> 193.0.
 static bool wide_sorting_node(const Geometry& g) { return node_grid<128>(g) > 256 && node_grid<256>(g) <= 256; }
 
 // Whether a node launch sorts by itself.  Every workgroup then counts its whole node, some 4 us of its life at 4096 keys,
@@ -917,7 +920,7 @@ int launch_attn_mfma(const AttnArgs& a, int mode, hipStream_t st) {
   if (a.g.dtype != HA_BF16) return HA_ERR_DTYPE;
   if (mode == kModeExact && a.merge_levels > 0 && !a.part_bf16) return HA_ERR_DTYPE;  // this kernel folds bf16 partial rows
   const bool split = mode == kModeExact && split_exact(a);
-  if (a.stamps != nullptr) {  // the measuring instantiations of the forms the forward pass launches
+  if (a.stamps != nullptr) {  // the measuring instantiations: the node launch behind a sorting launch, the base case
     if (a.g.d == 128) {
       if (mode == kModeNode) return launch_one<128, kModeNode, HA_NW_NODE, true>(a, st);
       return split ? launch_one<128, kModeExact, 4, true, 2>(a, st) : launch_one<128, kModeExact, HA_NW_EXACT, true>(a, st);

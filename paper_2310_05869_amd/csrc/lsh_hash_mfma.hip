@@ -240,12 +240,16 @@ __global__ __launch_bounds__(256) void lsh_hash_mfma_kernel(HashArgs a) {
   }
 }
 
-// Workgroups of four waves, at most: one per CU, every wave streaming its 32-row groups with two of them ahead.  With two per CU small
-// calls give some CUs half a round more than others, and rows of 256 bytes do not need them; rows of 128 bytes, whose groups are half
-// the bytes in flight, do from some 32 groups per wave on.  Forward, 512 -> 256 (MI355X, us): d = 128: 6 heads, n = 4096 29.0 -> 26.9, 16 heads
-// 41.9 -> 41.0, 15 heads, n = 6300 51.0 -> 50.1, 12 heads, n = 32768 188.7 -> 187.2, 32 heads 493.8 -> 487.5, 32 causal heads, n = 131072 9137 ->
-// 9123; d = 64: 8 heads, n = 4096 22.0 -> 21.4, 12 heads 25.3 -> 25.4, 16 heads 28.1 -> 27.3, 32 heads, n = 16384 (32 groups) 133.4 -> 132.7, 64
-// heads, n = 65536 (256 groups) 1338 -> 1363.  320 to 448: up to 6 % slower at small sizes, 768: 4 to 6 %.
+// Workgroups of four waves, at most: one per CU, every wave streaming its 32-row groups with two of them ahead; two for rows of 128 bytes,
+// whose groups are half the bytes in flight, past 32 groups per wave.  Forward, 512 -> 256 (MI355X, us; groups per wave of 256 workgroups;
+// b = m = 64):
+//   d = 64: 8 heads, n = 4096 (2) 18.2 -> 17.5, 12 (3) 20.7 -> 20.6, 16 (4) 27.8 -> 27.0, 32 (8) 38.8 -> 38.6; n = 16384: 24 heads (24) 81.4 -> 81.1,
+//     32 (32) 110.1 -> 110.0, 40 (40) 138.5 -> 140.0, 48 (48) 162.3 -> 166.6, 64 (64) 216.4 -> 221.6; 64 heads, n = 65536 (256) 845 -> 865;
+//     b = m = 256: n = 16384: 29 heads (29) 125.2 -> 125.8, 32 (32) 136.0 -> 135.9, 48 (48) 201.8 -> 204.6; 64 heads, n = 65536 1044 -> 1066
+//   d = 128: 4 heads, n = 4096 (1) 18.9 both, 6 (1.5) 24.1 -> 22.2, 8 (2) 25.6 -> 23.8, 12 (3) 35.6 -> 34.6, 16 (4) 40.2 -> 39.2, 32 (8) 59.2 -> 59.1; 24 heads,
+//     n = 16384 (24) 147.7 -> 147.3; 32 heads, n = 32768 (64) 394 -> 391; 64 heads, n = 65536 (256) 1525 -> 1511; 32 causal heads, n = 131072 no difference
+// The gain of the small calls does not show in the launch's own time (12 heads, n = 4096, d = 64: 7.0 -> 7.3 us in a kernel trace): where it
+// comes from is open.  320 to 448: up to 6 % slower at small sizes, 768: 4 to 6 %.
 static int most_hash_blocks(int64_t ngroups, int d) { return d == 64 && ngroups > 32 * 4 * 256 ? 512 : 256; }
 
 template <int D>

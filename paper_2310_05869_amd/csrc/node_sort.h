@@ -4,7 +4,8 @@
 // What bounds a small call is the number of dependent launches, each some 1.5 us before its first instruction and 2 us
 // until its first data has arrived, so a chain of LDS passes over the node's codes in every workgroup (6 us with the codes' arrival
 // at 4096 keys) beats a sorting launch (6.5 to 8 us and the wait for it), though each workgroup counts the whole node.  Cycles of
-// that (four waves, 4096 keys, 128 buckets): 3.7 k until the codes are there, 2.7 k counting (the LDS atomics), 1.1 k positions, 2.2 k keys
+// that (four waves, 4096 keys, 128 buckets; counters read at these points in a build made for it: the stamped forward keeps the
+// sorting launch): 3.7 k until the codes are there, 2.7 k counting (the LDS atomics), 1.1 k positions, 2.2 k keys
 // of the range, 1.9 k ranks, 1.9 k samples and the last barriers; 17.5 k before two waves' counts shared a word and every wave
 // formed its own positions (forward, 12 heads, n = 4096, d = 64 28.1 -> 26.4 us; fp32, one head, n = 1024 18.5 -> 17.2).  A stable counting sort by bucket, of which
 // only what lies in the workgroup's range of sorted positions is carried out: all keys are counted, the range is found in

@@ -510,11 +510,21 @@ int64_t attn_f32_node_grid(const Geometry& g) {
 //   32 rows, of long blocks: 4 heads, n = 4096, b = m = 256 (512) 70.1 -> 67.0, 6 (768) 99.0 -> 108.2; 8 heads, n = 2100, b = 100 (672) 67.9 -> 68.2;
 //     2 heads, n = 8192, b = 256 (512) 70.8 -> 75.1; of blocks that 64 rows do not fill: 24 heads, n = 1024, b = 32 (768) 57.0 -> 55.0, 32
 //     (1024) 63.9 -> 62.8; 8 heads, n = 4096, b = 32 (1024) 65.1 -> 64.7
+// Where the sort's tables cost a CU one of its workgroups, calls that need it lose more the longer the attention is: d = 64, b = m = 64: 7 heads,
+// n = 6144 (672) 52.7 -> 51.9, m = 256 74.1 -> 73.5; b = m = 256, 11 heads (528) 152.9 -> 154.4; b = 64, m = 1000: 6 heads (576) 152.9 -> 160.0; r = 8: 9
+// heads, n = 4096 (576) 152.0 -> 157.7; b = 128, m = 2000, 8 heads, n = 8192 (512, one to a CU) 352 -> 396; d = 128, the same 643 -> 723.
+template <int D>
+static bool f32_tables_cost(const Geometry& g, int64_t wgs, int kw) {
+  const int64_t sorting = lds_workgroups(f32_qrows_at<D>(g) + 128 / kw * 4, D == 64 ? 3 : 2);
+  return wgs > 256 * sorting && sorting < lds_workgroups(f32_lds_bytes<D>(g.b, g.m, kModeNode), D == 64 ? 3 : 2);
+}
+
 bool attn_f32_sorts(const Geometry& g) {
   const int rows = node_sort_rows(g);
   const int64_t wgs = attn_f32_node_grid(g);
   if (rows > kNodeSortMax || wgs > 1024 || wgs * rows > 4 << 20) return false;
   const int kw = f32_waves_per_group(g.b, node_grid<128>(g));
+  if (g.b + g.m > 320 && (g.d == 64 ? f32_tables_cost<64>(g, wgs, kw) : f32_tables_cost<128>(g, wgs, kw))) return false;
   if (g.d == 64 || 4 * g.b < 3 * 64) return true;
   if (kw > 1 && wgs * rows > 5 << 19) return false;
   return wgs <= (kw == 4 ? 512 : kw == 1 && g.b % 128 == 0 ? 704 : 576) || (kw == 1 && wgs > 768);

@@ -902,12 +902,9 @@ bool attn_mfma_sorts(const Geometry& g) {
   if (wide_sorting_node(g)) return true;
   if (g.d == 128) return wgs <= 512;
   const size_t plain = mfma_lds_bytes<64>(g.b, g.m, kModeNode), sorting = plain + sort_pushes_list<64, 4>(g) + 32 * 4 * 4;
-  auto per_cu = [](size_t lds) {  // LDS is dealt in 128 pieces of 1280 bytes; a fourth workgroup has no registers
-    const size_t fit = 128 / ((lds + 1279) / 1280);
-    return fit < 3 ? (int64_t)fit : (int64_t)3;
-  };
-  if (wgs <= 256 * per_cu(sorting)) return true;
-  if (per_cu(sorting) < per_cu(plain) || wgs > 1024) return false;
+  const int64_t per_cu = lds_workgroups(sorting, 3);  // (a fourth has no registers)
+  if (wgs <= 256 * per_cu) return true;
+  if (per_cu < lds_workgroups(plain, 3) || wgs > 1024) return false;
   const bool whole_words = (g.causal ? g.n_min : g.n) % 16 == 0;
   return rows <= 2048 || (rows > 3200 && rows <= 4096 && whole_words);
 }

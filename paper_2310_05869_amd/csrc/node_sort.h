@@ -60,6 +60,12 @@ constexpr int kNodeSortMax = 32 * 64 * 4;  // keys of a node: 32 per thread of t
 
 __host__ __device__ inline int node_sort_rows(const Geometry& g) { return ((g.causal ? g.n >> 1 : g.n) + 63) & ~63; }
 
+// Workgroups of `lds` bytes that a CU holds, up to `most` by their registers: its 160 KB are dealt in 128 pieces.
+inline int64_t lds_workgroups(size_t lds, int most) {
+  const int64_t fit = 128 / (int64_t)((lds + 1279) / 1280);
+  return fit < most ? fit : most;
+}
+
 typedef uint32_t words4 __attribute__((ext_vector_type(4)));
 // half of a word of `pos`, which is written as words4: no two accesses of the table may be taken for independent by their types
 typedef uint16_t half_word __attribute__((may_alias));

@@ -197,6 +197,12 @@ def test_backward_shared_launches_hold_their_workgroups(ha):
 ]] + [("fp32", *c) for c in [
     (64, 16, 4096, 64, 64, 7, 0, True),        # 1024 workgroups
     (64, 17, 4096, 64, 64, 7, 0, False),
+    (64, 9, 4096, 64, 1000, 7, 0, True),       # 576: three fit the LDS
+    (64, 9, 4096, 64, 1000, 8, 0, False),      # two
+    (64, 8, 4096, 64, 1000, 8, 0, True),       # 512
+    (64, 8, 8192, 128, 2000, 8, 0, False),     # one
+    (64, 7, 6144, 64, 64, 8, 0, True),         # two, of few keys
+    (128, 8, 8192, 128, 2000, 8, 0, False),    # one
     (128, 48, 2048, 128, 128, 7, 0, False),    # of 128 rows: 768
     (128, 44, 2048, 128, 128, 7, 0, True),     # 704
     (128, 52, 2048, 128, 128, 7, 0, True),     # 832

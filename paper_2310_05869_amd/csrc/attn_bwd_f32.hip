@@ -1,6 +1,5 @@
-// Backward pass on the fp32 matrix cores: the arithmetic path for HA_FP32 tensors
-// (v_mfma_f32_32x32x2_f32: every product and sum in fp32), with the same passes and the
-// same buffers as the bf16 backward kernel, so that the host sequence is one and the same.
+// Backward pass of HA_FP32 tensors, with the same passes and the same buffers as the bf16 backward kernel, so that the host sequence is
+// one and the same.  Its products run on the bf16 matrix cores, every operand split in three (split_f32.h).
 //
 // As there, a row of the forward is one softmax over its block keys, its kept sampled keys (weight
 // s/m) and, when causal, the keys of its base-case block (Algorithms 1, 2, 4), and with the final
@@ -8,29 +7,28 @@
 //   P_ij = w_ij exp(<q_i, k_j> - L_i),  dV_j += P_ij dO_i,  dS_ij = P_ij (<dO_i, v_j> - delta_i),
 //   dQ_i += dS_ij k_j,  dK_j += dS_ij q_i.
 //
-// A wave owns 32 "R rows" (queries in the dQ passes, keys in the dK / dV passes): the row, the operand of
-// dP and the accumulators live in its registers.  The "T rows" (keys, resp. queries) come in tiles of 32
-// straight from the caches in operand layout, once row-major for the scores and dP and once
-// transposed for the accumulating products (attn_f32.hip has the layouts): no LDS staging and no
-// barrier, because 64-cycle instructions leave the caches 16 B/clk per CU to deliver.  The dK / dV passes
-// form S and dP once and accumulate both gradients: 4 products, 3 in the dQ passes.
+// A wave owns 32 "R rows" (queries in the dQ passes, keys in the dK / dV passes) and their accumulators.  The "T rows" (keys, resp.
+// queries) come in tiles of 32, row-major for the scores and dP and transposed for the accumulating products (attn_f32.hip has
+// the layouts).  The dK / dV passes form S and dP once and accumulate both gradients: 4 products, 3 in the dQ passes.  The scores are formed
+// as the forward forms them, step by step (P = exp(S - L) then cancels their rounding where scores are large: with the columns of d in
+// another order than the forward's, 64 clusters, scores to 250, dQ's error was 7.3e-5 instead of 1.2e-5).
 //
-// KW waves share a group of R rows, each taking every KW-th tile; their sums are added through LDS in
-// wave order, so results are bit-reproducible.
+// KW ways share a group of R rows, each taking every KW-th tile; their sums are added through LDS in
+// order, so results are bit-reproducible.  KW = 1: four waves of different R rows share the tiles, split once into LDS.  KW = 4 or 8: one group of
+// 32 R rows per workgroup, which lie split in LDS; a wave's T rows come straight from the caches in operand layout, twice (as rows and in
+// columns), and are split in registers.
 //
-// What bounds it: the matrix pipe where the chip is full.  At 4 heads, n = 4096 (at most two waves per SIMD) it is busy
-// 52 - 57 % of the cycles in the exact passes and 14 - 24 % in the node passes; waves wait for issue 55 - 65 % of their
-// time in the former.  The dK / dV passes at d = 64 spill 56 to 108 bytes per lane (two fragments in flight beside rows and
-// accumulators in 256 registers), the launches that small causal problems share 144 (base case) and 64 (a level): one allocation serves all
-// their passes.
-// Measured (MI355X, backward of exact attention, the five algorithmic products
-// counted, seven executed), against two lanes per row with fp32 FMA and separate dK and dV passes, the form before:
-// 8 heads, n = 4096, d = 64 5.5 -> 1.29 ms, d = 128 12.0 -> 2.4 ms; 32 heads, n = 8192, d = 64 17.1 ms = 80 TFLOP/s
-// (112 executed, of 157); 4 causal heads, n = 4096, n_min = 1024, forward + backward 4.07 -> 0.45 ms.  Then the vector
-// work beside the products (masks behind a branch; in the exact passes row addresses in the instructions' offsets and
-// L, delta as four values per load instead of lane exchanges): there dQ 51 -> 45, dK / dV 68 -> 61 us.
+// What bounds it: in large launches the matrix pipe at the clock that the chip's power leaves it (32 heads, n = 8192, d = 64: the seven products
+// of a pair at 1110 TFLOP/s of bf16 products); in small ones (4 heads, n = 4096 in causal blocks of 1024, base case with the sampled keys, 1152
+// workgroups) vector issue, half of the cycles, the splits being some 60 % of it, and workgroups of unequal length (matrix pipe 25 %; 1.4 waves
+// per SIMD of two).  At d = 64 the dK / dV passes spill 176 to 196 bytes per lane with one way, 24 to 28 with more.
+// Measured (MI355X, us; fp32 matrix instructions, T rows always from the caches -> this form), backward of exact attention: 32 heads,
+// n = 8192, d = 64 15000 -> 10430, 16 heads, d = 128 16210 -> 10540; causal, 16 heads, n = 1024 95.6 -> 84.9, d = 128 205 -> 177; 8 heads, n = 4096 547 -> 471,
+// 1120 -> 995; one head, n = 1024 77.3 -> 60.3, 136 -> 119; of HyperAttention: one head, n = 1024, b = m = 64 45.6 -> 39.0, 8 heads, n = 4096, b = m = 256
+// 190 -> 150, d = 128 393 -> 260; causal, 4 heads, n = 4096 in blocks of 1024, b = m = 64 150 -> 115, 279 -> 246.
 #include "attn_common.h"
 #include "bwd_common.h"
+#include "split_f32.h"
 
 namespace ha {
 
@@ -38,47 +36,53 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kFTT = 32;   // T rows per tile
-constexpr int f32_bwd_waves(int kw) { return kw == 8 ? 8 : 4; }  // of a workgroup, by the waves that share 32 R rows
 
-template <int D, int NW = 4>
+// LDS: the ways' tiles (Y and B) and L and delta of their rows, or, RG = 1, the R rows; the key list of a node's dQ pass; in the end the
+// staged rows, over the tiles; behind all else the sampled keys of a block-key pass.
+template <int D, int RG, int KW>
 struct F32BwdLds {
+  static constexpr int WAY = 2 * SplitTile<D>::BYTES;  // bytes of a way's tiles
+  static constexpr int SC_AT = (RG > 1 ? KW : 1) * WAY;
+  static constexpr int LIST_AT = SC_AT + (RG > 1 ? KW * 2 * kFTT * 4 : 0);
   static constexpr int ROW = D + 4;  // floats per staged row
-  static constexpr int BYTES = NW * 32 * ROW * 4;
+  static constexpr int ROWS = RG * KW * 32 * ROW * 4;
+  __host__ __device__ static size_t hits_at(const Geometry& g, int mode) {
+    const size_t list = mode == kBwdDqNode ? (size_t)(((g.b + g.m + 63) & ~63) + 64) * 4 + 64 : 0;
+    return LIST_AT + list > (size_t)ROWS ? LIST_AT + list : (size_t)ROWS;
+  }
+  __host__ __device__ static size_t bytes(const Geometry& g, int mode) {
+    return hits_at(g, mode) + (mode == kBwdDkvBlock && !g.causal ? sample_hits_bytes(g) : 0);
+  }
 };
 
-template <int D>
-__host__ __device__ inline size_t bwd_f32_lds_bytes(const Geometry& g, int mode) {
-  const size_t list = mode == kBwdDqNode ? (size_t)(((g.b + g.m + 63) & ~63) + 64) * 4 + 64 : 0;
-  const size_t hits = mode == kBwdDkvBlock && !g.causal ? sample_hits_bytes(g) : 0;  // behind the rows
-  return list > (size_t)F32BwdLds<D>::BYTES ? list : (size_t)F32BwdLds<D>::BYTES + hits;
-}
-
-// d = 128 keeps up to 483 registers per lane (two fragments in flight beside rows and accumulators): one wave per SIMD
+// RG waves, of 32 R rows each, share the T tiles of a way; the KW ways take every KW-th tile.  RG = 1: a wave's tiles are its own
+// and come straight from the caches in operand layout, each row twice (as a row and in columns), and the KW waves share the R rows.
 // FINAL: the node passes of an unmasked problem, which write the final gradients.
 // wg: the workgroup's number among the pass's wgs.
-template <int D, int MODE, int KW, bool FINAL>
+template <int D, int MODE, int RG, int KW, bool FINAL>
 __device__ __forceinline__ void bwd_f32_pass(const BwdArgs& a, const int wg, const int wgs, unsigned char* smem) {
   constexpr bool kDq = (MODE == kBwdDqNode || MODE == kBwdDqExact);
   constexpr bool kExact = (MODE == kBwdDqExact || MODE == kBwdDkvExact);
   constexpr bool kSorted = (MODE == kBwdDkvBlock || MODE == kBwdDkvSamp);
   constexpr bool kHits = FINAL && MODE == kBwdDkvBlock;  // sampled keys' sums added here
-  constexpr int NW = f32_bwd_waves(KW), kFBT = 64 * NW;
-  constexpr int kRT = 32 * (NW / KW);
-  constexpr int KJ = D / 8;
+  constexpr int NW = RG * KW, kFBT = 64 * NW;
+  constexpr int kRT = 32 * RG;
+  constexpr int KS = D / 16;  // steps of a score's product
   constexpr int DT = D / 32;
-  // dQ: a dP is two sums of half the columns each; as one chain of d products it had dQ's error above that of the half-row
-  // sums of the form before (4 blocks of 256 rows, d = 128: 4.8e-7 against 4.2e-7 relative; with this and log row sums of
-  // one rounding 4.0e-7).  The scores stay one chain, the forward's: P = exp(S - L) then cancels their rounding where
-  // scores are large (64 clusters, scores to 250: dQ's error 2.1e-5, with halves 1.7e-4).  The dK / dV passes have no
-  // registers for it, and their errors are below those of the form before.
-  constexpr int kChains = kDq ? 2 : 1;
+  using L = F32BwdLds<D, RG, KW>;
+  using T = SplitTile<D>;
   const AttnArgs& f = a.f;
   const Geometry& g = f.g;
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lq = lane & 31, h = lane >> 5;
-  const int kw = wave % KW, grp = wave / KW;
-  int32_t* scratch = reinterpret_cast<int32_t*>(smem);
+  const int grp = wave % RG, kw = wave / RG;
+  const int wtid = tid % (64 * RG);  // within the way
+  constexpr bool kShared = RG > 1;
+  unsigned char* ytile = smem + (kShared ? kw * L::WAY : 0);
+  unsigned char* btile = ytile + T::BYTES;
+  float* sc = reinterpret_cast<float*>(smem + L::SC_AT) + kw * 2 * kFTT;
+  int32_t* scratch = reinterpret_cast<int32_t*>(smem + L::LIST_AT);
   int32_t* list = scratch + 16;
 
   // ---- which part of the problem this workgroup owns ----
@@ -102,33 +106,56 @@ __device__ __forceinline__ void bwd_f32_pass(const BwdArgs& a, const int wg, con
   const int r_use = r_in_tile < w.rows_valid ? r_in_tile : 0;
   int blk_r = -1;
   const int r_row = bwd_r_row<MODE>(a, b, r_use, &blk_r);
-  f32x4 x[KJ], av[KJ];
-#pragma unroll
-  for (int j = 0; j < KJ; ++j) {
-    x[j] = *reinterpret_cast<const f32x4*>(Xh + (int64_t)r_row * D + 8 * j + 4 * h);
-    av[j] = *reinterpret_cast<const f32x4*>(Ah + (int64_t)r_row * D + 8 * j + 4 * h);
-  }
+  Split8 xs[kShared ? KS : 1], as[kShared ? KS : 1];
   float L_r = 0.f, del_r = 0.f;
-  if (kDq) {
-    L_r = lse_h[r_row];
-    if (a.delta_out == nullptr) {
-      del_r = del_h[r_row];
-    } else {
-      const float* Oh = reinterpret_cast<const float*>(a.O) + ((int64_t)w.bh * g.n + r_row) * D + 4 * h;
-      f32x4 s = {0.f, 0.f, 0.f, 0.f};
+  {
+    f32x4 x[2 * KS], av[2 * KS];  // columns 16 s + 8 h ... + 7 of step s
+    if (kShared || (kDq && a.delta_out != nullptr)) {
 #pragma unroll
-      for (int j = 0; j < KJ; ++j) {
-        const f32x4 o = *reinterpret_cast<const f32x4*>(Oh + 8 * j);
-#pragma unroll
-        for (int z = 0; z < 4; ++z) s[z] = __builtin_fmaf(o[z], av[j][z], s[z]);
+      for (int j = 0; j < 2 * KS; ++j) {
+        const int64_t at = (int64_t)r_row * D + 16 * (j / 2) + 8 * h + 4 * (j % 2);
+        if (kShared) x[j] = *reinterpret_cast<const f32x4*>(Xh + at);
+        av[j] = *reinterpret_cast<const f32x4*>(Ah + at);
       }
-      del_r = (s[0] + s[1]) + (s[2] + s[3]);
-      del_r += __shfl_xor(del_r, 32);
-      if (h == 0 && kw == 0 && r_in_tile < w.rows_valid) a.delta_out[(int64_t)w.bh * g.n + r_row] = del_r;
+    }
+    if constexpr (kShared) {
+#pragma unroll
+      for (int s = 0; s < KS; ++s) {
+        xs[s] = split8<true>([&](int e) { return x[2 * s + e / 4][e % 4]; });
+        as[s] = split8<true>([&](int e) { return av[2 * s + e / 4][e % 4]; });
+      }
+    } else {
+      for (int i = tid; i < 32 * T::PPR; i += kFBT) {
+        const int r = i / T::PPR, piece = i % T::PPR;
+        int blk;
+        const int64_t at = (int64_t)bwd_r_row<MODE>(a, b, r < w.rows_valid ? r : 0, &blk) * D + piece * 8;
+        const f32x4 x0 = *reinterpret_cast<const f32x4*>(Xh + at), x1 = *reinterpret_cast<const f32x4*>(Xh + at + 4);
+        const f32x4 a0 = *reinterpret_cast<const f32x4*>(Ah + at), a1 = *reinterpret_cast<const f32x4*>(Ah + at + 4);
+        T::store(ytile, r, piece, x0, x1);
+        T::store(btile, r, piece, a0, a1);
+      }
+    }
+    if (kDq) {
+      L_r = lse_h[r_row];
+      if (a.delta_out == nullptr) {
+        del_r = del_h[r_row];
+      } else {
+        const float* Oh = reinterpret_cast<const float*>(a.O) + ((int64_t)w.bh * g.n + r_row) * D + 8 * h;
+        f32x4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < 2 * KS; ++j) {
+          const f32x4 o = *reinterpret_cast<const f32x4*>(Oh + 16 * (j / 2) + 4 * (j % 2));
+#pragma unroll
+          for (int z = 0; z < 4; ++z) s[z] = __builtin_fmaf(o[z], av[j][z], s[z]);
+        }
+        del_r = (s[0] + s[1]) + (s[2] + s[3]);
+        del_r += __shfl_xor(del_r, 32);
+        if (h == 0 && kw == 0 && r_in_tile < w.rows_valid) a.delta_out[(int64_t)w.bh * g.n + r_row] = del_r;
+      }
     }
   }
 
-  const SampleHits sh = sample_hits(smem + F32BwdLds<D>::BYTES);
+  const SampleHits sh = sample_hits(smem + L::hits_at(g, MODE));
   if (kHits) find_sample_hits<kFBT>(a, b, sh, fetch_sample_head(a, b, tid));
 
   // ---- the T rows ----
@@ -146,31 +173,80 @@ __device__ __forceinline__ void bwd_f32_pass(const BwdArgs& a, const int wg, con
     nT = max(0, w.k1 - w.k0);
   }
   const float nat_bias = ((MODE == kBwdDqNode || MODE == kBwdDkvSamp) && g.m > 0) ? logf((float)w.nr.s / (float)g.m) : 0.f;
-  // tiles of this wave's group: causal passes leave out those that lie wholly on the masked side
-  int kt_lo = 0, kt_hi = (nT + kFTT - 1) / kFTT;
+  // tiles of the workgroup; in causal passes a wave leaves out those that lie wholly on its masked side
+  const int tiles = (nT + kFTT - 1) / kFTT;
+  int kt_lo = 0, kt_hi = tiles;
   if (MODE == kBwdDqExact && f.exact_causal) kt_hi = min(kt_hi, (w.q0 - w.k0 + grp * 32 + 31) / kFTT + 1);
   if (MODE == kBwdDkvExact && f.exact_causal) kt_lo = grp;  // T starts at the workgroup's first key
-  auto t_row = [&](int kt) -> int {  // row within the head of T position kt * 32 + lq (clamped to an existing one)
-    if (kExact) return w.k0 + kt * kFTT + lq;
-    const int tp = min(kt * kFTT + lq, nT - 1);
-    if (kSorted) return tperm[tp];
-    return list[tp];
-  };
 
+  // ---- tile movers.  Shared tiles: a thread fetches pieces of eight floats, splits them and puts them into its way's tiles ----
   // (exact passes: rows past the T rows' end read as zeros and are masked)
+  constexpr int NP = kFTT * T::PPR / (64 * RG);  // pieces per thread and tensor
   const uint32_t bytes = (uint32_t)(kExact ? w.k1 : g.n) * (uint32_t)(D * 4);
   const __amdgpu_buffer_rsrc_t yrsrc = __builtin_amdgcn_make_buffer_rsrc((void*)Yh, 0, (int)bytes, 0x00020000);
   const __amdgpu_buffer_rsrc_t brsrc = __builtin_amdgcn_make_buffer_rsrc((void*)Bh, 0, (int)bytes, 0x00020000);
   const __amdgpu_buffer_rsrc_t lrsrc = __builtin_amdgcn_make_buffer_rsrc((void*)lse_h, 0, (kExact ? w.k1 : g.n) * 4, 0x00020000);
   const __amdgpu_buffer_rsrc_t drsrc = __builtin_amdgcn_make_buffer_rsrc((void*)del_h, 0, (kExact ? w.k1 : g.n) * 4, 0x00020000);
-  auto load_rows = [&](const __amdgpu_buffer_rsrc_t& rsrc, int row, f32x4 (&v)[KJ]) {
+  int trow[NP];  // rows of the tile that is fetched next
+  auto find_rows = [&](int kt) {
 #pragma unroll
-    for (int j = 0; j < KJ; ++j)
-      v[j] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, row * (D * 4) + 16 * h, 32 * j, 0));
+    for (int i = 0; i < NP; ++i) {
+      const int tp = kt * kFTT + (wtid + i * 64 * RG) / T::PPR;
+      if (kExact) trow[i] = w.k0 + tp;
+      else trow[i] = kSorted ? tperm[min(tp, nT - 1)] : list[min(tp, nT - 1)];
+    }
   };
-  // element i of an accumulator is T row 8 (i / 4) + 4 h + i % 4 of the tile; lane l < 32 holds row l's values
+  f32x4 ys[NP][2], bs[NP][2];
+  float sl[NP], sd[NP];  // dK / dV passes: L and delta of the row
+  auto fetch = [&]() {
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      const int off = trow[i] * (D * 4) + (wtid + i * 64 * RG) % T::PPR * 32;
+      ys[i][0] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(yrsrc, off, 0, 0));
+      ys[i][1] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(yrsrc, off + 16, 0, 0));
+      bs[i][0] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(brsrc, off, 0, 0));
+      bs[i][1] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(brsrc, off + 16, 0, 0));
+      if (!kDq) {
+        sl[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(lrsrc, trow[i] * 4, 0, 0));
+        sd[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(drsrc, trow[i] * 4, 0, 0));
+      }
+    }
+  };
+  auto store = [&]() {
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      const int r = (wtid + i * 64 * RG) / T::PPR, piece = (wtid + i * 64 * RG) % T::PPR;
+      T::store(ytile, r, piece, ys[i][0], ys[i][1]);
+      T::store(btile, r, piece, bs[i][0], bs[i][1]);
+      if (!kDq && piece == 0) {
+        sc[r] = sl[i];
+        sc[kFTT + r] = sd[i];
+      }
+    }
+  };
+  const int row_at = T::row_at(lane), col_at = T::col_at(lane);
+  // RG = 1: the lane's T row (position 32 kt + lq) in pieces, and columns 32 dt + lq of rows 8 (i / 4) + 4 h + i % 4
+  int row = 0;
+  float scl = 0.f, scd = 0.f;  // dK / dV of sorted rows: L and delta of the T row this lane holds
+  f32x4 yf[kShared ? 1 : 2 * KS];
+  auto load_rows = [&](const __amdgpu_buffer_rsrc_t& rsrc, int of, f32x4 (&v)[kShared ? 1 : 2 * KS]) {
+    if constexpr (!kShared) {
+#pragma unroll
+      for (int j = 0; j < 2 * KS; ++j)
+        v[j] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, of * (D * 4) + 32 * h + 16 * (j % 2), 64 * (j / 2), 0));
+    }
+  };
+  auto fetch_own = [&](int kt) {
+    const int tp = min(kt * kFTT + lq, nT - 1);
+    row = kExact ? w.k0 + kt * kFTT + lq : kSorted ? tperm[tp] : list[tp];
+    load_rows(yrsrc, row, yf);
+    if (!kDq && !kExact) {
+      scl = lse_h[row];
+      scd = del_h[row];
+    }
+  };
   auto of_elem = [&](auto v, int i) { return __shfl(v, 8 * (i / 4) + 4 * h + (i % 4)); };
-  auto load_cols = [&](const __amdgpu_buffer_rsrc_t& rsrc, int row, int kt, float (&v)[16][DT], int i0, int count) {
+  auto load_cols = [&](const __amdgpu_buffer_rsrc_t& rsrc, int of, int kt, float (&v)[16][DT], int i0, int count) {
     // Consecutive rows.  All of the row is in the lane's offset: the bounds check covers it, not the scalar one.  One
     // running offset (opaque, or the compiler keeps one register per eight rows across the loop): 241.3 us where constants of
     // one offset take 245.6 (4 heads, n = 4096 in causal blocks of 1024, forward + backward).
@@ -190,7 +266,7 @@ __device__ __forceinline__ void bwd_f32_pass(const BwdArgs& a, const int wg, con
     }
 #pragma unroll
     for (int i = i0; i < i0 + count; ++i) {
-      const int off = of_elem(row, i) * (D * 4) + 4 * lq;
+      const int off = of_elem(of, i) * (D * 4) + 4 * lq;
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt) v[i][dt] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, off, 128 * dt, 0));
     }
@@ -205,52 +281,69 @@ __device__ __forceinline__ void bwd_f32_pass(const BwdArgs& a, const int wg, con
     for (int dt = 0; dt < (kDq ? 1 : DT); ++dt) acc2[dt][i] = 0.f;
   }
 
-  int row = 0;
-  float sc_l = 0.f, sc_d = 0.f;  // dK / dV passes: L and delta of the T row this lane holds
-  f32x4 yf[KJ];
-  auto fetch = [&](int kt) {
-    row = t_row(kt);
-    load_rows(yrsrc, row, yf);
-    if (!kDq && !kExact) {
-      sc_l = lse_h[row];
-      sc_d = del_h[row];
+  if constexpr (kShared) {
+    if (kw < tiles) {
+      find_rows(kw);
+      fetch();
+      if (!kExact) find_rows(kw + KW);
     }
-  };
-  if (kt_lo + kw < kt_hi) fetch(kt_lo + kw);
-  for (int kt = kt_lo + kw; kt < kt_hi; kt += KW) {
-    const int row_c = row;
-    const float scl = sc_l, scd = sc_d;
-    f32x4 l4[4], d4[4];  // dK / dV of exact attention: L and delta of the lane's T rows, four consecutive ones at a time
-    if (kExact && !kDq) {
+  } else {
+    __syncthreads();  // the R rows stand
+    if (kt_lo + kw < kt_hi) fetch_own(kt_lo + kw);
+  }
+  // (shared tiles: the same trips for all ways, the barriers are the workgroup's)
+  const int kt_end = kShared ? (tiles + KW - 1) / KW * KW : kt_hi;
+  for (int kt = (kShared ? 0 : kt_lo) + kw; kt < kt_end; kt += KW) {
+    if constexpr (kShared) {
+      if (kt >= KW) __syncthreads();  // the tiles before are read no more
+      if (kt < tiles) store();
+      __syncthreads();
+      if (kt + KW < tiles) {
+        if (kExact) find_rows(kt + KW);
+        fetch();
+        if (!kExact) find_rows(kt + 2 * KW);
+      }
+      if (kt < kt_lo || kt >= kt_hi) continue;
+    }
+    f32x4 l4[4], d4[4];  // dK / dV passes: L and delta of the lane's T rows
+    if (!kDq && (kShared || kExact)) {
 #pragma unroll
       for (int q4 = 0; q4 < 4; ++q4) {
         const int at = (w.k0 + kt * kFTT + 8 * q4 + 4 * h) * 4;
-        l4[q4] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(lrsrc, at, 0, 0));
-        d4[q4] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(drsrc, at, 0, 0));
+        l4[q4] = kShared ? *reinterpret_cast<const f32x4*>(sc + 8 * q4 + 4 * h) : __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(lrsrc, at, 0, 0));
+        d4[q4] = kShared ? *reinterpret_cast<const f32x4*>(sc + kFTT + 8 * q4 + 4 * h) : __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(drsrc, at, 0, 0));
       }
     }
-    f32x4 bf[KJ];
-    load_rows(brsrc, row_c, bf);
-    f32x16 c, es[kChains];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      c[i] = 0.f;
-#pragma unroll
-      for (int k = 0; k < kChains; ++k) es[k][i] = 0.f;
-    }
-#pragma unroll
-    for (int j = 0; j < KJ; ++j)
-#pragma unroll
-      for (int z = 0; z < 4; ++z) c = __builtin_amdgcn_mfma_f32_32x32x2f32(yf[j][z], x[j][z], c, 0, 0, 0);
-    float tv[16][DT];
-    load_cols(kDq ? yrsrc : brsrc, row_c, kt, tv, 0, 16);
-#pragma unroll
-    for (int j = 0; j < KJ; ++j)
-#pragma unroll
-      for (int z = 0; z < 4; ++z) es[j % kChains] = __builtin_amdgcn_mfma_f32_32x32x2f32(bf[j][z], av[j][z], es[j % kChains], 0, 0, 0);
+    const int row_c = row;
+    const float scl_c = scl, scd_c = scd;
+    f32x4 bf[kShared ? 1 : 2 * KS];
+    if (!kShared) load_rows(brsrc, row_c, bf);
 
-    f32x16 e = es[0];
-    if constexpr (kChains == 2) e += es[1];
+    f32x16 c, e;
+    {
+      f32x16 small;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) c[i] = small[i] = 0.f;
+#pragma unroll
+      for (int s = 0; s < KS; ++s) {
+        if constexpr (kShared) split_product(T::row_frag(ytile, row_at, s), xs[s], c, small);
+        else split_product(split8<true>([&](int i) { return yf[2 * s + i / 4][i % 4]; }), T::row_frag(ytile, row_at, s), c, small);
+      }
+      split_sum(c, small);
+    }
+    float tv[kShared ? 1 : 16][DT];
+    if constexpr (!kShared) load_cols(kDq ? yrsrc : brsrc, row_c, kt, tv, 0, 16);
+    {
+      f32x16 small;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) e[i] = small[i] = 0.f;
+#pragma unroll
+      for (int s = 0; s < KS; ++s) {
+        if constexpr (kShared) split_product(T::row_frag(btile, row_at, s), as[s], e, small);
+        else split_product(split8<true>([&](int i) { return bf[2 * s + i / 4][i % 4]; }), T::row_frag(btile, row_at, s), e, small);
+      }
+      split_sum(e, small);
+    }
 
     // masks, on the tiles that have any: in the sampled-key pass the keys differ by lane
     const int tbase = kt * kFTT;
@@ -283,35 +376,49 @@ __device__ __forceinline__ void bwd_f32_pass(const BwdArgs& a, const int wg, con
     }
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-      const float L = kDq ? L_r : kExact ? l4[i / 4][i % 4] : of_elem(scl, i);
-      const float dl = kDq ? del_r : kExact ? d4[i / 4][i % 4] : of_elem(scd, i);
+      const bool quads = kShared || kExact;
+      const float L = kDq ? L_r : quads ? l4[i / 4][i % 4] : of_elem(scl_c, i);
+      const float dl = kDq ? del_r : quads ? d4[i / 4][i % 4] : of_elem(scd_c, i);
       float p = exp_split(c[i] + tile_bias - L);
       if (L == -INFINITY) p = 0.f;  // (a row without keys)
       c[i] = p;
       e[i] = p * (e[i] - dl);
     }
-    if constexpr (!kDq) {
+    if constexpr (kShared) {
+      Split8 ps[2];  // 16 T rows each
+      if constexpr (!kDq) {
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf) ps[hf] = split8<false>([&](int i) { return c[8 * hf + i]; });
+        split_tile_products([&](int dt, int hf) { return T::col_frag(btile, col_at, hf, dt); }, ps, acc2);
+      }
+#pragma unroll
+      for (int hf = 0; hf < 2; ++hf) ps[hf] = split8<true>([&](int i) { return e[8 * hf + i]; });
+      split_tile_products([&](int dt, int hf) { return T::col_frag(ytile, col_at, hf, dt); }, ps, acc1);
+    } else if constexpr (!kDq) {
       // dV and dK half a tile at a time: the Q rows of a half arrive while the other half's dV products run
       float yv[16][DT];
 #pragma unroll
       for (int hf = 0; hf < 2; ++hf) {
         load_cols(yrsrc, row_c, kt, yv, 8 * hf, 8);
+        const Split8 p = split8<false>([&](int i) { return c[8 * hf + i]; });
 #pragma unroll
-        for (int i = 8 * hf; i < 8 * hf + 8; ++i)
-#pragma unroll
-          for (int dt = 0; dt < DT; ++dt) acc2[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(tv[i][dt], c[i], acc2[dt], 0, 0, 0);
+        for (int dt = 0; dt < DT; ++dt) split_product(split8<true>([&](int i) { return tv[8 * hf + i][dt]; }), p, acc2[dt]);
       }
-      if (kt + KW < kt_hi) fetch(kt + KW);
+      if (kt + KW < kt_hi) fetch_own(kt + KW);
 #pragma unroll
-      for (int i = 0; i < 16; ++i)
+      for (int hf = 0; hf < 2; ++hf) {
+        const Split8 ds = split8<true>([&](int i) { return e[8 * hf + i]; });
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt) acc1[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(yv[i][dt], e[i], acc1[dt], 0, 0, 0);
+        for (int dt = 0; dt < DT; ++dt) split_product(split8<true>([&](int i) { return yv[8 * hf + i][dt]; }), ds, acc1[dt]);
+      }
     } else {
-      if (kt + KW < kt_hi) fetch(kt + KW);
+      if (kt + KW < kt_hi) fetch_own(kt + KW);
 #pragma unroll
-      for (int i = 0; i < 16; ++i)
+      for (int hf = 0; hf < 2; ++hf) {
+        const Split8 ds = split8<true>([&](int i) { return e[8 * hf + i]; });
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt) acc1[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(tv[i][dt], e[i], acc1[dt], 0, 0, 0);
+        for (int dt = 0; dt < DT; ++dt) split_product(split8<true>([&](int i) { return tv[8 * hf + i][dt]; }), ds, acc1[dt]);
+      }
     }
   }
 
@@ -319,7 +426,7 @@ __device__ __forceinline__ void bwd_f32_pass(const BwdArgs& a, const int wg, con
   // (the first level that holds the row on the pass's side) or add (later levels) fp32 rows of the accumulated
   // gradient; exact passes write the final gradient after adding the accumulated row where some level
   // holds this row (queries: second half of the node; keys: first half) ----
-  constexpr int RS = F32BwdLds<D>::ROW;
+  constexpr int RS = L::ROW;
   float* rows_lds = reinterpret_cast<float*>(smem);
   const int64_t srow0 = (int64_t)w.bh * bwd_chunks_per_node(g, a.chunk, 0) * g.m;  // sample 0's sums (kHits)
   auto write_out = [&](const auto& acc, float* node_dst, const float* samp, float* fin, const float* lvl) {
@@ -334,10 +441,10 @@ __device__ __forceinline__ void bwd_f32_pass(const BwdArgs& a, const int wg, con
     constexpr int LPR = D / 4;  // lanes per row
     for (int idx = tid; idx < w.rows_valid * LPR; idx += kFBT) {
       const int r = idx / LPR, col = (idx % LPR) * 4;
-      const float* src = rows_lds + ((r / 32) * KW * 32 + (r & 31)) * RS + col;
+      const float* src = rows_lds + r * RS + col;
       f32x4 v = *reinterpret_cast<const f32x4*>(src);
 #pragma unroll
-      for (int k = 1; k < KW; ++k) v += *reinterpret_cast<const f32x4*>(src + k * 32 * RS);
+      for (int k = 1; k < KW; ++k) v += *reinterpret_cast<const f32x4*>(src + k * kRT * RS);
       if (kHits && samp != nullptr) {
         const int j = sh.first[r];
         const f32x4 sv = *reinterpret_cast<const f32x4*>(samp + (srow0 + (j != kNoSample ? j : 0)) * D + col);
@@ -362,10 +469,10 @@ __device__ __forceinline__ void bwd_f32_pass(const BwdArgs& a, const int wg, con
   if constexpr (!kDq) write_out(acc2, a.out2, a.samp2, reinterpret_cast<float*>(a.fin2), a.lvl2);
 }
 
-template <int D, int MODE, int KW, bool FINAL>
-__global__ __launch_bounds__(64 * f32_bwd_waves(KW), D == 64 ? 2 : 1) void attn_bwd_f32_kernel(BwdArgs a) {
+template <int D, int MODE, int RG, int KW, bool FINAL>
+__global__ __launch_bounds__(64 * RG * KW, D == 64 ? 2 : 1) void attn_bwd_f32_kernel(BwdArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  bwd_f32_pass<D, MODE, KW, FINAL>(a, (int)blockIdx.x, (int)gridDim.x, smem);
+  bwd_f32_pass<D, MODE, RG, KW, FINAL>(a, (int)blockIdx.x, (int)gridDim.x, smem);
 }
 
 // Passes of a small causal problem side by side in one launch.  One behind the other each of them leaves the chip half empty and
@@ -373,10 +480,11 @@ __global__ __launch_bounds__(64 * f32_bwd_waves(KW), D == 64 ? 2 : 1) void attn_
 // gradients of fp32 tensors can hold the sums over the parts themselves, so the base case, which writes every row, comes
 // first, and nothing but the order of additions ties the passes together: the base case's dK / dV and dQ and the sampled
 // keys are one launch, longest workgroups first, then each level's dK / dV and dQ another.
-// Forward + backward, passes apart -> shared (MI355X): 4 heads, n = 4096, n_min = 1024, b = m = 64, d = 64 239 -> 214 us, d = 128 447 ->
-// 386; 1 head, n = 2048 170 -> 112; 1 head, n = 8192 251 -> 183; 3 heads, n = 1024, n_min = 256 134 -> 85; 12 heads, n = 4096 558 -> 502.
-// Where the passes fill the chip (one wave per group of rows) they stay apart, with the sums in rows of the workspace: base
-// case first there too, 8 heads, n = 8192, n_min = 2048, b = m = 256 took 1319 instead of 1284 us.
+// Backward, passes apart -> shared (MI355X, us; d = 64, d = 128): 4 heads, n = 4096, n_min = 1024, b = m = 64 140 -> 109, 293 -> 236; 1 head, n = 2048
+// 92 -> 51, 175 -> 89; 1 head, n = 8192 145 -> 92, 266 -> 162; 3 heads, n = 1024, n_min = 256 85 -> 45, 141 -> 72; 12 heads, n = 4096 297 -> 264, 714 -> 650.
+// Where the passes fill the chip (small_pass) they stay apart, with the sums in rows of the workspace: d = 64, 16 heads, n = 4096, n_min = 1024, b = m = 128
+// (512 workgroups of 128 rows in the base case) 422 -> 391, 24 (768) 593 -> 602; 8 heads, n = 8192, n_min = 2048, b = m = 256 (512) 708 -> 678, 10 heads,
+// n_min = 4096 (640) 1149 -> 1270; d = 128: 14 heads, n = 4096 (448) 970 -> 864, 16 (512) 909 -> 963.
 template <int D, bool NODES>
 __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_bwd_f32_shared_kernel(BwdShared m) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -384,50 +492,55 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_bwd_f32_shared_kern
   const int first1 = m.part[1].first, first2 = m.part[2].first;
   if constexpr (NODES) {
     if (wg < first1) {
-      if (wg < m.part[0].count) bwd_f32_pass<D, kBwdDkvBlock, 4, false>(m.part[0].a, wg, m.part[0].count, smem);
+      if (wg < m.part[0].count) bwd_f32_pass<D, kBwdDkvBlock, 1, 4, false>(m.part[0].a, wg, m.part[0].count, smem);
     } else if (wg - first1 < m.part[1].count) {
-      bwd_f32_pass<D, kBwdDqNode, 4, false>(m.part[1].a, wg - first1, m.part[1].count, smem);
+      bwd_f32_pass<D, kBwdDqNode, 1, 4, false>(m.part[1].a, wg - first1, m.part[1].count, smem);
     }
   } else {
     if (wg < first1) {
-      if (wg < m.part[0].count) bwd_f32_pass<D, kBwdDkvExact, 4, false>(m.part[0].a, wg, m.part[0].count, smem);
+      if (wg < m.part[0].count) bwd_f32_pass<D, kBwdDkvExact, 1, 4, false>(m.part[0].a, wg, m.part[0].count, smem);
     } else if (wg < first2) {
-      if (wg - first1 < m.part[1].count) bwd_f32_pass<D, kBwdDqExact, 4, false>(m.part[1].a, wg - first1, m.part[1].count, smem);
+      if (wg - first1 < m.part[1].count) bwd_f32_pass<D, kBwdDqExact, 1, 4, false>(m.part[1].a, wg - first1, m.part[1].count, smem);
     } else if (wg - first2 < m.part[2].count) {
-      bwd_f32_pass<D, kBwdDkvSamp, 4, false>(m.part[2].a, wg - first2, m.part[2].count, smem);
+      bwd_f32_pass<D, kBwdDkvSamp, 1, 4, false>(m.part[2].a, wg - first2, m.part[2].count, smem);
     }
   }
 }
 
-template <int D, int MODE, int KW, bool FINAL>
+template <int D, int MODE, int RG, int KW, bool FINAL>
 static int launch_bwd_f32_form(const BwdArgs& args, int grid, hipStream_t st) {
   BwdArgs a = args;
-  constexpr int NW = f32_bwd_waves(KW);
-  if (MODE == kBwdDqNode || MODE == kBwdDkvBlock) set_node_divs<32 * (NW / KW)>(a.f);
-  if (MODE == kBwdDqExact || MODE == kBwdDkvExact) set_exact_divs<32 * (NW / KW)>(a.f);
+  if (MODE == kBwdDqNode || MODE == kBwdDkvBlock) set_node_divs<32 * RG>(a.f);
+  if (MODE == kBwdDqExact || MODE == kBwdDkvExact) set_exact_divs<32 * RG>(a.f);
   a.f.exact_lpt = KW == 8;
-  const size_t lds = KW == 8 ? (size_t)F32BwdLds<D, NW>::BYTES : bwd_f32_lds_bytes<D>(a.f.g, MODE);
+  const size_t lds = F32BwdLds<D, RG, KW>::bytes(a.f.g, MODE);
   static std::atomic<uint64_t> lds_set{0};  // per instantiation: devices on which the LDS limit is raised
-  if (allow_full_lds(reinterpret_cast<const void*>(&attn_bwd_f32_kernel<D, MODE, KW, FINAL>), lds_set) != HA_OK) return HA_ERR_LAUNCH;
-  hipLaunchKernelGGL((attn_bwd_f32_kernel<D, MODE, KW, FINAL>), dim3((unsigned)grid), dim3(64 * NW), lds, st, a);
+  if (allow_full_lds(reinterpret_cast<const void*>(&attn_bwd_f32_kernel<D, MODE, RG, KW, FINAL>), lds_set) != HA_OK) return HA_ERR_LAUNCH;
+  hipLaunchKernelGGL((attn_bwd_f32_kernel<D, MODE, RG, KW, FINAL>), dim3((unsigned)grid), dim3(64 * RG * KW), lds, st, a);
   return check_launch();
 }
 
-template <int D, int MODE, int KW>
+template <int D, int MODE, int RG, int KW>
 static int launch_bwd_f32_one(const BwdArgs& a, hipStream_t st) {
-  const int64_t grid = bwd_grid<32 * (f32_bwd_waves(KW) / KW)>(a, MODE);
+  const int64_t grid = bwd_grid<32 * RG>(a, MODE);
   if (grid <= 0) return HA_OK;
   if (grid > kMaxGrid) return HA_ERR_SHAPE;
   if constexpr (MODE == kBwdDqNode || MODE == kBwdDkvBlock)
-    if (!a.f.g.causal) return launch_bwd_f32_form<D, MODE, KW, true>(a, (int)grid, st);
-  return launch_bwd_f32_form<D, MODE, KW, false>(a, (int)grid, st);
+    if (!a.f.g.causal) return launch_bwd_f32_form<D, MODE, RG, KW, true>(a, (int)grid, st);
+  return launch_bwd_f32_form<D, MODE, RG, KW, false>(a, (int)grid, st);
+}
+
+// Whether workgroups of 128 R rows fill the runs of rows they are cut from (blocks, sample sets) to three quarters.
+template <int MODE>
+static bool rows_fit_128(const BwdArgs& a) {
+  const Geometry& g = a.f.g;
+  const int run = MODE == kBwdDkvSamp ? g.m : (MODE == kBwdDqNode || MODE == kBwdDkvBlock) ? g.b : a.f.exact_block;
+  return 3 * (int64_t)((run + 127) / 128 * 128) <= 4 * (int64_t)run;
 }
 
 template <int MODE>
-static bool four_waves(const BwdArgs& a) {
-  const Geometry& g = a.f.g;
-  const int run = MODE == kBwdDkvSamp ? g.m : (MODE == kBwdDqNode || MODE == kBwdDkvBlock) ? g.b : a.f.exact_block;
-  return 3 * (int64_t)((run + 127) / 128 * 128) > 4 * (int64_t)run || 4 * bwd_grid<128>(a, MODE) < 2048;
+static bool small_pass(const BwdArgs& a) {
+  return !rows_fit_128<MODE>(a) || bwd_grid<128>(a, MODE) < (a.f.g.d == 64 ? 576 : 512);
 }
 
 // a part begins at a multiple of 8, so that its workgroups' XCDs are those of a launch of its own
@@ -441,17 +554,13 @@ int64_t bwd_f32_shared_workgroups(const BwdArgs& a) {
 }
 
 bool bwd_f32_shares(const BwdArgs& a) {
-  return four_waves<kBwdDqExact>(a) && !f32_exact_eight(a.f) && four_waves<kBwdDqNode>(a) && (a.f.g.m == 0 || four_waves<kBwdDkvSamp>(a)) &&
+  return small_pass<kBwdDqExact>(a) && small_pass<kBwdDqNode>(a) && (a.f.g.m == 0 || small_pass<kBwdDkvSamp>(a)) &&
          bwd_f32_shared_workgroups(a) <= kMaxLaunch;
 }
 
 template <int D, bool NODES>
 static int launch_shared_form(const BwdShared& m, int64_t grid, hipStream_t st) {
-  size_t lds = F32BwdLds<D>::BYTES;
-  if (NODES) {
-    const size_t l = bwd_f32_lds_bytes<D>(m.part[1].a.f.g, kBwdDqNode);
-    lds = l > lds ? l : lds;
-  }
+  const size_t lds = F32BwdLds<D, 1, 4>::bytes(m.part[0].a.f.g, NODES ? kBwdDqNode : kBwdDqExact);
   static std::atomic<uint64_t> lds_set{0};  // per instantiation: devices on which the LDS limit is raised
   if (allow_full_lds(reinterpret_cast<const void*>(&attn_bwd_f32_shared_kernel<D, NODES>), lds_set) != HA_OK) return HA_ERR_LAUNCH;
   hipLaunchKernelGGL((attn_bwd_f32_shared_kernel<D, NODES>), dim3((unsigned)grid), dim3(256), lds, st, m);
@@ -498,18 +607,23 @@ int launch_attn_bwd_f32_level(const BwdArgs& block, const BwdArgs& dq, hipStream
   return launch_shared(m, 2, modes, true, st);
 }
 
-// Waves that share a group of 32 R rows, by the rule of the forward (launch_f32_mode): few groups or short runs
-// of rows (blocks, sample sets) take four; exact launches of few groups and long rows take eight at d = 64 (forward + backward, 6
-// causal heads, n = 2048: 204 -> 183 us; 3 heads, n = 4000: 372 -> 340; at d = 128 a wave's registers leave one per SIMD).
+// Ways of a workgroup, as in the forward (f32_ways): one where there are workgroups of 128 rows enough, else four, of 32 rows; exact
+// launches of few groups and long rows take eight at d = 64 (at d = 128 a wave's registers leave one per SIMD).  One way / four (MI355X, us; backward
+// passes, workgroups of 128 rows in brackets):
+//   d = 64: exact, causal, 32 heads, n = 1024 (256) 205 / 131, 64 (512) 225 / 240, 16 heads, n = 4096 (512) 819 / 826; unmasked, 32 heads, n = 1024 (256)
+//     207 / 220; nodes: b = m = 256, 8 heads, n = 4096 (256) 180 / 149, b = m = 128: 10 heads (320) 129 / 120, 12 (384) 132 / 133, 14 (448) 138 / 153
+//   d = 128: exact, causal, 64 heads, n = 1024 (512) 595 / 564, 128 (1024) 1102 / 1184; unmasked, 32 heads (256) 401 / 472; nodes: 8 heads, n = 2048 (128)
+//     156 / 114; b = m = 256, 8 heads, n = 4096 (256) 267 / 321; b = m = 128: 10 heads (320) 246 / 272, 18 (576) 404 / 466
+//   eight ways, d = 64, causal: one head, n = 1024 56.9 (four: 62.5), 8 heads 61.5 (66.2), 16 80.1 (76.9); 4 heads, n = 2048 103 (120)
 template <int D, int MODE>
 static int launch_bwd_f32_mode(const BwdArgs& a, hipStream_t st) {
-  const Geometry& g = a.f.g;
-  const int run = MODE == kBwdDkvSamp ? g.m : (MODE == kBwdDqNode || MODE == kBwdDkvBlock) ? g.b : a.f.exact_block;
-  const bool fits = 3 * (int64_t)((run + 127) / 128 * 128) <= 4 * (int64_t)run;
-  if constexpr (D == 64 && (MODE == kBwdDqExact || MODE == kBwdDkvExact))
-    if (f32_exact_eight(a.f)) return launch_bwd_f32_one<D, MODE, 8>(a, st);  // the forward's rule
-  if (fits && 4 * bwd_grid<128>(a, MODE) >= 2048) return launch_bwd_f32_one<D, MODE, 1>(a, st);
-  return launch_bwd_f32_one<D, MODE, 4>(a, st);
+  constexpr bool kExact = MODE == kBwdDqExact || MODE == kBwdDkvExact;
+  const int64_t grid128 = bwd_grid<128>(a, MODE);
+  if constexpr (D == 64 && kExact)
+    if (f32_exact_eight(a.f)) return launch_bwd_f32_one<D, MODE, 1, 8>(a, st);
+  const int64_t enough = kExact && a.f.exact_causal ? (D == 64 ? 512 : 1024) : D == 128 ? 208 : kExact ? 256 : 384;
+  if (rows_fit_128<MODE>(a) && grid128 >= enough) return launch_bwd_f32_one<D, MODE, 4, 1>(a, st);
+  return launch_bwd_f32_one<D, MODE, 1, 4>(a, st);
 }
 
 template <int D>

@@ -1,35 +1,32 @@
-// fp32 attention on the fp32 matrix cores: the arithmetic path for HA_FP32 tensors
-// (v_mfma_f32_32x32x2_f32: fp32 products, fp32 sums), with the same node / cap / exact
-// modes and the same outputs as the bf16 kernel (attn_mfma.hip).
+// fp32 attention: the arithmetic path for HA_FP32 tensors, with the same node / cap / exact modes and the same outputs as the
+// bf16 kernel (attn_mfma.hip).  Its products run on the bf16 matrix cores, every operand split in three (split_f32.h).
 //
-// What bounds it: the matrix pipe where the chip is full (4 heads, n = 4096 in blocks of 1024, two waves per SIMD: busy 46 %
-// of the cycles).  At d = 128, 32 to 64 bytes per lane spill (256 registers).  One 32 x 32 tile of scores and its product with V
-// take D/2 + D/2 instructions of 64 cycles each, against 8 KiB of K and 8 KiB of V
-// fragments at d = 64 that every wave reads straight from the caches into the operand
-// layout (16 B/clk per CU where four waves share nothing): no LDS staging, hence no
-// barrier in the loop and waves that run independently of each other.
+// What bounds it: in large launches the matrix pipe at the clock that the chip's power leaves it (32 heads, n = 8192, d = 64: 179 TFLOP/s, 1070
+// of bf16 products), in small ones the vector work of the splits and the chain of one wave's tiles (4 heads, n = 4096 in causal blocks of
+// 1024, 512 workgroups: matrix pipe 15 %, vector issue 41 % of the cycles).
 //
 // A wave owns 32 query rows and computes S^T = K Q^T, so that a lane holds 16 keys of
-// ONE query (as in the bf16 kernel) and an accumulator register, exponentiated, is
-// directly the B operand of O^T += V^T P^T: the two lanes of a query hold the keys
-// 8 g + z and 8 g + 4 + z of the instruction's pair.  The columns of d are walked in
-// the order the lanes load them (lane half h: columns 8 j + 4 h ... + 3), which the
-// K and the Q fragments share.
+// ONE query (as in the bf16 kernel) and accumulator registers, exponentiated and split, are
+// directly the B operand of O^T += V^T P^T: the eight of a step hold the lane's keys
+// 8 g + 4 h + z, g = 0, 1, in the order that V's operand has them too.
 //
-// KW waves of a workgroup share one group of 32 queries, every wave taking each KW-th
-// key tile, and their results are merged through LDS.  KW = 4 quarters the serial
-// chain of a small problem (the one-head n = 1024 call has 32 groups of queries for
-// 1024 SIMDs) and lets a workgroup fit blocks of 32 rows.
+// A workgroup has KW ways, every way taking each KW-th key tile, and their results are merged through LDS; the other waves of a way hold
+// further queries and share its tiles.  KW = 1 or 2 (KW = 2 at d = 64): a tile of K and V is split once, by all threads of its way, into LDS (a
+// wave's splits are otherwise a third to a half of its vector work), and read from there, V through the transposing read.  KW = 4 or 8:
+// small problems, one group of 32 queries per workgroup (the one-head n = 1024 call has 32 groups of queries for 1024 SIMDs), where no
+// two waves share a tile: K and V come straight from the caches in operand layout and are split in registers, no barrier
+// in the loop, and the queries lie split in LDS.
 //
-// Measured (MI355X; fp32 matrix peak 157 TFLOP/s, library product of 8192^3: 154), against
-// one thread per query row with LDS-broadcast keys, the form before: exact attention,
-// 32 heads, n = 8192: d = 64 14.8 -> 4.8 ms (114 TFLOP/s), d = 128 95 -> 8.9 ms (124);
-// n = 1024, one head, d = 64, b = m = 64: whole forward call 124 -> 35 us.  Then the vector work beside the products:
-// the wave's number is a scalar (with a per-lane key loop the compiler wrapped every buffer load in a loop over
-// possible descriptors), exponentials in seven instructions, fewer rescales: 32 heads, n = 1024, d = 64, unmasked:
-// 111 -> 79 us; 4 heads, n = 4096 in causal blocks of 1024: 50 -> 39 us.  Errors against 64 bits as before.
+// Measured (MI355X, us; fp32 matrix instructions, K and V always from the caches -> this form): exact attention, 32 heads, n = 8192:
+// d = 64 4270 -> 3070; 16 heads, d = 128 4240 -> 3550; causal, 16 heads, n = 1024 d = 64 33.1 -> 26.4, d = 128 58.6 -> 44.8; 8 heads, n = 4096
+// 164 -> 136, 346 -> 255; one head, n = 1024 23.8 -> 18.3, 43.1 -> 32.7; whole calls: one head, n = 1024, d = 64, b = m = 64 17.8 -> 17.0, 8 heads, n = 4096,
+// b = m = 256 64.4 -> 54.6, d = 128 112 -> 92; 16 causal heads, n = 4096 in blocks of 1024, b = m = 128 192 -> 148, 352 -> 298.  What keeps an
+// infinite operand infinite (split8) is 3 % of these.
+// Tried: the next step's split in slices between the products, by the compiler's issue-order hints (+-1 %: the other waves fill the gaps);
+// KW = 2 at d = 128 (one wave per SIMD: 16 heads, n = 2048, causal 138 -> 187).
 #include "attn_common.h"
 #include "node_sort.h"
+#include "split_f32.h"
 
 namespace ha {
 
@@ -46,21 +43,39 @@ struct F32Lds {
   static constexpr int BYTES = NW * 32 * ROW * 4 + NW * 32 * 2 * 4;
 };
 
-template <int D>
-__host__ __device__ inline size_t f32_lds_bytes(int b, int m, int mode) {
-  const size_t list = mode != kModeExact ? (size_t)(((b + m + 63) & ~63) + 64) * 4 + 64 : 0;
-  // behind the list: the rows drawn by value norm with their weights, the waves' masked sums; two more values per staged row
+// What the loop keeps in front of the tiles: the key list, and behind it the rows drawn by value norm with their weights and the waves'
+// masked sums.
+__host__ __device__ inline size_t f32_list_bytes(int b, int m, int mode) {
+  if (mode == kModeExact) return 0;
+  const size_t list = (size_t)(((b + m + 63) & ~63) + 64) * 4 + 64;
   const size_t cap = mode == kModeCap || mode == kModeValue ? 4 * 32 * 2 * 4 : 0;
   const size_t drawn = mode == kModeValue ? 2 * (size_t)((m + 63) & ~63) * 4 : 0;
-  return list + drawn + cap > (size_t)F32Lds<D>::BYTES + cap ? list + drawn + cap : (size_t)F32Lds<D>::BYTES + cap;
+  return (list + drawn + cap + 15) & ~(size_t)15;
 }
 
-// SORT: the sort's tables lie behind the list, the tile's query rows behind all else
-template <int D>
+// K and V tiles of every way, or, where the waves of a workgroup share one group of queries, its rows
+template <int D, int KW>
+__host__ __device__ constexpr size_t f32_tile_bytes() {
+  return (size_t)SplitTile<D>::BYTES * (KW < 4 ? 2 * KW : 1);
+}
+
+template <int D, int KW>
+__host__ __device__ inline size_t f32_lds_bytes(int b, int m, int mode) {
+  constexpr int NW = f32_waves(KW);
+  const size_t loop = f32_list_bytes(b, m, mode) + f32_tile_bytes<D, KW>();
+  // staged rows: two more values each in cap mode
+  const size_t rows = (size_t)F32Lds<D, NW>::BYTES + (mode == kModeCap || mode == kModeValue ? NW * 32 * 2 * 4 : 0);
+  return loop > rows ? loop : rows;
+}
+
+// SORT: the sort's tables lie behind the list, where the tiles come later, the tile's query rows behind all else
+__host__ __device__ inline size_t f32_sort_end(const Geometry& g) {
+  return f32_list_bytes(g.b, g.m, kModeNode) + ((node_sort_lds_bytes<4>(g) + 15) & ~(size_t)15);
+}
+template <int D, int KW>
 __host__ __device__ inline size_t f32_qrows_at(const Geometry& g) {
-  const size_t list = ((size_t)(((g.b + g.m + 63) & ~63) + 64) * 4 + 64 + 15) & ~(size_t)15;
-  const size_t both = list + ((node_sort_lds_bytes<4>(g) + 15) & ~(size_t)15);
-  return both > (size_t)F32Lds<D>::BYTES ? both : (size_t)F32Lds<D>::BYTES;
+  const size_t sort = f32_sort_end(g), rest = f32_lds_bytes<D, KW>(g.b, g.m, kModeNode);
+  return sort > rest ? sort : rest;
 }
 
 // m + ln l to one rounding of the result: l = f 2^k with f in [1/2, 1), m + k ln 2 kept in two parts.  The reference m only
@@ -79,18 +94,22 @@ __device__ inline float add_log(float m, float l) {
 // FAR (node mode): a head's rows pass the reach of a buffer load's 32-bit offset, so they are addressed in 64 bits.
 // SORT (node mode): the workgroup finds its rows from the node's bucket codes (node_sort.h).
 template <int D, int MODE, int KW, bool FAR, bool SORT>
-__global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void attn_f32_kernel(AttnArgs a) {
+__global__ __launch_bounds__(64 * f32_waves(KW), D == 128 && KW < 4 ? 1 : 2) void attn_f32_kernel(AttnArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   constexpr int NW = f32_waves(KW), kFNT = 64 * NW;
-  constexpr int kQT = 32 * (NW / KW);
+  constexpr int RG = NW / KW;  // waves that share the tiles of a way
+  constexpr bool kShared = RG > 1;
+  constexpr int kQT = 32 * RG;
+  using T = SplitTile<D>;
   constexpr bool kValue = MODE == kModeValue, kCap = MODE == kModeCap || kValue, kNode = MODE == kModeNode || kCap;
   constexpr int KJ = D / 8;    // 16-byte pieces of a row per lane
+  constexpr int KS = D / 16;   // steps of a score's product
   constexpr int DT = D / 32;
   constexpr int DTA = DT < 2 ? DT : 2;  // V columns are fetched 64 at a time
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // a scalar: so are the key loop and the descriptors
   const int lq = lane & 31, h = lane >> 5;
-  const int kw = wave % KW;
+  const int grp = wave % RG, kw = wave / RG;
 
   int32_t* scratch = reinterpret_cast<int32_t*>(smem);
   int32_t* list = scratch + 16;
@@ -98,11 +117,12 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
   const int bid = a.wg_first + (kNode ? logical_block(blockIdx.x, gridDim.x) : (int)blockIdx.x);
   TileWork w;
   int nb, nkeys;
-  int32_t* qrows = reinterpret_cast<int32_t*>(smem + (SORT ? f32_qrows_at<D>(a.g) : 0));
+  int32_t* qrows = reinterpret_cast<int32_t*>(smem + (SORT ? f32_qrows_at<D, KW>(a.g) : 0));
+  unsigned char* tiles_at = smem + f32_list_bytes(a.g.b, a.g.m, MODE);
   if constexpr (SORT) {
     w = decode_node_tile<kQT>(a, bid);
     const int l0 = first_node_sample(a, w);
-    unsigned char* sort_lds = reinterpret_cast<unsigned char*>(list) + (((((a.g.b + a.g.m + 63) & ~63) + 64) * 4 + 15) & ~15);
+    unsigned char* sort_lds = smem + f32_list_bytes(a.g.b, a.g.m, MODE);
     sort_node_tile<4>(a, w, sort_lds, list, qrows);
     nb = a.g.b;
     nkeys = append_node_samples<4>(a, w, sort_lds, list, scratch, l0);
@@ -117,7 +137,8 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
   int ntiles = (nkeys + kFKT - 1) / kFKT;
   // causal: a wave ends with the tile that holds its own last row.  Tiles wholly behind its rows are not only idle work:
   // weight 0 times a V that is Inf or NaN is NaN.
-  if (MODE == kModeExact && a.exact_causal) ntiles = min(ntiles, (w.q0 - w.k0) / kFKT + wave / KW + 1);
+  int wg_tiles = ntiles;  // of the workgroup
+  if (MODE == kModeExact && a.exact_causal) ntiles = min(ntiles, (w.q0 - w.k0) / kFKT + grp + 1);
   // value mode: the rows drawn by value norm, all m of them for every block, follow in tiles of their own
   const int vt0 = ntiles, drawn_at = (((a.g.b + a.g.m + 63) & ~63) + 64) + ((a.g.m + 63) & ~63);
   float* drawn_w = reinterpret_cast<float*>(list + drawn_at);  // -log(m p); -inf past the end
@@ -128,6 +149,7 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
       drawn_w[j] = j < a.g.m ? a.vlogw[draws + j] : -INFINITY;
     }
     ntiles += (a.g.m + 31) / kFKT;
+    wg_tiles = ntiles;
     __syncthreads();
   }
   const float nat_bias = (kNode && a.g.m > 0) ? logf((float)w.nr.s / (float)a.g.m) : 0.f;
@@ -135,7 +157,7 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
   const float* Qh = reinterpret_cast<const float*>(a.Q) + (int64_t)w.bh * a.q_bh_stride;
   const float* Kh = reinterpret_cast<const float*>(a.K) + (int64_t)w.bh * a.k_bh_stride;
   const float* Vh = reinterpret_cast<const float*>(a.V) + (int64_t)w.bh * a.k_bh_stride;
-  const int r_in_tile = (wave / KW) * 32 + lq;
+  const int r_in_tile = grp * 32 + lq;
   const int r_use = r_in_tile < w.rows_valid ? r_in_tile : 0;
   int qrow, q_global = 0;
   if constexpr (SORT) {
@@ -146,30 +168,46 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
     q_global = w.q0 + r_in_tile;
     qrow = w.q0 + r_use;
   }
-  f32x4 q[KJ];
+  // Columns 16 s + 8 h ... + 7 are the lane's eight of step s, of Q and of K.  Where a workgroup's waves share the queries, these lie
+  // split in LDS.
+  Split8 q[kShared ? KS : 1];
+  if constexpr (kShared) {
+    f32x4 qf[KJ];
 #pragma unroll
-  for (int j = 0; j < KJ; ++j) q[j] = *reinterpret_cast<const f32x4*>(Qh + (int64_t)qrow * D + 8 * j + 4 * h);
+    for (int j = 0; j < KJ; ++j) qf[j] = *reinterpret_cast<const f32x4*>(Qh + (int64_t)qrow * D + 16 * (j / 2) + 8 * h + 4 * (j % 2));
+#pragma unroll
+    for (int s = 0; s < KS; ++s) q[s] = split8<true>([&](int e) { return qf[2 * s + e / 4][e % 4]; });
+  } else {
+    for (int i = tid; i < 32 * T::PPR; i += kFNT) {
+      const int r = i / T::PPR, piece = i % T::PPR, ru = r < w.rows_valid ? r : 0;
+      const int row = SORT ? qrows[ru] : kNode && a.perm_q ? a.perm_q[w.seg_off + w.p0 + ru] : kNode ? w.nr.q_start + w.p0 + ru : w.q0 + ru;
+      const f32x4* at = reinterpret_cast<const f32x4*>(Qh + (int64_t)row * D + piece * 8);
+      T::store(tiles_at, r, piece, at[0], at[1]);
+    }
+  }
 
   // rows past the end of the keys read as zeros (such keys are masked by position)
   const uint32_t bytes = (uint32_t)(kNode ? a.g.n : w.k1) * (uint32_t)(D * 4);
   const __amdgpu_buffer_rsrc_t krsrc = __builtin_amdgcn_make_buffer_rsrc((void*)Kh, 0, (int)bytes, 0x00020000);
   const __amdgpu_buffer_rsrc_t vrsrc = __builtin_amdgcn_make_buffer_rsrc((void*)Vh, 0, (int)bytes, 0x00020000);
-  f32x4 kf[KJ];
+  f32x4 kf[kShared ? 1 : KJ];
   auto load_k = [&](int kt) {
+    if constexpr (kShared) return;
     const int row = kNode ? list[kt * kFKT + lq] : w.k0 + kt * kFKT + lq;
     if constexpr (FAR) {  // (every row of the list exists)
 #pragma unroll
-      for (int j = 0; j < KJ; ++j) kf[j] = *reinterpret_cast<const f32x4*>(Kh + (int64_t)row * D + 8 * j + 4 * h);
+      for (int j = 0; j < KJ; ++j) kf[kShared ? 0 : j] = *reinterpret_cast<const f32x4*>(Kh + (int64_t)row * D + 16 * (j / 2) + 8 * h + 4 * (j % 2));
       return;
     }
-    const int off = row * (D * 4) + 16 * h;
+    const int off = row * (D * 4) + 32 * h;
 #pragma unroll
     for (int j = 0; j < KJ; ++j)
-      kf[j] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(krsrc, off, 32 * j, 0));
+      kf[kShared ? 0 : j] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(krsrc, off + 16 * (j % 2), 64 * (j / 2), 0));
   };
   // V rows of the tile, columns 32 dt + lq for dt in [dt0, dt0 + DTA): element i of a lane is key
   // 8 (i / 4) + 4 h + i % 4, the key of accumulator register i
-  auto load_v = [&](int kt, int dt0, float (&v)[16][DTA]) {
+  auto load_v = [&](int kt, int dt0, float (&v)[kShared ? 1 : 16][DTA]) {
+    if constexpr (kShared) return;
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
       i32x4 rows;
@@ -183,11 +221,40 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
       for (int z = 0; z < 4; ++z)
 #pragma unroll
         for (int dt = 0; dt < DTA; ++dt)
-          v[4 * g + z][dt] = FAR ? Vh[(int64_t)rows[z] * D + 32 * (dt0 + dt) + lq]
+          v[kShared ? 0 : 4 * g + z][dt] = FAR ? Vh[(int64_t)rows[z] * D + 32 * (dt0 + dt) + lq]
                                  : __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(vrsrc, rows[z] * (D * 4) + 4 * lq,
                                                                                        128 * (dt0 + dt), 0));
     }
   };
+
+  // Shared tiles: a thread fetches pieces of eight floats, splits them and puts them into its way's tiles.
+  constexpr int NP = kShared ? kFKT * T::PPR / (64 * RG) : 1;  // pieces per thread and tensor
+  const int wtid = tid % (64 * RG);
+  unsigned char* ktile = tiles_at + (kShared ? kw * 2 * T::BYTES : 0);
+  unsigned char* vtile = ktile + T::BYTES;
+  f32x4 ks[NP][2], vs[NP][2];
+  auto fetch = [&](int kt) {
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      const int r = (wtid + i * 64 * RG) / T::PPR, piece = (wtid + i * 64 * RG) % T::PPR;
+      const int off = (kNode ? list[kt * kFKT + r] : w.k0 + kt * kFKT + r) * (D * 4) + piece * 32;
+      ks[i][0] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(krsrc, off, 0, 0));
+      ks[i][1] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(krsrc, off + 16, 0, 0));
+      if (kValue && kt < vt0) continue;
+      vs[i][0] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(vrsrc, off, 0, 0));
+      vs[i][1] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(vrsrc, off + 16, 0, 0));
+    }
+  };
+  auto store = [&](int kt) {
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      const int r = (wtid + i * 64 * RG) / T::PPR, piece = (wtid + i * 64 * RG) % T::PPR;
+      T::store(ktile, r, piece, ks[i][0], ks[i][1]);
+      if (kValue && kt < vt0) continue;
+      T::store(vtile, r, piece, vs[i][0], vs[i][1]);
+    }
+  };
+  const int row_at = T::row_at(lane), col_at = T::col_at(lane);
 
   f32x16 o[DT];
 #pragma unroll
@@ -229,10 +296,10 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
     __syncthreads();
     float top = -INFINITY, sum = 0.f;
 #pragma unroll
-    for (int k = 0; k < KW; ++k) top = fmaxf(top, ex[((wave / KW * KW + k) * 32 + lq) * 2]);
+    for (int k = 0; k < KW; ++k) top = fmaxf(top, ex[((k * RG + grp) * 32 + lq) * 2]);
 #pragma unroll
     for (int k = 0; k < KW; ++k) {
-      const float* e = ex + ((wave / KW * KW + k) * 32 + lq) * 2;
+      const float* e = ex + ((k * RG + grp) * 32 + lq) * 2;
       sum += e[1] * (top == -INFINITY ? 0.f : expf(e[0] - top));
     }
     log_masked = sum > 0.f ? add_log(top, sum) : -INFINITY;
@@ -244,22 +311,42 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
     if (kValue) m_run = -INFINITY;
     sampled = true;
   };
-  if (kw < ntiles) load_k(kw);
-  for (int kt = kw; kt < ntiles; kt += KW) {
-    float va[16][DTA];
-    if constexpr (DT == 2 && !kValue) load_v(kt, 0, va);
-    f32x16 c;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) c[i] = 0.f;
-#pragma unroll
-    for (int j = 0; j < KJ; ++j) {
-      if (DT > 2 && !kValue && j == KJ / 2) {  // d = 128: V takes the registers of the K pieces already multiplied
-        __builtin_amdgcn_sched_barrier(0);
-        load_v(kt, 0, va);
-      }
-#pragma unroll
-      for (int e = 0; e < 4; ++e) c = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[j][e], q[j][e], c, 0, 0, 0);
+  if constexpr (kShared) {
+    if (kw < wg_tiles) fetch(kw);
+  } else {
+    __syncthreads();  // the queries stand
+    if (kw < ntiles) load_k(kw);
+  }
+  // (shared tiles: the same trips for all ways, the barriers are the workgroup's)
+  const int kt_end = kShared ? (wg_tiles + KW - 1) / KW * KW : ntiles;
+  for (int kt = kw; kt < kt_end; kt += KW) {
+    if constexpr (kShared) {
+      if (kt >= KW) __syncthreads();  // the tiles before are read no more
+      if (kt < wg_tiles) store(kt);
+      __syncthreads();
+      if (kt + KW < wg_tiles) fetch(kt + KW);
+      if (kt >= ntiles) continue;
     }
+    float va[kShared ? 1 : 16][DTA];
+    if constexpr (!kShared && DT == 2 && !kValue) load_v(kt, 0, va);
+    f32x16 c, small;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) c[i] = small[i] = 0.f;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      if constexpr (kShared) {
+        split_product(T::row_frag(ktile, row_at, s), q[s], c, small);
+      } else {
+        if constexpr (DT > 2 && !kValue) {
+          if (s == KS / 2) {  // d = 128: V takes the registers of the K pieces already multiplied
+            __builtin_amdgcn_sched_barrier(0);
+            load_v(kt, 0, va);
+          }
+        }
+        split_product(split8<true>([&](int e) { return kf[2 * s + e / 4][e % 4]; }), T::row_frag(tiles_at, row_at, s), c, small);
+      }
+    }
+    split_sum(c, small);
 
     const int base = kt * kFKT;
     if constexpr (kCap) {
@@ -287,7 +374,7 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
       }
     }
     const bool plain = kCap || base + kFKT <= min(nkeys, nb) &&
-                       !(MODE == kModeExact && a.exact_causal && w.k0 + base + kFKT - 1 > w.q0 + (wave / KW) * 32);
+                       !(MODE == kModeExact && a.exact_causal && w.k0 + base + kFKT - 1 > w.q0 + grp * 32);
     if (!plain) {
       int lim = nkeys;
       if (MODE == kModeExact && a.exact_causal) lim = min(lim, q_global - w.k0 + 1);
@@ -324,43 +411,49 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
         capw = 0.f;
       }
     }
+    float ls[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       c[i] = exp_split(c[i] - m_use);
-      if (!kValue || kt < vt0) l_run += kCap ? fminf(c[i], capw) : c[i];
+      ls[i % 4] += kCap ? fminf(c[i], capw) : c[i];
     }
+    if (!kValue || kt < vt0) l_run += (ls[0] + ls[1]) + (ls[2] + ls[3]);
     if constexpr (DT == 2) {
       if (kt + KW < ntiles) load_k(kt + KW);
     }
-    float vb[16][DTA];
+    float vb[kShared ? 1 : 16][DTA];
+    Split8 p[2];  // the weights: elements 8 s ... 8 s + 7 are the lane's keys of step s
+#pragma unroll
+    for (int s = 0; s < 2; ++s) p[s] = split8<false>([&](int e) { return c[8 * s + e]; });
+    auto add_pv = [&](const float (&v)[kShared ? 1 : 16][DTA], int dt0) {
+      if constexpr (!kShared) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+          for (int dt = 0; dt < DTA; ++dt) split_product(split8<true>([&](int e) { return v[8 * s + e][dt]; }), p[s], o[dt0 + dt]);
+      }
+    };
+    if constexpr (kShared) {
+      if (!kValue || kt >= vt0) split_tile_products<DT>([&](int dt, int s) { return T::col_frag(vtile, col_at, s, dt); }, p, o);
+      continue;
+    }
     if constexpr (kValue) {  // V behind the sums, 64 columns at a time (fetched amid the products, under a branch: 168 spills at d = 128)
       if (DT > 2 && kt + KW < ntiles) load_k(kt + KW);
       if (kt < vt0) continue;
 #pragma unroll
       for (int dt0 = 0; dt0 < DT; dt0 += 2) {
         load_v(kt, dt0, va);
-#pragma unroll
-        for (int i = 0; i < 16; ++i)
-#pragma unroll
-          for (int dt = 0; dt < DTA; ++dt)
-            o[dt0 + dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(va[i][dt], c[i], o[dt0 + dt], 0, 0, 0);
+        add_pv(va, dt0);
         __builtin_amdgcn_sched_barrier(0);
       }
       continue;
     }
     if constexpr (DT > 2) load_v(kt, 2, vb);
-#pragma unroll
-    for (int i = 0; i < 16; ++i)
-#pragma unroll
-      for (int dt = 0; dt < DTA; ++dt) o[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(va[i][dt], c[i], o[dt], 0, 0, 0);
+    add_pv(va, 0);
     if constexpr (DT > 2) {
       __builtin_amdgcn_sched_barrier(0);  // the next K rows take the registers of the first half of V
       if (kt + KW < ntiles) load_k(kt + KW);
-#pragma unroll
-      for (int i = 0; i < 16; ++i)
-#pragma unroll
-        for (int dt = 0; dt < DTA; ++dt)
-          o[2 + dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(vb[i][dt], c[i], o[2 + dt], 0, 0, 0);
+      add_pv(vb, 2);
     }
   }
   if constexpr (kCap) {
@@ -395,18 +488,17 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
   const bool to_partial = kNode && a.part_o != nullptr;
   for (int idx = tid; idx < w.rows_valid * LPR; idx += kFNT) {
     const int r = idx / LPR, col = (idx % LPR) * 4;
-    const int w0 = (r / 32) * KW;  // first of the waves that hold the row
     float mx = -INFINITY, dmx = -INFINITY;
 #pragma unroll
     for (int k = 0; k < KW; ++k) {
-      mx = fmaxf(mx, ml[((w0 + k) * 32 + (r & 31)) * ML]);
-      if (kCap) dmx = fmaxf(dmx, ml[((w0 + k) * 32 + (r & 31)) * ML + 2]);
+      mx = fmaxf(mx, ml[(k * kQT + r) * ML]);
+      if (kCap) dmx = fmaxf(dmx, ml[(k * kQT + r) * ML + 2]);
     }
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     float l = 0.f;
 #pragma unroll
     for (int k = 0; k < KW; ++k) {
-      const int at = (w0 + k) * 32 + (r & 31);
+      const int at = k * kQT + r;
       const float wk = KW == 1 ? 1.f : (mx == -INFINITY ? 0.f : expf(ml[at * ML] - mx));
       l += (kCap && KW > 1 ? expf(ml[at * ML + 2] - finite_ref(dmx)) : wk) * ml[at * ML + 1];
       acc += wk * *reinterpret_cast<const f32x4*>(orow + at * RS + col);
@@ -415,7 +507,7 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
     float lse = empty ? -INFINITY : add_log(kCap ? dmx : mx, l);
     float ref = lse;  // of a partial row
     if constexpr (kCap) {  // d~_i = masked + max(d_i, tau / kappa)
-      lse = logaddexpf(ml[(w0 * 32 + (r & 31)) * ML + 3], fmaxf(lse, floor_term));
+      lse = logaddexpf(ml[r * ML + 3], fmaxf(lse, floor_term));
       ref = to_partial && a.part_ref != nullptr && lse != -INFINITY ? fmaxf(lse, mx) : lse;
       acc *= (mx == -INFINITY || lse == -INFINITY) ? 0.f : expf(mx - ref);
     } else {
@@ -458,7 +550,7 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 64 && KW < 8 ? 3 : 2) void
 
 template <int D, int MODE, int KW, bool FAR = false, bool SORT = false>
 static int launch_f32_one(const AttnArgs& args, hipStream_t st) {
-  constexpr int NW = f32_waves(KW), kQT = 32 * (NW / KW);
+  constexpr int kQT = 32 * (f32_waves(KW) / KW), NT = 64 * f32_waves(KW);
   AttnArgs a = args;
   if (MODE != kModeExact) set_node_divs<kQT>(a);
   else set_exact_divs<kQT>(a);
@@ -466,64 +558,66 @@ static int launch_f32_one(const AttnArgs& args, hipStream_t st) {
   const int64_t grid = MODE != kModeExact ? node_grid<kQT>(a.g) : exact_grid<kQT>(a);
   if (grid <= 0) return HA_OK;
   if (grid > kMaxGrid) return HA_ERR_SHAPE;
-  const size_t lds = KW == 8 ? (size_t)F32Lds<D, NW>::BYTES : SORT ? f32_qrows_at<D>(a.g) + kQT * 4 : f32_lds_bytes<D>(a.g.b, a.g.m, MODE);
+  const size_t lds = SORT ? f32_qrows_at<D, KW>(a.g) + kQT * 4 : f32_lds_bytes<D, KW>(a.g.b, a.g.m, MODE);
   static std::atomic<uint64_t> lds_set{0};  // per instantiation: devices on which the LDS limit is raised
   if (allow_full_lds(reinterpret_cast<const void*>(&attn_f32_kernel<D, MODE, KW, FAR, SORT>), lds_set) != HA_OK) return HA_ERR_LAUNCH;
   for (int64_t first = 0; first < grid; first += kMaxLaunch) {
     a.wg_first = (int32_t)first;
     const int64_t count = grid - first < kMaxLaunch ? grid - first : kMaxLaunch;
-    hipLaunchKernelGGL((attn_f32_kernel<D, MODE, KW, FAR, SORT>), dim3((unsigned)count), dim3(64 * NW), lds, st, a);
+    hipLaunchKernelGGL((attn_f32_kernel<D, MODE, KW, FAR, SORT>), dim3((unsigned)count), dim3(NT), lds, st, a);
     const int rc = check_launch();
     if (rc != HA_OK) return rc;
   }
   return HA_OK;
 }
 
-// Waves that share a group of 32 queries: as few as leave the chip's 1024 SIMDs two waves each, but
-// enough that a workgroup's 128 / KW rows do not outgrow the run of rows it is cut from (a block of b
-// sorted positions, an exact diagonal block) by more than a third: idle rows cost matrix time like real
-// ones, while the merge of KW results costs a few LDS reads per row.
-static int f32_waves_per_group(int run, int64_t grid128) {
-  auto padded = [&](int qt) { return (int64_t)((run + qt - 1) / qt) * qt; };
-  const int64_t waves = 4 * grid128;
-  if (waves >= 2048 && 3 * padded(128) <= 4 * (int64_t)run) return 1;
-  return waves >= 1024 && 3 * padded(64) <= 4 * (int64_t)run ? 2 : 4;
+// Ways of a workgroup of four waves: one where there are workgroups of 128 rows enough for it, four (of 32 rows) where there are not, two in
+// between at d = 64 (at d = 128 its two tiles and registers leave one wave per SIMD); but not so few that a workgroup's 128 / KW rows
+// outgrow the run of rows it is cut from (a block of b sorted positions, an exact diagonal block) by more than a third: idle rows
+// cost matrix time like real ones, while the merge of KW results costs a few LDS reads per row.  Causal tiles differ in length, so workgroups of
+// 128 rows pay only where a CU gets several; at d = 128 a CU holds one of them, and a last round that is not nearly full loses what they gain.
+// One way / two / four (MI355X, us; workgroups of 128 rows in brackets):
+//   d = 64, causal: 32 heads, n = 1024 (256) 66.4 / 44.5 / 41.5, 64 (512) 74.7 / 72.6 / 75.1, 128 (1024) 120 / 139 / 154; 16 heads, n = 4096 (512) 270 / 241 /
+//     254; unmasked: 32 heads, n = 1024 (256) 72 / 65 / 69; 16 heads, n = 4000 (500) 415 / 442 / 467; nodes: b = m = 256, 8 heads, n = 4096 (256) 54.2 / 51.6 /
+//     56.1, 16 (512) 86.8 / 98.9 / 102.2; b = m = 128, 12 heads, n = 4096 (384) 52.1 / 54.9 / 59.0; b = m = 64, 16 heads, n = 4096 58.3 / 54.2 / 57.2
+//   d = 128 (one / four): causal, 64 heads, n = 1024 (512) 158 / 146, 128 (1024) 278 / 296; unmasked, 32 heads (256) 119 / 130; nodes: b = m = 256, 8
+//     heads, n = 4096 (256) 87.4 / 97.9; b = m = 128, 12 heads, n = 4096 (384) 106 / 100, 32 heads, n = 2048 (512) 116 / 126, 44 (704) 163 / 167, 52 (832)
+//     205 / 194; 24 heads, n = 2000, b = 100 (480) 92 / 113
+static bool f32_fits(int run, int rows) { return 3 * (int64_t)((run + rows - 1) / rows * rows) <= 4 * (int64_t)run; }
+static int f32_ways(int d, int run, int64_t grid128, bool causal) {
+  const int64_t rounds = (grid128 + 255) / 256;
+  const bool full = d == 64 || 100 * grid128 >= 92 * 256 * rounds;  // (d = 128: one workgroup of 128 rows to a CU)
+  if (f32_fits(run, 128) && full && grid128 >= (causal ? 1024 : d == 64 ? 384 : 236)) return 1;
+  return d == 64 && f32_fits(run, 64) && grid128 >= (causal ? 512 : 256) ? 2 : 4;
 }
 
-int64_t attn_f32_node_grid(const Geometry& g) {
-  const int kw = f32_waves_per_group(g.b, node_grid<128>(g));
-  return kw == 1 ? node_grid<128>(g) : kw == 2 ? node_grid<64>(g) : node_grid<32>(g);
-}
+static int f32_node_ways(const Geometry& g) { return f32_ways(g.d, g.b, node_grid<128>(g), false); }
 
-// Whether a node launch sorts by itself (attn_mfma_sorts, for the kernel without it).  d = 64: up to 1024 workgroups.  d = 128 has 512
-// places, two to a CU; past them, from some 580 to 768 workgroups, calls whose workgroups sort take up to a fifth longer (they start and
-// end together, and the second round seems to fall on the CUs unevenly: its places were not recorded).  Sorting launch -> in the attention (MI355X, us; workgroups, of
-// 128 rows, of 64, of 32):
-//   d = 64, b = m = 64: one head, n = 1024 (32) 21.2 -> 17.2; 24 heads, n = 2048 (768) 51.4 -> 46.8; 16 heads, n = 4096 (1024) 66.7 -> 62.7,
-//     32 (2048) 106.1 -> 108.1; 64 heads, n = 1024 (1024) 65.3 -> 61.8; 6 heads, n = 4100, b = 82 (900) 48.6 -> 49.1
-//   d = 128, 128 rows: 32 heads, n = 2048, b = m = 128 (512) 134.0 -> 128.3, 36 (576) 179.9 -> 173.6, 44 (704) 189.2 -> 183.7, 48 (768) 196.7 ->
-//     223.8, 52 (832) 238.0 -> 231.8, 64 (1024) 254.4 -> 247.4; b = m = 256: 40 (640) 287.9 -> 280.0, 48 (768) 334.2 -> 348.1; n = 512, b = 128, m =
-//     32: 180 heads (720) 152.7 -> 158.2; n = 1000, b = 100, m = 64: 56 heads (560) 133.7 -> 129.8, 61 (610) 137.4 -> 151.0, 90 (900) 180.4 -> 175.3
-//   64 rows: 16 heads, n = 2048, b = m = 64 (512) 60.6 -> 59.1, 18 (576) 79.9 -> 78.7, 20 (640) 81.1 -> 80.2, 23 (736) 85.0 -> 87.8, 24 (768) 86.0 ->
-//     97.2, 32 (1024) 109.3 -> 110.2; b = m = 256: 18 (576) 156.8 -> 156.0, 20 (640) 167.7 -> 183.5; n = 6144, b = 64: 4 heads (384) 59.0 -> 58.8,
-//     n = 8192: 2 heads (256) 42.2 -> 38.3, 3 (384) 58.9 -> 60.4; b = 128: 4 heads (512) 80.5 -> 85.2
-//   32 rows, of long blocks: 4 heads, n = 4096, b = m = 256 (512) 70.1 -> 67.0, 6 (768) 99.0 -> 108.2; 8 heads, n = 2100, b = 100 (672) 67.9 -> 68.2;
-//     2 heads, n = 8192, b = 256 (512) 70.8 -> 75.1; of blocks that 64 rows do not fill: 24 heads, n = 1024, b = 32 (768) 57.0 -> 55.0, 32
-//     (1024) 63.9 -> 62.8; 8 heads, n = 4096, b = 32 (1024) 65.1 -> 64.7
-// Where the sort's tables cost a CU one of its workgroups, calls that need it lose more the longer the attention is: d = 64, b = m = 64: 7 heads,
-// n = 6144 (672) 52.7 -> 51.9, m = 256 74.1 -> 73.5; b = m = 256, 11 heads (528) 152.9 -> 154.4; b = 64, m = 1000: 6 heads (576) 152.9 -> 160.0; r = 8: 9
-// heads, n = 4096 (576) 152.0 -> 157.7; b = 128, m = 2000, 8 heads, n = 8192 (512, one to a CU) 352 -> 396; d = 128, the same 643 -> 723.
+// Whether a node launch sorts by itself (attn_mfma_sorts, for the kernel without it): up to 1024 workgroups (of 128 rows where there are 512 of
+// those, of 64 from 256 of 128 rows on, else of 32: the forms of the kernel whose limits these are; its ways are now f32_ways'); at d = 128 fewer, since
+// a workgroup that sorts counts its whole node.  Sorting launch -> in the attention (MI355X, us):
+//   d = 64, b = m = 64: one head, n = 1024 19.7 -> 16.4; 8 heads, n = 2048 25.3 -> 21.7, 16 34.7 -> 30.4, 18 44.5 -> 42.7, 24 46.9 -> 44.5; 16
+//     heads, n = 4096 56.3 -> 54.2; 2 heads, n = 8192 26.2 -> 23.3; b = m = 128: 8 heads, n = 2048 27.9 -> 25.4, 32 62.0 -> 57.4, 52 97.4 -> 92.5;
+//     b = m = 256: 4 heads, n = 4096 37.6 -> 34.6, 8 55.6 -> 51.6; 24 heads, n = 2000, b = 100, m = 77 51.4 -> 46.5; 8 heads, n = 4096, b = 32 35.8 -> 34.1
+//   d = 128, b = m = 64: one head, n = 1024 23.5 -> 19.7; 8 heads, n = 2048 37.4 -> 33.1, 18 66.9 -> 66.1, 24 77.5 -> 77.7; 16 heads, n = 4096 98.7 ->
+//     101.5; b = m = 128: 8 heads, n = 2048 43.1 -> 39.1, 32 121.2 -> 115.8, 44 160.9 -> 162.7; 12 heads, n = 4096 99.5 -> 100.1; b = m = 256: 4 heads,
+//     n = 4096 62.0 -> 57.1, 8 95.3 -> 87.4; 24 heads, n = 2000, b = 100, m = 77 96.4 -> 92.3; 8 heads, n = 4096, b = 32 56.0 -> 54.3
+// Not where the sort's tables cost a CU one of its workgroups and the call needs it: it then loses more the longer the attention is.  (Measured
+// on the form with fp32 products: d = 64, b = 64, m = 1000: 6 heads, n = 6144 (576 workgroups) 152.9 -> 160.0; r = 8: 9 heads, n = 4096 (576)
+// 152.0 -> 157.7; b = 128, m = 2000, 8 heads, n = 8192 (512, one to a CU) 352 -> 396; d = 128, the same 643 -> 723.)
 template <int D>
 static bool f32_tables_cost(const Geometry& g, int64_t wgs, int kw) {
-  const int64_t sorting = lds_workgroups(f32_qrows_at<D>(g) + 128 / kw * 4, D == 64 ? 3 : 2);
-  return wgs > 256 * sorting && sorting < lds_workgroups(f32_lds_bytes<D>(g.b, g.m, kModeNode), D == 64 ? 3 : 2);
+  const size_t rows = F32Lds<D>::BYTES, sort = f32_sort_end(g), list = f32_list_bytes(g.b, g.m, kModeNode);
+  const int64_t sorting = lds_workgroups((sort > rows ? sort : rows) + 128 / kw * 4, D == 64 ? 3 : 2);
+  return wgs > 256 * sorting && sorting < lds_workgroups(list > rows ? list : rows, D == 64 ? 3 : 2);
 }
 
 bool attn_f32_sorts(const Geometry& g) {
   const int rows = node_sort_rows(g);
-  const int64_t wgs = attn_f32_node_grid(g);
+  const int64_t tiles = node_grid<128>(g);
+  const int kw = tiles >= 512 && f32_fits(g.b, 128) ? 1 : tiles >= 256 && f32_fits(g.b, 64) ? 2 : 4;
+  const int64_t wgs = kw == 1 ? tiles : kw == 2 ? node_grid<64>(g) : node_grid<32>(g);
   if (rows > kNodeSortMax || wgs > 1024 || wgs * rows > 4 << 20) return false;
-  const int kw = f32_waves_per_group(g.b, node_grid<128>(g));
   if (g.b + g.m > 320 && (g.d == 64 ? f32_tables_cost<64>(g, wgs, kw) : f32_tables_cost<128>(g, wgs, kw))) return false;
   if (g.d == 64 || 4 * g.b < 3 * 64) return true;
   if (kw > 1 && wgs * rows > 5 << 19) return false;
@@ -532,33 +626,35 @@ bool attn_f32_sorts(const Geometry& g) {
 
 // Exact launches of few workgroups and long rows are bound by the longest chain of key tiles: eight waves then share 32 queries,
 // two per SIMD where four left one, a workgroup that fills a CU (causal: up to one and a half or two rounds of those, heaviest first).
-// Four waves -> eight (MI355X, us; groups of 32 rows in brackets): d = 128: causal, 16 heads, n = 512 (256) 29.9 -> 28.8; 12 heads,
-// n = 1024 (384) 54.7 -> 49.5, 16 (512) 55.1 -> 58.9; 8 heads, n = 2048 (512) 96.4 -> 92.9; 4 heads, n = 4000 (500) 176 -> 162, 1 head 179 -> 141;
-// unmasked, 8 heads, n = 1024 (256) 52.1 -> 48.2, 12 (384) 79.8 -> 87.9; 1 head, n = 4000 181 -> 146, 3 (375) 275 -> 285.
-// d = 64: causal, 8 heads, n = 1024 (256) 24.0 -> 25.0; 6 heads, n = 2048 (384) 48.9 -> 41.8, 8 (512) 49.0 -> 50.6; 3 heads, n = 4000 (375)
-// 84.5 -> 75.1; unmasked, 1 head, n = 2048 (64) 42.4 -> 41.9, 4 (256) 42.7 -> 42.6.
+// Four waves -> eight (MI355X, us; groups of 32 rows in brackets): d = 64: causal, 16 heads, n = 512 (256) 13.5 -> 12.6; n = 1024: one head (32)
+// 19.8 -> 17.7, 8 heads (256) 22.0 -> 19.5, 16 (512) 24.5 -> 26.1; n = 2048: 4 heads (256) 37.9 -> 32.3, 8 (512) 42.0 -> 41.3; 3 heads, n = 4000 (375)
+// 71.2 -> 61.5; unmasked: 8 heads, n = 1024 (256) 23.0 -> 21.7, 4 heads, n = 2048 (256) 40.0 -> 38.5, 4 heads, n = 4000 (500) 127.4 -> 131.5.  d = 128:
+// causal, 16 heads, n = 512 (256) 23.7 -> 21.7; 8 heads, n = 1024 (256) 38.4 -> 34.8, 16 (512) 43.8 -> 45.4; 8 heads, n = 2048 (512) 78.4 -> 76.8; 3 heads,
+// n = 4000 (375) 135 -> 113; unmasked, 8 heads, n = 1024 (256) 40.5 -> 39.8, 4 heads, n = 4000 (500) 235.9 -> 242.5.
 bool f32_exact_eight(const AttnArgs& a) {
   const int rows = a.exact_block < a.exact_rows_q ? a.exact_block : a.exact_rows_q;
-  const int64_t groups = exact_grid<32>(a);
-  if (a.g.d == 128) return rows >= 512 && groups <= (!a.exact_causal ? 256 : rows < 2048 ? 384 : 512);
-  return rows >= 2048 && groups <= (a.exact_causal ? 384 : 128);
+  return rows >= 512 && exact_grid<32>(a) <= (!a.exact_causal ? 256 : rows < 2048 ? 384 : 512);
 }
 
 template <int D, int MODE>
 static int launch_f32_mode(const AttnArgs& a, hipStream_t st) {
   if constexpr (MODE == kModeNode)  // stage calls alone: the whole-call entry points take up to 2^22 rows per head
     if ((int64_t)a.g.n * (D * 4) > 0x7fffffff + 1ll) return launch_f32_one<D, MODE, 4, true>(a, st);
-  const int run = MODE != kModeExact ? a.g.b : (a.exact_block < a.exact_rows_q ? a.exact_block : a.exact_rows_q);
-  const int kw = f32_waves_per_group(run, MODE != kModeExact ? node_grid<128>(a.g) : exact_grid<128>(a));
+  if constexpr (MODE == kModeExact)
+    if (f32_exact_eight(a)) return launch_f32_one<D, MODE, 8>(a, st);
+  const int run = a.exact_block < a.exact_rows_q ? a.exact_block : a.exact_rows_q;
+  const int kw = MODE != kModeExact ? f32_node_ways(a.g) : f32_ways(D, run, exact_grid<128>(a), a.exact_causal);
   if constexpr (MODE == kModeNode)
     if (a.codes_q) {
       if (kw == 1) return launch_f32_one<D, MODE, 1, false, true>(a, st);
-      return kw == 2 ? launch_f32_one<D, MODE, 2, false, true>(a, st) : launch_f32_one<D, MODE, 4, false, true>(a, st);
+      if constexpr (D == 64)
+        if (kw == 2) return launch_f32_one<D, MODE, 2, false, true>(a, st);
+      return launch_f32_one<D, MODE, 4, false, true>(a, st);
     }
-  if constexpr (MODE == kModeExact)
-    if (f32_exact_eight(a)) return launch_f32_one<D, MODE, 8>(a, st);
   if (kw == 1) return launch_f32_one<D, MODE, 1>(a, st);
-  return kw == 2 ? launch_f32_one<D, MODE, 2>(a, st) : launch_f32_one<D, MODE, 4>(a, st);
+  if constexpr (D == 64)
+    if (kw == 2) return launch_f32_one<D, MODE, 2>(a, st);
+  return launch_f32_one<D, MODE, 4>(a, st);
 }
 
 int launch_attn_f32(const AttnArgs& a, int mode, hipStream_t st) {

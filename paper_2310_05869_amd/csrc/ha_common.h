@@ -178,7 +178,6 @@ int64_t attn_mfma_grid(const AttnArgs& a, int mode);  // workgroups of the four-
 bool attn_mfma_sorts(const Geometry& g);               // whether the node launch sorts its nodes by itself
 int launch_attn_f32(const AttnArgs& a, int mode, hipStream_t st);
 bool f32_exact_eight(const AttnArgs& a);  // whether eight waves share 32 rows of an exact fp32 launch
-int64_t attn_f32_node_grid(const Geometry& g);        // workgroups of the node launch
 bool attn_f32_sorts(const Geometry& g);               // whether it sorts its nodes by itself
 int launch_gather_rows(const void* src, const int32_t* idx, void* dst, int groups, int n, int d, int dtype,
                        hipStream_t st);

@@ -1,0 +1,149 @@
+// fp32 products on the bf16 matrix cores, to the precision of fp32 ones.
+//
+// A float's 24 significant bits are three bf16 numbers of 8: x = hi + mid + lo, without remainder (hi: the upper half of x's bits; mid:
+// what is left, rounded; lo: what is left then).  Of the nine products of two such numbers the six that reach 2^-22 of the
+// whole are formed, exactly, and summed in fp32 by v_mfma_f32_32x32x16_bf16: six instructions of 32 cycles for 16 terms, where
+// v_mfma_f32_32x32x2_f32 takes eight of 64.  The sums are rounded once per 16 terms instead of once per two, which is worth more than the three
+// products left out.  Errors against 64 bits, fp32 instruction -> split (2-norm, relative; exact attention, 2 heads, n = 2048,
+// d = 64): out 4.2e-7 -> 2.9e-7, dQ 5.4e-7 -> 4.4e-7, dK 5.4e-7 -> 4.3e-7, dV 5.1e-7 -> 4.2e-7; causal 2.6e-7 -> 1.5e-7, 3.6e-7 -> 2.6e-7, 5.1e-7 -> 3.8e-7,
+// 4.6e-7 -> 3.6e-7; 64 clusters, scores to 250: 9.3e-6 -> 4.3e-6, 2.2e-5 -> 1.2e-5, 2.1e-5 -> 1.2e-5, 1.2e-5 -> 8.6e-6; d = 128 likewise.
+//
+// What it costs is vector work: 15 instructions per two numbers, 240 for a wave's operand of 32 rows of 64 floats, beside 24 products.  So
+// where several waves use a tile it is split once and kept in LDS (SplitTile).
+#pragma once
+
+#include "attn_common.h"
+
+namespace ha {
+
+typedef __bf16 split_bf16x8 __attribute__((ext_vector_type(8)));
+typedef float split_f32x16 __attribute__((ext_vector_type(16)));
+typedef float split_f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t split_u32x4 __attribute__((ext_vector_type(4)));
+
+struct Split8 {  // eight numbers, a lane's share of an operand
+  split_bf16x8 hi, mid, lo;
+};
+
+// INF: the numbers may be infinite or NaN.  lo, which meets the other operand's hi alone, then carries that and hi and mid are finite, so that a
+// product has the sign, and a sum of products the value, that they have in fp32 (an infinite hi times the other's mid or lo, of
+// either sign or 0, would make a NaN of them).
+template <bool INF, class F>
+__device__ inline Split8 split8(F&& x) {
+  constexpr float kMax = 3.40282347e38f;
+  auto upper = [](float v) { return __uint_as_float(__float_as_uint(v) & 0xffff0000u); };
+  split_u32x4 h, m, l;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float a = x(2 * e), b = x(2 * e + 1);
+    const float fa = INF ? __builtin_amdgcn_fmed3f(a, -kMax, kMax) : a, fb = INF ? __builtin_amdgcn_fmed3f(b, -kMax, kMax) : b;
+    const float ha = upper(fa), hb = upper(fb);
+    h[e] = __builtin_amdgcn_perm(__float_as_uint(fb), __float_as_uint(fa), 0x07060302u);
+    m[e] = pack_bf16x2(fa - ha, fb - hb);
+    const float la = (a - ha) - __uint_as_float(m[e] << 16), lb = (b - hb) - upper(__uint_as_float(m[e]));
+    l[e] = __builtin_amdgcn_perm(__float_as_uint(lb), __float_as_uint(la), 0x07060302u);
+  }
+  Split8 s;
+  s.hi = __builtin_bit_cast(split_bf16x8, h);
+  s.mid = __builtin_bit_cast(split_bf16x8, m);
+  s.lo = __builtin_bit_cast(split_bf16x8, l);
+  return s;
+}
+
+__device__ inline split_f32x16 split_mfma(split_bf16x8 a, split_bf16x8 b, split_f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+
+// c += a b, the small products first
+__device__ inline void split_product(const Split8& a, const Split8& b, split_f32x16& c) {
+  c = split_mfma(a.lo, b.hi, c);
+  c = split_mfma(a.hi, b.lo, c);
+  c = split_mfma(a.mid, b.mid, c);
+  c = split_mfma(a.mid, b.hi, c);
+  c = split_mfma(a.hi, b.mid, c);
+  c = split_mfma(a.hi, b.hi, c);
+}
+
+// The same with the small products in a sum of their own: a score's rounding is then that of a few additions of 16 terms, and the
+// same whichever operand is a.
+__device__ inline void split_product(const Split8& a, const Split8& b, split_f32x16& big, split_f32x16& small) {
+  small = split_mfma(a.lo, b.hi, small);
+  small = split_mfma(a.hi, b.lo, small);
+  small = split_mfma(a.mid, b.mid, small);
+  small = split_mfma(a.mid, b.hi, small);
+  small = split_mfma(a.hi, b.mid, small);
+  big = split_mfma(a.hi, b.hi, big);
+}
+
+// acc[k] += a(k, 0) b[0] + a(k, 1) b[1] for N accumulators: the 32 rows of a tile, rounded once.  Where one wave's sums run over all tiles of a
+// long row, twelve roundings a tile are most of the result's error (exact attention, n = 4013, one way: out 1.1e-6 -> 2.9e-7).  A tile's sum
+// is added while the next accumulator's products run: behind its own the wave waits for the last of them.
+template <int N, class A>
+__device__ inline void split_tile_products(A&& a, const Split8 (&b)[2], split_f32x16 (&acc)[N]) {
+  split_f32x16 t[2];
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) t[k & 1][i] = 0.f;
+#pragma unroll
+    for (int s = 0; s < 2; ++s) split_product(a(k, s), b[s], t[k & 1]);
+    __builtin_amdgcn_sched_barrier(0);
+    if (k > 0) acc[k - 1] += t[(k - 1) & 1];
+  }
+  acc[N - 1] += t[(N - 1) & 1];
+}
+
+// c += small, here: behind a branch the compiler (ROCm 7.2) counts the wait states from the last product to its first reader along one
+// of the two ways only, and on the other the reader came too early.
+__device__ inline void split_sum(split_f32x16& c, const split_f32x16& small) {
+  c += small;
+  asm volatile("" : "+v"(c));
+}
+
+// A tile of 32 rows in LDS: three planes of bf16 rows, unpadded; piece c (16 bytes) of row r sits at place c ^ swz(r), which keeps the
+// writes and both readers free of bank conflicts (attn_bwd_mfma.hip's layout).
+template <int D>
+struct SplitTile {
+  static constexpr int ROWB = D * 2, PLANE = 32 * ROWB, BYTES = 3 * PLANE;
+  static constexpr int PPR = D / 8;  // pieces per row
+  __device__ static int swz(int row) {
+    if (D == 128) return ((row & 3) << 2) | ((row >> 2) & 3);
+    return ((row & 2) << 1) | ((row >> 2) & 3);
+  }
+  __device__ static void store(unsigned char* tile, int row, int piece, split_f32x4 x0, split_f32x4 x1) {
+    const Split8 s = split8<true>([&](int e) { return e < 4 ? x0[e] : x1[e - 4]; });
+    unsigned char* at = tile + row * ROWB + ((piece ^ swz(row)) << 4);
+    *reinterpret_cast<split_bf16x8*>(at) = s.hi;
+    *reinterpret_cast<split_bf16x8*>(at + PLANE) = s.mid;
+    *reinterpret_cast<split_bf16x8*>(at + 2 * PLANE) = s.lo;
+  }
+  // Row lane & 31, columns 16 s + 8 h ... + 7; `at` = row_at(lane).
+  __device__ static int row_at(int lane) {
+    const int row = lane & 31;
+    return row * ROWB + (((lane >> 5) ^ swz(row)) << 4);
+  }
+  __device__ static Split8 row_frag(const unsigned char* tile, int at, int s) {
+    const unsigned char* p = tile + (at ^ (32 * s));
+    return Split8{*reinterpret_cast<const split_bf16x8*>(p), *reinterpret_cast<const split_bf16x8*>(p + PLANE),
+                  *reinterpret_cast<const split_bf16x8*>(p + 2 * PLANE)};
+  }
+  // Column 32 dt + (lane & 31) of rows 16 j + 4 h ... + 3 and 16 j + 8 + 4 h ... + 3, the rows of accumulator elements 8 j ... 8 j + 7;
+  // `at` = col_at(lane).
+  __device__ static int col_at(int lane) {
+    const int row = 4 * (lane >> 5) + ((lane & 15) >> 2);
+    return row * ROWB + (((((lane >> 4) & 1) * 2 + ((lane & 3) >> 1)) ^ swz(row)) << 4) + (lane & 1) * 8;
+  }
+  __device__ static Split8 col_frag(const unsigned char* tile, int at, int j, int dt) {
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    typedef short s16x8 __attribute__((ext_vector_type(8)));
+    typedef s16x4 __attribute__((address_space(3))) * lds_s16x4_ptr;
+    auto plane = [&](const unsigned char* p) {
+      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p + (at ^ (64 * dt)) + 16 * j * ROWB));
+      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p + (at ^ (64 * dt + 32)) + (16 * j + 8) * ROWB));
+      return __builtin_bit_cast(split_bf16x8, (s16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
+    return Split8{plane(tile), plane(tile + PLANE), plane(tile + 2 * PLANE)};
+  }
+};
+
+}  // namespace ha

@@ -1,0 +1,101 @@
+"""fp32 attention on operands split in three bf16 parts: every form of the kernels at lengths that no tile divides, against
+64-bit attention; infinities; powers of two, which change no bit of a product."""
+import pytest
+
+from ha_testutil import have_gpu
+
+pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not have_gpu(), reason="needs a GPU")]
+
+
+@pytest.fixture(scope="module")
+def ha():
+    import paper_2310_05869_amd as mod
+    mod.lib()
+    return mod
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as t
+    return t
+
+
+def _inputs(torch, H, n, d, seed, count=4):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    return [torch.randn((1, H, n, d), generator=gen, device="cuda") * d ** -0.25 for _ in range(count)]
+
+
+def _reference(torch, q, k, v, g, causal):
+    """Output, log row sums and gradients of one head in 64 bits."""
+    q, k, v = (x.double().detach().requires_grad_(True) for x in (q, k, v))
+    s = torch.matmul(q, k.transpose(-1, -2).contiguous())
+    if causal:
+        s = s.masked_fill(torch.ones(s.shape[-2:], dtype=torch.bool, device="cuda").triu(1), float("-inf"))
+    lse = torch.logsumexp(s, -1)
+    out = torch.matmul(torch.exp(s - lse[..., None]), v)
+    out.backward(g.double())
+    return out.detach(), lse.detach(), q.grad, k.grad, v.grad
+
+
+@pytest.mark.parametrize("d,H,n,causal", [
+    (64, 13, 4013, False),   # one way; a last tile of 13 keys, a last workgroup of 45 rows
+    (64, 70, 2007, True),
+    (64, 9, 3700, False),    # two ways, the second without a last tile
+    (64, 33, 2031, True),
+    (64, 20, 1001, True),    # four ways
+    (64, 3, 1003, True),     # eight
+    (64, 1, 33, False),
+    (128, 8, 4013, False),   # one way
+    (128, 66, 2007, True),
+    (128, 9, 3001, True),    # four
+    (128, 2, 777, False),    # eight (backward: four)
+])
+def test_exact_forms(ha, torch, d, H, n, causal):
+    """Outputs within the fp32 criterion 1e-5 + 1e-5 |ref|; gradients: 2-norm of the error at most 1e-6 of the gradient's (sums of up to n
+    terms in fp32, 2^-24 each with random signs, measured 3e-7 to 7e-7)."""
+    print(f"split fp32 d={d} H={H} n={n} causal={causal}", flush=True)
+    q, k, v, g = _inputs(torch, H, n, d, n + d)
+    out, lse = ha.exact_attn_forward(q, k, v, causal=causal)
+    grads = ha.exact_attn_backward(q, k, v, out, lse, g, causal=causal)
+    for h in {0, H - 1}:
+        ref = _reference(torch, *(x[:, h:h + 1] for x in (q, k, v, g)), causal)
+        assert ((out[:, h:h + 1].double() - ref[0]).abs() <= 1e-5 + 1e-5 * ref[0].abs()).all()
+        assert ((lse[:, h:h + 1].double() - ref[1]).abs() <= 2e-5).all()
+        for got, want in zip(grads, ref[2:]):
+            assert (got[:, h:h + 1].double() - want).norm() <= 1e-6 * want.norm()
+
+
+@pytest.mark.parametrize("d,H,n", [(64, 13, 4000), (64, 2, 700), (128, 8, 4096), (128, 2, 700)])
+def test_infinite_values(ha, torch, d, H, n):
+    """A value row of +inf makes the outputs of every row that sees it +inf, as a sum of products in fp32 does; a key whose score is -inf has
+    no weight."""
+    print(f"split fp32 inf d={d} H={H} n={n}", flush=True)
+    q, k, v = _inputs(torch, H, n, d, d, 3)
+    v[:, :, 5, 3] = float("inf")
+    out, _ = ha.exact_attn_forward(q, k, v)
+    assert torch.isposinf(out[..., 3]).all()
+    assert torch.isfinite(out[..., :3]).all() and torch.isfinite(out[..., 4:]).all()
+    v[:, :, 5, 3] = 0.0
+    q[..., 7] = q[..., 7].abs() + 0.1
+    k[:, :, 9, 7] = float("-inf")
+    out, lse = ha.exact_attn_forward(q, k, v)
+    others = [i for i in range(n) if i != 9]
+    s = torch.matmul(q[:, :1].double(), k[:, :1, others].double().transpose(-1, -2).contiguous())
+    want = torch.matmul(torch.softmax(s, -1), v[:, :1, others].double())
+    assert ((out[:, :1].double() - want).abs() <= 1e-5 + 1e-5 * want.abs()).all()
+    assert torch.isfinite(lse).all()
+
+
+@pytest.mark.parametrize("d,H,n,causal", [(64, 13, 4000, False), (64, 2, 700, True), (128, 8, 4096, False), (128, 2, 700, True)])
+def test_powers_of_two_change_no_bit(ha, torch, d, H, n, causal):
+    print(f"split fp32 scales d={d} H={H} n={n}", flush=True)
+    q, k, v, g = _inputs(torch, H, n, d, 2 * n)
+    a, b = 2.0 ** 30, 2.0 ** -50
+    out, lse = ha.exact_attn_forward(q, k, v, causal=causal)
+    out2, lse2 = ha.exact_attn_forward(q * a, k / a, v * b, causal=causal)
+    assert torch.equal(lse, lse2) and torch.equal(out * b, out2)
+    grads = ha.exact_attn_backward(q, k, v, out, lse, g, causal=causal)
+    grads2 = ha.exact_attn_backward(q * a, k / a, v * b, out2, lse2, g, causal=causal)
+    for x, y, scale in zip(grads, grads2, (b / a, b * a, 1.0)):
+        assert torch.equal(x * scale, y)

@@ -15,17 +15,20 @@
 //
 // KW ways share a group of R rows, each taking every KW-th tile; their sums are added through LDS in
 // order, so results are bit-reproducible.  KW = 1: four waves of different R rows share the tiles, split once into LDS.  KW = 4 or 8: one group of
-// 32 R rows per workgroup, which lie split in LDS; a wave's T rows come straight from the caches in operand layout, twice (as rows and in
-// columns), and are split in registers.
+// 32 R rows per workgroup, which lie split in LDS; a wave's T rows come straight from the caches in operand layout and are split in
+// registers, B's in the dK / dV passes twice (as rows and in columns); the split rows of Y go to a tile of the wave's own for the product
+// that takes them in columns (24 KB with R, 12 KB a wave: both tensors' tiles would leave a CU one workgroup).  Fetched and split twice as
+// well (backward, MI355X, us): causal, 4 heads, n = 4096 in blocks of 1024, b = m = 64 116 -> 108, d = 128 248 -> 235; exact, causal, 8 heads, n = 4096 482 ->
+// 457, 1012 -> 951, one head, n = 1024 60.0 -> 56.0, 119 -> 112; 8 heads, n = 4096, b = m = 256 152 -> 142.
 //
 // What bounds it: in large launches the matrix pipe at the clock that the chip's power leaves it (32 heads, n = 8192, d = 64: the seven products
 // of a pair at 1110 TFLOP/s of bf16 products); in small ones (4 heads, n = 4096 in causal blocks of 1024, base case with the sampled keys, 1152
-// workgroups) vector issue, half of the cycles, the splits being some 60 % of it, and workgroups of unequal length (matrix pipe 25 %; 1.4 waves
-// per SIMD of two).  At d = 64 the dK / dV passes spill 176 to 196 bytes per lane with one way, 24 to 28 with more.
+// workgroups) vector issue, half of the cycles, the splits being some 55 % of it, and workgroups of unequal length (matrix pipe 25 %; 1.4 waves
+// per SIMD of two).  At d = 64 the dK / dV passes spill 176 to 196 bytes per lane with one way, up to 56 with more.
 // Measured (MI355X, us; fp32 matrix instructions, T rows always from the caches -> this form), backward of exact attention: 32 heads,
-// n = 8192, d = 64 15000 -> 10430, 16 heads, d = 128 16210 -> 10540; causal, 16 heads, n = 1024 95.6 -> 84.9, d = 128 205 -> 177; 8 heads, n = 4096 547 -> 471,
-// 1120 -> 995; one head, n = 1024 77.3 -> 60.3, 136 -> 119; of HyperAttention: one head, n = 1024, b = m = 64 45.6 -> 39.0, 8 heads, n = 4096, b = m = 256
-// 190 -> 150, d = 128 393 -> 260; causal, 4 heads, n = 4096 in blocks of 1024, b = m = 64 150 -> 115, 279 -> 246.
+// n = 8192, d = 64 15000 -> 10430, 16 heads, d = 128 16210 -> 10540; causal, 16 heads, n = 1024 95.6 -> 81.1, d = 128 205 -> 169; 8 heads, n = 4096 547 -> 457,
+// 1120 -> 951; one head, n = 1024 77.3 -> 56.0, 136 -> 112; of HyperAttention: one head, n = 1024, b = m = 64 45.6 -> 38.0, 8 heads, n = 4096, b = m = 256
+// 190 -> 142, d = 128 393 -> 259; causal, 4 heads, n = 4096 in blocks of 1024, b = m = 64 150 -> 108, 279 -> 235.
 #include "attn_common.h"
 #include "bwd_common.h"
 #include "split_f32.h"
@@ -39,16 +42,22 @@ constexpr int kFTT = 32;   // T rows per tile
 
 // LDS: the ways' tiles (Y and B) and L and delta of their rows, or, RG = 1, the R rows; the key list of a node's dQ pass; in the end the
 // staged rows, over the tiles; behind all else the sampled keys of a block-key pass.
+// (RG = 1: whether a wave keeps the split rows of its Y tile for the accumulating products; the lists of a d = 128 node leave no room)
+constexpr bool f32_bwd_keeps_y(int d, int mode) { return d == 64 || mode != kBwdDqNode; }
+
 template <int D, int RG, int KW>
 struct F32BwdLds {
   static constexpr int WAY = 2 * SplitTile<D>::BYTES;  // bytes of a way's tiles
   static constexpr int SC_AT = (RG > 1 ? KW : 1) * WAY;
-  static constexpr int LIST_AT = SC_AT + (RG > 1 ? KW * 2 * kFTT * 4 : 0);
+  static constexpr int OWN_AT = SC_AT + (RG > 1 ? KW * 2 * kFTT * 4 : 0);  // RG = 1: the waves' Y tiles
+  __host__ __device__ static constexpr int list_at(int mode) {
+    return OWN_AT + (RG == 1 && f32_bwd_keeps_y(D, mode) ? KW * SplitTile<D>::BYTES : 0);
+  }
   static constexpr int ROW = D + 4;  // floats per staged row
   static constexpr int ROWS = RG * KW * 32 * ROW * 4;
   __host__ __device__ static size_t hits_at(const Geometry& g, int mode) {
     const size_t list = mode == kBwdDqNode ? (size_t)(((g.b + g.m + 63) & ~63) + 64) * 4 + 64 : 0;
-    return LIST_AT + list > (size_t)ROWS ? LIST_AT + list : (size_t)ROWS;
+    return list_at(mode) + list > (size_t)ROWS ? list_at(mode) + list : (size_t)ROWS;
   }
   __host__ __device__ static size_t bytes(const Geometry& g, int mode) {
     return hits_at(g, mode) + (mode == kBwdDkvBlock && !g.causal ? sample_hits_bytes(g) : 0);
@@ -78,11 +87,12 @@ __device__ __forceinline__ void bwd_f32_pass(const BwdArgs& a, const int wg, con
   const int lq = lane & 31, h = lane >> 5;
   const int grp = wave % RG, kw = wave / RG;
   const int wtid = tid % (64 * RG);  // within the way
-  constexpr bool kShared = RG > 1;
+  constexpr bool kShared = RG > 1, kKeepY = !kShared && f32_bwd_keeps_y(D, MODE);
   unsigned char* ytile = smem + (kShared ? kw * L::WAY : 0);
   unsigned char* btile = ytile + T::BYTES;
+  unsigned char* own_y = smem + L::OWN_AT + (kKeepY ? wave * T::BYTES : 0);
   float* sc = reinterpret_cast<float*>(smem + L::SC_AT) + kw * 2 * kFTT;
-  int32_t* scratch = reinterpret_cast<int32_t*>(smem + L::LIST_AT);
+  int32_t* scratch = reinterpret_cast<int32_t*>(smem + L::list_at(MODE));
   int32_t* list = scratch + 16;
 
   // ---- which part of the problem this workgroup owns ----
@@ -246,7 +256,7 @@ __device__ __forceinline__ void bwd_f32_pass(const BwdArgs& a, const int wg, con
     }
   };
   auto of_elem = [&](auto v, int i) { return __shfl(v, 8 * (i / 4) + 4 * h + (i % 4)); };
-  auto load_cols = [&](const __amdgpu_buffer_rsrc_t& rsrc, int of, int kt, float (&v)[16][DT], int i0, int count) {
+  auto load_cols = [&](const __amdgpu_buffer_rsrc_t& rsrc, int of, int kt, auto& v, int i0, int count) {
     // Consecutive rows.  All of the row is in the lane's offset: the bounds check covers it, not the scalar one.  One
     // running offset (opaque, or the compiler keeps one register per eight rows across the loop): 241.3 us where constants of
     // one offset take 245.6 (4 heads, n = 4096 in causal blocks of 1024, forward + backward).
@@ -327,12 +337,16 @@ __device__ __forceinline__ void bwd_f32_pass(const BwdArgs& a, const int wg, con
 #pragma unroll
       for (int s = 0; s < KS; ++s) {
         if constexpr (kShared) split_product(T::row_frag(ytile, row_at, s), xs[s], c, small);
-        else split_product(split8<true>([&](int i) { return yf[2 * s + i / 4][i % 4]; }), T::row_frag(ytile, row_at, s), c, small);
+        else {
+          const Split8 y = split8<true>([&](int i) { return yf[2 * s + i / 4][i % 4]; });
+          if (kKeepY) T::store(own_y, lq, 2 * s + h, y);
+          split_product(y, T::row_frag(ytile, row_at, s), c, small);
+        }
       }
       split_sum(c, small);
     }
     float tv[kShared ? 1 : 16][DT];
-    if constexpr (!kShared) load_cols(kDq ? yrsrc : brsrc, row_c, kt, tv, 0, 16);
+    if constexpr (!kShared && !(kDq && kKeepY)) load_cols(kDq ? yrsrc : brsrc, row_c, kt, tv, 0, 16);
     {
       f32x16 small;
 #pragma unroll
@@ -394,30 +408,38 @@ __device__ __forceinline__ void bwd_f32_pass(const BwdArgs& a, const int wg, con
 #pragma unroll
       for (int hf = 0; hf < 2; ++hf) ps[hf] = split8<true>([&](int i) { return e[8 * hf + i]; });
       split_tile_products([&](int dt, int hf) { return T::col_frag(ytile, col_at, hf, dt); }, ps, acc1);
-    } else if constexpr (!kDq) {
-      // dV and dK half a tile at a time: the Q rows of a half arrive while the other half's dV products run
-      float yv[16][DT];
-#pragma unroll
-      for (int hf = 0; hf < 2; ++hf) {
-        load_cols(yrsrc, row_c, kt, yv, 8 * hf, 8);
-        const Split8 p = split8<false>([&](int i) { return c[8 * hf + i]; });
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) split_product(split8<true>([&](int i) { return tv[8 * hf + i][dt]; }), p, acc2[dt]);
-      }
-      if (kt + KW < kt_hi) fetch_own(kt + KW);
-#pragma unroll
-      for (int hf = 0; hf < 2; ++hf) {
-        const Split8 ds = split8<true>([&](int i) { return e[8 * hf + i]; });
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) split_product(split8<true>([&](int i) { return yv[8 * hf + i][dt]; }), ds, acc1[dt]);
-      }
     } else {
+      // Y^T dS from the wave's own tile, or, half a tile at a time, from the caches: the rows of a half arrive while the other half's
+      // dV products run
+      float yv[kKeepY || kDq ? 1 : 16][DT];
+      if constexpr (!kDq) {
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf) {
+          if constexpr (!kKeepY) load_cols(yrsrc, row_c, kt, yv, 8 * hf, 8);
+          const Split8 p = split8<false>([&](int i) { return c[8 * hf + i]; });
+#pragma unroll
+          for (int dt = 0; dt < DT; ++dt) split_product(split8<true>([&](int i) { return tv[8 * hf + i][dt]; }), p, acc2[dt]);
+        }
+      }
       if (kt + KW < kt_hi) fetch_own(kt + KW);
+      if constexpr (kKeepY) {  // (the tile's rows came from other lanes of the wave)
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      }
 #pragma unroll
       for (int hf = 0; hf < 2; ++hf) {
         const Split8 ds = split8<true>([&](int i) { return e[8 * hf + i]; });
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt) split_product(split8<true>([&](int i) { return tv[8 * hf + i][dt]; }), ds, acc1[dt]);
+        for (int dt = 0; dt < DT; ++dt) {
+          if constexpr (kKeepY) split_product(T::col_frag(own_y, col_at, hf, dt), ds, acc1[dt]);
+          else split_product(split8<true>([&](int i) { return (kDq ? tv : yv)[kDq || !kKeepY ? 8 * hf + i : 0][dt]; }), ds, acc1[dt]);
+        }
+      }
+      if constexpr (kKeepY) {  // (the next tile's rows are written behind these reads)
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
       }
     }
   }

@@ -111,7 +111,9 @@ struct SplitTile {
     return ((row & 2) << 1) | ((row >> 2) & 3);
   }
   __device__ static void store(unsigned char* tile, int row, int piece, split_f32x4 x0, split_f32x4 x1) {
-    const Split8 s = split8<true>([&](int e) { return e < 4 ? x0[e] : x1[e - 4]; });
+    store(tile, row, piece, split8<true>([&](int e) { return e < 4 ? x0[e] : x1[e - 4]; }));
+  }
+  __device__ static void store(unsigned char* tile, int row, int piece, const Split8& s) {
     unsigned char* at = tile + row * ROWB + ((piece ^ swz(row)) << 4);
     *reinterpret_cast<split_bf16x8*>(at) = s.hi;
     *reinterpret_cast<split_bf16x8*>(at + PLANE) = s.mid;

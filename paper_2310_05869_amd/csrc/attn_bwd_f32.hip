@@ -582,7 +582,11 @@ bool bwd_f32_shares(const BwdArgs& a) {
 
 template <int D, bool NODES>
 static int launch_shared_form(const BwdShared& m, int64_t grid, hipStream_t st) {
-  const size_t lds = F32BwdLds<D, 1, 4>::bytes(m.part[0].a.f.g, NODES ? kBwdDqNode : kBwdDqExact);
+  size_t lds = 0;  // the most that a part takes
+  for (const int mode : {NODES ? kBwdDkvBlock : kBwdDkvExact, NODES ? kBwdDqNode : kBwdDqExact, NODES ? kBwdDqNode : kBwdDkvSamp}) {
+    const size_t l = F32BwdLds<D, 1, 4>::bytes(m.part[0].a.f.g, mode);
+    lds = l > lds ? l : lds;
+  }
   static std::atomic<uint64_t> lds_set{0};  // per instantiation: devices on which the LDS limit is raised
   if (allow_full_lds(reinterpret_cast<const void*>(&attn_bwd_f32_shared_kernel<D, NODES>), lds_set) != HA_OK) return HA_ERR_LAUNCH;
   hipLaunchKernelGGL((attn_bwd_f32_shared_kernel<D, NODES>), dim3((unsigned)grid), dim3(256), lds, st, m);

@@ -7,7 +7,8 @@
 //   P'  = |X| |R|      same shape: sum_c |x_c R_ck|, the scale of the rounding error
 //
 // A wave reads 32 rows straight from global memory in the MFMA's operand layout
-// (lane l: row l%32, 8 consecutive elements starting at 16*ks + 8*(l/32)); R
+// (lane l: row l%32, 8 consecutive elements starting at 16*ks + 8*(l/32); or, of
+// a large problem, as they lie and into that layout through LDS); R
 // and |R| sit in registers as the other operand.  The products are formed as
 // R^T X^T so that a lane ends up with the projections of ONE row.  bf16 x bf16 products are exact; the
 // fp32 accumulation of the d products deviates from the exact sum by far less
@@ -34,8 +35,18 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
+// A group of 32 rows in LDS: piece c (16 bytes) of row n at place c ^ swz(n), free of bank conflicts for writes of whole rows
+// and for reads of one piece of many rows.
+template <int D>
+struct HashTile {
+  static constexpr int ROWB = D * 2, PPR = D / 8, BYTES = 32 * ROWB;
+  __device__ static int at(int row, int piece) { return row * ROWB + ((piece ^ (D == 128 ? row & 15 : (row >> 1) & 7)) << 4); }
+};
+
 // ARGS: R comes in the arguments (bf16 values by construction), else from a.R.
-template <int D, bool ARGS>
+// STREAM: rows are read as they lie in memory, 1 KiB per instruction and non-temporally, and take the operand layout through LDS
+// (stream_rows).
+template <int D, bool ARGS, bool STREAM>
 __global__ __launch_bounds__(256) void lsh_hash_mfma_kernel(HashArgs a) {
   constexpr int KS = D / 16;
   constexpr int EL = D / 64;  // elements per lane on the fp64 path
@@ -53,6 +64,16 @@ __global__ __launch_bounds__(256) void lsh_hash_mfma_kernel(HashArgs a) {
     const bool second = g >= gpt;
     const int64_t row0 = (second ? g - gpt : g) * 32;
     const uint16_t* X = reinterpret_cast<const uint16_t*>(second ? a.X[1] : a.X[0]) + row0 * D;
+    if constexpr (STREAM) {
+      const int pieces = (int)(rows - row0 < 32 ? rows - row0 : 32) * HashTile<D>::PPR;
+      const u32x4* xs = reinterpret_cast<const u32x4*>(X);
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        const int i = lane + 64 * ks;
+        xa[ks] = __builtin_nontemporal_load(xs + (i < pieces ? i : pieces - 1));
+      }
+      return;
+    }
     const int last = (int)(rows - row0 < 32 ? rows - row0 - 1 : 31);
     const u32x4* xp = reinterpret_cast<const u32x4*>(X + (n < last ? n : last) * D + 8 * h);
 #pragma unroll
@@ -110,14 +131,35 @@ __global__ __launch_bounds__(256) void lsh_hash_mfma_kernel(HashArgs a) {
   if (a.store_draws) store_draws(a);
   if constexpr (!ARGS) __syncthreads();
 
+  __shared__ __attribute__((aligned(16))) unsigned char tiles[STREAM ? 4 : 1][STREAM ? HashTile<D>::BYTES : 16];
   const uint32_t mask_r = (1u << r) - 1u;
-  auto trip = [&](int64_t g, u32x4 (&xa)[KS], u32x4 (&xn)[KS]) {
+  auto trip = [&](int64_t g, u32x4 (&xs)[KS], u32x4 (&xn)[KS]) {
     const bool second = g >= gpt;
     const int64_t row0 = (second ? g - gpt : g) * 32;
     // unconditional (past the end: this trip's own rows again, a cache hit), so
     // the count of loads in flight is the same on every path and the waits
     // before the MFMAs below leave the two younger groups in flight
     load_group(g + 2 * nwaves < ngroups ? g + 2 * nwaves : g, xn);
+
+    u32x4 xa[KS];
+    if constexpr (STREAM) {  // (LDS serves one wave's requests in order)
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        const int i = lane + 64 * ks;
+        *reinterpret_cast<u32x4*>(tiles[wv] + HashTile<D>::at(i / HashTile<D>::PPR, i % HashTile<D>::PPR)) = xs[ks];
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) xa[ks] = *reinterpret_cast<const u32x4*>(tiles[wv] + HashTile<D>::at(n, 2 * ks + h));
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    } else {
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) xa[ks] = xs[ks];
+    }
 
     f32x16 p, pa;
 #pragma unroll
@@ -252,20 +294,30 @@ __global__ __launch_bounds__(256) void lsh_hash_mfma_kernel(HashArgs a) {
 // comes from is open.  320 to 448: up to 6 % slower at small sizes, 768: 4 to 6 %.
 static int most_hash_blocks(int64_t ngroups, int d) { return d == 64 && ngroups > 32 * 4 * 256 ? 512 : 256; }
 
-template <int D>
+// In the operand layout a load takes 32 bytes from each of 32 rows, four loads to a line, which non-temporal loads would fetch four times (a
+// plain read of 2 GB: 6.4 TB/s so, 3.85 non-temporally; of whole lines 6.3 and 7.0 to 7.2).  From what the Infinity Cache holds (256 MB) on
+// the rows are therefore read as they lie and go through LDS; below, what the launch leaves in the caches serves the attention launch.
+// Forward, in the operand layout -> as they lie (MI355X, us; Q and K together):
+//   d = 128: 46 MB 52.2 -> 53.0, 64 MB 75.2 -> 78.4, 128 MB 127.3 -> 132.4, 256 MB 247.6 -> 244.5, 512 MB 477.3 -> 467.0, 2 GB 1517 -> 1476
+//   d = 64: 256 MB 263.3 -> 260.7, 1 GB 1326 -> 1310
+// Three or four groups ahead instead of two: no gain.
+static bool stream_rows(int64_t bytes) { return bytes >= 256ll << 20; }
+
+template <int D, bool STREAM>
 static void launch_d(const HashArgs& a, dim3 grid, hipStream_t st) {
-  if (a.R) hipLaunchKernelGGL((lsh_hash_mfma_kernel<D, false>), grid, dim3(256), 0, st, a);
-  else hipLaunchKernelGGL((lsh_hash_mfma_kernel<D, true>), grid, dim3(256), 0, st, a);
+  if (a.R) hipLaunchKernelGGL((lsh_hash_mfma_kernel<D, false, STREAM>), grid, dim3(256), 0, st, a);
+  else hipLaunchKernelGGL((lsh_hash_mfma_kernel<D, true, STREAM>), grid, dim3(256), 0, st, a);
 }
 
 int launch_lsh_hash_mfma(const HashArgs& a, int d, hipStream_t st) {
   if (a.rows <= 0) return HA_OK;
   const int64_t ngroups = (a.rows + 31) / 32 * (a.X[1] ? 2 : 1);
   int64_t blocks = (ngroups + 3) / 4;
+  const bool stream = stream_rows(ngroups * 32 * d * 2);
   if (blocks > most_hash_blocks(ngroups, d)) blocks = most_hash_blocks(ngroups, d);
   const dim3 grid((unsigned)blocks);
-  if (d == 128) launch_d<128>(a, grid, st);
-  else if (d == 64) launch_d<64>(a, grid, st);
+  if (d == 128) stream ? launch_d<128, true>(a, grid, st) : launch_d<128, false>(a, grid, st);
+  else if (d == 64) stream ? launch_d<64, true>(a, grid, st) : launch_d<64, false>(a, grid, st);
   else return HA_ERR_SHAPE;
   return check_launch();
 }

@@ -802,3 +802,22 @@ def test_stage_times_add_up(ha, torch):
     assert ms["prep"] == 0.0
     assert all(ms[k] > 0 for k in ("lsh_hash", "seg_sort", "node_attn", "causal_base"))
     assert abs(sum(ms[k] for k in ("lsh_hash", "seg_sort", "node_attn", "causal_base")) - ms["total"]) < 1e-3
+
+
+@pytest.mark.parametrize("d,rows", [(64, (1 << 21) - 31), (64, (1 << 21) + 17), (128, (1 << 20) + 1), (128, (1 << 20) + 64)])
+@pytest.mark.parametrize("exact_R", [True, False])
+def test_lsh_hash_of_many_rows_is_that_of_its_parts(ha, torch, d, rows, exact_R):
+    """From 256 MB on the rows are read in another order: the same codes, bit for bit, as those of parts below it, with rows of zeros
+    (redone in 64 bits) among them."""
+    print(f"lsh_hash d={d} rows={rows} exact_R={exact_R}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(rows)
+    X = torch.randn((rows, d), generator=gen, device="cuda").to(torch.bfloat16)
+    X[::97] = 0.0
+    X[-1] = 0.0
+    R = torch.from_numpy(orc.make_projection(3, d, 7).astype(np.float32)).cuda()
+    if not exact_R:
+        R = R[:, :5] * 1.0001
+    got = ha.ha_lsh_hash(X, R.contiguous())
+    for part in range(0, rows, 300007):
+        assert torch.equal(got[part:part + 300007], ha.ha_lsh_hash(X[part:part + 300007].contiguous(), R.contiguous()))

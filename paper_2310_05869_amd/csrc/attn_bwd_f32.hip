@@ -42,22 +42,26 @@ constexpr int kFTT = 32;   // T rows per tile
 
 // LDS: the ways' tiles (Y and B) and L and delta of their rows, or, RG = 1, the R rows; the key list of a node's dQ pass; in the end the
 // staged rows, over the tiles; behind all else the sampled keys of a block-key pass.
-// (RG = 1: whether a wave keeps the split rows of its Y tile for the accumulating products; the lists of a d = 128 node leave no room)
-constexpr bool f32_bwd_keeps_y(int d, int mode) { return d == 64 || mode != kBwdDqNode; }
+// (RG = 1: whether a wave keeps the split rows of its Y tile for the accumulating products; the lists of a d = 128 node leave no room,
+// nor do 4096 sampled keys of an unmasked problem's block keys)
+constexpr bool f32_bwd_keeps_y(int d, int mode, bool causal) {
+  return d == 64 || (mode != kBwdDqNode && (mode != kBwdDkvBlock || causal));
+}
 
 template <int D, int RG, int KW>
 struct F32BwdLds {
   static constexpr int WAY = 2 * SplitTile<D>::BYTES;  // bytes of a way's tiles
   static constexpr int SC_AT = (RG > 1 ? KW : 1) * WAY;
   static constexpr int OWN_AT = SC_AT + (RG > 1 ? KW * 2 * kFTT * 4 : 0);  // RG = 1: the waves' Y tiles
-  __host__ __device__ static constexpr int list_at(int mode) {
-    return OWN_AT + (RG == 1 && f32_bwd_keeps_y(D, mode) ? KW * SplitTile<D>::BYTES : 0);
+  __host__ __device__ static constexpr int list_at(int mode, bool causal) {
+    return OWN_AT + (RG == 1 && f32_bwd_keeps_y(D, mode, causal) ? KW * SplitTile<D>::BYTES : 0);
   }
   static constexpr int ROW = D + 4;  // floats per staged row
   static constexpr int ROWS = RG * KW * 32 * ROW * 4;
   __host__ __device__ static size_t hits_at(const Geometry& g, int mode) {
     const size_t list = mode == kBwdDqNode ? (size_t)(((g.b + g.m + 63) & ~63) + 64) * 4 + 64 : 0;
-    return list_at(mode) + list > (size_t)ROWS ? list_at(mode) + list : (size_t)ROWS;
+    const size_t end = list_at(mode, g.causal) + list;
+    return end > (size_t)ROWS ? end : (size_t)ROWS;
   }
   __host__ __device__ static size_t bytes(const Geometry& g, int mode) {
     return hits_at(g, mode) + (mode == kBwdDkvBlock && !g.causal ? sample_hits_bytes(g) : 0);
@@ -87,12 +91,12 @@ __device__ __forceinline__ void bwd_f32_pass(const BwdArgs& a, const int wg, con
   const int lq = lane & 31, h = lane >> 5;
   const int grp = wave % RG, kw = wave / RG;
   const int wtid = tid % (64 * RG);  // within the way
-  constexpr bool kShared = RG > 1, kKeepY = !kShared && f32_bwd_keeps_y(D, MODE);
+  constexpr bool kShared = RG > 1, kKeepY = !kShared && f32_bwd_keeps_y(D, MODE, !FINAL);
   unsigned char* ytile = smem + (kShared ? kw * L::WAY : 0);
   unsigned char* btile = ytile + T::BYTES;
   unsigned char* own_y = smem + L::OWN_AT + (kKeepY ? wave * T::BYTES : 0);
   float* sc = reinterpret_cast<float*>(smem + L::SC_AT) + kw * 2 * kFTT;
-  int32_t* scratch = reinterpret_cast<int32_t*>(smem + L::list_at(MODE));
+  int32_t* scratch = reinterpret_cast<int32_t*>(smem + L::list_at(MODE, !FINAL));
   int32_t* list = scratch + 16;
 
   // ---- which part of the problem this workgroup owns ----

@@ -3,6 +3,7 @@
 import pytest
 
 from ha_testutil import have_gpu
+from test_gpu_backward import _run_case
 
 pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not have_gpu(), reason="needs a GPU")]
 
@@ -99,3 +100,12 @@ def test_powers_of_two_change_no_bit(ha, torch, d, H, n, causal):
     grads2 = ha.exact_attn_backward(q * a, k / a, v * b, out2, lse2, g, causal=causal)
     for x, y, scale in zip(grads, grads2, (b / a, b * a, 1.0)):
         assert torch.equal(x * scale, y)
+
+
+@pytest.mark.parametrize("d,n,b,m,causal,n_min", [(128, 256, 32, 4096, 0, 4096), (64, 256, 32, 4096, 0, 4096), (128, 256, 32, 4096, 1, 64),
+                                                  (128, 8192, 4096, 4096, 0, 4096), (64, 8192, 4096, 4096, 1, 4096)])
+def test_most_sampled_keys(ha, torch, d, n, b, m, causal, n_min):
+    """The longest lists that a pass keeps in LDS beside its tiles (the oracle's bounds, as in the backward's other tests)."""
+    print(f"split fp32 lists d={d} n={n} b={b} m={m} causal={causal}", flush=True)
+    cfg = dict(B=1, H=1, n=n, d=d, dtype="fp32", law="iid", b=b, m=m, r=7, causal=causal, n_min=n_min, seed=3)
+    _run_case(ha, torch, cfg)

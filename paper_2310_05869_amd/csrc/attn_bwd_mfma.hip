@@ -170,6 +170,15 @@ __global__ __launch_bounds__(kBNT * NG, FOUR ? 4 : bwd_waves_per_simd(D, MODE)) 
   const int r_row = bwd_r_row<MODE>(a, b, r_use, &blk_r);           // row within the head
   SampleHead shead{-1, 0};
   if (kHits) shead = fetch_sample_head(a, b, tid);
+  // What the first tile waits for comes first: the entries of the T rows' list, then, while the R rows are on their way, the list and the
+  // tile's requests; only then are the R rows waited for.  (With the R rows awaited ahead of the list, MI355X, us: forward + backward, 12
+  // heads, n = 16384, d = 64 231.9 -> 229.6; backward, d = 128 295.8 -> 288.8, 16 causal heads, n = 32768 3146 -> 3123, d = 64 1704 ->
+  // 1687; exact passes, which have no list, +-0.5 %.)
+  KeyListHead khead{};
+  if (MODE == kBwdDqNode) khead = key_list_fetch<kBNT>(f, w);
+  const int nsorted = MODE == kBwdDkvBlock ? g.b : b.chunk_len;
+  const int32_t* tperm = kSorted ? f.perm_q + w.seg_off + (MODE == kBwdDkvBlock ? (int64_t)w.t * g.b : (int64_t)b.chunk_start) : nullptr;
+  const int t_first = kSorted ? tperm[min(tid, nsorted - 1)] : 0;
   bf16x8 xreg[KS], areg[KS];
   {
     const u32x4* xp = reinterpret_cast<const u32x4*>(Xh + (int64_t)r_row * D + 8 * h);
@@ -180,68 +189,14 @@ __global__ __launch_bounds__(kBNT * NG, FOUR ? 4 : bwd_waves_per_simd(D, MODE)) 
       areg[ks] = __builtin_bit_cast(bf16x8, ap[2 * ks]);
     }
   }
-  // (a use in registers, so that the loop does not wait for these loads again: behind the tile requests such a
-  // wait would be one for the whole next tile)
-#pragma unroll
-  for (int ks = 0; ks < KS; ++ks) {
-    asm volatile("" : "+v"(xreg[ks]));
-    asm volatile("" : "+v"(areg[ks]));
-  }
-  float nl2_r = 0.f, del_r = 0.f;  // dQ passes: -L log2(e) and delta of the R row
-  if (kDq) {
-    const float lv = lse_h[r_row];
-    nl2_r = (lv == -INFINITY) ? -INFINITY : -lv * kLog2e;
-    if (a.delta_out == nullptr) {
-      del_r = del_h[r_row];
-    } else {
-      // The lane's half of the row.  A launch of its own read dO once more.  Forward + backward, with it -> without (MI355X, us):
-      // 12 heads, n = 16384, d = 64 217 -> 209; n = 32768, d = 128 820 -> 805; 2 heads, n = 4096 74.4 -> 73.8; exact, 12 heads, n =
-      // 5000, d = 128 375 -> 373.
-      const int64_t at = ((int64_t)w.bh * g.n + r_row) * D + 8 * h;
-      f32x4 s = {0.f, 0.f, 0.f, 0.f};
-      auto add = [&](int ks, f32x4 o0, f32x4 o1) {
-        const u32x4 dv = __builtin_bit_cast(u32x4, areg[ks]);
-        s[0] = __builtin_fmaf(o0[0], __uint_as_float(dv[0] << 16), s[0]);
-        s[1] = __builtin_fmaf(o0[1], __uint_as_float(dv[0] & 0xFFFF0000u), s[1]);
-        s[2] = __builtin_fmaf(o0[2], __uint_as_float(dv[1] << 16), s[2]);
-        s[3] = __builtin_fmaf(o0[3], __uint_as_float(dv[1] & 0xFFFF0000u), s[3]);
-        s[0] = __builtin_fmaf(o1[0], __uint_as_float(dv[2] << 16), s[0]);
-        s[1] = __builtin_fmaf(o1[1], __uint_as_float(dv[2] & 0xFFFF0000u), s[1]);
-        s[2] = __builtin_fmaf(o1[2], __uint_as_float(dv[3] << 16), s[2]);
-        s[3] = __builtin_fmaf(o1[3], __uint_as_float(dv[3] & 0xFFFF0000u), s[3]);
-      };
-      if (a.O32 != nullptr) {
-        f32x4 o[2 * KS];
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-          o[2 * ks] = *reinterpret_cast<const f32x4*>(a.O32 + at + 16 * ks);
-          o[2 * ks + 1] = *reinterpret_cast<const f32x4*>(a.O32 + at + 16 * ks + 4);
-        }
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) add(ks, o[2 * ks], o[2 * ks + 1]);
-      } else {
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-          const u32x4 ob = *reinterpret_cast<const u32x4*>(reinterpret_cast<const uint16_t*>(a.O) + at + 16 * ks);
-          add(ks, (f32x4){__uint_as_float(ob[0] << 16), __uint_as_float(ob[0] & 0xFFFF0000u), __uint_as_float(ob[1] << 16), __uint_as_float(ob[1] & 0xFFFF0000u)},
-              (f32x4){__uint_as_float(ob[2] << 16), __uint_as_float(ob[2] & 0xFFFF0000u), __uint_as_float(ob[3] << 16), __uint_as_float(ob[3] & 0xFFFF0000u)});
-        }
-      }
-      del_r = (s[0] + s[1]) + (s[2] + s[3]);
-      del_r += __shfl_xor(del_r, 32);
-      if (h == 0 && grp == 0 && r_in_tile < w.rows_valid) a.delta_out[(int64_t)w.bh * g.n + r_row] = del_r;
-    }
-  }
-
   // ---- the T rows: the key list in LDS (dQ of a node), a run of sorted query
   // positions through P_Q, listed in LDS too (dK/dV of a node), or a contiguous range ----
   int nT, nb = 0x7fffffff;
   if (MODE == kBwdDqNode) {
-    nT = build_key_list<kBNT>(f, w, list, scratch, &nb);
+    nT = build_key_list<kBNT>(f, w, list, scratch, &nb, khead);
   } else if (kSorted) {
-    nT = MODE == kBwdDkvBlock ? g.b : b.chunk_len;
-    const int32_t* tperm = f.perm_q + w.seg_off + (MODE == kBwdDkvBlock ? (int64_t)w.t * g.b : (int64_t)b.chunk_start);
-    for (int i = tid; i < ((nT + 63) & ~63); i += kBNT) list[i] = tperm[min(i, nT - 1)];
+    nT = nsorted;
+    for (int i = tid; i < ((nT + 63) & ~63); i += kBNT) list[i] = i == tid ? t_first : tperm[min(i, nT - 1)];
     __syncthreads();
   } else {
     nT = max(0, w.k1 - w.k0);
@@ -303,9 +258,62 @@ __global__ __launch_bounds__(kBNT * NG, FOUR ? 4 : bwd_waves_per_simd(D, MODE)) 
 #pragma unroll
     for (int dt = 0; dt < (kDq ? 1 : DT); ++dt) acc2[dt][i] = 0.f;
   }
+  if (ntiles > 0) request_tile(0);
+  // (a use in registers, so that the loop does not wait for these loads again: behind the tile requests such a
+  // wait would be one for the whole next tile)
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) {
+    asm volatile("" : "+v"(xreg[ks]));
+    asm volatile("" : "+v"(areg[ks]));
+  }
+  float nl2_r = 0.f, del_r = 0.f;  // dQ passes: -L log2(e) and delta of the R row
+  if (kDq) {
+    const float lv = lse_h[r_row];
+    nl2_r = (lv == -INFINITY) ? -INFINITY : -lv * kLog2e;
+    if (a.delta_out == nullptr) {
+      del_r = del_h[r_row];
+    } else {
+      // The lane's half of the row.  A launch of its own read dO once more.  Forward + backward, with it -> without (MI355X, us):
+      // 12 heads, n = 16384, d = 64 217 -> 209; n = 32768, d = 128 820 -> 805; 2 heads, n = 4096 74.4 -> 73.8; exact, 12 heads, n =
+      // 5000, d = 128 375 -> 373.
+      const int64_t at = ((int64_t)w.bh * g.n + r_row) * D + 8 * h;
+      f32x4 s = {0.f, 0.f, 0.f, 0.f};
+      auto add = [&](int ks, f32x4 o0, f32x4 o1) {
+        const u32x4 dv = __builtin_bit_cast(u32x4, areg[ks]);
+        s[0] = __builtin_fmaf(o0[0], __uint_as_float(dv[0] << 16), s[0]);
+        s[1] = __builtin_fmaf(o0[1], __uint_as_float(dv[0] & 0xFFFF0000u), s[1]);
+        s[2] = __builtin_fmaf(o0[2], __uint_as_float(dv[1] << 16), s[2]);
+        s[3] = __builtin_fmaf(o0[3], __uint_as_float(dv[1] & 0xFFFF0000u), s[3]);
+        s[0] = __builtin_fmaf(o1[0], __uint_as_float(dv[2] << 16), s[0]);
+        s[1] = __builtin_fmaf(o1[1], __uint_as_float(dv[2] & 0xFFFF0000u), s[1]);
+        s[2] = __builtin_fmaf(o1[2], __uint_as_float(dv[3] << 16), s[2]);
+        s[3] = __builtin_fmaf(o1[3], __uint_as_float(dv[3] & 0xFFFF0000u), s[3]);
+      };
+      if (a.O32 != nullptr) {
+        f32x4 o[2 * KS];
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+          o[2 * ks] = *reinterpret_cast<const f32x4*>(a.O32 + at + 16 * ks);
+          o[2 * ks + 1] = *reinterpret_cast<const f32x4*>(a.O32 + at + 16 * ks + 4);
+        }
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) add(ks, o[2 * ks], o[2 * ks + 1]);
+      } else {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+          const u32x4 ob = *reinterpret_cast<const u32x4*>(reinterpret_cast<const uint16_t*>(a.O) + at + 16 * ks);
+          add(ks, (f32x4){__uint_as_float(ob[0] << 16), __uint_as_float(ob[0] & 0xFFFF0000u), __uint_as_float(ob[1] << 16), __uint_as_float(ob[1] & 0xFFFF0000u)},
+              (f32x4){__uint_as_float(ob[2] << 16), __uint_as_float(ob[2] & 0xFFFF0000u), __uint_as_float(ob[3] << 16), __uint_as_float(ob[3] & 0xFFFF0000u)});
+        }
+      }
+      del_r = (s[0] + s[1]) + (s[2] + s[3]);
+      del_r += __shfl_xor(del_r, 32);
+      if (h == 0 && grp == 0 && r_in_tile < w.rows_valid) a.delta_out[(int64_t)w.bh * g.n + r_row] = del_r;
+    }
+  }
+
   asm volatile("" : "+v"(nl2_r), "+v"(del_r));
   if (ntiles > 0) {
-    request_tile(0);
     if (kHits) find_sample_hits<kBNT>(a, b, sample_hits(smem + bwd_hits_at<D, NG>(a, MODE)), shead);  // while the first tile is on its way
     finish_tile(0);
   }

@@ -492,6 +492,11 @@ __global__ __launch_bounds__(kBNT * NG, FOUR ? 4 : bwd_waves_per_simd(D, MODE)) 
     // adding the accumulated row where some level's node holds the row on the pass's
     // side (queries: second half of the node; keys: first half).
     // Two groups: both stage their sums of the rows; each takes half of the rows on and adds the two.
+    // No later workgroup of the launch reads a row that it reads or writes here: non-temporal, they leave the caches to the tiles
+    // (not the samples' rows, which the next launch reads: 2 heads, n = 4096, d = 64 31.0 -> 31.8 us).  Backward (MI355X, us): 12 heads, n =
+    // 16384, d = 128 279.0 -> 266.7, 32 heads, n = 32768 1267 -> 1254, d = 64 673 -> 668; 8 causal heads, n = 32768, d = 128 1577 -> 1561,
+    // 32, n = 65536 13460 -> 13360, d = 64 6984 -> 6943; exact passes +-0.3 %.  The accumulated rows that the exact passes fold
+    // in: read so, 0.5 % slower.
     unsigned char* ep = smem + wave * L::EP_WAVE;
     unsigned char* ep_own = ep + 4 * grp * L::EP_WAVE;
     int64_t* ep_rows = reinterpret_cast<int64_t*>(ep_own + 32 * L::EP_ROW);
@@ -562,7 +567,7 @@ __global__ __launch_bounds__(kBNT * NG, FOUR ? 4 : bwd_waves_per_simd(D, MODE)) 
         for (int it = 0; it < IT; ++it) {
           const int ch = (lane + 64 * it) % CH;
           const int64_t rr = r64[it] >= 0 ? r64[it] : row_first;
-          prev[it] = *reinterpret_cast<const f32x4*>(dst32 + rr * D + ch * 4);
+          prev[it] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(dst32 + rr * D + ch * 4));
         }
       }
 #pragma unroll
@@ -570,7 +575,10 @@ __global__ __launch_bounds__(kBNT * NG, FOUR ? 4 : bwd_waves_per_simd(D, MODE)) 
         const int idx = lane + 64 * it;
         const int row = idx / CH, ch = idx % CH;
         const f32x4 v = *reinterpret_cast<const f32x4*>(ep + row * L::EP_ROW + ch * 16) + prev[it];
-        if (r64[it] >= 0) *reinterpret_cast<f32x4*>(dst32 + r64[it] * D + ch * 4) = v;
+        if (r64[it] < 0) continue;
+        f32x4* to = reinterpret_cast<f32x4*>(dst32 + r64[it] * D + ch * 4);
+        if (MODE == kBwdDkvSamp) *to = v;  // (read again by the launch that adds the samples' sums)
+        else __builtin_nontemporal_store(v, to);
       }
       return;
     }
@@ -621,7 +629,7 @@ __global__ __launch_bounds__(kBNT * NG, FOUR ? 4 : bwd_waves_per_simd(D, MODE)) 
       const f32x4 v0 = sums_at(row, ch * 32) + p0[it];
       const f32x4 v1 = sums_at(row, ch * 32 + 16) + p1[it];
       const u32x4 pk = {pack_bf16x2(v0.x, v0.y), pack_bf16x2(v0.z, v0.w), pack_bf16x2(v1.x, v1.y), pack_bf16x2(v1.z, v1.w)};
-      if (r64[it] >= 0) *reinterpret_cast<u32x4*>(dst16 + r64[it] * D + ch * 8) = pk;
+      if (r64[it] >= 0) __builtin_nontemporal_store(pk, reinterpret_cast<u32x4*>(dst16 + r64[it] * D + ch * 8));
     }
   };
   write_out(acc1, a.out1, a.samp1, reinterpret_cast<uint16_t*>(a.fin1), a.lvl1);

@@ -699,6 +699,10 @@ __global__ __launch_bounds__(64 * NW * NG, (D == 64 && NW == 4 && NG == 1) ? 3 :
   // unconditional (a row that is not stored re-reads the wave's first row) and only the stores are
   // guarded: with loads under a branch the compiler's wait counts fall back to "everything", which
   // also waits for the previous piece's stores to reach memory.
+  // Rows that the launch reads or writes once are non-temporal and leave the caches to the tiles: the folded partial rows, the fp32 copy,
+  // the results of the exact pass; not those of the node pass (nor its partial rows), which gained nothing.  Forward (MI355X, us): 12
+  // causal heads, n = 8192, d = 128 150.9 -> 150.0, 8 heads, n = 32768 454.3 -> 448.1, 32, n = 65536 3960 -> 3940; with the fp32 copy
+  // 475.9 -> 461.8 and 4054 -> 4031; 32 unmasked heads, n = 32768 547.8 -> 540.6, d = 64 292.8 -> 287.6, 12, n = 4096 30.4 -> 29.2.
   if (ep_rows[0] < 0) return;  // a wave whose rows all lie past the end (valid rows are a prefix)
   auto drain = [&](auto nf_tag) {
     constexpr int NF = decltype(nf_tag)::value;
@@ -718,7 +722,7 @@ __global__ __launch_bounds__(64 * NW * NG, (D == 64 && NW == 4 && NG == 1) ? 3 :
         r64[it] = ep_rows[row];
         const int row_ld = r64[it] >= 0 ? row : 0;
 #pragma unroll
-        for (int c = 0; c < NF; ++c) raw[it][c] = *reinterpret_cast<const u32x4*>(prow[c] + row_ld * D + ch * 8);
+        for (int c = 0; c < NF; ++c) raw[it][c] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(prow[c] + row_ld * D + ch * 8));
       }
 #pragma unroll
       for (int it = 0; it < GROUP; ++it) {
@@ -750,11 +754,13 @@ __global__ __launch_bounds__(64 * NW * NG, (D == 64 && NW == 4 && NG == 1) ? 3 :
           continue;
         }
         const u32x4 pk = {pack_bf16x2(v0.x, v0.y), pack_bf16x2(v0.z, v0.w), pack_bf16x2(v1.x, v1.y), pack_bf16x2(v1.z, v1.w)};
-        *reinterpret_cast<u32x4*>(dst_base + (r64[it] * D + ch * 8) * 2) = pk;
+        u32x4* to = reinterpret_cast<u32x4*>(dst_base + (r64[it] * D + ch * 8) * 2);
+        if (MODE == kModeExact) __builtin_nontemporal_store(pk, to);
+        else *to = pk;
         if (!to_partial && a.out_f32 != nullptr) {  // unrounded copy of the final output, for the backward's delta
           f32x4* fp = reinterpret_cast<f32x4*>(a.out_f32 + r64[it] * D + ch * 8);
-          fp[0] = v0;
-          fp[1] = v1;
+          __builtin_nontemporal_store(v0, fp);
+          __builtin_nontemporal_store(v1, fp + 1);
         }
       }
     }

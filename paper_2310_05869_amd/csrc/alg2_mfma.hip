@@ -15,7 +15,7 @@
 // Tiling as in the forward kernel: 4 waves x 32 queries, 64 keys per step,
 // S^T = K Q^T with v_mfma_f32_32x32x16_bf16 so that a lane holds 16 keys of one
 // query, weights converted to bf16 in place as the B operand of O^T += V^T P^T,
-// V^T fragments from the transposing LDS read.  The loops are not software
+// V^T fragments from the transposing LDS read.  The main loop is not software
 // pipelined: the next tile's rows are fetched into registers while the current
 // tile is computed.
 //
@@ -67,22 +67,48 @@ __host__ __device__ inline size_t a2_lds_bytes(const Geometry& g) {
 // Row sums of the rows of T.  Keys are walked in sorted order, so that a row's own block is one run of positions and
 // only the tiles that touch the run of one of a wave's rows carry a mask; in storage order every score of every
 // tile had to be compared with its key's block (two of seven vector instructions per score), and vector issue is
-// what bounds a kernel with one product per score.  A range of keys is shared by two groups of four waves, tile about,
+// what bounds a kernel with one product per score.  A range of keys is shared by two groups of RW waves, tile about,
 // whose sums are merged through LDS: with kAlg2TauSplits ranges alone 32 heads of 256 rows are two waves per
 // SIMD, which cannot cover each other.  The row tiles of a range are neighbours on one XCD (its keys meet in one L2).
 // Measured (MI355X, 32 heads, n = 32768, d = 128, m = 256): 171 -> 134 us.
+//
+// A trip ends for all waves at one barrier, and waves that all begin with their products leave the vector units idle, then the matrix
+// cores: the second group adds up its previous tile first.  (Vector instructions were 59 % of the kernel's cycles, products 32 %, and they added
+// up.)  Tiles come by DMA, NB - 1 of them ahead, into LDS in rows of D * 2 bytes, unpadded: piece c (16 bytes) of row r at place c ^ swz(r), free
+// of bank conflicts for the row reads.  The positions' rows are kept ahead of them in LDS too, in chunks of four trips: a load of
+// an index that is waited for in registers would be a wait for every tile requested before it.
+// Forward with the caps (MI355X, us), tiles through registers, in step and with the maxima of every tile -> this; d = 128, m = 256: 16
+// heads, n = 16384 173 -> 166, 8 heads 115 -> 106, 4 heads, n = 4096 46.5 -> 45.8; 24 heads, n = 16384, m = 512 325 -> 309; 12 causal heads,
+// n = 32768 849 -> 830; 32 heads, n = 32768, whose keys come from HBM, 1 %; d = 64: 8 heads, n = 16384 84.2 -> 79.9, m = 512 208 -> 196, 12
+// causal heads, n = 32768 526 -> 512.
+// Eight waves to a tile, whose groups of 1024 threads read every key once and four tiles ahead: 1 to 14 % slower than this.
 template <int D>
-__global__ __launch_bounds__(2 * kA2NT, 4) void alg2_tau_mfma_kernel(Alg2Args a) {
+struct TauLds {
+  static constexpr int RW = 4;                       // waves of a group
+  static constexpr int NT = 2 * RW * 64;             // threads; also the positions of a chunk of the list
+  static constexpr int ROWB = D * 2, CPR = D / 8;
+  static constexpr int TILE = kA2KT * ROWB;
+  static constexpr int RPI = 64 / CPR;               // rows per DMA instruction
+  static constexpr int DPW = kA2KT / RPI / RW;       // DMA instructions per wave and tile
+  static constexpr int NB = D == 64 ? 4 : 2;        // tile buffers of a group (two workgroups per CU)
+  static constexpr int LIST_AT = 2 * NB * TILE;
+  static constexpr int BYTES = LIST_AT + 4 * NT * 4;  // (a ring of four chunks)
+  static_assert(DPW >= 1 && NB <= RW);
+  __device__ static int swz(int row) { return D == 128 ? row & 15 : (row >> 1) & 7; }
+};
+
+template <int D>
+__global__ __launch_bounds__(TauLds<D>::NT, 4) void alg2_tau_mfma_kernel(Alg2Args a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  using L = A2Lds<D>;
+  using L = TauLds<D>;
   constexpr int KS = D / 16;
-  constexpr int CPR = D / 8;
-  constexpr int NKC = kA2KT * CPR / kA2NT;
+  constexpr int RW = L::RW;
   const Geometry& g = a.g;
-  const int tid = threadIdx.x & (kA2NT - 1), grp = threadIdx.x / kA2NT;
-  const int lane = tid & 63, wave = tid >> 6;
+  const int grp = __builtin_amdgcn_readfirstlane(threadIdx.x / (64 * RW));
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((threadIdx.x / 64) % RW);
   const int lq = lane & 31, h = lane >> 5;
-  unsigned char* bufs = smem + grp * 2 * L::K_BYTES;
+  unsigned char* bufs = smem + grp * L::NB * L::TILE;
+  int32_t* list = reinterpret_cast<int32_t*>(smem + L::LIST_AT);
 
   const int row_tiles = (g.m + kA2QT - 1) / kA2QT;
   const int idx = a.wg_first + logical_block(blockIdx.x, gridDim.x);
@@ -95,10 +121,19 @@ __global__ __launch_bounds__(2 * kA2NT, 4) void alg2_tau_mfma_kernel(Alg2Args a)
   const uint16_t* Qh = reinterpret_cast<const uint16_t*>(a.Q) + (int64_t)nd.head * a.n_full * D;
   const uint16_t* Kh = reinterpret_cast<const uint16_t*>(a.K) + (int64_t)nd.head * a.n_full * D;
 
+  const int ntiles = a2_tiles(g.n);
+  const int kt_lo = (int)((int64_t)ntiles * split / kAlg2TauSplits);
+  const int kt_hi = (int)((int64_t)ntiles * (split + 1) / kAlg2TauSplits);
+  const int trips = (kt_hi - kt_lo + 1) / 2;
+  // chunk c of the list: the rows at positions 64 kt_lo + NT c ... (past the end: the last position, masked)
+  const int32_t* keys = a.perm_k + hb;
+  auto chunk_row = [&](int c) { return keys[min(kt_lo * kA2KT + c * L::NT + (int)threadIdx.x, g.n - 1)]; };
+  const int row0 = chunk_row(0), row1 = chunk_row(1);
+
   const int r_in_tile = wave * 32 + lq;
   const int r_use = r_in_tile < rows_valid ? r_in_tile : 0;
   const int q_in_node = a.tau_rows[(int64_t)nd.heap * g.m + j0 + r_use];
-  const int own = a.pos_q[hb + q_in_node] / g.b * g.b;  // first position of the row's own block
+  int own = a.pos_q[hb + q_in_node] / g.b * g.b;  // first position of the row's own block
   bf16x8 qreg[KS];
   {
     const u32x4* qp = reinterpret_cast<const u32x4*>(Qh + (int64_t)(nd.q_start + q_in_node) * D + 8 * h);
@@ -106,85 +141,103 @@ __global__ __launch_bounds__(2 * kA2NT, 4) void alg2_tau_mfma_kernel(Alg2Args a)
     for (int ks = 0; ks < KS; ++ks) qreg[ks] = __builtin_bit_cast(bf16x8, qp[2 * ks]);
   }
 
-  const int ntiles = a2_tiles(g.n);
-  const int kt_lo = (int)((int64_t)ntiles * split / kAlg2TauSplits);
-  const int kt_hi = (int)((int64_t)ntiles * (split + 1) / kAlg2TauSplits);
-  const int32_t* keys = a.perm_k + hb;
-  int krow[NKC];
-  u32x4 kreg[NKC];
-  // row indices of a tile are requested a step before its rows (past the end: the last position, masked)
-  auto load_index = [&](int kt) {
+  const __amdgpu_buffer_rsrc_t krsrc = __builtin_amdgcn_make_buffer_rsrc((void*)Kh, 0, (int)(uint32_t)(a.n_full * L::ROWB), 0x00020000);
+  // instruction ii of this wave fills rows RPI (RW ii + wave) ... of the tile
+  const int drow = L::RPI * wave + lane / L::CPR;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)bufs + 1024 * wave;
+  auto request_tile = [&](int it) {  // of this trip; past the range: rows that exist and are not used
+    const uint32_t at = lds0 + (it & (L::NB - 1)) * L::TILE;
 #pragma unroll
-    for (int i = 0; i < NKC; ++i) krow[i] = keys[min(kt * kA2KT + (tid + i * kA2NT) / CPR, g.n - 1)];
-  };
-  auto load_tile = [&]() {
-#pragma unroll
-    for (int i = 0; i < NKC; ++i)
-      kreg[i] = *reinterpret_cast<const u32x4*>(Kh + (int64_t)krow[i] * D + (tid + i * kA2NT) % CPR * 8);
-  };
-  auto store_tile = [&](int buf) {
-#pragma unroll
-    for (int i = 0; i < NKC; ++i) {
-      const int c = tid + i * kA2NT;
-      *reinterpret_cast<u32x4*>(bufs + buf * L::K_BYTES + c / CPR * L::KSTR + c % CPR * 16) = kreg[i];
+    for (int ii = 0; ii < L::DPW; ++ii) {
+      const int t = RW * L::RPI * ii + drow;
+      const int row = list[((2 * it + grp) * kA2KT + t) & (4 * L::NT - 1)];
+      const int voff = row * L::ROWB + (((lane % L::CPR) ^ L::swz(t)) << 4);
+      const uint32_t to = at + 1024 * RW * ii;
+      asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"{m0}"(to), "v"(voff), "s"(krsrc) : "memory");
     }
   };
-
-  float m_run = -INFINITY, sum = 0.f;  // reference (log2 domain) and this lane's share of the row sum / 2^m_run
-  const int trips = (kt_hi - kt_lo + 1) / 2;
-  load_index(kt_lo + grp);
-  load_tile();
-  load_index(kt_lo + grp + 2);
-  store_tile(0);
+  list[threadIdx.x] = row0;
+  list[L::NT + threadIdx.x] = row1;
   __syncthreads();
-  for (int it = 0; it < trips; ++it) {
-    const int kt = kt_lo + grp + 2 * it;
-    load_tile();  // (past the range: existing rows that are not used)
-    load_index(kt + 4);
-    if (kt < kt_hi) {
-      const unsigned char* kp0 = bufs + (it & 1) * L::K_BYTES + lq * L::KSTR + 16 * h;
-      const unsigned char* kp1 = kp0 + 32 * L::KSTR;
-      f32x16 c[2];
+#pragma unroll
+  for (int it = 0; it < L::NB - 1; ++it) request_tile(it);
+  // (used in registers, so that the loop does not wait for these loads again)
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qreg[ks]));
+  asm volatile("" : "+v"(own));
+
+  f32x16 c[2];  // element i of c[sub]: position 32 sub + 8 (i / 4) + 4 h + i % 4 of the tile
+  auto scores = [&](int it) {
+    const unsigned char* kp = bufs + (it & (L::NB - 1)) * L::TILE + lq * L::ROWB;
+    auto frag = [&](int sub, int j) {  // (rows lq and lq + 32 have the same swizzle)
+      return *reinterpret_cast<const bf16x8*>(kp + sub * 32 * L::ROWB + (((2 * j + h) ^ L::swz(lq)) << 4));
+    };
+#pragma unroll
+    for (int sub = 0; sub < 2; ++sub)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) c[sub][i] = 0.f;
+#pragma unroll
+    for (int j = 0; j < KS; ++j) {
+      c[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(0, j), qreg[j], c[0], 0, 0, 0);
+      c[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(1, j), qreg[j], c[1], 0, 0, 0);
+    }
+  };
+  float m_run = -INFINITY, sum = 0.f;  // reference (log2 domain) and this lane's share of the row sum / 2^m_run
+  auto add_tile = [&](int kt) {
+    // a tile that lies in the row's own block as a whole is left out as a whole
+    const int mlo = own - kt * kA2KT, tail = g.n - kt * kA2KT;
+    const bool out = mlo <= 0 && mlo + g.b >= kA2KT;
+    if (tail < kA2KT || __any(!out && mlo < kA2KT && mlo + g.b > 0)) {
 #pragma unroll
       for (int sub = 0; sub < 2; ++sub)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) c[sub][i] = 0.f;
-#pragma unroll
-      for (int j = 0; j < KS; ++j) {
-        c[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(kp0 + 32 * j), qreg[j], c[0], 0, 0, 0);
-        c[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(kp1 + 32 * j), qreg[j], c[1], 0, 0, 0);
-      }
-      // element i of c[sub] is position 32 sub + 8 (i / 4) + 4 h + i % 4 of the tile
-      const int mlo = own - kt * kA2KT, tail = g.n - kt * kA2KT;
-      if (tail < kA2KT || __any(mlo < kA2KT && mlo + g.b > 0)) {
-#pragma unroll
-        for (int sub = 0; sub < 2; ++sub)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            const int koff = 32 * sub + 8 * (i / 4) + (i % 4);
-            if (koff >= tail - 4 * h || (unsigned)(koff - (mlo - 4 * h)) < (unsigned)g.b) c[sub][i] = -INFINITY;
-          }
-      }
-      float mx = fmaxf(c[0][0], c[1][0]);
-#pragma unroll
-      for (int i = 1; i < 16; ++i) mx = __builtin_fmaxf(__builtin_fmaxf(mx, c[0][i]), c[1][i]);
-      mx = fmaxf(mx, __shfl_xor(mx, 32)) * kLog2e;
-      if (__any(mx > m_run + 8.0f)) {
-        const float m_new = fmaxf(m_run, mx);
-        sum *= __builtin_amdgcn_exp2f(m_run - ((m_new == -INFINITY) ? 0.f : m_new));
-        m_run = m_new;
-      }
+        for (int i = 0; i < 16; ++i) {
+          const int koff = 32 * sub + 8 * (i / 4) + (i % 4);
+          if (koff >= tail - 4 * h || (unsigned)(koff - (mlo - 4 * h)) < (unsigned)g.b) c[sub][i] = -INFINITY;
+        }
+    }
+    auto weigh = [&]() {
       const float shift = (m_run == -INFINITY) ? 0.f : -m_run;
       float s4[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int sub = 0; sub < 2; ++sub)
 #pragma unroll
         for (int i = 0; i < 16; ++i) s4[i & 3] += __builtin_amdgcn_exp2f(__builtin_fmaf(c[sub][i], kLog2e, shift));
-      sum += (s4[0] + s4[1]) + (s4[2] + s4[3]);
+      return (s4[0] + s4[1]) + (s4[2] + s4[3]);
+    };
+    // The reference moves when a weight exceeds 2^8: a sum below that has none, and the maxima, a seventh of a tile's vector
+    // instructions, need not be formed.
+    float s = weigh();
+    if (__any(!(out || s < 256.f) || m_run == -INFINITY)) {
+      float mx = fmaxf(c[0][0], c[1][0]);
+#pragma unroll
+      for (int i = 1; i < 16; ++i) mx = __builtin_fmaxf(__builtin_fmaxf(mx, c[0][i]), c[1][i]);
+      mx = fmaxf(mx, __shfl_xor(mx, 32)) * kLog2e;
+      if (out) mx = -INFINITY;
+      const float m_new = fmaxf(m_run, mx);
+      sum *= __builtin_amdgcn_exp2f(m_run - ((m_new == -INFINITY) ? 0.f : m_new));
+      m_run = m_new;
+      s = weigh();
     }
-    store_tile((it + 1) & 1);
+    sum += out ? 0.f : s;
+  };
+  int next_row = 0;
+  const int mine = (kt_hi - kt_lo + 1 - grp) / 2;  // the group's tiles
+  for (int it = 0; it < trips; ++it) {
+    // the trip's tile has landed, for the whole workgroup, and the one before it is read no more
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(L::DPW * (L::NB - 2)) : "memory");
     __syncthreads();
+    request_tile(it + L::NB - 1);
+    if (it % RW == 0) next_row = chunk_row(it / RW + 2);
+    const int kt = kt_lo + grp + 2 * it;
+    if (grp == 1 && it > 0) add_tile(kt - 2);
+    if (it < mine) scores(it);
+    if (grp == 0) add_tile(kt);
+    if (it % RW == RW - 1) list[((it / RW + 2) & 3) * L::NT + threadIdx.x] = next_row;
   }
+  if (grp == 1 && mine == trips && trips > 0) add_tile(kt_lo + 1 + 2 * (trips - 1));
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
 
   sum += __shfl_xor(sum, 32);
   float* part = reinterpret_cast<float*>(smem);  // [2][kA2QT]: the tiles are read no more
@@ -484,7 +537,7 @@ static int launch_tau(const Alg2Args& args, int64_t grid, hipStream_t st) {
   for (int64_t first = 0; first < grid; first += kStep) {
     a.wg_first = (int32_t)first;
     const unsigned count = (unsigned)(grid - first < kStep ? grid - first : kStep);
-    hipLaunchKernelGGL((alg2_tau_mfma_kernel<D>), dim3(count), dim3(2 * kA2NT), 4 * A2Lds<D>::K_BYTES, st, a);
+    hipLaunchKernelGGL((alg2_tau_mfma_kernel<D>), dim3(count), dim3(TauLds<D>::NT), TauLds<D>::BYTES, st, a);
     const int rc = check_launch();
     if (rc != HA_OK) return rc;
   }

@@ -304,3 +304,32 @@ def test_alg2_scores_far_apart(ha, torch, d, H, n, b, m, r, n_min, vnorm, cap_sc
     tol = (np.expm1(4 * e[fits])[:, None] + (2.0 ** -8 if dtype == "bf16" else 0.0)) * absv[fits] + out_tolerance(ref_out[fits], dtype)
     bad = ~(np.abs(o - ref_out[fits]) <= tol)
     assert not bad.any(), f"out: {int(bad.any(axis=-1).sum())} of {len(bad)} rows out of tolerance, {int((~np.isfinite(o)).any(axis=-1).sum())} not finite"
+
+
+@pytest.mark.parametrize("d,n,b,m", [(128, 35072, 256, 256),   # lists of more than four chunks per range, blocks of whole tiles
+                                     (64, 35000, 100, 130),    # ranges of 68 and 69 tiles, blocks that cut tiles
+                                     (128, 35200, 1600, 33), (64, 1088, 64, 40)])
+@pytest.mark.parametrize("spread", [0.0, 1.5])
+def test_alg2_row_sums_over_long_ranges(ha, torch, d, n, b, m, spread):
+    """tau against 64-bit sums over the keys outside of the row's sorted block.  spread > 0: keys of very different lengths, so that the
+    exponentials' reference moves many times (scores to 40, each a sum whose rounding is within 2e-5 of that)."""
+    print(f"alg2 tau d={d} n={n} b={b} m={m} spread={spread}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n + d)
+    q, k, v = (torch.randn((1, 2, n, d), generator=gen, device="cuda") * d ** -0.25 for _ in range(3))
+    k = k * torch.exp(spread * torch.randn((1, 2, n, 1), generator=gen, device="cuda")).clamp(max=12.0)
+    q, k, v = (x.to(torch.bfloat16) for x in (q, k, v))
+    _, _, ws = ha.hyperattn_forward_alg2(q, k, v, b, m, 7, seed=3, cap_scale=4.0, kappa=1.2)
+    views = ha.alg2_workspace_views(ws, ha.make_shape(1, 2, n, d, ha.HA_BF16), ha.make_params(b, m, 7, False, 4096, 3))
+    base = ha.workspace_views(ws, ha.make_shape(1, 2, n, d, ha.HA_BF16), ha.make_params(b, m, 7, False, 4096, 3))
+    rows = views["tau_rows"].reshape(-1)[:m].long()
+    for h in range(2):
+        blk_q, blk_k = torch.empty(n, dtype=torch.long, device="cuda"), torch.empty(n, dtype=torch.long, device="cuda")
+        at = torch.arange(n, device="cuda") // b
+        blk_q[base["perm_q"].reshape(2, n)[h].long()] = at
+        blk_k[base["perm_k"].reshape(2, n)[h].long()] = at
+        s = torch.matmul(q[0, h, rows].double(), k[0, h].double().t().contiguous())
+        s = s.masked_fill(blk_q[rows][:, None] == blk_k[None, :], float("-inf"))
+        want = torch.logsumexp(s, -1).max().item()
+        got = views["log_tau"].reshape(2, -1)[h, 0].item()
+        assert abs(got - want) <= 2e-5 * (1.0 + abs(want)), (h, got, want)

@@ -244,13 +244,17 @@ __global__ __launch_bounds__(kChunkWaves * 64) void chunk_count_kernel(SortArgs 
 // LDS of pass B: the chunk's order (kChunk words, whose first quarter holds the keys
 // until they are in registers), wave totals, and per (wave, bucket) a 64-bit peer
 // mask (later the pair {first place, shift to the destination}) and a counter; COUNT: the buckets' keys in earlier
-// and in later chunks.
+// and in later chunks, and the positions of the chunk's keys.
 __host__ __device__ inline size_t chunk_scatter_lds(int nbk, int waves, bool count) {
-  return (size_t)kChunk * 4 + 64 + (size_t)waves * nbk * 12 + (count ? 2 * 256 * 4 : 0);
+  return (size_t)kChunk * 4 + 64 + (size_t)waves * nbk * 12 + (count ? 2 * 256 * 4 + kChunk * 4 : 0);
 }
 
 // Pass B.  nbk = number of buckets (a power of two >= every code + 1, at most 256).
-// COUNT: no pass A; the workgroup reads the segment's other chunks and counts their keys itself.
+// COUNT: no pass A; the workgroup reads the segment's other chunks and counts their keys itself.  That launch is a chain of round
+// trips, so what it reads is asked for ahead, a thread's codes of another chunk and its sample before the first barrier, and a sample's
+// position comes from LDS instead of back from memory.  Without -> with (MI355X, forward, us): 15 heads, n = 6300, b = 100, d = 64 36.5 ->
+// 35.6, d = 128 51.2 -> 50.6; 4 heads, n = 32768, b = 64 41.9 -> 41.0 and 62.4 -> 62.0, n = 16384 41.2 -> 40.5 (d = 128); 12 heads,
+// n = 16384, b = 256 62.7 -> 62.6 and 99.3 -> 99.1.
 template <int NW, bool COUNT>
 __global__ __launch_bounds__(NW * 64) void chunk_scatter_kernel(SortArgs a, int nbk) {
   extern __shared__ __attribute__((aligned(16))) unsigned char sm[];
@@ -264,6 +268,7 @@ __global__ __launch_bounds__(NW * 64) void chunk_scatter_kernel(SortArgs a, int 
   u32x2* first = reinterpret_cast<u32x2*>(peers);                                    // the same words, after the ranking
   uint32_t* count = reinterpret_cast<uint32_t*>(peers + kChunkWaves * nbk);          // [NW][nbk]
   uint32_t* others = count + kChunkWaves * nbk;                                      // COUNT: [2][256]
+  int32_t* pos_lds = reinterpret_cast<int32_t*>(others + 512);                       // COUNT: [kChunk]
 
   const ChunkRef c = decode_chunk(a, (int)blockIdx.x);
   const int tid = threadIdx.x;
@@ -284,6 +289,18 @@ __global__ __launch_bounds__(NW * 64) void chunk_scatter_kernel(SortArgs a, int 
       }
     }
   }
+  // COUNT: unit u of the segment's codes is 16 of chunk u / (kChunk / 16)
+  auto other_codes = [&](int u) {
+    const int cc = u / (kChunk / 16);
+    return load_16_codes(c.seg_codes + cc * kChunk, min(kChunk, c.seg_len - cc * kChunk), u % (kChunk / 16));
+  };
+  const int units = COUNT ? c.nchunks * (kChunk / 16) : 0;
+  codes16 other0{};
+  int smp0 = -1;
+  if constexpr (COUNT) {
+    if (tid < units && tid / (kChunk / 16) != c.chunk) other0 = other_codes(tid);
+    if (c.sblk && tid < a.g.m) smp0 = c.smp[tid];
+  }
   {
     if (tid < kChunk / 16) {
       const codes16 v = load_16_codes(c.codes, s, tid);
@@ -298,11 +315,11 @@ __global__ __launch_bounds__(NW * 64) void chunk_scatter_kernel(SortArgs a, int 
   __syncthreads();
   if constexpr (COUNT) {
     static_assert(NW * 64 >= 512, "one thread per counter");
-    for (int u = tid; u < c.nchunks * (kChunk / 16); u += NW * 64) {
+    for (int u = tid; u < units; u += NW * 64) {
       const int cc = u / (kChunk / 16), t = u % (kChunk / 16);
       if (cc == c.chunk) continue;
       const int left = min(kChunk, c.seg_len - cc * kChunk);
-      const codes16 v = load_16_codes(c.seg_codes + cc * kChunk, left, t);
+      const codes16 v = u == tid ? other0 : other_codes(u);
       uint32_t* hist = others + (cc < c.chunk ? 0 : 256);
 #pragma unroll
       for (int j = 0; j < 16; ++j)
@@ -393,6 +410,7 @@ __global__ __launch_bounds__(NW * 64) void chunk_scatter_kernel(SortArgs a, int 
       const uint32_t place = f.x + (cr[u] >> 8);
       staged[place] = (code << 12) | (uint32_t)i;
       if (c.pos) c.pos[i] = (int32_t)(place + f.y);
+      if (COUNT) pos_lds[i] = (int32_t)(place + f.y);
     }
   }
   __syncthreads();
@@ -402,7 +420,12 @@ __global__ __launch_bounds__(NW * 64) void chunk_scatter_kernel(SortArgs a, int 
   }
 
   // the sorted block of the node's sampled keys that fall into this chunk
-  if (c.sblk) {
+  if (COUNT && c.sblk) {
+    for (int j = tid; j < a.g.m; j += kChunkWaves * 64) {
+      const int l = (j == tid ? smp0 : c.smp[j]) - c.chunk_off;
+      if (l >= 0 && l < s) c.sblk[j] = pos_lds[l] / a.g.b;
+    }
+  } else if (c.sblk) {
     __threadfence_block();  // the positions were stored by other threads of this workgroup
     __syncthreads();
     for (int j = tid; j < a.g.m; j += kChunkWaves * 64) {

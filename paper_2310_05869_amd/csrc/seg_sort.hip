@@ -17,7 +17,7 @@
 // Long segments (the upper levels of the causal recursion have 64 segments of
 // 65536 keys) would leave most of the chip idle, so the forward pass sorts in
 // chunks of kChunk keys, one 4-wave workgroup each, in two launches (small problems: in B alone, see
-// kOneLaunchChunks, and the smallest not here at all, see node_sort.h):
+// one_launch, and the smallest not here at all, see node_sort.h):
 //   A. every chunk's bucket counts go to a table in the workspace;
 //   B. every chunk finds where its buckets start (buckets before it in the
 //      segment + the same bucket in earlier chunks), ranks its keys and
@@ -63,8 +63,18 @@ struct SortArgs {
 // Forward call (MI355X, d = 64, b = m = 256), two launches -> one: 12 heads, n = 4096 36.4 -> 32.7 us; 4 heads,
 // n = 8192 (2 chunks) 31.0 -> 27.6; 12 heads, 16384 (4) 66.6 -> 64.3; 8 heads, 32768 (8) 81.0 -> 80.4; one
 // head, 65536 (16) 38.8 -> 39.5; 131072 (32) 53.8 -> 59.6.
-constexpr int kOneLaunchChunks = 256;
-constexpr int kOneLaunchLongest = 8;
+// Two workgroups to a CU (r <= 7): up to 512 of segments of up to four chunks, 1024 of whole segments; past that nothing is gained (us;
+// b = m = 64):
+//   8 chunks, n = 32768: 24 heads (384) d = 64 161.5 -> 161.8, d = 128 283.4 -> 282.4, 32 (512) 263.9 -> 264.0 and 467.7 -> 469.2
+//   4 chunks, n = 16384: 48 heads (384) 164.0 -> 161.4, 283.3 -> 279.7, 64 (512) 213.2 -> 210.4, 367.9 -> 363.9, 72 (576) 240.9 -> 240.4,
+//     410.3 both, 128 (1024) 402.0 -> 402.8
+//   2 chunks: n = 6300, b = 100, m = 77, 90 heads (360) 118.2 -> 114.4, 202.1 -> 197.7; n = 8192: 100 heads (400) 171.1 -> 167.4, 295.3 ->
+//     290.7, 128 (512) 214.7 -> 210.9, 368.6 -> 364.1, 192 (768) 308.9 -> 308.2, 543.8 -> 544.9, 256 (1024) 403.8 -> 405.3, 722.2 -> 724.1
+//   one chunk, n = 4096: 300 heads (600) 245.8 -> 242.5, 430.4 -> 427.0, 512 (1024) 407.7 -> 403.4, 719.4 -> 716.7
+static bool one_launch(int64_t chunks, int longest, bool two_per_cu) {
+  if (chunks <= 256) return longest <= 8;
+  return two_per_cu && chunks <= (longest == 1 ? 1024 : 512) && longest <= 4;
+}
 
 constexpr int kFlatWaves = 16;   // whole-segment mode: one workgroup has to cover a long segment
 constexpr int kChunkWaves = 4;   // chunked mode: many small workgroups per CU hide each other's barriers
@@ -474,8 +484,8 @@ int launch_seg_sort_nodes(const uint8_t* codes_q, const uint8_t* codes_k, int32_
   const int nbk = 1 << g.r;  // bucket codes of Definition 1 are below 2^r
   dim3 grid((unsigned)wg), block(kChunkWaves * 64);
   const int longest = ((g.causal ? g.n >> 1 : g.n) + kChunk - 1) / kChunk;  // chunks of the longest segment
-  if (wg <= kOneLaunchChunks && longest <= kOneLaunchLongest) {
-    static std::atomic<uint64_t> lds_set{0};  // devices on which the LDS limit is raised: 66 KiB at r = 8
+  if (one_launch(wg, longest, 2 * chunk_scatter_lds(nbk, 16, true) <= 160 * 1024)) {
+    static std::atomic<uint64_t> lds_set{0};  // devices on which the LDS limit is raised: 83 KiB at r = 8
     if (allow_full_lds(reinterpret_cast<const void*>(&chunk_scatter_kernel<16, true>), lds_set) != HA_OK) return HA_ERR_LAUNCH;
     hipLaunchKernelGGL((chunk_scatter_kernel<16, true>), grid, dim3(16 * 64), chunk_scatter_lds(nbk, 16, true), st, a, nbk);
     return check_launch();

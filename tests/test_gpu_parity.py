@@ -821,3 +821,28 @@ def test_lsh_hash_of_many_rows_is_that_of_its_parts(ha, torch, d, rows, exact_R)
     got = ha.ha_lsh_hash(X, R.contiguous())
     for part in range(0, rows, 300007):
         assert torch.equal(got[part:part + 300007], ha.ha_lsh_hash(X[part:part + 300007].contiguous(), R.contiguous()))
+
+
+@pytest.mark.parametrize("H,n,b,r,causal,n_min", [
+    (64, 16384, 64, 7, 0, 0), (65, 16384, 64, 7, 0, 0),    # 512 chunks, four per segment: one launch; 520: two
+    (24, 32768, 64, 7, 0, 0),                              # 384 chunks, eight per segment: two launches
+    (512, 4096, 64, 7, 0, 0), (513, 4096, 64, 7, 0, 0),    # 1024 chunks, whole segments: one launch; 1026: two
+    (40, 16384, 64, 8, 0, 0),                              # 320 chunks of 256 buckets, one workgroup to a CU: two launches
+    (31, 16400, 10, 5, 1, 2050)])                          # segments of 8200, 4100 and 2050 keys: 434 chunks
+def test_node_sort_in_one_launch_of_more_chunks_than_cus(ha, torch, H, n, b, r, causal, n_min):
+    test_node_sort_is_the_stable_order(ha, torch, H, n, b, r, causal, n_min)
+
+
+@pytest.mark.parametrize("n,b,m", [(4096, 64, 1500), (12000, 100, 4096)])
+def test_sorted_blocks_of_more_samples_than_threads(ha, torch, n, b, m):
+    H = 40
+    print(f"node sort n={n} b={b} m={m}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n)
+    Q, K, V = (torch.randn((1, H, n, 64), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(3))
+    shape, params = ha.make_shape(1, H, n, 64, ha.HA_BF16), ha.make_params(b, m, 7, False, 4096, 3)
+    ws = ha.alloc_workspace(shape, params)
+    ha.hyperattn_forward(Q, K, V, b, m, 7, seed=3, workspace=ws)
+    v = ha.workspace_views(ws, shape, params)
+    pos = v["codes_k"].view(H, n).long().sort(dim=1, stable=True).indices.argsort(dim=1)
+    assert torch.equal(v["samp_blk"].view(H, m).long(), pos[:, v["samples"].view(m).long()] // b)

@@ -260,7 +260,7 @@ int ha_merge_unpermute(const float* o_b, const float* lse_b, const float* o_r, c
  * Backward pass (Section 4.2 times forward + backward; the backward is the
  * derivative of the forward above with the random draws, and so the
  * permutations, held fixed).  bf16 tensors run on the matrix cores; fp32 tensors
- * take the same passes on the fp32 matrix cores.
+ * take the same passes, with operands split in three bf16 parts.
  *
  * Because every output row is one softmax over the union of its parts (block
  * keys, kept samples weighted s/m, base-case keys; Algorithms 1, 2, 4), with

@@ -402,7 +402,7 @@ static int stage_geometry(Geometry* g, int groups, int n, int d, int dtype, int 
 // ---------------------------------------------------------------------------
 // Backward pass
 // ---------------------------------------------------------------------------
-// bf16 tensors: bf16 matrix cores; fp32 tensors: fp32 matrix cores, the same passes
+// fp32 tensors: the same passes, operands split in three bf16 parts
 static int launch_attn_bwd(const BwdArgs& a, int mode, hipStream_t st) {
   return use_mfma(a.f.g) ? launch_attn_bwd_mfma(a, mode, st) : launch_attn_bwd_f32(a, mode, st);
 }

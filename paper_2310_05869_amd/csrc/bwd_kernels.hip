@@ -226,8 +226,12 @@ int launch_bwd_sample_scatter(const BwdArgs& a, const float* samp_k, const float
 
 // Unmasked problems, whose block-key pass adds the sampled sums itself: the rows of the sampled-key pass summed over the
 // query chunks, one thread per four columns of a (head, sample) row of dK or dV, in place into the first chunk's row.
+// U, the rows that a thread has in flight: as many as there are chunks, up to 32 (sums in one order for each).  With few heads their round trips
+// are the launch: 8 -> 32 (MI355X, backward, us): 2 heads, n = 65536, d = 64 112.7 -> 105.2, d = 128 181.1 -> 175.4; 24 heads, n = 16384, m = 128 198.4 ->
+// 196.5 and 425.1 -> 421.8; 12 heads, n = 16384 +-0.4 %.
 // Bound by the rows it reads (12 heads, n = 16384, m = 256, d = 64: 50 MB in 9.8 us); left to the block-key pass,
 // where few waves hold a sampled key and wait for its chunks one after the other, that pass took 76 instead of 46 us.
+template <int U>
 __global__ __launch_bounds__(256) void bwd_sample_reduce_kernel(float* samp_k, float* samp_v, int cpn, int m, int d, int64_t total) {
   int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= total) return;
@@ -242,12 +246,12 @@ __global__ __launch_bounds__(256) void bwd_sample_reduce_kernel(float* samp_k, f
   f32x4 part[8];
 #pragma unroll
   for (int u = 0; u < 8; ++u) part[u] = zero;
-  for (int q = 0; q < cpn; q += 8) {  // eight rows in flight: requested unconditionally (a load under a branch is waited for alone)
-    f32x4 v[8];
+  for (int q = 0; q < cpn; q += U) {  // U rows in flight: requested unconditionally (a load under a branch is waited for alone)
+    f32x4 v[U];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const f32x4*>(p + min(q + u, cpn - 1) * step);
+    for (int u = 0; u < U; ++u) v[u] = *reinterpret_cast<const f32x4*>(p + min(q + u, cpn - 1) * step);
 #pragma unroll
-    for (int u = 0; u < 8; ++u) part[u] += q + u < cpn ? v[u] : zero;
+    for (int u = 0; u < U; ++u) part[u % 8] += q + u < cpn ? v[u] : zero;
   }
   *reinterpret_cast<f32x4*>(p) = ((part[0] + part[1]) + (part[2] + part[3])) + ((part[4] + part[5]) + (part[6] + part[7]));
 }
@@ -258,7 +262,9 @@ int launch_bwd_sample_reduce(const BwdArgs& a, float* samp_k, float* samp_v, hip
   if (cpn == 1) return HA_OK;
   const int64_t total = (int64_t)g.BH * g.m * 2 * (g.d / 4), grid = (total + 255) / 256;
   if (grid > kMaxGrid) return HA_ERR_SHAPE;
-  hipLaunchKernelGGL(bwd_sample_reduce_kernel, dim3((unsigned)grid), dim3(256), 0, st, samp_k, samp_v, cpn, g.m, g.d, total);
+  if (cpn > 16) hipLaunchKernelGGL((bwd_sample_reduce_kernel<32>), dim3((unsigned)grid), dim3(256), 0, st, samp_k, samp_v, cpn, g.m, g.d, total);
+  else if (cpn > 8) hipLaunchKernelGGL((bwd_sample_reduce_kernel<16>), dim3((unsigned)grid), dim3(256), 0, st, samp_k, samp_v, cpn, g.m, g.d, total);
+  else hipLaunchKernelGGL((bwd_sample_reduce_kernel<8>), dim3((unsigned)grid), dim3(256), 0, st, samp_k, samp_v, cpn, g.m, g.d, total);
   return check_launch();
 }
 

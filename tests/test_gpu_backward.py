@@ -457,3 +457,10 @@ def test_every_tile_of_a_causal_launch_runs_once(ha, torch, dtype, d, H, n):
         diff = (got[0].float() - want).flatten(1).norm(dim=1) / want.flatten(1).norm(dim=1)
         print(f"  {name}: worst head {diff.max().item():.2e}", flush=True)
         assert (diff <= tol).all(), name
+
+
+@pytest.mark.parametrize("d,n,m,dtype", [(64, 2304, 40, "bf16"), (64, 4352, 40, "bf16"), (128, 8448, 30, "bf16"), (64, 5120, 33, "fp32")])
+def test_backward_unmasked_sums_of_many_chunks(ha, torch, d, n, m, dtype):
+    """9, 17 and 33 (fp32: 20) chunks of 256 sorted queries to a sample: sums of up to 32 rows in flight, and one more."""
+    cfg = dict(B=1, H=1, n=n, d=d, dtype=dtype, law="iid", b=64, m=m, r=6, causal=0, n_min=4096, seed=5)
+    _run_case(ha, torch, cfg)

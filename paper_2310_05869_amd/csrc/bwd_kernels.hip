@@ -226,9 +226,11 @@ int launch_bwd_sample_scatter(const BwdArgs& a, const float* samp_k, const float
 
 // Unmasked problems, whose block-key pass adds the sampled sums itself: the rows of the sampled-key pass summed over the
 // query chunks, one thread per four columns of a (head, sample) row of dK or dV, in place into the first chunk's row.
-// U, the rows that a thread has in flight: as many as there are chunks, up to 32 (sums in one order for each).  With few heads their round trips
-// are the launch: 8 -> 32 (MI355X, backward, us): 2 heads, n = 65536, d = 64 112.7 -> 105.2, d = 128 181.1 -> 175.4; 24 heads, n = 16384, m = 128 198.4 ->
-// 196.5 and 425.1 -> 421.8; 12 heads, n = 16384 +-0.4 %.
+// U: the rows that a thread has in flight (sums in one order for each).  With fewer than 256 workgroups their round trips are the
+// launch, and U is as many as there are chunks, up to 32; from there on the requests past the last chunk cost more than
+// that.  8 -> 32 (MI355X, backward, us; workgroups): 2 heads, n = 65536, d = 64 (64) 112.7 -> 105.2, n = 33792 82.0 -> 79.4, 4 heads, n = 65536 (128) 184.8 ->
+// 177.5, d = 128, 2 heads, n = 65536 (128) 181.1 -> 175.4, n = 33792 133.0 -> 131.1; 4 heads, n = 65536 (256) 367.4 -> 372.6; d = 64, 12 heads,
+// n = 20480 (384) 175.0 -> 176.1, 40 heads, n = 8448, m = 100 (500) 197.2 -> 200.2.
 // Bound by the rows it reads (12 heads, n = 16384, m = 256, d = 64: 50 MB in 9.8 us); left to the block-key pass,
 // where few waves hold a sampled key and wait for its chunks one after the other, that pass took 76 instead of 46 us.
 template <int U>
@@ -262,8 +264,8 @@ int launch_bwd_sample_reduce(const BwdArgs& a, float* samp_k, float* samp_v, hip
   if (cpn == 1) return HA_OK;
   const int64_t total = (int64_t)g.BH * g.m * 2 * (g.d / 4), grid = (total + 255) / 256;
   if (grid > kMaxGrid) return HA_ERR_SHAPE;
-  if (cpn > 16) hipLaunchKernelGGL((bwd_sample_reduce_kernel<32>), dim3((unsigned)grid), dim3(256), 0, st, samp_k, samp_v, cpn, g.m, g.d, total);
-  else if (cpn > 8) hipLaunchKernelGGL((bwd_sample_reduce_kernel<16>), dim3((unsigned)grid), dim3(256), 0, st, samp_k, samp_v, cpn, g.m, g.d, total);
+  if (grid < 256 && cpn > 16) hipLaunchKernelGGL((bwd_sample_reduce_kernel<32>), dim3((unsigned)grid), dim3(256), 0, st, samp_k, samp_v, cpn, g.m, g.d, total);
+  else if (grid < 256 && cpn > 8) hipLaunchKernelGGL((bwd_sample_reduce_kernel<16>), dim3((unsigned)grid), dim3(256), 0, st, samp_k, samp_v, cpn, g.m, g.d, total);
   else hipLaunchKernelGGL((bwd_sample_reduce_kernel<8>), dim3((unsigned)grid), dim3(256), 0, st, samp_k, samp_v, cpn, g.m, g.d, total);
   return check_launch();
 }

@@ -109,3 +109,16 @@ def test_most_sampled_keys(ha, torch, d, n, b, m, causal, n_min):
     print(f"split fp32 lists d={d} n={n} b={b} m={m} causal={causal}", flush=True)
     cfg = dict(B=1, H=1, n=n, d=d, dtype="fp32", law="iid", b=b, m=m, r=7, causal=causal, n_min=n_min, seed=3)
     _run_case(ha, torch, cfg)
+
+
+@pytest.mark.parametrize("d,H,n", [(64, 13, 2000), (64, 2, 700), (128, 2, 700)])
+def test_values_of_2_to_the_minus_100(ha, torch, d, H, n):
+    """Their lowest parts are still normal numbers: the 2-norm bounds of test_exact_forms."""
+    print(f"split fp32 small values d={d} H={H} n={n}", flush=True)
+    q, k, v, g = _inputs(torch, H, n, d, d + n)
+    v = v * 2.0 ** -100
+    out, lse = ha.exact_attn_forward(q, k, v)
+    dq = ha.exact_attn_backward(q, k, v, out, lse, g)[0]
+    ref = _reference(torch, *(x[:, :1] for x in (q, k, v, g)), False)
+    assert (out[:, :1].double() - ref[0]).norm() <= 1e-6 * ref[0].norm()
+    assert (dq[:, :1].double() - ref[2]).norm() <= 1e-6 * ref[2].norm()

@@ -29,6 +29,8 @@
 // n = 8192, d = 64 15000 -> 10430, 16 heads, d = 128 16210 -> 10540; causal, 16 heads, n = 1024 95.6 -> 81.1, d = 128 205 -> 169; 8 heads, n = 4096 547 -> 457,
 // 1120 -> 951; one head, n = 1024 77.3 -> 56.0, 136 -> 112; of HyperAttention: one head, n = 1024, b = m = 64 45.6 -> 38.0, 8 heads, n = 4096, b = m = 256
 // 190 -> 142, d = 128 393 -> 259; causal, 4 heads, n = 4096 in blocks of 1024, b = m = 64 150 -> 108, 279 -> 235.
+#include <type_traits>
+
 #include "attn_common.h"
 #include "bwd_common.h"
 #include "split_f32.h"
@@ -41,7 +43,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kFTT = 32;   // T rows per tile
 
 // LDS: the ways' tiles (Y and B) and L and delta of their rows, or, RG = 1, the R rows; the key list of a node's dQ pass; in the end the
-// staged rows, over the tiles; behind all else the sampled keys of a block-key pass.
+// staged rows, over the tiles; behind all else a word per wave (SplitFinite) and the sampled keys of a block-key pass.
 // (RG = 1: whether a wave keeps the split rows of its Y tile for the accumulating products; the lists of a d = 128 node leave no room,
 // nor do 4096 sampled keys of an unmasked problem's block keys)
 constexpr bool f32_bwd_keeps_y(int d, int mode, bool causal) {
@@ -58,11 +60,12 @@ struct F32BwdLds {
   }
   static constexpr int ROW = D + 4;  // floats per staged row
   static constexpr int ROWS = RG * KW * 32 * ROW * 4;
-  __host__ __device__ static size_t hits_at(const Geometry& g, int mode) {
+  __host__ __device__ static size_t finite_at(const Geometry& g, int mode) {
     const size_t list = mode == kBwdDqNode ? (size_t)(((g.b + g.m + 63) & ~63) + 64) * 4 + 64 : 0;
     const size_t end = list_at(mode, g.causal) + list;
     return end > (size_t)ROWS ? end : (size_t)ROWS;
   }
+  __host__ __device__ static size_t hits_at(const Geometry& g, int mode) { return finite_at(g, mode) + SplitFinite<RG * KW>::BYTES; }
   __host__ __device__ static size_t bytes(const Geometry& g, int mode) {
     return hits_at(g, mode) + (mode == kBwdDkvBlock && !g.causal ? sample_hits_bytes(g) : 0);
   }
@@ -122,23 +125,26 @@ __device__ __forceinline__ void bwd_f32_pass(const BwdArgs& a, const int wg, con
   const int r_row = bwd_r_row<MODE>(a, b, r_use, &blk_r);
   Split8 xs[kShared ? KS : 1], as[kShared ? KS : 1];
   float L_r = 0.f, del_r = 0.f;
-  {
-    f32x4 x[2 * KS], av[2 * KS];  // columns 16 s + 8 h ... + 7 of step s
-    if (kShared || (kDq && a.delta_out != nullptr)) {
+  auto load_r = [&](f32x4 (&av)[2 * KS]) {  // columns 16 s + 8 h ... + 7 of step s
+    f32x4 x[2 * KS];
 #pragma unroll
-      for (int j = 0; j < 2 * KS; ++j) {
-        const int64_t at = (int64_t)r_row * D + 16 * (j / 2) + 8 * h + 4 * (j % 2);
-        if (kShared) x[j] = *reinterpret_cast<const f32x4*>(Xh + at);
-        av[j] = *reinterpret_cast<const f32x4*>(Ah + at);
-      }
+    for (int j = 0; j < 2 * KS; ++j) {
+      const int64_t at = (int64_t)r_row * D + 16 * (j / 2) + 8 * h + 4 * (j % 2);
+      if (kShared) x[j] = *reinterpret_cast<const f32x4*>(Xh + at);
+      av[j] = *reinterpret_cast<const f32x4*>(Ah + at);
     }
     if constexpr (kShared) {
 #pragma unroll
       for (int s = 0; s < KS; ++s) {
-        xs[s] = split8<true>([&](int e) { return x[2 * s + e / 4][e % 4]; });
-        as[s] = split8<true>([&](int e) { return av[2 * s + e / 4][e % 4]; });
+        xs[s] = split8_raw([&](int e) { return x[2 * s + e / 4][e % 4]; });
+        as[s] = split8_raw([&](int e) { return av[2 * s + e / 4][e % 4]; });
       }
-    } else {
+    }
+  };
+  {
+    f32x4 av[2 * KS];
+    if (kShared || (kDq && a.delta_out != nullptr)) load_r(av);
+    if constexpr (!kShared) {
       for (int i = tid; i < 32 * T::PPR; i += kFBT) {
         const int r = i / T::PPR, piece = i % T::PPR;
         int blk;
@@ -287,165 +293,180 @@ __device__ __forceinline__ void bwd_f32_pass(const BwdArgs& a, const int wg, con
   };
 
   f32x16 acc1[DT], acc2[kDq ? 1 : DT];  // dQ or dK; dV
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt) acc1[dt][i] = 0.f;
-#pragma unroll
-    for (int dt = 0; dt < (kDq ? 1 : DT); ++dt) acc2[dt][i] = 0.f;
-  }
-
-  if constexpr (kShared) {
-    if (kw < tiles) {
-      find_rows(kw);
-      fetch();
-      if (!kExact) find_rows(kw + KW);
-    }
-  } else {
-    __syncthreads();  // the R rows stand
-    if (kt_lo + kw < kt_hi) fetch_own(kt_lo + kw);
-  }
-  // (shared tiles: the same trips for all ways, the barriers are the workgroup's)
-  const int kt_end = kShared ? (tiles + KW - 1) / KW * KW : kt_hi;
-  for (int kt = (kShared ? 0 : kt_lo) + kw; kt < kt_end; kt += KW) {
-    if constexpr (kShared) {
-      if (kt >= KW) __syncthreads();  // the tiles before are read no more
-      if (kt < tiles) store();
-      __syncthreads();
-      if (kt + KW < tiles) {
-        if (kExact) find_rows(kt + KW);
-        fetch();
-        if (!kExact) find_rows(kt + 2 * KW);
-      }
-      if (kt < kt_lo || kt >= kt_hi) continue;
-    }
-    f32x4 l4[4], d4[4];  // dK / dV passes: L and delta of the lane's T rows
-    if (!kDq && (kShared || kExact)) {
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const int at = (w.k0 + kt * kFTT + 8 * q4 + 4 * h) * 4;
-        l4[q4] = kShared ? *reinterpret_cast<const f32x4*>(sc + 8 * q4 + 4 * h) : __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(lrsrc, at, 0, 0));
-        d4[q4] = kShared ? *reinterpret_cast<const f32x4*>(sc + kFTT + 8 * q4 + 4 * h) : __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(drsrc, at, 0, 0));
-      }
-    }
-    const int row_c = row;
-    const float scl_c = scl, scd_c = scd;
-    f32x4 bf[kShared ? 1 : 2 * KS];
-    if (!kShared) load_rows(brsrc, row_c, bf);
-
-    f32x16 c, e;
-    {
-      f32x16 small;
-#pragma unroll
-      for (int i = 0; i < 16; ++i) c[i] = small[i] = 0.f;
-#pragma unroll
-      for (int s = 0; s < KS; ++s) {
-        if constexpr (kShared) split_product(T::row_frag(ytile, row_at, s), xs[s], c, small);
-        else {
-          const Split8 y = split8<true>([&](int i) { return yf[2 * s + i / 4][i % 4]; });
-          if (kKeepY) T::store(own_y, lq, 2 * s + h, y);
-          split_product(y, T::row_frag(ytile, row_at, s), c, small);
-        }
-      }
-      split_sum(c, small);
-    }
-    float tv[kShared ? 1 : 16][DT];
-    if constexpr (!kShared && !(kDq && kKeepY)) load_cols(kDq ? yrsrc : brsrc, row_c, kt, tv, 0, 16);
-    {
-      f32x16 small;
-#pragma unroll
-      for (int i = 0; i < 16; ++i) e[i] = small[i] = 0.f;
-#pragma unroll
-      for (int s = 0; s < KS; ++s) {
-        if constexpr (kShared) split_product(T::row_frag(btile, row_at, s), as[s], e, small);
-        else split_product(split8<true>([&](int i) { return bf[2 * s + i / 4][i % 4]; }), T::row_frag(btile, row_at, s), e, small);
-      }
-      split_sum(e, small);
-    }
-
-    // masks, on the tiles that have any: in the sampled-key pass the keys differ by lane
-    const int tbase = kt * kFTT;
-    bool special = tbase + kFTT > nT;
-    if (MODE == kBwdDqNode) special = special || (tbase < nb && tbase + kFTT > nb);
-    if (MODE == kBwdDqExact && f.exact_causal) special = special || (w.k0 + tbase + kFTT - 1 > w.q0 + grp * 32);
-    if (MODE == kBwdDkvExact && f.exact_causal) special = special || (w.k0 + tbase < w.q0 + grp * 32 + 31);
-    if (MODE == kBwdDkvSamp) {
-      const int mlo = blk_r * g.b - (b.chunk_start + tbase);
-      special = special || __any(mlo < kFTT && mlo + g.b > 0);
-    }
-    float tile_bias = MODE == kBwdDkvSamp ? nat_bias : 0.f;
-    if (MODE == kBwdDqNode && tbase >= nb) tile_bias = nat_bias;
-    if (special) {
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int tpos = tbase + 8 * (i / 4) + 4 * h + (i % 4);
-        bool masked = tpos >= nT;
-        if (MODE == kBwdDqNode && tbase < nb && tpos >= nb) c[i] += nat_bias;
-        // queries of the key's own block: factor 1 - M of Algorithm 2
-        if (MODE == kBwdDkvSamp) masked = masked || (unsigned)(b.chunk_start + tpos - blk_r * g.b) < (unsigned)g.b;
-        if (MODE == kBwdDqExact && f.exact_causal) masked = masked || (w.k0 + tpos > r_row);   // keys after the query
-        if (MODE == kBwdDkvExact && f.exact_causal) masked = masked || (w.k0 + tpos < r_row);  // queries before the key
-        if (masked) c[i] = -INFINITY;
-        if (kExact && !kDq && masked) {  // (a piece of four values can end past the head's last row)
-          l4[i / 4][i % 4] = 0.f;
-          d4[i / 4][i % 4] = 0.f;
-        }
-      }
-    }
+  // BOUND: split_tile_products'; tiles are then not fetched ahead, so that this form needs no more registers.
+  auto run = [&](auto bound) {
+    constexpr bool BOUND = decltype(bound)::value;
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-      const bool quads = kShared || kExact;
-      const float L = kDq ? L_r : quads ? l4[i / 4][i % 4] : of_elem(scl_c, i);
-      const float dl = kDq ? del_r : quads ? d4[i / 4][i % 4] : of_elem(scd_c, i);
-      float p = exp_split(c[i] + tile_bias - L);
-      if (L == -INFINITY) p = 0.f;  // (a row without keys)
-      c[i] = p;
-      e[i] = p * (e[i] - dl);
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) acc1[dt][i] = 0.f;
+#pragma unroll
+      for (int dt = 0; dt < (kDq ? 1 : DT); ++dt) acc2[dt][i] = 0.f;
+    }
+
+    if constexpr (kShared && BOUND) {  // (kept through the first run, they would take registers that its loop needs)
+      f32x4 av[2 * KS];
+      load_r(av);
     }
     if constexpr (kShared) {
+      if (!BOUND && kw < tiles) {
+        find_rows(kw);
+        fetch();
+        if (!kExact) find_rows(kw + KW);
+      }
+    } else if (!BOUND && kt_lo + kw < kt_hi) {
+      fetch_own(kt_lo + kw);
+    }
+    // (shared tiles: the same trips for all ways, the barriers are the workgroup's)
+    const int kt_end = kShared ? (tiles + KW - 1) / KW * KW : kt_hi;
+    for (int kt = (kShared ? 0 : kt_lo) + kw; kt < kt_end; kt += KW) {
+      if constexpr (kShared) {
+        if (kt >= KW) __syncthreads();  // the tiles before are read no more
+        if (BOUND && kt < tiles) {
+          find_rows(kt);
+          fetch();
+        }
+        if (kt < tiles) store();
+        __syncthreads();
+        if (!BOUND && kt + KW < tiles) {
+          if (kExact) find_rows(kt + KW);
+          fetch();
+          if (!kExact) find_rows(kt + 2 * KW);
+        }
+        if (kt < kt_lo || kt >= kt_hi) continue;
+      } else if (BOUND) {
+        fetch_own(kt);
+      }
+      f32x4 l4[4], d4[4];  // dK / dV passes: L and delta of the lane's T rows
+      if (!kDq && (kShared || kExact)) {
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+          const int at = (w.k0 + kt * kFTT + 8 * q4 + 4 * h) * 4;
+          l4[q4] = kShared ? *reinterpret_cast<const f32x4*>(sc + 8 * q4 + 4 * h) : __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(lrsrc, at, 0, 0));
+          d4[q4] = kShared ? *reinterpret_cast<const f32x4*>(sc + kFTT + 8 * q4 + 4 * h) : __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(drsrc, at, 0, 0));
+        }
+      }
+      const int row_c = row;
+      const float scl_c = scl, scd_c = scd;
+      f32x4 bf[kShared ? 1 : 2 * KS];
+      if (!kShared) load_rows(brsrc, row_c, bf);
+
+      f32x16 c, e;
+      {
+        f32x16 small;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) c[i] = small[i] = 0.f;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+          if constexpr (kShared) split_product(T::row_frag(ytile, row_at, s), xs[s], c, small);
+          else {
+            const Split8 y = split8_raw([&](int i) { return yf[2 * s + i / 4][i % 4]; });
+            if (kKeepY) T::store(own_y, lq, 2 * s + h, y);
+            split_product(y, T::row_frag(ytile, row_at, s), c, small);
+          }
+        }
+        split_sum<BOUND>(c, small);
+      }
+      float tv[kShared ? 1 : 16][DT];
+      if constexpr (!kShared && !(kDq && kKeepY)) load_cols(kDq ? yrsrc : brsrc, row_c, kt, tv, 0, 16);
+      {
+        f32x16 small;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) e[i] = small[i] = 0.f;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+          if constexpr (kShared) split_product(T::row_frag(btile, row_at, s), as[s], e, small);
+          else split_product(split8_raw([&](int i) { return bf[2 * s + i / 4][i % 4]; }), T::row_frag(btile, row_at, s), e, small);
+        }
+        split_sum<BOUND>(e, small);
+      }
+
+      // masks, on the tiles that have any: in the sampled-key pass the keys differ by lane
+      const int tbase = kt * kFTT;
+      bool special = tbase + kFTT > nT;
+      if (MODE == kBwdDqNode) special = special || (tbase < nb && tbase + kFTT > nb);
+      if (MODE == kBwdDqExact && f.exact_causal) special = special || (w.k0 + tbase + kFTT - 1 > w.q0 + grp * 32);
+      if (MODE == kBwdDkvExact && f.exact_causal) special = special || (w.k0 + tbase < w.q0 + grp * 32 + 31);
+      if (MODE == kBwdDkvSamp) {
+        const int mlo = blk_r * g.b - (b.chunk_start + tbase);
+        special = special || __any(mlo < kFTT && mlo + g.b > 0);
+      }
+      float tile_bias = MODE == kBwdDkvSamp ? nat_bias : 0.f;
+      if (MODE == kBwdDqNode && tbase >= nb) tile_bias = nat_bias;
+      if (special) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const int tpos = tbase + 8 * (i / 4) + 4 * h + (i % 4);
+          bool masked = tpos >= nT;
+          if (MODE == kBwdDqNode && tbase < nb && tpos >= nb) c[i] += nat_bias;
+          // queries of the key's own block: factor 1 - M of Algorithm 2
+          if (MODE == kBwdDkvSamp) masked = masked || (unsigned)(b.chunk_start + tpos - blk_r * g.b) < (unsigned)g.b;
+          if (MODE == kBwdDqExact && f.exact_causal) masked = masked || (w.k0 + tpos > r_row);   // keys after the query
+          if (MODE == kBwdDkvExact && f.exact_causal) masked = masked || (w.k0 + tpos < r_row);  // queries before the key
+          if (masked) c[i] = -INFINITY;
+          if (kExact && !kDq && masked) {  // (a piece of four values can end past the head's last row)
+            l4[i / 4][i % 4] = 0.f;
+            d4[i / 4][i % 4] = 0.f;
+          }
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const bool quads = kShared || kExact;
+        const float L = kDq ? L_r : quads ? l4[i / 4][i % 4] : of_elem(scl_c, i);
+        const float dl = kDq ? del_r : quads ? d4[i / 4][i % 4] : of_elem(scd_c, i);
+        float p = exp_split(c[i] + tile_bias - L);
+        if (L == -INFINITY) p = 0.f;  // (a row without keys)
+        c[i] = p;
+        e[i] = p * (e[i] - dl);
+      }
       Split8 ps[2];  // 16 T rows each
-      if constexpr (!kDq) {
+      if constexpr (kShared) {
+        if constexpr (!kDq) {
 #pragma unroll
-        for (int hf = 0; hf < 2; ++hf) ps[hf] = split8<false>([&](int i) { return c[8 * hf + i]; });
-        split_tile_products([&](int dt, int hf) { return T::col_frag(btile, col_at, hf, dt); }, ps, acc2);
-      }
-#pragma unroll
-      for (int hf = 0; hf < 2; ++hf) ps[hf] = split8<true>([&](int i) { return e[8 * hf + i]; });
-      split_tile_products([&](int dt, int hf) { return T::col_frag(ytile, col_at, hf, dt); }, ps, acc1);
-    } else {
-      // Y^T dS from the wave's own tile, or, half a tile at a time, from the caches: the rows of a half arrive while the other half's
-      // dV products run
-      float yv[kKeepY || kDq ? 1 : 16][DT];
-      if constexpr (!kDq) {
-#pragma unroll
-        for (int hf = 0; hf < 2; ++hf) {
-          if constexpr (!kKeepY) load_cols(yrsrc, row_c, kt, yv, 8 * hf, 8);
-          const Split8 p = split8<false>([&](int i) { return c[8 * hf + i]; });
-#pragma unroll
-          for (int dt = 0; dt < DT; ++dt) split_product(split8<true>([&](int i) { return tv[8 * hf + i][dt]; }), p, acc2[dt]);
+          for (int hf = 0; hf < 2; ++hf) ps[hf] = split8([&](int i) { return c[8 * hf + i]; });
+          split_tile_products<DT, D == 64 && !kDq ? kSumSmall : kSumTile, BOUND>([&](int dt, int hf) { return T::col_frag(btile, col_at, hf, dt); }, ps, acc2);
         }
-      }
-      if (kt + KW < kt_hi) fetch_own(kt + KW);
-      if constexpr (kKeepY) {  // (the tile's rows came from other lanes of the wave)
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      }
 #pragma unroll
-      for (int hf = 0; hf < 2; ++hf) {
-        const Split8 ds = split8<true>([&](int i) { return e[8 * hf + i]; });
+        for (int hf = 0; hf < 2; ++hf) ps[hf] = split8([&](int i) { return e[8 * hf + i]; });
+        split_tile_products<DT, D == 64 && !kDq ? kSumSmall : kSumTile, BOUND>([&](int dt, int hf) { return T::col_frag(ytile, col_at, hf, dt); }, ps, acc1);
+      } else {
+        // Y^T dS from the wave's own tile, or from the caches: the rows arrive while the dV products run
+        float yv[kKeepY || kDq ? 1 : 16][DT];
+        if constexpr (!kDq) {
+          if constexpr (!kKeepY) load_cols(yrsrc, row_c, kt, yv, 0, 16);
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt) {
-          if constexpr (kKeepY) split_product(T::col_frag(own_y, col_at, hf, dt), ds, acc1[dt]);
-          else split_product(split8<true>([&](int i) { return (kDq ? tv : yv)[kDq || !kKeepY ? 8 * hf + i : 0][dt]; }), ds, acc1[dt]);
+          for (int hf = 0; hf < 2; ++hf) ps[hf] = split8([&](int i) { return c[8 * hf + i]; });
+          split_tile_products<DT, kSumEach, BOUND>([&](int dt, int hf) { return split8_raw([&](int i) { return tv[8 * hf + i][dt]; }); }, ps, acc2);
         }
-      }
-      if constexpr (kKeepY) {  // (the next tile's rows are written behind these reads)
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        if (!BOUND && kt + KW < kt_hi) fetch_own(kt + KW);
+        if constexpr (kKeepY) {  // (the tile's rows came from other lanes of the wave)
+          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+          __builtin_amdgcn_wave_barrier();
+          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        }
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf) ps[hf] = split8([&](int i) { return e[8 * hf + i]; });
+        split_tile_products<DT, kSumEach, BOUND>([&](int dt, int hf) {
+          if constexpr (kKeepY) return T::col_frag(own_y, col_at, hf, dt);
+          else return split8_raw([&](int i) { return (kDq ? tv : yv)[kDq || !kKeepY ? 8 * hf + i : 0][dt]; });
+        }, ps, acc1);
+        if constexpr (kKeepY) {  // (the next tile's rows are written behind these reads)
+          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+          __builtin_amdgcn_wave_barrier();
+          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        }
       }
     }
+  };
+  if constexpr (!kShared) __syncthreads();  // the R rows stand
+  run(std::false_type{});
+  const SplitFinite<NW> finite{reinterpret_cast<int32_t*>(smem + L::finite_at(g, MODE))};
+  finite.post(wave, split_finite(acc1) && (kDq || split_finite(acc2)));
+  __syncthreads();  // the key list is read no more
+  if (!finite.all()) {
+    run(std::true_type{});
+    __syncthreads();
   }
 
   // ---- results: the waves' rows through LDS, the KW parts of a row added in wave order.  Node passes write
@@ -456,7 +477,6 @@ __device__ __forceinline__ void bwd_f32_pass(const BwdArgs& a, const int wg, con
   float* rows_lds = reinterpret_cast<float*>(smem);
   const int64_t srow0 = (int64_t)w.bh * bwd_chunks_per_node(g, a.chunk, 0) * g.m;  // sample 0's sums (kHits)
   auto write_out = [&](const auto& acc, float* node_dst, const float* samp, float* fin, const float* lvl) {
-    __syncthreads();  // the key list, or the rows of the other gradient, are read no more
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
@@ -492,7 +512,10 @@ __device__ __forceinline__ void bwd_f32_pass(const BwdArgs& a, const int wg, con
     }
   };
   write_out(acc1, a.out1, a.samp1, reinterpret_cast<float*>(a.fin1), a.lvl1);
-  if constexpr (!kDq) write_out(acc2, a.out2, a.samp2, reinterpret_cast<float*>(a.fin2), a.lvl2);
+  if constexpr (!kDq) {
+    __syncthreads();  // the rows of the other gradient are read no more
+    write_out(acc2, a.out2, a.samp2, reinterpret_cast<float*>(a.fin2), a.lvl2);
+  }
 }
 
 template <int D, int MODE, int RG, int KW, bool FINAL>

@@ -20,10 +20,11 @@
 // Measured (MI355X, us; fp32 matrix instructions, K and V always from the caches -> this form): exact attention, 32 heads, n = 8192:
 // d = 64 4270 -> 3070; 16 heads, d = 128 4240 -> 3550; causal, 16 heads, n = 1024 d = 64 33.1 -> 26.4, d = 128 58.6 -> 44.8; 8 heads, n = 4096
 // 164 -> 136, 346 -> 255; one head, n = 1024 23.8 -> 18.3, 43.1 -> 32.7; whole calls: one head, n = 1024, d = 64, b = m = 64 17.8 -> 17.0, 8 heads, n = 4096,
-// b = m = 256 64.4 -> 54.6, d = 128 112 -> 92; 16 causal heads, n = 4096 in blocks of 1024, b = m = 128 192 -> 148, 352 -> 298.  What keeps an
-// infinite operand infinite (split8) is 3 % of these.
+// b = m = 256 64.4 -> 54.6, d = 128 112 -> 92; 16 causal heads, n = 4096 in blocks of 1024, b = m = 128 192 -> 148, 352 -> 298.
 // Tried: the next step's split in slices between the products, by the compiler's issue-order hints (+-1 %: the other waves fill the gaps);
 // KW = 2 at d = 128 (one wave per SIMD: 16 heads, n = 2048, causal 138 -> 187).
+#include <type_traits>
+
 #include "attn_common.h"
 #include "node_sort.h"
 #include "split_f32.h"
@@ -60,12 +61,17 @@ __host__ __device__ constexpr size_t f32_tile_bytes() {
 }
 
 template <int D, int KW>
-__host__ __device__ inline size_t f32_lds_bytes(int b, int m, int mode) {
+__host__ __device__ inline size_t f32_finite_at(int b, int m, int mode) {
   constexpr int NW = f32_waves(KW);
   const size_t loop = f32_list_bytes(b, m, mode) + f32_tile_bytes<D, KW>();
   // staged rows: two more values each in cap mode
   const size_t rows = (size_t)F32Lds<D, NW>::BYTES + (mode == kModeCap || mode == kModeValue ? NW * 32 * 2 * 4 : 0);
   return loop > rows ? loop : rows;
+}
+
+template <int D, int KW>
+__host__ __device__ inline size_t f32_lds_bytes(int b, int m, int mode) {
+  return f32_finite_at<D, KW>(b, m, mode) + SplitFinite<f32_waves(KW)>::BYTES;
 }
 
 // SORT: the sort's tables lie behind the list, where the tiles come later, the tile's query rows behind all else
@@ -94,7 +100,7 @@ __device__ inline float add_log(float m, float l) {
 // FAR (node mode): a head's rows pass the reach of a buffer load's 32-bit offset, so they are addressed in 64 bits.
 // SORT (node mode): the workgroup finds its rows from the node's bucket codes (node_sort.h).
 template <int D, int MODE, int KW, bool FAR, bool SORT>
-__global__ __launch_bounds__(64 * f32_waves(KW), D == 128 && KW < 4 ? 1 : 2) void attn_f32_kernel(AttnArgs a) {
+__global__ __launch_bounds__(64 * f32_waves(KW), D == 128 && KW < 4 ? 1 : D == 64 && KW == 4 ? 3 : 2) void attn_f32_kernel(AttnArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   constexpr int NW = f32_waves(KW), kFNT = 64 * NW;
   constexpr int RG = NW / KW;  // waves that share the tiles of a way
@@ -176,7 +182,7 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 128 && KW < 4 ? 1 : 2) voi
 #pragma unroll
     for (int j = 0; j < KJ; ++j) qf[j] = *reinterpret_cast<const f32x4*>(Qh + (int64_t)qrow * D + 16 * (j / 2) + 8 * h + 4 * (j % 2));
 #pragma unroll
-    for (int s = 0; s < KS; ++s) q[s] = split8<true>([&](int e) { return qf[2 * s + e / 4][e % 4]; });
+    for (int s = 0; s < KS; ++s) q[s] = split8_raw([&](int e) { return qf[2 * s + e / 4][e % 4]; });
   } else {
     for (int i = tid; i < 32 * T::PPR; i += kFNT) {
       const int r = i / T::PPR, piece = i % T::PPR, ru = r < w.rows_valid ? r : 0;
@@ -191,17 +197,17 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 128 && KW < 4 ? 1 : 2) voi
   const __amdgpu_buffer_rsrc_t krsrc = __builtin_amdgcn_make_buffer_rsrc((void*)Kh, 0, (int)bytes, 0x00020000);
   const __amdgpu_buffer_rsrc_t vrsrc = __builtin_amdgcn_make_buffer_rsrc((void*)Vh, 0, (int)bytes, 0x00020000);
   f32x4 kf[kShared ? 1 : KJ];
-  auto load_k = [&](int kt) {
+  auto load_k = [&](int kt, int j0 = 0, int j1 = D / 8) {
     if constexpr (kShared) return;
     const int row = kNode ? list[kt * kFKT + lq] : w.k0 + kt * kFKT + lq;
     if constexpr (FAR) {  // (every row of the list exists)
 #pragma unroll
-      for (int j = 0; j < KJ; ++j) kf[kShared ? 0 : j] = *reinterpret_cast<const f32x4*>(Kh + (int64_t)row * D + 16 * (j / 2) + 8 * h + 4 * (j % 2));
+      for (int j = j0; j < j1; ++j) kf[kShared ? 0 : j] = *reinterpret_cast<const f32x4*>(Kh + (int64_t)row * D + 16 * (j / 2) + 8 * h + 4 * (j % 2));
       return;
     }
     const int off = row * (D * 4) + 32 * h;
 #pragma unroll
-    for (int j = 0; j < KJ; ++j)
+    for (int j = j0; j < j1; ++j)
       kf[kShared ? 0 : j] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(krsrc, off + 16 * (j % 2), 64 * (j / 2), 0));
   };
   // V rows of the tile, columns 32 dt + lq for dt in [dt0, dt0 + DTA): element i of a lane is key
@@ -257,11 +263,7 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 128 && KW < 4 ? 1 : 2) voi
   const int row_at = T::row_at(lane), col_at = T::col_at(lane);
 
   f32x16 o[DT];
-#pragma unroll
-  for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) o[dt][i] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;
+  float m_run, l_run;
 
   // Cap mode (Algorithm 2 as printed): the block's keys, padded to whole tiles, come first; then every sample's weight
   // counts at most C_i in the row sum, whose cap follows from the masked sum of all waves of the row.  One thread per query row
@@ -279,13 +281,13 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 128 && KW < 4 ? 1 : 2) voi
   // log d~ to underflow: 150 of 2048, d = 64, b = m = 64, cap 8.  Time: 32 heads, n = 8192, b = m = 256, d = 64 590 -> 578 us, d = 128 1134 ->
   // 1122, with value sampling 1214 -> 1210, 4 heads, n = 2048 82.3 -> 83.7.)
   const int nbt = kCap ? ((nb + 63) & ~63) / kFKT : 0;
-  float log_masked = -INFINITY, log_capw = INFINITY;  // log of the row's masked sum, of (s / m) C_i
-  float d_ref = -INFINITY;
+  float log_masked, log_capw;  // log of the row's masked sum, of (s / m) C_i
+  float d_ref;
   constexpr float kFarCap = 40.f;  // a term that underflows against m_run is then e^-47 of the cap or less
   auto sum_ref = [&](float m) { return kCap && !kValue && m > log_capw + kFarCap ? log_capw : m; };
   auto finite_ref = [](float m) { return m == -INFINITY ? 0.f : m; };
   const float floor_term = kCap && a.kappa > 0.f ? a.log_tau[(int64_t)w.bh * a.g.total_nodes + w.nr.heap] - logf(a.kappa) : -INFINITY;
-  bool sampled = false, drawn = false;
+  bool sampled, drawn;
   auto to_samples = [&]() {  // every wave comes here once
     float* ex = reinterpret_cast<float*>(list + (kValue ? drawn_at + ((a.g.m + 63) & ~63) : ((a.g.b + a.g.m + 63) & ~63) + 64));  // [4 waves][32][2]
     const float mine = l_run + __shfl_xor(l_run, 32);
@@ -311,153 +313,173 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 128 && KW < 4 ? 1 : 2) voi
     if (kValue) m_run = -INFINITY;
     sampled = true;
   };
-  if constexpr (kShared) {
-    if (kw < wg_tiles) fetch(kw);
-  } else {
-    __syncthreads();  // the queries stand
-    if (kw < ntiles) load_k(kw);
-  }
-  // (shared tiles: the same trips for all ways, the barriers are the workgroup's)
-  const int kt_end = kShared ? (wg_tiles + KW - 1) / KW * KW : ntiles;
-  for (int kt = kw; kt < kt_end; kt += KW) {
+  // BOUND: split_tile_products'; tiles are then not fetched ahead, so that this form needs no more registers.
+  auto run = [&](auto bound) {
+    constexpr bool BOUND = decltype(bound)::value;
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) o[dt][i] = 0.f;
+    m_run = log_masked = d_ref = -INFINITY;
+    l_run = 0.f;
+    log_capw = INFINITY;
+    sampled = drawn = false;
     if constexpr (kShared) {
-      if (kt >= KW) __syncthreads();  // the tiles before are read no more
-      if (kt < wg_tiles) store(kt);
-      __syncthreads();
-      if (kt + KW < wg_tiles) fetch(kt + KW);
-      if (kt >= ntiles) continue;
+      if (!BOUND && kw < wg_tiles) fetch(kw);
+    } else if (!BOUND && kw < ntiles) {
+      load_k(kw);
     }
-    float va[kShared ? 1 : 16][DTA];
-    if constexpr (!kShared && DT == 2 && !kValue) load_v(kt, 0, va);
-    f32x16 c, small;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) c[i] = small[i] = 0.f;
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
+    // (shared tiles: the same trips for all ways, the barriers are the workgroup's)
+    const int kt_end = kShared ? (wg_tiles + KW - 1) / KW * KW : ntiles;
+    for (int kt = kw; kt < kt_end; kt += KW) {
       if constexpr (kShared) {
-        split_product(T::row_frag(ktile, row_at, s), q[s], c, small);
-      } else {
-        if constexpr (DT > 2 && !kValue) {
-          if (s == KS / 2) {  // d = 128: V takes the registers of the K pieces already multiplied
-            __builtin_amdgcn_sched_barrier(0);
-            load_v(kt, 0, va);
+        if (kt >= KW) __syncthreads();  // the tiles before are read no more
+        if (BOUND && kt < wg_tiles) fetch(kt);
+        if (kt < wg_tiles) store(kt);
+        __syncthreads();
+        if (!BOUND && kt + KW < wg_tiles) fetch(kt + KW);
+        if (kt >= ntiles) continue;
+      } else if (BOUND) {
+        load_k(kt);
+      }
+      float va[kShared ? 1 : 16][DTA];
+      if constexpr (!kShared && DT == 2 && !kValue) load_v(kt, 0, va);
+      f32x16 c, small;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) c[i] = small[i] = 0.f;
+#pragma unroll
+      for (int s = 0; s < KS; ++s) {
+        if constexpr (kShared) {
+          split_product(T::row_frag(ktile, row_at, s), q[s], c, small);
+        } else {
+          if constexpr (DT > 2 && !kValue) {
+            if (s == KS / 2) {  // d = 128: V takes the registers of the K pieces already multiplied
+              __builtin_amdgcn_sched_barrier(0);
+              load_v(kt, 0, va);
+            }
+          }
+          split_product(split8_raw([&](int e) { return kf[2 * s + e / 4][e % 4]; }), T::row_frag(tiles_at, row_at, s), c, small);
+        }
+      }
+      split_sum<BOUND || kCap>(c, small);
+
+      const int base = kt * kFKT;
+      if constexpr (kCap) {
+        if (kt >= nbt && !sampled) to_samples();
+        const int lim = sampled ? nkeys : nb;
+        if (kValue && kt >= vt0) {
+          if (!drawn) {
+            d_ref = m_run;
+            m_run = -INFINITY;
+            drawn = true;
+          }
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            const f32x4 lw = *reinterpret_cast<const f32x4*>(drawn_w + (kt - vt0) * kFKT + 8 * g + 4 * h);
+#pragma unroll
+            for (int z = 0; z < 4; ++z) c[4 * g + z] = lw[z] == -INFINITY ? -INFINITY : c[4 * g + z] + lw[z];
+          }
+        } else if (sampled || base + kFKT > lim) {
+#pragma unroll
+          for (int i = 0; i < 16; ++i) {
+            const int pos = base + 8 * (i / 4) + 4 * h + (i % 4);
+            c[i] = pos >= lim ? -INFINITY : c[i] + (sampled ? nat_bias : 0.f);
+            if (kValue && sampled && a.cap_scale > 0.f) c[i] = fminf(c[i], log_capw);
           }
         }
-        split_product(split8<true>([&](int e) { return kf[2 * s + e / 4][e % 4]; }), T::row_frag(tiles_at, row_at, s), c, small);
       }
-    }
-    split_sum(c, small);
-
-    const int base = kt * kFKT;
-    if constexpr (kCap) {
-      if (kt >= nbt && !sampled) to_samples();
-      const int lim = sampled ? nkeys : nb;
-      if (kValue && kt >= vt0) {
-        if (!drawn) {
-          d_ref = m_run;
-          m_run = -INFINITY;
-          drawn = true;
-        }
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const f32x4 lw = *reinterpret_cast<const f32x4*>(drawn_w + (kt - vt0) * kFKT + 8 * g + 4 * h);
-#pragma unroll
-          for (int z = 0; z < 4; ++z) c[4 * g + z] = lw[z] == -INFINITY ? -INFINITY : c[4 * g + z] + lw[z];
-        }
-      } else if (sampled || base + kFKT > lim) {
+      const bool plain = kCap || base + kFKT <= min(nkeys, nb) &&
+                         !(MODE == kModeExact && a.exact_causal && w.k0 + base + kFKT - 1 > w.q0 + grp * 32);
+      if (!plain) {
+        int lim = nkeys;
+        if (MODE == kModeExact && a.exact_causal) lim = min(lim, q_global - w.k0 + 1);
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
           const int pos = base + 8 * (i / 4) + 4 * h + (i % 4);
-          c[i] = pos >= lim ? -INFINITY : c[i] + (sampled ? nat_bias : 0.f);
-          if (kValue && sampled && a.cap_scale > 0.f) c[i] = fminf(c[i], log_capw);
+          const float s = c[i] + (pos >= nb ? nat_bias : 0.f);
+          c[i] = pos >= lim ? -INFINITY : s;
         }
       }
-    }
-    const bool plain = kCap || base + kFKT <= min(nkeys, nb) &&
-                       !(MODE == kModeExact && a.exact_causal && w.k0 + base + kFKT - 1 > w.q0 + grp * 32);
-    if (!plain) {
-      int lim = nkeys;
-      if (MODE == kModeExact && a.exact_causal) lim = min(lim, q_global - w.k0 + 1);
+      float mx = c[0];
+#pragma unroll
+      for (int i = 1; i < 16; ++i) mx = fmaxf(mx, c[i]);
+      mx = fmaxf(mx, __shfl_xor(mx, 32));
+      // (the reference only moves by steps of 2^8, as in the bf16 kernel: a rescale is a twelfth of a tile's vector work)
+      if (__any(mx > m_run + 5.5f)) {
+        const float m_new = fmaxf(m_run, mx);
+        const float alpha = expf(m_run - finite_ref(m_new));
+        if (!kValue || kt < vt0) l_run *= kCap ? expf(sum_ref(m_run) - finite_ref(sum_ref(m_new))) : alpha;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) o[dt][i] *= alpha;
+        m_run = m_new;
+      }
+      const float m_use = finite_ref(m_run);
+      float capw = INFINITY;
+      if constexpr (kCap && !kValue) {
+        if (sampled) capw = expf(log_capw - m_use);
+        if (sampled && __any(m_run > log_capw + kFarCap)) {  // rare: exponentials of the sum's own
+          const float ref = finite_ref(sum_ref(m_run));
+#pragma unroll
+          for (int i = 0; i < 16; ++i) l_run += exp_split(fminf(c[i], log_capw) - ref);
+          capw = 0.f;
+        }
+      }
+      float ls[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
-        const int pos = base + 8 * (i / 4) + 4 * h + (i % 4);
-        const float s = c[i] + (pos >= nb ? nat_bias : 0.f);
-        c[i] = pos >= lim ? -INFINITY : s;
+        c[i] = exp_split(c[i] - m_use);
+        ls[i % 4] += kCap ? fminf(c[i], capw) : c[i];
+      }
+      if (!kValue || kt < vt0) l_run += (ls[0] + ls[1]) + (ls[2] + ls[3]);
+      if constexpr (DT == 2) {
+        if (!BOUND && kt + KW < ntiles) load_k(kt + KW);
+      }
+      float vb[kShared ? 1 : 16][DTA];
+      Split8 p[2];  // the weights: elements 8 s ... 8 s + 7 are the lane's keys of step s
+#pragma unroll
+      for (int s = 0; s < 2; ++s) p[s] = split8([&](int e) { return c[8 * s + e]; });
+      auto add_pv = [&](const float (&v)[kShared ? 1 : 16][DTA], int dt0) {
+        if constexpr (!kShared)
+          split_tile_products<DTA, kSumEach, BOUND>([&](int dt, int s) { return split8_raw([&](int e) { return v[8 * s + e][dt]; }); }, p, o + dt0);
+      };
+      if constexpr (kShared) {
+        if (!kValue || kt >= vt0) split_tile_products<DT, kSumTile, BOUND>([&](int dt, int s) { return T::col_frag(vtile, col_at, s, dt); }, p, o);
+        continue;
+      }
+      if constexpr (kValue) {  // V behind the sums, 64 columns at a time (fetched amid the products, under a branch: 168 spills at d = 128)
+        if (DT > 2 && !BOUND && kt + KW < ntiles) load_k(kt + KW);
+        if (kt < vt0) continue;
+#pragma unroll
+        for (int dt0 = 0; dt0 < DT; dt0 += 2) {
+          load_v(kt, dt0, va);
+          add_pv(va, dt0);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        continue;
+      }
+      if constexpr (DT > 2) load_v(kt, 2, vb);
+      add_pv(va, 0);
+      if constexpr (DT > 2) {
+        __builtin_amdgcn_sched_barrier(0);  // the next K rows take the registers of the first half of V
+        if (!BOUND && kt + KW < ntiles) load_k(kt + KW, 0, KJ / 2);
+        add_pv(vb, 2);
+        if (!BOUND && kt + KW < ntiles) load_k(kt + KW, KJ / 2);
       }
     }
-    float mx = c[0];
-#pragma unroll
-    for (int i = 1; i < 16; ++i) mx = fmaxf(mx, c[i]);
-    mx = fmaxf(mx, __shfl_xor(mx, 32));
-    // (the reference only moves by steps of 2^8, as in the bf16 kernel: a rescale is a twelfth of a tile's vector work)
-    if (__any(mx > m_run + 5.5f)) {
-      const float m_new = fmaxf(m_run, mx);
-      const float alpha = expf(m_run - finite_ref(m_new));
-      if (!kValue || kt < vt0) l_run *= kCap ? expf(sum_ref(m_run) - finite_ref(sum_ref(m_new))) : alpha;
-#pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) o[dt][i] *= alpha;
-      m_run = m_new;
+    if constexpr (kCap) {
+      if (!sampled) to_samples();
     }
-    const float m_use = finite_ref(m_run);
-    float capw = INFINITY;
-    if constexpr (kCap && !kValue) {
-      if (sampled) capw = expf(log_capw - m_use);
-      if (sampled && __any(m_run > log_capw + kFarCap)) {  // rare: exponentials of the sum's own
-        const float ref = finite_ref(sum_ref(m_run));
-#pragma unroll
-        for (int i = 0; i < 16; ++i) l_run += exp_split(fminf(c[i], log_capw) - ref);
-        capw = 0.f;
-      }
-    }
-    float ls[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      c[i] = exp_split(c[i] - m_use);
-      ls[i % 4] += kCap ? fminf(c[i], capw) : c[i];
-    }
-    if (!kValue || kt < vt0) l_run += (ls[0] + ls[1]) + (ls[2] + ls[3]);
-    if constexpr (DT == 2) {
-      if (kt + KW < ntiles) load_k(kt + KW);
-    }
-    float vb[kShared ? 1 : 16][DTA];
-    Split8 p[2];  // the weights: elements 8 s ... 8 s + 7 are the lane's keys of step s
-#pragma unroll
-    for (int s = 0; s < 2; ++s) p[s] = split8<false>([&](int e) { return c[8 * s + e]; });
-    auto add_pv = [&](const float (&v)[kShared ? 1 : 16][DTA], int dt0) {
-      if constexpr (!kShared) {
-#pragma unroll
-        for (int s = 0; s < 2; ++s)
-#pragma unroll
-          for (int dt = 0; dt < DTA; ++dt) split_product(split8<true>([&](int e) { return v[8 * s + e][dt]; }), p[s], o[dt0 + dt]);
-      }
-    };
-    if constexpr (kShared) {
-      if (!kValue || kt >= vt0) split_tile_products<DT>([&](int dt, int s) { return T::col_frag(vtile, col_at, s, dt); }, p, o);
-      continue;
-    }
-    if constexpr (kValue) {  // V behind the sums, 64 columns at a time (fetched amid the products, under a branch: 168 spills at d = 128)
-      if (DT > 2 && kt + KW < ntiles) load_k(kt + KW);
-      if (kt < vt0) continue;
-#pragma unroll
-      for (int dt0 = 0; dt0 < DT; dt0 += 2) {
-        load_v(kt, dt0, va);
-        add_pv(va, dt0);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      continue;
-    }
-    if constexpr (DT > 2) load_v(kt, 2, vb);
-    add_pv(va, 0);
-    if constexpr (DT > 2) {
-      __builtin_amdgcn_sched_barrier(0);  // the next K rows take the registers of the first half of V
-      if (kt + KW < ntiles) load_k(kt + KW);
-      add_pv(vb, 2);
-    }
-  }
-  if constexpr (kCap) {
-    if (!sampled) to_samples();
+  };
+  if constexpr (!kShared) __syncthreads();  // the queries stand
+  run(std::false_type{});
+  const SplitFinite<NW> finite{reinterpret_cast<int32_t*>(smem + f32_finite_at<D, KW>(a.g.b, a.g.m, MODE))};
+  finite.post(wave, split_finite(o));
+  __syncthreads();  // the key list is read no more
+  if (!finite.all()) {
+    run(std::true_type{});
+    __syncthreads();
   }
 
   // ---- results: every wave's rows through LDS, where the KW parts of a row are merged and rows
@@ -468,7 +490,6 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 128 && KW < 4 ? 1 : 2) voi
   constexpr int ML = kCap ? 4 : 2;
   const float l_tot = l_run + __shfl_xor(l_run, 32);
   if (kCap && !drawn) d_ref = sum_ref(m_run);
-  __syncthreads();  // the key list is read no more
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt)
 #pragma unroll

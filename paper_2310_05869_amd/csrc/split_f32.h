@@ -28,22 +28,18 @@ struct Split8 {  // eight numbers, a lane's share of an operand
   split_bf16x8 hi, mid, lo;
 };
 
-// INF: the numbers may be infinite or NaN.  lo, which meets the other operand's hi alone, then carries that and hi and mid are finite, so that a
-// product has the sign, and a sum of products the value, that they have in fp32 (an infinite hi times the other's mid or lo, of
-// either sign or 0, would make a NaN of them).
-template <bool INF, class F>
+// An infinity's hi is infinite and its mid and lo are NaN: of its products only that of hi and hi counts (split_bound).
+template <class F>
 __device__ inline Split8 split8(F&& x) {
-  constexpr float kMax = 3.40282347e38f;
   auto upper = [](float v) { return __uint_as_float(__float_as_uint(v) & 0xffff0000u); };
   split_u32x4 h, m, l;
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     const float a = x(2 * e), b = x(2 * e + 1);
-    const float fa = INF ? __builtin_amdgcn_fmed3f(a, -kMax, kMax) : a, fb = INF ? __builtin_amdgcn_fmed3f(b, -kMax, kMax) : b;
-    const float ha = upper(fa), hb = upper(fb);
-    h[e] = __builtin_amdgcn_perm(__float_as_uint(fb), __float_as_uint(fa), 0x07060302u);
-    m[e] = pack_bf16x2(fa - ha, fb - hb);
-    const float la = (a - ha) - __uint_as_float(m[e] << 16), lb = (b - hb) - upper(__uint_as_float(m[e]));
+    const float ra = a - upper(a), rb = b - upper(b);
+    h[e] = __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);
+    m[e] = pack_bf16x2(ra, rb);
+    const float la = ra - __uint_as_float(m[e] << 16), lb = rb - upper(__uint_as_float(m[e]));
     l[e] = __builtin_amdgcn_perm(__float_as_uint(lb), __float_as_uint(la), 0x07060302u);
   }
   Split8 s;
@@ -53,55 +49,133 @@ __device__ inline Split8 split8(F&& x) {
   return s;
 }
 
+// Numbers of the caller's tensors: a NaN among them may have its bits where the upper half of a word does not show them.
+template <class F>
+__device__ inline Split8 split8_raw(F&& x) {
+  return split8([&](int e) { return __builtin_canonicalizef(x(e)); });
+}
+
 __device__ inline split_f32x16 split_mfma(split_bf16x8 a, split_bf16x8 b, split_f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
-// c += a b, the small products first
-__device__ inline void split_product(const Split8& a, const Split8& b, split_f32x16& c) {
-  c = split_mfma(a.lo, b.hi, c);
-  c = split_mfma(a.hi, b.lo, c);
-  c = split_mfma(a.mid, b.mid, c);
-  c = split_mfma(a.mid, b.hi, c);
-  c = split_mfma(a.hi, b.mid, c);
-  c = split_mfma(a.hi, b.hi, c);
-}
-
-// The same with the small products in a sum of their own: a score's rounding is then that of a few additions of 16 terms, and the
-// same whichever operand is a.
-__device__ inline void split_product(const Split8& a, const Split8& b, split_f32x16& big, split_f32x16& small) {
+// The products of a b but that of hi and hi, smallest first
+__device__ inline void split_small(const Split8& a, const Split8& b, split_f32x16& small) {
   small = split_mfma(a.lo, b.hi, small);
   small = split_mfma(a.hi, b.lo, small);
   small = split_mfma(a.mid, b.mid, small);
   small = split_mfma(a.mid, b.hi, small);
   small = split_mfma(a.hi, b.mid, small);
-  big = split_mfma(a.hi, b.hi, big);
 }
 
-// acc[k] += a(k, 0) b[0] + a(k, 1) b[1] for N accumulators: the 32 rows of a tile, rounded once.  Where one wave's sums run over all tiles of a
-// long row, twelve roundings a tile are most of the result's error (exact attention, n = 4013, one way: out 1.1e-6 -> 2.9e-7).  A tile's sum
-// is added while the next accumulator's products run: behind its own the wave waits for the last of them.
-template <int N, class A>
-__device__ inline void split_tile_products(A&& a, const Split8 (&b)[2], split_f32x16 (&acc)[N]) {
-  split_f32x16 t[2];
-#pragma unroll
-  for (int k = 0; k < N; ++k) {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) t[k & 1][i] = 0.f;
-#pragma unroll
-    for (int s = 0; s < 2; ++s) split_product(a(k, s), b[s], t[k & 1]);
-    __builtin_amdgcn_sched_barrier(0);
-    if (k > 0) acc[k - 1] += t[(k - 1) & 1];
-  }
-  acc[N - 1] += t[(N - 1) & 1];
+// Their sum where it is finite, else something finite.  Where an operand is infinite or a product overflows, hi and hi have the result that
+// fp32 has, and what the other products have, an infinity of either sign or NaN, must not be added to it.
+__device__ inline float split_bound(float small) {
+  constexpr float kMax = 3.40282347e38f;
+  return __builtin_amdgcn_fmed3f(small, -kMax, kMax);
+}
+
+// A score's: the small products in a sum of their own, so that its rounding is that of a few additions of 16 terms, and the same whichever
+// operand is a.
+__device__ inline void split_product(const Split8& a, const Split8& b, split_f32x16& big, split_f32x16& small) {
+  split_small(a, b, small);
+  big = split_mfma(a.hi, b.hi, big);
 }
 
 // c += small, here: behind a branch the compiler (ROCm 7.2) counts the wait states from the last product to its first reader along one
 // of the two ways only, and on the other the reader came too early.
+template <bool BOUND>
 __device__ inline void split_sum(split_f32x16& c, const split_f32x16& small) {
-  c += small;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) c[i] += BOUND ? split_bound(small[i]) : small[i];
   asm volatile("" : "+v"(c));
 }
+
+// acc[k] += a(k, 0) b[0] + a(k, 1) b[1] for N accumulators, 32 rows of a tile.
+// kSumTile: a tile's sum is rounded once.  Where one wave's sums run over all tiles of a long row, twelve roundings a tile (kSumEach) are most of
+// the result's error (exact attention, n = 4013, one way: out 1.1e-6 -> 2.9e-7).  The sum is added while the next accumulator's
+// products run: behind its own the wave waits for the last of them.  kSumSmall, three roundings: for the dK / dV passes of one way at d = 64, which
+// have no registers for it (backward, exact, 32 heads, n = 1024 244 -> 226 us, 16 heads, n = 4096 1402 -> 1380).
+// BOUND: the small products are bounded before they are added.  A workgroup forms its sums without that first; only where they hold an infinity or
+// NaN, which a product of parts may have left there, it forms them again with it (SplitFinite).  (Bounded always, exact passes of one way took
+// 8 % longer forward and 15 % backward at d = 128, where a SIMD has one wave; a branch at each tile left the passes 100 to 300 bytes of spills.)
+enum SplitSum { kSumEach, kSumSmall, kSumTile };
+template <int N, SplitSum SUM, bool BOUND, class A>
+__device__ inline void split_tile_products(A&& a, const Split8 (&b)[2], split_f32x16* acc) {
+  if constexpr (BOUND || SUM == kSumSmall) {
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      split_f32x16 t;
+      split_bf16x8 hi[2];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) t[i] = 0.f;
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const Split8 f = a(k, s);
+        split_small(f, b[s], t);
+        hi[s] = f.hi;
+      }
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[k][i] += BOUND ? split_bound(t[i]) : t[i];
+#pragma unroll
+      for (int s = 0; s < 2; ++s) acc[k] = split_mfma(hi[s], b[s].hi, acc[k]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  } else if constexpr (SUM == kSumTile) {
+    split_f32x16 t[2];
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) t[k & 1][i] = 0.f;
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const Split8 f = a(k, s);
+        split_small(f, b[s], t[k & 1]);
+        t[k & 1] = split_mfma(f.hi, b[s].hi, t[k & 1]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if (k > 0) acc[k - 1] += t[(k - 1) & 1];
+    }
+    acc[N - 1] += t[(N - 1) & 1];
+  } else {
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int k = 0; k < N; ++k) {
+        const Split8 f = a(k, s);
+        split_small(f, b[s], acc[k]);
+        acc[k] = split_mfma(f.hi, b[s].hi, acc[k]);
+      }
+  }
+}
+
+// Whether a lane's sums are finite
+template <int N>
+__device__ inline bool split_finite(const split_f32x16 (&acc)[N]) {
+  float z[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int k = 0; k < N; ++k)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) z[i % 4] = __builtin_fmaf(acc[k][i], 0.f, z[i % 4]);
+  return (z[0] + z[1]) + (z[2] + z[3]) == 0.f;
+}
+
+// The same of a workgroup of NW waves: each wave posts its lanes' ahead of a barrier, all read it behind that.
+template <int NW>
+struct SplitFinite {
+  static constexpr int BYTES = NW * 4;
+  int32_t* flags;
+  __device__ void post(int wave, bool finite) const {
+    const int all = __all(finite);
+    if (__lane_id() == 0) flags[wave] = all;
+  }
+  __device__ bool all() const {
+    int f = 1;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) f &= flags[w];
+    return __builtin_amdgcn_readfirstlane(f) != 0;
+  }
+};
 
 // A tile of 32 rows in LDS: three planes of bf16 rows, unpadded; piece c (16 bytes) of row r sits at place c ^ swz(r), which keeps the
 // writes and both readers free of bank conflicts (attn_bwd_mfma.hip's layout).
@@ -114,7 +188,7 @@ struct SplitTile {
     return ((row & 2) << 1) | ((row >> 2) & 3);
   }
   __device__ static void store(unsigned char* tile, int row, int piece, split_f32x4 x0, split_f32x4 x1) {
-    store(tile, row, piece, split8<true>([&](int e) { return e < 4 ? x0[e] : x1[e - 4]; }));
+    store(tile, row, piece, split8_raw([&](int e) { return e < 4 ? x0[e] : x1[e - 4]; }));
   }
   __device__ static void store(unsigned char* tile, int row, int piece, const Split8& s) {
     unsigned char* at = tile + row * ROWB + ((piece ^ swz(row)) << 4);

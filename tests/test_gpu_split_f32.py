@@ -122,3 +122,94 @@ def test_values_of_2_to_the_minus_100(ha, torch, d, H, n):
     ref = _reference(torch, *(x[:, :1] for x in (q, k, v, g)), False)
     assert (out[:, :1].double() - ref[0]).norm() <= 1e-6 * ref[0].norm()
     assert (dq[:, :1].double() - ref[2]).norm() <= 1e-6 * ref[2].norm()
+
+
+# Every form of the kernels: one way, two, four, eight (tests of infinities and of largest numbers).
+FORMS = [(64, 13, 4000, False), (64, 9, 3700, False), (64, 20, 1001, True), (64, 2, 700, False), (128, 8, 4096, False),
+         (128, 9, 2501, True), (128, 2, 700, False)]
+
+
+def _far_scores(torch, q, k, partner, key):
+    """Column 7 carries nothing but key 9's score: partner (both signs of its bits, no two alike) times key."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    q[..., 7] = partner * (1.0 + torch.rand(q.shape[:-1], generator=gen, device="cuda"))
+    k[..., 7] = 0.0
+    k[:, :, 9, 7] = key
+
+
+@pytest.mark.parametrize("partner,key", [(3e5, float("-inf")), (1e20, -1e20), (1e20, -3.4028234e38)])
+@pytest.mark.parametrize("d,H,n,causal", FORMS)
+def test_scores_that_overflow(ha, torch, d, H, n, causal, partner, key):
+    """A score of -inf, as an infinite key or as products past the largest number, is a key without weight, forward and backward: all
+    but the column of dQ that 0 times the key enters, as without the key."""
+    print(f"split fp32 far scores d={d} H={H} n={n} causal={causal} {partner} {key}", flush=True)
+    q, k, v, g = _inputs(torch, H, n, d, n + 1)
+    _far_scores(torch, q, k, partner, key)
+    out, lse = ha.exact_attn_forward(q, k, v, causal=causal)
+    grads = ha.exact_attn_backward(q, k, v, out, lse, g, causal=causal)
+    k0 = k.clone()
+    k0[:, :, 9, 7] = -1e25 / partner  # a score of -1e25: no weight either
+    ref = _reference(torch, *(x[:, H - 1:] for x in (q, k0, v, g)), causal)
+    got = [x[:, H - 1:].double() for x in (out, lse, *grads)]
+    if key == float("-inf"):
+        got[2], ref[2][..., 7] = got[2].clone(), 0.0
+        got[2][..., 7] = 0.0
+    assert ((got[0] - ref[0]).abs() <= 1e-5 + 1e-5 * ref[0].abs()).all()
+    assert ((got[1] - ref[1]).abs() <= 2e-5).all()
+    for x, want in zip(got[2:], ref[2:]):  # (dQ's and dK's column 7 is partner times the others: a norm of its own)
+        for cols in ([7], [c for c in range(d) if c != 7]):
+            assert (x[..., cols] - want[..., cols]).norm() <= 2e-6 * want[..., cols].norm()
+
+
+@pytest.mark.parametrize("value", [0x7f800000, 0x7f800001, 0x7fc00000, 0x7f7fffff])
+@pytest.mark.parametrize("d,H,n,causal", FORMS)
+def test_value_at_the_end_of_the_range(ha, torch, d, H, n, causal, value):
+    """One value, infinite, NaN (a signalling one too) or the largest number: its column is that times its weight, the others are as without it;
+    the other way round, through dO, for dV."""
+    print(f"split fp32 last values d={d} H={H} n={n} causal={causal} {value:#x}", flush=True)
+    q, k, v, g = _inputs(torch, H, n, d, n + 2)
+    x = torch.tensor([value], dtype=torch.int32).view(torch.float32).item() if value != 0x7f800001 else None
+    for t, row in ((v, 5), (g, n - 1)):
+        t[..., 3] = 0.0
+        if x is None:
+            t.view(torch.int32)[:, :, row, 3] = value
+        else:
+            t[:, :, row, 3] = x
+    out, lse = ha.exact_attn_forward(q, k, v, causal=causal)
+    v1 = v.clone()
+    v1[..., 3] = 0.0
+    out1, lse1 = ha.exact_attn_forward(q, k, v1, causal=causal)
+    s = torch.matmul(q[:, :1].double(), k[:, :1].double().transpose(-1, -2).contiguous())
+    weights = torch.exp(s - lse[:, :1, :, None].double())
+    rows = slice(5, n) if causal else slice(0, n)
+    assert torch.equal(lse, lse1)
+    other = [c for c in range(d) if c != 3]
+    assert ((out[..., other] - out1[..., other]).abs() <= 1e-5 + 1e-5 * out1[..., other].abs()).all()
+    dv = ha.exact_attn_backward(q, k, v1, out1, lse1, g, causal=causal)[2]
+    seen = {0x7f800000: torch.isposinf, 0x7f800001: torch.isnan, 0x7fc00000: torch.isnan}.get(value)
+    if seen is not None:
+        assert seen(out[:, :, rows, 3]).all() and seen(dv[..., 3]).all()
+    else:
+        for got, want in ((out[:, :1, rows, 3].double(), weights[:, :, rows, 5] * x), (dv[:, :1, :, 3].double(), weights[:, :, n - 1, :] * x)):
+            assert ((got - want).abs() <= 2e-5 * want.abs()).all()
+    assert torch.isfinite(dv[..., other]).all()
+
+
+@pytest.mark.parametrize("d,H,n,b,m,causal,n_min", [(64, 16, 4096, 128, 128, False, 4096), (64, 8, 4096, 256, 256, False, 4096), (64, 2, 2048, 64, 64, True, 512),
+                                                    (128, 8, 4096, 256, 256, False, 4096), (128, 2, 2048, 64, 64, True, 512)])
+def test_scores_that_overflow_in_nodes(ha, torch, d, H, n, b, m, causal, n_min):
+    """The same through the blocks and samples: bit for bit what scores of -1e25, which overflow nowhere, give."""
+    print(f"split fp32 far scores, nodes d={d} H={H} n={n} b={b} m={m} causal={causal}", flush=True)
+    q, k, v, g = _inputs(torch, H, n, d, n + 3)
+    shape, params = ha.make_shape(1, H, n, d, ha.HA_FP32), ha.make_params(b, m, 7, causal, n_min, 0)
+    got = []
+    for key in (-1e20, -1e5):
+        _far_scores(torch, q, k, 1e20, key)
+        ws = ha.alloc_workspace(shape, params)
+        out, lse = ha.hyperattn_forward(q, k, v, b, m, 7, causal=causal, n_min=n_min, seed=0, workspace=ws)
+        got.append((out, lse, *ha.hyperattn_backward(q, k, v, out, lse, g, b, m, 7, causal=causal, n_min=n_min, seed=0, fwd_workspace=ws)))
+    for x, want in zip(*got):
+        assert torch.isfinite(want).all()
+        assert torch.equal(x, want)
+

@@ -398,7 +398,7 @@ __device__ __forceinline__ void bwd_f32_pass(const BwdArgs& a, const int wg, con
         for (int i = 0; i < 16; ++i) {
           const int tpos = tbase + 8 * (i / 4) + 4 * h + (i % 4);
           bool masked = tpos >= nT;
-          if (MODE == kBwdDqNode && tbase < nb && tpos >= nb) c[i] += nat_bias;
+          if (MODE == kBwdDqNode && tbase < nb && tpos >= nb) c[i] += nat_bias * (1.f / kSplitScore);
           // queries of the key's own block: factor 1 - M of Algorithm 2
           if (MODE == kBwdDkvSamp) masked = masked || (unsigned)(b.chunk_start + tpos - blk_r * g.b) < (unsigned)g.b;
           if (MODE == kBwdDqExact && f.exact_causal) masked = masked || (w.k0 + tpos > r_row);   // keys after the query
@@ -415,10 +415,10 @@ __device__ __forceinline__ void bwd_f32_pass(const BwdArgs& a, const int wg, con
         const bool quads = kShared || kExact;
         const float L = kDq ? L_r : quads ? l4[i / 4][i % 4] : of_elem(scl_c, i);
         const float dl = kDq ? del_r : quads ? d4[i / 4][i % 4] : of_elem(scd_c, i);
-        float p = exp_split(c[i] + tile_bias - L);
+        float p = exp_split(__builtin_fmaf(c[i], kSplitScore, tile_bias) - L);
         if (L == -INFINITY) p = 0.f;  // (a row without keys)
         c[i] = p;
-        e[i] = p * (e[i] - dl);
+        e[i] = p * __builtin_fmaf(e[i], kSplitScore, -dl);
       }
       Split8 ps[2];  // 16 T rows each
       if constexpr (kShared) {
@@ -482,7 +482,7 @@ __device__ __forceinline__ void bwd_f32_pass(const BwdArgs& a, const int wg, con
 #pragma unroll
       for (int q4 = 0; q4 < 4; ++q4)
         *reinterpret_cast<f32x4*>(rows_lds + (wave * 32 + lq) * RS + 32 * dt + 8 * q4 + 4 * h) =
-            (f32x4){acc[dt][4 * q4], acc[dt][4 * q4 + 1], acc[dt][4 * q4 + 2], acc[dt][4 * q4 + 3]};
+            (f32x4){acc[dt][4 * q4], acc[dt][4 * q4 + 1], acc[dt][4 * q4 + 2], acc[dt][4 * q4 + 3]} * (1.f / kSplitRaw);
     __syncthreads();
     constexpr int LPR = D / 4;  // lanes per row
     for (int idx = tid; idx < w.rows_valid * LPR; idx += kFBT) {

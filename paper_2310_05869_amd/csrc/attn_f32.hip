@@ -364,7 +364,10 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 128 && KW < 4 ? 1 : D == 6
       split_sum<BOUND || kCap>(c, small);
 
       const int base = kt * kFKT;
+      constexpr float kUnit = kCap ? 1.f : kSplitScore;  // of c: biases are divided by it, what is read of c multiplied
       if constexpr (kCap) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) c[i] *= kSplitScore;
         if (kt >= nbt && !sampled) to_samples();
         const int lim = sampled ? nkeys : nb;
         if (kValue && kt >= vt0) {
@@ -396,14 +399,14 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 128 && KW < 4 ? 1 : D == 6
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
           const int pos = base + 8 * (i / 4) + 4 * h + (i % 4);
-          const float s = c[i] + (pos >= nb ? nat_bias : 0.f);
+          const float s = c[i] + (pos >= nb ? nat_bias * (1.f / kUnit) : 0.f);
           c[i] = pos >= lim ? -INFINITY : s;
         }
       }
       float mx = c[0];
 #pragma unroll
       for (int i = 1; i < 16; ++i) mx = fmaxf(mx, c[i]);
-      mx = fmaxf(mx, __shfl_xor(mx, 32));
+      mx = fmaxf(mx, __shfl_xor(mx, 32)) * kUnit;
       // (the reference only moves by steps of 2^8, as in the bf16 kernel: a rescale is a twelfth of a tile's vector work)
       if (__any(mx > m_run + 5.5f)) {
         const float m_new = fmaxf(m_run, mx);
@@ -429,7 +432,7 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 128 && KW < 4 ? 1 : D == 6
       float ls[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
-        c[i] = exp_split(c[i] - m_use);
+        c[i] = exp_split(__builtin_fmaf(c[i], kUnit, -m_use));
         ls[i % 4] += kCap ? fminf(c[i], capw) : c[i];
       }
       if (!kValue || kt < vt0) l_run += (ls[0] + ls[1]) + (ls[2] + ls[3]);
@@ -495,7 +498,7 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 128 && KW < 4 ? 1 : D == 6
 #pragma unroll
     for (int g = 0; g < 4; ++g)
       *reinterpret_cast<f32x4*>(orow + (wave * 32 + lq) * RS + 32 * dt + 8 * g + 4 * h) =
-          (f32x4){o[dt][4 * g], o[dt][4 * g + 1], o[dt][4 * g + 2], o[dt][4 * g + 3]};
+          (f32x4){o[dt][4 * g], o[dt][4 * g + 1], o[dt][4 * g + 2], o[dt][4 * g + 3]} * (1.f / kSplitRaw);
   if (h == 0) {
     ml[(wave * 32 + lq) * ML] = m_run;
     ml[(wave * 32 + lq) * ML + 1] = l_tot;

@@ -1,17 +1,21 @@
 // fp32 products on the bf16 matrix cores, to the precision of fp32 ones.
 //
-// A float's 24 significant bits are three bf16 numbers of 8: x = hi + mid + lo, without remainder (hi: the upper half of x's bits; mid:
-// what is left, rounded; lo: what is left then).  Of the nine products of two such numbers the six that reach 2^-22 of the
-// whole are formed, exactly, and summed in fp32 by v_mfma_f32_32x32x16_bf16: six instructions of 32 cycles for 16 terms, where
-// v_mfma_f32_32x32x2_f32 takes eight of 64.  The sums are rounded once per 16 terms instead of once per two, which is worth more than the three
-// products left out.  Errors against 64 bits, fp32 instruction -> split (2-norm, relative; exact attention, 2 heads, n = 2048,
-// d = 64): out 4.2e-7 -> 2.9e-7, dQ 5.4e-7 -> 4.4e-7, dK 5.4e-7 -> 4.3e-7, dV 5.1e-7 -> 4.2e-7; causal 2.6e-7 -> 1.5e-7, 3.6e-7 -> 2.6e-7, 5.1e-7 -> 3.8e-7,
-// 4.6e-7 -> 3.6e-7; 64 clusters, scores to 250: 9.3e-6 -> 4.3e-6, 2.2e-5 -> 1.2e-5, 2.1e-5 -> 1.2e-5, 1.2e-5 -> 8.6e-6; d = 128 likewise.
-// The matrix cores take parts below 2^-126 as zeros: a number keeps its 24 bits down to 2^-110, 16 at 2^-118.  Errors of dQ at values of 2^-100 are
-// those of 1 (5.1e-7 against 5.0e-7), at 2^-110 4e-5, where fp32 instructions hold 6e-7 down to 2^-116: 2^-100 is what the criterion for
+// A float's 24 significant bits are three bf16 numbers: x = hi + mid + lo, without remainder (hi: x rounded to 8 bits; mid: what is left,
+// rounded; lo: what is left then).  Of the nine products of two such numbers six are formed, exactly, and summed in fp32 by
+// v_mfma_f32_32x32x16_bf16: six instructions of 32 cycles for 16 terms, where v_mfma_f32_32x32x2_f32 takes eight of 64.  The three left out are at
+// most 2^-24.2 of the whole; one product, rounded, is off by at most 2^-23.2, r.m.s. 2^-25.21 over all mantissas (a fused fp32 product 2^-24,
+// 2^-25.24).  (hi cut off instead of rounded: 2^-22 and 2^-24.85.  mid lo and lo mid formed as well: 2^-24 and 2^-25.24, for 5 to 20 % of
+// the calls' time.)  The sums are rounded once per 16 terms instead of once per two, so that errors fall wherever more than a term or two counts.
+// Errors against 64 bits, fp32 instruction -> split (2-norm, relative; exact attention, 2 heads, n = 2048):
+//   d = 64: out 4.3e-7 -> 2.9e-7, dQ 5.4e-7 -> 4.3e-7, dK 5.5e-7 -> 4.3e-7, dV 5.7e-7 -> 4.6e-7; causal 2.7e-7 -> 1.5e-7, 3.6e-7 -> 2.5e-7, 5.0e-7 -> 3.6e-7,
+//   4.7e-7 -> 3.5e-7; 64 clusters, scores to 250: 2.0e-5 -> 8.6e-6, 2.2e-5 -> 1.3e-5, 1.9e-5 -> 9.3e-6, 2.1e-5 -> 9.9e-6; d = 128 likewise
+//   scores to 250 and gradients that one column carries (geometric means of eight shapes): dK 2.6e-7 -> 2.3e-7, dV 2.5e-7 -> 1.9e-7, largest of a log row
+//   sum 1.5e-5 both; two of d columns: dQ 9.4e-6 -> 9.1e-6, dK 1.5e-5 -> 1.4e-5, dV 3.1e-6 -> 3.4e-6, log row sum 1.2e-4 -> 8.5e-5
+// The matrix cores take parts below 2^-126 as zeros: a number keeps its 24 bits down to 2^-102 in any case, 16 at 2^-117, none below 2^-125.  Errors of dQ at
+// values of 2^-100 are those of 1 (5.1e-7 against 5.0e-7); fp32 instructions hold theirs down to 2^-116.  2^-100 is what the criterion for
 // gradients takes for zero.
 //
-// What it costs is vector work: 15 instructions per two numbers, 240 for a wave's operand of 32 rows of 64 floats, beside 24 products.  So
+// What it costs is vector work: 13 instructions per two numbers, 208 for a wave's operand of 32 rows of 64 floats, beside 24 products.  So
 // where several waves use a tile it is split once and kept in LDS (SplitTile).
 #pragma once
 
@@ -31,15 +35,16 @@ struct Split8 {  // eight numbers, a lane's share of an operand
 // An infinity's hi is infinite and its mid and lo are NaN: of its products only that of hi and hi counts (split_bound).
 template <class F>
 __device__ inline Split8 split8(F&& x) {
-  auto upper = [](float v) { return __uint_as_float(__float_as_uint(v) & 0xffff0000u); };
+  auto upper = [](uint32_t w) { return __uint_as_float(w & 0xffff0000u); };
+  auto lower = [](uint32_t w) { return __uint_as_float(w << 16); };
   split_u32x4 h, m, l;
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     const float a = x(2 * e), b = x(2 * e + 1);
-    const float ra = a - upper(a), rb = b - upper(b);
-    h[e] = __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);
+    h[e] = pack_bf16x2(a, b);
+    const float ra = a - lower(h[e]), rb = b - upper(h[e]);
     m[e] = pack_bf16x2(ra, rb);
-    const float la = ra - __uint_as_float(m[e] << 16), lb = rb - upper(__uint_as_float(m[e]));
+    const float la = ra - lower(m[e]), lb = rb - upper(m[e]);
     l[e] = __builtin_amdgcn_perm(__float_as_uint(lb), __float_as_uint(la), 0x07060302u);
   }
   Split8 s;
@@ -49,10 +54,11 @@ __device__ inline Split8 split8(F&& x) {
   return s;
 }
 
-// Numbers of the caller's tensors: a NaN among them may have its bits where the upper half of a word does not show them.
+// Numbers of the caller's tensors, at half their value: rounding hi up leaves the largest ones finite.
+constexpr float kSplitRaw = 0.5f;
 template <class F>
 __device__ inline Split8 split8_raw(F&& x) {
-  return split8([&](int e) { return __builtin_canonicalizef(x(e)); });
+  return split8([&](int e) { return x(e) * kSplitRaw; });
 }
 
 __device__ inline split_f32x16 split_mfma(split_bf16x8 a, split_bf16x8 b, split_f32x16 c) {
@@ -83,7 +89,9 @@ __device__ inline void split_product(const Split8& a, const Split8& b, split_f32
 }
 
 // c += small, here: behind a branch the compiler (ROCm 7.2) counts the wait states from the last product to its first reader along one
-// of the two ways only, and on the other the reader came too early.
+// of the two ways only, and on the other the reader came too early.  Of raw operands the sum is the score times kSplitRaw^2; kSplitScore takes it
+// back where its reader has an fma for it.
+constexpr float kSplitScore = 1.f / (kSplitRaw * kSplitRaw);
 template <bool BOUND>
 __device__ inline void split_sum(split_f32x16& c, const split_f32x16& small) {
 #pragma unroll

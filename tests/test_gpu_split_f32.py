@@ -213,3 +213,52 @@ def test_scores_that_overflow_in_nodes(ha, torch, d, H, n, b, m, causal, n_min):
         assert torch.isfinite(want).all()
         assert torch.equal(x, want)
 
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_one_product(ha, torch, d):
+    """The first row of a causal head has one key, and its log row sum is their score: with one column each, a single product of two numbers.
+    Its parts leave out at most 2^-24.2 of it, and it is rounded once: at most 2^-23.1; r.m.s. over all mantissas 2^-25.21 (2^-25.24 rounded
+    alone, as a fused fp32 product is), here within what 8192 samples scatter."""
+    print(f"split fp32 one product d={d}", flush=True)
+    H, n = 8192, 32
+    q, k, v = _inputs(torch, H, n, d, d + 5, 3)
+    for t in (q, k):
+        t.zero_()
+        t[..., d - 5] = torch.rand(t.shape[:-1], generator=torch.Generator(device="cuda").manual_seed(11 if t is q else 12), device="cuda") + 1.0
+    _, lse = ha.exact_attn_forward(q, k, v, causal=True)
+    want = q[:, :, 0, d - 5].double() * k[:, :, 0, d - 5].double()
+    err = (lse[:, :, 0].double() - want) / want
+    assert err.abs().max() <= 2.0 ** -23.1
+    assert err.square().mean().sqrt() <= 2.0 ** -25.1
+
+
+@pytest.mark.parametrize("kind", ["one column", "sparse"])
+@pytest.mark.parametrize("d,H,n,causal", FORMS)
+def test_products_that_few_terms_carry(ha, torch, d, H, n, causal, kind):
+    """Scores to 250 and gradients that one column carries, or two of d columns: next to no term whose rounding could average the others'.  Errors
+    (2-norm; largest of a log row sum) as of products and sums in fp32, whose matrix instructions have, over eight shapes, geometric
+    means, split in brackets: one column: dK 2.6e-7 (2.3e-7), dV 2.5e-7 (1.9e-7), lse 1.5e-5 (1.5e-5); sparse: dK 1.5e-5 (1.4e-5), dV
+    3.1e-6 (3.4e-6), lse 1.2e-4 (8.5e-5).  Bounds: lse, scores of s each rounded to 2^-23 s and once more in the sum, 2^-22 of the largest score;
+    gradients of one column, products to 2^-23 with weights to the scores' errors, where both average over n, 1e-6."""
+    print(f"split fp32 few terms d={d} H={H} n={n} causal={causal} {kind}", flush=True)
+    q, k, v, g = _inputs(torch, H, n, d, n + 4)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n)
+    if kind == "one column":
+        for t, col, scale, low, width in ((q, 5, 2.0 ** -12, 6.0, 10.0), (k, 5, 2.0 ** -12, 6.0, 10.0), (v, 7, 2.0 ** -14, 1.0, 1.0), (g, 7, 2.0 ** -14, 1.0, 1.0)):
+            t *= scale
+            t[..., col] = torch.rand(t.shape[:-1], generator=gen, device="cuda") * width + low
+    else:
+        for t in (q, k, v, g):
+            t *= (torch.rand(t.shape, generator=gen, device="cuda") < 2 / d) * (d / 2)
+    out, lse = ha.exact_attn_forward(q, k, v, causal=causal)
+    grads = ha.exact_attn_backward(q, k, v, out, lse, g, causal=causal)
+    ref = _reference(torch, *(x[:, :1] for x in (q, k, v, g)), causal)
+    top = torch.matmul(q[:, :1].double(), k[:, :1].double().transpose(-1, -2).contiguous()).abs().max().item()
+    assert (lse[:, :1].double() - ref[1]).abs().max() <= 2.0 ** -22 * max(top, 1.0)
+    if kind == "one column":
+        for got, want in zip(grads[1:], ref[3:]):
+            assert (got[:, :1].double() - want).norm() <= 1e-6 * want.norm()
+    else:
+        for got, want, bound in zip(grads, ref[2:], (6e-5, 6e-5, 2e-5)):
+            assert (got[:, :1].double() - want).norm() <= bound * want.norm()

@@ -617,35 +617,37 @@ static int f32_ways(int d, int run, int64_t grid128, bool causal) {
 
 static int f32_node_ways(const Geometry& g) { return f32_ways(g.d, g.b, node_grid<128>(g), false); }
 
-// Whether a node launch sorts by itself (attn_mfma_sorts, for the kernel without it): up to 1024 workgroups (of 128 rows where there are 512 of
-// those, of 64 from 256 of 128 rows on, else of 32: the forms of the kernel whose limits these are; its ways are now f32_ways'); at d = 128 fewer, since
-// a workgroup that sorts counts its whole node.  Sorting launch -> in the attention (MI355X, us):
-//   d = 64, b = m = 64: one head, n = 1024 19.7 -> 16.4; 8 heads, n = 2048 25.3 -> 21.7, 16 34.7 -> 30.4, 18 44.5 -> 42.7, 24 46.9 -> 44.5; 16
-//     heads, n = 4096 56.3 -> 54.2; 2 heads, n = 8192 26.2 -> 23.3; b = m = 128: 8 heads, n = 2048 27.9 -> 25.4, 32 62.0 -> 57.4, 52 97.4 -> 92.5;
-//     b = m = 256: 4 heads, n = 4096 37.6 -> 34.6, 8 55.6 -> 51.6; 24 heads, n = 2000, b = 100, m = 77 51.4 -> 46.5; 8 heads, n = 4096, b = 32 35.8 -> 34.1
-//   d = 128, b = m = 64: one head, n = 1024 23.5 -> 19.7; 8 heads, n = 2048 37.4 -> 33.1, 18 66.9 -> 66.1, 24 77.5 -> 77.7; 16 heads, n = 4096 98.7 ->
-//     101.5; b = m = 128: 8 heads, n = 2048 43.1 -> 39.1, 32 121.2 -> 115.8, 44 160.9 -> 162.7; 12 heads, n = 4096 99.5 -> 100.1; b = m = 256: 4 heads,
-//     n = 4096 62.0 -> 57.1, 8 95.3 -> 87.4; 24 heads, n = 2000, b = 100, m = 77 96.4 -> 92.3; 8 heads, n = 4096, b = 32 56.0 -> 54.3
-// Not where the sort's tables cost a CU one of its workgroups and the call needs it: it then loses more the longer the attention is.  (Measured
-// on the form with fp32 products: d = 64, b = 64, m = 1000: 6 heads, n = 6144 (576 workgroups) 152.9 -> 160.0; r = 8: 9 heads, n = 4096 (576)
-// 152.0 -> 157.7; b = 128, m = 2000, 8 heads, n = 8192 (512, one to a CU) 352 -> 396; d = 128, the same 643 -> 723.)
-template <int D>
-static bool f32_tables_cost(const Geometry& g, int64_t wgs, int kw) {
-  const size_t rows = F32Lds<D>::BYTES, sort = f32_sort_end(g), list = f32_list_bytes(g.b, g.m, kModeNode);
-  const int64_t sorting = lds_workgroups((sort > rows ? sort : rows) + 128 / kw * 4, D == 64 ? 3 : 2);
-  return wgs > 256 * sorting && sorting < lds_workgroups(list > rows ? list : rows, D == 64 ? 3 : 2);
+// Workgroups of a node launch that a CU holds by their registers
+static constexpr int f32_places(int d, int kw) { return d == 64 ? (kw == 4 ? 3 : 2) : kw == 4 ? 2 : 1; }
+
+// Whether the sort's tables in the LDS cost a CU one of the workgroups that the launch needs it to hold
+template <int D, int KW>
+static bool f32_tables_cost(const Geometry& g, int64_t wgs) {
+  const int64_t sorting = lds_workgroups(f32_qrows_at<D, KW>(g) + 128 / KW * 4, f32_places(D, KW));
+  return wgs > 256 * sorting && sorting < lds_workgroups(f32_lds_bytes<D, KW>(g.b, g.m, kModeNode), f32_places(D, KW));
 }
 
+// Whether a node launch sorts by itself (attn_mfma_sorts, for the kernel without it): up to 1024 workgroups of the form that is launched
+// (f32_node_ways), each of which counts its whole node, and up to 2^22 rows counted.  Sorting launch -> in the attention (MI355X, us; workgroups):
+//   d = 64, four ways: b = m = 64: one head, n = 1024 (32) 20.9 -> 17.7; b = m = 256, 6 heads, n = 4096 (768) 48.3 -> 45.0, 3 heads, n = 8192 (768) 48.7 ->
+//     51.6; n = 4096, b = 32: 8 heads (1024) 36.1 -> 35.5, 12 (1536) 46.8 -> 46.9, 16 (2048) 54.6 -> 56.7
+//   two: b = m = 64: 16 heads, n = 2048 (512) 35.4 -> 31.2, n = 4096: 9 (576) 46.6 -> 45.3, 16 (1024) 56.7 -> 55.1, 17 (1088) 64.9 -> 67.1, 20 (1280) 67.4 ->
+//     68.9; n = 8192: 4 (512) 36.7 -> 33.4, 6 (768) 49.5 -> 49.6; n = 6144: 7 (672) 47.8 -> 48.1, 12 (1152) 65.7 -> 69.6
+//   one: b = m = 128: 32 heads, n = 2048 (512) 62.6 -> 58.0, 64 (1024) 106.1 -> 103.6, 48, n = 4096 (1536) 145.3 -> 145.5; b = m = 256, 6 heads, n = 8192
+//     (384) 80.6 -> 76.8; n = 2000, b = 100, 64 heads (1280) 101.3 -> 101.5, 90 (1800) 138.9 -> 140.7
+//   d = 128, four: b = m = 64: one head, n = 1024 (32) 24.6 -> 20.9; 16 heads, n = 2048 (1024) 58.6 -> 56.4, 18 (1152) 68.4 -> 68.2, 24 (1536) 79.4 -> 79.6, 32
+//     (2048) 100.0 -> 102.2; b = m = 128: 24 (1536) 96.9 -> 96.7, 36 (2304) 135.3 -> 138.7, 44 (2816) 160.7 -> 164.5, 52 (3328) 185.2 -> 192.4; b = m = 256,
+//     6 heads, n = 4096 (768) 82.7 -> 80.0, 10 (1280) 119.9 -> 119.8, 20 (2560) 216.0 -> 219.8; b = m = 64, n = 8192: 2 (512) 39.1 -> 35.0, 3 (768)
+//     51.0 -> 50.9, 6 (1536) 81.1 -> 83.4
+//   one: b = m = 128: 16 heads, n = 2048 (256) 70.2 -> 63.5, 64 (1024) 229.8 -> 223.1, n = 8192: 4 (256) 71.1 -> 65.2, 8 (512) 127.1 -> 122.6
+// Not where the tables cost a CU one of its workgroups and the call needs it: b = 128, m = 2000, r = 8, n = 8192: d = 64, 2 heads (four ways, 512) 96.8 ->
+// 113.1, 8 (one, 512) 256.8 -> 320.3; d = 128, 2 heads (four, 512) 158.6 -> 182.6, but 8 (one, 512, of which a CU holds one in any case) 546.5 -> 542.3.
 bool attn_f32_sorts(const Geometry& g) {
-  const int rows = node_sort_rows(g);
-  const int64_t tiles = node_grid<128>(g);
-  const int kw = tiles >= 512 && f32_fits(g.b, 128) ? 1 : tiles >= 256 && f32_fits(g.b, 64) ? 2 : 4;
-  const int64_t wgs = kw == 1 ? tiles : kw == 2 ? node_grid<64>(g) : node_grid<32>(g);
+  const int rows = node_sort_rows(g), kw = f32_node_ways(g);
+  const int64_t wgs = kw == 1 ? node_grid<128>(g) : kw == 2 ? node_grid<64>(g) : node_grid<32>(g);
   if (rows > kNodeSortMax || wgs > 1024 || wgs * rows > 4 << 20) return false;
-  if (g.b + g.m > 320 && (g.d == 64 ? f32_tables_cost<64>(g, wgs, kw) : f32_tables_cost<128>(g, wgs, kw))) return false;
-  if (g.d == 64 || 4 * g.b < 3 * 64) return true;
-  if (kw > 1 && wgs * rows > 5 << 19) return false;
-  return wgs <= (kw == 4 ? 512 : kw == 1 && g.b % 128 == 0 ? 704 : 576) || (kw == 1 && wgs > 768);
+  if (g.d == 128) return !(kw == 1 ? f32_tables_cost<128, 1>(g, wgs) : f32_tables_cost<128, 4>(g, wgs));
+  return !(kw == 1 ? f32_tables_cost<64, 1>(g, wgs) : kw == 2 ? f32_tables_cost<64, 2>(g, wgs) : f32_tables_cost<64, 4>(g, wgs));
 }
 
 // Exact launches of few workgroups and long rows are bound by the longest chain of key tiles: eight waves then share 32 queries,

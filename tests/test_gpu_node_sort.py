@@ -42,6 +42,10 @@ CASES = [  # dtype, d, B, H, n, b, m, r, n_min (0: unmasked)
     ("fp32", 64, 2, 8, 2048, 256, 256, 7, 0),
     ("fp32", 64, 1, 16, 4096, 128, 64, 7, 0),      # one wave per group of rows
     ("fp32", 128, 1, 32, 2048, 128, 0, 7, 0),      # likewise, no samples
+    ("fp32", 128, 1, 8, 8192, 128, 2000, 8, 0),    # likewise, the longest node, the most that its LDS holds
+    ("fp32", 64, 1, 6, 8192, 256, 256, 7, 0),      # likewise
+    ("fp32", 64, 1, 9, 4096, 64, 1000, 8, 0),      # two
+    ("fp32", 128, 1, 16, 2048, 64, 64, 7, 0),      # four, the most workgroups
 ]
 
 EIGHT_WAVES = [  # more than 256 tiles of 128 rows, at most 256 of 256: workgroups of eight waves

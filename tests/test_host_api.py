@@ -195,27 +195,28 @@ def test_backward_shared_launches_hold_their_workgroups(ha):
     (128, 32, 1024, 64, 64, 7, 0, True),
     (128, 33, 1024, 64, 64, 7, 0, False),      # two to a CU
 ]] + [("fp32", *c) for c in [
-    (64, 16, 4096, 64, 64, 7, 0, True),        # 1024 workgroups
+    (64, 16, 4096, 64, 64, 7, 0, True),        # two ways: 1024 workgroups
     (64, 17, 4096, 64, 64, 7, 0, False),
-    (64, 9, 4096, 64, 1000, 7, 0, True),       # 576: three fit the LDS
-    (64, 9, 4096, 64, 1000, 8, 0, False),      # two
-    (64, 8, 4096, 64, 1000, 8, 0, True),       # 512
+    (64, 9, 4096, 64, 1000, 8, 0, True),       # 576, of which a CU holds two by their registers and by their tables
+    (64, 2, 8192, 128, 2000, 7, 0, True),      # four ways, 512: three by their registers, two by the LDS
+    (64, 2, 8192, 128, 2000, 8, 0, False),     # with more buckets' tables one
+    (64, 8, 8192, 128, 2000, 7, 0, True),      # one way, 512: two
     (64, 8, 8192, 128, 2000, 8, 0, False),     # one
-    (64, 7, 6144, 64, 64, 8, 0, True),         # two, of few keys
-    (128, 8, 8192, 128, 2000, 8, 0, False),    # one
-    (128, 48, 2048, 128, 128, 7, 0, False),    # of 128 rows: 768
-    (128, 44, 2048, 128, 128, 7, 0, True),     # 704
-    (128, 52, 2048, 128, 128, 7, 0, True),     # 832
-    (128, 61, 1000, 100, 64, 7, 0, False),     # 610, blocks that the tiles do not divide
-    (128, 18, 2048, 64, 64, 7, 0, True),       # of 64 rows: 576
-    (128, 24, 2048, 64, 64, 7, 0, False),      # 768
-    (128, 32, 2048, 64, 64, 7, 0, False),      # 1024
-    (128, 2, 8192, 64, 64, 7, 0, True),        # 256 of 8192 keys
-    (128, 4, 8192, 128, 128, 7, 0, False),     # 512
-    (128, 4, 4096, 256, 256, 7, 0, True),      # of 32 rows: 512
-    (128, 6, 4096, 256, 256, 7, 0, False),     # 768
+    (64, 6, 8192, 256, 256, 7, 0, True),       # one way, 384 of 8192 keys
+    (64, 3, 8192, 256, 256, 7, 0, False),      # four, 768
+    (128, 8, 8192, 128, 2000, 8, 0, True),     # one way, 512, of which a CU holds one in any case
+    (128, 2, 8192, 128, 2000, 8, 0, False),    # four, 512: the tables cost the second
+    (128, 48, 2048, 128, 128, 7, 0, True),     # one way, 768
+    (128, 44, 2048, 128, 128, 7, 0, False),    # four, 2816
+    (128, 16, 2048, 64, 64, 7, 0, True),       # four, 1024
+    (128, 18, 2048, 64, 64, 7, 0, False),      # 1152
+    (128, 61, 1000, 100, 64, 7, 0, False),     # blocks that the tiles do not divide: 2440
+    (128, 2, 8192, 64, 64, 7, 0, True),        # 512 of 8192 keys
+    (128, 3, 8192, 64, 64, 7, 0, False),       # 768
+    (128, 4, 8192, 128, 128, 7, 0, True),      # one way, 256
+    (128, 6, 4096, 256, 256, 7, 0, True),      # four, 768
     (128, 8, 4096, 32, 64, 7, 0, True),        # 1024, of blocks that 64 rows do not fill
-    (128, 12, 4096, 64, 64, 7, 1024, False),   # two levels, 768
+    (128, 12, 4096, 64, 64, 7, 1024, False),   # two levels, 1536
 ]])
 def test_forward_sorts_in_the_attention_launch(ha, dtype, d, H, n, b, m, r, n_min, sorts):
     """While its workgroups fit the chip, the sort's tables in the LDS counted."""

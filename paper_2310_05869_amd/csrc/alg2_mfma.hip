@@ -75,8 +75,9 @@ __host__ __device__ inline size_t a2_lds_bytes(const Geometry& g) {
 // A trip ends for all waves at one barrier, and waves that all begin with their products leave the vector units idle, then the matrix
 // cores: the second group adds up its previous tile first.  (Vector instructions were 59 % of the kernel's cycles, products 32 %, and they added
 // up.)  Tiles come by DMA, NB - 1 of them ahead, into LDS in rows of D * 2 bytes, unpadded: piece c (16 bytes) of row r at place c ^ swz(r), free
-// of bank conflicts for the row reads.  The positions' rows are kept ahead of them in LDS too, in chunks of four trips: a load of
-// an index that is waited for in registers would be a wait for every tile requested before it.
+// of bank conflicts for the row reads.  The positions' rows are kept ahead of them in LDS too, in chunks of four trips, and come by DMA
+// as well: a load of an index into a register is waited for with every tile requested before it (twice a chunk, the compiler's count
+// knowing nothing of the DMA; 16 heads, n = 16384, d = 128 165.1 -> 163.0, 24 heads, m = 512 312.7 -> 309.7, d = 64 1 %).
 // Forward with the caps (MI355X, us), tiles through registers, in step and with the maxima of every tile -> this; d = 128, m = 256: 16
 // heads, n = 16384 173 -> 166, 8 heads 115 -> 106, 4 heads, n = 4096 46.5 -> 45.8; 24 heads, n = 16384, m = 512 325 -> 309; 12 causal heads,
 // n = 32768 849 -> 830; 32 heads, n = 32768, whose keys come from HBM, 1 %; d = 64: 8 heads, n = 16384 84.2 -> 79.9, m = 512 208 -> 196, 12
@@ -93,7 +94,7 @@ struct TauLds {
   static constexpr int NB = D == 64 ? 4 : 2;        // tile buffers of a group (two workgroups per CU)
   static constexpr int LIST_AT = 2 * NB * TILE;
   static constexpr int BYTES = LIST_AT + 4 * NT * 4;  // (a ring of four chunks)
-  static_assert(DPW >= 1 && NB <= RW);
+  static_assert(DPW >= 1 && (NB == 2 || NB == 4) && NB <= RW && NT == 4 * 2 * kA2KT);
   __device__ static int swz(int row) { return D == 128 ? row & 15 : (row >> 1) & 7; }
 };
 
@@ -127,8 +128,8 @@ __global__ __launch_bounds__(TauLds<D>::NT, 4) void alg2_tau_mfma_kernel(Alg2Arg
   const int trips = (kt_hi - kt_lo + 1) / 2;
   // chunk c of the list: the rows at positions 64 kt_lo + NT c ... (past the end: the last position, masked)
   const int32_t* keys = a.perm_k + hb;
-  auto chunk_row = [&](int c) { return keys[min(kt_lo * kA2KT + c * L::NT + (int)threadIdx.x, g.n - 1)]; };
-  const int row0 = chunk_row(0), row1 = chunk_row(1);
+  auto chunk_at = [&](int c) { return min(kt_lo * kA2KT + c * L::NT + (int)threadIdx.x, g.n - 1); };
+  const int row0 = keys[chunk_at(0)], row1 = keys[chunk_at(1)];
 
   const int r_in_tile = wave * 32 + lq;
   const int r_use = r_in_tile < rows_valid ? r_in_tile : 0;
@@ -155,6 +156,13 @@ __global__ __launch_bounds__(TauLds<D>::NT, 4) void alg2_tau_mfma_kernel(Alg2Arg
       const uint32_t to = at + 1024 * RW * ii;
       asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"{m0}"(to), "v"(voff), "s"(krsrc) : "memory");
     }
+  };
+  const __amdgpu_buffer_rsrc_t lrsrc = __builtin_amdgcn_make_buffer_rsrc((void*)keys, 0, g.n * 4, 0x00020000);
+  const uint32_t list0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) int32_t*)list + 256 * (grp * RW + wave);
+  auto request_chunk = [&](int c) {
+    const int voff = chunk_at(c) * 4;
+    const uint32_t to = list0 + (c & 3) * (L::NT * 4);
+    asm volatile("s_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds" ::"{m0}"(to), "v"(voff), "s"(lrsrc) : "memory");
   };
   list[threadIdx.x] = row0;
   list[L::NT + threadIdx.x] = row1;
@@ -221,19 +229,19 @@ __global__ __launch_bounds__(TauLds<D>::NT, 4) void alg2_tau_mfma_kernel(Alg2Arg
     }
     sum += out ? 0.f : s;
   };
-  int next_row = 0;
   const int mine = (kt_hi - kt_lo + 1 - grp) / 2;  // the group's tiles
   for (int it = 0; it < trips; ++it) {
     // the trip's tile has landed, for the whole workgroup, and the one before it is read no more
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(L::DPW * (L::NB - 2)) : "memory");
+    // (the list's chunk of a trip that RW divides was requested ahead of its tile: one request more lies behind the tiles of the next two)
+    if (L::NB == 4 && (unsigned)(it % RW - 1) < 2u) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(L::DPW * (L::NB - 2) + 1) : "memory");
+    else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(L::DPW * (L::NB - 2)) : "memory");
     __syncthreads();
+    if (it % RW == 0) request_chunk(it / RW + 2);
     request_tile(it + L::NB - 1);
-    if (it % RW == 0) next_row = chunk_row(it / RW + 2);
     const int kt = kt_lo + grp + 2 * it;
     if (grp == 1 && it > 0) add_tile(kt - 2);
     if (it < mine) scores(it);
     if (grp == 0) add_tile(kt);
-    if (it % RW == RW - 1) list[((it / RW + 2) & 3) * L::NT + threadIdx.x] = next_row;
   }
   if (grp == 1 && mine == trips && trips > 0) add_tile(kt_lo + 1 + 2 * (trips - 1));
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");

@@ -82,6 +82,8 @@ __host__ __device__ inline size_t a2_lds_bytes(const Geometry& g) {
 // heads, n = 16384 173 -> 166, 8 heads 115 -> 106, 4 heads, n = 4096 46.5 -> 45.8; 24 heads, n = 16384, m = 512 325 -> 309; 12 causal heads,
 // n = 32768 849 -> 830; 32 heads, n = 32768, whose keys come from HBM, 1 %; d = 64: 8 heads, n = 16384 84.2 -> 79.9, m = 512 208 -> 196, 12
 // causal heads, n = 32768 526 -> 512.
+// Clustered inputs (64 clusters, scores to 250), whose references move often: 16 heads, n = 16384, d = 128 170.3 -> 163.6, 8 heads 114.5 -> 108.5, 12 causal
+// heads, n = 32768 845 -> 822; d = 64: 8 heads, n = 16384 84.8 -> 81.8, 12 heads, n = 4096 47.6 -> 47.5 (weights formed twice where one moves: 49.0).
 // Eight waves to a tile, whose groups of 1024 threads read every key once and four tiles ahead: 1 to 14 % slower than this.
 template <int D>
 struct TauLds {
@@ -214,18 +216,31 @@ __global__ __launch_bounds__(TauLds<D>::NT, 4) void alg2_tau_mfma_kernel(Alg2Arg
       return (s4[0] + s4[1]) + (s4[2] + s4[3]);
     };
     // The reference moves when a weight exceeds 2^8: a sum below that has none, and the maxima, a seventh of a tile's vector
-    // instructions, need not be formed.
-    float s = weigh();
-    if (__any(!(out || s < 256.f) || m_run == -INFINITY)) {
+    // instructions, need not be formed.  Where it moves, a sum of weights in range is taken to the new reference as a whole, and the
+    // weights are formed again only where they left it.
+    auto move = [&]() {  // returns the factor of sums against the reference before
       float mx = fmaxf(c[0][0], c[1][0]);
 #pragma unroll
       for (int i = 1; i < 16; ++i) mx = __builtin_fmaxf(__builtin_fmaxf(mx, c[0][i]), c[1][i]);
       mx = fmaxf(mx, __shfl_xor(mx, 32)) * kLog2e;
       if (out) mx = -INFINITY;
       const float m_new = fmaxf(m_run, mx);
-      sum *= __builtin_amdgcn_exp2f(m_run - ((m_new == -INFINITY) ? 0.f : m_new));
+      const float factor = __builtin_amdgcn_exp2f(m_run - ((m_new == -INFINITY) ? 0.f : m_new));
+      sum *= factor;
       m_run = m_new;
+      return factor;
+    };
+    float s;
+    if (__any(m_run == -INFINITY)) {
+      move();
       s = weigh();
+    } else {
+      s = weigh();
+      if (__any(!(out || s < 256.f))) {
+        const float factor = move();
+        if (__any(!(out || s < 0x1p100f))) s = weigh();
+        else s *= factor;
+      }
     }
     sum += out ? 0.f : s;
   };

@@ -192,6 +192,11 @@ int hyperattn_forward_stamped(const void* Q, const void* K, const void* V, void*
  * *shared_workgroups the workgroups of the larger launch that passes of hyperattn_backward share, 0 if they do not. */
 int ha_call_routes(const ha_shape* shape, const ha_params* params, int32_t* sorts_in_attention, int64_t* shared_workgroups);
 
+/* Host only.  fp32 tensors: by how many of a workgroup's waves the key tiles of one group of rows are taken in turn (tests): *forward in the
+ * node launches of hyperattn_forward and, unmasked, of hyperattn_forward_alg2; *backward in the node passes of hyperattn_backward, 0 where they
+ * share launches.  Both 0 without nodes and for bf16 tensors. */
+int ha_fp32_ways(const ha_shape* shape, const ha_params* params, int32_t* forward, int32_t* backward);
+
 /* Plain exact attention D^-1 A V (Section 1.1), or D_C^-1 (M^C . A) V with
  * M^C_ij = 1{i >= j} (Section 3.1) when causal != 0; the denominator of the
  * speed-up ratio.  Any n >= 1; d in {64,128}.  Needs no workspace. */

@@ -69,6 +69,7 @@ _SIGNATURES = {
                                                         c_void_p, POINTER(c_float)]),
     "ha_forward_workgroups": (c_int, [POINTER(HaShape), POINTER(HaParams), POINTER(c_int64), POINTER(c_int64)]),
     "ha_call_routes": (c_int, [POINTER(HaShape), POINTER(HaParams), POINTER(c_int32), POINTER(c_int64)]),
+    "ha_fp32_ways": (c_int, [POINTER(HaShape), POINTER(HaParams), POINTER(c_int32), POINTER(c_int32)]),
     "hyperattn_forward_stamped": (c_int, [c_void_p] * 5 + [POINTER(HaShape), POINTER(HaParams), c_void_p, c_size_t,
                                                           c_void_p, c_void_p, c_size_t, c_void_p, c_size_t]),
     "exact_attn_forward": (c_int, [c_void_p] * 5 + [POINTER(HaShape), c_int, c_void_p]),
@@ -380,6 +381,13 @@ def ha_call_routes(shape, params):
     sorts, shared = c_int32(0), c_int64(0)
     _check(lib().ha_call_routes(ctypes.byref(shape), ctypes.byref(params), ctypes.byref(sorts), ctypes.byref(shared)), "ha_call_routes")
     return bool(sorts.value), int(shared.value)
+
+
+def ha_fp32_ways(shape, params):
+    """fp32 tensors: ways of the forward's node launches and of the backward's node passes, 0 where they share launches."""
+    forward, backward = c_int32(0), c_int32(0)
+    _check(lib().ha_fp32_ways(ctypes.byref(shape), ctypes.byref(params), ctypes.byref(forward), ctypes.byref(backward)), "ha_fp32_ways")
+    return int(forward.value), int(backward.value)
 
 
 def hyperattn_forward_stamped(Q, K, V, b, m, r, causal=False, n_min=4096, seed=0, workspace=None, out=None, lse=None,

@@ -747,6 +747,19 @@ int ha_call_routes(const ha_shape* shape, const ha_params* params, int32_t* sort
   return HA_OK;
 }
 
+int ha_fp32_ways(const ha_shape* shape, const ha_params* params, int32_t* forward, int32_t* backward) {
+  if (!forward || !backward) return HA_ERR_NULL;
+  Geometry g;
+  const int rc = make_geometry(shape, params, &g);
+  if (rc != HA_OK) return rc;
+  *forward = *backward = 0;
+  if (g.BH == 0 || g.n == 0 || g.levels == 0 || use_mfma(g)) return HA_OK;
+  *forward = attn_f32_node_ways(g);
+  const BwdArgs a = bwd_shape_args(g);
+  if (!backward_shares(a)) *backward = bwd_f32_node_ways(a);
+  return HA_OK;
+}
+
 int hyperattn_forward_stamped(const void* Q, const void* K, const void* V, void* out, float* lse,
                               const ha_shape* shape, const ha_params* params, void* workspace,
                               size_t workspace_bytes, void* stream, int64_t* node_stamps_dev,

@@ -668,15 +668,23 @@ int launch_attn_bwd_f32_level(const BwdArgs& block, const BwdArgs& dq, hipStream
 //   d = 128: exact, causal, 64 heads, n = 1024 (512) 595 / 564, 128 (1024) 1102 / 1184; unmasked, 32 heads (256) 401 / 472; nodes: 8 heads, n = 2048 (128)
 //     156 / 114; b = m = 256, 8 heads, n = 4096 (256) 267 / 321; b = m = 128: 10 heads (320) 246 / 272, 18 (576) 404 / 466
 //   eight ways, d = 64, causal: one head, n = 1024 56.9 (four: 62.5), 8 heads 61.5 (66.2), 16 80.1 (76.9); 4 heads, n = 2048 103 (120)
+template <int MODE>
+static int bwd_f32_ways(const BwdArgs& a) {
+  constexpr bool kExact = MODE == kBwdDqExact || MODE == kBwdDkvExact;
+  const int d = a.f.g.d;
+  if (d == 64 && kExact && f32_exact_eight(a.f)) return 8;
+  const int64_t enough = kExact && a.f.exact_causal ? (d == 64 ? 512 : 1024) : d == 128 ? 208 : kExact ? 256 : 384;
+  return rows_fit_128<MODE>(a) && bwd_grid<128>(a, MODE) >= enough ? 1 : 4;
+}
+
+int bwd_f32_node_ways(const BwdArgs& a) { return bwd_f32_ways<kBwdDqNode>(a); }
+
 template <int D, int MODE>
 static int launch_bwd_f32_mode(const BwdArgs& a, hipStream_t st) {
-  constexpr bool kExact = MODE == kBwdDqExact || MODE == kBwdDkvExact;
-  const int64_t grid128 = bwd_grid<128>(a, MODE);
-  if constexpr (D == 64 && kExact)
-    if (f32_exact_eight(a.f)) return launch_bwd_f32_one<D, MODE, 1, 8>(a, st);
-  const int64_t enough = kExact && a.f.exact_causal ? (D == 64 ? 512 : 1024) : D == 128 ? 208 : kExact ? 256 : 384;
-  if (rows_fit_128<MODE>(a) && grid128 >= enough) return launch_bwd_f32_one<D, MODE, 4, 1>(a, st);
-  return launch_bwd_f32_one<D, MODE, 1, 4>(a, st);
+  const int kw = bwd_f32_ways<MODE>(a);
+  if constexpr (D == 64 && (MODE == kBwdDqExact || MODE == kBwdDkvExact))
+    if (kw == 8) return launch_bwd_f32_one<D, MODE, 1, 8>(a, st);
+  return kw == 1 ? launch_bwd_f32_one<D, MODE, 4, 1>(a, st) : launch_bwd_f32_one<D, MODE, 1, 4>(a, st);
 }
 
 template <int D>

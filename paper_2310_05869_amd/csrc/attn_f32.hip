@@ -615,7 +615,7 @@ static int f32_ways(int d, int run, int64_t grid128, bool causal) {
   return d == 64 && f32_fits(run, 64) && grid128 >= (causal ? 512 : 256) ? 2 : 4;
 }
 
-static int f32_node_ways(const Geometry& g) { return f32_ways(g.d, g.b, node_grid<128>(g), false); }
+int attn_f32_node_ways(const Geometry& g) { return f32_ways(g.d, g.b, node_grid<128>(g), false); }
 
 // Workgroups of a node launch that a CU holds by their registers
 static constexpr int f32_places(int d, int kw) { return d == 64 ? (kw == 4 ? 3 : 2) : kw == 4 ? 2 : 1; }
@@ -628,7 +628,7 @@ static bool f32_tables_cost(const Geometry& g, int64_t wgs) {
 }
 
 // Whether a node launch sorts by itself (attn_mfma_sorts, for the kernel without it): up to 1024 workgroups of the form that is launched
-// (f32_node_ways), each of which counts its whole node, and up to 2^22 rows counted.  Sorting launch -> in the attention (MI355X, us; workgroups):
+// (attn_f32_node_ways), each of which counts its whole node, and up to 2^22 rows counted.  Sorting launch -> in the attention (MI355X, us; workgroups):
 //   d = 64, four ways: b = m = 64: one head, n = 1024 (32) 20.9 -> 17.7; b = m = 256, 6 heads, n = 4096 (768) 48.3 -> 45.0, 3 heads, n = 8192 (768) 48.7 ->
 //     51.6; n = 4096, b = 32: 8 heads (1024) 36.1 -> 35.5, 12 (1536) 46.8 -> 46.9, 16 (2048) 54.6 -> 56.7
 //   two: b = m = 64: 16 heads, n = 2048 (512) 35.4 -> 31.2, n = 4096: 9 (576) 46.6 -> 45.3, 16 (1024) 56.7 -> 55.1, 17 (1088) 64.9 -> 67.1, 20 (1280) 67.4 ->
@@ -643,7 +643,7 @@ static bool f32_tables_cost(const Geometry& g, int64_t wgs) {
 // Not where the tables cost a CU one of its workgroups and the call needs it: b = 128, m = 2000, r = 8, n = 8192: d = 64, 2 heads (four ways, 512) 96.8 ->
 // 113.1, 8 (one, 512) 256.8 -> 320.3; d = 128, 2 heads (four, 512) 158.6 -> 182.6, but 8 (one, 512, of which a CU holds one in any case) 546.5 -> 542.3.
 bool attn_f32_sorts(const Geometry& g) {
-  const int rows = node_sort_rows(g), kw = f32_node_ways(g);
+  const int rows = node_sort_rows(g), kw = attn_f32_node_ways(g);
   const int64_t wgs = kw == 1 ? node_grid<128>(g) : kw == 2 ? node_grid<64>(g) : node_grid<32>(g);
   if (rows > kNodeSortMax || wgs > 1024 || wgs * rows > 4 << 20) return false;
   if (g.d == 128) return !(kw == 1 ? f32_tables_cost<128, 1>(g, wgs) : f32_tables_cost<128, 4>(g, wgs));
@@ -669,7 +669,7 @@ static int launch_f32_mode(const AttnArgs& a, hipStream_t st) {
   if constexpr (MODE == kModeExact)
     if (f32_exact_eight(a)) return launch_f32_one<D, MODE, 8>(a, st);
   const int run = a.exact_block < a.exact_rows_q ? a.exact_block : a.exact_rows_q;
-  const int kw = MODE != kModeExact ? f32_node_ways(a.g) : f32_ways(D, run, exact_grid<128>(a), a.exact_causal);
+  const int kw = MODE != kModeExact ? attn_f32_node_ways(a.g) : f32_ways(D, run, exact_grid<128>(a), a.exact_causal);
   if constexpr (MODE == kModeNode)
     if (a.codes_q) {
       if (kw == 1) return launch_f32_one<D, MODE, 1, false, true>(a, st);

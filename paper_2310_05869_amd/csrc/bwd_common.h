@@ -272,6 +272,7 @@ struct BwdShared {
   BwdPart part[3];
 };
 bool bwd_f32_shares(const BwdArgs& a);
+int bwd_f32_node_ways(const BwdArgs& a);  // ways of the node passes' workgroups in launches of their own (attn_bwd_f32.hip)
 int64_t bwd_f32_shared_workgroups(const BwdArgs& a);  // of the larger of those launches
 int launch_attn_bwd_f32_base(const BwdArgs& dkv, const BwdArgs& dq, const BwdArgs* samp, hipStream_t st);
 int launch_attn_bwd_f32_level(const BwdArgs& block, const BwdArgs& dq, hipStream_t st);

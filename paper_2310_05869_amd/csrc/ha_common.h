@@ -178,7 +178,8 @@ int64_t attn_mfma_grid(const AttnArgs& a, int mode);  // workgroups of the four-
 bool attn_mfma_sorts(const Geometry& g);               // whether the node launch sorts its nodes by itself
 int launch_attn_f32(const AttnArgs& a, int mode, hipStream_t st);
 bool f32_exact_eight(const AttnArgs& a);  // whether eight waves share 32 rows of an exact fp32 launch
-bool attn_f32_sorts(const Geometry& g);               // whether it sorts its nodes by itself
+bool attn_f32_sorts(const Geometry& g);               // whether the node launch sorts its nodes by itself
+int attn_f32_node_ways(const Geometry& g);            // ways of its workgroups (attn_f32.hip)
 int launch_gather_rows(const void* src, const int32_t* idx, void* dst, int groups, int n, int d, int dtype,
                        hipStream_t st);
 int launch_merge_unpermute(const float* o_b, const float* lse_b, const float* o_r, const float* lse_r,

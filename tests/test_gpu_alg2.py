@@ -186,18 +186,23 @@ def test_alg2_caps_in_the_node_kernel(ha, torch, dtype, d, n, b, m, r, cap_scale
 
 @pytest.mark.parametrize("vnorm", [False, True])
 @pytest.mark.parametrize("d,H,n,b,m,r,cap_scale,kappa", [
-    (64, 2, 300, 100, 130, 4, 6.0, 1.3),     # four waves per row; padded tail of a block, samples from its next tile on
+    (64, 2, 300, 100, 130, 4, 6.0, 1.3),     # four ways; padded tail of a block, samples from its next tile on
     (128, 2, 256, 256, 40, 5, 0.0, 0.0),     # one block: no sample is kept, every row of T sums nothing
-    (64, 2, 48, 16, 33, 3, 5.0, 1.2),        # waves without a tile of the block; seven of eight key ranges empty
+    (64, 2, 48, 16, 33, 3, 5.0, 1.2),        # ways without a tile of the block; seven of eight key ranges empty
     (128, 2, 2080, 65, 300, 6, 6.0, 1.4),    # ragged ranges, blocks across tiles
     (64, 2, 650, 65, 0, 4, 0.0, 0.0),        # no samples at all
-    (128, 40, 896, 64, 77, 5, 6.0, 1.3),     # two waves per row
-    (64, 80, 896, 128, 31, 5, 6.0, 1.3),     # one wave per row
-    (128, 80, 700, 100, 0, 5, 0.0, 0.0),     # one wave per row, no samples
-    (64, 80, 700, 100, 65, 5, 0.0, 1.4)])    # lower cap alone
+    (128, 40, 896, 64, 77, 5, 6.0, 1.3),     # four ways, blocks of two row tiles
+    (64, 80, 896, 128, 31, 5, 6.0, 1.3),     # one way
+    (128, 80, 700, 100, 0, 5, 0.0, 0.0),     # four, no samples
+    (64, 80, 700, 100, 65, 5, 0.0, 1.4),     # one; lower cap alone
+    (64, 24, 704, 64, 96, 5, 6.0, 1.3),      # two ways: 5 tiles of keys, the second way's turn at the samples without one
+    (64, 24, 704, 64, 40, 5, 6.0, 1.3),      # 4 tiles
+    (64, 24, 704, 64, 20, 5, 0.0, 1.4),      # 3: the second way comes to the samples behind its loop
+    (128, 35, 896, 128, 70, 5, 6.0, 1.3),    # one way
+    (128, 70, 700, 100, 31, 5, 0.0, 1.4)])   # one, blocks that its rows do not fill
 def test_alg2_fp32_caps_in_the_node_kernel(ha, torch, d, H, n, b, m, r, cap_scale, kappa, vnorm):
     """The fp32 forward kernel's cap and value modes and the sums of the rows of T at the edges of their tiles and for each number of
-    waves that share a row; two heads (all share the draws, but the first two Lemma 2's of such a call) against the oracle:
+    ways (test_fp32_forms_of_the_gpu_tests); two heads (all share the draws, but the first two Lemma 2's of such a call) against the oracle:
     criteria as above."""
     print(f"alg2 fp32 d={d} H={H} n={n} b={b} m={m} r={r} cap={cap_scale} kappa={kappa} vnorm={vnorm}", flush=True)
     Q, K, V = (x.astype(np.float32) for x in synth_inputs.make_qkv(dict(B=1, H=H, n=n, d=d, dtype="fp32", law="iid"), seed=n))
@@ -250,8 +255,10 @@ def test_alg2_more_heads_than_one_launch_holds(ha, torch):
     (64, 1, 2048, 64, 64, 7, 0),
     (128, 1, 2048, 128, 128, 7, 0),
     (64, 1, 4096, 256, 256, 7, 0),
-    (128, 40, 896, 64, 77, 5, 0),      # fp32: two waves per row
-    (64, 80, 896, 128, 31, 5, 0),      # fp32: one wave per row
+    (128, 40, 896, 64, 77, 5, 0),
+    (64, 80, 896, 128, 31, 5, 0),      # fp32: one way
+    (64, 24, 704, 64, 96, 5, 0),       # fp32: two
+    (128, 35, 896, 128, 70, 5, 0),     # fp32: one
     (64, 1, 2048, 64, 64, 7, 512),     # causal, two levels
     (128, 1, 2048, 64, 64, 7, 256),
     (64, 1, 1024, 2, 5, 5, 2)])        # nine levels, folded one by one

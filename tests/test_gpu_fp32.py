@@ -1,6 +1,6 @@
-"""fp32 tensors on the fp32 matrix cores: the forms of the kernels that the smaller parity cases do not
-reach (one, two or four waves per group of 32 queries, chosen by the number of groups and the length of the
-run of rows), at lengths around their tiles, against the fp64 oracle on single heads."""
+"""fp32 tensors: the forms of the kernels that the smaller parity cases do not reach (a workgroup's waves take the key tiles of
+one group of rows in one, two, four or eight ways, chosen by the number of groups and the length of the
+run of rows; test_fp32_forms_of_the_gpu_tests has which), at lengths around their tiles, against the fp64 oracle on single heads."""
 import pytest
 
 import synth_inputs
@@ -11,11 +11,12 @@ pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not have_gpu(), reason="needs 
 
 
 @pytest.mark.parametrize("H,n,d,b,m,causal,n_min", [
-    (16, 4096, 64, 128, 40, 0, 4096),     # one wave per group: 128-row tiles
+    (16, 4096, 64, 128, 40, 0, 4096),     # one way: 128-row tiles
     (16, 4096, 128, 128, 33, 0, 4096),
-    (8, 4096, 64, 64, 64, 1, 1024),       # two waves per group: 64-row tiles, blocks of 64
-    (6, 4032, 128, 63, 7, 0, 4096),       # two waves, one row of the tile idle
-    (3, 1056, 64, 33, 31, 0, 4096),       # four waves per group: 32-row tiles, one row in the second
+    (8, 4096, 64, 64, 64, 1, 1024),       # two ways: 64-row tiles, blocks of 64
+    (6, 4032, 128, 63, 7, 0, 4096),       # four, one row of the second 32-row tile idle
+    (6, 4032, 64, 63, 7, 0, 4096),        # two, one row idle
+    (3, 1056, 64, 33, 31, 0, 4096),       # four: 32-row tiles, one row in the second
     (1, 264, 128, 33, 0, 1, 132)])
 def test_forward_fp32_forms(H, n, d, b, m, causal, n_min):
     import paper_2310_05869_amd as ha
@@ -43,9 +44,10 @@ def test_exact_attention_fp32_forms(H, n, d, causal):
 
 
 @pytest.mark.parametrize("H,n,d,b,m,causal,n_min", [
-    (32, 4096, 64, 128, 100, 0, 4096),    # one wave per group in every pass, samples included
+    (32, 4096, 64, 128, 100, 0, 4096),    # one way in every pass, samples included
     (32, 4096, 128, 128, 128, 1, 2048),
-    (5, 2112, 64, 33, 65, 0, 4096),       # four waves per group, one row in the second 32-row tile
+    (30, 896, 128, 128, 64, 0, 4096),     # one way, delta formed and samples' sums added in the pass
+    (5, 2112, 64, 33, 65, 0, 4096),       # four ways, one row in the second 32-row tile
     (1, 264, 128, 33, 5, 1, 132)])
 def test_backward_fp32_forms(H, n, d, b, m, causal, n_min):
     """Criterion |got - ref| <= 2^-14 bound (fp32 sums of up to 2^10 terms; bound: the oracle on absolute values)."""
@@ -127,7 +129,7 @@ def test_backward_fp32_shared_launches(B, H, n, n_min, d, b, m):
             assert (err <= 2.0 ** -12 * lim + 2.0 ** -100).all(), (name, err.max())
 
 
-# eight waves per group of 32 rows: ragged last tiles, a wave without a tile, more workgroups than CUs (11 x 33)
+# eight ways: ragged last tiles, a way without a tile, more workgroups than CUs (11 x 33)
 @pytest.mark.parametrize("H,n,d,causal", [(1, 2079, 64, True), (1, 2100, 64, False), (1, 513, 128, True), (2, 700, 128, False),
                                           (11, 1025, 128, True)])
 def test_exact_fp32_eight_waves(H, n, d, causal):

@@ -224,6 +224,25 @@ def test_forward_sorts_in_the_attention_launch(ha, dtype, d, H, n, b, m, r, n_mi
     assert bool(ha.ha_call_routes(shape, ha.make_params(b, m, r, n_min > 0, n_min or 4096, 0))[0]) == sorts
 
 
+@pytest.mark.parametrize("d,H,n,b,m,n_min,forward,backward", [  # (n_min 0: unmasked)
+    # Algorithm 2's caps and value sampling
+    (64, 2, 300, 100, 130, 0, 4, 4), (64, 80, 896, 128, 31, 0, 1, 1), (64, 80, 700, 100, 65, 0, 1, 1), (64, 24, 704, 64, 96, 0, 2, 4),
+    (64, 24, 704, 64, 40, 0, 2, 4), (64, 24, 704, 64, 20, 0, 2, 4), (128, 40, 896, 64, 77, 0, 4, 4), (128, 80, 700, 100, 0, 0, 4, 1),
+    (128, 35, 896, 128, 70, 0, 1, 1), (128, 70, 700, 100, 31, 0, 1, 1),
+    # forward, forward and backward
+    (64, 16, 4096, 128, 40, 0, 1, 1), (128, 16, 4096, 128, 33, 0, 1, 1), (64, 8, 4096, 64, 64, 1024, 2, 0), (128, 6, 4032, 63, 7, 0, 4, 4),
+    (64, 6, 4032, 63, 7, 0, 2, 4), (64, 3, 1056, 33, 31, 0, 4, 4), (64, 32, 4096, 128, 100, 0, 1, 1), (128, 32, 4096, 128, 128, 2048, 1, 1),
+    (128, 30, 896, 128, 64, 0, 4, 1), (64, 5, 2112, 33, 65, 0, 4, 4),
+    # scores that overflow
+    (64, 16, 4096, 128, 128, 0, 1, 1), (64, 8, 4096, 256, 256, 0, 2, 4), (64, 2, 2048, 64, 64, 512, 4, 0), (128, 8, 4096, 256, 256, 0, 1, 1),
+    (128, 2, 2048, 64, 64, 512, 4, 0)])
+def test_fp32_forms_of_the_gpu_tests(ha, d, H, n, b, m, n_min, forward, backward):
+    """The forms of the fp32 node kernels that tests on the GPU were given their sizes for: where a limit of the dispatch moves, they move too."""
+    shape = ha.make_shape(1, H, n, d, ha.HA_FP32)
+    assert ha.ha_fp32_ways(shape, ha.make_params(b, m, 5, n_min > 0, n_min or 4096, 0)) == (forward, backward)
+    assert ha.ha_fp32_ways(ha.make_shape(1, H, n, d, ha.HA_BF16), ha.make_params(b, m, 5, n_min > 0, n_min or 4096, 0)) == (0, 0)
+
+
 def test_forward_workgroup_counts(ha):
     """Records of the stamped forward: one per 128-query tile of every node (levels x half the rows when causal)
     and of the base case; none for fp32 tensors, which run the kernel without matrix cores."""

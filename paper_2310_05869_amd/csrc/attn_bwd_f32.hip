@@ -461,12 +461,18 @@ __device__ __forceinline__ void bwd_f32_pass(const BwdArgs& a, const int wg, con
   };
   if constexpr (!kShared) __syncthreads();  // the R rows stand
   run(std::false_type{});
-  const SplitFinite<NW> finite{reinterpret_cast<int32_t*>(smem + L::finite_at(g, MODE))};
-  finite.post(wave, split_finite(acc1) && (kDq || split_finite(acc2)));
-  __syncthreads();  // the key list is read no more
-  if (!finite.all()) {
-    run(std::true_type{});
-    __syncthreads();
+  const bool sums_finite = split_finite(acc1) && (kDq || split_finite(acc2));
+  if constexpr (kShared) {
+    const SplitFinite<NW> finite{reinterpret_cast<int32_t*>(smem + L::finite_at(g, MODE))};
+    finite.post(wave, sums_finite);
+    __syncthreads();  // the key list is read no more
+    if (__builtin_expect(!finite.all(), 0)) {
+      run(std::true_type{});
+      __syncthreads();
+    }
+  } else {
+    if (__builtin_expect(!__all(sums_finite), 0)) run(std::true_type{});
+    __syncthreads();  // the key list is read no more
   }
 
   // ---- results: the waves' rows through LDS, the KW parts of a row added in wave order.  Node passes write

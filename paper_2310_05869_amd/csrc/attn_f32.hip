@@ -477,12 +477,17 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 128 && KW < 4 ? 1 : D == 6
   };
   if constexpr (!kShared) __syncthreads();  // the queries stand
   run(std::false_type{});
-  const SplitFinite<NW> finite{reinterpret_cast<int32_t*>(smem + f32_finite_at<D, KW>(a.g.b, a.g.m, MODE))};
-  finite.post(wave, split_finite(o));
-  __syncthreads();  // the key list is read no more
-  if (!finite.all()) {
-    run(std::true_type{});
-    __syncthreads();
+  if constexpr (kShared || kCap) {
+    const SplitFinite<NW> finite{reinterpret_cast<int32_t*>(smem + f32_finite_at<D, KW>(a.g.b, a.g.m, MODE))};
+    finite.post(wave, split_finite(o));
+    __syncthreads();  // the key list is read no more
+    if (__builtin_expect(!finite.all(), 0)) {
+      run(std::true_type{});
+      __syncthreads();
+    }
+  } else {
+    if (__builtin_expect(!__all(split_finite(o)), 0)) run(std::true_type{});
+    __syncthreads();  // the key list is read no more
   }
 
   // ---- results: every wave's rows through LDS, where the KW parts of a row are merged and rows

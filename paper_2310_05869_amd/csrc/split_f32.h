@@ -104,8 +104,8 @@ __device__ inline void split_sum(split_f32x16& c, const split_f32x16& small) {
 // the result's error (exact attention, n = 4013, one way: out 1.1e-6 -> 2.9e-7).  The sum is added while the next accumulator's
 // products run: behind its own the wave waits for the last of them.  kSumSmall, three roundings: for the dK / dV passes of one way at d = 64, which
 // have no registers for it (backward, exact, 32 heads, n = 1024 244 -> 226 us, 16 heads, n = 4096 1402 -> 1380).
-// BOUND: the small products are bounded before they are added.  A workgroup forms its sums without that first; only where they hold an infinity or
-// NaN, which a product of parts may have left there, it forms them again with it (SplitFinite).  (Bounded always, exact passes of one way took
+// BOUND: the small products are bounded before they are added.  A workgroup, or a wave whose tiles are its own, forms its sums without that first; only where they
+// hold an infinity or NaN, which a product of parts may have left there, it forms them again with it (split_finite).  (Bounded always, exact passes of one way took
 // 8 % longer forward and 15 % backward at d = 128, where a SIMD has one wave; a branch at each tile left the passes 100 to 300 bytes of spills.)
 enum SplitSum { kSumEach, kSumSmall, kSumTile };
 template <int N, SplitSum SUM, bool BOUND, class A>
@@ -160,15 +160,18 @@ __device__ inline void split_tile_products(A&& a, const Split8 (&b)[2], split_f3
 // Whether a lane's sums are finite
 template <int N>
 __device__ inline bool split_finite(const split_f32x16 (&acc)[N]) {
-  float z[4] = {0.f, 0.f, 0.f, 0.f};
+  float z[2] = {0.f, 0.f};
 #pragma unroll
   for (int k = 0; k < N; ++k)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) z[i % 4] = __builtin_fmaf(acc[k][i], 0.f, z[i % 4]);
-  return (z[0] + z[1]) + (z[2] + z[3]) == 0.f;
+    for (int i = 0; i < 16; i += 4) {  // (maxima that a NaN passes through)
+      z[0] = __builtin_elementwise_maximum(__builtin_elementwise_maximum(z[0], __builtin_fabsf(acc[k][i])), __builtin_fabsf(acc[k][i + 1]));
+      z[1] = __builtin_elementwise_maximum(__builtin_elementwise_maximum(z[1], __builtin_fabsf(acc[k][i + 2])), __builtin_fabsf(acc[k][i + 3]));
+    }
+  return __builtin_elementwise_maximum(z[0], z[1]) <= 3.40282347e38f;
 }
 
-// The same of a workgroup of NW waves: each wave posts its lanes' ahead of a barrier, all read it behind that.
+// The same of a workgroup of NW waves, where their loops have barriers: each wave posts its lanes' ahead of a barrier, all read it behind that.
 template <int NW>
 struct SplitFinite {
   static constexpr int BYTES = NW * 4;

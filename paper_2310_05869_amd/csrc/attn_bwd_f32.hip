@@ -458,6 +458,7 @@ __device__ __forceinline__ void bwd_f32_pass(const BwdArgs& a, const int wg, con
         }
       }
     }
+    split_settle();
   };
   if constexpr (!kShared) __syncthreads();  // the R rows stand
   run(std::false_type{});

@@ -474,6 +474,7 @@ __global__ __launch_bounds__(64 * f32_waves(KW), D == 128 && KW < 4 ? 1 : D == 6
     if constexpr (kCap) {
       if (!sampled) to_samples();
     }
+    split_settle();
   };
   if constexpr (!kShared) __syncthreads();  // the queries stand
   run(std::false_type{});

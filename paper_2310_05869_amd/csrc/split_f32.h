@@ -157,6 +157,13 @@ __device__ inline void split_tile_products(A&& a, const Split8 (&b)[2], split_f3
   }
 }
 
+// Behind a loop of products, ahead of what reads its sums: the wait states of the last one whichever way the loop was left (split_sum).
+__device__ inline void split_settle() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_nop 15" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
 // Whether a lane's sums are finite
 template <int N>
 __device__ inline bool split_finite(const split_f32x16 (&acc)[N]) {

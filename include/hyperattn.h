@@ -36,6 +36,11 @@
  *   - Same inputs, parameters and seed give bit-identical outputs (no floating
  *     point atomics anywhere).
  *   - Pointers named *_host are host memory, everything else is device memory.
+ *   - fp32 tensors: attention's products of two fp32 numbers are formed from three bf16 parts of each and summed in fp32.  A product,
+ *     rounded, is within 2^-23.2 of its value (2^-25.2 r.m.s., as one rounding to fp32 is).  Infinities, NaN and products past
+ *     the largest number have the results that they have in fp32.  Parts below 2^-126 count as zeros: numbers of Q, K, V and d_out are taken
+ *     with an absolute error of up to 2^-125, weights and what the backward forms of them with 2^-126, so that numbers keep their
+ *     24 bits from 2^-101 upwards and those below 2^-125 count as 0 (an infinity times such a number is NaN).
  */
 #ifndef HYPERATTN_H
 #define HYPERATTN_H
@@ -339,7 +344,7 @@ size_t exact_attn_backward_workspace_bytes(const ha_shape* shape);
  * Algorithm 2 as printed and Lemma 2 / Algorithm 3, as options (the Section 4
  * form above leaves them out); both dtypes (bf16 tensors on the matrix cores,
  * weights rounded to bf16 as operands like in the forward; fp32 tensors with
- * fp32 products and sums).  Causal problems run them at every off-diagonal node of
+ * products and sums to fp32, as above).  Causal problems run them at every off-diagonal node of
  * Algorithm 4 ("the unmasked algorithm on Q_2, K_1"): below, n is then the
  * node's size s, every node has its own subset T, index set and value rows
  * (counters offset by the node's heap index 2^level - 1 + node), the diagonal

@@ -22,13 +22,14 @@
 // 457, 1012 -> 951, one head, n = 1024 60.0 -> 56.0, 119 -> 112; 8 heads, n = 4096, b = m = 256 152 -> 142.
 //
 // What bounds it: in large launches the matrix pipe at the clock that the chip's power leaves it (32 heads, n = 8192, d = 64: the seven products
-// of a pair at 1110 TFLOP/s of bf16 products); in small ones (4 heads, n = 4096 in causal blocks of 1024, base case with the sampled keys, 1152
-// workgroups) vector issue, half of the cycles, the splits being some 55 % of it, and workgroups of unequal length (matrix pipe 25 %; 1.4 waves
-// per SIMD of two).  At d = 64 the dK / dV passes spill 176 to 196 bytes per lane with one way, up to 56 with more.
+// of a pair at 1120 TFLOP/s of bf16 products); in small ones (4 heads, n = 4096 in causal blocks of 1024, base case with the sampled keys, 1152
+// workgroups) vector issue, half of the cycles, the splits being about half of it, and workgroups of unequal length (matrix pipe 32 %; 1.4 waves
+// per SIMD of two).  The dK / dV passes of one way spill 176 to 204 bytes per lane at d = 64, 100 to 180 at d = 128, mostly outside the first
+// run's loop; with more ways up to 28.
 // Measured (MI355X, us; fp32 matrix instructions, T rows always from the caches -> this form), backward of exact attention: 32 heads,
-// n = 8192, d = 64 15000 -> 10430, 16 heads, d = 128 16210 -> 10540; causal, 16 heads, n = 1024 95.6 -> 81.1, d = 128 205 -> 169; 8 heads, n = 4096 547 -> 457,
-// 1120 -> 951; one head, n = 1024 77.3 -> 56.0, 136 -> 112; of HyperAttention: one head, n = 1024, b = m = 64 45.6 -> 38.0, 8 heads, n = 4096, b = m = 256
-// 190 -> 142, d = 128 393 -> 259; causal, 4 heads, n = 4096 in blocks of 1024, b = m = 64 150 -> 108, 279 -> 235.
+// n = 8192, d = 64 14850 -> 10340, 16 heads, d = 128 16010 -> 10650; causal, 16 heads, n = 1024 91.1 -> 71.2, d = 128 204 -> 166; 8 heads, n = 4096 550 -> 419,
+// 1120 -> 913; one head, n = 1024 77.4 -> 53.5, 138 -> 109; of HyperAttention: one head, n = 1024, b = m = 64 45.8 -> 36.9, 8 heads, n = 4096, b = m = 256
+// 190 -> 138, d = 128 391 -> 258; causal, 4 heads, n = 4096 in blocks of 1024, b = m = 64 150 -> 106, 278 -> 235.
 #include <type_traits>
 
 #include "attn_common.h"

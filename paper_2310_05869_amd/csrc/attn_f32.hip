@@ -1,9 +1,9 @@
 // fp32 attention: the arithmetic path for HA_FP32 tensors, with the same node / cap / exact modes and the same outputs as the
 // bf16 kernel (attn_mfma.hip).  Its products run on the bf16 matrix cores, every operand split in three (split_f32.h).
 //
-// What bounds it: in large launches the matrix pipe at the clock that the chip's power leaves it (32 heads, n = 8192, d = 64: 179 TFLOP/s, 1070
+// What bounds it: in large launches the matrix pipe at the clock that the chip's power leaves it (32 heads, n = 8192, d = 64: 178 TFLOP/s, 1070
 // of bf16 products), in small ones the vector work of the splits and the chain of one wave's tiles (4 heads, n = 4096 in causal blocks of
-// 1024, 512 workgroups: matrix pipe 15 %, vector issue 41 % of the cycles).
+// 1024, 512 workgroups: matrix pipe 21 %, vector issue 59 % of the cycles).
 //
 // A wave owns 32 query rows and computes S^T = K Q^T, so that a lane holds 16 keys of
 // ONE query (as in the bf16 kernel) and accumulator registers, exponentiated and split, are
@@ -18,9 +18,9 @@
 // in the loop, and the queries lie split in LDS.
 //
 // Measured (MI355X, us; fp32 matrix instructions, K and V always from the caches -> this form): exact attention, 32 heads, n = 8192:
-// d = 64 4270 -> 3070; 16 heads, d = 128 4240 -> 3550; causal, 16 heads, n = 1024 d = 64 33.1 -> 26.4, d = 128 58.6 -> 44.8; 8 heads, n = 4096
-// 164 -> 136, 346 -> 255; one head, n = 1024 23.8 -> 18.3, 43.1 -> 32.7; whole calls: one head, n = 1024, d = 64, b = m = 64 17.8 -> 17.0, 8 heads, n = 4096,
-// b = m = 256 64.4 -> 54.6, d = 128 112 -> 92; 16 causal heads, n = 4096 in blocks of 1024, b = m = 128 192 -> 148, 352 -> 298.
+// d = 64 4220 -> 3090; 16 heads, d = 128 4210 -> 3490; causal, 16 heads, n = 1024 d = 64 30.7 -> 23.8, d = 128 54.1 -> 41.7; 8 heads, n = 4096
+// 166 -> 135, 349 -> 251; one head, n = 1024 23.7 -> 17.8, 43.2 -> 30.5; whole calls: one head, n = 1024, d = 64, b = m = 64 17.5 -> 16.6, 8 heads, n = 4096,
+// b = m = 256 67.6 -> 55.8, d = 128 115 -> 94; 16 causal heads, n = 4096 in blocks of 1024, b = m = 128 192 -> 149, 352 -> 294.
 // Tried: the next step's split in slices between the products, by the compiler's issue-order hints (+-1 %: the other waves fill the gaps);
 // KW = 2 at d = 128 (one wave per SIMD: 16 heads, n = 2048, causal 138 -> 187).
 #include <type_traits>
@@ -608,11 +608,11 @@ static int launch_f32_one(const AttnArgs& args, hipStream_t st) {
 // 128 rows pay only where a CU gets several; at d = 128 a CU holds one of them, and a last round that is not nearly full loses what they gain.
 // One way / two / four (MI355X, us; workgroups of 128 rows in brackets):
 //   d = 64, causal: 32 heads, n = 1024 (256) 66.4 / 44.5 / 41.5, 64 (512) 74.7 / 72.6 / 75.1, 128 (1024) 120 / 139 / 154; 16 heads, n = 4096 (512) 270 / 241 /
-//     254; unmasked: 32 heads, n = 1024 (256) 72 / 65 / 69; 16 heads, n = 4000 (500) 415 / 442 / 467; nodes: b = m = 256, 8 heads, n = 4096 (256) 54.2 / 51.6 /
-//     56.1, 16 (512) 86.8 / 98.9 / 102.2; b = m = 128, 12 heads, n = 4096 (384) 52.1 / 54.9 / 59.0; b = m = 64, 16 heads, n = 4096 58.3 / 54.2 / 57.2
+//     254; unmasked: 32 heads, n = 1024 (256) 72 / 65 / 69; 16 heads, n = 4000 (500) 415 / 442 / 467; nodes: b = m = 256, 8 heads, n = 4096 (256) 54.6 / 53.1 /
+//     56.7, 16 (512) 83.5 / 95.6 / 99.4; b = m = 128, 12 heads, n = 4096 (384) 53.0 / 56.8 / 57.9; b = m = 64, 16 heads, n = 4096 61.4 / 54.7 / 58.1
 //   d = 128 (one / four): causal, 64 heads, n = 1024 (512) 158 / 146, 128 (1024) 278 / 296; unmasked, 32 heads (256) 119 / 130; nodes: b = m = 256, 8
-//     heads, n = 4096 (256) 87.4 / 97.9; b = m = 128, 12 heads, n = 4096 (384) 106 / 100, 32 heads, n = 2048 (512) 116 / 126, 44 (704) 163 / 167, 52 (832)
-//     205 / 194; 24 heads, n = 2000, b = 100 (480) 92 / 113
+//     heads, n = 4096 (256) 91.1 / 98.9; b = m = 128, 12 heads, n = 4096 (384) 109.6 / 98.4, 32 heads, n = 2048 (512) 118.9 / 124.6, 44 (704) 167.5 / 162.0,
+//     52 (832) 210 / 185; 24 heads, n = 2000, b = 100 (480) 94.5 / 109.0
 static bool f32_fits(int run, int rows) { return 3 * (int64_t)((run + rows - 1) / rows * rows) <= 4 * (int64_t)run; }
 static int f32_ways(int d, int run, int64_t grid128, bool causal) {
   const int64_t rounds = (grid128 + 255) / 256;

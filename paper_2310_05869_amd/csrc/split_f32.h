@@ -11,8 +11,9 @@
 //   4.7e-7 -> 3.5e-7; 64 clusters, scores to 250: 2.0e-5 -> 8.6e-6, 2.2e-5 -> 1.3e-5, 1.9e-5 -> 9.3e-6, 2.1e-5 -> 9.9e-6; d = 128 likewise
 //   scores to 250 and gradients that one column carries (geometric means of eight shapes): dK 2.6e-7 -> 2.3e-7, dV 2.5e-7 -> 1.9e-7, largest of a log row
 //   sum 1.5e-5 both; two of d columns: dQ 9.4e-6 -> 9.1e-6, dK 1.5e-5 -> 1.4e-5, dV 3.1e-6 -> 3.4e-6, log row sum 1.2e-4 -> 8.5e-5
-// The matrix cores take parts below 2^-126 as zeros: a number keeps its 24 bits down to 2^-102 in any case, 16 at 2^-117, none below 2^-125.  Errors of dQ at
-// values of 2^-100 are those of 1 (5.1e-7 against 5.0e-7); fp32 instructions hold theirs down to 2^-116.  2^-100 is what the criterion for
+// The matrix cores take parts below 2^-126 as zeros: numbers of the tensors (split at half their value) are taken with an absolute error of up
+// to 2^-125, computed ones with 2^-126, so that 24 bits are kept from 2^-101 upwards.  Errors of dQ at values of 2^-100 are
+// those of 1 (5.1e-7 against 5.0e-7); fp32 instructions hold theirs down to 2^-116.  2^-100 is what the criterion for
 // gradients takes for zero.
 //
 // What it costs is vector work: 13 instructions per two numbers, 208 for a wave's operand of 32 rows of 64 floats, beside 24 products.  So

@@ -24,8 +24,8 @@ are allowed that much absolute error.
 A dropped term, a wrong mask, sign or weight moves an element by the size of
 the term, hundreds of times the tolerance.
 
-fp32 tensors take the same passes on the fp32 matrix cores (fp32 products and sums).  Nothing is rounded to bf16 there; what
-remains is the rounding of fp32 sums: a score or dP is a dot product of d <= 128 terms and a
+fp32 tensors take the same passes with operands split in three bf16 parts, whose products are within 2^-23.2 of those of the
+numbers; what remains is the rounding of fp32 sums: a score or dP is a dot product of d <= 128 terms and a
 gradient element a sum over up to a few thousand pairs, each with relative error at most
 (number of terms) * 2^-24 of the sum of magnitudes in the worst case.  The criterion is
     |got - ref| <= 2^-14 * bound
@@ -165,7 +165,7 @@ def test_backward_causal(ha, torch, d, n, n_min, b, m):
                                                   (64, 192, 96, 7, 0, 4096),        # block not a multiple of 64, odd m
                                                   (64, 128, 8, 20, 1, 8)])          # more samples than keys in the deep nodes
 def test_backward_fp32(ha, torch, d, n, b, m, causal, n_min):
-    """fp32 tensors: the fp32 matrix-core kernels, same passes and buffers as the bf16 path."""
+    """fp32 tensors: operands split in three, same passes and buffers as the bf16 path."""
     print(f"backward fp32 d={d} n={n} b={b} m={m} causal={causal} n_min={n_min}", flush=True)
     cfg = dict(B=1, H=2, n=n, d=d, dtype="fp32", law="iid", b=b, m=m, r=7, causal=causal, n_min=n_min, seed=2)
     _run_case(ha, torch, cfg)

@@ -124,6 +124,20 @@ def test_values_of_2_to_the_minus_100(ha, torch, d, H, n):
     assert (dq[:, :1].double() - ref[2]).norm() <= 1e-6 * ref[2].norm()
 
 
+@pytest.mark.parametrize("exponent", [-101, -110, -118, -124])
+@pytest.mark.parametrize("d,H,n", [(64, 13, 2000), (64, 2, 700), (128, 8, 4013), (128, 2, 700)])
+def test_small_values(ha, torch, d, H, n, exponent):
+    """Each is taken with an absolute error of up to 2^-125, and the weights of a row add up to 1."""
+    print(f"split fp32 values of 2^{exponent} d={d} H={H} n={n}", flush=True)
+    q, k, v = _inputs(torch, H, n, d, d + n, 3)
+    v = v * 2.0 ** exponent
+    out, lse = ha.exact_attn_forward(q, k, v)
+    q1, k1, v1 = (x[:, :1].double() for x in (q, k, v))
+    s = torch.matmul(q1, k1.transpose(-1, -2).contiguous())
+    want = torch.matmul(torch.softmax(s, -1), v1)
+    assert ((out[:, :1].double() - want).abs() <= 2.0 ** -125 + 1e-5 * want.abs() + 1e-6 * v1.abs().max()).all()
+
+
 # Every form of the kernels: one way, two, four, eight (tests of infinities and of largest numbers).
 FORMS = [(64, 13, 4000, False), (64, 9, 3700, False), (64, 20, 1001, True), (64, 2, 700, False), (128, 8, 4096, False),
          (128, 9, 2501, True), (128, 2, 700, False)]

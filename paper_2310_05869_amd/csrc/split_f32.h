@@ -75,11 +75,11 @@ __device__ inline void split_small(const Split8& a, const Split8& b, split_f32x1
   small = split_mfma(a.hi, b.mid, small);
 }
 
-// Their sum where it is finite, else something finite.  Where an operand is infinite or a product overflows, hi and hi have the result that
-// fp32 has, and what the other products have, an infinity of either sign or NaN, must not be added to it.
+// Their sum, or something finite that takes no sum past the largest number.  Where an operand is infinite or a product overflows, hi and hi
+// have the result that fp32 has, and what the other products have, an infinity of either sign or NaN, must not be added to it.  (They are at
+// most 2^-8 of theirs: 2^126 is none of a sum that is finite.)
 __device__ inline float split_bound(float small) {
-  constexpr float kMax = 3.40282347e38f;
-  return __builtin_amdgcn_fmed3f(small, -kMax, kMax);
+  return __builtin_amdgcn_fmed3f(small, -0x1p126f, 0x1p126f);
 }
 
 // A score's: the small products in a sum of their own, so that its rounding is that of a few additions of 16 terms, and the same whichever

@@ -185,7 +185,7 @@ def test_value_at_the_end_of_the_range(ha, torch, d, H, n, causal, value):
     q, k, v, g = _inputs(torch, H, n, d, n + 2)
     x = torch.tensor([value], dtype=torch.int32).view(torch.float32).item() if value != 0x7f800001 else None
     for t, row in ((v, 5), (g, n - 1)):
-        t[..., 3] = 0.0
+        t[..., 3] = -1e34 if value == 0x7f800000 else 0.0  # (sums that are far from the largest number, whatever is added to them)
         if x is None:
             t.view(torch.int32)[:, :, row, 3] = value
         else:
